@@ -4,8 +4,13 @@ Every function has the name of the C entry point it calls (include/radar.h) and
 takes torch tensors that already live on the GPU; it passes their device
 pointers, a host descriptor and the current HIP stream.  Nothing is computed
 here and there is no fallback: if the library is missing, loading fails.
+
+A direct call (prepared=False) goes through the native marshaller
+(csrc/radar_native.cpp) when its arguments are what that expects; the ctypes
+path below it makes prepared calls and raises the errors.
 """
 import ctypes
+import importlib
 import os
 
 import torch
@@ -13,7 +18,9 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # RADAR_LIB_SANITIZE=1 selects the build whose host code runs under the sanitizers (CPU tests only)
 LIB_PATH = os.path.join(_HERE, "libradar_san.so" if os.environ.get("RADAR_LIB_SANITIZE", "0") == "1" else "libradar.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 _lib = None
+_native = None
 
 RADAR_OK = 0
 RADAR_ACCEPT_GREEDY = 0
@@ -150,8 +157,29 @@ def load():
     lib.radar_profile_begin.argtypes = [i32]
     lib.radar_profile_end.restype = i32
     lib.radar_profile_end.argtypes = [ctypes.POINTER(KernelTime), i32, ctypes.POINTER(i32)]
+    if not LIB_PATH.endswith("_san.so"):        # the sanitized build is for host-side checks, made through ctypes alone
+        _load_native()
     _lib = lib
     return lib
+
+
+def _load_native():
+    global _native
+    if not os.path.exists(NATIVE_PATH):
+        raise RuntimeError(f"{NATIVE_PATH} is missing: build it with __graft_entry__.build() "
+                           "(python -m paper_2512_14069_amd.build)")
+    module = importlib.import_module("._native", __package__)
+    module.bind(LIB_PATH)
+    _native = module
+
+
+def _direct(prepared):
+    """The native marshaller for a direct call, or None (prepared calls, sanitized build)."""
+    if prepared:
+        return None
+    if _lib is None:
+        load()
+    return _native
 
 
 def status_string(status):
@@ -251,6 +279,10 @@ def radar_tree_attention(q, k_cache, v_cache, parents, ctx_lens, n_nodes=None, o
                          desc=None, workspace=None, keys_per_split=0, softmax_scale=0.0, prepared=False):
     """q bf16 [B,T,Hq,D]; k_cache, v_cache bf16 [B,Hkv,S,D] (same strides, D contiguous);
     parents i32 [B,T]; ctx_lens i32 [B]; n_nodes i32 [B] or None.  Returns out bf16 [B,T,Hq,D]."""
+    if desc is None and workspace is not None and (native := _direct(prepared)):
+        done = native.tree_attention(q, k_cache, v_cache, parents, ctx_lens, n_nodes, out, lse_out, keys_per_split, softmax_scale, workspace)
+        if done is not None:
+            return done
     if q.stride(-1) != 1 or k_cache.stride(-1) != 1 or v_cache.stride() != k_cache.stride():
         raise ValueError("innermost axis must be contiguous and k/v caches must share strides")
     if desc is None:
@@ -312,9 +344,13 @@ def radar_draft_expand(logits, parent_scores, parent_pool_idx, k, pool, out=None
     """logits f32 [F,V]; parent_scores f32 [F]; parent_pool_idx i32 [F]; pool: DraftPool
     (appended to; pool.count advances by F*k).  Returns an ExpandOut."""
     F, V = logits.shape
-    desc = expand_desc(F, V, k, pool.count, pool.capacity)
     if out is None:
         out = ExpandOut(F, k, logits.device)
+    if workspace is not None and (native := _direct(prepared)) and native.draft_expand(
+            0, logits, parent_scores, parent_pool_idx, k, pool.count, pool.capacity, *_expand_outputs(out, pool), None, 0, workspace):
+        pool.count += F * k
+        return out
+    desc = expand_desc(F, V, k, pool.count, pool.capacity)
     if workspace is None:
         workspace = new_workspace(radar_draft_expand_workspace_bytes(desc), logits.device)
     wp, wn = _ws_args(workspace)
@@ -330,6 +366,18 @@ def radar_draft_expand(logits, parent_scores, parent_pool_idx, k, pool, out=None
     keep = (logits, parent_scores, parent_pool_idx, out, pool, desc, workspace)
     pool.count += F * k
     return _finish("radar_draft_expand", load().radar_draft_expand, args, keep, out, prepared)
+
+
+def _expand_outputs(out, pool):
+    return (out.cand_tokens, out.cand_scores, out.frontier_pool_idx, out.frontier_tokens, out.frontier_scores, out.frontier_conf,
+            pool.tokens, pool.scores, pool.parents)
+
+
+def _policy_tensors(params, policy_out, h, c, uniform):
+    """The prediction model's part of a native expansion call: (address of the parameters, its tensors)."""
+    if params is None:
+        return (0,)
+    return (ctypes.addressof(params[0]), h, c, uniform, policy_out.h, policy_out.c, policy_out.logits, policy_out.probs, policy_out.action)
 
 
 RADAR_NOALLOC_SCRATCH_BYTES = 1 << 20
@@ -365,11 +413,16 @@ def radar_draft_expand_policy(logits, parent_scores, parent_pool_idx, k, pool, p
     Returns (ExpandOut, PolicyOut)."""
     F, V = logits.shape
     pp, held = params
-    desc = expand_desc(F, V, k, pool.count, pool.capacity)
     if out is None:
         out = ExpandOut(F, k, logits.device)
     if policy_out is None:
         policy_out = PolicyOut(1, pp.H, logits.device)
+    if workspace is not None and (native := _direct(prepared)) and native.draft_expand(
+            0, logits, parent_scores, parent_pool_idx, k, pool.count, pool.capacity, *_expand_outputs(out, pool), None,
+            *_policy_tensors(params, policy_out, h, c, uniform), workspace):
+        pool.count += F * k
+        return out, policy_out
+    desc = expand_desc(F, V, k, pool.count, pool.capacity)
     if (h is None) != (c is None):
         raise ValueError("h and c must be given together")
     for n, t in (("h", h), ("c", c)):
@@ -409,6 +462,10 @@ class TreeOut:
         self.n_nodes = torch.empty(1 if B is None else int(B), dtype=torch.int32, device=device)
 
 
+def _tree_outputs(out):
+    return out.tokens, out.parents, out.scores, out.depth, out.pool_idx, out.n_nodes
+
+
 def radar_draft_rerank_workspace_bytes(pool_count, N):
     return int(load().radar_draft_rerank_workspace_bytes(int(pool_count), int(N)))
 
@@ -417,6 +474,9 @@ def radar_draft_rerank(pool, N, root_token, out=None, workspace=None, prepared=F
     """Keep the best N pool entries; returns a TreeOut (device tensors)."""
     if out is None:
         out = TreeOut(N, pool.tokens.device)
+    if (native := _direct(prepared)) and native.draft_rerank(0, pool.tokens, pool.scores, pool.parents, None, pool.count, pool.capacity, N,
+                                                             root_token, *_tree_outputs(out)):
+        return out
     wp, wn = _ws_args(workspace)
     args = (
         _ptr(pool.tokens, torch.int32), _ptr(pool.scores, torch.float32), _ptr(pool.parents, torch.int32),
@@ -446,16 +506,20 @@ def radar_draft_expand_cycle(logits, parent_scores, parent_pool_idx, k, pool, po
     params None: no decision after this call.  pool.count is not touched.
     Returns (ExpandOut, PolicyOut or None)."""
     F, V = logits.shape
-    desc = expand_desc(F, V, k, int(pool_count_max), pool.capacity)
     if out is None:
         out = ExpandOut(F, k, logits.device)
+    if params is not None and policy_out is None:
+        policy_out = PolicyOut(1, params[0].H, logits.device)
+    if workspace is not None and state is not None and (native := _direct(prepared)) and native.draft_expand(
+            0, logits, parent_scores, parent_pool_idx, k, pool_count_max, pool.capacity, *_expand_outputs(out, pool), state,
+            *_policy_tensors(params, policy_out, h, c, uniform), workspace):
+        return out, policy_out
+    desc = expand_desc(F, V, k, int(pool_count_max), pool.capacity)
     if workspace is None:
         workspace = new_workspace(radar_draft_expand_workspace_bytes(desc), logits.device)
     pp = held = io = None
     if params is not None:
         pp, held = params
-        if policy_out is None:
-            policy_out = PolicyOut(1, pp.H, logits.device)
         if (h is None) != (c is None):
             raise ValueError("h and c must be given together")
         io = PolicyIO()
@@ -495,16 +559,22 @@ def radar_draft_expand_batch(logits, parent_scores, parent_pool_idx, k, pool, st
         raise ValueError("pool: expected DraftPool(capacity, B=%d)" % B)
     if states is not None and pool_count_max is None:
         raise ValueError("a call with states needs pool_count_max")
-    desc = expand_desc(F, V, k, int(pool.count if states is None else pool_count_max), pool.capacity)
     if out is None:
         out = ExpandOut(F, k, logits.device, B=B)
+    if params is not None and policy_out is None:
+        policy_out = PolicyOut(B, params[0].H, logits.device)
+    if workspace is not None and (states is None or states.numel() == 4 * B) and (native := _direct(prepared)) and native.draft_expand(
+            B, logits, parent_scores, parent_pool_idx, k, pool.count if states is None else pool_count_max, pool.capacity,
+            *_expand_outputs(out, pool), states, *_policy_tensors(params, policy_out, h, c, uniform), workspace):
+        if states is None:
+            pool.count += F * k
+        return out, policy_out
+    desc = expand_desc(F, V, k, int(pool.count if states is None else pool_count_max), pool.capacity)
     if workspace is None:
         workspace = new_workspace(radar_draft_expand_batch_workspace_bytes(desc, B), logits.device)
     pp = held = io = None
     if params is not None:
         pp, held = params
-        if policy_out is None:
-            policy_out = PolicyOut(B, pp.H, logits.device)
         if (h is None) != (c is None):
             raise ValueError("h and c must be given together")
         for n, t, want in (("h", h, B * pp.H), ("c", c, B * pp.H), ("uniform", uniform, B)):
@@ -539,6 +609,9 @@ def radar_draft_rerank_cycle(pool, state, pool_count_max, N, root_token, out=Non
     """radar_draft_rerank over the candidates `state` counts (at most pool_count_max)."""
     if out is None:
         out = TreeOut(N, pool.tokens.device)
+    if state is not None and (native := _direct(prepared)) and native.draft_rerank(
+            0, pool.tokens, pool.scores, pool.parents, state, pool_count_max, pool.capacity, N, root_token, *_tree_outputs(out)):
+        return out
     wp, wn = _ws_args(workspace)
     args = (
         _ptr(pool.tokens, torch.int32), _ptr(pool.scores, torch.float32), _ptr(pool.parents, torch.int32),
@@ -562,6 +635,9 @@ def radar_draft_rerank_batch(pool, N, root_tokens, states=None, pool_count_max=N
     if out is None:
         out = TreeOut(N, pool.tokens.device, B=B)
     count = pool.count if states is None else (pool.capacity if pool_count_max is None else pool_count_max)
+    if (native := _direct(prepared)) and native.draft_rerank(B, pool.tokens, pool.scores, pool.parents, states, count, pool.capacity, N,
+                                                             root_tokens, *_tree_outputs(out)):
+        return out
     wp, wn = _ws_args(workspace)
     args = (
         _ptr(pool.tokens, torch.int32), _ptr(pool.scores, torch.float32), _ptr(pool.parents, torch.int32),
@@ -575,6 +651,9 @@ def radar_draft_rerank_batch(pool, N, root_tokens, states=None, pool_count_max=N
 
 
 # ------------------------------------------------------------ verification
+
+_NO_OUT = (None, None, None)
+
 
 def accept_desc(B, T, V, D_max, mode, temperature):
     d = AcceptDesc()
@@ -593,6 +672,10 @@ def radar_verify_accept(target_logits, draft_tokens, parents, n_nodes=None, unif
     B, T, V = target_logits.shape
     if D_max is None:
         D_max = T - 1
+    if workspace is not None and (native := _direct(prepared)):
+        done = native.verify_accept(target_logits, draft_tokens, parents, n_nodes, uniforms, mode, temperature, D_max, *(out or _NO_OUT), workspace)
+        if done is not None:
+            return out if done is True else done
     desc = accept_desc(B, T, V, D_max, mode, temperature)
     dev = target_logits.device
     if out is None:
@@ -639,6 +722,11 @@ def radar_verify_accept_q(target_logits, draft_logits, draft_tokens, parents, n_
         raise ValueError(f"uniforms: expected shape {(B, T + 1)}")
     if D_max is None:
         D_max = T - 1
+    if workspace is not None and (native := _direct(prepared)):
+        done = native.verify_accept_q(target_logits, draft_logits, q_rows, draft_tokens, parents, n_nodes, uniforms, temperature,
+                                      draft_temperature, D_max, walk_spin_limit, *(out or _NO_OUT), workspace)
+        if done is not None:
+            return out if done is True else done
     desc = accept_q_desc(B, T, Tq, V, D_max, temperature, draft_temperature, walk_spin_limit)
     dev = target_logits.device
     if out is None:
@@ -669,6 +757,10 @@ def radar_accept_length_distribution(target_logits, draft_tokens, parents, n_nod
     B, T, V = target_logits.shape
     if D_max is None:
         D_max = T - 1
+    if workspace is not None and (native := _direct(prepared)):
+        done = native.accept_length_distribution(target_logits, draft_tokens, parents, n_nodes, temperature, D_max, out, workspace)
+        if done is not None:
+            return done
     desc = accept_desc(B, T, V, D_max, RADAR_ACCEPT_SAMPLE, temperature)
     dev = target_logits.device
     if out is None:
@@ -731,6 +823,9 @@ def radar_policy_step(conf, params, h=None, c=None, uniforms=None, out=None, pre
         raise ValueError("h and c must be given together")
     if out is None:
         out = PolicyOut(B, pp.H, conf.device)
+    if (native := _direct(prepared)) and native.policy_step(conf, ctypes.addressof(pp), h, c, uniforms, out.h, out.c, out.logits, out.probs,
+                                                            out.action):
+        return out
     for n, t in (("h", h), ("c", c)):
         if t is not None and tuple(t.shape) != (B, pp.H):
             raise ValueError(f"{n}: expected shape {(B, pp.H)}, got {tuple(t.shape)}")

@@ -15,6 +15,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Wno-inline-asm"]
 
 
+NATIVE = os.path.join(HERE, "_native.so")
+CXX = os.environ.get("CXX", "g++")
+
+
 def _stale(target, deps):
     if not os.path.exists(target):
         return True
@@ -36,7 +40,7 @@ def sanitizer_runtime():
 
 
 def build_library(force=True, verbose=False, sanitize=False):
-    """Compile every kernel source and link paper_2512_14069_amd/libradar.so.  sanitize=True builds
+    """Compile every kernel source and link paper_2512_14069_amd/libradar.so, and the binding's native half.  sanitize=True builds
     libradar_san.so instead: the same sources with the HOST code (argument checks, planning, launch
     paths) under AddressSanitizer and UndefinedBehaviorSanitizer; used by the CPU tests only."""
     headers = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
@@ -44,7 +48,29 @@ def build_library(force=True, verbose=False, sanitize=False):
     if sanitize:
         return _build(os.path.join(HERE, "_build", "san"), SAN_LIB, [f for f in FLAGS if f != "-O3"] + ["-O1"] + SAN_FLAGS,
                       ["-fsanitize=address", "-fsanitize=undefined", "-shared-libsan"], headers, force, verbose)
+    build_native(force)
     return _build(os.path.join(HERE, "_build"), LIB, FLAGS, [], headers, force, verbose)
+
+
+def build_native(force=True):
+    """Compile the binding's argument marshaller (host code only) against the installed torch."""
+    import sysconfig
+
+    import torch
+    src, root = os.path.join(CSRC, "radar_native.cpp"), os.path.dirname(torch.__file__)
+    if not (force or _stale(NATIVE, [src, os.path.join(os.path.dirname(HERE), "include", "radar.h")])):
+        return NATIVE
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+    for inc in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                os.path.join(os.path.dirname(HIPCC), "..", "include"), sysconfig.get_paths()["include"]):
+        cmd += ["-isystem", inc]
+    lib = os.path.join(root, "lib")
+    cmd += [src, "-o", NATIVE, "-L" + lib, "-Wl,-rpath," + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-ldl"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{CXX} failed for radar_native.cpp:\n{r.stderr}")
+    return NATIVE
 
 
 def _build(objdir, lib, flags, link_flags, headers, force, verbose):

@@ -181,3 +181,27 @@ def test_verify_step_replays_from_a_graph(oracle):
                 for bb in range(a.B):
                     n = a.n_nodes[bb]
                     check_close(bf16_bits(o)[bb, :n], want[bb, :n], f"graph replay b={bb}")
+
+
+@pytest.mark.parametrize("B,T,V", [(1, 1, 17), (2, 9, 1000), (3, 64, 4099)])
+def test_direct_calls_match_prepared_calls(B, T, V):
+    """The native marshaller and the ctypes path make the same calls; arguments the first does not take reach the second's checks."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(B * 100 + T)
+    logits, uni = dev(synth.normal_logits(rng, (B, T, V), 2.0)), dev(rng.random((B, T + 1), dtype=np.float32))
+    par = dev(np.tile(synth.chain_tree(T), (B, 1)))
+    tok = dev(rng.integers(0, V, size=(B, T)).astype(np.int32))
+    ws = b.new_workspace(b.radar_verify_accept_workspace_bytes(b.accept_desc(B, T, V, T - 1, b.RADAR_ACCEPT_SAMPLE, 1.0)))
+    qws = b.new_workspace(b.radar_verify_accept_q_workspace_bytes(b.accept_q_desc(B, T, T, V, T - 1)))
+    for name, args, kw in (("radar_verify_accept", (logits, tok, par, None, uni), dict(mode=b.RADAR_ACCEPT_SAMPLE, workspace=ws)),
+                           ("radar_accept_length_distribution", (logits, tok, par), dict(workspace=ws)),
+                           ("radar_verify_accept_q", (logits, logits, tok, par, None, uni), dict(workspace=qws))):
+        f = getattr(b, name)
+        b.radar_workspace_init(kw["workspace"])
+        direct, prepared = f(*args, **kw), f(*args, prepared=True, **kw)()
+        for x, y in zip(direct if isinstance(direct, tuple) else (direct,), prepared if isinstance(prepared, tuple) else (prepared,)):
+            assert x.dtype == y.dtype and x.shape == y.shape and torch.equal(x, y), name
+        with pytest.raises(ValueError):
+            f(args[0].double(), *args[1:], **kw)
+        with pytest.raises(ValueError):
+            f(args[0].transpose(0, 1).contiguous().transpose(0, 1)[:, :, ::2], *args[1:], **kw)
