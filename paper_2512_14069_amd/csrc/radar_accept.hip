@@ -1,17 +1,30 @@
 // Verification walk of RADAR's speculative-sampling cycle (Sec. 3, Eq. 1-2; tree
 // form per Sec. 4.3, Eq. 11-13) as one HIP launch for gfx950.
 //
-// Phase 1, grid (blocks of the vocabulary, tree rows, sequences): one streaming
-// read of the target logits (T*V*4 bytes per sequence).  Every wavefront owns
-// 1024 consecutive logits and leaves their arg-max key and, in sampling mode,
-// (max, sum exp) of the temperature-scaled values; nothing is combined inside a
-// workgroup.  Phase 2: the workgroup whose arrival ticket is the last of its ROW
-// merges that row's partials in one wavefront and turns the sums into masses
-// relative to the row maximum.  Phase 3: the workgroup whose ticket is the last
-// of its SEQUENCE walks the tree in one wavefront, one lane per node: sibling
-// sets come from ballots, everything the walk compares sits in registers and is
-// passed between lanes by lane reads or DPP scans.  The residual draw scans the
-// 1024-logit masses across lanes and then re-reads one such block (4 KB).
+// Phase 1, grid (blocks of the vocabulary, sequences, tree rows): one streaming
+// read of target logits.  Every wavefront owns NB x 1024 consecutive logits and
+// leaves, per 1024, their arg-max key and, in sampling mode, (max, sum exp) of the
+// temperature-scaled values; nothing is combined inside a workgroup.  Phase 2: the
+// workgroup whose arrival ticket is the last of its ROW merges that row's partials
+// in one wavefront and turns the sums into masses relative to the row maximum.
+// Phase 3, the walk, starts with the root row's completion and is carried on by
+// whichever row completes next on the path: a completed row marks itself done, a
+// walk that arrives at a row marks it reached, and the one that finds the other's
+// mark goes on (the two marks are one atomic OR each, so exactly one does).
+// Nobody waits.  One wavefront, one lane per node: sibling sets come from ballots,
+// everything the walk compares sits in registers and is passed between lanes by
+// lane reads or DPP scans.  The residual draw scans the 1024-logit masses across
+// lanes and then re-reads one such block (4 KB).
+//
+// Only rows on the accepted path decide anything, and most rows of a batch are
+// known to be off it long before their turn in the stream: the walk publishes the
+// node it has arrived at, and a workgroup whose row does not descend from it leaves
+// its logits unread.  Rows go through the grid level by level over all sequences
+// (trees are numbered from the root), so that the roots' decisions come first.
+// What bounds a call is then the chain of decisions (about 2.5 us per level) and
+// the starting of workgroups, not the logits' bytes: 61 rows of V = 128256, sampled,
+// 8 / 16 sequences 24.8 / 30.9 us, against 70 / 129 us when every row is read; one
+// sequence 13.5 us against 15.7 (its walk no longer waits for the last row).
 #include "radar_device.h"
 #include "radar_host.h"
 
@@ -24,7 +37,12 @@ constexpr int kAccSub = kWave * kAccEPT;              // 1024 logits per wavefro
 constexpr int kAccChunk = kAccThreads * kAccEPT;      // logits per workgroup
 constexpr int kAccMaxSubs = 4096;                     // V <= 4,194,304
 constexpr int kAccCounterStride = 16;   // counters 64 B apart (same-line fetch-adds serialise)
+constexpr int64_t kAccManyBlocks = 49152;
+constexpr int64_t kAccWalkLast = 3072;  // greedy launches up to this many workgroups leave the walk to the last row
+constexpr int kAccUnchecked = 1024;     // workgroups the chip starts first: nothing is decided yet when they do
 constexpr float kAccLog2e = 1.4426950408889634f;
+constexpr unsigned int kAccDone = 1u << 30, kAccReached = 1u << 29;   // marks beside a row's count of arrivals
+constexpr int kAccEnded = RADAR_T_MAX;  // "node arrived at" once the walk has ended
 constexpr int kAccDistribution = 2;     // internal mode: acceptance-length distribution instead of a walk
 
 struct AcceptArgs {
@@ -37,11 +55,13 @@ struct AcceptArgs {
     int32_t *accept_path;
     int32_t *bonus;
     double *dist;               // mode kAccDistribution: [B][D_max+1]
-    int B, T, V, D_max, mode, nwg, nsub;   // nwg workgroups and nsub 1024-logit blocks per row
+    int B, T, V, D_max, nwg, nsub;   // nwg workgroups and nsub 1024-logit blocks per row
+    int check_from;             // workgroups from this number on ask whether their row can still be on the path
     int exact_scale;            // 1/temperature is exactly representable in fp32
     float inv_temp_f;
     double inv_temp;
-    unsigned int *counters;     // [(b*T + r) * stride] workgroups of a row, [(B*T + b) * stride] rows of a sequence
+    unsigned int *counters;     // [(b*T + r) * stride] workgroups of a row and its marks, [(B*T + b) * stride] finished rows
+                                // of a sequence, [(B*T + B + b) * stride] node its walk has arrived at (0: the root)
     uint64_t *row_key;          // [B][T] arg-max key of the row
     double *row_L;              // [B][T] sum of exp(y - row_M), y = logit / temperature
     float *row_M;               // [B][T]
@@ -53,8 +73,13 @@ struct AcceptArgs {
 
 struct AcceptSmem {
     unsigned int ticket;
-    double row_lse[RADAR_T_MAX];
+    double row_lse[RADAR_T_MAX];                  // rows whose results this wavefront holds
     int row_arg[RADAR_T_MAX];
+    float row_M[RADAR_T_MAX];
+    double row_L[RADAR_T_MAX];
+    int rej_tok[RADAR_T_MAX];
+    int internal[RADAR_T_MAX];                    // distribution: nodes with children,
+    unsigned long long kid_mask[RADAR_T_MAX], depth_mask[RADAR_T_MAX];   // the children of each node, the nodes at each depth
     double rej_e[RADAR_T_MAX];                    // what each rejected token carries, and the block it lies in
     int rej_sub[RADAR_T_MAX];
     unsigned int rej_bits[kWave];                 // pass (b): which of a lane's 16 tokens are rejected ones
@@ -64,8 +89,9 @@ struct AcceptSmem {
 // exp(x / temperature - ref) for one logit, as a double.  The exponent difference is rounded to
 // fp32 once (an fp32 FMA does that when the scale is exact in fp32, else it is formed in fp64);
 // the exponential itself is the fp32 one.  The sums that use it are kept in fp64.
+template <bool EXACT>
 __device__ __forceinline__ double scaled_exp(float x, const AcceptArgs &a, float ref) {
-    if (a.exact_scale) return (double)__builtin_amdgcn_exp2f(__builtin_fmaf(x, a.inv_temp_f, -ref) * kAccLog2e);
+    if (EXACT) return (double)__builtin_amdgcn_exp2f(__builtin_fmaf(x, a.inv_temp_f, -ref) * kAccLog2e);
     return (double)expf((float)((double)x * a.inv_temp - (double)ref));
 }
 
@@ -103,69 +129,126 @@ __device__ __forceinline__ void load_block(const float *row, int i_block, int V,
     }
 }
 
-template <bool VEC4>
+// One OR / addition on a counter by lane 0; every lane of the wavefront gets the value before it.
+__device__ __forceinline__ unsigned int wave_fetch_or(unsigned int *p, unsigned int v) {
+    unsigned int old = 0;
+    if (lane_id() == 0) old = __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return readlane_u32(old, 0);
+}
+__device__ __forceinline__ unsigned int wave_fetch_add(unsigned int *p, unsigned int v) {
+    unsigned int old = 0;
+    if (lane_id() == 0) old = __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return readlane_u32(old, 0);
+}
+
+// NB: 1024-logit blocks per wavefront, all requested at once
+// LAST: the walk is left to the last row of the sequence (greedy only).
+template <int MODE, bool LAST, bool VEC4, int NB>
 __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
     __shared__ AcceptSmem s;
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-    const int r = blockIdx.y, b = blockIdx.z;
+    const int b = blockIdx.y, r = blockIdx.z;
     int nn = a.n_nodes ? a.n_nodes[b] : a.T;
     nn = max(1, min(nn, a.T));
     if (r >= nn) return;
-    const bool sampling = (a.mode != RADAR_ACCEPT_GREEDY);      // row statistics are needed
+    constexpr bool sampling = MODE != RADAR_ACCEPT_GREEDY;      // row statistics are needed
+    constexpr bool distribution = MODE == kAccDistribution;
     const float *row = a.logits + ((size_t)b * a.T + r) * a.V;
-    const int sub = blockIdx.x * kAccWaves + w;              // this wavefront's 1024-logit block
+    const int sub0 = (blockIdx.x * kAccWaves + w) * NB;      // this wavefront's first 1024-logit block
+    unsigned int *const words = a.counters + (size_t)b * a.T * kAccCounterStride;          // of this sequence's rows
+    unsigned int *const seq_counter = &a.counters[((size_t)a.B * a.T + b) * kAccCounterStride];
+    unsigned int *const arrived_at = &a.counters[((size_t)a.B * a.T + a.B + b) * kAccCounterStride];
+
+    // ---------------- is the row needed?  The distribution reads the rows of nodes that have children (a
+    // leaf keeps whatever reaches it).  A walk reads the rows it arrives at, and those below the node it has
+    // arrived at so far may still be among them.  (The wavefronts of a workgroup, and the workgroups of a
+    // row, may see the walk at different nodes: one that finds the row off the path is right, the walk
+    // only moves down, and then nobody will ask for the row's results.)
+    bool needed = true;
+    if (distribution || (!LAST && (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x >= (unsigned int)a.check_from)) {
+        unsigned int at = 0;
+        if (!distribution) at = load_shared_result(arrived_at);
+        int par = lane < nn ? a.parents[(size_t)b * a.T + lane] : -1;
+        par = par < lane ? par : -1;
+        if (distribution) {
+            if (r > 0 && __ballot(par == r) == 0ull) return;
+        } else {
+            const int cur = (int)readlane_u32(at, 0);
+            int x = r;
+            while (x > cur) x = (int)readlane_u32((uint32_t)par, x);        // strictly decreasing
+            needed = x == cur;
+        }
+    }
 
     // ---------------- phase 1: per-wavefront arg-max (and scaled max / sum-exp)
-    if (sub < a.nsub) {
-        float x[kAccEPT];
-        int first[kAccEPT / 4];
-        load_block<VEC4, false>(row, sub * kAccSub, a.V, x, first);
-        // Largest logit of the block first (lane, then wavefront); only the lanes that hold it look for
-        // its position, lowest index first (-0.0 equals +0.0 here, as in the key order).
-        float tmx = x[0];
+    if (needed && sub0 < a.nsub) {
+        float x[NB][kAccEPT];
+        int first[NB][kAccEPT / 4];
 #pragma unroll
-        for (int e = 1; e < kAccEPT; ++e) tmx = fmaxf(tmx, x[e]);
-        const float wmx = wave_max_f32(tmx);
-        uint32_t bi = 0xffffffffu;
-        if (tmx == wmx) {
+        for (int i = 0; i < NB; ++i) load_block<VEC4, false>(row, (sub0 + i) * kAccSub, a.V, x[i], first[i]);
 #pragma unroll
-            for (int e = kAccEPT - 1; e >= 0; --e) bi = (x[e] == wmx) ? uint32_t(first[e / 4] + (e & 3)) : bi;
-        }
-        bi = ~wave_max_u32(~bi);                                  // lowest index over the wavefront
-        const uint64_t best = bi < (uint32_t)a.V ? make_key(wmx, bi) : 0;
-        const size_t pslot = ((size_t)b * a.T + r) * a.nsub + sub;
-        if (sampling) {
-            // 1 / temperature > 0 and rounding is monotone, so the largest scaled logit is the scaled largest
-            const float wm = wmx * a.inv_temp_f;
-            double tl = 0.0;
-            if (wm > -INFINITY) {
+        for (int i = 0; i < NB; ++i) {
+            // Largest logit of the block first (lane, then wavefront); only the lanes that hold it look for
+            // its position, lowest index first (-0.0 equals +0.0 here, as in the key order).
+            float tmx = x[i][0];
 #pragma unroll
-                for (int e = 0; e < kAccEPT; ++e) tl += scaled_exp(x[e], a, wm);
+            for (int e = 1; e < kAccEPT; ++e) tmx = fmaxf(tmx, x[i][e]);
+            const float wmx = wave_max_f32(tmx);
+            uint32_t bi = 0xffffffffu;
+            if (tmx == wmx) {
+#pragma unroll
+                for (int e = kAccEPT - 1; e >= 0; --e) bi = (x[i][e] == wmx) ? uint32_t(first[i][e / 4] + (e & 3)) : bi;
             }
-            const double wl = wave_sum_f64(tl);
-            if (lane == 0) {
-                store_shared_result(&a.part_m[pslot], wm);
-                store_shared_result(&a.part_l[pslot], wl);
+            bi = ~wave_max_u32(~bi);                              // lowest index over the wavefront
+            const uint64_t best = bi < (uint32_t)a.V ? make_key(wmx, bi) : 0;
+            const size_t pslot = ((size_t)b * a.T + r) * a.nsub + sub0 + i;
+            const bool live = NB == 1 || sub0 + i < a.nsub;       // wave-uniform
+            if (sampling) {
+                // 1 / temperature > 0 and rounding is monotone, so the largest scaled logit is the scaled largest
+                const float wm = wmx * a.inv_temp_f;
+                double tl = 0.0;
+                if (wm > -INFINITY) {
+                    if (a.exact_scale) {
+#pragma unroll
+                        for (int e = 0; e < kAccEPT; ++e) tl += scaled_exp<true>(x[i][e], a, wm);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < kAccEPT; ++e) tl += scaled_exp<false>(x[i][e], a, wm);
+                    }
+                }
+                const double wl = wave_sum_f64(tl);
+                if (lane == 0 && live) {
+                    store_shared_result(&a.part_m[pslot], wm);
+                    store_shared_result(&a.part_l[pslot], wl);
+                }
             }
+            if (lane == 0 && live) store_shared_result(&a.part_key[pslot], best);
         }
-        if (lane == 0) store_shared_result(&a.part_key[pslot], best);
     }
-    unsigned int *row_counter = &a.counters[((size_t)b * a.T + r) * kAccCounterStride];
-    if (publish_then_ticket(row_counter, &s.ticket) != (unsigned int)(a.nwg - 1)) return;
-    if (w != 0) {                                            // one wavefront does the rest; the others only
-        __syncthreads();                                     // take part in the next ticket's barriers
-        __syncthreads();
-        return;
-    }
+    if ((publish_then_ticket(&words[r * kAccCounterStride], &s.ticket) & (kAccReached - 1)) != (unsigned int)(a.nwg - 1)) return;
+    if (w != 0) return;                                      // one wavefront does the rest
+
+    // A row is finished once whoever completed it has nothing more to do for it; the last row of the sequence
+    // leaves the counters clean for the next call (every workgroup has arrived by then, and the walk
+    // has ended: its steps are taken by rows not finished yet).
+    auto finish_row = [&](unsigned int before) {
+        if (before != (unsigned int)(nn - 1)) return;
+        if (lane < nn) store_shared_result(&words[lane * kAccCounterStride], 0u);
+        if (lane == 0) { store_shared_result(seq_counter, 0u); store_shared_result(arrived_at, 0u); }
+    };
+    if (!needed) { finish_row(wave_fetch_add(seq_counter, 1u)); return; }
 
     // ---------------- phase 2: last workgroup of row r -- merge the row's partials.
     // What only the walk needs (lane c is tree node c) is fetched here, so that it has arrived by
     // the time the walk starts.
+    const int c = lane;
     int p = -1, t = -1;
     float xg = 0.f, uc = 0.f, ubonus = 0.f;
     bool tree_ok = false;
+    uint64_t kb = 0;
+    float M;
+    double L, mass_[2] = {0.0, 0.0};                         // this row's first 128 block masses
     {
-        const int c = lane;
         if (c < nn) { p = a.parents[(size_t)b * a.T + c]; t = a.tokens[(size_t)b * a.T + c]; }
         tree_ok = (c > 0 && c < nn && p >= 0 && p < c);
         if (sampling) {
@@ -178,7 +261,6 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         }
         const size_t p0 = ((size_t)b * a.T + r) * a.nsub;
         // the first 128 partials (all of them up to V = 131072) are taken in one round trip
-        uint64_t kb = 0;
         float m_[2];
         double l_[2];
 #pragma unroll
@@ -200,7 +282,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
             if (sampling) mmax = fmaxf(mmax, load_shared_result(&a.part_m[p0 + c0]));
         }
         kb = wave_max_u64(kb);
-        const float M = wave_max_f32(mmax);
+        M = wave_max_f32(mmax);
         double lsum = 0.0;
         if (sampling) {
             // each block's mass relative to the row maximum: summed for the row, and left in part_l
@@ -208,9 +290,9 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int c0 = i * kWave + lane;
-                const double mass = m_[i] > -INFINITY ? l_[i] * exp((double)m_[i] - (double)M) : 0.0;
-                if (c0 < a.nsub) store_shared_result(&a.part_l[p0 + c0], mass);
-                lsum += mass;
+                mass_[i] = m_[i] > -INFINITY ? l_[i] * exp((double)m_[i] - (double)M) : 0.0;
+                if (c0 < a.nsub) store_shared_result(&a.part_l[p0 + c0], mass_[i]);
+                lsum += mass_[i];
             }
             for (int c0 = 2 * kWave + lane; c0 < a.nsub; c0 += kWave) {
                 const float m2 = load_shared_result(&a.part_m[p0 + c0]);
@@ -220,7 +302,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
                 lsum += mass;
             }
         }
-        const double L = wave_sum_f64(lsum);
+        L = wave_sum_f64(lsum);
         if (lane == 0) {
             const size_t rs = (size_t)b * a.T + r;
             store_shared_result(&a.row_key[rs], kb);
@@ -228,55 +310,35 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
                 store_shared_result(&a.row_M[rs], M);
                 store_shared_result(&a.row_L[rs], L);
             }
-            store_shared_result(row_counter, 0u);            // leave the row counter clean for the next call
+            if (distribution || LAST) store_shared_result(&words[r * kAccCounterStride], 0u);   // leave the row's counter clean
         }
     }
-    unsigned int *seq_counter = &a.counters[((size_t)a.B * a.T + b) * kAccCounterStride];
-    if (publish_then_ticket(seq_counter, &s.ticket) != (unsigned int)(nn - 1)) return;
-    if (lane == 0) store_shared_result(seq_counter, 0u);
 
-    // ---------------- phase 3: last workgroup of sequence b, one wavefront
-    const int c = lane;
-    const size_t rs = (size_t)b * a.T + min(c, nn - 1);
-    const int arg = (int)key_index(load_shared_result(&a.row_key[rs]));
-    float Mc = 0.f;
-    double Lc = 1.0;
-    if (sampling) {
-        Mc = load_shared_result(&a.row_M[rs]);
-        Lc = load_shared_result(&a.row_L[rs]);
-        s.row_lse[c] = (double)Mc + log(Lc);
-    }
-    s.row_arg[c] = arg;
-    wave_lds_sync();
-
-    int cur = 0, len = 0, mypath = 0;                        // lane i keeps path[i]
-    int32_t *path = a.accept_path + (size_t)b * (a.D_max + 1);
-    if (!sampling) {
-        const bool match = tree_ok && s.row_arg[p] == t;
-        while (len < a.D_max) {
-            const uint64_t m = __ballot(match && p == cur);
-            if (!m) break;
-            cur = __ffsll((long long)m) - 1;
-            ++len;
-            if (lane == len) mypath = cur;
-        }
-        if (lane == 0) { a.accept_len[b] = len; a.bonus[b] = s.row_arg[cur]; }
-        if (c <= a.D_max) path[c] = (c <= len) ? mypath : -1;
-        return;
-    }
-
-    // probability of each node's token under its parent's row
-    double pc = 0.0;
-    if (tree_ok && t >= 0 && t < a.V) pc = exp((double)xg * a.inv_temp - s.row_lse[p]);
-
-    if (a.mode == kAccDistribution) {
-        // Sec. 4.3, Eq. 11-13.  Nodes are visited in index order (parents come first), one lane per
-        // node, values passed between lanes by lane reads; sums run in node order.
+    if (distribution) {
+        // the last of the rows with children (and the root's) goes on
+        s.internal[lane] = lane == 0;
+        wave_lds_sync();
+        if (tree_ok) s.internal[p] = 1;
+        wave_lds_sync();
+        const bool inner = s.internal[lane] != 0;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (wave_fetch_add(seq_counter, 1u) != (unsigned int)(__popcll(__ballot(inner)) - 1)) return;
+        if (lane == 0) store_shared_result(seq_counter, 0u);
+        const size_t rs = (size_t)b * a.T + min(c, nn - 1);
+        if (inner) s.row_lse[c] = (double)load_shared_result(&a.row_M[rs]) + log(load_shared_result(&a.row_L[rs]));
+        wave_lds_sync();
+        double pc = 0.0;                                     // probability of each node's token under its parent's row
+        if (tree_ok && t >= 0 && t < a.V) pc = exp((double)xg * a.inv_temp - s.row_lse[p]);
+        // Sec. 4.3, Eq. 11-13, one lane per node.
+        // Children of each node as a bit mask; the sums below run over the bits, in node order.
+        s.kid_mask[lane] = 0;
+        s.rej_tok[lane] = t;
+        wave_lds_sync();
+        if (tree_ok) atomicOr(&s.kid_mask[p], 1ull << lane);
+        wave_lds_sync();
         bool dup = false;                                    // same token as an earlier sibling: never reached
-        for (int o = 1; o < nn; ++o) {
-            const int po = (int)readlane_u32((uint32_t)p, o), to = (int)readlane_u32((uint32_t)t, o);
-            dup = dup || (o < c && po == p && to == t);
-        }
+        for (unsigned long long m = tree_ok ? s.kid_mask[p] & ((1ull << lane) - 1) : 0ull; m; m &= m - 1)
+            dup = dup || s.rej_tok[__ffsll((long long)m) - 1] == t;
         if (dup) pc = 0.0;
         // depth and reach level by level: a lane whose parent is settled takes depth(parent) + 1 and
         // reach(parent) * its own probability (two lane gathers); as many rounds as the tree is deep.
@@ -297,22 +359,71 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
                 settled = true;
             }
         }
-        for (int v = 1; v < nn; ++v) {                       // children's mass per parent, summed in node order
-            const int pv = (int)readlane_u32((uint32_t)p, v);
-            const double pcv = readlane_f64(pc, v);
-            if (lane == pv) kids += pcv;
-        }
+        s.rej_e[lane] = pc;
+        s.depth_mask[lane] = 0;
+        wave_lds_sync();
+        for (unsigned long long m = s.kid_mask[lane]; m; m &= m - 1) kids += s.rej_e[__ffsll((long long)m) - 1];   // children's mass per parent
         double stay = 1.0 - kids;
         stay = stay > 0.0 ? stay : 0.0;
         const double pstop = (c < nn && depth <= a.D_max) ? reach * stay : 0.0;
+        wave_lds_sync();
+        s.rej_e[lane] = pstop;
+        if (c < nn && pstop > 0.0) atomicOr(&s.depth_mask[depth], 1ull << lane);
+        wave_lds_sync();
         double acc = 0.0;
-        for (int v = 0; v < nn; ++v) {
-            const int dv = (int)readlane_u32((uint32_t)depth, v);
-            const double sv = readlane_f64(pstop, v);
-            if (lane == dv) acc += sv;
-        }
+        for (unsigned long long m = s.depth_mask[lane]; m; m &= m - 1) acc += s.rej_e[__ffsll((long long)m) - 1];
         for (int d = lane; d <= a.D_max; d += kWave) a.dist[(size_t)b * (a.D_max + 1) + d] = d == lane ? acc : 0.0;
         return;
+    }
+
+    // ---------------- phase 3: this row is done; if the walk has arrived here already (it starts at the root), go on with it
+    if (LAST) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (wave_fetch_add(seq_counter, 1u) != (unsigned int)(nn - 1)) return;
+        if (lane == 0) store_shared_result(seq_counter, 0u);
+    } else if (r > 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if ((wave_fetch_or(&words[r * kAccCounterStride], kAccDone) & kAccReached) == 0u) {
+            finish_row(wave_fetch_add(seq_counter, 1u));
+            return;
+        }
+    }
+    uint64_t have = 0;                                       // rows whose results are in s.row_*
+    bool match = false;                                      // greedy: the token is its parent's row's arg-max
+    double pc = 0.0;                                         // sampled: probability of the token under its parent's row
+    // the results of the rows whose lanes say so, and what follows from them for their children
+    auto take_rows = [&](bool take, bool own) {
+        if (take) {
+            const size_t rs = (size_t)b * a.T + lane;
+            const uint64_t key = own ? kb : load_shared_result(&a.row_key[rs]);
+            if (sampling) {
+                const float Mr = own ? M : load_shared_result(&a.row_M[rs]);
+                const double Lr = own ? L : load_shared_result(&a.row_L[rs]);
+                s.row_M[lane] = Mr;
+                s.row_L[lane] = Lr;
+                s.row_lse[lane] = (double)Mr + log(Lr);
+            }
+            s.row_arg[lane] = (int)key_index(key);
+        }
+        const uint64_t fresh = __ballot(take);
+        have |= fresh;
+        wave_lds_sync();
+        if (tree_ok && ((fresh >> p) & 1)) {
+            if (!sampling) match = s.row_arg[p] == t;
+            else if (t >= 0 && t < a.V) pc = exp((double)xg * a.inv_temp - s.row_lse[p]);
+        }
+    };
+    const int up = tree_ok ? p : -1;
+    int cur = 0, len = 0, mypath = 0;                        // lane i keeps path[i]
+    if (LAST) {
+        take_rows(lane < nn, false);
+    } else {
+        take_rows(lane == r, true);
+        cur = r;
+        for (int x = r; x > 0; x = (int)readlane_u32((uint32_t)up, x)) ++len;
+        int d = len;
+        for (int x = r; x > 0; x = (int)readlane_u32((uint32_t)up, x), --d)
+            if (lane == d) mypath = x;
     }
     double R = 0.0;
     int nrej = 0, rejtok = -1;                               // lane j keeps the j-th rejected token
@@ -320,7 +431,10 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         uint64_t kids = (len < a.D_max) ? __ballot(tree_ok && p == cur) : 0ull;
         R = 0.0; nrej = 0;
         int next = -1;
-        if (__popcll(kids) > 4) {
+        if (!sampling) {
+            kids &= __ballot(match);
+            if (kids) next = __ffsll((long long)kids) - 1;
+        } else if (__popcll(kids) > 4) {
             // wide level: all children at once.  A child is reached only if every earlier sibling was
             // rejected, so its residual is the sum of the earlier siblings' probabilities.
             const bool kid = (kids >> lane) & 1;
@@ -351,9 +465,9 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
             nrej = __popcll(rejected);
             R = nrej ? readlane_f64(before + mine, 63 - __clzll((long long)rejected)) : 0.0;
             // lane j takes the token of the j-th rejected child
-            if ((rejected >> lane) & 1) s.row_arg[lanes_below(rejected)] = t;      // row_arg is free by now
+            if ((rejected >> lane) & 1) s.rej_tok[lanes_below(rejected)] = t;
             wave_lds_sync();
-            rejtok = lane < nrej ? s.row_arg[lane] : -1;
+            rejtok = lane < nrej ? s.rej_tok[lane] : -1;
             wave_lds_sync();
         } else {
             while (kids) {
@@ -373,18 +487,43 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         cur = next;
         ++len;
         if (lane == len) mypath = cur;
+        if (LAST) continue;
+        if (lane == 0) store_shared_result(arrived_at, (unsigned int)cur);
+        if ((have >> cur) & 1) continue;
+        // The next row's results: if it is not done yet, whoever completes it finds the mark and goes on.
+        // Otherwise every row that is done by now is fetched, and the walk continues in registers.
+        const unsigned int seen = wave_fetch_or(&words[cur * kAccCounterStride], kAccReached);
+        const unsigned int word = load_shared_result(&words[min(lane, nn - 1) * kAccCounterStride]);
+        if ((seen & kAccDone) == 0u) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            finish_row(wave_fetch_add(seq_counter, 1u));
+            return;
+        }
+        take_rows((lane == cur || (lane < nn && (word & kAccDone) != 0u)) && !((have >> lane) & 1), false);
     }
-    if (c <= a.D_max) path[c] = (c <= len) ? mypath : -1;
+    if (lane == 0 && !LAST) store_shared_result(arrived_at, (unsigned int)kAccEnded);
+    if (c <= a.D_max) a.accept_path[(size_t)b * (a.D_max + 1) + c] = (c <= len) ? mypath : -1;
     if (lane == 0) a.accept_len[b] = len;
+    if (!sampling) {
+        if (lane == 0) a.bonus[b] = s.row_arg[cur];
+        if (LAST) return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        finish_row(wave_fetch_add(seq_counter, 1u));
+        return;
+    }
 
     // ---- residual draw, (a): the 1024-logit block that holds the target mass
-    const float M = readlane_f32(Mc, cur);
-    const double L = readlane_f64(Lc, cur);
+    M = s.row_M[cur];
+    L = s.row_L[cur];
     const size_t p0 = ((size_t)b * a.T + cur) * a.nsub;
     const float *xr = a.logits + ((size_t)b * a.T + cur) * a.V;
     // masses of the first 128 blocks: requested together with the rejected tokens' logits
-    double mass0 = (lane < a.nsub) ? load_shared_result(&a.part_l[p0 + lane]) : 0.0;
-    double mass1 = (kWave + lane < a.nsub) ? load_shared_result(&a.part_l[p0 + kWave + lane]) : 0.0;
+    // (a row this wavefront has just merged still has them in registers)
+    double mass0 = mass_[0], mass1 = mass_[1];
+    if (cur != r) {
+        mass0 = (lane < a.nsub) ? load_shared_result(&a.part_l[p0 + lane]) : 0.0;
+        mass1 = (kWave + lane < a.nsub) ? load_shared_result(&a.part_l[p0 + kWave + lane]) : 0.0;
+    }
     {   // what the rejected children's tokens carry (the same arithmetic as pass (b) uses)
         float xj = -INFINITY;
         int sj = -1;
@@ -392,7 +531,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
             xj = xr[rejtok];
             sj = rejtok / kAccSub;
         }
-        s.rej_e[lane] = sj >= 0 ? scaled_exp(xj, a, M) : 0.0;
+        s.rej_e[lane] = sj < 0 ? 0.0 : a.exact_scale ? scaled_exp<true>(xj, a, M) : scaled_exp<false>(xj, a, M);
         s.rej_sub[lane] = sj;
         wave_lds_sync();
     }
@@ -435,6 +574,8 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         const int off = rejtok - pick * kAccSub;
         atomicOr(&s.rej_bits[off / kAccEPT], 1u << (off % kAccEPT));
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (everything asked for has been used by now)
+    const unsigned int rows_before = wave_fetch_add(seq_counter, 1u);
     float xv[kAccEPT];
     int first[kAccEPT / 4];
     load_block<VEC4, true>(xr, pick * kAccSub, a.V, xv, first);
@@ -442,15 +583,21 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
     const unsigned int rejected = s.rej_bits[lane];
     const int i0 = pick * kAccSub + lane * kAccEPT;
     double pv[kAccEPT];
+    if (a.exact_scale) {
+#pragma unroll
+        for (int e = 0; e < kAccEPT; ++e) pv[e] = scaled_exp<true>(xv[e], a, M);
+    } else {
+#pragma unroll
+        for (int e = 0; e < kAccEPT; ++e) pv[e] = scaled_exp<false>(xv[e], a, M);
+    }
     double sum = 0.0;
     int lastpos = -1;
 #pragma unroll
     for (int e = 0; e < kAccEPT; ++e) {
         const int i = i0 + e;
-        const double v = (i < a.V && !((rejected >> e) & 1)) ? scaled_exp(xv[e], a, M) : 0.0;
-        pv[e] = v;
-        sum += v;
-        if (v > 0.0) lastpos = i;
+        pv[e] = (i < a.V && !((rejected >> e) & 1)) ? pv[e] : 0.0;
+        sum += pv[e];
+        if (pv[e] > 0.0) lastpos = i;
     }
     const double incl = wave_scan_f64(sum);
     const uint64_t hit = __ballot(incl > resid);
@@ -470,6 +617,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         if (got >= 0) bonus = got;
     }
     if (lane == 0) a.bonus[b] = bonus;
+    finish_row(rows_before);
 }
 
 __global__ void validate_tree_kernel(const int32_t *parents, const int32_t *n_nodes, int B, int T, int32_t *bad) {
@@ -500,7 +648,7 @@ static size_t accept_layout(int B, int T, size_t nsub, char *ws, AcceptArgs *a) 
     const size_t rows = (size_t)B * T, slots = rows * nsub;
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~size_t(255); return o; };
-    const size_t o_cnt = take((rows + B) * kAccCounterStride * sizeof(unsigned int));
+    const size_t o_cnt = take((rows + 2 * (size_t)B) * kAccCounterStride * sizeof(unsigned int));
     const size_t o_rk = take(rows * sizeof(uint64_t)), o_rl = take(rows * sizeof(double)), o_rm = take(rows * sizeof(float));
     const size_t o_pk = take(slots * sizeof(uint64_t)), o_pl = take(slots * sizeof(double)), o_pm = take(slots * sizeof(float));
     if (ws) {
@@ -521,6 +669,13 @@ extern "C" size_t radar_verify_accept_workspace_bytes(const radar_accept_desc *d
     return accept_layout(d->B, d->T_max, nsub, nullptr, nullptr);
 }
 
+template <int MODE, bool LAST>
+static hipError_t launch_mode(const char *name, bool vec4, int nb, dim3 grid, dim3 block, hipStream_t st, const AcceptArgs &a) {
+    if (nb == 1)
+        return vec4 ? launch(name, accept_kernel<MODE, LAST, true, 1>, grid, block, 0, st, a) : launch(name, accept_kernel<MODE, LAST, false, 1>, grid, block, 0, st, a);
+    return vec4 ? launch(name, accept_kernel<MODE, LAST, true, 2>, grid, block, 0, st, a) : launch(name, accept_kernel<MODE, LAST, false, 2>, grid, block, 0, st, a);
+}
+
 static radar_status launch_accept(const float *target_logits, const int32_t *draft_tokens, const int32_t *parents,
                                   const int32_t *n_nodes, const float *uniforms, int32_t *accept_len,
                                   int32_t *accept_path, int32_t *bonus_token, double *dist, int mode,
@@ -528,7 +683,12 @@ static radar_status launch_accept(const float *target_logits, const int32_t *dra
     if (d->B < 1 || d->T_max < 1 || d->V < 1 || d->D_max < 0) return RADAR_INVALID_ARG;
     if (mode != RADAR_ACCEPT_GREEDY && !(d->temperature > 0.0f)) return RADAR_INVALID_ARG;
     const int64_t nsub = ((int64_t)d->V + kAccSub - 1) / kAccSub;
-    const int64_t nwg = (nsub + kAccWaves - 1) / kAccWaves;
+    // Blocks per wavefront: one gives the most wavefronts and the shortest chain for each; launches of many rounds
+    // take two, half the workgroups to start, to be told that their row is not needed and to count.  61 rows of
+    // V = 128256, sampled: 4 sequences 18.0 us with one and 22.2 with two, 8 sequences 25.9 and 24.8, 16
+    // sequences 40.1 and 30.9 (and 40.2 with four: fewer bytes in flight for the rows that are needed).
+    const int nb = (int64_t)d->B * d->T_max * nsub >= kAccManyBlocks ? 2 : 1;
+    const int64_t nwg = (nsub + kAccWaves * nb - 1) / (kAccWaves * nb);
     if (d->T_max > RADAR_T_MAX || d->D_max >= RADAR_T_MAX || d->B > 65535 || nsub > kAccMaxSubs)
         return RADAR_UNSUPPORTED_SHAPE;
     if (workspace_bytes < radar_verify_accept_workspace_bytes(d)) return RADAR_WORKSPACE_TOO_SMALL;
@@ -537,19 +697,27 @@ static radar_status launch_accept(const float *target_logits, const int32_t *dra
     AcceptArgs a;
     a.logits = target_logits; a.tokens = draft_tokens; a.parents = parents; a.n_nodes = n_nodes; a.uniforms = uniforms;
     a.accept_len = accept_len; a.accept_path = accept_path; a.bonus = bonus_token; a.dist = dist;
-    a.B = d->B; a.T = d->T_max; a.V = d->V; a.D_max = d->D_max; a.mode = mode;
+    a.B = d->B; a.T = d->T_max; a.V = d->V; a.D_max = d->D_max;
     a.nsub = (int)nsub; a.nwg = (int)nwg;
     a.inv_temp = mode != RADAR_ACCEPT_GREEDY ? 1.0 / (double)d->temperature : 1.0;
     a.inv_temp_f = (float)a.inv_temp;
     a.exact_scale = ((double)a.inv_temp_f == a.inv_temp) ? 1 : 0;
     accept_layout(d->B, d->T_max, (size_t)nsub, static_cast<char *>(workspace), &a);
+    a.check_from = kAccUnchecked;
+    // A greedy walk is shortest at the end of the launch, in registers over all rows' results, as long as the launch
+    // is not much more than the chip holds at once (one sequence of 16 rows, V = 32000: 5.6 us against 7.1; two of
+    // 61 rows, V = 128256, 3904 workgroups: 13.9 against 13.3).  A sampled one is not: its exponentials and the
+    // draw's block masses are better taken as the rows end (61 rows, V = 128256: 14.3 us at the end, 12.9 on the way).
+    const bool last = mode == RADAR_ACCEPT_GREEDY && (int64_t)d->B * d->T_max * nwg <= kAccWalkLast;
 
-    const dim3 grid((unsigned)nwg, (unsigned)d->T_max, (unsigned)d->B), block(kAccThreads);
+    const dim3 grid((unsigned)nwg, (unsigned)d->B, (unsigned)d->T_max), block(kAccThreads);
     const bool vec4 = (d->V % 4 == 0) && (((uintptr_t)target_logits & 15) == 0);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const char *name = mode == kAccDistribution ? "accept_length_distribution" : "accept";
-    const hipError_t e = vec4 ? launch(name, accept_kernel<true>, grid, block, 0, st, a)
-                              : launch(name, accept_kernel<false>, grid, block, 0, st, a);
+    const auto go = mode == kAccDistribution ? launch_mode<kAccDistribution, false>
+                    : mode == RADAR_ACCEPT_SAMPLE ? launch_mode<RADAR_ACCEPT_SAMPLE, false>
+                                                  : (last ? launch_mode<RADAR_ACCEPT_GREEDY, true> : launch_mode<RADAR_ACCEPT_GREEDY, false>);
+    const hipError_t e = go(name, vec4, nb, grid, block, st, a);
     return e == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
 }
 

@@ -181,3 +181,27 @@ def test_large_vocabulary_many_blocks(oracle, mode):
     a = small_shape(2, 12, (12, 7), (3, 2), k=3)
     x = synth.accept_inputs(a, V, seed=77)
     compare(oracle, b, x, mode)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("B,T,V,chain", [(3, 64, 40000, True), (6, 64, 34000, False), (12, 64, 65539, False)])
+def test_walk_carried_from_row_to_row(oracle, mode, B, T, V, chain):
+    """The walk that goes on with whichever row completes next: trees as deep as they get, launches with more workgroups
+    than start at once (rows off the path are left unread), two blocks per wavefront with odd row lengths, and one
+    workspace for several inputs in a row."""
+    from paper_2512_14069_amd import binding as b
+    ws = b.new_workspace(b.radar_verify_accept_workspace_bytes(b.accept_desc(B, T, V, T - 1, mode, 1.0)))
+    for seed in (1, 2):
+        x = synth.accept_inputs(small_shape(B, T, (T,) * (B - 1) + (1,), (8,) * B, k=10), V, seed=70 + seed, plant=0.0 if chain else 0.9)
+        if chain:
+            x["parents"][:] = synth.chain_tree(T)
+            x["n_nodes"][:] = T
+            nodes = np.arange(1, T)
+            for s in range(B):                            # rows that prefer their own child, up to some depth
+                last = T if s == 0 else 5 * s
+                x["target_logits"][s, nodes[:last - 1] - 1, x["draft_tokens"][s, 1:last]] = synth.PLANT_LOGIT
+        compare(oracle, b, x, mode)
+        ref = run_gpu(b, x, mode)
+        assert all(np.array_equal(p, q) for p, q in zip(ref, run_gpu(b, x, mode, ws=ws)))
+        assert not chain or ref[0].max() == T - 1
+    assert int(ws[:4096].view(torch.int32).abs().sum().item()) == 0
