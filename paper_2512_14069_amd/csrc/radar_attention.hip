@@ -9,7 +9,7 @@
 // exponentiated scores already sit in the register order the next MFMA wants as
 // its B operand (the key order inside a 16-key step is permuted consistently for
 // P^T and V^T, which a contraction does not care about).  The running output is
-// rescaled only when some lane's maximum actually moved.
+// rescaled only when some lane's maximum has risen past its reference by a factor of 256.
 //
 // The ancestor mask is never materialised in memory: each lane walks parents[]
 // once for its query row and keeps the ancestor set as one 64-bit word; a tile
@@ -22,9 +22,11 @@
 // wavefront's MFMAs run underneath the other's softmax arithmetic.  Tiles are
 // double-buffered in LDS (one barrier per tile) and the next tile's global loads
 // are in flight during the arithmetic.  Ranges of cache rows are merged from partials
-// (fp16 pairs scaled per row, plus maximum, sum and scale in fp32) by a small second kernel; how many ranges to cut is decided on the host
-// from a cost model that counts whole rounds of resident workgroups and the
-// partial traffic.
+// (fp16 pairs scaled per row, plus maximum, sum and scale in fp32) by a small second kernel.  Short
+// ranges: how many to cut is decided on the host from a cost model that counts whole rounds of
+// resident workgroups and the partial traffic.  Long ranges: the workgroups read the lengths and
+// deal the batch's cache rows out among themselves, so that a batch of unlike sequences keeps every
+// CU busy to the end.
 #include "radar_device.h"
 #include <type_traits>
 #include "radar_host.h"
@@ -41,6 +43,7 @@ constexpr int kAttnWaves = 4;
 constexpr int kKT = 64;                    // cache rows per LDS tile
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
+constexpr float kMaxSlack = 8.0f;          // how far a row's maximum may pass its reference (log2 units)
 constexpr float kNegBig = -1.0e30f;        // finite stand-in for "no score yet" (log2 units)
 
 struct AttnArgs {
@@ -51,8 +54,12 @@ struct AttnArgs {
     int B, T, Hq, Hkv, G, S, kps, max_splits, n_ublk, nqb;   // nqb 32-row blocks per head, n_ublk workgroups per KV range
     int64_t q_sb, q_st, q_sh, kv_sb, kv_sh, kv_ss, o_sb, o_st, o_sh;
     float scale_log2;                      // softmax scale * log2(e), > 0
-    uint32_t *part_o;                      // [B][Hq][max_splits][D/2][64]: partial outputs, fp16 pairs (d, d+1), scaled per row
-    float *part_ml;                        // [B][Hq][max_splits][3][64]: running maximum (log2 units), sum, and the scale of part_o
+    uint32_t shares_inv;                   // ceil(2^32 / shares)
+    int per_unit;                          // shares / (B * Hkv)
+    int shares;                            // > 0: the rows are dealt out on the device, to so many workgroups per unit block
+    uint64_t *part_o;                      // [slot][n_ublk * 8][D/8][32][8]: partial outputs, fp16, scaled per row
+    uint64_t *unit_tab;                    // [B][Hkv] dealt-out rows: first slot (low half) and number of a head's partials (high half)
+    float *part_ml;                        // [slot][n_ublk * 8][3][32]: running maximum (log2 units), sum, and the scale of part_o
 };
 
 // Byte offset of the 16-byte chunk `chunk` of cache row `key` in a K tile.  The chunks of a row are
@@ -105,7 +112,7 @@ __device__ __forceinline__ uint64_t ancestor_word(const int *par, int i) {
 
 // One wavefront, one 64-row tile that sits in LDS, in three phases: scores into
 // `sacc` (register r of sub-tile `sub` is row 32*sub + 8*(r/4) + 4*g2 + r%4), masked online softmax
-// from `sacc` into the bf16 operand `pk` (rescaling the output accumulators when the maximum moved),
+// from `sacc` into the bf16 operand `pk` (rescaling the output accumulators when the maximum moved far),
 // and the update of the transposed output accumulators, from a transposed V tile (vt_off) or, with
 // VTR, from a row-major one (vs_off) through transposing LDS reads.
 // The lane's query operands are passed in registers (qop: row j32 of the block, d = 16*st + 8*g2
@@ -170,17 +177,20 @@ __device__ __forceinline__ void tile_softmax(floatx16 (&sacc)[2], floatx16 (&oac
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[sub][r]);
     mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float m_new = fmaxf(m_run, mx * scale_log2);               // scale_log2 > 0; -inf stays -inf
-    if (!first) {
+    // The reference the exponentials are taken against follows the maximum only when that has risen by
+    // more than 8 (a factor of 256 in a probability, which neither bf16 nor the fp32 sums notice): the
+    // maxima of 32 rows keep moving a little in most tiles, and each move would cost rescaling the
+    // accumulators, a sixth of a tile's vector instructions.
+    const float mt = mx * scale_log2;                                // scale_log2 > 0; -inf stays -inf
+    const float m_new = mt > m_run + kMaxSlack ? mt : m_run;
+    if (!first && __any(m_new != m_run)) {                           // wave-uniform
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         l_run *= alpha;
-        if (__any(alpha != 1.0f)) {                                  // wave-uniform: most tiles skip this
 #pragma unroll
-            for (int db = 0; db < DB; ++db) {
+        for (int db = 0; db < DB; ++db) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[db][0][r] *= alpha;
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int r = 0; r < 16; ++r) oacc[db][0][r] *= alpha;
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     m_run = m_new;
@@ -304,13 +314,14 @@ __device__ __forceinline__ void gs_store_tile(const GsTileRegs<D> &g, unsigned c
 
 // End of a group-share kernel: a lane owns query i; its accumulator registers O(db, r) hold
 // d = 32*db + 8*(r/4) + 4*g2 + r%4 of the transposed output.
+// direct: this wavefront saw all of its rows' keys; otherwise its result is partial number `entry`.
 template <int D, typename Acc>
 __device__ __forceinline__ void gs_finish(const AttnArgs &a, Acc O, float m_run, float l_run, int b, int h, int i, int nn,
-                                          int sp, int nsplit) {
+                                          bool direct, int entry) {
     constexpr int DB = D / 32;
     const int g2 = lane_id() >> 5;
     const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (nsplit == 1) {
+    if (direct) {
         if (i >= a.T) return;
         __bf16 *orow = a.out + (size_t)b * a.o_sb + (size_t)i * a.o_st + (size_t)h * a.o_sh;
         const float inv = (i < nn && l_tot > 0.f) ? 1.0f / l_tot : 0.f;
@@ -327,14 +338,14 @@ __device__ __forceinline__ void gs_finish(const AttnArgs &a, Acc O, float m_run,
             a.lse[((size_t)b * a.T + i) * a.Hq + h] = (i < nn) ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : 0.f;
     } else {
         // Partial result of this key range: the row's output normalised by its own l and by the row's
-        // largest magnitude, as fp16 pairs (d, d+1) -- [D/2][64 rows] words, so that 32 lanes still write
-        // 128 contiguous bytes -- plus (m, l, magnitude) in fp32.  The partials of all ranges together
+        // largest magnitude, as fp16 -- [D/8][32 rows][8 d], so that a wavefront's 8-byte stores cover 512
+        // contiguous bytes and the merge reads 16 bytes per lane -- plus (m, l, magnitude) in fp32.  The partials of all ranges together
         // outweigh the K/V bytes, and writing them is what the tail of this kernel waits for; halving
         // them costs 2^-11 of the row's largest element in precision, an eighth of the bf16 rounding of
         // the final output.  Written through: nothing is left dirty in L2 for the end of the kernel.
-        const size_t unit = ((size_t)b * a.Hq + h) * a.max_splits + sp;
-        uint32_t *po = a.part_o + unit * (size_t)(D / 2 * 64);
-        float *pml = a.part_ml + unit * 192;
+        const int j32 = i & 31;
+        uint64_t *po = a.part_o + (size_t)entry * (D / 4 * 32);
+        float *pml = a.part_ml + (size_t)entry * 96;
         const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
         float amax = 0.f;
 #pragma unroll
@@ -347,17 +358,17 @@ __device__ __forceinline__ void gs_finish(const AttnArgs &a, Acc O, float m_run,
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int rp = 0; rp < 8; ++rp) {
-                const int r = 2 * rp;
-                const int d = 32 * db + 8 * (r >> 2) + 4 * g2 + (r & 3);
-                const _Float16 lo = (_Float16)(O(db, r) * scl), hi = (_Float16)(O(db, r + 1) * scl);
-                const uint32_t word = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
-                store_shared_result(&po[(d >> 1) * 64 + i], word);
+            for (int r4 = 0; r4 < 4; ++r4) {                     // d = 32 * db + 8 * r4 + 4 * g2 + 0..3
+                uint64_t four = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    four |= (uint64_t)__builtin_bit_cast(uint16_t, (_Float16)(O(db, 4 * r4 + e) * scl)) << (16 * e);
+                store_shared_result(&po[((4 * db + r4) * 32 + j32) * 2 + g2], four);
             }
         if (g2 == 0) {
-            store_shared_result(&pml[i], m_run);
-            store_shared_result(&pml[64 + i], l_tot);
-            store_shared_result(&pml[128 + i], mag);
+            store_shared_result(&pml[j32], m_run);
+            store_shared_result(&pml[32 + j32], l_tot);
+            store_shared_result(&pml[64 + j32], mag);
         }
     }
 }
@@ -469,7 +480,99 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(AttnArgs a) {
         for (int t = 0; t < ntiles; ++t) step(t, regs0, 2);
     }
     if (!active) return;
-    gs_finish<D>(a, [&](int db, int r) { return oacc[db][0][r]; }, m_run[0], l_run[0], b, h, i, nn, sp, nsplit);
+    gs_finish<D>(a, [&](int db, int r) { return oacc[db][0][r]; }, m_run[0], l_run[0], b, h, i, nn, nsplit == 1,
+                 (((b * a.Hkv + hk) * a.max_splits + sp) * a.n_ublk + ublk) * kGsWaves + w);
+}
+
+// ===================================================================== dealing the rows out on the device
+// The work of a launch over long ranges is one line of pairs of tiles: sequence by sequence, KV head by
+// KV head, pair by pair, each with the time it takes.  It is cut into equal shares, one per workgroup,
+// wherever the cuts fall; a workgroup takes the pieces of its share one after the other and leaves a
+// partial result for each.  With a range of rows per workgroup fixed on the host by the longest
+// sequence, a batch lasts as long as that sequence's ranges while the workgroups of the others have
+// long left: 16 sequences of 700 ... 8192 rows (8 KV heads, 4 query heads each) took 121 us that way and
+// take 80 us this way, 11 of them in the merge of their 380 pieces; what is left of the imbalance is the
+// granule of a pair (4.5 us with the whole chip at work).
+// All of it in units of an eighth of a full tile.
+constexpr int kTileCost = 8;               // a tile for eight units
+constexpr int kTileCostHalf = 5;             // for half of them: the pair is shared by two wavefronts per unit; the loads stay
+constexpr int kUnitCost = 20;               // query rows, ancestor words and partials of a unit's first piece
+constexpr int kFlatMaxB = kWave;           // one lane per sequence
+
+struct FlatPlan {                          // lane = sequence
+    int L, nn, pairs, cost, start, len;    // cost: of a tile; start: where the sequence's KV heads begin on the line, len each
+    int total, share, unit;                // of the line; what a unit costs besides its tiles; the same in every lane
+};
+
+// Blocks of 32 rows that a sequence's tree fills, and whether two wavefronts share a unit's keys: where the
+// tree is small enough that only half of the launch's wavefronts have a unit, the other half takes every
+// second tile (all units in one workgroup) or the second half of the piece (units in half of the workgroups).
+__device__ __forceinline__ int flat_row_blocks(const AttnArgs &a, int nn) { return nn <= 32 ? 1 : a.nqb; }
+__device__ __forceinline__ bool flat_shared(const AttnArgs &a, int nn) {
+    const int units = a.G * flat_row_blocks(a, nn);
+    return a.n_ublk == 1 ? units * 2 <= kGsWaves : (a.n_ublk & 1) == 0 && units * 2 == kGsWaves * a.n_ublk;
+}
+
+__device__ __forceinline__ FlatPlan flat_plan(const AttnArgs &a) {
+    FlatPlan f;
+    const int lane = lane_id(), b = min(lane, a.B - 1);
+    f.L = a.ctx_lens[b];
+    f.nn = a.n_nodes ? a.n_nodes[b] : a.T;
+    f.nn = max(1, min(f.nn, a.T));
+    const int rows = min(f.L + f.nn, a.S);
+    const int tiles = (lane < a.B && f.L >= 0) ? (rows + kKT - 1) / kKT : 0;
+    f.pairs = (tiles + 1) / 2;
+    f.cost = flat_shared(a, f.nn) ? kTileCostHalf : kTileCost;
+    f.unit = kUnitCost;
+    f.len = tiles > 0 ? kUnitCost + tiles * f.cost : 0;
+    const uint32_t mine = (uint32_t)(f.len * a.Hkv);
+    const uint32_t incl = wave_scan_u32(mine);
+    f.start = (int)(incl - mine);
+    f.total = (int)readlane_u32(incl, kWave - 1);
+    // Every piece of a unit costs writing and merging a partial, about 0.3 of a tile's time; with p pairs
+    // per unit and s pairs per piece, s + 0.15 p / s is least at s = sqrt(0.15 p).
+    const int most = (int)wave_max_u32((uint32_t)f.pairs);
+    const int least = max(2 * kTileCost * (int)(__builtin_amdgcn_sqrtf(0.15f * (float)most) + 0.5f), kUnitCost + 2 * kTileCost);
+    // total / shares rounded up (exactly so below 2^24; never less)
+    f.share = max((int)__umulhi((uint32_t)(f.total + a.shares - 1), a.shares_inv), least);
+    // Equal sequences: whole pieces, as long as they are not longer than a share with one more beginning in it.
+    const int len0 = (int)readlane_u32((uint32_t)f.len, 0) - kUnitCost;
+    if (a.per_unit > 0 && __ballot(lane < a.B && f.len - kUnitCost != len0) == 0 && len0 > 0) {
+        const int whole = max((len0 + a.per_unit - 1) / a.per_unit, least);
+        if (whole <= f.share + kUnitCost) {
+            f.share = whole;
+            f.unit = 0;
+            f.len = lane < a.B ? (len0 + whole - 1) / whole * whole : 0;
+            f.start = lane * a.Hkv * f.len;
+            f.total = a.B * a.Hkv * (int)readlane_u32((uint32_t)f.len, 0);
+        }
+    }
+    return f;
+}
+
+struct FlatUnit { int b, hk, start, pairs, cost, len, unit; };     // one sequence's KV head on the line
+
+__device__ __forceinline__ FlatUnit flat_unit(const AttnArgs &a, const FlatPlan &f, int pos) {
+    const uint64_t before = __ballot(f.len > 0 && f.start <= pos);
+    FlatUnit u;
+    u.unit = f.unit;
+    u.b = 63 - __clzll((long long)before);
+    const int base = (int)readlane_u32((uint32_t)f.start, u.b);
+    u.len = (int)readlane_u32((uint32_t)f.len, u.b);
+    u.pairs = (int)readlane_u32((uint32_t)f.pairs, u.b);
+    u.cost = (int)readlane_u32((uint32_t)f.cost, u.b);
+    u.hk = __popcll(__ballot(lane_id() < a.Hkv && base + lane_id() * u.len <= pos)) - 1;    // at most 64 KV heads
+    u.start = base + u.hk * u.len;
+    return u;
+}
+// The share that holds a pair's middle (its first tile's end: the second may be missing) takes it; the
+// unit's own cost goes with its first pair.
+__device__ __forceinline__ int flat_middle(const FlatUnit &u, int j) { return u.start + u.unit + (2 * j + 1) * u.cost - 1; }
+// first pair whose middle is not before pos
+__device__ __forceinline__ int flat_pair_at(const FlatUnit &u, int pos) {
+    const uint32_t x = (uint32_t)max(pos - flat_middle(u, 0), 0);
+    const uint32_t j = u.cost == kTileCost ? (x + 2 * kTileCost - 1) / (2 * kTileCost) : (x + 2 * kTileCostHalf - 1) / (2 * kTileCostHalf);
+    return min(u.pairs, (int)j);
 }
 
 // ===================================================================== group-share kernel, long ranges
@@ -545,7 +648,8 @@ __device__ __forceinline__ void ld_issue_tile(unsigned char *buf, const __bf16 *
     }
 }
 
-template <int D>
+// FLAT: the rows are dealt out on the device; otherwise one fixed range of kps rows per workgroup.
+template <int D, bool FLAT>
 __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
     constexpr int DB = D / 32;
     constexpr int TILE = 2 * kKT * D * 2;   // one K tile ([64][D] bf16, swizzled) + one V tile (row-major, swizzled)
@@ -553,70 +657,91 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
     int *s_par = reinterpret_cast<int *>(smem + kLdBufs * TILE);
 
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-    const int sp = blockIdx.x;
-    // The blocks of units that share a range of cache rows are ranges x KV heads apart in workgroup number:
-    // a multiple of eight with eight KV heads, and consecutive numbers go to consecutive XCDs, so the
-    // blocks meet in one XCD's L2 and their rows come from HBM once.
-    const int hk = blockIdx.y, ublk = blockIdx.z % a.n_ublk;
-    const int b = blockIdx.z / a.n_ublk;
-    const int L = a.ctx_lens[b];
-    int nn = a.n_nodes ? a.n_nodes[b] : a.T;
-    nn = max(1, min(nn, a.T));
-    const int total = min(L + nn, a.S);                  // never read past the cache the caller described
-    const int kbeg = sp * a.kps;
-    if (L < 0 || kbeg >= total) return;
-    const int kend = min(total, kbeg + a.kps);
-    const int nsplit = (total + a.kps - 1) / a.kps;
-
-    const int u = ublk * kGsWaves + w;                    // (head within the group, block of 32 rows)
-    const int g = u / a.nqb, qb = u % a.nqb;
-    const bool active = g < a.G;
-    const int h = hk * a.G + (active ? g : 0);
     const int j32 = lane & 31, g2 = lane >> 5;
-    const int i = 32 * qb + j32;                          // this lane's tree row
-
-    const __bf16 *kbase = a.k + (size_t)b * a.kv_sb + (size_t)hk * a.kv_sh;
-    const __bf16 *vbase = a.v + (size_t)b * a.kv_sb + (size_t)hk * a.kv_sh;
     const int kv_ss = (int)a.kv_ss;          // 32-bit offsets inside one head's cache (checked on the host)
-    const int ntiles = (kend - kbeg + kKT - 1) / kKT;
+    // The blocks of units that share a range of cache rows are a multiple of eight apart in workgroup
+    // number (256 / n_ublk shares; ranges x KV heads with eight KV heads), and consecutive numbers go to
+    // consecutive XCDs, so the blocks meet in one XCD's L2 and their rows come from HBM once.
+    const int ublk = FLAT ? (int)blockIdx.z : (int)(blockIdx.z % a.n_ublk);
+
+    // a piece: tiles [t0, t1) of one sequence's KV head
+    struct Piece {
+        int b, hk, L, nn, kend;               // kend: end of the rows that count
+        int t0, t1, slot;
+        bool direct;
+    };
+    FlatPlan f;
+    int pos = 0, end = 0;                     // what is left of this workgroup's share
+    auto next_piece = [&](Piece &p) -> bool { // the first piece of [pos, end); all values the same in every lane
+        while (pos < end) {
+            const FlatUnit u = flat_unit(a, f, pos);
+            const int j0 = flat_pair_at(u, pos), j1 = flat_pair_at(u, end);
+            const bool whole = j0 == 0 && j1 == u.pairs;
+            pos = u.start + u.len;
+            if (j0 >= j1) continue;
+            p.b = u.b; p.hk = u.hk;
+            p.L = (int)readlane_u32((uint32_t)f.L, u.b);
+            p.nn = (int)readlane_u32((uint32_t)f.nn, u.b);
+            p.kend = min(p.L + p.nn, a.S);                    // never read past the cache the caller described
+            p.t0 = 2 * j0;
+            p.t1 = min(2 * j1, (p.kend + kKT - 1) / kKT);
+            p.slot = (int)blockIdx.x + u.b * a.Hkv + u.hk;
+            p.direct = whole && !flat_shared(a, p.nn) && flat_row_blocks(a, p.nn) == a.nqb;
+            if (j0 == 0 && ublk == 0 && tid == 0) {           // for the merge (whose time is short; it does not plan again)
+                const int pieces = flat_middle(u, u.pairs - 1) / f.share - (int)blockIdx.x + 1;
+                a.unit_tab[u.b * a.Hkv + u.hk] = (uint64_t)(uint32_t)p.slot | (uint64_t)(uint32_t)(p.direct ? 0 : pieces) << 32;
+            }
+            return true;
+        }
+        return false;
+    };
+    Piece pc;
+    if constexpr (FLAT) {
+        f = flat_plan(a);
+        pos = (int)blockIdx.x * f.share;
+        end = min(pos + f.share, f.total);
+        if (!next_piece(pc)) return;
+    } else {
+        const int sp = blockIdx.x;
+        pc.b = blockIdx.z / a.n_ublk; pc.hk = blockIdx.y;
+        pc.L = a.ctx_lens[pc.b];
+        pc.nn = a.n_nodes ? a.n_nodes[pc.b] : a.T;
+        pc.nn = max(1, min(pc.nn, a.T));
+        const int total = min(pc.L + pc.nn, a.S);
+        if (pc.L < 0 || sp * a.kps >= total) return;
+        pc.kend = min(total, (sp + 1) * a.kps);
+        pc.t0 = sp * (a.kps / kKT);
+        pc.t1 = (pc.kend + kKT - 1) / kKT;
+        pc.slot = (pc.b * a.Hkv + pc.hk) * a.max_splits + sp;
+        pc.direct = total <= a.kps;
+    }
+    // Shared keys with the units in half of the workgroups: the other half takes the second half of the
+    // piece's pairs (and, where there is one pair only, the same rows with none of them allowed).
+    auto own_half = [&](Piece &p) {
+        if (!FLAT || a.n_ublk == 1 || !flat_shared(a, p.nn)) return;
+        const int mid = p.t0 + ((p.t1 - p.t0 + 3) / 4) * 2;
+        if (2 * ublk < a.n_ublk) p.t1 = min(p.t1, mid);
+        else if (mid < p.t1) p.t0 = mid;
+        else p.L = p.nn = p.kend = 0;
+    };
+    // where the loads are, one pair ahead of the arithmetic
+    const __bf16 *kb, *vb;
+    int lt, lt1, lend;                                    // next tile, the piece's end, the row that loads are clamped to
+    auto load_from = [&](const Piece &p) {
+        const size_t at = (size_t)p.b * a.kv_sb + (size_t)p.hk * a.kv_sh;
+        kb = a.k + at; vb = a.v + at;
+        lt = p.t0; lt1 = p.t1; lend = max(p.kend, 1);
+    };
 
     // the first two tiles are requested before anything else: the query rows below are consumed as soon as
     // they arrive, and loads issued behind that wait would start a memory round trip late
     const LdLane ldo = ld_lane_offsets<D>(kv_ss, w, lane);
-    ld_issue_tile<D>(smem, kbase, vbase, kv_ss, kbeg, kend, w, lane, ldo);
-    ld_issue_tile<D>(smem + TILE, kbase, vbase, kv_ss, kbeg + kKT, kend, w, lane, ldo);
-    if (tid < RADAR_T_MAX) s_par[tid] = a.parents[(size_t)b * a.T + min(tid, nn - 1)];
-    bf16x8 qop[D / 16];                                  // row i, d = 16*st + 8*g2 .. +8, for the whole kernel
-    {
-        const __bf16 *qrow = a.q + (size_t)b * a.q_sb + (size_t)h * a.q_sh + (uint32_t)(min(i, a.T - 1) * (int)a.q_st);
-#pragma unroll
-        for (int st = 0; st < D / 16; ++st) {
-            u32x4 raw = *reinterpret_cast<const u32x4 *>(qrow + 16 * st + 8 * g2);
-            and_mask(raw, active && i < a.T);
-            qop[st] = __builtin_bit_cast(bf16x8, raw);
-        }
-    }
-    __syncthreads();                                     // the parents are in LDS
-    uint64_t anc[1];
-    anc[0] = (kend > L && i < nn) ? ancestor_word(s_par, i) : 0ull;
+    own_half(pc);
+    load_from(pc);
+    ld_issue_tile<D>(smem, kb, vb, kv_ss, lt * kKT, lend, w, lane, ldo);
+    ld_issue_tile<D>(smem + TILE, kb, vb, kv_ss, lt * kKT + kKT, lend, w, lane, ldo);
+    lt += 2;
 
-    floatx16 oacc[DB][1];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[db][0][r] = 0.f;
-    float m_run[1] = {kNegBig}, l_run[1] = {0.f};
-
-    // Tiles are taken in pairs, four buffers: while the pair (t, t+1) is consumed from two of them the
-    // loads of the next pair arrive in the other two.  One barrier per pair: it publishes the pair
-    // (every wavefront has waited for its own loads) and tells that nobody reads the previous pair
-    // any more, whose buffers the loads issued right after it overwrite -- issued whether or not the
-    // range still has such tiles (see above).  (Not __syncthreads(): nothing here needs its fence.)
-    // The two wavefronts of a SIMD (w and w + 4) are favoured in turn, one in the first tile of a pair
-    // and the other in the second.  Left alone, the older wavefront wins the arbitration in every
-    // tile and finishes it a third ahead of the other; taking turns measured 3-4 % faster at 16 K
-    // cached rows.  (A barrier per pair without the priorities is slower than one per tile, and
-    // priorities with a barrier per tile change nothing.)
     // Operand addresses: a lane's are the same in every tile up to the tile's place in LDS, so they are
     // kept in registers (eight for K: the XOR swizzle is not additive in the chunk; four for V) and the
     // sub-tile, the step inside the tile and the second tile of a pair are instruction offsets; only the
@@ -633,44 +758,123 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
             va[db] = base + TILE / 2 + vs_off<D>(kv0, d0 >> 3) + (d0 & 7) * 2;
         }
     }
-    floatx16 sacc[2];
-    bf16x8 pk[2][2];
-    auto run_tile = [&](auto second, int t0, bool first) {
-        constexpr int TOFF = decltype(second)::value ? TILE : 0;
-        // sub-tile k % 2: 32 rows on, the same swizzle (32 is a multiple of 16)
-        tile_scores<D>([&](int k) { return (lds_u32x4)(ka[k >> 1] + TOFF + (k & 1) * (32 * D * 2)); }, qop, sacc);
-        tile_softmax<D>(sacc, oacc, m_run[0], l_run[0], anc[0], t0, L, kend, first, a.scale_log2, pk);
-        // step k: output block k % DB, rows 16 * (k / DB) on (a multiple of 4: the same swizzle), hi: 8 rows on
-        tile_pv<D, true>([&](int k, int hi) { return va[k % DB] + TOFF + (k / DB) * (16 * D * 2) + hi * (8 * D * 2); }, pk, oacc);
-    };
-    const int fav = w < kGsWaves / 2 ? 1 : 0;
-    for (int t = 0; t < ntiles; t += 2) {
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        const int half = (t >> 1) & 1;                                     // this pair sits in buffers 2*half, 2*half + 1
-        ld_issue_tile<D>(smem + (2 - 2 * half) * TILE, kbase, vbase, kv_ss, kbeg + (t + 2) * kKT, kend, w, lane, ldo);
-        ld_issue_tile<D>(smem + (3 - 2 * half) * TILE, kbase, vbase, kv_ss, kbeg + (t + 3) * kKT, kend, w, lane, ldo);
-        if (active) {
-            if (fav) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
-            run_tile(std::false_type{}, kbeg + t * kKT, t == 0);
-            if (fav) __builtin_amdgcn_s_setprio(0); else __builtin_amdgcn_s_setprio(1);
-            if (t + 1 < ntiles) run_tile(std::true_type{}, kbeg + (t + 1) * kKT, false);
+    int half = 0;                                         // the current pair sits in buffers 2*half, 2*half + 1
+
+    for (;;) {
+        // which unit this wavefront is: (head within the group, block of 32 rows), and which keys of the piece
+        const int nqb = FLAT ? flat_row_blocks(a, pc.nn) : a.nqb, units = a.G * nqb;
+        const bool by_tile = FLAT && a.n_ublk == 1 && flat_shared(a, pc.nn);     // two wavefronts take a pair's tiles
+        int u = ublk * kGsWaves + w;
+        int odd = 0;                                      // by_tile: 1 if this wavefront takes the second tile of every pair
+        const int entry = (pc.slot * a.n_ublk + ublk) * kGsWaves + w;
+        bool active = u < units;
+        if (FLAT && flat_shared(a, pc.nn)) {
+            active = u < 2 * units;
+            if (by_tile && u >= units) odd = 1;
+            if (u >= units) u -= units;
         }
-        const int step = half ? -2 * TILE : 2 * TILE;                     // the next pair sits in the other two buffers
+        const int g = u / nqb, qb = u % nqb;
+        const int h = pc.hk * a.G + (active ? g : 0);
+        const int i = 32 * qb + j32;                      // this lane's tree row
+        const int L = pc.L, nn = pc.nn, kend = pc.kend;
+
+        if (tid < RADAR_T_MAX) s_par[tid] = a.parents[(size_t)pc.b * a.T + min(tid, max(nn, 1) - 1)];
+        bf16x8 qop[D / 16];                               // row i, d = 16*st + 8*g2 .. +8, for the whole piece
+        {
+            const __bf16 *qrow = a.q + (size_t)pc.b * a.q_sb + (size_t)h * a.q_sh + (uint32_t)(min(i, a.T - 1) * (int)a.q_st);
 #pragma unroll
-        for (int st = 0; st < D / 16; ++st) ka[st] += step;
+            for (int st = 0; st < D / 16; ++st) {
+                u32x4 raw = *reinterpret_cast<const u32x4 *>(qrow + 16 * st + 8 * g2);
+                and_mask(raw, active && i < a.T);
+                qop[st] = __builtin_bit_cast(bf16x8, raw);
+            }
+        }
+        Piece nx;
+        bool more = false;
+        if constexpr (FLAT) {
+            more = next_piece(nx);
+            if (more) own_half(nx);
+        }
+        // the next piece's query rows and parents: brought close by, not kept (a row is two cache lines)
+        uint32_t touched = 0;
+        if (FLAT && more) {
+            const int nq = flat_row_blocks(a, nx.nn);
+            int v = ublk * kGsWaves + w;
+            if (v >= a.G * nq) v -= a.G * nq;
+            const int row = min(32 * (v % nq) + j32, a.T - 1), hd = nx.hk * a.G + min(v / nq, a.G - 1);
+            touched = *reinterpret_cast<const uint32_t *>(a.q + (size_t)nx.b * a.q_sb + (size_t)hd * a.q_sh +
+                                                          (uint32_t)(row * (int)a.q_st + (D / 2) * g2));
+            touched ^= (uint32_t)a.parents[(size_t)nx.b * a.T + min(lane, a.T - 1)];
+        }
+        __syncthreads();                                  // the parents are in LDS
+        uint64_t anc[1];
+        anc[0] = (kend > L && i < nn) ? ancestor_word(s_par, i) : 0ull;
+
+        floatx16 oacc[DB][1];
 #pragma unroll
-        for (int db = 0; db < DB; ++db) va[db] += step;
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[db][0][r] = 0.f;
+        float m_run[1] = {kNegBig}, l_run[1] = {0.f};
+
+        // Tiles are taken in pairs, four buffers: while the pair (t, t+1) is consumed from two of them the
+        // loads of the next pair (the next piece's first, at the end of one) arrive in the other two.
+        // One barrier per pair: it publishes the pair (every wavefront has waited for its own loads) and
+        // tells that nobody reads the previous pair any more, whose buffers the loads issued right after
+        // it overwrite.  (Not __syncthreads(): nothing here needs its fence.)
+        // The two wavefronts of a SIMD (w and w + 4) are favoured in turn, one in the first tile of a pair
+        // and the other in the second.  Left alone, the older wavefront wins the arbitration in every
+        // tile and finishes it a third ahead of the other; taking turns measured 3-4 % faster at 16 K
+        // cached rows.  (A barrier per pair without the priorities is slower than one per tile, and
+        // priorities with a barrier per tile change nothing.)
+        floatx16 sacc[2];
+        bf16x8 pk[2][2];
+        auto run_tile = [&](auto second, int t0) {
+            constexpr int TOFF = decltype(second)::value ? TILE : 0;
+            // sub-tile k % 2: 32 rows on, the same swizzle (32 is a multiple of 16)
+            tile_scores<D>([&](int k) { return (lds_u32x4)(ka[k >> 1] + TOFF + (k & 1) * (32 * D * 2)); }, qop, sacc);
+            tile_softmax<D>(sacc, oacc, m_run[0], l_run[0], anc[0], t0, L, kend, false, a.scale_log2, pk);   // (zeros rescaled once: no second copy of the loop for the first pair)
+            // step k: output block k % DB, rows 16 * (k / DB) on (a multiple of 4: the same swizzle), hi: 8 rows on
+            tile_pv<D, true>([&](int k, int hi) { return va[k % DB] + TOFF + (k / DB) * (16 * D * 2) + hi * (8 * D * 2); }, pk, oacc);
+        };
+        const int fav = w < kGsWaves / 2 ? 1 : 0;
+        auto shift = [&](int by) {
+#pragma unroll
+            for (int st = 0; st < D / 16; ++st) ka[st] += by;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) va[db] += by;
+        };
+        if (FLAT && by_tile) shift(odd * TILE);
+        for (int t = pc.t0; t < pc.t1; t += 2) {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (FLAT && lt >= lt1 && more) load_from(nx);            // (past the last piece: its last rows once more)
+            ld_issue_tile<D>(smem + (2 - 2 * half) * TILE, kb, vb, kv_ss, lt * kKT, lend, w, lane, ldo);
+            ld_issue_tile<D>(smem + (3 - 2 * half) * TILE, kb, vb, kv_ss, lt * kKT + kKT, lend, w, lane, ldo);
+            lt += 2;
+            if (active) {
+                if (fav) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
+                // (an odd wavefront's tile may lie past the end of the range: nothing of it is allowed then)
+                run_tile(std::false_type{}, (t + odd) * kKT);
+                if (fav) __builtin_amdgcn_s_setprio(0); else __builtin_amdgcn_s_setprio(1);
+                if (!by_tile && t + 1 < pc.t1) run_tile(std::true_type{}, (t + 1) * kKT);
+            }
+            shift(half ? -2 * TILE : 2 * TILE);                      // the next pair sits in the other two buffers
+            half ^= 1;
+        }
+        if (FLAT && by_tile) shift(-odd * TILE);
+        asm volatile("" :: "v"(touched));
+        __builtin_amdgcn_s_setprio(0);
+        if (!more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be on its way into LDS at the end
+        if (active) gs_finish<D>(a, [&](int db, int r) { return oacc[db][0][r]; }, m_run[0], l_run[0], pc.b, h, i, nn, pc.direct, entry);
+        if (!more) return;
+        pc = nx;
     }
-    __builtin_amdgcn_s_setprio(0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // nothing may still be on its way into LDS at the end
-    if (!active) return;
-    gs_finish<D>(a, [&](int db, int r) { return oacc[db][0][r]; }, m_run[0], l_run[0], b, h, i, nn, sp, nsplit);
 }
 
 // Merges the group-share kernel's per-split partials.  A workgroup takes one (sequence, query
 // head, 32-wide slice of the head dimension): lane = (tree row i, 8 consecutive d), so that the
-// reads of a d-row of the [D][64] partial are 256 contiguous bytes.  Splits are taken four at a
-// time so that a batch's loads are in flight together.
+// reads of 32 rows are 512 contiguous bytes.  Partials are taken four or
+// eight at a time so that a batch's loads are in flight together.
 template <int D>
 __global__ __launch_bounds__(kAttnThreads) void tree_attn_merge_kernel(AttnArgs a) {
     constexpr int SL = 32, DQ = 8;                          // slice width, floats per lane
@@ -678,14 +882,29 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_merge_kernel(AttnArgs 
     const int L = a.ctx_lens[b];
     int nn = a.n_nodes ? a.n_nodes[b] : a.T;
     nn = max(1, min(nn, a.T));
-    const int total = min(L + nn, a.S);
-    const int nsplit = (total + a.kps - 1) / a.kps;
-    if (L < 0 || nsplit <= 1) return;                       // the split kernel wrote the result itself
+    const int hk = h / a.G, g = h - hk * a.G;
+    int slot0, count, nqb = a.nqb, shared = 0;              // partials of this head's KV head: consecutive slots, each once or twice
+    if (a.shares > 0) {
+        const uint64_t tab = a.unit_tab[b * a.Hkv + hk];
+        slot0 = (int)(uint32_t)tab;
+        count = (int)(uint32_t)(tab >> 32);
+        if (L < 0 || count == 0) return;                    // the workgroup wrote the result itself
+        nqb = flat_row_blocks(a, nn);
+        shared = flat_shared(a, nn) ? 1 : 0;
+        count <<= shared;
+    } else {
+        const int total = min(L + nn, a.S);
+        count = (total + a.kps - 1) / a.kps;
+        if (L < 0 || count <= 1) return;                    // the split kernel wrote the result itself
+        slot0 = (b * a.Hkv + hk) * a.max_splits;
+    }
 
     const int i = threadIdx.x & 63, part = threadIdx.x >> 6; // query row, which 8 of the slice's 32
     if (i >= a.T) return;
     const int d0 = slice * SL + part * DQ;
-    const size_t unit0 = ((size_t)b * a.Hq + h) * a.max_splits;
+    const int units = a.G * nqb, j32 = i & 31;
+    const int entry0 = slot0 * a.n_ublk * kGsWaves + g * nqb + (nqb == 1 ? 0 : i >> 5);
+    auto entry_of = [&](int n) { return (size_t)(entry0 + (n >> shared) * a.n_ublk * kGsWaves + ((n & shared) ? units : 0)); };
     __bf16 *orow = a.out + (size_t)b * a.o_sb + (size_t)i * a.o_st + (size_t)h * a.o_sh + d0;
     const bool lse_lane = a.lse && slice == 0 && part == 0;
     if (i >= nn) {
@@ -700,27 +919,26 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_merge_kernel(AttnArgs 
     float acc[DQ];
 #pragma unroll
     for (int d = 0; d < DQ; ++d) acc[d] = 0.f;
-    for (int s0 = 0; s0 < nsplit; s0 += 4) {
-        float ms[4], ls[4];
-        uint32_t ow[4][DQ / 2];
+    auto take = [&](auto batch, int s0) {                   // so many partials at a time, all of their loads in flight
+        constexpr int NB = decltype(batch)::value;
+        float ms[NB], l0[NB], ls[NB];
+        u32x4 ow[NB];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int sc = min(s0 + j, nsplit - 1);
-            ms[j] = a.part_ml[(unit0 + sc) * 192 + i];
-            ls[j] = a.part_ml[(unit0 + sc) * 192 + 64 + i] * a.part_ml[(unit0 + sc) * 192 + 128 + i];   // l x magnitude
-            const uint32_t *po = a.part_o + (unit0 + sc) * (size_t)(D / 2 * 64);
-#pragma unroll
-            for (int d = 0; d < DQ / 2; ++d) ow[j][d] = po[((d0 >> 1) + d) * 64 + i];
+        for (int j = 0; j < NB; ++j) {
+            const size_t en = entry_of(min(s0 + j, count - 1));
+            ms[j] = a.part_ml[en * 96 + j32];
+            l0[j] = a.part_ml[en * 96 + 32 + j32];
+            ls[j] = l0[j] * a.part_ml[en * 96 + 64 + j32];   // l x magnitude
+            ow[j] = *reinterpret_cast<const u32x4 *>(a.part_o + en * (size_t)(D / 4 * 32) + ((d0 >> 3) * 32 + j32) * 2);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool valid = s0 + j < nsplit;
+        for (int j = 0; j < NB; ++j) {
+            const bool valid = s0 + j < count;
             const float m = valid ? ms[j] : kNegBig;
             const float Mn = fmaxf(M, m);
             const float aold = __builtin_amdgcn_exp2f(M - Mn);
             const float wnew = valid ? __builtin_amdgcn_exp2f(m - Mn) : 0.f;
-            const float lj = a.part_ml[(unit0 + min(s0 + j, nsplit - 1)) * 192 + 64 + i];
-            lsum = lsum * aold + wnew * lj;
+            lsum = lsum * aold + wnew * l0[j];
             const float wo = wnew * ls[j];                        // the stored rows are o / (l x magnitude)
 #pragma unroll
             for (int d = 0; d < DQ / 2; ++d) {
@@ -731,7 +949,9 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_merge_kernel(AttnArgs 
             }
             M = Mn;
         }
-    }
+    };
+    if (count <= 4) take(std::integral_constant<int, 4>{}, 0);
+    else for (int s0 = 0; s0 < count; s0 += 8) take(std::integral_constant<int, 8>{}, s0);
     const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
     bf16x8 o8;
 #pragma unroll
@@ -742,8 +962,8 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_merge_kernel(AttnArgs 
 
 // ------------------------------------------------------------------ host-side planning
 struct AttnPlan {
-    int kps, max_splits, n_ublk, nqb;
-    size_t off_part_o, off_part_ml, bytes;
+    int kps, max_splits, n_ublk, nqb, shares;
+    size_t off_part_o, off_part_ml, off_tab, bytes;
 };
 
 static AttnPlan plan_attention(const radar_attn_desc *d) {
@@ -772,12 +992,23 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
     }
     p.kps = (int)kps;
     p.max_splits = (int)(((long)d->S_max + kps - 1) / kps);
+    // Long ranges are dealt out on the device, one share per CU and unit block, unless the caller fixed them.
+    // (A lane per sequence and per KV head; positions on the line and partial numbers stay within 32 bits.  Beyond that the
+    // workgroups are many rounds, and the hardware's dispatch evens them out.)
+    p.shares = 0;
+    const long pairs = ((long)d->S_max + 2 * kKT - 1) / (2 * kKT), heads = (long)d->B * d->Hkv;
+    if (d->keys_per_split == 0 && kps >= 8 * kKT && d->D == 128 && d->B <= kFlatMaxB && d->Hkv <= kWave && p.n_ublk <= 16 &&
+        heads * (2 * pairs * kTileCost + kUnitCost) < (1l << 30))
+        p.shares = 256 / p.n_ublk;
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~size_t(255); return o; };
     take(256);                                             // never empty: callers always pass a workspace
-    const size_t units = p.max_splits > 1 ? (size_t)d->B * d->Hq * p.max_splits : 0;
-    p.off_part_o = take(units * 64 * (d->D / 2) * sizeof(uint32_t));
-    p.off_part_ml = take(units * 192 * sizeof(float));
+    // shares and KV heads cut the same line: a piece's slot is the sum of its share's and its head's number
+    const size_t slots = p.shares > 0 ? (size_t)(p.shares + heads) : p.max_splits > 1 ? (size_t)heads * p.max_splits : 0;
+    const size_t entries = slots * p.n_ublk * kGsWaves;
+    p.off_part_o = take(entries * 32 * (d->D / 2) * sizeof(uint32_t));
+    p.off_part_ml = take(entries * 96 * sizeof(float));
+    p.off_tab = take(p.shares > 0 ? heads * sizeof(uint64_t) : 0);
     p.bytes = off;
     return p;
 }
@@ -805,13 +1036,13 @@ extern "C" size_t radar_tree_attention_workspace_bytes(const radar_attn_desc *d)
 template <int D>
 constexpr int gs_smem_bytes() { return 2 * (2 * kKT * D * 2) + RADAR_T_MAX * 4; }
 
-template <int D>
+template <int D, bool FLAT>
 static hipError_t launch_ld(const AttnArgs &a, dim3 grid, hipStream_t s) {
     constexpr int bytes = kLdBufs * (2 * kKT * D * 2) + RADAR_T_MAX * 4;
-    static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_ld_kernel<D>),
+    static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_ld_kernel<D, FLAT>),
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (configured != hipSuccess) return configured;
-    return launch("tree_attn_group_share", tree_attn_ld_kernel<D>, grid, dim3(kGsThreads), bytes, s, a);
+    return launch("tree_attn_group_share", tree_attn_ld_kernel<D, FLAT>, grid, dim3(kGsThreads), bytes, s, a);
 }
 
 template <int D, bool DEEP>
@@ -841,7 +1072,8 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
     a.parents = parents; a.ctx_lens = ctx_lens; a.n_nodes = n_nodes;
     a.out = static_cast<__bf16 *>(out); a.lse = lse_out;
     a.B = d->B; a.T = d->T_max; a.Hq = d->Hq; a.Hkv = d->Hkv; a.G = d->Hq / d->Hkv; a.S = d->S_max;
-    a.kps = p.kps; a.max_splits = p.max_splits; a.n_ublk = p.n_ublk; a.nqb = p.nqb;
+    a.kps = p.kps; a.max_splits = p.max_splits; a.n_ublk = p.n_ublk; a.nqb = p.nqb; a.shares = p.shares;
+    a.shares_inv = p.shares > 0 ? (uint32_t)(((uint64_t(1) << 32) + p.shares - 1) / p.shares) : 0;
     const int64_t D = d->D;
     a.q_sh = d->q_stride_h ? d->q_stride_h : D;
     a.q_st = d->q_stride_t ? d->q_stride_t : D * d->Hq;
@@ -863,20 +1095,24 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
     const float scale = d->softmax_scale != 0.f ? d->softmax_scale : 1.0f / sqrtf((float)d->D);
     a.scale_log2 = scale * kLog2e;
     char *ws = static_cast<char *>(workspace);
-    a.part_o = reinterpret_cast<uint32_t *>(ws + p.off_part_o);
+    a.part_o = reinterpret_cast<uint64_t *>(ws + p.off_part_o);
     a.part_ml = reinterpret_cast<float *>(ws + p.off_part_ml);
+    a.per_unit = p.shares / (d->B * d->Hkv);
+    a.unit_tab = reinterpret_cast<uint64_t *>(ws + p.off_tab);
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 block(kAttnThreads);
     if ((long)a.B * a.n_ublk > 65535) return RADAR_UNSUPPORTED_SHAPE;
-    const dim3 grid((unsigned)a.max_splits, (unsigned)a.Hkv, (unsigned)(a.B * a.n_ublk));
+    const dim3 grid = p.shares > 0 ? dim3((unsigned)p.shares, 1, (unsigned)p.n_ublk)
+                                   : dim3((unsigned)a.max_splits, (unsigned)a.Hkv, (unsigned)(a.B * a.n_ublk));
     {
         hipError_t e;
-        if (p.kps >= 8 * kKT) e = d->D == 128 ? launch_ld<128>(a, grid, s) : launch_gs<64, true>(a, grid, s);
+        if (p.shares > 0)     e = launch_ld<128, true>(a, grid, s);
+        else if (p.kps >= 8 * kKT) e = d->D == 128 ? launch_ld<128, false>(a, grid, s) : launch_gs<64, true>(a, grid, s);
         else                  e = d->D == 128 ? launch_gs<128, false>(a, grid, s) : launch_gs<64, false>(a, grid, s);
         if (e != hipSuccess) return RADAR_HIP_ERROR;
     }
-    if (a.max_splits > 1) {
+    if (a.max_splits > 1 || p.shares > 0) {
         const dim3 mgrid((unsigned)(a.Hq * (d->D / 32)), (unsigned)a.B);
         const hipError_t e = d->D == 128 ? launch("tree_attn_merge", tree_attn_merge_kernel<128>, mgrid, block, 0, s, a)
                                          : launch("tree_attn_merge", tree_attn_merge_kernel<64>, mgrid, block, 0, s, a);

@@ -116,6 +116,45 @@ def test_long_ranges_match_oracle(oracle, name, kps):
         assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)
 
 
+def _ragged(seed, B, hi, T):
+    rng = np.random.default_rng(seed)
+    nodes = [int(v) for v in rng.integers(1, T + 1, B)]
+    ctx = [int(v) for v in rng.integers(0, hi + 1, B)]
+    ctx[B // 2] = hi
+    return ctx, nodes, [min(8, max(1, n - 1)) for n in nodes]
+
+
+DEALT_CASES = {                                   # name: B, Hq, Hkv, T, longest prefix, equal lengths
+    "group_of_4": (33, 32, 8, 60, 700, False),                # trees on both sides of one block of 32 rows
+    "one_head_per_kv_head": (64, 4, 4, 20, 640, False),       # one unit: two wavefronts share its keys
+    "group_of_8_two_unit_blocks": (17, 64, 8, 64, 900, False),    # small trees: the unit blocks share a piece
+    "group_of_12_three_unit_blocks": (22, 48, 4, 40, 500, False),
+    "many_pieces_per_head": (3, 8, 2, 33, 9000, False),       # more partials than one batch of the merge
+    "equal_lengths": (5, 16, 8, 40, 3000, True),              # whole pieces
+    "one_sequence": (1, 8, 8, 60, 5000, True),
+}
+
+
+@pytest.mark.parametrize("name", list(DEALT_CASES))
+def test_rows_dealt_out_on_the_device(oracle, name):
+    """Long ranges that the caller does not fix are cut into shares on the device: pieces that begin and end
+    anywhere, several pieces per workgroup, heads cut into many, idle workgroups, and trees that fill half of
+    the wavefronts, whose keys are then shared."""
+    from paper_2512_14069_amd import binding as b
+    B, Hq, Hkv, T, hi, equal = DEALT_CASES[name]
+    ctx, nodes, depth = ([hi] * B, [T] * B, [8] * B) if equal else _ragged(len(name), B, hi, T)
+    a = shape(B, Hq, Hkv, 128, T, ctx, nodes, depth, k=10)
+    x = synth.attention_inputs(a, seed=synth.seed_for(1, 11 * len(name)), shuffle=True)
+    ref, ref_lse = oracle.tree_attention(x["q"], x["k_cache"], x["v_cache"], x["parents"], x["ctx_lens"],
+                                         x["n_nodes"], want_lse=True)
+    got, lse = run_gpu(b, x, want_lse=True)
+    for bb in range(B):
+        n = a.n_nodes[bb]
+        check_close(got[bb, :n], ref[bb, :n], f"{name} b={bb}")
+        assert np.max(np.abs(lse[bb, :n] - ref_lse[bb, :n])) < LSE_TOL
+        assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)
+
+
 def test_chain_and_star_trees_depth_63(oracle):
     from paper_2512_14069_amd import binding as b
     a = shape(2, 4, 1, 128, 64, [100, 31], [64, 64], [8, 8], k=10)
