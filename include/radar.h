@@ -310,7 +310,8 @@ radar_status radar_accept_length_distribution(const float *target_logits, const 
  * draft_tokens, parents i32 [B,T_max]; n_nodes i32 [B] or NULL; uniforms f32
  * [B,T_max+1].  Nodes whose token or draft row is out of range are skipped.
  * Limits: T_max <= RADAR_T_MAX; V <= 1048576; B * (T_max + Tq) <= 65535;
- *         both temperatures > 0.  Two or three kernels are enqueued.  The shared walk needs its
+ *         both temperatures > 0.  One kernel is enqueued, which reads the rows that
+ *         the walk visits and no others.  The shared walk needs its
  *         B * G workgroups resident together; the library sizes G from the occupancy the runtime
  *         reports for the device (CUs x workgroups per CU) and bounds every wait (about 100 us by
  *         default): where other work keeps some of them from running, the wait ends and the
@@ -320,9 +321,9 @@ typedef struct radar_accept_q_desc {
     int32_t B, T_max, Tq, V, D_max;
     float   temperature, draft_temperature;
     int32_t walk_spin_limit;    /* 0: the library's choice.  The walk of one sequence is shared by several
-                                   workgroups that meet at a counter after every rejection; the wait there is
-                                   bounded, and a sequence whose workgroups gave up is redone by a single one
-                                   (same results).  > 0: polls (about 0.4 us each) before giving up (tests
+                                   workgroups that meet at every node and after every rejection; the wait there
+                                   is bounded, and a sequence whose workgroups gave up is redone by a single one
+                                   (same results).  > 0: polls (about 0.5 us each) before giving up (tests
                                    pass 1 to force that path; the default is 256); < 0: single-workgroup
                                    walk only */
 } radar_accept_q_desc;

@@ -1,30 +1,37 @@
 // radar_verify_accept_q: verification with draft distributions (Sec. 3, Eq. 1-2), for trees
 // whose tokens were drawn from the draft model's distributions.
 //
-// Two launches, or three when the walk is shared.  (1) Row statistics, spread over the whole chip: one workgroup per 16384
-// logits of every target row and every draft row streams its chunk once and leaves (max, sum
-// of exp) partials; the workgroup that completes a row (arrival ticket) merges them into the
-// row's normaliser.  This is the HBM-bound part: it reads every logit once.  (2) The walk, one
-// workgroup per sequence: sequential by nature (Eq. 1 is applied child by child, Eq. 2 changes
-// the distribution every later test sees).  Every rejection is one vocabulary-wide pass of the
-// workgroup that turns the unnormalised residual u into max(0, u - W q) (W = sum u), keeps it
-// in a workspace row and leaves sums per 256 tokens in LDS; the bonus token is then found from
-// those sums without another pass.  A walk that ends without a rejection draws the bonus from
-// the row's chunk partials and one 16384-token chunk.  Where the chip has room the walk of a
-// sequence is shared by up to 32 workgroups instead (further down), followed by a launch that
-// redoes, with one workgroup, any sequence whose workgroups could not meet.
+// One launch.  The walk is sequential by nature (Eq. 1 is applied child by child, Eq. 2 changes the
+// distribution every later test sees), and it visits few rows: the target rows on the accepted path and
+// the draft rows of the children it tests.  Only those are read.  (Taking every row's normaliser first,
+// with the whole chip, read 62 MB at 61 + 61 rows of V = 128256 and was 17 of a call's 42 us; the walk
+// that followed read its rows again.)
+//
+// The walk of a sequence is shared by up to 32 workgroups, each of which holds a slice of the rows at hand
+// in registers; after every row and every rejection they meet and exchange a few numbers each.  What
+// bounds a call is that chain: rows from HBM (about 2 us, requested one node ahead) and a meeting (about
+// 1.5 us) per node and per rejection.  Where the chip has no room for several workgroups per sequence,
+// and where workgroups of a sequence could not meet, one workgroup walks alone: every rejection is then a
+// vocabulary-wide pass that turns the unnormalised residual u into max(0, u - W q) (W = sum u), keeps it
+// in a workspace row and leaves sums per 256 tokens in LDS, from which the bonus token is found.
+#include <type_traits>
+
 #include "radar_device.h"
 #include "radar_host.h"
 
 namespace radar {
 
-constexpr int kAqThreads = 1024;
-constexpr int kAqWaves = kAqThreads / kWave;
-constexpr int kAqChunk = 16 * kAqThreads;             // logits per workgroup in the statistics launch
-constexpr int kAqMaxChunks = 64;                      // V <= 1,048,576
-constexpr int kAqGran = 4 * kWave;                    // tokens per partial sum in the walk (one wavefront x 16 B)
-constexpr int kAqMaxGran = kAqMaxChunks * kAqChunk / kAqGran;   // 4096
-constexpr int kAqCounterStride = 8;                   // arrival counters 32 B apart
+constexpr int kAqWaves = 8;                           // wavefronts that hold the vocabulary
+constexpr int kAqStream = kAqWaves * kWave;
+constexpr int kAqThreads = kAqStream + kWave;         // and one that meets the other workgroups and decides
+constexpr int kAqAllWaves = kAqWaves + 1;
+constexpr int kAqMaxV = 1 << 20;
+constexpr int kAqGran = 4 * kWave;                    // tokens per partial sum in the lone walk (one wavefront x 16 B)
+constexpr int kAqMaxGran = kAqMaxV / kAqGran;         // 4096
+constexpr int kCoG = 32;                              // most workgroups per sequence
+constexpr int kCoR = 8;                               // most float4 per lane (V <= 32 * 8 * 2048; larger vocabularies walk alone)
+constexpr int kCoCtl = 32;                            // uints per sequence in the control block: leave counter, abort flag at 8, 16
+constexpr int kCoWords = 4;                           // 8-byte words a workgroup brings to a meeting
 
 struct AqArgs {
     const float *target;        // [B][T][V]
@@ -33,20 +40,13 @@ struct AqArgs {
     const int32_t *tokens, *parents, *n_nodes;
     const float *uniforms;      // [B][T+1]
     int32_t *accept_len, *accept_path, *bonus;
-    int B, T, Tq, V, D_max, nchunks;
+    int B, T, Tq, V, D_max;
     double inv_t, inv_td;
-    unsigned int *counters;     // one per row of the statistics launch
-    float *part_m;              // [rows][nchunks] chunk maximum (raw logit)
-    double *part_l;             // [rows][nchunks] sum of exp((x - part_m) * inv_temperature)
-    float *row_m;               // [rows]
-    double *row_l;              // [rows]
-    float *ubuf;                // [B][V] unnormalised residual of the node being verified
-    // walk by several workgroups per sequence
-    unsigned int *co_ctl;       // [B][32]: arrival counter, leave counter, abort flag (each on its own 32 bytes)
-    double *co_psum;            // [B][2][32] slice sums of the last two meetings
-    float *co_sib;              // [B][2][64] residual at the tokens of untried children
-    int co_R;                   // float4 per lane
-    unsigned int co_spin_limit; // polls of the arrival counter before a workgroup gives up
+    float *ubuf;                // [B][V] unnormalised residual of the node being verified (lone walk)
+    unsigned int *co_ctl;       // [B][32]
+    uint64_t *co_words;         // [B][2][32][4] what the workgroups brought to the last two meetings
+    uint64_t *co_sib;           // [B][2][64] residual at the tokens of untried children
+    unsigned int co_spin_limit; // polls of a meeting before a workgroup gives up
 };
 
 // exp((x - m) * inv_temp) with the difference formed in fp64, rounded to fp32 once, and the fp32
@@ -66,109 +66,71 @@ __device__ __forceinline__ double block_sum_f64(double v, double *wred) {
     __syncthreads();
     double t = 0.0;
 #pragma unroll
-    for (int i = 0; i < kAqWaves; ++i) t += wred[i];
+    for (int i = 0; i < kAqAllWaves; ++i) t += wred[i];
     return t;
 }
 
-// rows of the statistics launch: b * (T + Tq) + r, r < T a target row, else draft row r - T
-template <bool VEC4>
-__global__ __launch_bounds__(kAqThreads) void accept_q_stats_kernel(AqArgs a) {
-    __shared__ float wmax[kAqWaves];
-    __shared__ double wred[kAqWaves];
-    __shared__ unsigned int ticket;
-    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-    const int R = blockIdx.y, rows_per_seq = a.T + a.Tq;
-    const int b = R / rows_per_seq, r = R - b * rows_per_seq;
-    const int nn = a.n_nodes ? min(max(a.n_nodes[b], 0), a.T) : a.T;
-    const bool is_target = r < a.T;
-    // rows nothing will read: target rows past the tree, and, when nodes use their own draft
-    // row, the root's and those past the tree
-    if (is_target ? r >= nn : (a.q_rows == nullptr && (r - a.T == 0 || r - a.T >= nn))) return;
-    const float *row = is_target ? a.target + ((size_t)b * a.T + r) * a.V : a.draft + ((size_t)b * a.Tq + (r - a.T)) * a.V;
-    const double inv = is_target ? a.inv_t : a.inv_td;
-    const int base = blockIdx.x * kAqChunk;
-
-    float x[16];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int i0 = base + g * (kAqThreads * 4) + tid * 4;
-        if (VEC4) {
-            const float4 v = *reinterpret_cast<const float4 *>(row + (i0 < a.V ? i0 : 0));
-            x[4 * g] = v.x; x[4 * g + 1] = v.y; x[4 * g + 2] = v.z; x[4 * g + 3] = v.w;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) x[4 * g + j] = row[min(i0 + j, a.V - 1)];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (i0 + j >= a.V) x[4 * g + j] = -INFINITY;
-    }
-    float m = x[0];
-#pragma unroll
-    for (int e = 1; e < 16; ++e) m = fmaxf(m, x[e]);
-    m = wave_max_f32(m);
-    if (lane == 0) wmax[w] = m;
-    __syncthreads();
-    m = wmax[0];
-#pragma unroll
-    for (int i = 1; i < kAqWaves; ++i) m = fmaxf(m, wmax[i]);
-    double l = 0.0;
-    if (m > -INFINITY) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) l += exp_rel(x[e], m, inv);
-    }
-    l = block_sum_f64(l, wred);
-    const size_t slot = (size_t)R * a.nchunks + blockIdx.x;
-    if (tid == 0) {
-        store_shared_result(&a.part_m[slot], m);
-        store_shared_result(&a.part_l[slot], l);
-    }
-    unsigned int *counter = &a.counters[(size_t)R * kAqCounterStride];
-    if (publish_then_ticket(counter, &ticket) != (unsigned int)(a.nchunks - 1)) return;
-    if (w != 0) return;
-    // last chunk of the row: merge the partials (the counter goes back to zero for the next call)
-    float mr = -INFINITY;
-    for (int c = lane; c < a.nchunks; c += kWave) mr = fmaxf(mr, load_shared_result(&a.part_m[(size_t)R * a.nchunks + c]));
-    mr = wave_max_f32(mr);
-    double lr = 0.0;
-    for (int c = lane; c < a.nchunks; c += kWave) {
-        const float mc = load_shared_result(&a.part_m[(size_t)R * a.nchunks + c]);
-        const double lc = load_shared_result(&a.part_l[(size_t)R * a.nchunks + c]);
-        if (mc > -INFINITY) lr += lc * exp(((double)mc - (double)mr) * inv);
-    }
-    lr = wave_sum_f64(lr);
-    if (lane == 0) {
-        a.row_m[R] = mr;
-        a.row_l[R] = lr;
-        store_shared_result(counter, 0u);
-    }
-}
-
-// ------------------------------------------------------------------------------------ walk
+// ------------------------------------------------------------------------ walk by one workgroup
 struct AqSmem {
     double gsum[kAqMaxGran];     // residual mass per 256 tokens (of the last pass)
-    double wred[kAqWaves];
-    double px[kWave], qx[kWave]; // per node: residual at its token under its parent, draft probability of its token
+    double wred[kAqAllWaves];
+    float wmax[kAqAllWaves];
+    double px[kWave];            // per node: residual at its token under its parent
+    float qx[kWave];             // draft logit of its token
     int par[kWave], tok[kWave], qrow[kWave];
     float uni[kWave + 1];
     double W;                    // mass of the residual
     unsigned long long kids;     // untried children of the current node
-    int cur, len, next, have_u, pick, gran;
-    double before;               // residual mass in front of the chosen granule
+    int cur, len, next, have_u;
 };
 
-// One pass over tokens [lo, hi) (lo a multiple of 4096) of sequence b:
+// maximum of a row and sum of exp((x - maximum) * inv) (all threads call it)
+template <bool VEC4>
+__device__ __forceinline__ void row_stats(const AqArgs &a, AqSmem &s, const float *row, double inv, float *m_out, double *l_out) {
+    const int tid = threadIdx.x;
+    float m = -INFINITY;
+    double l = 0.0;
+    for (int pass = 0; pass < 2; ++pass) {
+        if (VEC4) {
+#pragma unroll 4
+            for (int i = tid * 4; i < a.V; i += kAqThreads * 4) {
+                const float4 v = *reinterpret_cast<const float4 *>(row + i);
+                if (pass == 0) m = fmaxf(fmaxf(fmaxf(m, v.x), fmaxf(v.y, v.z)), v.w);
+                else l += (exp_rel(v.x, m, inv) + exp_rel(v.y, m, inv)) + (exp_rel(v.z, m, inv) + exp_rel(v.w, m, inv));
+            }
+        } else {
+#pragma unroll 4
+            for (int i = tid; i < a.V; i += kAqThreads) {
+                if (pass == 0) m = fmaxf(m, row[i]);
+                else l += exp_rel(row[i], m, inv);
+            }
+        }
+        if (pass == 0) {
+            m = wave_max_f32(m);
+            __syncthreads();
+            if (lane_id() == 0) s.wmax[wave_id()] = m;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kAqAllWaves; ++i) m = fmaxf(m, s.wmax[i]);
+        }
+    }
+    *m_out = m;
+    *l_out = block_sum_f64(l, s.wred);
+}
+
+// One pass over tokens [0, hi) of sequence b:
 //   u(i) = have_u ? ubuf[i] : softmax(target row)[i];   u(i) <- max(0, u(i) - W * q(i)) when q is given;
-// u is written to ubuf (as fp32), its sums per 256 tokens to s.gsum[(i - lo) / 256]; returns the total
+// u is written to ubuf (as fp32), its sums per 256 tokens to s.gsum[i / 256]; returns the total
 // of the stored values.  All threads call it.
 template <bool VEC4>
 __device__ __forceinline__ double residual_pass(const AqArgs &a, AqSmem &s, int b, const float *prow, float pm, double pinv_l,
-                                                const float *qrow, float qm, double qinv_l, double W, int lo, int hi) {
+                                                const float *qrow, float qm, double qinv_l, double W, int hi) {
+    constexpr int lo = 0;
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     float *ub = a.ubuf + (size_t)b * a.V;
     const int ngran = (hi - lo + kAqGran - 1) / kAqGran;
     const float it_f = (float)a.inv_t, itd_f = (float)a.inv_td, pinv_l_f = (float)pinv_l, qinv_l_f = (float)qinv_l, W_f = (float)W;
-    constexpr int U = 4;                                             // 4096-token steps whose loads are in flight together
+    constexpr int U = 4;                                             // 2304-token steps whose loads are in flight together
     for (int base0 = lo + tid * 4; base0 - lane * 4 < hi; base0 += U * kAqThreads * 4) {
         float u4[U][4], q4[U][4];
 #pragma unroll
@@ -221,11 +183,13 @@ __device__ __forceinline__ double residual_pass(const AqArgs &a, AqSmem &s, int 
     return block_sum_f64(part, s.wred);
 }
 
-// Inverse CDF by wavefront 0: first token i in [lo, hi) with before0 + sum_{lo..i} u > target, or, if
+// Inverse CDF by wavefront 0: first token i in [0, hi) with sum_{0..i} u > target, or, if
 // the sums never get there (rounding), the last token with u > 0; -1 if there is none.  The sums per
 // 256 tokens are in s.gsum, u itself in ubuf.  Returns the token to every lane of wavefront 0.
 template <bool VEC4>
-__device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, double before0, double target, int lo, int hi) {
+__device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, double target, int hi) {
+    constexpr int lo = 0;
+    constexpr double before0 = 0.0;
     const int lane = lane_id();
     const float *ub = a.ubuf + (size_t)b * a.V;
     const int ngran = (hi - lo + kAqGran - 1) / kAqGran;
@@ -309,7 +273,6 @@ __device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, dou
 template <bool VEC4>
 __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-    const int rows_per_seq = a.T + a.Tq;
     const int nn = a.n_nodes ? min(max(a.n_nodes[b], 0), a.T) : a.T;
     int32_t *path = a.accept_path + (size_t)b * (a.D_max + 1);
     for (int d = tid; d <= a.D_max; d += kAqThreads) path[d] = d == 0 && nn >= 1 ? 0 : -1;
@@ -329,18 +292,19 @@ __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
 
     for (;;) {                                                       // one iteration per visited node; at most T of them
         const int cur = s.cur, len = s.len;
-        const int prow_id = b * rows_per_seq + cur;
         const float *prow = a.target + ((size_t)b * a.T + cur) * a.V;
-        const float pm = a.row_m[prow_id];
-        const double pinv_l = 1.0 / a.row_l[prow_id];
-        // ---- children of cur (ascending node index) and, for each, p(token) and q(token)
+        float pm, qm = 0.f;
+        double pl, ql = 1.0;
+        int q_have = -1;                                             // the draft row whose statistics are at hand
+        row_stats<VEC4>(a, s, prow, a.inv_t, &pm, &pl);
+        const double pinv_l = 1.0 / pl;
+        // ---- children of cur (ascending node index) and, for each, p(token) and its draft logit
         if (w == 0) {
             const int x = s.tok[lane], qr = s.qrow[lane];
             const bool kid = lane > cur && lane < nn && s.par[lane] == cur && len < a.D_max && x >= 0 && x < a.V && qr >= 0 && qr < a.Tq;
             if (kid) {
-                const int qid = b * rows_per_seq + a.T + qr;
                 s.px[lane] = exp_rel(prow[x], pm, a.inv_t) * pinv_l;
-                s.qx[lane] = exp_rel(a.draft[((size_t)b * a.Tq + qr) * a.V + x], a.row_m[qid], a.inv_td) / a.row_l[qid];
+                s.qx[lane] = a.draft[((size_t)b * a.Tq + qr) * a.V + x];
             }
             const unsigned long long kids = __ballot(kid);
             if (lane == 0) { s.kids = kids; s.W = 1.0; s.have_u = 0; s.next = -1; }
@@ -348,20 +312,20 @@ __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
         __syncthreads();
         // ---- Eq. 1 child by child; Eq. 2 after every rejection
         while (s.kids != 0 && s.next < 0 && s.W > 0.0) {
-            const int c = __ffsll((long long)s.kids) - 1;
+            const int c = __ffsll((long long)s.kids) - 1, qr = s.qrow[c];
+            const float *qrow = a.draft + ((size_t)b * a.Tq + qr) * a.V;
+            if (qr != q_have) { row_stats<VEC4>(a, s, qrow, a.inv_td, &qm, &ql); q_have = qr; }
             const double W = s.W;
-            const bool accept = (double)s.uni[c] * W * s.qx[c] < s.px[c];
+            const bool accept = (double)s.uni[c] * W * (exp_rel(s.qx[c], qm, a.inv_td) / ql) < s.px[c];
             __syncthreads();                                         // everyone has read the state of this test
             if (accept) {
                 if (tid == 0) s.next = c;
             } else {
-                const int qr = s.qrow[c], qid = b * rows_per_seq + a.T + qr;
-                const double total = residual_pass<VEC4>(a, s, b, s.have_u ? nullptr : prow, pm, pinv_l,
-                                                         a.draft + ((size_t)b * a.Tq + qr) * a.V, a.row_m[qid], 1.0 / a.row_l[qid],
-                                                         W, 0, a.V);
+                const double total = residual_pass<VEC4>(a, s, b, s.have_u ? nullptr : prow, pm, pinv_l, qrow, qm, 1.0 / ql, W, a.V);
                 // the residual at the tokens of the children still to be tried (written by this workgroup)
                 const unsigned long long rest = s.kids & ~(1ull << c);
                 if (w == 0 && ((rest >> lane) & 1)) s.px[lane] = (double)a.ubuf[(size_t)b * a.V + s.tok[lane]];
+                __syncthreads();
                 if (tid == 0) { s.kids = rest; s.W = total; s.have_u = 1; }
             }
             __syncthreads();
@@ -378,36 +342,12 @@ __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
         }
         // ---- bonus token from the residual (or from p itself when nothing was rejected, or when
         // the residual vanished)
-        const bool use_u = s.have_u && s.W > 0.0;
-        int lo = 0, hi = a.V;
-        double before0 = 0.0, W = s.W;
+        double W = s.W;
+        const bool use_u = s.have_u && W > 0.0;
         __syncthreads();
-        if (!use_u) {
-            // find the 16384-token chunk from the row's partials, then make u = p on that chunk only
-            W = 1.0;
-            const double target = (double)s.uni[a.T] * W;
-            if (w == 0) {
-                double mass = 0.0;
-                if (lane < a.nchunks) {
-                    const float mc = a.part_m[(size_t)prow_id * a.nchunks + lane];
-                    if (mc > -INFINITY) mass = a.part_l[(size_t)prow_id * a.nchunks + lane] * exp(((double)mc - (double)pm) * a.inv_t) * pinv_l;
-                }
-                const double incl = wave_scan_f64(mass);
-                const uint64_t cross = __ballot(lane < a.nchunks && incl > target);
-                const uint64_t has = __ballot(mass > 0.0);
-                const int ch = cross ? __ffsll((long long)cross) - 1 : (has ? 63 - __clzll((long long)has) : 0);
-                const double bef = readlane_f64(incl - mass, ch);
-                if (lane == 0) { s.gran = ch; s.before = bef; }
-            }
-            __syncthreads();
-            lo = s.gran * kAqChunk;
-            hi = min(a.V, lo + kAqChunk);
-            before0 = s.before;
-            residual_pass<VEC4>(a, s, b, prow, pm, pinv_l, nullptr, 0.f, 0.0, 0.0, lo, hi);
-        }
+        if (!use_u) W = residual_pass<VEC4>(a, s, b, prow, pm, pinv_l, nullptr, 0.f, 0.0, 0.0, a.V);
         if (w == 0) {
-            const double target = (double)s.uni[a.T] * W;
-            const int pick = pick_token<VEC4>(a, s, b, before0, target, lo, hi);
+            const int pick = pick_token<VEC4>(a, s, b, (double)s.uni[a.T] * W, a.V);
             if (lane == 0) {
                 a.bonus[b] = pick;
                 a.accept_len[b] = len;
@@ -417,308 +357,463 @@ __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
     }
 }
 
-// only_marked: the launch that follows the shared walk; it redoes the sequences that walk marked
-// (and clears the mark), and leaves the others alone.
 template <bool VEC4>
-__global__ __launch_bounds__(kAqThreads) void accept_q_walk_kernel(AqArgs a, int only_marked) {
+__global__ __launch_bounds__(kAqThreads) void accept_q_walk_kernel(AqArgs a) {
     __shared__ AqSmem s;
-    if (only_marked) {
-        unsigned int *mark = &a.co_ctl[(size_t)blockIdx.x * 32 + 24];
-        const unsigned int m = *mark;                     // written by the previous launch
-        __syncthreads();                                  // everyone has read it
-        if (m == 0u) return;
-        if (threadIdx.x == 0) *mark = 0u;
-    }
     walk_single<VEC4>(a, s, blockIdx.x);
 }
 
 // ------------------------------------------------------------------- walk by several workgroups
-// G workgroups per sequence; workgroup g keeps the residual of tokens [g * slice, (g + 1) * slice) in
-// registers (R float4 per lane) for as long as the walk stays at a node, so a rejection costs each
-// of them one 16-byte load per float4 (its part of the draft row) instead of a vocabulary-wide pass
-// by a single CU.  Every workgroup takes the same decisions from the same numbers: after a
-// rejection each publishes the sum of its slice and the residual at the tokens of the children
-// still to be tried, all meet at an arrival counter, and all add the G sums in the same order.
-// The wait at the counter is bounded: a workgroup that gives up (the workgroups of a sequence
-// were not all resident, which the host avoids by keeping G * B within the chip) raises the
-// sequence's abort flag, everyone leaves, and the last one to leave redoes the sequence alone.
-constexpr int kCoG = 32;                     // most workgroups per sequence
-constexpr int kCoR = 4;                      // most float4 per lane (V <= 32 * 4 * 4096; larger vocabularies walk with one workgroup)
-constexpr int kCoCtl = 32;                   // uints per sequence in the control block: arrive, leave, abort, redo mark at 0, 8, 16, 24
+// G workgroups per sequence; workgroup g holds tokens [g * slice, (g + 1) * slice) of the rows at hand in
+// the registers of eight wavefronts (R float4 per lane and row): the current node's target row, which
+// becomes the residual at the first rejection, the draft row of the child being tested, and, one node
+// ahead, the rows that will be asked for if that child is accepted.  The ninth wavefront does everything
+// that is said and decided: it merges the wavefronts' results, meets the other workgroups and tests the
+// next child.  (It loads no rows: a wavefront's loads return in order, and a poll would wait for them.)
+//
+// Every workgroup takes the same decisions from the same numbers, added in the same order.  At a meeting
+// a workgroup stores up to four 8-byte words, each with the meeting's number in its low byte, and polls
+// all workgroups' words until they carry that number: the values need no counter to vouch for them, no
+// acknowledgement is awaited and nothing is fetched afterwards.  Two sets of words alternate; one is
+// written again only after everyone has read the set after it.
+// The wait is bounded: a workgroup that gives up (the workgroups of a sequence were not all resident,
+// which the host avoids by keeping G * B within the chip) raises the sequence's abort flag, everyone
+// leaves, and the last one to leave redoes the sequence alone.
+enum { kCoAccept, kCoReject, kCoBonusP, kCoBonusU, kCoAbort };
 
 struct CoSmem {
-    double wred[kAqWaves];
-    double psum[kCoG];
-    double px[kWave], qx[kWave];
-    int par[kWave], tok[kWave], qrow[kWave];
-    float uni[kWave + 1];
-    double W;
-    unsigned long long kids;
-    int wlast[kAqWaves];
-    int cur, len, next, aborted, pick;
+    float wm[2][kAqWaves];       // per wavefront: maximum and sum of exponentials of its part of the target / draft row
+    double wl[2][kAqWaves];
+    double wsum[kAqWaves];       // residual mass of its part
+    float gx[kWave], gq[kWave];  // per child of the current node: target and draft logit of its token
+    float pm, pinv_l, qm, qinv_l, W;
+    int cmd, arg;
+    int owner, take_last, pick, wlast[kAqWaves];
+    double before, goal;
+    double wtot[kCoR][kAqWaves];
+    int last, redo;
 };
 
-template <bool VEC4>
+union CoLds {
+    CoSmem s;
+    AqSmem alone;
+};
+
+__device__ __forceinline__ uint64_t word_of_f64(double v, unsigned int tag) { return ((uint64_t)__double_as_longlong(v) & ~0xffull) | tag; }
+__device__ __forceinline__ double f64_of_word(uint64_t w) { return __longlong_as_double((long long)(w & ~0xffull)); }
+__device__ __forceinline__ uint64_t word_of_f32(float v, unsigned int tag) { return ((uint64_t)__float_as_uint(v) << 32) | tag; }
+__device__ __forceinline__ float f32_of_word(uint64_t w) { return __uint_as_float((uint32_t)(w >> 32)); }
+
+template <bool VEC4, int R>
 __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
-    __shared__ CoSmem s;
+    __shared__ CoLds lds;
+    CoSmem &s = lds.s;
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    const bool control = w == kAqWaves;
     const int g = blockIdx.x, G = gridDim.x, b = blockIdx.y;
-    const int R = a.co_R, slice = R * kAqThreads * 4, lo = g * slice;
-    const int rows_per_seq = a.T + a.Tq;
+    constexpr int slice = R * kAqStream * 4;
+    const int lo = g * slice;
     const int nn = a.n_nodes ? min(max(a.n_nodes[b], 0), a.T) : a.T;
     unsigned int *ctl = a.co_ctl + (size_t)b * kCoCtl;
-    double *psum_g = a.co_psum + (size_t)b * 2 * kCoG;    // [2][kCoG]
-    float *sib_g = a.co_sib + (size_t)b * 2 * kWave;      // [2][64]
+    uint64_t *words = a.co_words + (size_t)b * 2 * kCoG * kCoWords;
+    uint64_t *sibs = a.co_sib + (size_t)b * 2 * kWave;
     int32_t *path = a.accept_path + (size_t)b * (a.D_max + 1);
-    unsigned int nsync = 0;
+    const float *target = a.target + (size_t)b * a.T * a.V, *draft = a.draft + (size_t)b * a.Tq * a.V;
 
-    // leave: every workgroup of the sequence ends here.  The last one to arrive clears the control
-    // block for the next call and learns whether anybody gave up on the way (all their stores are
-    // complete by then); if so it marks the sequence for the launch that follows, in which a single
-    // workgroup redoes it.  (Calling that code from here would give this kernel a stack, which
-    // costs every launch 8 us.)
-    auto leave = [&]() {
-        __syncthreads();
-        if (tid == 0) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            const unsigned int before = __hip_atomic_fetch_add(&ctl[8], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (before == (unsigned int)(G - 1)) {
-                store_shared_result(&ctl[24], load_shared_result(&ctl[16]));
-                store_shared_result(&ctl[0], 0u);
-                store_shared_result(&ctl[8], 0u);
-                store_shared_result(&ctl[16], 0u);
-            }
-        }
+    // the tree, one node per lane, in every wavefront
+    const bool live = lane < nn;
+    const int nl = min(lane, a.T - 1);
+    int par = a.parents[(size_t)b * a.T + nl], tok = a.tokens[(size_t)b * a.T + nl];
+    int qrow = a.q_rows ? a.q_rows[(size_t)b * a.T + nl] : lane;
+    const float uni = control ? a.uniforms[(size_t)b * (a.T + 1) + min(lane, a.T)] : 0.f;
+    const float uni_bonus = control ? a.uniforms[(size_t)b * (a.T + 1) + a.T] : 0.f;
+    if (!live) { par = -2; tok = -1; qrow = -1; }
+    const bool usable = live && tok >= 0 && tok < a.V && qrow >= 0 && qrow < a.Tq;
+    auto kids_of = [&](int node, int depth) -> uint64_t {
+        return depth < a.D_max ? __ballot(usable && lane > node && par == node) : 0ull;
     };
-    // meet: publish this workgroup's sum (and whatever the caller stored before), wait for all G,
-    // return the total.  Sets s.aborted when the wait gave up or somebody else did.
-    auto meet = [&](double mine) -> double {
-        const int par = nsync & 1;
-        ++nsync;
-        if (tid == 0) store_shared_result(&psum_g[par * kCoG + g], mine);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0) {
-            __hip_atomic_fetch_add(&ctl[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const unsigned int want = nsync * (unsigned int)G;
-            unsigned int spins = 0;
-            int bad = 0;
-            while (__hip_atomic_load(&ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want) {
-                if (++spins > a.co_spin_limit || load_shared_result(&ctl[16]) != 0u) { bad = 1; break; }
-                __builtin_amdgcn_s_sleep(4);
-            }
-            if (bad) store_shared_result(&ctl[16], 1u);
-            s.aborted = bad;
-        }
-        __syncthreads();
-        if (s.aborted) return 0.0;
-        if (tid < G) s.psum[tid] = load_shared_result(&psum_g[par * kCoG + tid]);
-        __syncthreads();
-        double t = 0.0;
-        for (int i = 0; i < G; ++i) t += s.psum[i];
-        return t;
-    };
+    auto first_of = [](uint64_t m) { return __ffsll((long long)m) - 1; };
+    auto qrow_of = [&](int node) { return (int)readlane_u32((uint32_t)qrow, node); };
 
-    if (tid == 0) s.aborted = load_shared_result(&ctl[16]) != 0u;   // somebody gave up before this workgroup even started
-    if (tid < kWave) {
-        const bool live = tid < nn;
-        s.par[tid] = live ? a.parents[(size_t)b * a.T + tid] : -2;
-        s.tok[tid] = live ? a.tokens[(size_t)b * a.T + tid] : -1;
-        s.qrow[tid] = !live ? -1 : a.q_rows ? a.q_rows[(size_t)b * a.T + tid] : tid;
-        s.uni[tid] = tid <= a.T ? a.uniforms[(size_t)b * (a.T + 1) + tid] : 0.f;
-        if (tid == 0) { s.uni[kWave] = a.T == kWave ? a.uniforms[(size_t)b * (a.T + 1) + kWave] : 0.f; s.cur = 0; s.len = 0; }
-    }
     // Outputs are written through (agent-scope stores): should the sequence be redone by another
     // workgroup, on another die, no older copy of them may linger in this die's L2 to be written back later.
     if (g == 0) for (int d = tid; d <= a.D_max; d += kAqThreads) store_shared_result(&path[d], d == 0 && nn >= 1 ? 0 : -1);
-    __syncthreads();
-    bool fall_back = s.aborted != 0;
-    if (nn < 1) {
+    if (nn < 1) {                                         // nobody meets on this path
         if (g == 0 && tid == 0) { store_shared_result(&a.accept_len[b], 0); store_shared_result(&a.bonus[b], -1); }
-        leave();                                          // nobody meets on this path, so nobody can have given up
         return;
     }
 
     const float it_f = (float)a.inv_t, itd_f = (float)a.inv_td;
-    float u4[kCoR][4];
-    // this lane's tokens: float4 r covers lo + (r * 1024 + tid) * 4 .. + 3
-    auto load_row = [&](const float *row, float m, float inv_l, float inv_temp, float (&out)[kCoR][4]) {
+    // this lane's tokens: float4 r covers lo + (r * 512 + tid) * 4 .. + 3
+    auto load_row = [&](const float *row, float (&x)[R][4]) {
 #pragma unroll
-        for (int r = 0; r < kCoR; ++r) {
-            if (r < R) {
-                const int i0 = lo + (r * kAqThreads + tid) * 4;
-                float x[4];
-                if (VEC4) {
-                    const float4 v = *reinterpret_cast<const float4 *>(row + (i0 < a.V ? i0 : 0));
-                    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-                } else {
+        for (int r = 0; r < R; ++r) {
+            const int i0 = lo + (r * kAqStream + tid) * 4;
+            if (VEC4) {
+                const float4 v = *reinterpret_cast<const float4 *>(row + (i0 < a.V ? i0 : 0));
+                x[r][0] = v.x; x[r][1] = v.y; x[r][2] = v.z; x[r][3] = v.w;
+            } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) x[j] = row[min(i0 + j, a.V - 1)];
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) out[r][j] = (i0 + j < a.V) ? exp_rel_f32(x[j], m, inv_temp) * inv_l : 0.f;
+                for (int j = 0; j < 4; ++j) x[r][j] = row[min(i0 + j, a.V - 1)];
             }
         }
     };
-    auto my_sum = [&]() -> double {
+    // tokens past the vocabulary (in the last slice only) are -inf from here on: no mass in a row, none in a residual
+    auto settle = [&](float (&x)[R][4]) {
+        if (lo + slice <= a.V) return;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[r][j] = lo + (r * kAqStream + tid) * 4 + j < a.V ? x[r][j] : -INFINITY;
+    };
+    auto wave_stats = [&](const float (&x)[R][4], double inv, int which) {
+        float m = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) m = fmaxf(m, x[r][j]);
+        m = wave_max_f32(m);
+        double l = 0.0;
+        if (m > -INFINITY) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) l += inv == 1.0 ? (double)exp_rel_f32(x[r][j], m, 1.f) : exp_rel(x[r][j], m, inv);   // (the same value)
+            }
+        }
+        l = wave_sum_f64(l);
+        if (lane == 0) { s.wm[which][w] = m; s.wl[which][w] = l; }
+    };
+    auto wave_mass = [&](const float (&u)[R][4]) {
         double t = 0.0;
 #pragma unroll
-        for (int r = 0; r < kCoR; ++r)
-            if (r < R) t += ((double)u4[r][0] + (double)u4[r][1]) + ((double)u4[r][2] + (double)u4[r][3]);
-        return block_sum_f64(t, s.wred);
+        for (int r = 0; r < R; ++r) t += ((double)u[r][0] + (double)u[r][1]) + ((double)u[r][2] + (double)u[r][3]);
+        t = wave_sum_f64(t);
+        if (lane == 0) s.wsum[w] = t;
     };
 
-    while (!fall_back) {                                  // one iteration per visited node
-        const int cur = s.cur, len = s.len;
-        const int prow_id = b * rows_per_seq + cur;
-        const float *prow = a.target + ((size_t)b * a.T + cur) * a.V;
-        const float pm = a.row_m[prow_id];
-        const double pinv_l = 1.0 / a.row_l[prow_id];
-        if (w == 0) {
-            const int x = s.tok[lane], qr = s.qrow[lane];
-            const bool kid = lane > cur && lane < nn && s.par[lane] == cur && len < a.D_max && x >= 0 && x < a.V && qr >= 0 && qr < a.Tq;
-            if (kid) {
-                const int qid = b * rows_per_seq + a.T + qr;
-                s.px[lane] = exp_rel(prow[x], pm, a.inv_t) * pinv_l;
-                s.qx[lane] = exp_rel(a.draft[((size_t)b * a.Tq + qr) * a.V + x], a.row_m[qid], a.inv_td) / a.row_l[qid];
-            }
-            const unsigned long long kids = __ballot(kid);
-            if (lane == 0) { s.kids = kids; s.W = 1.0; s.next = -1; }
+    // ---- streaming wavefronts' state
+    constexpr bool kAhead = R <= 2;                       // rows are requested one node ahead (wider slices have no registers left)
+    float x[R][4], q[R][4];                               // target row (logits; after a rejection the residual), draft row
+    bool q_ready = false;                                 // q holds probabilities (else logits)
+    float nx[kAhead ? R : 1][4], nq[kAhead ? R : 1][4], ngx = 0.f, ngq = 0.f;   // one ahead; its children's logits (wavefront 0)
+    auto look_ahead = [&](int node, int depth) {
+        const uint64_t k = kids_of(node, depth);
+        if constexpr (kAhead) {
+            load_row(target + (size_t)node * a.V, nx);
+            if (k != 0) load_row(draft + (size_t)qrow_of(first_of(k)) * a.V, nq);
         }
-        load_row(prow, pm, (float)pinv_l, it_f, u4);      // u = p_cur on this workgroup's slice
-        __syncthreads();
-        bool rejected_here = false;
-        while (s.kids != 0 && s.next < 0 && s.W > 0.0) {
-            const int c = __ffsll((long long)s.kids) - 1;
-            const double W = s.W;
-            const bool accept = (double)s.uni[c] * W * s.qx[c] < s.px[c];
-            __syncthreads();
-            if (accept) {
-                if (tid == 0) s.next = c;
+        if (w == 0 && ((k >> lane) & 1)) {
+            ngx = target[(size_t)node * a.V + tok];
+            ngq = draft[(size_t)qrow * a.V + tok];
+        }
+    };
+    unsigned int meetings = 0;                            // so far
+    // ---- the control wavefront's state (the same in all of its lanes unless said otherwise)
+    double W = 1.0, pl = 1.0, ql = 1.0, px = 0.0, qx = 0.0, psum = 0.0;      // px, qx: lane = node; psum: lane = workgroup
+    float pm = 0.f, qm = 0.f;
+
+    // Maximum and sum of exponentials over the eight wavefronts (lanes 0-7 the target row's, 32-39 the draft
+    // row's), then over the workgroups (lane, lane - 32 = workgroup).  m: -inf where a lane has none.
+    auto half_merge = [&](float m, double l, double inv, float *mo, double *lo_) {
+        float M = m;
+        M = fmaxf(M, dpp_f32<0xB1>(M));
+        M = fmaxf(M, dpp_f32<0x4E>(M));
+        M = fmaxf(M, dpp_f32<0x141>(M));
+        M = fmaxf(M, dpp_f32<0x140>(M));                  // every lane: the maximum of its 16-lane row
+        const float Mp = fmaxf(readlane_f32(M, 0), readlane_f32(M, 16)), Mq = fmaxf(readlane_f32(M, 32), readlane_f32(M, 48));
+        M = lane < 32 ? Mp : Mq;
+        double t = m > -INFINITY ? l * exp(((double)m - (double)M) * inv) : 0.0;
+        auto add = [](double v, uint64_t moved) { return v + __longlong_as_double((long long)moved); };
+        t = add(t, dpp_u64<0xB1>((uint64_t)__double_as_longlong(t)));
+        t = add(t, dpp_u64<0x4E>((uint64_t)__double_as_longlong(t)));
+        t = add(t, dpp_u64<0x141>((uint64_t)__double_as_longlong(t)));
+        t = add(t, dpp_u64<0x140>((uint64_t)__double_as_longlong(t)));
+        const double Lp = readlane_f64(t, 0) + readlane_f64(t, 16), Lq = readlane_f64(t, 32) + readlane_f64(t, 48);
+        *mo = M;
+        *lo_ = lane < 32 ? Lp : Lq;
+    };
+    const double inv_half = lane < 32 ? a.inv_t : a.inv_td;
+    // One meeting.  with_p / with_q: statistics of a target / draft row are exchanged; with_u: residual masses;
+    // rest: children whose tokens' residuals their owners publish.  false: somebody gave up.
+    auto meet = [&](bool with_p, bool with_q, bool with_u, uint64_t rest) -> bool {
+        const unsigned int set = meetings & 1, tag = meetings % 255 + 1;
+        uint64_t *mine = words + ((size_t)set * kCoG + g) * kCoWords;
+        if (with_p || with_q) {
+            const int which = lane >> 5, i = lane & 31;
+            const bool has = i < kAqWaves && (which ? with_q : with_p);
+            const float m0 = s.wm[which][i & (kAqWaves - 1)];
+            const double l0 = s.wl[which][i & (kAqWaves - 1)];
+            float m;
+            double l;
+            half_merge(has ? m0 : -INFINITY, has ? l0 : 0.0, inv_half, &m, &l);
+            if (i == 0 && (which ? with_q : with_p)) {
+                store_shared_result(&mine[2 * which], word_of_f64(l, tag));
+                store_shared_result(&mine[2 * which + 1], word_of_f32(m, tag));
+            }
+        }
+        if (with_u) {
+            double t = 0.0;
+#pragma unroll
+            for (int i = 0; i < kAqWaves; ++i) t += s.wsum[i];
+            if (lane == 0) store_shared_result(&mine[0], word_of_f64(t, tag));
+        }
+        const int from = lane & 31, which = lane >> 5;
+        const uint64_t *theirs = words + ((size_t)set * kCoG + min(from, G - 1)) * kCoWords + 2 * which;
+        const bool first = from < G && (which ? with_q : (with_p || with_u)), second = from < G && (which ? with_q : with_p);
+        const bool sib = (rest >> lane) & 1;
+        uint64_t a0, a1, as;
+        for (unsigned int spins = 0;;) {
+            a0 = load_shared_result(&theirs[0]);
+            a1 = load_shared_result(&theirs[1]);
+            as = load_shared_result(&sibs[set * kWave + lane]);
+            const unsigned int given_up = load_shared_result(&ctl[16]);
+            const bool ok = (!first || (a0 & 0xff) == tag) && (!second || (a1 & 0xff) == tag) && (!sib || (as & 0xff) == tag);
+            if (__ballot(!ok) == 0) break;
+            if (++spins > a.co_spin_limit || given_up != 0u) {
+                if (lane == 0) store_shared_result(&ctl[16], 1u);
+                return false;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        if (with_p || with_q) {
+            float m;
+            double l;
+            half_merge(second ? f32_of_word(a1) : -INFINITY, second ? f64_of_word(a0) : 0.0, inv_half, &m, &l);
+            if (with_p) { pm = readlane_f32(m, 0); pl = readlane_f64(l, 0); }
+            if (with_q) { qm = readlane_f32(m, 32); ql = readlane_f64(l, 32); }
+        }
+        if (with_u) {
+            psum = lane < G ? f64_of_word(a0) : 0.0;
+            W = wave_sum_f64(psum);
+        }
+        if (sib) px = (double)f32_of_word(as);
+        return true;
+    };
+    // Eq. 1 for the next child (qx: used at the child's lane).  What a meeting about rows has changed is passed on
+    // to the streaming wavefronts.
+    auto decide = [&](uint64_t kids, bool was_rejected, bool new_p, bool new_q) {
+        int cmd = was_rejected && W > 0.0 ? kCoBonusU : kCoBonusP, arg = -1;
+        if (new_q) qx = exp_rel(s.gq[lane], qm, a.inv_td) / ql;
+        if (kids != 0 && W > 0.0) {
+            arg = first_of(kids);
+            const uint64_t yes = __ballot((double)uni * W * qx < px);
+            cmd = (yes >> arg) & 1 ? kCoAccept : kCoReject;
+        }
+        if (lane == 0) {
+            s.cmd = cmd; s.arg = arg; s.W = (float)W;
+            if (new_p) { s.pm = pm; s.pinv_l = (float)(1.0 / pl); }
+            if (new_q) { s.qm = qm; s.qinv_l = (float)(1.0 / ql); }
+        }
+    };
+    auto give_up = [&]() { if (lane == 0) s.cmd = kCoAbort; };
+
+    int cur = 0, len = 0, cmd;
+    bool rejected = false;
+    if (!control) look_ahead(0, 0);
+    for (;;) {                                            // one iteration per visited node
+        uint64_t kids = kids_of(cur, len);
+        rejected = false;
+        if (!control) {
+            if constexpr (kAhead) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) { x[r][j] = nx[r][j]; q[r][j] = nq[r][j]; }
             } else {
-                const int qr = s.qrow[c], qid = b * rows_per_seq + a.T + qr;
-                float q4[kCoR][4];
-                load_row(a.draft + ((size_t)b * a.Tq + qr) * a.V, a.row_m[qid], (float)(1.0 / a.row_l[qid]), itd_f, q4);
-                const float W_f = (float)W;
+                load_row(target + (size_t)cur * a.V, x);
+                if (kids != 0) load_row(draft + (size_t)qrow_of(first_of(kids)) * a.V, q);
+            }
+            if (w == 0) { s.gx[lane] = ngx; s.gq[lane] = ngq; }
+            q_ready = false;
+            settle(x);
+            wave_stats(x, a.inv_t, 0);
+            if (kids != 0) {
+                settle(q);
+                wave_stats(q, a.inv_td, 1);
+            }
+        }
+        __syncthreads();
+        if (!control) {
+            if (kids != 0) look_ahead(first_of(kids), len + 1);
+        } else {
+            if (meet(true, kids != 0, false, 0)) {
+                W = 1.0;
+                px = exp_rel(s.gx[lane], pm, a.inv_t) * (1.0 / pl);
+                decide(kids, false, true, kids != 0);
+            } else {
+                give_up();
+            }
+        }
+        ++meetings;
+        __syncthreads();
+        while ((cmd = s.cmd) == kCoReject) {
+            // Eq. 2: u <- max(0, u - W q), then the next child (whose draft row may be another one)
+            const int c = s.arg;
+            kids &= ~(1ull << c);
+            const int next = kids != 0 ? first_of(kids) : -1;
+            const bool other_q = next >= 0 && qrow_of(next) != qrow_of(c);
+            if (!control) {
+                const float m_p = s.pm, il_p = s.pinv_l, m_q = s.qm, il_q = s.qinv_l, W_f = s.W;
+                if (!q_ready) {
 #pragma unroll
-                for (int r = 0; r < kCoR; ++r)
-                    if (r < R) {
+                    for (int r = 0; r < R; ++r)
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) u4[r][j] = fmaxf(0.f, fmaf(-W_f, q4[r][j], u4[r][j]));
-                    }
+                        for (int j = 0; j < 4; ++j) q[r][j] = exp_rel_f32(q[r][j], m_q, itd_f) * il_q;
+                }
+                if (!rejected) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) x[r][j] = exp_rel_f32(x[r][j], m_p, it_f) * il_p;
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[r][j] = fmaxf(0.f, fmaf(-W_f, q[r][j], x[r][j]));
+                q_ready = !other_q;
+                if (other_q) load_row(draft + (size_t)qrow_of(next) * a.V, q);
                 // the residual at the tokens of the children still to be tried: their owners publish it
-                const unsigned long long rest = s.kids & ~(1ull << c);
-                const int par = nsync & 1;
-                for (unsigned long long m = rest; m != 0; m &= m - 1) {
-                    const int c2 = __ffsll((long long)m) - 1;
-                    const int off = s.tok[c2] - lo;
-                    if (off >= 0 && off < slice && ((off >> 2) & (kAqThreads - 1)) == tid) {
-                        const int r2 = off >> 12, j2 = off & 3;                 // float4 index, element
+                for (uint64_t m = kids; m != 0; m &= m - 1) {
+                    const int c2 = first_of(m);
+                    const int off = (int)readlane_u32((uint32_t)tok, c2) - lo;
+                    if (off >= 0 && off < slice && ((off >> 2) & (kAqStream - 1)) == tid) {
+                        const int r2 = off / (kAqStream * 4), j2 = off & 3;      // float4 index, element
                         float val = 0.f;
 #pragma unroll
-                        for (int r = 0; r < kCoR; ++r)
+                        for (int r = 0; r < R; ++r)
 #pragma unroll
                             for (int j = 0; j < 4; ++j)
-                                if (r == r2 && j == j2) val = u4[r][j];
-                        store_shared_result(&sib_g[par * kWave + c2], val);
+                                if (r == r2 && j == j2) val = x[r][j];
+                        store_shared_result(&sibs[(meetings & 1) * kWave + c2], word_of_f32(val, meetings % 255 + 1));
                     }
                 }
-                const double total = meet(my_sum());
-                if (s.aborted) break;
-                if (w == 0 && ((rest >> lane) & 1)) s.px[lane] = (double)load_shared_result(&sib_g[par * kWave + lane]);
-                if (tid == 0) { s.kids = rest; s.W = total; }
-                rejected_here = true;
+                wave_mass(x);
+                if (other_q) { settle(q); wave_stats(q, a.inv_td, 1); }
             }
+            rejected = true;
+            __syncthreads();
+            if (!control) {
+                if (next >= 0) look_ahead(next, len + 1);
+            } else {
+                if (meet(false, other_q, true, kids)) decide(kids, true, false, other_q);
+                else give_up();
+            }
+            ++meetings;
             __syncthreads();
         }
-        if (s.aborted) { fall_back = true; break; }
-        if (s.next >= 0) {
-            if (tid == 0) {
-                const int c = s.next;
-                s.cur = c;
-                s.len = len + 1;
-                if (g == 0) store_shared_result(&path[len + 1], c);
+        if (cmd != kCoAccept) break;
+        cur = s.arg;
+        ++len;
+        if (g == 0 && tid == 0) store_shared_result(&path[len], cur);
+    }
+
+    // ---- bonus token, from the residual, or from p where nothing was rejected or the residual vanished
+    if (cmd == kCoBonusP) {
+        if (!control) {
+            const float m_p = s.pm, il_p = s.pinv_l;
+            if (rejected) { load_row(target + (size_t)cur * a.V, x); settle(x); }   // the residual vanished
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[r][j] = exp_rel_f32(x[r][j], m_p, it_f) * il_p;
             }
-            __syncthreads();
-            continue;
+            wave_mass(x);
         }
-        // ---- bonus token.  Everybody needs the G slice sums of what the bonus is drawn from.
-        double W = s.W;
         __syncthreads();
-        if (!rejected_here || !(W > 0.0)) {               // nothing rejected here, or the residual vanished: draw from p_cur
-            if (rejected_here) load_row(prow, pm, (float)pinv_l, it_f, u4);
-            W = meet(my_sum());
-            if (s.aborted) { fall_back = true; break; }
-        }
-        // (after a rejection s.psum still holds the sums of the last meeting)
-        const double target = (double)s.uni[a.T] * W;
-        int owner = -1, last_pos = -1;
-        double before = 0.0, acc = 0.0;
-        for (int i = 0; i < G; ++i) {
-            if (s.psum[i] > 0.0) last_pos = i;
-            if (owner < 0 && acc + s.psum[i] > target) { owner = i; before = acc; }
-            acc += s.psum[i];
-        }
-        const bool take_last = owner < 0;                 // rounding: the sums never exceed the target
-        if (take_last) owner = last_pos;
-        if (g == 0 && tid == 0) store_shared_result(&a.accept_len[b], len);
-        if (owner < 0) { if (g == 0 && tid == 0) store_shared_result(&a.bonus[b], -1); break; }
-        if (g == owner) {
-            // token order inside the slice: float4 row r, then thread, then element
-            if (tid == 0) s.pick = 0x7fffffff;
-            __syncthreads();
-            double run = before;
-            int lastp = -1;
-            for (int r = 0; r < R; ++r) {                 // uniform; the row is picked by comparison (r is not a constant here)
-                float v[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int rr = 0; rr < kCoR; ++rr)
-                    if (rr == r) { v[0] = u4[rr][0]; v[1] = u4[rr][1]; v[2] = u4[rr][2]; v[3] = u4[rr][3]; }
-                const double lsum = ((double)v[0] + (double)v[1]) + ((double)v[2] + (double)v[3]);
-                const double linc = wave_scan_f64(lsum);
-                if (lane == kWave - 1) s.wred[w] = linc;
-                __syncthreads();
-                double wbefore = run, rtot = 0.0;
-                for (int i = 0; i < kAqWaves; ++i) {
-                    if (i < w) wbefore += s.wred[i];
-                    rtot += s.wred[i];
-                }
-                const int i0 = lo + (r * kAqThreads + tid) * 4;
-                double accl = wbefore + linc - lsum;
-                int pick = -1;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (v[j] > 0.f) lastp = i0 + j;
-                    accl += (double)v[j];
-                    if (pick < 0 && accl > target) pick = i0 + j;
-                }
-                if (pick >= 0 && !take_last) atomicMin(&s.pick, pick);
-                run += rtot;
-                __syncthreads();
+        if (control && !meet(false, false, true, 0)) give_up();
+    }
+    if (cmd != kCoAbort) {
+        if (control) {
+            const double goal = (double)uni_bonus * W, incl = wave_scan_f64(psum);
+            const uint64_t over = __ballot(lane < G && incl > goal), mass = __ballot(psum > 0.0);
+            const int owner = over ? first_of(over) : mass ? 63 - __clzll((long long)mass) : -1;
+            if (lane == 0) {
+                s.owner = owner; s.take_last = over == 0; s.goal = goal;
+                s.pick = 0x7fffffff;
+                if (g == 0) store_shared_result(&a.accept_len[b], len);
+                if (g == 0 && owner < 0) store_shared_result(&a.bonus[b], -1);
             }
+            const double before = incl - psum;
+            if (lane == max(owner, 0)) s.before = before;
+        }
+        __syncthreads();
+        if (s.cmd != kCoAbort && g == s.owner) {
+            // token order inside the slice: float4 row r, then thread, then element
+            double linc[R], lsum[R];
+            if (!control) {
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) lastp = max(lastp, __shfl_xor(lastp, off));
-            if (lane == 0) s.wlast[w] = lastp;
+                for (int r = 0; r < R; ++r) {
+                    lsum[r] = ((double)x[r][0] + (double)x[r][1]) + ((double)x[r][2] + (double)x[r][3]);
+                    linc[r] = wave_scan_f64(lsum[r]);
+                    if (lane == kWave - 1) s.wtot[r][w] = linc[r];
+                    }
+            }
+            __syncthreads();
+            if (!control) {
+                double run = s.before;
+                int lastp = -1;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    double wbefore = run;
+#pragma unroll
+                    for (int i = 0; i < kAqWaves; ++i) {
+                        if (i < w) wbefore += s.wtot[r][i];
+                        run += s.wtot[r][i];
+                    }
+                    const int i0 = lo + (r * kAqStream + tid) * 4;
+                    double acc = wbefore + linc[r] - lsum[r];
+                    int pick = -1;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (x[r][j] > 0.f) lastp = i0 + j;
+                        acc += (double)x[r][j];
+                        if (pick < 0 && acc > s.goal) pick = i0 + j;
+                    }
+                    if (pick >= 0 && !s.take_last) atomicMin(&s.pick, pick);
+                    }
+                lastp = (int)wave_max_u32((uint32_t)(lastp + 1)) - 1;
+                if (lane == 0) s.wlast[w] = lastp;
+            }
             __syncthreads();
             if (tid == 0) {
                 int lp = -1;
+#pragma unroll
                 for (int i = 0; i < kAqWaves; ++i) lp = max(lp, s.wlast[i]);
                 store_shared_result(&a.bonus[b], s.pick != 0x7fffffff ? s.pick : lp);
             }
         }
-        break;
     }
-    (void)fall_back;
-    leave();
+
+    // ---- leave: every workgroup of the sequence ends here.  The last one clears what the next call's
+    // meetings start from, and redoes the sequence if anybody gave up on the way (all their stores are
+    // complete by then).
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) {
+        const unsigned int before = __hip_atomic_fetch_add(&ctl[8], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s.last = before == (unsigned int)(G - 1);
+        s.redo = s.last ? (int)load_shared_result(&ctl[16]) : 0;
+    }
+    __syncthreads();
+    if (!s.last) return;
+    const bool redo = s.redo != 0;
+    for (int i = tid; i < 2 * kCoG * kCoWords; i += kAqThreads) store_shared_result(&words[i], (uint64_t)0);
+    for (int i = tid; i < 2 * kWave; i += kAqThreads) store_shared_result(&sibs[i], (uint64_t)0);
+    if (tid == 0) {
+        store_shared_result(&ctl[8], 0u);
+        store_shared_result(&ctl[16], 0u);
+    }
+    if (!redo) return;
+    __syncthreads();
+    walk_single<VEC4>(a, lds.alone, b);
 }
 
 }  // namespace radar
 
 using namespace radar;
 
-static int aq_chunks(int V) { return (V + kAqChunk - 1) / kAqChunk; }
-
-// How many 1024-lane workgroups of the shared walk the current device can hold at once: the
+// How many workgroups of the shared walk the current device can hold at once: the
 // occupancy the runtime reports for the kernel times the number of CUs (queried once; 0 if the
 // queries fail, which selects the single-workgroup walk).
 static int aq_resident_capacity() {
@@ -726,7 +821,7 @@ static int aq_resident_capacity() {
         int dev = 0, per_cu = 0;
         hipDeviceProp_t prop;
         if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(&accept_q_coop_kernel<true>),
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(&accept_q_coop_kernel<true, kCoR>),
                                                          kAqThreads, 0) != hipSuccess)
             return 0;
         return per_cu * prop.multiProcessorCount;
@@ -743,10 +838,11 @@ static void aq_coop_plan(const radar_accept_q_desc *d, int *G, int *R) {
     const int cap = aq_resident_capacity();
     if (d->walk_spin_limit < 0 || cap < 2 || d->B > cap / 2) return;
     const int gcap = cap / d->B < kCoG ? cap / d->B : kCoG;
-    const int per_wg = kAqThreads * 4;
-    int r = ((d->V + per_wg - 1) / per_wg + gcap - 1) / gcap;              // float4 per lane needed with gcap workgroups
-    if (r > kCoR) return;
-    if (r < 1) r = 1;
+    const int per_wg = kAqStream * 4;
+    const int need = ((d->V + per_wg - 1) / per_wg + gcap - 1) / gcap;     // float4 per lane needed with gcap workgroups
+    if (need > kCoR) return;
+    int r = 1;
+    while (r < need) r *= 2;                                              // compiled for 1, 2, 4 and 8
     const int g = (d->V + per_wg * r - 1) / (per_wg * r);
     if (g < 2) return;                                                    // one workgroup would cover it anyway
     *G = g; *R = r;
@@ -754,16 +850,10 @@ static void aq_coop_plan(const radar_accept_q_desc *d, int *G, int *R) {
 
 extern "C" size_t radar_verify_accept_q_workspace_bytes(const radar_accept_q_desc *d) {
     if (!d || d->B < 1 || d->T_max < 1 || d->Tq < 1 || d->V < 1) return 0;
-    const size_t rows = (size_t)d->B * ((size_t)d->T_max + d->Tq), nch = aq_chunks(d->V);
-    size_t bytes = (rows * kAqCounterStride * sizeof(unsigned int) + 255) & ~size_t(255);
-    bytes += (rows * nch * sizeof(double) + 255) & ~size_t(255);
-    bytes += (rows * nch * sizeof(float) + 255) & ~size_t(255);
-    bytes += (rows * sizeof(double) + 255) & ~size_t(255);
-    bytes += (rows * sizeof(float) + 255) & ~size_t(255);
-    bytes += ((size_t)d->B * d->V * sizeof(float) + 255) & ~size_t(255);
+    size_t bytes = ((size_t)d->B * d->V * sizeof(float) + 255) & ~size_t(255);
     bytes += ((size_t)d->B * kCoCtl * sizeof(unsigned int) + 255) & ~size_t(255);
-    bytes += ((size_t)d->B * 2 * kCoG * sizeof(double) + 255) & ~size_t(255);
-    bytes += ((size_t)d->B * 2 * kWave * sizeof(float) + 255) & ~size_t(255);
+    bytes += ((size_t)d->B * 2 * kCoG * kCoWords * sizeof(uint64_t) + 255) & ~size_t(255);
+    bytes += ((size_t)d->B * 2 * kWave * sizeof(uint64_t) + 255) & ~size_t(255);
     return bytes;
 }
 
@@ -779,8 +869,8 @@ extern "C" radar_status radar_verify_accept_q(const float *target_logits, const 
         !(d->draft_temperature > 0.f))
         return RADAR_INVALID_ARG;
     if (!q_rows && d->Tq != d->T_max) return RADAR_INVALID_ARG;
-    if (d->T_max > RADAR_T_MAX || d->D_max >= RADAR_T_MAX || aq_chunks(d->V) > kAqMaxChunks) return RADAR_UNSUPPORTED_SHAPE;
-    if ((int64_t)d->B * ((int64_t)d->T_max + d->Tq) > 65535) return RADAR_UNSUPPORTED_SHAPE;      // rows ride on gridDim.y
+    if (d->T_max > RADAR_T_MAX || d->D_max >= RADAR_T_MAX || d->V > kAqMaxV) return RADAR_UNSUPPORTED_SHAPE;
+    if ((int64_t)d->B * ((int64_t)d->T_max + d->Tq) > 65535) return RADAR_UNSUPPORTED_SHAPE;
     if (workspace_bytes < radar_verify_accept_q_workspace_bytes(d)) return RADAR_WORKSPACE_TOO_SMALL;
     if (((uintptr_t)workspace & 255) != 0) return RADAR_INVALID_ARG;
 
@@ -788,43 +878,35 @@ extern "C" radar_status radar_verify_accept_q(const float *target_logits, const 
     a.target = target_logits; a.draft = draft_logits; a.q_rows = q_rows;
     a.tokens = draft_tokens; a.parents = parents; a.n_nodes = n_nodes; a.uniforms = uniforms;
     a.accept_len = accept_len; a.accept_path = accept_path; a.bonus = bonus_token;
-    a.B = d->B; a.T = d->T_max; a.Tq = d->Tq; a.V = d->V; a.D_max = d->D_max; a.nchunks = aq_chunks(d->V);
+    a.B = d->B; a.T = d->T_max; a.Tq = d->Tq; a.V = d->V; a.D_max = d->D_max;
     a.inv_t = 1.0 / (double)d->temperature; a.inv_td = 1.0 / (double)d->draft_temperature;
-    const size_t rows = (size_t)d->B * ((size_t)d->T_max + d->Tq), nch = a.nchunks;
     char *ws = static_cast<char *>(workspace);
     auto take = [&](size_t bytes) { char *p = ws; ws += (bytes + 255) & ~size_t(255); return p; };
-    a.counters = reinterpret_cast<unsigned int *>(take(rows * kAqCounterStride * sizeof(unsigned int)));
-    a.part_l = reinterpret_cast<double *>(take(rows * nch * sizeof(double)));
-    a.part_m = reinterpret_cast<float *>(take(rows * nch * sizeof(float)));
-    a.row_l = reinterpret_cast<double *>(take(rows * sizeof(double)));
-    a.row_m = reinterpret_cast<float *>(take(rows * sizeof(float)));
-    a.ubuf = reinterpret_cast<float *>(take((size_t)d->B * d->V * sizeof(float)));
     a.co_ctl = reinterpret_cast<unsigned int *>(take((size_t)d->B * kCoCtl * sizeof(unsigned int)));
-    a.co_psum = reinterpret_cast<double *>(take((size_t)d->B * 2 * kCoG * sizeof(double)));
-    a.co_sib = reinterpret_cast<float *>(take((size_t)d->B * 2 * kWave * sizeof(float)));
+    a.co_words = reinterpret_cast<uint64_t *>(take((size_t)d->B * 2 * kCoG * kCoWords * sizeof(uint64_t)));
+    a.co_sib = reinterpret_cast<uint64_t *>(take((size_t)d->B * 2 * kWave * sizeof(uint64_t)));
+    a.ubuf = reinterpret_cast<float *>(take((size_t)d->B * d->V * sizeof(float)));
     int G = 1, R = 1;
     aq_coop_plan(d, &G, &R);
-    a.co_R = R;
-    // default: 256 polls of about 0.4 us (an atomic load and a short sleep): the workgroups of a walk reach a
+    // default: 256 polls of about 0.5 us (an atomic load and a short sleep): the workgroups of a walk reach a
     // meeting within microseconds of each other, so 100 us without progress means one of them is not running
     a.co_spin_limit = d->walk_spin_limit > 0 ? (unsigned int)d->walk_spin_limit : 256u;
 
     const bool vec4 = (d->V % 4 == 0) && (((uintptr_t)target_logits & 15) == 0) && (((uintptr_t)draft_logits & 15) == 0);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const dim3 g1((unsigned)a.nchunks, (unsigned)rows), g2((unsigned)d->B), block(kAqThreads);
-    hipError_t e = vec4 ? launch("accept_q_stats", accept_q_stats_kernel<true>, g1, block, 0, st, a)
-                        : launch("accept_q_stats", accept_q_stats_kernel<false>, g1, block, 0, st, a);
-    if (e != hipSuccess) return RADAR_HIP_ERROR;
-    if (G > 1) {
-        const dim3 g3((unsigned)G, (unsigned)d->B);
-        e = vec4 ? launch("accept_q_walk_shared", accept_q_coop_kernel<true>, g3, block, 0, st, a)
-                 : launch("accept_q_walk_shared", accept_q_coop_kernel<false>, g3, block, 0, st, a);
-        if (e != hipSuccess) return RADAR_HIP_ERROR;
-        e = vec4 ? launch("accept_q_walk_redo", accept_q_walk_kernel<true>, g2, block, 0, st, a, 1)
-                 : launch("accept_q_walk_redo", accept_q_walk_kernel<false>, g2, block, 0, st, a, 1);
+    const dim3 grid((unsigned)G, (unsigned)d->B), block(kAqThreads);
+    hipError_t e;
+    if (G == 1) {
+        e = vec4 ? launch("accept_q_walk", accept_q_walk_kernel<true>, dim3((unsigned)d->B), block, 0, st, a)
+                 : launch("accept_q_walk", accept_q_walk_kernel<false>, dim3((unsigned)d->B), block, 0, st, a);
     } else {
-        e = vec4 ? launch("accept_q_walk", accept_q_walk_kernel<true>, g2, block, 0, st, a, 0)
-                 : launch("accept_q_walk", accept_q_walk_kernel<false>, g2, block, 0, st, a, 0);
+        auto go = [&](auto r) {
+            constexpr int RR = decltype(r)::value;
+            return vec4 ? launch("accept_q_walk_shared", accept_q_coop_kernel<true, RR>, grid, block, 0, st, a)
+                        : launch("accept_q_walk_shared", accept_q_coop_kernel<false, RR>, grid, block, 0, st, a);
+        };
+        e = R == 1 ? go(std::integral_constant<int, 1>{}) : R == 2 ? go(std::integral_constant<int, 2>{})
+          : R == 4 ? go(std::integral_constant<int, 4>{}) : go(std::integral_constant<int, 8>{});
     }
     return e == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
 }

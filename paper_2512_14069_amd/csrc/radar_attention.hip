@@ -532,7 +532,8 @@ __device__ __forceinline__ FlatPlan flat_plan(const AttnArgs &a) {
     // Every piece of a unit costs writing and merging a partial, about 0.3 of a tile's time; with p pairs
     // per unit and s pairs per piece, s + 0.15 p / s is least at s = sqrt(0.15 p).
     const int most = (int)wave_max_u32((uint32_t)f.pairs);
-    const int least = max(2 * kTileCost * (int)(__builtin_amdgcn_sqrtf(0.15f * (float)most) + 0.5f), kUnitCost + 2 * kTileCost);
+    const int tile = __ballot(f.pairs == most && f.cost == kTileCostHalf) != 0 ? kTileCostHalf : kTileCost;
+    const int least = max(2 * tile * (int)(__builtin_amdgcn_sqrtf(0.15f * (float)most) + 0.5f), kUnitCost + 2 * kTileCost);
     // total / shares rounded up (exactly so below 2^24; never less)
     f.share = max((int)__umulhi((uint32_t)(f.total + a.shares - 1), a.shares_inv), least);
     // Equal sequences: whole pieces, as long as they are not longer than a share with one more beginning in it.

@@ -91,6 +91,17 @@ def test_ragged_batch_matches_oracle(oracle, V, T, shared):
         assert all(np.array_equal(p, q) for p, q in zip(ref[:3], ref2[:3]))
 
 
+@pytest.mark.parametrize("V,B", [(2049, 3), (70004, 18), (70001, 40), (20000, 140)])
+def test_batches_that_leave_few_workgroups_per_sequence(oracle, V, B):
+    """Slices of one, four and eight float4 per lane, and more sequences than workgroups that can meet; rows
+    that end inside a slice, draft rows of the nodes' own (a rejection changes the draft row) and shared ones."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(synth.seed_for(32, V % 1000 + B))
+    x = synth.sampled_draft_inputs(rng, ragged_trees(rng, B, 6, 4, V), V, 6, std=2.0, noise=1.5, shared_rows=B % 4 == 0)
+    ref, got = run_both(oracle, b, x)
+    compare(ref, got)
+
+
 def test_many_rejections_at_one_node_and_the_depth_cut(oracle):
     """A poor draft (independent of the target) under a star: most children are rejected one after the
     other, each rejection one more pass of Eq. 2; then the same trees cut at depth 1 and 0."""
