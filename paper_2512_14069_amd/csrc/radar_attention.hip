@@ -533,7 +533,8 @@ __device__ __forceinline__ FlatPlan flat_plan(const AttnArgs &a) {
     // per unit and s pairs per piece, s + 0.15 p / s is least at s = sqrt(0.15 p).
     const int most = (int)wave_max_u32((uint32_t)f.pairs);
     const int tile = __ballot(f.pairs == most && f.cost == kTileCostHalf) != 0 ? kTileCostHalf : kTileCost;
-    const int least = max(2 * tile * (int)(__builtin_amdgcn_sqrtf(0.15f * (float)most) + 0.5f), kUnitCost + 2 * kTileCost);
+    const float merge = tile == kTileCost ? 0.15f : 0.3f;       // (two partials where keys are shared)
+    const int least = max(2 * tile * (int)(__builtin_amdgcn_sqrtf(merge * (float)most) + 0.5f), kUnitCost + 2 * kTileCost);
     // total / shares rounded up (exactly so below 2^24; never less)
     f.share = max((int)__umulhi((uint32_t)(f.total + a.shares - 1), a.shares_inv), least);
     // Equal sequences: whole pieces, as long as they are not longer than a share with one more beginning in it.
@@ -872,12 +873,16 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
     }
 }
 
-// Merges the group-share kernel's per-split partials.  A workgroup takes one (sequence, query
-// head, 32-wide slice of the head dimension): lane = (tree row i, 8 consecutive d), so that the
-// reads of 32 rows are 512 contiguous bytes.  Partials are taken four or
-// eight at a time so that a batch's loads are in flight together.
-template <int D>
-__global__ __launch_bounds__(kAttnThreads) void tree_attn_merge_kernel(AttnArgs a) {
+// Merges the group-share kernels' partials.  A workgroup takes one (sequence, query head, 32-wide slice
+// of the head dimension): lane = (8 consecutive d, tree row i), rows rounded up to 16, 32 or 64, so that a
+// small tree's rows sit in few wavefronts (four rows, 48 partials: 31 us for the call with 64 lanes per
+// d, 22 with 16).  The time is that of dependent rounds of loads, so a lane asks for four or eight
+// partials at once; where a head is cut into sixteen pieces or more two groups of lanes take every other
+// one and meet in LDS (3 heads of 16000 rows 26.5 -> 24.8 us; with 11 pieces it costs 0.1 us more than it
+// gives, and four groups cost more than two nearly everywhere: a workgroup of 1024 lanes starts late).
+template <int D, int E>
+__global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(AttnArgs a) {
+    __shared__ float red[E > 1 ? E - 1 : 1][10][kAttnThreads];
     constexpr int SL = 32, DQ = 8;                          // slice width, floats per lane
     const int slice = blockIdx.x % (D / SL), h = blockIdx.x / (D / SL), b = blockIdx.y;
     const int L = a.ctx_lens[b];
@@ -900,22 +905,17 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_merge_kernel(AttnArgs 
         slot0 = (b * a.Hkv + hk) * a.max_splits;
     }
 
-    const int i = threadIdx.x & 63, part = threadIdx.x >> 6; // query row, which 8 of the slice's 32
-    if (i >= a.T) return;
+    const int t256 = threadIdx.x & (kAttnThreads - 1), eg = E > 1 ? (int)threadIdx.x / kAttnThreads : 0;
+    const int rbits = a.T > 32 ? 6 : a.T > 16 ? 5 : 4;
+    const int i = t256 & ((1 << rbits) - 1), part = t256 >> rbits;      // query row, which 8 of the slice's 32
+    if (E == 1 && part >= SL / DQ) return;
+    const bool live = i < nn && part < SL / DQ;
     const int d0 = slice * SL + part * DQ;
     const int units = a.G * nqb, j32 = i & 31;
     const int entry0 = slot0 * a.n_ublk * kGsWaves + g * nqb + (nqb == 1 ? 0 : i >> 5);
     auto entry_of = [&](int n) { return (size_t)(entry0 + (n >> shared) * a.n_ublk * kGsWaves + ((n & shared) ? units : 0)); };
     __bf16 *orow = a.out + (size_t)b * a.o_sb + (size_t)i * a.o_st + (size_t)h * a.o_sh + d0;
     const bool lse_lane = a.lse && slice == 0 && part == 0;
-    if (i >= nn) {
-        bf16x8 z;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) z[e] = (__bf16)0.f;
-        *reinterpret_cast<bf16x8 *>(orow) = z;
-        if (lse_lane) a.lse[((size_t)b * a.T + i) * a.Hq + h] = 0.f;
-        return;
-    }
     float M = kNegBig, lsum = 0.f;
     float acc[DQ];
 #pragma unroll
@@ -926,7 +926,7 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_merge_kernel(AttnArgs 
         u32x4 ow[NB];
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-            const size_t en = entry_of(min(s0 + j, count - 1));
+            const size_t en = entry_of(min(s0 + j * E, count - 1));
             ms[j] = a.part_ml[en * 96 + j32];
             l0[j] = a.part_ml[en * 96 + 32 + j32];
             ls[j] = l0[j] * a.part_ml[en * 96 + 64 + j32];   // l x magnitude
@@ -934,7 +934,7 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_merge_kernel(AttnArgs 
         }
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-            const bool valid = s0 + j < count;
+            const bool valid = s0 + j * E < count;
             const float m = valid ? ms[j] : kNegBig;
             const float Mn = fmaxf(M, m);
             const float aold = __builtin_amdgcn_exp2f(M - Mn);
@@ -951,14 +951,38 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_merge_kernel(AttnArgs 
             M = Mn;
         }
     };
-    if (count <= 4) take(std::integral_constant<int, 4>{}, 0);
-    else for (int s0 = 0; s0 < count; s0 += 8) take(std::integral_constant<int, 8>{}, s0);
+    if (live) {
+        if (E > 1 || count <= 4) for (int s0 = eg; s0 < count; s0 += 4 * E) take(std::integral_constant<int, 4>{}, s0);
+        else for (int s0 = 0; s0 < count; s0 += 8) take(std::integral_constant<int, 8>{}, s0);
+    }
+    if constexpr (E > 1) {
+        if (live && eg > 0) {
+            red[eg - 1][0][t256] = M;
+            red[eg - 1][1][t256] = lsum;
+#pragma unroll
+            for (int d = 0; d < DQ; ++d) red[eg - 1][2 + d][t256] = acc[d];
+        }
+        __syncthreads();
+        if (eg > 0) return;
+        if (live) {
+#pragma unroll
+            for (int e = 0; e < E - 1; ++e) {
+                const float m = red[e][0][t256], Mn = fmaxf(M, m);
+                const float aold = __builtin_amdgcn_exp2f(M - Mn), wnew = __builtin_amdgcn_exp2f(m - Mn);
+                lsum = lsum * aold + red[e][1][t256] * wnew;
+#pragma unroll
+                for (int d = 0; d < DQ; ++d) acc[d] = acc[d] * aold + red[e][2 + d][t256] * wnew;
+                M = Mn;
+            }
+        }
+    }
+    if (i >= a.T || part >= SL / DQ) return;
     const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
     bf16x8 o8;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o8[e] = (__bf16)(acc[e] * inv);
+    for (int e = 0; e < 8; ++e) o8[e] = (__bf16)(live ? acc[e] * inv : 0.f);      // rows past the tree are zeroed
     *reinterpret_cast<bf16x8 *>(orow) = o8;
-    if (lse_lane) a.lse[((size_t)b * a.T + i) * a.Hq + h] = (M + __builtin_amdgcn_logf(lsum)) * kLn2;
+    if (lse_lane) a.lse[((size_t)b * a.T + i) * a.Hq + h] = live ? (M + __builtin_amdgcn_logf(lsum)) * kLn2 : 0.f;
 }
 
 // ------------------------------------------------------------------ host-side planning
@@ -1115,8 +1139,12 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
     }
     if (a.max_splits > 1 || p.shares > 0) {
         const dim3 mgrid((unsigned)(a.Hq * (d->D / 32)), (unsigned)a.B);
-        const hipError_t e = d->D == 128 ? launch("tree_attn_merge", tree_attn_merge_kernel<128>, mgrid, block, 0, s, a)
-                                         : launch("tree_attn_merge", tree_attn_merge_kernel<64>, mgrid, block, 0, s, a);
+        const bool many = p.shares >= 16l * d->B * d->Hkv;          // sixteen pieces per head or more
+        const dim3 block2(kAttnThreads * 2);
+        const hipError_t e = d->D == 128 ? (many ? launch("tree_attn_merge", tree_attn_merge_kernel<128, 2>, mgrid, block2, 0, s, a)
+                                                 : launch("tree_attn_merge", tree_attn_merge_kernel<128, 1>, mgrid, block, 0, s, a))
+                                         : (many ? launch("tree_attn_merge", tree_attn_merge_kernel<64, 2>, mgrid, block2, 0, s, a)
+                                                 : launch("tree_attn_merge", tree_attn_merge_kernel<64, 1>, mgrid, block, 0, s, a));
         if (e != hipSuccess) return RADAR_HIP_ERROR;
     }
     return RADAR_OK;
