@@ -33,7 +33,11 @@ constexpr size_t kCounterBytes = 16384;               // leading counter block o
 constexpr float kLog2eF = 1.4426950408889634f;
 constexpr int kDumpCap = 64;                          // hot lanes (largest logit reaches the threshold) whose logits go through LDS
 constexpr int kFastCap = 512;                         // chunk candidates ranked by the short path; more (runs of equal values) rank per wavefront
+constexpr int kFrontierMax = 256;                     // candidates of a call that are ranked by counting
 constexpr int64_t kStreamMinLogits = 4 << 20;         // batched calls of at least 16 MB of logits take the streaming path
+
+// what a launch carries beside the expansion itself: nothing; a batch or a cycle state; a prediction model, too
+enum { kExpPlain, kExpExt, kExpPolicy };
 
 struct ExpandArgs {
     const float *logits;
@@ -70,9 +74,12 @@ struct alignas(16) ExpandSmem {
     unsigned int ndump;                           // lanes whose largest logit reached it
     float tau;                                    // the threshold
     unsigned short dump_lane[kDumpCap];           // which lane left each block of logits
-    // last workgroup only: candidate (row f, rank r) at f * 16 + r
+    // last workgroup only: candidate c = f * k + r (row f, rank r in it)
     float cand_sc[RADAR_F_MAX * 16];
     int cand_tok[RADAR_F_MAX * 16];
+    alignas(16) uint64_t cand_key[kFrontierMax];
+    int rank[kExpThreads];                        // larger keys in each part of cand_key
+    PolicySmem pol;
     unsigned int ticket, ticket2;
 };
 
@@ -98,49 +105,66 @@ __device__ __forceinline__ uint64_t row_topk(uint64_t (&kk)[9], const uint64_t *
     return top;
 }
 
-// Next frontier: top-k of the F*k candidates in s.cand_sc by cumulative score (candidate index
-// breaks ties), by one wavefront.  conf_lds, when given, also receives the k confidences.
-__device__ __forceinline__ void select_frontier(const ExpandArgs &a, ExpandSmem &s, float *conf_lds) {
-    const int lane = lane_id();
-    const int K = a.k;
-    // ---- next frontier: top-k of the candidates by cumulative score (candidate index breaks ties)
-    const int nfs = a.F * 16;
-    uint64_t top;
-    if (nfs <= 4 * kWave) {                                    // F <= 16 rows: four slots per lane
-        uint64_t kk[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = topk_slot_of(e);
-            const float sc = s.cand_sc[min(i, nfs - 1)];
-            kk[e] = (i < nfs && (i & 15) < K) ? make_key(sc, uint32_t((i >> 4) * K + (i & 15))) : 0;
+// Entry `at` of the next frontier is candidate c.  conf_lds, when given, also receives the confidence.
+__device__ __forceinline__ void put_frontier(const ExpandArgs &a, const ExpandSmem &s, int at, int c, float *conf_lds) {
+    const float sc = s.cand_sc[c];
+    a.frontier_pool_idx[at] = a.pool_count + c;
+    a.frontier_tokens[at] = s.cand_tok[c];
+    a.frontier_scores[at] = sc;
+    const float conf = expf(sc);
+    a.frontier_conf[at] = conf;
+    if (conf_lds) conf_lds[at] = conf;
+}
+
+// Next frontier: the k largest of n <= kFrontierMax candidates by cumulative score (candidate index breaks
+// ties), by the whole workgroup: a thread counts the keys in a part of the list (an eighth up to 128
+// candidates, else a quarter) that are larger than its candidate's, the counts of the parts add up to the
+// rank, and whoever has a rank below k writes that entry.  (By one wavefront with a threshold, a
+// compaction and a ranking it was a chain of 1.5 us.  What counting costs is LDS bandwidth: a broadcast
+// read takes as long as any other, so no wavefront reads for candidates that do not exist.)
+// s.cand_key holds zeros from n on; a barrier has passed since it was written.  All lanes call.
+template <int WIDE>                                                // candidates per part
+__device__ __forceinline__ void rank_frontier(const ExpandArgs &a, ExpandSmem &s, int n, float *conf_lds) {
+    constexpr int kParts = kExpThreads / WIDE;
+    const int tid = threadIdx.x, c = tid % WIDE, part = tid / WIDE;
+    const int per = (n + 2 * kParts - 1) / (2 * kParts) * 2;       // keys per part
+    if (c - lane_id() < n) {                                       // wave-uniform
+        const uint64_t mine = s.cand_key[c];
+        int larger = 0;
+        for (int j = part * per; j < (part + 1) * per; j += 2) {
+            const uint64_t k0 = s.cand_key[j], k1 = s.cand_key[j + 1];
+            larger += (k0 > mine ? 1 : 0) + (k1 > mine ? 1 : 0);
         }
-        top = wave_topk<4>(kk, K, s.wtk[0]);
-    } else {
-        top = 0;
-        for (int c0 = 0; c0 < nfs; c0 += 8 * kWave) {
-            uint64_t kk[9];
+        s.rank[tid] = larger;
+    }
+    __syncthreads();
+    if (tid < n) {
+        int at = 0;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int i = c0 + topk_slot_of(e);
-                const float sc = s.cand_sc[min(i, nfs - 1)];
-                kk[e] = (i < nfs && (i & 15) < K) ? make_key(sc, uint32_t((i >> 4) * K + (i & 15))) : 0;
-            }
-            kk[8] = top;
-            top = wave_topk<9>(kk, K, s.wtk[0]);
+        for (int i = 0; i < kParts; ++i) at += s.rank[i * WIDE + tid];
+        if (at < a.k) put_frontier(a, s, at, tid, conf_lds);
+    }
+}
+
+// The same for any number of candidates, by one wavefront.
+__device__ __forceinline__ void select_frontier(const ExpandArgs &a, ExpandSmem &s, int n, float *conf_lds) {
+    const int lane = lane_id(), K = a.k, nfs = a.F * 16;           // slot i: rank i % 16 of row i / 16
+    uint64_t top = 0;
+    for (int c0 = 0; c0 < nfs; c0 += 8 * kWave) {
+        uint64_t kk[9];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int i = c0 + topk_slot_of(e), c = (i >> 4) * K + (i & 15);
+            const float sc = s.cand_sc[min(c, n - 1)];
+            kk[e] = (i < nfs && (i & 15) < K) ? make_key(sc, uint32_t(c)) : 0;
         }
+        kk[8] = top;
+        top = wave_topk<9>(kk, K, s.wtk[0]);
     }
     if (lane < K) {
-        const int C = a.F * K;
         int c = (int)key_index(top);
-        if (c < 0 || c >= C) c = 0;                               // only reachable with NaN scores
-        const int fr = c / K, r = c - fr * K;
-        const float sc = s.cand_sc[fr * 16 + r];
-        a.frontier_pool_idx[lane] = a.pool_count + c;
-        a.frontier_tokens[lane] = s.cand_tok[fr * 16 + r];
-        a.frontier_scores[lane] = sc;
-        const float conf = expf(sc);
-        a.frontier_conf[lane] = conf;
-        if (conf_lds) conf_lds[lane] = conf;
+        if (c < 0 || c >= n) c = 0;                               // only reachable with NaN scores
+        put_frontier(a, s, lane, c, conf_lds);
     }
 }
 
@@ -164,21 +188,28 @@ __device__ __forceinline__ void sequence_view(ExpandArgs &a, int bz) {
 // sequence is in the workspace (all 1024 lanes must call): rows are merged, candidates scored and
 // pooled, the next frontier chosen; with a prediction model its step follows, with a cycle state
 // its update.  `a` is already the sequence's own view of the call (bz = its index in the batch).
+// settle() is called once the first loads are on their way and says whether the call is made at all (a
+// batched call learns here that the sequence's cycle has stopped, and its pool count).
 // hidden(row) returns row `row` of w_hh h (complete before the call; only used with a prediction
 // model that has a state).
-template <bool EXT, typename Hidden>
-__device__ __forceinline__ void expand_finish(const ExpandArgs &a, ExpandSmem &s, int bz, radar_cycle_state *cycle,
-                                              bool cycle_first, Hidden &&hidden) {
-    const bool has_policy = EXT && a.has_policy != 0;
-    const int lane = lane_id(), w = wave_id();
-    const int K = a.k;
+template <int MODE, typename Settle, typename Hidden>
+__device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int bz, radar_cycle_state *cycle,
+                                              bool cycle_first, Settle &&settle, Hidden &&hidden) {
+    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    const int K = a.k, n = a.F * K;
+    const bool few = a.nchunks <= 16;                              // (V <= 131072 at 8 logits per lane)
+    const int nslot = a.nchunks * RADAR_K_MAX;
+    if (tid >= n && tid < kFrontierMax) s.cand_key[tid] = 0;
+    if (MODE == kExpPolicy && tid < RADAR_K_MAX) s.pol.in[kPolH + tid] = 0.f;
+
     // One wavefront per row (rows w, w+16, ...):
     // top-k of the row's chunk lists, log-sum-exp of the row, cumulative scores, pool append.
-    const int nslot = a.nchunks * RADAR_K_MAX;
-    for (int fr = w; fr < a.F; fr += kExpWaves) {
+    uint64_t kk[9];
+    float ml = 0.f, pscore = 0.f;
+    double ll = 0.0;
+    int ppool = 0;
+    auto load_row = [&](int fr) {
         const uint64_t *pk = a.part_keys + (size_t)fr * nslot;
-        const bool few = nslot <= 4 * kWave;                       // up to 16 chunks per row (V <= 131072 at 8 per lane)
-        uint64_t kk[9];
         if (few) {                                                 // four slots per lane: half the loads, a shorter selection
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -189,25 +220,25 @@ __device__ __forceinline__ void expand_finish(const ExpandArgs &a, ExpandSmem &s
         } else {
             load_key_block(pk, nslot, 0, K, kk);
         }
-        float ml;
-        double ll;
-        const bool few_chunks = a.nchunks <= 16;                   // every 16-lane row of the wavefront takes all chunks
-        {                                                          // chunk partials, one chunk per lane first
-            const int cl = few_chunks ? (lane & 15) : lane;
-            const int c = min(cl, a.nchunks - 1);
-            ml = load_shared_result(&a.part_m[(size_t)fr * a.nchunks + c]);
-            ll = load_shared_result(&a.part_l[(size_t)fr * a.nchunks + c]);
-            if (cl >= a.nchunks) { ml = -INFINITY; ll = 0.0; }
-        }
-        const float pscore = a.parent_scores[fr];
-        const int ppool = a.parent_pool_idx[fr];
+        // chunk partials, one chunk per lane first (up to 16 chunks: every 16-lane row of the wavefront takes all)
+        const int c = min(few ? (lane & 15) : lane, a.nchunks - 1);
+        ml = load_shared_result(&a.part_m[(size_t)fr * a.nchunks + c]);
+        ll = load_shared_result(&a.part_l[(size_t)fr * a.nchunks + c]);
+        pscore = a.parent_scores[fr];
+        ppool = a.parent_pool_idx[fr];
+    };
+    auto merge_row = [&](int fr, auto &&arrived) {
+        const uint64_t *pk = a.part_keys + (size_t)fr * nslot;
         uint64_t top;
+        asm volatile("" :: "v"(kk[0]), "v"(kk[3]), "v"(ppool));
+        arrived();
         if (few) {
             const uint64_t k4[4] = {kk[0], kk[1], kk[2], kk[3]};
             top = wave_topk<4>(k4, K, s.wtk[w]);
         } else {
             top = row_topk(kk, pk, nslot, K, s.wtk[w]);
         }
+        if ((few ? (lane & 15) : lane) >= a.nchunks) { ml = -INFINITY; ll = 0.0; }
         for (int c = lane + kWave; c < a.nchunks; c += kWave) {        // V > 262144 only
             const float m2 = load_shared_result(&a.part_m[(size_t)fr * a.nchunks + c]);
             const double l2 = load_shared_result(&a.part_l[(size_t)fr * a.nchunks + c]);
@@ -218,7 +249,7 @@ __device__ __forceinline__ void expand_finish(const ExpandArgs &a, ExpandSmem &s
         }
         float M;
         double L;
-        if (few_chunks) {
+        if (few) {
             // maximum and sum inside each 16-lane row by DPP steps alone (no lane reads: those cost a
             // scalar round trip each); fixed order of addition, every lane ends up with the result
             M = ml;
@@ -244,51 +275,52 @@ __device__ __forceinline__ void expand_finish(const ExpandArgs &a, ExpandSmem &s
             const double logp = (double)key_value(top) - lse;
             const float cum = (float)((double)pscore + logp);
             const int c = fr * K + lane;
+            s.cand_sc[c] = cum;
+            s.cand_tok[c] = tok;
+            if (n <= kFrontierMax) s.cand_key[c] = make_key(cum, uint32_t(c));
             a.cand_tokens[c] = tok;
             a.cand_scores[c] = cum;
             a.pool_tokens[a.pool_count + c] = tok;
             a.pool_scores[a.pool_count + c] = cum;
             a.pool_parents[a.pool_count + c] = ppool;
-            s.cand_sc[fr * 16 + lane] = cum;
-            s.cand_tok[fr * 16 + lane] = tok;
         }
-    }
+    };
+    if (w < a.F) load_row(w);
+    if (!settle()) return;
+    // the prediction model's operands are requested once the first rows' lists have arrived (ahead of them they
+    // hold the lists up by a microsecond) and arrive while rows are merged
+    PolicyRegs pr;
+    auto fetch = [&] { if constexpr (MODE == kExpPolicy) policy_fetch_head(a.pol, pr); };
+    if (w < a.F) merge_row(w, fetch);
+    else fetch();
+    for (int fr = w + kExpWaves; fr < a.F; fr += kExpWaves) { load_row(fr); merge_row(fr, [] {}); }
+    if constexpr (MODE == kExpPolicy) policy_fetch_rest<true>(a.pol, bz, a.pol_has_state != 0, pr, hidden);
     __syncthreads();
-    if (!has_policy) {
-        if (w == 0) {
-            select_frontier(a, s, nullptr);
-            if (cycle && lane == 0) {
-                cycle->pool_count = a.pool_count + a.F * a.k;
-                cycle->steps_done = cycle_first ? 1 : cycle->steps_done + 1;
-                if (cycle_first) { cycle->stopped = 0; cycle->last_action = -1; }
-            }
-        }
-        return;
+    float *const conf = MODE == kExpPolicy ? &s.pol.in[kPolH] : nullptr;
+    if (n <= kFrontierMax / 2) rank_frontier<kFrontierMax / 2>(a, s, n, conf);
+    else if (n <= kFrontierMax) rank_frontier<kFrontierMax>(a, s, n, conf);
+    else if (w == 0) select_frontier(a, s, n, conf);
+    auto advance = [&](int action) {                               // by one lane
+        if (!cycle) return;
+        cycle->pool_count = a.pool_count + n;
+        cycle->steps_done = cycle_first ? 1 : cycle->steps_done + 1;
+        if (action >= 0 || cycle_first) cycle->last_action = action;
+        if (action == 0) cycle->stopped = 1;
+        else if (cycle_first) cycle->stopped = 0;
+    };
+    if constexpr (MODE == kExpPolicy) {
+        // ---- prediction-model step on the new frontier's confidences
+        __syncthreads();
+        policy_decide<true>(a.pol, bz, a.pol_has_state != 0, s.pol, pr, hidden, advance);
+    } else {
+        if (tid == 0) advance(-1);
     }
-    // ---- prediction-model step on the new frontier's confidences.  Its LDS reuses the
-    // selection scratch of wavefronts 1.., idle since the barrier above; the other wavefronts
-    // fetch the model's operands while wavefront 0 still selects the frontier.
-    static_assert(sizeof(PolicySmem) <= (kExpWaves - 1) * sizeof(WaveTopkSmem) && sizeof(WaveTopkSmem) % 16 == 0, "policy LDS overlay");
-    PolicySmem &ps = *reinterpret_cast<PolicySmem *>(&s.wtk[1]);
-    policy_step_block<true>(
-        a.pol, bz, a.pol_has_state != 0, ps, hidden,
-        [&] { select_frontier(a, s, ps.x); },
-        [&](int action) {
-            if (cycle) {
-                cycle->pool_count = a.pool_count + a.F * a.k;
-                cycle->steps_done = cycle_first ? 1 : cycle->steps_done + 1;
-                cycle->last_action = action;
-                if (action == 0) cycle->stopped = 1;
-                else if (cycle_first) cycle->stopped = 0;
-            }
-        });
 }
 
-// EXT: the launch may carry a prediction model and / or a device-side cycle state; the plain
-// expansion is compiled without any of that code.
-template <bool VEC4, int EPT, bool EXT>
+// MODE: the plain expansion is compiled without any code for batches, cycle states or the prediction model.
+template <bool VEC4, int EPT, int MODE>
 __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(ExpandArgs a) {
-    const bool has_policy = EXT && a.has_policy != 0;
+    constexpr bool EXT = MODE != kExpPlain;
     static_assert(EPT == 4 || EPT == 8 || EPT == 16, "EPT");
     static_assert(kFastCap + 8 <= kWave * kWaveTopkMaxEPL + 8 && kExpWaves == 16, "candidate list inside the selection scratch");
     constexpr int kChunk = kExpThreads * EPT;
@@ -354,11 +386,12 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(ExpandArgs a) {
         }
     }
     // The prediction model's input-free part (w_hh h) is shared out over the workgroups of the
-    // launch: its loads travel with the logits', its results are handed to the last workgroup
-    // through the workspace like the chunk partials.
-    if (has_policy && a.pol_has_state)
-        policy_hidden_rows<4>(a.pol, bz, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y,
-                              [&](int r, float v) { store_shared_result(&a.gate_pre[r], v); });
+    // launch: its loads travel with the logits', and what is made of them, after the selection, is
+    // handed to the last workgroup through the workspace like the chunk partials.  By the wavefronts that
+    // do not stream.
+    HiddenRows<2, 2 * (kExpWaves - kStreamers)> hrows;
+    const bool hidden_rows = MODE == kExpPolicy && a.pol_has_state && !streamer;
+    if (hidden_rows) hrows.load(a.pol, bz, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid / 32 - 2 * kStreamers);
 
     // ---- the chunk's maximum, and the threshold of its top-k: the k-th largest of the maxima of the
     // sixteen 16-lane rows of the streaming wavefronts.  At least k logits of the chunk reach it (one
@@ -523,6 +556,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(ExpandArgs a) {
             store_shared_result(&a.part_l[pslot], l);
         }
     }
+    if (hidden_rows) hrows.finish(a.pol, bz, [&](int r, float v) { store_shared_result(&a.gate_pre[r], v); });
     unsigned int *row_counter = &a.counters[(1 + f) * kCounterStride];
     if (publish_then_ticket(row_counter, &s.ticket) != (unsigned int)(a.nchunks - 1)) return;
 
@@ -537,7 +571,8 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(ExpandArgs a) {
     if (tid == 0) store_shared_result(&a.counters[0], 0u);
 
     // ================= last workgroup of the call
-    expand_finish<EXT>(a, s, bz, cycle, cycle_first, [&](int row) { return load_shared_result(&a.gate_pre[row]); });
+    expand_finish<MODE>(a, s, bz, cycle, cycle_first, [] { return true; },
+                        [&](int row) { return load_shared_result(&a.gate_pre[row]); });
 }
 
 // ------------------------------------------------------------------ rerank
@@ -681,7 +716,7 @@ __device__ __forceinline__ bool cycle_skips(const radar_cycle_state *st, int poo
 }
 
 template <bool VEC4>
-__global__ __launch_bounds__(kStreamThreads) void expand_stream_kernel(ExpandArgs a) {
+__global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(ExpandArgs a) {
     __shared__ WaveTopkSmem wtk[kStreamWaves];
     __shared__ uint64_t wlists[kStreamWaves][kWaveListSlots];
     __shared__ float wave_m[kStreamWaves];
@@ -699,8 +734,9 @@ __global__ __launch_bounds__(kStreamThreads) void expand_stream_kernel(ExpandArg
     if (a.has_policy && a.pol_has_state) {
         const int bz = row / a.F;
         float *gate = a.gate_pre + (size_t)bz * (4 * kPolH);
-        policy_hidden_rows<4, kStreamThreads / 32>(a.pol, bz, (row - bz * a.F) * gridDim.x + blockIdx.x, a.F * gridDim.x,
-                                                   [&](int r, float v) { gate[r] = v; });
+        HiddenRows<4, kStreamThreads / 32> hrows;
+        hrows.load(a.pol, bz, (row - bz * a.F) * gridDim.x + blockIdx.x, a.F * gridDim.x, threadIdx.x / 32);
+        hrows.finish(a.pol, bz, [&](int r, float v) { gate[r] = v; });
     }
 
     float4 raw[4];
@@ -779,15 +815,16 @@ __global__ __launch_bounds__(kStreamThreads) void expand_stream_kernel(ExpandArg
 }
 
 // one workgroup per sequence, after expand_stream_kernel
+template <int MODE>
 __global__ __launch_bounds__(kExpThreads, 1) void expand_finish_kernel(ExpandArgs a) {
     __shared__ ExpandSmem s;
     const int bz = blockIdx.x;
     if (bz != 0) sequence_view(a, bz);
     radar_cycle_state *const cycle = a.cycle;
     const bool cycle_first = cycle != nullptr && a.pool_count == 0;
-    if (cycle_skips(cycle, a.pool_count, &a.pool_count)) return;
     // (the prediction model's input-free part was left in the workspace by the streaming kernel)
-    expand_finish<true>(a, s, bz, cycle, cycle_first, [&](int row) { return a.gate_pre[row]; });
+    expand_finish<MODE>(a, s, bz, cycle, cycle_first, [&] { return !cycle_skips(cycle, a.pool_count, &a.pool_count); },
+                        [&](int row) { return a.gate_pre[row]; });
 }
 
 }  // namespace radar
@@ -884,13 +921,15 @@ static radar_status launch_expand(const float *logits, const float *parent_score
         e = vec4 ? launch("expand_stream", expand_stream_kernel<true>, sgrid, dim3(kStreamThreads), 0, st, a)
                  : launch("expand_stream", expand_stream_kernel<false>, sgrid, dim3(kStreamThreads), 0, st, a);
         if (e != hipSuccess) return RADAR_HIP_ERROR;
-        e = launch("expand_finish", expand_finish_kernel, dim3((unsigned)B), block, 0, st, a);
+        e = pol ? launch("expand_finish", expand_finish_kernel<kExpPolicy>, dim3((unsigned)B), block, 0, st, a)
+                : launch("expand_finish", expand_finish_kernel<kExpExt>, dim3((unsigned)B), block, 0, st, a);
         return e == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
     }
-    const bool ext = pol != nullptr || cycle != nullptr || B > 1;
+    const bool ext = cycle != nullptr || B > 1;
 #define RADAR_EXPAND_LAUNCH(V4, E)                                                                   \
-    (ext ? launch("expand", expand_kernel<V4, E, true>, grid, block, 0, st, a)                        \
-         : launch("expand", expand_kernel<V4, E, false>, grid, block, 0, st, a))
+    (pol ? launch("expand", expand_kernel<V4, E, kExpPolicy>, grid, block, 0, st, a)                  \
+     : ext ? launch("expand", expand_kernel<V4, E, kExpExt>, grid, block, 0, st, a)                   \
+           : launch("expand", expand_kernel<V4, E, kExpPlain>, grid, block, 0, st, a))
     if (ept == 4)      e = vec4 ? RADAR_EXPAND_LAUNCH(true, 4) : RADAR_EXPAND_LAUNCH(false, 4);
     else if (ept == 8) e = vec4 ? RADAR_EXPAND_LAUNCH(true, 8) : RADAR_EXPAND_LAUNCH(false, 8);
     else               e = vec4 ? RADAR_EXPAND_LAUNCH(true, 16) : RADAR_EXPAND_LAUNCH(false, 16);

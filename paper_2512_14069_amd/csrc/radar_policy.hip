@@ -9,14 +9,19 @@ namespace radar {
 __global__ __launch_bounds__(kPolThreads) void policy_kernel(PolicyArgs p, const float *conf, int has_state) {
     __shared__ PolicySmem s;
     const int b = blockIdx.x;
-    if (has_state)
-        policy_hidden_rows<16>(p, b, 0, 1, [&](int row, float v) { s.gate[row] = v; });
-    policy_step_block<false>(
-        p, b, has_state != 0, s, [&](int row) { return s.gate[row]; },
-        [&] {
-            if ((int)threadIdx.x < p.k) s.x[threadIdx.x] = conf[(size_t)b * p.k + threadIdx.x];
-        },
-        [](int) {});
+    const int tid = threadIdx.x;
+    auto hidden = [&](int row) { return s.gate[row]; };
+    PolicyRegs r;
+    policy_fetch_head(p, r);
+    policy_fetch_rest<false>(p, b, has_state != 0, r, hidden);
+    if (tid < RADAR_K_MAX) s.in[kPolH + tid] = tid < p.k ? conf[(size_t)b * p.k + tid] : 0.f;
+    if (has_state) {
+        HiddenRows<16, kPolThreads / 32> hrows;
+        hrows.load(p, b, 0, 1, tid / 32);
+        hrows.finish(p, b, [&](int row, float v) { s.gate[row] = v; });
+    }
+    __syncthreads();
+    policy_decide<false>(p, b, has_state != 0, s, r, hidden, [](int) {});
 }
 
 // Host-side check of a parameter block; fills the kernel's argument struct.
