@@ -227,11 +227,9 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
         pscore = a.parent_scores[fr];
         ppool = a.parent_pool_idx[fr];
     };
-    auto merge_row = [&](int fr, auto &&arrived) {
+    auto merge_row = [&](int fr) {
         const uint64_t *pk = a.part_keys + (size_t)fr * nslot;
         uint64_t top;
-        asm volatile("" :: "v"(kk[0]), "v"(kk[3]), "v"(ppool));
-        arrived();
         if (few) {
             const uint64_t k4[4] = {kk[0], kk[1], kk[2], kk[3]};
             top = wave_topk<4>(k4, K, s.wtk[w]);
@@ -287,14 +285,15 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
     };
     if (w < a.F) load_row(w);
     if (!settle()) return;
-    // the prediction model's operands are requested once the first rows' lists have arrived (ahead of them they
-    // hold the lists up by a microsecond) and arrive while rows are merged
+    if (w < a.F) merge_row(w);
+    for (int fr = w + kExpWaves; fr < a.F; fr += kExpWaves) { load_row(fr); merge_row(fr); }
+    // The prediction model's operands are requested by every wavefront as its rows are done and arrive while the
+    // frontier is chosen.  (Requested earlier they hold up the lists or the merging: 2 % of a cycle.)
     PolicyRegs pr;
-    auto fetch = [&] { if constexpr (MODE == kExpPolicy) policy_fetch_head(a.pol, pr); };
-    if (w < a.F) merge_row(w, fetch);
-    else fetch();
-    for (int fr = w + kExpWaves; fr < a.F; fr += kExpWaves) { load_row(fr); merge_row(fr, [] {}); }
-    if constexpr (MODE == kExpPolicy) policy_fetch_rest<true>(a.pol, bz, a.pol_has_state != 0, pr, hidden);
+    if constexpr (MODE == kExpPolicy) {
+        policy_fetch_head(a.pol, pr);
+        policy_fetch_rest<true>(a.pol, bz, a.pol_has_state != 0, pr, hidden);
+    }
     __syncthreads();
     float *const conf = MODE == kExpPolicy ? &s.pol.in[kPolH] : nullptr;
     if (n <= kFrontierMax / 2) rank_frontier<kFrontierMax / 2>(a, s, n, conf);

@@ -25,7 +25,9 @@ constexpr int kPolWaves = kPolThreads / kWave;       // 16
 constexpr int kPolH = 128;                           // LSTM hidden size (App. A.3)
 constexpr int kPolMMax = 128;                        // largest hidden size of the head
 constexpr int kPolHeadLanes = 8;                     // lanes that share a row of the head
-constexpr int kPolHeadCols = (kPolH + RADAR_K_MAX) / kPolHeadLanes;        // columns each takes
+// Columns each of them takes: 4 l .. 4 l + 3 of every 32 of h', then l and l + 8 of x.
+constexpr int kPolHeadQuads = kPolH / (4 * kPolHeadLanes), kPolHeadTail = RADAR_K_MAX / kPolHeadLanes;
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));     // rows of any length: 16-byte loads from 4-byte addresses
 static_assert(kPolMMax * kPolHeadLanes == kPolThreads && 4 * kPolH * 2 == kPolThreads, "one thread per share of a head row, half of them one gate each");
 
 struct PolicyArgs {
@@ -47,8 +49,10 @@ struct alignas(16) PolicySmem {
 // What a thread holds of the model: half of the threads one gate row (four gates of a unit in a quad of
 // lanes), all of them an eighth of a head row, the last wavefront the last layer.
 struct PolicyRegs {
-    float wih[RADAR_K_MAX], b_ih, b_hh, c_prev, hid;
-    float w1[kPolHeadCols], b1;
+    float4u wih[RADAR_K_MAX / 4];
+    float b_ih, b_hh, c_prev, hid;
+    float4u w1[kPolHeadQuads];
+    float w1x[kPolHeadTail], b1;
     float w2[2][2], b2[2], uni;
 };
 
@@ -135,16 +139,18 @@ struct HiddenRows {
 };
 
 // Request what the step for state b will need, the head's rows (policy_fetch_head) and the rest, by the
-// kPolThreads threads of one workgroup; nothing waits here.  (In two parts because a caller with work in
-// between has registers for one of them only.)  Every load is from a clamped, valid address, taken or not (rows and columns that do not
+// kPolThreads threads of one workgroup; nothing waits here.  Every load is from a clamped, valid address, taken or not (rows and columns that do not
 // exist are discarded where the values are used); only which kind of load a wavefront makes depends on
 // its number.  hidden(row): (w_hh h)[row]; with EARLY a value in global memory, complete before the call,
 // otherwise it is read by policy_decide (a value this workgroup wrote to LDS).
 __device__ __forceinline__ void policy_fetch_head(const PolicyArgs &p, PolicyRegs &r) {
     const int tid = threadIdx.x, cols = kPolH + p.k, row = min(tid / kPolHeadLanes, p.M - 1);
     const float *src = p.w1 + (size_t)row * cols;
+    const int l = tid % kPolHeadLanes;
 #pragma unroll
-    for (int j = 0; j < kPolHeadCols; ++j) r.w1[j] = src[min(tid % kPolHeadLanes + kPolHeadLanes * j, cols - 1)];
+    for (int j = 0; j < kPolHeadQuads; ++j) r.w1[j] = *reinterpret_cast<const float4u *>(src + 4 * (l + kPolHeadLanes * j));
+#pragma unroll
+    for (int j = 0; j < kPolHeadTail; ++j) r.w1x[j] = src[min(kPolH + l + kPolHeadLanes * j, cols - 1)];
     r.b1 = p.b1[row];
 }
 template <bool EARLY, typename Hidden>
@@ -154,11 +160,13 @@ __device__ __forceinline__ void policy_fetch_rest(const PolicyArgs &p, int b, bo
         const int unit = (tid - kPolThreads / 2) >> 2, row = (tid & 3) * kPolH + unit;
         const float *src = p.w_ih + (size_t)row * p.k;
 #pragma unroll
-        for (int i4 = 0; i4 < RADAR_K_MAX; i4 += 4)
-            if (i4 < p.k) {                                          // the same in every lane
+        for (int i4 = 0; i4 < RADAR_K_MAX; i4 += 4) {                // (the conditions are the same in every lane)
+            if (i4 + 4 <= p.k) r.wih[i4 / 4] = *reinterpret_cast<const float4u *>(src + i4);
+            else if (i4 < p.k) {
 #pragma unroll
-                for (int i = i4; i < i4 + 4; ++i) r.wih[i] = src[min(i, p.k - 1)];
+                for (int i = 0; i < 4; ++i) r.wih[i4 / 4][i] = src[min(i4 + i, p.k - 1)];
             }
+        }
         r.b_ih = p.b_ih[row];
         r.b_hh = p.b_hh[row];
         r.c_prev = (has_state ? p.c_in + (size_t)b * kPolH : p.b_ih)[unit];
@@ -188,8 +196,14 @@ __device__ __forceinline__ void policy_decide(const PolicyArgs &p, int b, bool h
         float pre = r.b_ih + r.b_hh;
         if (has_state) pre += EARLY ? r.hid : hidden(gate * kPolH + unit);
 #pragma unroll
-        for (int i = 0; i < RADAR_K_MAX; ++i)
-            if (i < p.k) pre = fmaf(r.wih[i], s.in[kPolH + i], pre);
+        for (int i4 = 0; i4 < RADAR_K_MAX; i4 += 4) {
+            if (i4 >= p.k) break;
+            const float4 in = *reinterpret_cast<const float4 *>(&s.in[kPolH + i4]);
+            pre = fmaf(r.wih[i4 / 4].x, in.x, pre);
+            if (i4 + 1 < p.k) pre = fmaf(r.wih[i4 / 4].y, in.y, pre);
+            if (i4 + 2 < p.k) pre = fmaf(r.wih[i4 / 4].z, in.z, pre);
+            if (i4 + 3 < p.k) pre = fmaf(r.wih[i4 / 4].w, in.w, pre);
+        }
         const bool cand = gate == 2;
         const float sg = fast_sigmoid(cand ? 2.f * pre : pre);
         const float act = cand ? 2.f * sg - 1.f : sg;
@@ -207,14 +221,19 @@ __device__ __forceinline__ void policy_decide(const PolicyArgs &p, int b, bool h
     // ---- first layer of the head on [h'; x], ReLU: eight lanes per row
     {
         const int cols = kPolH + p.k, l = tid % kPolHeadLanes, row = tid / kPolHeadLanes;
-        float v[2] = {0.f, 0.f};
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < kPolHeadCols; ++j) {
-            const int col = l + kPolHeadLanes * j;
-            const float wv = kPolHeadLanes * (j + 1) <= kPolH || col < cols ? r.w1[j] : 0.f;
-            v[j & 1] = fmaf(wv, s.in[col], v[j & 1]);
+        for (int j = 0; j < kPolHeadQuads; ++j) {
+            const float4 in = *reinterpret_cast<const float4 *>(&s.in[4 * (l + kPolHeadLanes * j)]);
+            v[0] = fmaf(r.w1[j].x, in.x, v[0]); v[1] = fmaf(r.w1[j].y, in.y, v[1]);
+            v[2] = fmaf(r.w1[j].z, in.z, v[2]); v[3] = fmaf(r.w1[j].w, in.w, v[3]);
         }
-        float sum = v[0] + v[1];
+#pragma unroll
+        for (int j = 0; j < kPolHeadTail; ++j) {
+            const int col = kPolH + l + kPolHeadLanes * j;
+            v[j & 3] = fmaf(col < cols ? r.w1x[j] : 0.f, s.in[col], v[j & 3]);
+        }
+        float sum = (v[0] + v[1]) + (v[2] + v[3]);
         sum += dpp_f32<0xB1>(sum);
         sum += dpp_f32<0x4E>(sum);
         sum += dpp_f32<0x141>(sum);                                  // the other quad of the eight lanes

@@ -112,12 +112,46 @@ __device__ __forceinline__ void block_topk(const uint64_t (&keys)[EPT], int K, T
 // different scratch; all 64 lanes must call.
 constexpr int kWaveTopkMaxEPL = 9;
 
+template <int ROR>
+__device__ __forceinline__ void count_larger(uint32_t g, int &larger) {
+    if constexpr (ROR < 16) {
+        larger += dpp_u32<0x120 + ROR>(g) > g ? 1 : 0;              // row_ror
+        count_larger<ROR + 1>(g, larger);
+    }
+}
+
 // Threshold for a selection of the K <= 16 largest values held by the lanes of one wavefront
 // (v = largest value of the lane, 0 if it holds none): the K-th largest of the 16 quad maxima.
 // At least K values are >= the result (one per quad that reaches it), and unlike the smallest
 // quad maximum it does not collapse when a few quads happen to hold only small values.
 // Never 0, so that absent entries (0) fail the test "value >= threshold".
+// All 16 maxima are brought into every 16-lane row by row swaps (lane 4 i + r of a row receives the
+// maximum of row r's quad i) and ranked there by rotations: vector instructions throughout, where sixteen
+// lane reads cross to the scalar side and back.
 __device__ __forceinline__ uint32_t quad_threshold(uint32_t v, int K) {
+    uint32_t g = v;
+    g = max(g, dpp_u32<0xB1>(g));
+    g = max(g, dpp_u32<0x4E>(g));                 // quad maximum in every lane of the quad
+    const int lane = lane_id();
+    g = (lane & 3) == (lane >> 4) ? g : 0;
+    const auto a = __builtin_amdgcn_permlane16_swap(g, g, false, false);        // rows 0 0 2 2, rows 1 1 3 3
+    g = max(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(g, g, false, false);
+    g = max(b[0], b[1]);
+    int larger = 0;                               // quads whose maximum is strictly larger than this lane's
+    count_larger<1>(g, larger);
+    uint32_t c = larger < K ? g : 0xffffffffu;    // the K largest quad maxima (and their ties) stay
+    c = min(c, dpp_u32<0xB1>(c));
+    c = min(c, dpp_u32<0x4E>(c));
+    c = min(c, dpp_u32<0x141>(c));
+    c = min(c, dpp_u32<0x140>(c));                // smallest of them; the same in every row
+    return max(c, 1u);
+}
+
+
+// For the throughput of many wavefronts side by side: the same by sixteen lane reads, fewer vector
+// instructions (where a wavefront's own chain of steps counts, quad_threshold is the shorter one).
+__device__ __forceinline__ uint32_t quad_threshold_many(uint32_t v, int K) {
     uint32_t g = v;
     g = max(g, dpp_u32<0xB1>(g));
     g = max(g, dpp_u32<0x4E>(g));                 // quad maximum in every lane of the quad
@@ -130,7 +164,6 @@ __device__ __forceinline__ uint32_t quad_threshold(uint32_t v, int K) {
     const uint32_t t = min(min(readlane_u32(c, 0), readlane_u32(c, 16)), min(readlane_u32(c, 32), readlane_u32(c, 48)));
     return max(t, 1u);
 }
-
 
 struct WaveTopkSmem {
     uint64_t surv[kWave * kWaveTopkMaxEPL + 8];   // +8: the ranking reads keys eight at a time
@@ -180,47 +213,18 @@ __device__ __forceinline__ uint64_t wave_topk(const uint64_t (&keys)[EPL], int K
 // reaches tau = the K-th largest quad maximum (so the wavefront's K largest are among them), as
 // proper keys in list[0..32), 0 where there are fewer.  x[e] is element e of the lane (-inf where it
 // lies past the row), its index is idx0 + (e / 4) * gstride + e % 4, indices of a lane ascend with
-// e.  Keys are only built for the survivors (about K + 4 of them on random data).  Returns false,
-// with list untouched, when more than 32 survive (long runs of equal values): the caller then
-// ranks with wave_topk.  All 64 lanes must call; list is wavefront-private LDS.
+// e.  The survivors are counted first (comparison masks stay in scalar registers), and keys are only
+// built for them (about K + 4 of them on random data).  Returns false, with list untouched, when more
+// than 32 survive (long runs of equal values): the caller then ranks with wave_topk.  All 64 lanes must
+// call; list is wavefront-private LDS.
 constexpr int kWaveListSlots = 32;
 
-template <int EPL>
-__device__ __forceinline__ bool wave_candidates(const float (&x)[EPL], float lane_max, uint32_t idx0, uint32_t gstride,
-                                                uint32_t V, int K, WaveTopkSmem &s, uint64_t *list) {
-    static_assert(EPL <= kWaveTopkMaxEPL, "scratch too small");
-    const int lane = lane_id();
-    // a lane with no element inside the row counts as empty (0), not as a lane holding -inf
-    const uint32_t tau = quad_threshold(idx0 < V ? ord_of(lane_max) : 0u, K);
-    // as a float; thresholds at or below the image of -inf let every element of the row pass
-    const float tau_f = tau < 0x00800000u ? -INFINITY : float_of_ord(tau);
-    int n = 0;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        const uint32_t idx = idx0 + (uint32_t)(e >> 2) * gstride + (uint32_t)(e & 3);
-        const bool keep = x[e] >= tau_f && idx < V;
-        const uint64_t m = __ballot(keep);
-        if (keep) s.surv[n + lanes_below(m)] = (uint64_t(__float_as_uint(x[e])) << 32) | idx;
-        n += __popcll(m);
-    }
-    if (n > kWaveListSlots) return false;
-    wave_lds_sync();
-    if (lane < kWaveListSlots) {
-        const uint64_t raw = s.surv[min(lane, max(n - 1, 0))];
-        list[lane] = lane < n ? make_key(__uint_as_float(uint32_t(raw >> 32)), uint32_t(raw)) : 0;
-    }
-    wave_lds_sync();                              // scratch may be reused right after the return
-    return true;
-}
-
-// The same for up to 16 elements per lane with the same small scratch: the survivors are counted
-// first (comparison masks stay in scalar registers) and compacted only if they fit the list.
 template <int EPL>
 __device__ __forceinline__ bool wave_candidates_counted(const float (&x)[EPL], float lane_max, uint32_t idx0, uint32_t gstride,
                                                         uint32_t V, int K, uint64_t *list) {
     static_assert(EPL <= 16, "masks");
     const int lane = lane_id();
-    const uint32_t tau = quad_threshold(idx0 < V ? ord_of(lane_max) : 0u, K);
+    const uint32_t tau = quad_threshold_many(idx0 < V ? ord_of(lane_max) : 0u, K);
     const float tau_f = tau < 0x00800000u ? -INFINITY : float_of_ord(tau);
     uint64_t m[EPL];
     int total = 0;
