@@ -495,7 +495,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(AttnArgs a) {
 // granule of a pair (4.5 us with the whole chip at work).
 // All of it in units of an eighth of a full tile.
 constexpr int kTileCost = 8;               // a tile for eight units
-constexpr int kTileCostHalf = 5;             // for half of them: the pair is shared by two wavefronts per unit; the loads stay
+constexpr int kTileCostLight = 5;          // for at most half as many: the loads stay
 constexpr int kUnitCost = 20;               // query rows, ancestor words and partials of a unit's first piece
 constexpr int kFlatMaxB = kWave;           // one lane per sequence
 
@@ -504,13 +504,14 @@ struct FlatPlan {                          // lane = sequence
     int total, share, unit;                // of the line; what a unit costs besides its tiles; the same in every lane
 };
 
-// Blocks of 32 rows that a sequence's tree fills, and whether two wavefronts share a unit's keys: where the
-// tree is small enough that only half of the launch's wavefronts have a unit, the other half takes every
-// second tile (all units in one workgroup) or the second half of the piece (units in half of the workgroups).
+// Blocks of 32 rows that a sequence's tree fills; whether its units are at most half of what the workgroups
+// hold; and, where those are then in half of the workgroups, that the other half takes the second half
+// of every piece's rows.  (Inside one workgroup the idle wavefronts are left idle: having them take every
+// second tile was no faster, the loads bound such a tile, and doubled the partials: 1-15 % slower.)
 __device__ __forceinline__ int flat_row_blocks(const AttnArgs &a, int nn) { return nn <= 32 ? 1 : a.nqb; }
+__device__ __forceinline__ bool flat_light(const AttnArgs &a, int nn) { return a.G * flat_row_blocks(a, nn) * 2 <= kGsWaves * a.n_ublk; }
 __device__ __forceinline__ bool flat_shared(const AttnArgs &a, int nn) {
-    const int units = a.G * flat_row_blocks(a, nn);
-    return a.n_ublk == 1 ? units * 2 <= kGsWaves : (a.n_ublk & 1) == 0 && units * 2 == kGsWaves * a.n_ublk;
+    return (a.n_ublk & 1) == 0 && a.G * flat_row_blocks(a, nn) * 2 == kGsWaves * a.n_ublk;
 }
 
 __device__ __forceinline__ FlatPlan flat_plan(const AttnArgs &a) {
@@ -522,7 +523,7 @@ __device__ __forceinline__ FlatPlan flat_plan(const AttnArgs &a) {
     const int rows = min(f.L + f.nn, a.S);
     const int tiles = (lane < a.B && f.L >= 0) ? (rows + kKT - 1) / kKT : 0;
     f.pairs = (tiles + 1) / 2;
-    f.cost = flat_shared(a, f.nn) ? kTileCostHalf : kTileCost;
+    f.cost = flat_light(a, f.nn) && (a.n_ublk == 1 || flat_shared(a, f.nn)) ? kTileCostLight : kTileCost;
     f.unit = kUnitCost;
     f.len = tiles > 0 ? kUnitCost + tiles * f.cost : 0;
     const uint32_t mine = (uint32_t)(f.len * a.Hkv);
@@ -532,8 +533,8 @@ __device__ __forceinline__ FlatPlan flat_plan(const AttnArgs &a) {
     // Every piece of a unit costs writing and merging a partial, about 0.3 of a tile's time; with p pairs
     // per unit and s pairs per piece, s + 0.15 p / s is least at s = sqrt(0.15 p).
     const int most = (int)wave_max_u32((uint32_t)f.pairs);
-    const int tile = __ballot(f.pairs == most && f.cost == kTileCostHalf) != 0 ? kTileCostHalf : kTileCost;
-    const float merge = tile == kTileCost ? 0.15f : 0.3f;       // (two partials where keys are shared)
+    const int tile = __ballot(f.pairs == most && f.cost == kTileCostLight) != 0 ? kTileCostLight : kTileCost;
+    const float merge = tile == kTileCost || a.n_ublk == 1 ? 0.15f : 0.3f;       // (two partials where keys are shared)
     const int least = max(2 * tile * (int)(__builtin_amdgcn_sqrtf(merge * (float)most) + 0.5f), kUnitCost + 2 * kTileCost);
     // total / shares rounded up (exactly so below 2^24; never less)
     f.share = max((int)__umulhi((uint32_t)(f.total + a.shares - 1), a.shares_inv), least);
@@ -573,7 +574,7 @@ __device__ __forceinline__ int flat_middle(const FlatUnit &u, int j) { return u.
 // first pair whose middle is not before pos
 __device__ __forceinline__ int flat_pair_at(const FlatUnit &u, int pos) {
     const uint32_t x = (uint32_t)max(pos - flat_middle(u, 0), 0);
-    const uint32_t j = u.cost == kTileCost ? (x + 2 * kTileCost - 1) / (2 * kTileCost) : (x + 2 * kTileCostHalf - 1) / (2 * kTileCostHalf);
+    const uint32_t j = u.cost == kTileCost ? (x + 2 * kTileCost - 1) / (2 * kTileCost) : (x + 2 * kTileCostLight - 1) / (2 * kTileCostLight);
     return min(u.pairs, (int)j);
 }
 
@@ -720,7 +721,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
     // Shared keys with the units in half of the workgroups: the other half takes the second half of the
     // piece's pairs (and, where there is one pair only, the same rows with none of them allowed).
     auto own_half = [&](Piece &p) {
-        if (!FLAT || a.n_ublk == 1 || !flat_shared(a, p.nn)) return;
+        if (!FLAT || !flat_shared(a, p.nn)) return;
         const int mid = p.t0 + ((p.t1 - p.t0 + 3) / 4) * 2;
         if (2 * ublk < a.n_ublk) p.t1 = min(p.t1, mid);
         else if (mid < p.t1) p.t0 = mid;
@@ -765,14 +766,11 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
     for (;;) {
         // which unit this wavefront is: (head within the group, block of 32 rows), and which keys of the piece
         const int nqb = FLAT ? flat_row_blocks(a, pc.nn) : a.nqb, units = a.G * nqb;
-        const bool by_tile = FLAT && a.n_ublk == 1 && flat_shared(a, pc.nn);     // two wavefronts take a pair's tiles
         int u = ublk * kGsWaves + w;
-        int odd = 0;                                      // by_tile: 1 if this wavefront takes the second tile of every pair
         const int entry = (pc.slot * a.n_ublk + ublk) * kGsWaves + w;
         bool active = u < units;
         if (FLAT && flat_shared(a, pc.nn)) {
             active = u < 2 * units;
-            if (by_tile && u >= units) odd = 1;
             if (u >= units) u -= units;
         }
         const int g = u / nqb, qb = u % nqb;
@@ -840,13 +838,6 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
             tile_pv<D, true>([&](int k, int hi) { return va[k % DB] + TOFF + (k / DB) * (16 * D * 2) + hi * (8 * D * 2); }, pk, oacc);
         };
         const int fav = w < kGsWaves / 2 ? 1 : 0;
-        auto shift = [&](int by) {
-#pragma unroll
-            for (int st = 0; st < D / 16; ++st) ka[st] += by;
-#pragma unroll
-            for (int db = 0; db < DB; ++db) va[db] += by;
-        };
-        if (FLAT && by_tile) shift(odd * TILE);
         for (int t = pc.t0; t < pc.t1; t += 2) {
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
             if (FLAT && lt >= lt1 && more) load_from(nx);            // (past the last piece: its last rows once more)
@@ -855,15 +846,17 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
             lt += 2;
             if (active) {
                 if (fav) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
-                // (an odd wavefront's tile may lie past the end of the range: nothing of it is allowed then)
-                run_tile(std::false_type{}, (t + odd) * kKT);
+                run_tile(std::false_type{}, t * kKT);
                 if (fav) __builtin_amdgcn_s_setprio(0); else __builtin_amdgcn_s_setprio(1);
-                if (!by_tile && t + 1 < pc.t1) run_tile(std::true_type{}, (t + 1) * kKT);
+                if (t + 1 < pc.t1) run_tile(std::true_type{}, (t + 1) * kKT);
             }
-            shift(half ? -2 * TILE : 2 * TILE);                      // the next pair sits in the other two buffers
+            const int step = half ? -2 * TILE : 2 * TILE;            // the next pair sits in the other two buffers
+#pragma unroll
+            for (int st = 0; st < D / 16; ++st) ka[st] += step;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) va[db] += step;
             half ^= 1;
         }
-        if (FLAT && by_tile) shift(-odd * TILE);
         asm volatile("" :: "v"(touched));
         __builtin_amdgcn_s_setprio(0);
         if (!more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be on its way into LDS at the end

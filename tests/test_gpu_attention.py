@@ -126,7 +126,7 @@ def _ragged(seed, B, hi, T):
 
 DEALT_CASES = {                                   # name: B, Hq, Hkv, T, longest prefix, equal lengths
     "group_of_4": (33, 32, 8, 60, 700, False),                # trees on both sides of one block of 32 rows
-    "one_head_per_kv_head": (64, 4, 4, 20, 640, False),       # one unit: two wavefronts share its keys
+    "one_head_per_kv_head": (64, 4, 4, 20, 640, False),       # one unit
     "group_of_8_two_unit_blocks": (17, 64, 8, 64, 900, False),    # small trees: the unit blocks share a piece
     "group_of_12_three_unit_blocks": (22, 48, 4, 40, 500, False),
     "many_pieces_per_head": (3, 8, 2, 33, 9000, False),       # more partials than one batch of the merge
@@ -139,7 +139,7 @@ DEALT_CASES = {                                   # name: B, Hq, Hkv, T, longest
 def test_rows_dealt_out_on_the_device(oracle, name):
     """Long ranges that the caller does not fix are cut into shares on the device: pieces that begin and end
     anywhere, several pieces per workgroup, heads cut into many, idle workgroups, and trees that fill half of
-    the wavefronts, whose keys are then shared."""
+    the workgroups, whose keys are then shared."""
     from paper_2512_14069_amd import binding as b
     B, Hq, Hkv, T, hi, equal = DEALT_CASES[name]
     ctx, nodes, depth = ([hi] * B, [T] * B, [8] * B) if equal else _ragged(len(name), B, hi, T)
