@@ -993,9 +993,11 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
     if (kps <= 0) {
         // Number of key ranges: the one that minimises a small cost model, in units of one tile of
         // one workgroup (measured ~2.7 us): rounds of 256 resident workgroups x (tiles per range +
-        // 3 for prologue and epilogue), plus what the merge of the ranges costs (every range writes
-        // and re-reads T*Hq*D fp16 of partial output, which soon exceeds the KV bytes themselves).
-        // Counting whole rounds matters: 576 workgroups take as long as 768.
+        // 3 for prologue and epilogue), plus what the merge of the ranges costs: the launch, and every
+        // range's partials written and read again.  Counting whole rounds matters: 576 workgroups take
+        // as long as 768.  The two merge terms were fitted over 29 shapes of 90 ... 16000 rows (0.3 per
+        // range, from when a lane read its partials 4 bytes at a time, cost 5-15 % on most of them: one layer of
+        // 2048 rows 15.4 us with 11 ranges, 14.6 with 17; 8000 rows 22.1 and 20.4).
         const long units = (long)d->B * d->Hkv * p.n_ublk;
         const long tiles_all = ((long)d->S_max + kKT - 1) / kKT;
         double best = 1e30;
@@ -1003,7 +1005,7 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
         for (long ns = 1; ns <= 64 && ns <= tiles_all; ++ns) {
             const long tiles = (tiles_all + ns - 1) / ns;
             const long rounds = (units * ns + 255) / 256;
-            const double cost = (double)rounds * (double)(tiles + 3) + (ns > 1 ? 1.6 + 0.3 * (double)ns : 0.0);
+            const double cost = (double)rounds * (double)(tiles + 3) + (ns > 1 ? 1.2 + 0.08 * (double)ns : 0.0);
             if (cost < best) { best = cost; best_ns = ns; }
         }
         kps = (tiles_all + best_ns - 1) / best_ns * kKT;

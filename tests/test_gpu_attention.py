@@ -125,13 +125,13 @@ def _ragged(seed, B, hi, T):
 
 
 DEALT_CASES = {                                   # name: B, Hq, Hkv, T, longest prefix, equal lengths
-    "group_of_4": (33, 32, 8, 60, 700, False),                # trees on both sides of one block of 32 rows
+    "group_of_4": (32, 32, 8, 60, 700, False),                # trees on both sides of one block of 32 rows
     "one_head_per_kv_head": (64, 4, 4, 20, 640, False),       # one unit
-    "group_of_8_two_unit_blocks": (17, 64, 8, 64, 900, False),    # small trees: the unit blocks share a piece
-    "group_of_12_three_unit_blocks": (22, 48, 4, 40, 500, False),
-    "many_pieces_per_head": (3, 8, 2, 33, 9000, False),       # more partials than one batch of the merge
+    "group_of_8_two_unit_blocks": (16, 64, 8, 64, 900, False),    # small trees: the unit blocks share a piece
+    "group_of_12_three_unit_blocks": (21, 48, 4, 40, 520, False),
+    "many_pieces_per_head": (2, 4, 2, 33, 36000, False),      # more partials than one batch of the merge
     "equal_lengths": (5, 16, 8, 40, 3000, True),              # whole pieces
-    "one_sequence": (1, 8, 8, 60, 5000, True),
+    "one_sequence": (1, 8, 8, 60, 17000, True),
 }
 
 
