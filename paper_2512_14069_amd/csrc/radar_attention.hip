@@ -588,6 +588,9 @@ __device__ __forceinline__ int flat_pair_at(const FlatUnit &u, int pos) {
 // of a range re-read its last row: their scores are masked, and the row they repeat is a cache row
 // whose values the result depends on anyway (0 * finite = 0).
 constexpr int kLdBufs = 4;
+// Ranges of so many tiles take it.  At eight the compact one-ahead loop still wins (16 sequences of up to 900
+// rows 20.3 us against 22.0), at nine the long-range kernel (8 of up to 2000 rows 26.6 against 28.6).
+constexpr int kLongTiles = 9;
 
 // A lane's share of a tile: two chunks of K and two of V.  Wavefront w loads the row groups 2w and
 // 2w + 1 (four rows, 1 KB each); the lane's 16 bytes land at the group's LDS base + 16 * lane, i.e. in
@@ -1017,7 +1020,7 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
     // workgroups are many rounds, and the hardware's dispatch evens them out.)
     p.shares = 0;
     const long pairs = ((long)d->S_max + 2 * kKT - 1) / (2 * kKT), heads = (long)d->B * d->Hkv;
-    if (d->keys_per_split == 0 && kps >= 8 * kKT && d->D == 128 && d->B <= kFlatMaxB && d->Hkv <= kWave && p.n_ublk <= 16 &&
+    if (d->keys_per_split == 0 && kps >= kLongTiles * kKT && d->D == 128 && d->B <= kFlatMaxB && d->Hkv <= kWave && p.n_ublk <= 16 &&
         heads * (2 * pairs * kTileCost + kUnitCost) < (1l << 30))
         p.shares = 256 / p.n_ublk;
     size_t off = 0;
@@ -1128,7 +1131,7 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
     {
         hipError_t e;
         if (p.shares > 0)     e = launch_ld<128, true>(a, grid, s);
-        else if (p.kps >= 8 * kKT) e = d->D == 128 ? launch_ld<128, false>(a, grid, s) : launch_gs<64, true>(a, grid, s);
+        else if (p.kps >= kLongTiles * kKT) e = d->D == 128 ? launch_ld<128, false>(a, grid, s) : launch_gs<64, true>(a, grid, s);
         else                  e = d->D == 128 ? launch_gs<128, false>(a, grid, s) : launch_gs<64, false>(a, grid, s);
         if (e != hipSuccess) return RADAR_HIP_ERROR;
     }
