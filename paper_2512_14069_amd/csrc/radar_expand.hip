@@ -696,14 +696,12 @@ __global__ __launch_bounds__(kTopkThreads) void rerank_kernel(RerankArgs a) {
 // For many sequences per call the single launch above is bound by what every workgroup does around
 // its share of the stream (one workgroup per CU, hand-over and ticket per chunk).  Two launches
 // instead: a streaming kernel of small workgroups (several per CU, out of step with each other)
-// without tickets or hand-over -- a wavefront owns 1024 consecutive logits, the four of a workgroup
-// meet once to leave one top-k list, maximum and sum of exponentials per 4096 logits in the
-// workspace -- then one workgroup per sequence that does what the last workgroup of the single
+// without tickets or hand-over, each of which leaves one top-k list, maximum and sum of exponentials per
+// 4096 logits in the workspace, then one workgroup per sequence that does what the last workgroup of the single
 // launch does.
 constexpr int kStreamThreads = 256;
 constexpr int kStreamWaves = kStreamThreads / kWave;
-constexpr int kStreamWaveLogits = 1024;
-constexpr int kStreamChunk = kStreamWaves * kStreamWaveLogits;
+constexpr int kStreamChunk = kStreamThreads * 16;
 
 // true: the sequence's cycle has stopped (or its state is out of range) and the call leaves it alone
 __device__ __forceinline__ bool cycle_skips(const radar_cycle_state *st, int pool_count_max, int *pool_count) {
@@ -714,18 +712,34 @@ __device__ __forceinline__ bool cycle_skips(const radar_cycle_state *st, int poo
     return false;
 }
 
+constexpr int kStreamHot = 16;                                     // lanes of a wavefront whose logits go through LDS
+constexpr int kStreamCap = 128;                                    // candidates of a chunk; more (runs of equal values) rank per wavefront
+
+struct StreamFast {
+    alignas(16) float dump[kStreamWaves][kStreamHot * 16];
+    uint64_t surv[kStreamCap + 8];
+    unsigned char lane_of[kStreamWaves][kStreamHot];
+};
+
 template <bool VEC4>
 __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(ExpandArgs a) {
-    __shared__ WaveTopkSmem wtk[kStreamWaves];
-    __shared__ uint64_t wlists[kStreamWaves][kWaveListSlots];
-    __shared__ float wave_m[kStreamWaves];
+    __shared__ union {
+        StreamFast fast;
+        struct {
+            WaveTopkSmem wtk[kStreamWaves];
+            uint64_t wlists[kStreamWaves][kWaveListSlots];
+        } ties;
+    } s;
+    __shared__ float gmax[4 * kStreamWaves];                       // maxima of the sixteen 16-lane rows
     __shared__ double wave_l[kStreamWaves];
-    const int lane = lane_id(), w = wave_id();
+    __shared__ unsigned int nsurv;
+    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int row = blockIdx.y;                                    // sequence * F + frontier row
     int unused;
     if (cycle_skips(a.cycle ? a.cycle + row / a.F : nullptr, a.pool_count, &unused)) return;   // the whole workgroup
-    // which 1024 logits of the row; a wavefront past the end of the row sees -inf only and leaves an empty list
-    const int base = blockIdx.x * kStreamChunk + w * kStreamWaveLogits;
+    // sixteen logits per lane, four at a time and all wavefronts side by side: where a row ends inside the chunk,
+    // every wavefront still has some of it
+    const int base = blockIdx.x * kStreamChunk;
     const float *rowp = a.logits + (size_t)row * a.V;
     const int K = a.k;
     // The prediction model's input-free part (w_hh h) of this row's sequence is shared out over the
@@ -741,7 +755,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(Expand
     float4 raw[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-        const int idx0 = base + g * (kWave * 4) + lane * 4;
+        const int idx0 = base + g * (kStreamThreads * 4) + tid * 4;
         if (VEC4) {
             raw[g] = *reinterpret_cast<const float4 *>(rowp + (idx0 < a.V ? idx0 : 0));
         } else {
@@ -756,59 +770,132 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(Expand
     for (int g = 0; g < 4; ++g) {
         x[4 * g + 0] = raw[g].x; x[4 * g + 1] = raw[g].y; x[4 * g + 2] = raw[g].z; x[4 * g + 3] = raw[g].w;
     }
-    if (base + kStreamWaveLogits > a.V) {                          // wave-uniform: the row's last wavefront(s) only
+    if (base + kStreamChunk > a.V) {                               // the row's last chunk only
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int idx = base + (e >> 2) * (kWave * 4) + lane * 4 + (e & 3);
+            const int idx = base + (e >> 2) * (kStreamThreads * 4) + tid * 4 + (e & 3);
             x[e] = idx < a.V ? x[e] : -INFINITY;
         }
     }
+    // ---- the maxima of the sixteen 16-lane rows: the chunk's maximum, and as threshold of its top-k their k-th
+    // largest (at least k logits of the chunk reach it, one per row whose maximum does; on untied data
+    // only about 1.6 k do)
     float tm = x[0];
 #pragma unroll
     for (int e = 1; e < 16; ++e) tm = fmaxf(tm, x[e]);
-    const float wm = wave_max_f32(tm);
+    float rm = tm;
+    rm = fmaxf(rm, dpp_f32<0xB1>(rm));
+    rm = fmaxf(rm, dpp_f32<0x4E>(rm));
+    rm = fmaxf(rm, dpp_f32<0x141>(rm));
+    rm = fmaxf(rm, dpp_f32<0x140>(rm));
+    if ((lane & 15) == 0) gmax[w * 4 + (lane >> 4)] = rm;
+    if (threadIdx.x == 0) nsurv = 0;
+    __syncthreads();
+    const float g16 = gmax[lane & 15];
+    float cm = g16;
+    cm = fmaxf(cm, dpp_f32<0xB1>(cm));
+    cm = fmaxf(cm, dpp_f32<0x4E>(cm));
+    cm = fmaxf(cm, dpp_f32<0x141>(cm));
+    cm = fmaxf(cm, dpp_f32<0x140>(cm));
     float tl = 0.f;
-    if (wm > -INFINITY) {
+    if (cm > -INFINITY) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) tl += __builtin_amdgcn_exp2f((x[e] - wm) * kLog2eF);
+        for (int e = 0; e < 16; ++e) tl += __builtin_amdgcn_exp2f((x[e] - cm) * kLog2eF);
     }
     const double wl = wave_sum_f64((double)tl);
+    if (lane == 0) wave_l[w] = wl;
+    const uint32_t ov = ord_of(g16);
+    int larger = 0;                                                // ties: all of them rank with the first
+    count_larger<1>(ov, larger);
+    uint32_t c = larger < K ? ov : 0xffffffffu;
+    c = min(c, dpp_u32<0xB1>(c));
+    c = min(c, dpp_u32<0x4E>(c));
+    c = min(c, dpp_u32<0x141>(c));
+    c = min(c, dpp_u32<0x140>(c));
+    const float tau = float_of_ord(c);
 
-    // the wavefront's candidates (unranked; ranked only where more than 32 of them pass the threshold)
-    {
-        uint64_t *list = &wlists[w][0];
-        if (!wave_candidates_counted<16>(x, tm, uint32_t(base + lane * 4), uint32_t(kWave * 4), uint32_t(a.V), K, list)) {
-            uint64_t k1[8], k2[9];
+    // ---- Lanes whose largest logit reaches the threshold (about 1.6 k of the 256) leave all their logits in
+    // LDS; their wavefront compares those one per lane and appends what passes to the chunk's list.  (A
+    // threshold per wavefront and a comparison of every logit with it were 150 instructions, a sixth of the time.)
+    const bool hot = tm >= tau && base + tid * 4 < a.V;           // (a lane wholly past the row holds -inf only)
+    const uint64_t hm = __ballot(hot);
+    const int nhot = __popcll(hm);
+    if (nhot > kStreamHot) {
+        if (lane == 0) atomicAdd(&nsurv, kStreamCap + 1u);         // long runs of equal values
+    } else if (nhot > 0) {
+        float *const dump = s.fast.dump[w];
+        if (hot) {
+            const int at = lanes_below(hm);
+            float4 *d4 = reinterpret_cast<float4 *>(dump + at * 16);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int idx = base + (e >> 2) * (kWave * 4) + lane * 4 + (e & 3);
-                const uint64_t key = idx < a.V ? make_key(x[e], uint32_t(idx)) : 0;
-                if (e < 8) k1[e] = key; else k2[e - 8] = key;
+            for (int g = 0; g < 4; ++g) d4[g] = make_float4(x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]);
+            s.fast.lane_of[w][at] = (unsigned char)lane;
+        }
+        wave_lds_sync();
+        for (int d0 = 0; d0 < nhot; d0 += 4) {                     // four lanes' logits at a time
+            const int d = d0 + (lane >> 4), e = lane & 15;
+            const bool live = d < nhot;
+            const float v = dump[min(d, nhot - 1) * 16 + e];
+            const int idx = base + (e >> 2) * (kStreamThreads * 4) + (w * kWave + (int)s.fast.lane_of[w][min(d, nhot - 1)]) * 4 + (e & 3);
+            const uint64_t m = __ballot(live && v >= tau && idx < a.V);
+            if (m != 0) {
+                int at = 0;
+                if (lane == 0) at = (int)atomicAdd(&nsurv, (unsigned int)__popcll(m));
+                at = (int)readlane_u32((uint32_t)at, 0) + lanes_below(m);
+                if (((m >> lane) & 1) && at < kStreamCap) s.fast.surv[at] = make_key(v, uint32_t(idx));
             }
-            k2[8] = wave_topk<8>(k1, K, wtk[w]);
-            const uint64_t wt = wave_topk<9>(k2, K, wtk[w]);
-            if (lane < kWaveListSlots) list[lane] = wt;            // lanes 16.. hold 0
         }
     }
-    if (lane == 0) { wave_m[w] = wm; wave_l[w] = wl; }
     __syncthreads();
     const size_t slot = (size_t)row * a.nchunks + blockIdx.x;
-    if (w == 0) {                                                              // the chunk's list: top-k of the four lists
-        constexpr int NS = kStreamWaves * kWaveListSlots / kWave;
-        uint64_t kk[NS];
+    const int n = (int)nsurv;
+    if (n > kStreamCap) {
+        // Long runs of equal values: every wavefront ranks its own logits exactly, then one ranks the four lists.
+        __syncthreads();                                           // the short path's LDS is overlaid
+        uint64_t k1[8], k2[9];
 #pragma unroll
-        for (int e = 0; e < NS; ++e) kk[e] = (&wlists[0][0])[topk_slot_of(e)];   // rotated: the used slots lead each list
-        const uint64_t ctop = wave_topk<NS>(kk, K, wtk[0]);
-        if (lane < RADAR_K_MAX) a.part_keys[slot * RADAR_K_MAX + lane] = ctop;    // 0 beyond the k-th
-    } else if (w == 1 && lane == 0) {                                          // fixed order of addition
-        float m = wave_m[0];
+        for (int e = 0; e < 16; ++e) {
+            const int idx = base + (e >> 2) * (kStreamThreads * 4) + tid * 4 + (e & 3);
+            const uint64_t key = idx < a.V ? make_key(x[e], uint32_t(idx)) : 0;
+            if (e < 8) k1[e] = key; else k2[e - 8] = key;
+        }
+        k2[8] = wave_topk<8>(k1, K, s.ties.wtk[w]);
+        const uint64_t wt = wave_topk<9>(k2, K, s.ties.wtk[w]);
+        if (lane < kWaveListSlots) s.ties.wlists[w][lane] = wt;    // lanes 16.. hold 0
+        __syncthreads();
+        if (w == 0) {
+            constexpr int NS = kStreamWaves * kWaveListSlots / kWave;
+            uint64_t kk[NS];
 #pragma unroll
-        for (int i = 1; i < kStreamWaves; ++i) m = fmaxf(m, wave_m[i]);
+            for (int e = 0; e < NS; ++e) kk[e] = (&s.ties.wlists[0][0])[e * kWave + ((lane + 4 * e) & (kWave - 1))];
+            const uint64_t ctop = wave_topk<NS>(kk, K, s.ties.wtk[0]);
+            if (lane < RADAR_K_MAX) a.part_keys[slot * RADAR_K_MAX + lane] = ctop;    // 0 beyond the k-th
+        }
+    } else if (w == 0) {
+        // exact ranks among the chunk's candidates: every lane counts the larger keys with broadcast reads
+        uint64_t *const surv = s.fast.surv;
+        if (lane < 8) surv[n + lane] = 0;                          // padding for the grouped reads
+        wave_lds_sync();
+        for (int i0 = 0; i0 < n; i0 += kWave) {                    // one pass unless there are many ties
+            const int i = i0 + lane;
+            const uint64_t key = surv[min(i, n - 1)];
+            int rank = 0;
+            for (int q = 0; q < n; q += 8) {
+                uint64_t kj[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) kj[u] = surv[q + u];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) rank += (kj[u] > key) ? 1 : 0;
+            }
+            if (i < n && rank < K) a.part_keys[slot * RADAR_K_MAX + rank] = key;
+        }
+        if (lane >= n && lane < K) a.part_keys[slot * RADAR_K_MAX + lane] = 0;     // fewer than K in the chunk
+    }
+    if (w == 1 && lane == 0) {                                     // fixed order of addition
         double l = 0.0;
 #pragma unroll
-        for (int i = 0; i < kStreamWaves; ++i)
-            if (wave_m[i] > -INFINITY) l += wave_l[i] * (double)__builtin_amdgcn_exp2f((wave_m[i] - m) * kLog2eF);
-        a.part_m[slot] = m;
+        for (int i = 0; i < kStreamWaves; ++i) l += wave_l[i];
+        a.part_m[slot] = cm;
         a.part_l[slot] = l;
     }
 }

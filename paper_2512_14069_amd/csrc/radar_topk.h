@@ -149,22 +149,6 @@ __device__ __forceinline__ uint32_t quad_threshold(uint32_t v, int K) {
 }
 
 
-// For the throughput of many wavefronts side by side: the same by sixteen lane reads, fewer vector
-// instructions (where a wavefront's own chain of steps counts, quad_threshold is the shorter one).
-__device__ __forceinline__ uint32_t quad_threshold_many(uint32_t v, int K) {
-    uint32_t g = v;
-    g = max(g, dpp_u32<0xB1>(g));
-    g = max(g, dpp_u32<0x4E>(g));                 // quad maximum in every lane of the quad
-    int larger = 0;                               // quads whose maximum is strictly larger than this lane's
-#pragma unroll
-    for (int q = 0; q < 16; ++q) larger += (readlane_u32(g, 4 * q) > g) ? 1 : 0;
-    uint32_t c = larger < K ? g : 0xffffffffu;    // the K largest quad maxima (and their ties) stay
-    c = min(c, dpp_u32<0x141>(c));
-    c = min(c, dpp_u32<0x140>(c));                // smallest of them within the 16-lane row
-    const uint32_t t = min(min(readlane_u32(c, 0), readlane_u32(c, 16)), min(readlane_u32(c, 32), readlane_u32(c, 48)));
-    return max(t, 1u);
-}
-
 struct WaveTopkSmem {
     uint64_t surv[kWave * kWaveTopkMaxEPL + 8];   // +8: the ranking reads keys eight at a time
     uint64_t top[16];
@@ -209,43 +193,7 @@ __device__ __forceinline__ uint64_t wave_topk(const uint64_t (&keys)[EPL], int K
     return lane < 16 ? r : 0;
 }
 
-// Candidates for a later selection, without ranking them: every element of the wavefront whose value
-// reaches tau = the K-th largest quad maximum (so the wavefront's K largest are among them), as
-// proper keys in list[0..32), 0 where there are fewer.  x[e] is element e of the lane (-inf where it
-// lies past the row), its index is idx0 + (e / 4) * gstride + e % 4, indices of a lane ascend with
-// e.  The survivors are counted first (comparison masks stay in scalar registers), and keys are only
-// built for them (about K + 4 of them on random data).  Returns false, with list untouched, when more
-// than 32 survive (long runs of equal values): the caller then ranks with wave_topk.  All 64 lanes must
-// call; list is wavefront-private LDS.
-constexpr int kWaveListSlots = 32;
-
-template <int EPL>
-__device__ __forceinline__ bool wave_candidates_counted(const float (&x)[EPL], float lane_max, uint32_t idx0, uint32_t gstride,
-                                                        uint32_t V, int K, uint64_t *list) {
-    static_assert(EPL <= 16, "masks");
-    const int lane = lane_id();
-    const uint32_t tau = quad_threshold_many(idx0 < V ? ord_of(lane_max) : 0u, K);
-    const float tau_f = tau < 0x00800000u ? -INFINITY : float_of_ord(tau);
-    uint64_t m[EPL];
-    int total = 0;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        const uint32_t idx = idx0 + (uint32_t)(e >> 2) * gstride + (uint32_t)(e & 3);
-        m[e] = __ballot(x[e] >= tau_f && idx < V);
-        total += __popcll(m[e]);
-    }
-    if (total > kWaveListSlots) return false;
-    if (lane < kWaveListSlots) list[lane] = 0;
-    wave_lds_sync();
-    int n = 0;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        const uint32_t idx = idx0 + (uint32_t)(e >> 2) * gstride + (uint32_t)(e & 3);
-        if ((m[e] >> lane) & 1) list[n + lanes_below(m[e])] = make_key(x[e], idx);
-        n += __popcll(m[e]);
-    }
-    return true;
-}
+constexpr int kWaveListSlots = 32;               // a wavefront's list in LDS
 
 // Lists of 16 slots of which the first K are used (slot i: list i / 16, rank i % 16), taken 64
 // slots per step: which slot a lane takes at step e.  Lanes rotate by 4 per step, so a lane
