@@ -372,7 +372,7 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_walk_kernel(AqArgs a) {
 // next child.  (It loads no rows: a wavefront's loads return in order, and a poll would wait for them.)
 //
 // Every workgroup takes the same decisions from the same numbers, added in the same order.  At a meeting
-// a workgroup stores up to four 8-byte words, each with the meeting's number in its low byte, and polls
+// a workgroup stores two or four 8-byte words, each with the meeting's number in its low byte, and polls
 // all workgroups' words until they carry that number: the values need no counter to vouch for them, no
 // acknowledgement is awaited and nothing is fetched afterwards.  Two sets of words alternate; one is
 // written again only after everyone has read the set after it.
@@ -399,8 +399,13 @@ union CoLds {
     AqSmem alone;
 };
 
+// A double travels whole: its low byte, which the meeting's number replaces in the first word of a pair, sits
+// above that number in the second, whose upper half is free for a float.
 __device__ __forceinline__ uint64_t word_of_f64(double v, unsigned int tag) { return ((uint64_t)__double_as_longlong(v) & ~0xffull) | tag; }
-__device__ __forceinline__ double f64_of_word(uint64_t w) { return __longlong_as_double((long long)(w & ~0xffull)); }
+__device__ __forceinline__ uint64_t word_of_rest(double v, float m, unsigned int tag) {
+    return ((uint64_t)__float_as_uint(m) << 32) | (((uint64_t)__double_as_longlong(v) & 0xffull) << 8) | tag;
+}
+__device__ __forceinline__ double f64_of_words(uint64_t w, uint64_t rest) { return __longlong_as_double((long long)((w & ~0xffull) | ((rest >> 8) & 0xffull))); }
 __device__ __forceinline__ uint64_t word_of_f32(float v, unsigned int tag) { return ((uint64_t)__float_as_uint(v) << 32) | tag; }
 __device__ __forceinline__ float f32_of_word(uint64_t w) { return __uint_as_float((uint32_t)(w >> 32)); }
 
@@ -549,18 +554,21 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
             half_merge(has ? m0 : -INFINITY, has ? l0 : 0.0, inv_half, &m, &l);
             if (i == 0 && (which ? with_q : with_p)) {
                 store_shared_result(&mine[2 * which], word_of_f64(l, tag));
-                store_shared_result(&mine[2 * which + 1], word_of_f32(m, tag));
+                store_shared_result(&mine[2 * which + 1], word_of_rest(l, m, tag));
             }
         }
         if (with_u) {
             double t = 0.0;
 #pragma unroll
             for (int i = 0; i < kAqWaves; ++i) t += s.wsum[i];
-            if (lane == 0) store_shared_result(&mine[0], word_of_f64(t, tag));
+            if (lane == 0) {
+                store_shared_result(&mine[0], word_of_f64(t, tag));
+                store_shared_result(&mine[1], word_of_rest(t, 0.f, tag));
+            }
         }
         const int from = lane & 31, which = lane >> 5;
         const uint64_t *theirs = words + ((size_t)set * kCoG + min(from, G - 1)) * kCoWords + 2 * which;
-        const bool first = from < G && (which ? with_q : (with_p || with_u)), second = from < G && (which ? with_q : with_p);
+        const bool has_theirs = from < G && (which ? with_q : (with_p || with_u));
         const bool sib = (rest >> lane) & 1;
         uint64_t a0, a1, as;
         for (unsigned int spins = 0;;) {
@@ -568,7 +576,7 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
             a1 = load_shared_result(&theirs[1]);
             as = load_shared_result(&sibs[set * kWave + lane]);
             const unsigned int given_up = load_shared_result(&ctl[16]);
-            const bool ok = (!first || (a0 & 0xff) == tag) && (!second || (a1 & 0xff) == tag) && (!sib || (as & 0xff) == tag);
+            const bool ok = (!has_theirs || ((a0 & 0xff) == tag && (a1 & 0xff) == tag)) && (!sib || (as & 0xff) == tag);
             if (__ballot(!ok) == 0) break;
             if (++spins > a.co_spin_limit || given_up != 0u) {
                 if (lane == 0) store_shared_result(&ctl[16], 1u);
@@ -579,12 +587,13 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
         if (with_p || with_q) {
             float m;
             double l;
-            half_merge(second ? f32_of_word(a1) : -INFINITY, second ? f64_of_word(a0) : 0.0, inv_half, &m, &l);
+            const bool row = from < G && (which ? with_q : with_p);
+            half_merge(row ? f32_of_word(a1) : -INFINITY, row ? f64_of_words(a0, a1) : 0.0, inv_half, &m, &l);
             if (with_p) { pm = readlane_f32(m, 0); pl = readlane_f64(l, 0); }
             if (with_q) { qm = readlane_f32(m, 32); ql = readlane_f64(l, 32); }
         }
         if (with_u) {
-            psum = lane < G ? f64_of_word(a0) : 0.0;
+            psum = lane < G ? f64_of_words(a0, a1) : 0.0;
             W = wave_sum_f64(psum);
         }
         if (sib) px = (double)f32_of_word(as);

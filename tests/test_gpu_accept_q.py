@@ -158,6 +158,28 @@ def test_identical_distributions_and_point_mass(oracle):
         assert np.array_equal(host(p), host(q)) and np.array_equal(host(p), r)
 
 
+def test_sums_pass_between_workgroups_whole(oracle):
+    """A mass of 2^-48 of its row's decides an acceptance test and a bonus draw: the sums that the workgroups of a
+    walk exchange are doubles to the last bit (53 significant bits; 45 would lose it)."""
+    from paper_2512_14069_amd import binding as b
+    V, little = 8192, -33.27                                     # four workgroups; exp(-33.27) = 2^-48, the smallest mass here
+    x = np.full((2, 2, V), -1000.0, np.float32)
+    y = x.copy()
+    x[:, :, [0, 2048]] = 0.0                                     # p = 1/2 at a token of the first and of the second workgroup
+    x[1, 0, 5] = little
+    y[:, :, 0] = 0.0
+    y[:, :, 5] = little                                          # q(0) = 1 / (1 + 2^-48)
+    parents, tokens = np.array([[-1, 0], [-1, -1]], np.int32), np.array([[9, 0], [9, 0]], np.int32)
+    n_nodes, uniforms = np.array([2, 1], np.int32), np.full((2, 3), 0.5, np.float32)
+    # sequence 0: 1/2 q(0) < p(0) holds by 2^-49.  sequence 1: no child; the cumulated mass passes 1/2 at token 5, by 2^-50.
+    ref = oracle.verify_accept_q(x, y, tokens, parents, n_nodes, uniforms)
+    assert ref[0].tolist() == [1, 0] and ref[2][1] == 5
+    for limit in (0, -1, 1):
+        got = b.radar_verify_accept_q(*map(dev, (x, y, tokens, parents, n_nodes, uniforms)), walk_spin_limit=limit)
+        assert host(got[0]).tolist() == [1, 0], limit
+        assert host(got[2])[1] == 5, limit
+
+
 def test_workspace_reuse_prepared_call_and_errors(oracle):
     from paper_2512_14069_amd import binding as b
     V, T, B = 9000, 12, 5
