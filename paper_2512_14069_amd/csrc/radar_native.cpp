@@ -8,10 +8,13 @@
 // sequence.  Here the same work is 1-2 us.
 //
 // Every function returns None whenever something is not as it expects (a tensor on another device or
-// of another type, a shape that does not fit, an error status).  Nothing has been launched then, and
-// the caller goes on with its own, slower path, which raises the exact error.
+// of another type, a shape that does not fit, an error status), also where torch reports it by a C++
+// exception: no memory for an output, a tensor without storage, no device to take a stream from.
+// Nothing has been launched then, and the caller goes on with its own, slower path, which raises the
+// exact error.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
+#include <cxxabi.h>
 #include <dlfcn.h>
 
 #include <ATen/ATen.h>
@@ -63,7 +66,7 @@ public:
     void workspace(void **p, size_t *bytes) {
         *p = nullptr; *bytes = 0;
         PyObject *o = next();
-        if (o == nullptr || o == Py_None) return;
+        if (!ok || o == Py_None) return;
         if (!THPVariable_Check(o)) { fail(); return; }
         const at::Tensor &t = THPVariable_Unpack(o);
         *p = t.data_ptr();
@@ -108,12 +111,33 @@ private:
 void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
 // The library call itself, with the interpreter lock released (a full queue can hold a launch up).
+// (The lock is taken back outside of any handler or destructor: a thread that the interpreter ends at
+// shutdown is unwound from there.)
 template <typename Fn, typename... A>
 radar_status call(Fn fn, A... a) {
     PyThreadState *const held = PyEval_SaveThread();
-    const radar_status rc = fn(a...);
+    radar_status rc;
+    try {
+        rc = fn(a...);
+    } catch (...) {
+        rc = RADAR_HIP_ERROR;
+    }
     PyEval_RestoreThread(held);
     return rc;
+}
+
+// An entry point as Python calls it: no C++ exception leaves it, one becomes None.
+using Entry = PyObject *(PyObject *, PyObject *const *, Py_ssize_t);
+template <Entry *entry>
+PyObject *guarded(PyObject *self, PyObject *const *args, Py_ssize_t n) {
+    try {
+        return entry(self, args, n);
+    } catch (abi::__forced_unwind &) {           // the thread is being ended: not an error, and not to be swallowed
+        throw;
+    } catch (...) {
+        PyErr_Clear();                           // a tensor subclass may have raised in Python on the way
+        Py_RETURN_NONE;
+    }
 }
 
 PyObject *done(radar_status rc, PyObject *result = Py_True) {
@@ -246,7 +270,11 @@ struct AcceptOutputs {
         if (rc != RADAR_OK) Py_RETURN_NONE;
         if (given) Py_RETURN_TRUE;
         PyObject *t = PyTuple_New(3);
-        for (int i = 0; t && i < 3; ++i) PyTuple_SET_ITEM(t, i, THPVariable_Wrap(std::move(own[i])));
+        for (int i = 0; t && i < 3; ++i) {
+            PyObject *o = THPVariable_Wrap(std::move(own[i]));
+            if (o == nullptr) { Py_DECREF(t); return nullptr; }
+            PyTuple_SET_ITEM(t, i, o);
+        }
         return t;
     }
 };
@@ -265,7 +293,7 @@ PyObject *verify_accept(PyObject *, PyObject *const *args, Py_ssize_t n) {
     r.workspace(&ws, &ws_bytes);
     if (!r.ok || x->dim() != 3 || d.D_max < 0) Py_RETURN_NONE;
     d.B = (int32_t)x->size(0); d.T_max = (int32_t)x->size(1); d.V = (int32_t)x->size(2);
-    o.allocate(*x, d.B, d.D_max + 1);
+    o.allocate(*x, d.B, (int64_t)d.D_max + 1);
     return o.result(call(lib.verify_accept, Reader::pointer<float>(x), tok, par, nn, uni, o.len, o.path, o.bonus, &d, ws, ws_bytes, stream()));
 }
 
@@ -285,7 +313,7 @@ PyObject *verify_accept_q(PyObject *, PyObject *const *args, Py_ssize_t n) {
     if (!r.ok || x->dim() != 3 || y->dim() != 3 || d.D_max < 0) Py_RETURN_NONE;
     d.B = (int32_t)x->size(0); d.T_max = (int32_t)x->size(1); d.V = (int32_t)x->size(2); d.Tq = (int32_t)y->size(1);
     if (y->size(0) != d.B || y->size(2) != d.V || uni->dim() != 2 || uni->size(0) != d.B || uni->size(1) != d.T_max + 1) Py_RETURN_NONE;
-    o.allocate(*x, d.B, d.D_max + 1);
+    o.allocate(*x, d.B, (int64_t)d.D_max + 1);
     return o.result(call(lib.verify_accept_q, Reader::pointer<float>(x), Reader::pointer<float>(y), qr, tok, par, nn, Reader::pointer<float>(uni),
                                         o.len, o.path, o.bonus, &d, ws, ws_bytes, stream()));
 }
@@ -304,7 +332,7 @@ PyObject *accept_length_distribution(PyObject *, PyObject *const *args, Py_ssize
     if (!r.ok || x->dim() != 3 || d.D_max < 0) Py_RETURN_NONE;
     d.B = (int32_t)x->size(0); d.T_max = (int32_t)x->size(1); d.V = (int32_t)x->size(2);
     at::Tensor fresh;
-    if (out == nullptr) { fresh = at::empty({d.B, d.D_max + 1}, x->options().dtype(at::kDouble)); out = &fresh; }
+    if (out == nullptr) { fresh = at::empty({d.B, (int64_t)d.D_max + 1}, x->options().dtype(at::kDouble)); out = &fresh; }
     const radar_status rc = call(lib.accept_length_distribution, Reader::pointer<float>(x), tok, par, nn, Reader::pointer<double>(out), &d, ws, ws_bytes, stream());
     if (rc != RADAR_OK) Py_RETURN_NONE;
     return fresh.defined() ? THPVariable_Wrap(std::move(fresh)) : done(rc, out_obj);
@@ -356,7 +384,7 @@ PyObject *bind(PyObject *, PyObject *path) {
     Py_RETURN_NONE;
 }
 
-#define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
+#define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&guarded<name>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
     FAST(tree_attention), FAST(draft_expand), FAST(draft_rerank), FAST(verify_accept), FAST(verify_accept_q),
     FAST(accept_length_distribution), FAST(policy_step),
