@@ -94,6 +94,11 @@ __device__ __forceinline__ int vs_off(int row, int chunk) {
     return row * (D * 2) + ((chunk ^ ((row & 3) << 2)) << 4);
 }
 
+// Rows of the prefix: at most the cache's, so that the tree's rows can be added in 32 bits for any content of
+// ctx_lens (a length near 2^31 would wrap, and the sequence seem empty to one kernel and not to the next).
+// Where the prefix fills the cache nothing is left for the tree, as before.  Negative: no such sequence.
+__device__ __forceinline__ int prefix_rows(const AttnArgs &a, int b) { return min(a.ctx_lens[b], a.S); }
+
 // v = keep ? v : 0 without a branch (a select after a load tempts the compiler into a
 // conditional load, and conditional loads into register arrays wreck register allocation)
 __device__ __forceinline__ void and_mask(u32x4 &v, bool keep) {
@@ -422,7 +427,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(AttnArgs a) {
             qop[st] = __builtin_bit_cast(bf16x8, raw);
         }
     }
-    const int L = a.ctx_lens[b];
+    const int L = prefix_rows(a, b);
     int nn = a.n_nodes ? a.n_nodes[b] : a.T;
     nn = max(1, min(nn, a.T));
     const int total = min(L + nn, a.S);                  // never read past the cache the caller described
@@ -517,7 +522,7 @@ __device__ __forceinline__ bool flat_shared(const AttnArgs &a, int nn) {
 __device__ __forceinline__ FlatPlan flat_plan(const AttnArgs &a) {
     FlatPlan f;
     const int lane = lane_id(), b = min(lane, a.B - 1);
-    f.L = a.ctx_lens[b];
+    f.L = prefix_rows(a, b);
     f.nn = a.n_nodes ? a.n_nodes[b] : a.T;
     f.nn = max(1, min(f.nn, a.T));
     const int rows = min(f.L + f.nn, a.S);
@@ -710,7 +715,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
     } else {
         const int sp = blockIdx.x;
         pc.b = blockIdx.z / a.n_ublk; pc.hk = blockIdx.y;
-        pc.L = a.ctx_lens[pc.b];
+        pc.L = prefix_rows(a, pc.b);
         pc.nn = a.n_nodes ? a.n_nodes[pc.b] : a.T;
         pc.nn = max(1, min(pc.nn, a.T));
         const int total = min(pc.L + pc.nn, a.S);
@@ -881,7 +886,7 @@ __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(AttnA
     __shared__ float red[E > 1 ? E - 1 : 1][10][kAttnThreads];
     constexpr int SL = 32, DQ = 8;                          // slice width, floats per lane
     const int slice = blockIdx.x % (D / SL), h = blockIdx.x / (D / SL), b = blockIdx.y;
-    const int L = a.ctx_lens[b];
+    const int L = prefix_rows(a, b);
     int nn = a.n_nodes ? a.n_nodes[b] : a.T;
     nn = max(1, min(nn, a.T));
     const int hk = h / a.G, g = h - hk * a.G;

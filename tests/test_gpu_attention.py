@@ -155,6 +155,31 @@ def test_rows_dealt_out_on_the_device(oracle, name):
         assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)
 
 
+@pytest.mark.parametrize("D,S,kps", [(128, 300, 0), (128, 300, 64), (64, 1300, 1024), (128, 1300, 1024), (128, 41000, 0)])
+def test_context_lengths_past_the_cache_are_cut_to_it(D, S, kps):
+    """Lengths up to 2^31 - 1 (which wrap when the tree's rows are added): the rows that the caller described are
+    attended to, by every path, and the tree has none.  One workspace, which holds another call's partials.
+    Bound: as check_close, on both paths' arithmetic."""
+    from paper_2512_14069_amd import binding as b
+    g = torch.Generator().manual_seed(S + kps)
+    q, kc, vc = (torch.randn(s, generator=g).to(torch.bfloat16) for s in ((3, 40, 4, D), (3, 2, S, D), (3, 2, S, D)))
+    p = torch.einsum("btgd,bsd->btgs", q[:, :, :2].double(), kc[:, 0].double()).div(D ** 0.5).softmax(-1)
+    want = torch.einsum("btgs,bsd->btgd", p, vc[:, 0].double())                 # the first KV head's two query heads
+    par, nn = dev(np.tile(synth.chain_tree(40), (3, 1))), dev(np.array([40, 1, 33], np.int32))
+    qd, kd, vd = q.cuda(), kc.cuda(), vc.cuda()
+    ws = b.new_workspace(b.radar_tree_attention_workspace_bytes(b.attn_desc(qd, kd, keys_per_split=kps)))
+    attend = lambda ctx: b.radar_tree_attention(qd, kd, vd, par, dev(np.array(ctx, np.int32)), nn, workspace=ws, keys_per_split=kps,
+                                                out=torch.full(q.shape, 3.0, dtype=torch.bfloat16, device="cuda"))
+    full = attend([S, S, S])
+    attend([S - 40, 0, 7])
+    past = attend([2 ** 31 - 1, 2 ** 31 - 2, S + 1])
+    assert torch.equal(full, past)
+    for i, n in enumerate((40, 1, 33)):
+        assert torch.all(past[i, n:] == 0)
+        err = (past[i, :n, :2].double().cpu() - want[i, :n]).abs()
+        assert torch.all(err <= ABS_TIGHT + REL_TIGHT * want[i, :n].abs())
+
+
 def test_chain_and_star_trees_depth_63(oracle):
     from paper_2512_14069_amd import binding as b
     a = shape(2, 4, 1, 128, 64, [100, 31], [64, 64], [8, 8], k=10)
