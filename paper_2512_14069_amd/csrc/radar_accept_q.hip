@@ -58,6 +58,9 @@ __device__ __forceinline__ double exp_rel(float x, float m, double inv_temp) {
 // the same in fp32 throughout (relative error about 1e-7 per unit of |x - m| * inv_temp)
 __device__ __forceinline__ float exp_rel_f32(float x, float m, float inv_temp) { return __expf((x - m) * inv_temp); }
 
+// a value that is the same in every lane (read from LDS, say), kept in a scalar register
+__device__ __forceinline__ int uniform_of(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // sum over the workgroup of one double per thread, fixed order; every thread gets it
 __device__ __forceinline__ double block_sum_f64(double v, double *wred) {
     const double ws = wave_sum_f64(v);
@@ -413,7 +416,7 @@ template <bool VEC4, int R>
 __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
     __shared__ CoLds lds;
     CoSmem &s = lds.s;
-    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    const int tid = threadIdx.x, lane = lane_id(), w = uniform_of(wave_id());
     const bool control = w == kAqWaves;
     const int g = blockIdx.x, G = gridDim.x, b = blockIdx.y;
     constexpr int slice = R * kAqStream * 4;
@@ -450,26 +453,31 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
 
     const float it_f = (float)a.inv_t, itd_f = (float)a.inv_td;
     // this lane's tokens: float4 r covers lo + (r * 512 + tid) * 4 .. + 3
+    // (made anew for every row: the offsets and end-of-row masks of 4 R tokens are not worth keeping through the walk)
+    auto first_token = [&]() { int i = lo + tid * 4; asm volatile("" : "+v"(i)); return i; };
     auto load_row = [&](const float *row, float (&x)[R][4]) {
+        const int at = first_token();
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int i0 = lo + (r * kAqStream + tid) * 4;
+            const int i0 = at + r * kAqStream * 4;
             if (VEC4) {
-                const float4 v = *reinterpret_cast<const float4 *>(row + (i0 < a.V ? i0 : 0));
+                const float4 v = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(row) + (uint32_t)(i0 < a.V ? i0 : 0) * 4u);
                 x[r][0] = v.x; x[r][1] = v.y; x[r][2] = v.z; x[r][3] = v.w;
             } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) x[r][j] = row[min(i0 + j, a.V - 1)];
+                for (int j = 0; j < 4; ++j)
+                    x[r][j] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(row) + (uint32_t)min(i0 + j, a.V - 1) * 4u);
             }
         }
     };
     // tokens past the vocabulary (in the last slice only) are -inf from here on: no mass in a row, none in a residual
     auto settle = [&](float (&x)[R][4]) {
         if (lo + slice <= a.V) return;
+        const int at = first_token();
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[r][j] = lo + (r * kAqStream + tid) * 4 + j < a.V ? x[r][j] : -INFINITY;
+            for (int j = 0; j < 4; ++j) x[r][j] = at + r * kAqStream * 4 + j < a.V ? x[r][j] : -INFINITY;
     };
     auto wave_stats = [&](const float (&x)[R][4], double inv, int which) {
         float m = -INFINITY;
@@ -566,7 +574,9 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
                 store_shared_result(&mine[1], word_of_rest(t, 0.f, tag));
             }
         }
-        const int from = lane & 31, which = lane >> 5;
+        int from = lane & 31;
+        const int which = lane >> 5;
+        asm volatile("" : "+v"(from));                    // addresses made here and not kept through the walk
         const uint64_t *theirs = words + ((size_t)set * kCoG + min(from, G - 1)) * kCoWords + 2 * which;
         const bool has_theirs = from < G && (which ? with_q : (with_p || with_u));
         const bool sib = (rest >> lane) & 1;
@@ -617,13 +627,46 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
     };
     auto give_up = [&]() { if (lane == 0) s.cmd = kCoAbort; };
 
+    // The control wavefront and the streaming ones run loops of their own with the same barriers, command by
+    // command: the registers of a row and the state of the tests are never held by the same code.  (In one loop, with
+    // a row's addresses and end-of-row masks kept through the walk as well, eight float4 per lane spilled 69 registers,
+    // 154 without 16-byte loads: 24 sequences of V = 128256 70 us and now 54, 20 of 128257 110 and 72.)
     int cur = 0, len = 0, cmd;
     bool rejected = false;
-    if (!control) look_ahead(0, 0);
-    for (;;) {                                            // one iteration per visited node
-        uint64_t kids = kids_of(cur, len);
-        rejected = false;
-        if (!control) {
+    if (control) {
+        for (;;) {                                        // one iteration per visited node
+            uint64_t kids = kids_of(cur, len);
+            rejected = false;
+            __syncthreads();
+            if (meet(true, kids != 0, false, 0)) {
+                W = 1.0;
+                px = exp_rel(s.gx[lane], pm, a.inv_t) * (1.0 / pl);
+                decide(kids, false, true, kids != 0);
+            } else {
+                give_up();
+            }
+            ++meetings;
+            __syncthreads();
+            while ((cmd = uniform_of(s.cmd)) == kCoReject) {
+                const int c = uniform_of(s.arg);
+                kids &= ~(1ull << c);
+                const bool other_q = kids != 0 && qrow_of(first_of(kids)) != qrow_of(c);
+                rejected = true;
+                __syncthreads();
+                if (meet(false, other_q, true, kids)) decide(kids, true, false, other_q);
+                else give_up();
+                ++meetings;
+                __syncthreads();
+            }
+            if (cmd != kCoAccept) break;
+            cur = uniform_of(s.arg);
+            ++len;
+        }
+    } else {
+        look_ahead(0, 0);
+        for (;;) {
+            uint64_t kids = kids_of(cur, len);
+            rejected = false;
             if constexpr (kAhead) {
 #pragma unroll
                 for (int r = 0; r < R; ++r)
@@ -641,28 +684,16 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
                 settle(q);
                 wave_stats(q, a.inv_td, 1);
             }
-        }
-        __syncthreads();
-        if (!control) {
+            __syncthreads();
             if (kids != 0) look_ahead(first_of(kids), len + 1);
-        } else {
-            if (meet(true, kids != 0, false, 0)) {
-                W = 1.0;
-                px = exp_rel(s.gx[lane], pm, a.inv_t) * (1.0 / pl);
-                decide(kids, false, true, kids != 0);
-            } else {
-                give_up();
-            }
-        }
-        ++meetings;
-        __syncthreads();
-        while ((cmd = s.cmd) == kCoReject) {
-            // Eq. 2: u <- max(0, u - W q), then the next child (whose draft row may be another one)
-            const int c = s.arg;
-            kids &= ~(1ull << c);
-            const int next = kids != 0 ? first_of(kids) : -1;
-            const bool other_q = next >= 0 && qrow_of(next) != qrow_of(c);
-            if (!control) {
+            ++meetings;
+            __syncthreads();
+            while ((cmd = uniform_of(s.cmd)) == kCoReject) {
+                // Eq. 2: u <- max(0, u - W q), then the next child (whose draft row may be another one)
+                const int c = uniform_of(s.arg);
+                kids &= ~(1ull << c);
+                const int next = kids != 0 ? first_of(kids) : -1;
+                const bool other_q = next >= 0 && qrow_of(next) != qrow_of(c);
                 const float m_p = s.pm, il_p = s.pinv_l, m_q = s.qm, il_q = s.qinv_l, W_f = s.W;
                 if (!q_ready) {
 #pragma unroll
@@ -699,22 +730,17 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
                 }
                 wave_mass(x);
                 if (other_q) { settle(q); wave_stats(q, a.inv_td, 1); }
-            }
-            rejected = true;
-            __syncthreads();
-            if (!control) {
+                rejected = true;
+                __syncthreads();
                 if (next >= 0) look_ahead(next, len + 1);
-            } else {
-                if (meet(false, other_q, true, kids)) decide(kids, true, false, other_q);
-                else give_up();
+                ++meetings;
+                __syncthreads();
             }
-            ++meetings;
-            __syncthreads();
+            if (cmd != kCoAccept) break;
+            cur = uniform_of(s.arg);
+            ++len;
+            if (g == 0 && tid == 0) store_shared_result(&path[len], cur);
         }
-        if (cmd != kCoAccept) break;
-        cur = s.arg;
-        ++len;
-        if (g == 0 && tid == 0) store_shared_result(&path[len], cur);
     }
 
     // ---- bonus token, from the residual, or from p where nothing was rejected or the residual vanished
