@@ -314,7 +314,7 @@ radar_status radar_accept_length_distribution(const float *target_logits, const 
  *         the walk visits and no others.  The shared walk needs its
  *         B * G workgroups resident together; the library sizes G from the occupancy the runtime
  *         reports for the device (CUs x workgroups per CU) and bounds every wait (about 100 us by
- *         default): where other work keeps some of them from running, the wait ends and the
+ *         default, up to 2 ms where rows are too long for the workgroups' registers): where other work keeps some of them from running, the wait ends and the
  *         fall-back described at walk_spin_limit redoes the sequence.  On a GPU that is shared as a
  *         rule, pass walk_spin_limit < 0 (single-workgroup walk, no waiting at all). */
 typedef struct radar_accept_q_desc {
@@ -324,7 +324,8 @@ typedef struct radar_accept_q_desc {
                                    workgroups that meet at every node and after every rejection; the wait there
                                    is bounded, and a sequence whose workgroups gave up is redone by a single one
                                    (same results).  > 0: polls (about 0.5 us each) before giving up (tests
-                                   pass 1 to force that path; the default is 256); < 0: single-workgroup
+                                   pass 1 to force that path; the default is 256,
+                                   more for rows too long for registers); < 0: single-workgroup
                                    walk only */
 } radar_accept_q_desc;
 

@@ -10,7 +10,8 @@
 // The walk of a sequence is shared by up to 32 workgroups, each of which holds a slice of the rows at hand
 // in registers; after every row and every rejection they meet and exchange a few numbers each.  What
 // bounds a call is that chain: rows from HBM (about 2 us, requested one node ahead) and a meeting (about
-// 1.5 us) per node and per rejection.  Where the chip has no room for several workgroups per sequence,
+// 1.5 us) per node and per rejection.  Slices that do not fit into registers are walked over in laps.  Where
+// there are more sequences than pairs of workgroups, where a row fits one workgroup's first float4,
 // and where workgroups of a sequence could not meet, one workgroup walks alone: every rejection is then a
 // vocabulary-wide pass that turns the unnormalised residual u into max(0, u - W q) (W = sum u), keeps it
 // in a workspace row and leaves sums per 256 tokens in LDS, from which the bonus token is found.
@@ -29,7 +30,8 @@ constexpr int kAqMaxV = 1 << 20;
 constexpr int kAqGran = 4 * kWave;                    // tokens per partial sum in the lone walk (one wavefront x 16 B)
 constexpr int kAqMaxGran = kAqMaxV / kAqGran;         // 4096
 constexpr int kCoG = 32;                              // most workgroups per sequence
-constexpr int kCoR = 8;                               // most float4 per lane (V <= 32 * 8 * 2048; larger vocabularies walk alone)
+constexpr int kCoR = 8;                               // most float4 per lane that a row's slice may take in registers
+constexpr int kCoLapR = 4;                            // and what is taken at a time where a slice is longer
 constexpr int kCoCtl = 32;                            // uints per sequence in the control block: leave counter, abort flag at 8, 16
 constexpr int kCoWords = 4;                           // 8-byte words a workgroup brings to a meeting
 
@@ -42,7 +44,8 @@ struct AqArgs {
     int32_t *accept_len, *accept_path, *bonus;
     int B, T, Tq, V, D_max;
     double inv_t, inv_td;
-    float *ubuf;                // [B][V] unnormalised residual of the node being verified (lone walk)
+    float *ubuf;                // [B][V] unnormalised residual of the node being verified (lone walk, long slices)
+    int co_laps;                // long slices: how often R float4 per lane go into one
     unsigned int *co_ctl;       // [B][32]
     uint64_t *co_words;         // [B][2][32][4] what the workgroups brought to the last two meetings
     uint64_t *co_sib;           // [B][2][64] residual at the tokens of untried children
@@ -393,7 +396,7 @@ struct CoSmem {
     int cmd, arg;
     int owner, take_last, pick, wlast[kAqWaves];
     double before, goal;
-    double wtot[kCoR][kAqWaves];
+    double wtot[2][kCoR][kAqWaves];
     int last, redo;
 };
 
@@ -412,15 +415,18 @@ __device__ __forceinline__ double f64_of_words(uint64_t w, uint64_t rest) { retu
 __device__ __forceinline__ uint64_t word_of_f32(float v, unsigned int tag) { return ((uint64_t)__float_as_uint(v) << 32) | tag; }
 __device__ __forceinline__ float f32_of_word(uint64_t w) { return __uint_as_float((uint32_t)(w >> 32)); }
 
-template <bool VEC4, int R>
+// LAPS: slices longer than eight float4 per lane (large batches, V beyond 32 * 16384) are walked over in laps of R
+// float4 per lane: rows are read from memory as often as they are needed (one read for the statistics, one per
+// rejection), and the residual is kept in the workspace.  What bounds it is one CU's path to memory, some 64 KB/us.
+template <bool VEC4, int R, bool LAPS>
 __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
     __shared__ CoLds lds;
     CoSmem &s = lds.s;
     const int tid = threadIdx.x, lane = lane_id(), w = uniform_of(wave_id());
     const bool control = w == kAqWaves;
     const int g = blockIdx.x, G = gridDim.x, b = blockIdx.y;
-    constexpr int slice = R * kAqStream * 4;
-    const int lo = g * slice;
+    constexpr int lap_tokens = R * kAqStream * 4;
+    const int laps = LAPS ? a.co_laps : 1, slice = laps * lap_tokens, lo = g * slice;
     const int nn = a.n_nodes ? min(max(a.n_nodes[b], 0), a.T) : a.T;
     unsigned int *ctl = a.co_ctl + (size_t)b * kCoCtl;
     uint64_t *words = a.co_words + (size_t)b * 2 * kCoG * kCoWords;
@@ -452,11 +458,11 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
     }
 
     const float it_f = (float)a.inv_t, itd_f = (float)a.inv_td;
-    // this lane's tokens: float4 r covers lo + (r * 512 + tid) * 4 .. + 3
+    // this lane's tokens: float4 r of a lap covers lo + lap * lap_tokens + (r * 512 + tid) * 4 .. + 3
     // (made anew for every row: the offsets and end-of-row masks of 4 R tokens are not worth keeping through the walk)
-    auto first_token = [&]() { int i = lo + tid * 4; asm volatile("" : "+v"(i)); return i; };
-    auto load_row = [&](const float *row, float (&x)[R][4]) {
-        const int at = first_token();
+    auto first_token = [&](int lap) { int i = lo + lap * lap_tokens + tid * 4; asm volatile("" : "+v"(i)); return i; };
+    auto load_row = [&](const float *row, float (&x)[R][4], int lap = 0) {
+        const int at = first_token(lap);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int i0 = at + r * kAqStream * 4;
@@ -470,16 +476,18 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
             }
         }
     };
-    // tokens past the vocabulary (in the last slice only) are -inf from here on: no mass in a row, none in a residual
-    auto settle = [&](float (&x)[R][4]) {
-        if (lo + slice <= a.V) return;
-        const int at = first_token();
+    // tokens past the vocabulary (at the end of the last slice only) are -inf from here on: no mass in a row, none in
+    // a residual (a residual read back: 0)
+    auto settle = [&](float (&x)[R][4], int lap = 0, float none = -INFINITY) {
+        if (lo + (lap + 1) * lap_tokens <= a.V) return;
+        const int at = first_token(lap);
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[r][j] = at + r * kAqStream * 4 + j < a.V ? x[r][j] : -INFINITY;
+            for (int j = 0; j < 4; ++j) x[r][j] = at + r * kAqStream * 4 + j < a.V ? x[r][j] : none;
     };
-    auto wave_stats = [&](const float (&x)[R][4], double inv, int which) {
+    // maximum over the wavefront's tokens and this lane's sum of exponentials
+    auto lane_stats = [&](const float (&x)[R][4], double inv, double *l_out) -> float {
         float m = -INFINITY;
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -494,19 +502,85 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
                 for (int j = 0; j < 4; ++j) l += inv == 1.0 ? (double)exp_rel_f32(x[r][j], m, 1.f) : exp_rel(x[r][j], m, inv);   // (the same value)
             }
         }
+        *l_out = l;
+        return m;
+    };
+    auto put_stats = [&](float m, double l, int which) {
         l = wave_sum_f64(l);
         if (lane == 0) { s.wm[which][w] = m; s.wl[which][w] = l; }
     };
-    auto wave_mass = [&](const float (&u)[R][4]) {
+    auto wave_stats = [&](const float (&x)[R][4], double inv, int which) {
+        double l;
+        const float m = lane_stats(x, inv, &l);
+        put_stats(m, l, which);
+    };
+    auto lane_mass = [&](const float (&u)[R][4]) {
         double t = 0.0;
 #pragma unroll
         for (int r = 0; r < R; ++r) t += ((double)u[r][0] + (double)u[r][1]) + ((double)u[r][2] + (double)u[r][3]);
+        return t;
+    };
+    auto put_mass = [&](double t) {
         t = wave_sum_f64(t);
         if (lane == 0) s.wsum[w] = t;
     };
+    // logits -> probabilities, given the row's maximum and 1 / sum
+    auto to_probs = [&](float (&x)[R][4], float m, float inv, float inv_l) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[r][j] = exp_rel_f32(x[r][j], m, inv) * inv_l;
+    };
+    // Eq. 2: u <- max(0, u - W q)
+    auto subtract = [&](float (&u)[R][4], const float (&q)[R][4], float W) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) u[r][j] = fmaxf(0.f, fmaf(-W, q[r][j], u[r][j]));
+    };
+    // the same over a slice of several laps: each lap's sum is brought to the maximum so far
+    auto long_stats = [&](const float *row, double inv, int which) {
+        float m = -INFINITY;
+        double l = 0.0;
+        for (int lap = 0; lap < laps; ++lap) {
+            float y[R][4];
+            load_row(row, y, lap);
+            settle(y, lap);
+            double l1;
+            const float m1 = lane_stats(y, inv, &l1);
+            if (m1 > m) {                                 // (the same in every lane of the wavefront)
+                l = (m > -INFINITY ? l * exp(((double)m - (double)m1) * inv) : 0.0) + l1;
+                m = m1;
+            } else if (m1 > -INFINITY) {
+                l += m1 == m ? l1 : l1 * exp(((double)m1 - (double)m) * inv);
+            }
+        }
+        put_stats(m, l, which);
+    };
+    float *ub = a.ubuf + (size_t)b * a.V;                 // long slices: the residual; a lane reads back what it wrote
+    auto store_residual = [&](const float (&u)[R][4], int lap) {
+        // written through: should the sequence be redone on another die, no older copy may be written back over it
+        const int at = first_token(lap);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i0 = at + r * kAqStream * 4;
+            if (VEC4) {
+                if (i0 < a.V) {
+#pragma unroll
+                    for (int j = 0; j < 4; j += 2)
+                        store_shared_result(reinterpret_cast<uint64_t *>(ub + i0 + j),
+                                            (uint64_t)__float_as_uint(u[r][j]) | (uint64_t)__float_as_uint(u[r][j + 1]) << 32);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (i0 + j < a.V) store_shared_result(&ub[i0 + j], u[r][j]);
+            }
+        }
+    };
 
     // ---- streaming wavefronts' state
-    constexpr bool kAhead = R <= 2;                       // rows are requested one node ahead (wider slices have no registers left)
+    constexpr bool kAhead = R <= 2 && !LAPS;              // rows are requested one node ahead (wider slices have no registers left)
     float x[R][4], q[R][4];                               // target row (logits; after a rejection the residual), draft row
     bool q_ready = false;                                 // q holds probabilities (else logits)
     float nx[kAhead ? R : 1][4], nq[kAhead ? R : 1][4], ngx = 0.f, ngq = 0.f;   // one ahead; its children's logits (wavefront 0)
@@ -522,6 +596,23 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
         }
     };
     unsigned int meetings = 0;                            // so far
+    // the residual at the tokens of the children still to be tried: the lanes that hold them publish it
+    auto publish = [&](const float (&u)[R][4], uint64_t kids, int lap) {
+        for (uint64_t m = kids; m != 0; m &= m - 1) {
+            const int c2 = first_of(m);
+            const int off = (int)readlane_u32((uint32_t)tok, c2) - (lo + lap * lap_tokens);
+            if (off >= 0 && off < lap_tokens && ((off >> 2) & (kAqStream - 1)) == tid) {
+                const int r2 = off / (kAqStream * 4), j2 = off & 3;      // float4 index, element
+                float val = 0.f;
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (r == r2 && j == j2) val = u[r][j];
+                store_shared_result(&sibs[(meetings & 1) * kWave + c2], word_of_f32(val, meetings % 255 + 1));
+            }
+        }
+    };
     // ---- the control wavefront's state (the same in all of its lanes unless said otherwise)
     double W = 1.0, pl = 1.0, ql = 1.0, px = 0.0, qx = 0.0, psum = 0.0;      // px, qx: lane = node; psum: lane = workgroup
     float pm = 0.f, qm = 0.f;
@@ -667,69 +758,66 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
         for (;;) {
             uint64_t kids = kids_of(cur, len);
             rejected = false;
-            if constexpr (kAhead) {
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) { x[r][j] = nx[r][j]; q[r][j] = nq[r][j]; }
-            } else {
-                load_row(target + (size_t)cur * a.V, x);
-                if (kids != 0) load_row(draft + (size_t)qrow_of(first_of(kids)) * a.V, q);
-            }
+            const float *prow = target + (size_t)cur * a.V;
             if (w == 0) { s.gx[lane] = ngx; s.gq[lane] = ngq; }
-            q_ready = false;
-            settle(x);
-            wave_stats(x, a.inv_t, 0);
-            if (kids != 0) {
-                settle(q);
-                wave_stats(q, a.inv_td, 1);
+            if constexpr (LAPS) {
+                long_stats(prow, a.inv_t, 0);
+                if (kids != 0) long_stats(draft + (size_t)qrow_of(first_of(kids)) * a.V, a.inv_td, 1);
+            } else {
+                if constexpr (kAhead) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) { x[r][j] = nx[r][j]; q[r][j] = nq[r][j]; }
+                } else {
+                    load_row(prow, x);
+                    if (kids != 0) load_row(draft + (size_t)qrow_of(first_of(kids)) * a.V, q);
+                }
+                q_ready = false;
+                settle(x);
+                wave_stats(x, a.inv_t, 0);
+                if (kids != 0) {
+                    settle(q);
+                    wave_stats(q, a.inv_td, 1);
+                }
             }
             __syncthreads();
             if (kids != 0) look_ahead(first_of(kids), len + 1);
             ++meetings;
             __syncthreads();
             while ((cmd = uniform_of(s.cmd)) == kCoReject) {
-                // Eq. 2: u <- max(0, u - W q), then the next child (whose draft row may be another one)
+                // Eq. 2, then the next child (whose draft row may be another one)
                 const int c = uniform_of(s.arg);
                 kids &= ~(1ull << c);
                 const int next = kids != 0 ? first_of(kids) : -1;
                 const bool other_q = next >= 0 && qrow_of(next) != qrow_of(c);
                 const float m_p = s.pm, il_p = s.pinv_l, m_q = s.qm, il_q = s.qinv_l, W_f = s.W;
-                if (!q_ready) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) q[r][j] = exp_rel_f32(q[r][j], m_q, itd_f) * il_q;
-                }
-                if (!rejected) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) x[r][j] = exp_rel_f32(x[r][j], m_p, it_f) * il_p;
-                }
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) x[r][j] = fmaxf(0.f, fmaf(-W_f, q[r][j], x[r][j]));
-                q_ready = !other_q;
-                if (other_q) load_row(draft + (size_t)qrow_of(next) * a.V, q);
-                // the residual at the tokens of the children still to be tried: their owners publish it
-                for (uint64_t m = kids; m != 0; m &= m - 1) {
-                    const int c2 = first_of(m);
-                    const int off = (int)readlane_u32((uint32_t)tok, c2) - lo;
-                    if (off >= 0 && off < slice && ((off >> 2) & (kAqStream - 1)) == tid) {
-                        const int r2 = off / (kAqStream * 4), j2 = off & 3;      // float4 index, element
-                        float val = 0.f;
-#pragma unroll
-                        for (int r = 0; r < R; ++r)
-#pragma unroll
-                            for (int j = 0; j < 4; ++j)
-                                if (r == r2 && j == j2) val = x[r][j];
-                        store_shared_result(&sibs[(meetings & 1) * kWave + c2], word_of_f32(val, meetings % 255 + 1));
+                if constexpr (LAPS) {
+                    double mass = 0.0;
+                    for (int lap = 0; lap < laps; ++lap) {
+                        load_row(rejected ? ub : prow, x, lap);
+                        load_row(draft + (size_t)qrow_of(c) * a.V, q, lap);
+                        settle(x, lap, rejected ? 0.f : -INFINITY);
+                        settle(q, lap);
+                        if (!rejected) to_probs(x, m_p, it_f, il_p);
+                        to_probs(q, m_q, itd_f, il_q);
+                        subtract(x, q, W_f);
+                        store_residual(x, lap);
+                        publish(x, kids, lap);
+                        mass += lane_mass(x);
                     }
+                    put_mass(mass);
+                    if (other_q) long_stats(draft + (size_t)qrow_of(next) * a.V, a.inv_td, 1);
+                } else {
+                    if (!q_ready) to_probs(q, m_q, itd_f, il_q);
+                    if (!rejected) to_probs(x, m_p, it_f, il_p);
+                    subtract(x, q, W_f);
+                    q_ready = !other_q;
+                    if (other_q) load_row(draft + (size_t)qrow_of(next) * a.V, q);
+                    publish(x, kids, 0);
+                    put_mass(lane_mass(x));
+                    if (other_q) { settle(q); wave_stats(q, a.inv_td, 1); }
                 }
-                wave_mass(x);
-                if (other_q) { settle(q); wave_stats(q, a.inv_td, 1); }
                 rejected = true;
                 __syncthreads();
                 if (next >= 0) look_ahead(next, len + 1);
@@ -744,16 +832,22 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
     }
 
     // ---- bonus token, from the residual, or from p where nothing was rejected or the residual vanished
+    auto probs_of = [&](int lap) {                        // x: the current node's probabilities
+        load_row(target + (size_t)cur * a.V, x, lap);
+        settle(x, lap);
+        to_probs(x, s.pm, it_f, s.pinv_l);
+    };
     if (cmd == kCoBonusP) {
         if (!control) {
-            const float m_p = s.pm, il_p = s.pinv_l;
-            if (rejected) { load_row(target + (size_t)cur * a.V, x); settle(x); }   // the residual vanished
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) x[r][j] = exp_rel_f32(x[r][j], m_p, it_f) * il_p;
+            double mass = 0.0;
+            if constexpr (LAPS) {
+                for (int lap = 0; lap < laps; ++lap) { probs_of(lap); mass += lane_mass(x); }
+            } else {
+                if (rejected) probs_of(0);                // the residual vanished
+                else to_probs(x, s.pm, it_f, s.pinv_l);
+                mass = lane_mass(x);
             }
-            wave_mass(x);
+            put_mass(mass);
         }
         __syncthreads();
         if (control && !meet(false, false, true, 0)) give_up();
@@ -774,39 +868,48 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
         }
         __syncthreads();
         if (s.cmd != kCoAbort && g == s.owner) {
-            // token order inside the slice: float4 row r, then thread, then element
-            double linc[R], lsum[R];
-            if (!control) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    lsum[r] = ((double)x[r][0] + (double)x[r][1]) + ((double)x[r][2] + (double)x[r][3]);
-                    linc[r] = wave_scan_f64(lsum[r]);
-                    if (lane == kWave - 1) s.wtot[r][w] = linc[r];
+            // token order inside the slice: lap, float4 row r, then thread, then element
+            double run = s.before;
+            int lastp = -1;
+            for (int lap = 0; lap < laps; ++lap) {
+                double linc[R], lsum[R];
+                double (&wtot)[kCoR][kAqWaves] = s.wtot[lap & 1];
+                if (!control) {
+                    if (LAPS) {
+                        if (cmd == kCoBonusP) probs_of(lap);
+                        else { load_row(ub, x, lap); settle(x, lap, 0.f); }
                     }
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        lsum[r] = ((double)x[r][0] + (double)x[r][1]) + ((double)x[r][2] + (double)x[r][3]);
+                        linc[r] = wave_scan_f64(lsum[r]);
+                        if (lane == kWave - 1) wtot[r][w] = linc[r];
+                    }
+                }
+                __syncthreads();
+                if (!control) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        double wbefore = run;
+#pragma unroll
+                        for (int i = 0; i < kAqWaves; ++i) {
+                            if (i < w) wbefore += wtot[r][i];
+                            run += wtot[r][i];
+                        }
+                        const int i0 = lo + lap * lap_tokens + (r * kAqStream + tid) * 4;
+                        double acc = wbefore + linc[r] - lsum[r];
+                        int pick = -1;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            if (x[r][j] > 0.f) lastp = i0 + j;
+                            acc += (double)x[r][j];
+                            if (pick < 0 && acc > s.goal) pick = i0 + j;
+                        }
+                        if (pick >= 0 && !s.take_last) atomicMin(&s.pick, pick);
+                    }
+                }
             }
-            __syncthreads();
             if (!control) {
-                double run = s.before;
-                int lastp = -1;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    double wbefore = run;
-#pragma unroll
-                    for (int i = 0; i < kAqWaves; ++i) {
-                        if (i < w) wbefore += s.wtot[r][i];
-                        run += s.wtot[r][i];
-                    }
-                    const int i0 = lo + (r * kAqStream + tid) * 4;
-                    double acc = wbefore + linc[r] - lsum[r];
-                    int pick = -1;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        if (x[r][j] > 0.f) lastp = i0 + j;
-                        acc += (double)x[r][j];
-                        if (pick < 0 && acc > s.goal) pick = i0 + j;
-                    }
-                    if (pick >= 0 && !s.take_last) atomicMin(&s.pick, pick);
-                    }
                 lastp = (int)wave_max_u32((uint32_t)(lastp + 1)) - 1;
                 if (lane == 0) s.wlast[w] = lastp;
             }
@@ -856,7 +959,7 @@ static int aq_resident_capacity() {
         int dev = 0, per_cu = 0;
         hipDeviceProp_t prop;
         if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(&accept_q_coop_kernel<true, kCoR>),
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(&accept_q_coop_kernel<true, kCoR, false>),
                                                          kAqThreads, 0) != hipSuccess)
             return 0;
         return per_cu * prop.multiProcessorCount;
@@ -864,23 +967,25 @@ static int aq_resident_capacity() {
     return capacity;
 }
 
-// Workgroups per sequence (G) and float4 per lane (R) of the walk; G = 1 means the single-workgroup
-// walk.  The G * B workgroups of the shared walk meet at arrival counters, which only makes progress
+// Workgroups per sequence (G), float4 per lane (R) and laps of the walk; G = 1 means the single-workgroup
+// walk.  The G * B workgroups of the shared walk meet after every row, which only makes progress
 // while all of them are resident, so their number stays within what the device holds at once (on a
 // GPU that other work shares, the bounded wait turns a missing workgroup into the fall-back).
-static void aq_coop_plan(const radar_accept_q_desc *d, int *G, int *R) {
-    *G = 1; *R = 1;
+// Slices that fit eight float4 per lane stay in registers, longer ones are walked over in laps: a sequence left to
+// one workgroup gets 64 KB/us (one sequence of V = 1048576: 3013 us alone, 124 in laps; 40 of V = 128256: 399 and 126).
+static void aq_coop_plan(const radar_accept_q_desc *d, int *G, int *R, int *laps) {
+    *G = 1; *R = 1; *laps = 1;
     const int cap = aq_resident_capacity();
     if (d->walk_spin_limit < 0 || cap < 2 || d->B > cap / 2) return;
     const int gcap = cap / d->B < kCoG ? cap / d->B : kCoG;
     const int per_wg = kAqStream * 4;
     const int need = ((d->V + per_wg - 1) / per_wg + gcap - 1) / gcap;     // float4 per lane needed with gcap workgroups
-    if (need > kCoR) return;
-    int r = 1;
-    while (r < need) r *= 2;                                              // compiled for 1, 2, 4 and 8
-    const int g = (d->V + per_wg * r - 1) / (per_wg * r);
+    int r = 1, n = 1;
+    if (need > kCoR) { r = kCoLapR; n = (need + r - 1) / r; }
+    else while (r < need) r *= 2;                                         // compiled for 1, 2, 4 and 8
+    const int g = (d->V + per_wg * r * n - 1) / (per_wg * r * n);
     if (g < 2) return;                                                    // one workgroup would cover it anyway
-    *G = g; *R = r;
+    *G = g; *R = r; *laps = n;
 }
 
 extern "C" size_t radar_verify_accept_q_workspace_bytes(const radar_accept_q_desc *d) {
@@ -922,10 +1027,11 @@ extern "C" radar_status radar_verify_accept_q(const float *target_logits, const 
     a.co_sib = reinterpret_cast<uint64_t *>(take((size_t)d->B * 2 * kWave * sizeof(uint64_t)));
     a.ubuf = reinterpret_cast<float *>(take((size_t)d->B * d->V * sizeof(float)));
     int G = 1, R = 1;
-    aq_coop_plan(d, &G, &R);
+    aq_coop_plan(d, &G, &R, &a.co_laps);
     // default: 256 polls of about 0.5 us (an atomic load and a short sleep): the workgroups of a walk reach a
-    // meeting within microseconds of each other, so 100 us without progress means one of them is not running
-    a.co_spin_limit = d->walk_spin_limit > 0 ? (unsigned int)d->walk_spin_limit : 256u;
+    // meeting within microseconds of each other, so 100 us without progress means one of them is not running;
+    // a lap more takes them some 3 us more
+    a.co_spin_limit = d->walk_spin_limit > 0 ? (unsigned int)d->walk_spin_limit : 256u + 16u * (unsigned int)(a.co_laps - 1);
 
     const bool vec4 = (d->V % 4 == 0) && (((uintptr_t)target_logits & 15) == 0) && (((uintptr_t)draft_logits & 15) == 0);
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -935,13 +1041,17 @@ extern "C" radar_status radar_verify_accept_q(const float *target_logits, const 
         e = vec4 ? launch("accept_q_walk", accept_q_walk_kernel<true>, dim3((unsigned)d->B), block, 0, st, a)
                  : launch("accept_q_walk", accept_q_walk_kernel<false>, dim3((unsigned)d->B), block, 0, st, a);
     } else {
-        auto go = [&](auto r) {
+        auto go = [&](auto r, auto laps) {
             constexpr int RR = decltype(r)::value;
-            return vec4 ? launch("accept_q_walk_shared", accept_q_coop_kernel<true, RR>, grid, block, 0, st, a)
-                        : launch("accept_q_walk_shared", accept_q_coop_kernel<false, RR>, grid, block, 0, st, a);
+            constexpr bool LL = decltype(laps)::value;
+            return vec4 ? launch("accept_q_walk_shared", accept_q_coop_kernel<true, RR, LL>, grid, block, 0, st, a)
+                        : launch("accept_q_walk_shared", accept_q_coop_kernel<false, RR, LL>, grid, block, 0, st, a);
         };
-        e = R == 1 ? go(std::integral_constant<int, 1>{}) : R == 2 ? go(std::integral_constant<int, 2>{})
-          : R == 4 ? go(std::integral_constant<int, 4>{}) : go(std::integral_constant<int, 8>{});
+        using std::integral_constant;
+        using std::false_type;
+        e = a.co_laps > 1 ? go(integral_constant<int, kCoLapR>{}, std::true_type{})
+          : R == 1 ? go(integral_constant<int, 1>{}, false_type{}) : R == 2 ? go(integral_constant<int, 2>{}, false_type{})
+          : R == 4 ? go(integral_constant<int, 4>{}, false_type{}) : go(integral_constant<int, 8>{}, false_type{});
     }
     return e == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
 }

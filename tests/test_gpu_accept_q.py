@@ -102,6 +102,17 @@ def test_batches_that_leave_few_workgroups_per_sequence(oracle, V, B):
     compare(ref, got)
 
 
+@pytest.mark.parametrize("V,B", [(1048576, 2), (600001, 3), (128256, 45), (40001, 110)])
+def test_slices_too_long_for_registers(oracle, V, B):
+    """Rows walked over in laps, with the residual in the workspace: the largest vocabulary, two to four workgroups per
+    sequence, rows that end inside a lap and inside a float4; an independent draft, so that most children are rejected."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(synth.seed_for(32, V % 1000 + B))
+    x = synth.sampled_draft_inputs(rng, ragged_trees(rng, B, 5, 4, V), V, 5, std=2.0, noise=2.5, shared_rows=B % 2 == 0)
+    ref, got = run_both(oracle, b, x)
+    compare(ref, got)
+
+
 def test_many_rejections_at_one_node_and_the_depth_cut(oracle):
     """A poor draft (independent of the target) under a star: most children are rejected one after the
     other, each rejection one more pass of Eq. 2; then the same trees cut at depth 1 and 0."""
