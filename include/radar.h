@@ -314,7 +314,7 @@ radar_status radar_accept_length_distribution(const float *target_logits, const 
  *         the walk visits and no others.  The shared walk needs its
  *         B * G workgroups resident together; the library sizes G from the occupancy the runtime
  *         reports for the device (CUs x workgroups per CU) and bounds every wait (about 100 us by
- *         default, up to 2 ms where rows are too long for the workgroups' registers): where other work keeps some of them from running, the wait ends and the
+ *         default, up to 0.7 ms where rows are too long for the workgroups' registers): where other work keeps some of them from running, the wait ends and the
  *         fall-back described at walk_spin_limit redoes the sequence.  On a GPU that is shared as a
  *         rule, pass walk_spin_limit < 0 (single-workgroup walk, no waiting at all). */
 typedef struct radar_accept_q_desc {

@@ -131,19 +131,18 @@ __device__ __forceinline__ void row_stats(const AqArgs &a, AqSmem &s, const floa
 template <bool VEC4>
 __device__ __forceinline__ double residual_pass(const AqArgs &a, AqSmem &s, int b, const float *prow, float pm, double pinv_l,
                                                 const float *qrow, float qm, double qinv_l, double W, int hi) {
-    constexpr int lo = 0;
-    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    const int tid = threadIdx.x, lane = lane_id();
     float *ub = a.ubuf + (size_t)b * a.V;
-    const int ngran = (hi - lo + kAqGran - 1) / kAqGran;
+    const int ngran = (hi + kAqGran - 1) / kAqGran;
     const float it_f = (float)a.inv_t, itd_f = (float)a.inv_td, pinv_l_f = (float)pinv_l, qinv_l_f = (float)qinv_l, W_f = (float)W;
     constexpr int U = 4;                                             // 2304-token steps whose loads are in flight together
-    for (int base0 = lo + tid * 4; base0 - lane * 4 < hi; base0 += U * kAqThreads * 4) {
+    for (int base0 = tid * 4; base0 - lane * 4 < hi; base0 += U * kAqThreads * 4) {
         float u4[U][4], q4[U][4];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const int base = base0 + k * kAqThreads * 4;
             if (VEC4) {                                              // V % 4 == 0: a float4 is all in or all out
-                const int i0 = base < hi ? base : lo;                // out of range: any legal address, masked below
+                const int i0 = base < hi ? base : 0;                 // out of range: any legal address, masked below
                 const float4 v = *reinterpret_cast<const float4 *>((prow ? prow : ub) + i0);
                 u4[k][0] = v.x; u4[k][1] = v.y; u4[k][2] = v.z; u4[k][3] = v.w;
                 if (qrow) {
@@ -180,7 +179,7 @@ __device__ __forceinline__ double residual_pass(const AqArgs &a, AqSmem &s, int 
                     if (base + j < hi) ub[base + j] = out[j];
             }
             sum = wave_sum_f64(sum);
-            if (lane == 0) s.gsum[(base - lo) / kAqGran] = sum;
+            if (lane == 0) s.gsum[base / kAqGran] = sum;
         }
     }
     __syncthreads();
@@ -194,11 +193,9 @@ __device__ __forceinline__ double residual_pass(const AqArgs &a, AqSmem &s, int 
 // 256 tokens are in s.gsum, u itself in ubuf.  Returns the token to every lane of wavefront 0.
 template <bool VEC4>
 __device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, double target, int hi) {
-    constexpr int lo = 0;
-    constexpr double before0 = 0.0;
     const int lane = lane_id();
     const float *ub = a.ubuf + (size_t)b * a.V;
-    const int ngran = (hi - lo + kAqGran - 1) / kAqGran;
+    const int ngran = (hi + kAqGran - 1) / kAqGran;
     const int per = (ngran + kWave - 1) / kWave;
     // each lane owns `per` consecutive granules
     double mine = 0.0;
@@ -208,14 +205,14 @@ __device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, dou
         if (s.gsum[g] > 0.0) last_pos = g;
     }
     const double incl = wave_scan_f64(mine);
-    const uint64_t cross = __ballot(before0 + incl > target);
+    const uint64_t cross = __ballot(incl > target);
     int g_pick;
     double before;
     if (cross != 0) {
         const int owner = __ffsll((long long)cross) - 1;
         // the owner walks its granules
         int g_loc = -1;
-        double acc = before0 + incl - mine, bef = acc;
+        double acc = incl - mine, bef = acc;
         for (int g = lane * per; g < min((lane + 1) * per, ngran); ++g) {
             if (g_loc < 0) {
                 bef = acc;
@@ -239,7 +236,7 @@ __device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, dou
         before = -1.0;                                               // marks "take the last positive token"
     }
     // the 256 tokens of the granule, 4 per lane in token order
-    const int i0 = lo + g_pick * kAqGran + lane * 4;
+    const int i0 = g_pick * kAqGran + lane * 4;
     double v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = (i0 + j < hi) ? (double)ub[i0 + j] : 0.0;

@@ -595,6 +595,10 @@ __device__ __forceinline__ int flat_pair_at(const FlatUnit &u, int pos) {
 constexpr int kLdBufs = 4;
 // Ranges of so many tiles take it.  At eight the compact one-ahead loop still wins (16 sequences of up to 900
 // rows 20.3 us against 22.0), at nine the long-range kernel (8 of up to 2000 rows 26.6 against 28.6).
+// At D = 64 the choice is between one and two tiles ahead.  With one workgroup per CU two ahead gain 1 % at nine
+// tiles and 3 % from sixteen on (one layer of 32 heads, 2048 rows in ranges of 9, 16 and 32 tiles: 17.2, 24.9 and 42.9 us
+// against 17.4, 25.6 and 44.3); where workgroups are several rounds they lose 1-5 % at nine (32 sequences of 2048 rows
+// 30.4 against 29.0), are even at sixteen and gain 2-4 % at 32.  The library's own ranges of nine tiles or more: 1-4 % gained.
 constexpr int kLongTiles = 9;
 
 // A lane's share of a tile: two chunks of K and two of V.  Wavefront w loads the row groups 2w and
@@ -878,9 +882,10 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
 // of the head dimension): lane = (8 consecutive d, tree row i), rows rounded up to 16, 32 or 64, so that a
 // small tree's rows sit in few wavefronts (four rows, 48 partials: 31 us for the call with 64 lanes per
 // d, 22 with 16).  The time is that of dependent rounds of loads, so a lane asks for four or eight
-// partials at once; where a head is cut into sixteen pieces or more two groups of lanes take every other
-// one and meet in LDS (3 heads of 16000 rows 26.5 -> 24.8 us; with 11 pieces it costs 0.1 us more than it
-// gives, and four groups cost more than two nearly everywhere: a workgroup of 1024 lanes starts late).
+// partials at once; where the rows are dealt out on the device into sixteen shares or more per KV head, two groups
+// of lanes take every other partial and meet in LDS (3 heads of 16000 rows 26.5 -> 24.8 us; with 11 pieces it costs
+// 0.1 us more than it gives, and four groups cost more than two nearly everywhere: a workgroup of 1024 lanes starts
+// late).  Ranges cut on the host are merged by one group, however many they are.
 template <int D, int E>
 __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(AttnArgs a) {
     __shared__ float red[E > 1 ? E - 1 : 1][10][kAttnThreads];
@@ -1142,7 +1147,7 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
     }
     if (a.max_splits > 1 || p.shares > 0) {
         const dim3 mgrid((unsigned)(a.Hq * (d->D / 32)), (unsigned)a.B);
-        const bool many = p.shares >= 16l * d->B * d->Hkv;          // sixteen pieces per head or more
+        const bool many = p.shares >= 16l * d->B * d->Hkv;          // sixteen shares per KV head or more (dealt-out rows only)
         const dim3 block2(kAttnThreads * 2);
         const hipError_t e = d->D == 128 ? (many ? launch("tree_attn_merge", tree_attn_merge_kernel<128, 2>, mgrid, block2, 0, s, a)
                                                  : launch("tree_attn_merge", tree_attn_merge_kernel<128, 1>, mgrid, block, 0, s, a))

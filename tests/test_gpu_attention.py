@@ -99,8 +99,8 @@ LONG_CASES = {
 @pytest.mark.parametrize("kps", [512, 1024, 2048])
 @pytest.mark.parametrize("name", list(LONG_CASES))
 def test_long_ranges_match_oracle(oracle, name, kps):
-    """Ranges of eight tiles or more run the long-range kernels (tiles loaded straight into LDS and taken
-    in pairs at D = 128, two-ahead register staging at D = 64): ranges that end after one, two or several
+    """Ranges of nine tiles or more run the long-range kernels (tiles loaded straight into LDS and taken
+    in pairs at D = 128, two-ahead register staging at D = 64); eight tiles are the longest the short-range one gets.  Ranges that end after one, two or several
     tiles, an odd and an even number of tiles, tree rows that straddle a tile or a range boundary, a
     single range (no merge), wavefronts without a unit."""
     from paper_2512_14069_amd import binding as b
