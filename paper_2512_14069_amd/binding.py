@@ -10,15 +10,16 @@ A direct call (prepared=False) goes through the native marshaller
 path below it makes prepared calls and raises the errors.
 """
 import ctypes
-import importlib
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
-# RADAR_LIB_SANITIZE=1 selects the build whose host code runs under the sanitizers (CPU tests only)
-LIB_PATH = os.path.join(_HERE, "libradar_san.so" if os.environ.get("RADAR_LIB_SANITIZE", "0") == "1" else "libradar.so")
-NATIVE_PATH = os.path.join(_HERE, "_native.so")
+# RADAR_LIB_SANITIZE=1 selects the builds whose host code runs under the sanitizers (CPU tests only)
+_SUFFIX = "_san.so" if os.environ.get("RADAR_LIB_SANITIZE", "0") == "1" else ".so"
+LIB_PATH = os.path.join(_HERE, "libradar" + _SUFFIX)
+NATIVE_PATH = os.path.join(_HERE, "_native" + _SUFFIX)
 _lib = None
 _native = None
 
@@ -157,8 +158,7 @@ def load():
     lib.radar_profile_begin.argtypes = [i32]
     lib.radar_profile_end.restype = i32
     lib.radar_profile_end.argtypes = [ctypes.POINTER(KernelTime), i32, ctypes.POINTER(i32)]
-    if not LIB_PATH.endswith("_san.so"):        # the sanitized build is for host-side checks, made through ctypes alone
-        _load_native()
+    _load_native()
     _lib = lib
     return lib
 
@@ -168,13 +168,15 @@ def _load_native():
     if not os.path.exists(NATIVE_PATH):
         raise RuntimeError(f"{NATIVE_PATH} is missing: build it with __graft_entry__.build() "
                            "(python -m paper_2512_14069_amd.build)")
-    module = importlib.import_module("._native", __package__)
+    spec = importlib.util.spec_from_file_location(__package__ + "._native", NATIVE_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
     module.bind(LIB_PATH)
     _native = module
 
 
 def _direct(prepared):
-    """The native marshaller for a direct call, or None (prepared calls, sanitized build)."""
+    """The native marshaller for a direct call, or None (prepared calls)."""
     if prepared:
         return None
     if _lib is None:

@@ -27,6 +27,7 @@ def _stale(target, deps):
 
 
 SAN_LIB = os.path.join(HERE, "libradar_san.so")
+SAN_NATIVE = os.path.join(HERE, "_native_san.so")
 # host code only (the GPU side has no sanitizer here): each option directly after -Xarch_host
 SAN_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
              "-Xarch_host", "-fno-sanitize-recover=undefined", "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
@@ -41,36 +42,45 @@ def sanitizer_runtime():
 
 def build_library(force=True, verbose=False, sanitize=False):
     """Compile every kernel source and link paper_2512_14069_amd/libradar.so, and the binding's native half.  sanitize=True builds
-    libradar_san.so instead: the same sources with the HOST code (argument checks, planning, launch
-    paths) under AddressSanitizer and UndefinedBehaviorSanitizer; used by the CPU tests only."""
+    libradar_san.so and _native_san.so instead: the same sources with the HOST code (argument checks, planning,
+    launch paths, argument marshalling) under AddressSanitizer and UndefinedBehaviorSanitizer; used by the CPU tests only."""
     headers = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
     headers.append(os.path.join(os.path.dirname(HERE), "include", "radar.h"))
     if sanitize:
+        build_native(force, sanitize=True)
         return _build(os.path.join(HERE, "_build", "san"), SAN_LIB, [f for f in FLAGS if f != "-O3"] + ["-O1"] + SAN_FLAGS,
                       ["-fsanitize=address", "-fsanitize=undefined", "-shared-libsan"], headers, force, verbose)
     build_native(force)
     return _build(os.path.join(HERE, "_build"), LIB, FLAGS, [], headers, force, verbose)
 
 
-def build_native(force=True):
+def build_native(force=True, sanitize=False):
     """Compile the binding's argument marshaller (host code only) against the installed torch."""
     import sysconfig
 
     import torch
     src, root = os.path.join(CSRC, "radar_native.cpp"), os.path.dirname(torch.__file__)
-    if not (force or _stale(NATIVE, [src, os.path.join(os.path.dirname(HERE), "include", "radar.h")])):
-        return NATIVE
-    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+    target = SAN_NATIVE if sanitize else NATIVE
+    if not (force or _stale(target, [src, os.path.join(os.path.dirname(HERE), "include", "radar.h")])):
+        return target
+    # the sanitized one is built by clang, whose runtime the sanitized library brings along; torch has no type
+    # information that the vptr check could use
+    front = [CXX, "-O2"]
+    if sanitize:
+        front = [os.path.join(os.path.dirname(HIPCC), "..", "lib", "llvm", "bin", "clang++"), "-O1", "-g", "-fno-omit-frame-pointer",
+                 "-fsanitize=address", "-fsanitize=undefined", "-fno-sanitize=vptr", "-fno-sanitize=function",
+                 "-fno-sanitize-recover=undefined", "-shared-libsan"]
+    cmd = front + ["-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
     for inc in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
                 os.path.join(os.path.dirname(HIPCC), "..", "include"), sysconfig.get_paths()["include"]):
         cmd += ["-isystem", inc]
     lib = os.path.join(root, "lib")
-    cmd += [src, "-o", NATIVE, "-L" + lib, "-Wl,-rpath," + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-ldl"]
+    cmd += [src, "-o", target, "-L" + lib, "-Wl,-rpath," + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-ldl"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"{CXX} failed for radar_native.cpp:\n{r.stderr}")
-    return NATIVE
+        raise RuntimeError(f"{front[0]} failed for radar_native.cpp:\n{r.stderr}")
+    return target
 
 
 def _build(objdir, lib, flags, link_flags, headers, force, verbose):

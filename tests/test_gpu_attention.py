@@ -100,9 +100,9 @@ LONG_CASES = {
 @pytest.mark.parametrize("name", list(LONG_CASES))
 def test_long_ranges_match_oracle(oracle, name, kps):
     """Ranges of nine tiles or more run the long-range kernels (tiles loaded straight into LDS and taken
-    in pairs at D = 128, two-ahead register staging at D = 64); eight tiles are the longest the short-range one gets.  Ranges that end after one, two or several
-    tiles, an odd and an even number of tiles, tree rows that straddle a tile or a range boundary, a
-    single range (no merge), wavefronts without a unit."""
+    in pairs at D = 128, two-ahead register staging at D = 64), eight tiles are the longest that the
+    short-range one gets.  Ranges that end after one, two or several tiles, an odd and an even number of
+    tiles, tree rows that straddle a tile or a range boundary, a single range (no merge), wavefronts without a unit."""
     from paper_2512_14069_amd import binding as b
     a = LONG_CASES[name]
     x = synth.attention_inputs(a, seed=synth.seed_for(1, 7 * len(name) + kps // 512), shuffle=True)

@@ -1,6 +1,6 @@
 """The CPU side under AddressSanitizer and UndefinedBehaviorSanitizer: the oracle (plain C) runs its
 whole pin suite instrumented, and the library's host code (argument checks, planning, launch paths
-that reject before any launch) runs the ABI tests instrumented.  Each runs in a child process with
+that reject before any launch) and the binding's native half run their tests instrumented.  Each runs in a child process with
 the matching sanitizer runtime preloaded (gcc's for the oracle, clang's for the HIP host code)."""
 import glob
 import os
@@ -38,6 +38,6 @@ def test_oracle_pin_suite_under_sanitizers():
 def test_library_host_code_under_sanitizers():
     from paper_2512_14069_amd import build
     build.build_library(force=False, sanitize=True)
-    out = run_child([os.path.join(ROOT, "tests", "test_library_abi.py")], {"RADAR_LIB_SANITIZE": "1"},
-                    build.sanitizer_runtime())
+    tests = [os.path.join(ROOT, "tests", t) for t in ("test_library_abi.py", "test_native.py")]
+    out = run_child(tests, {"RADAR_LIB_SANITIZE": "1"}, build.sanitizer_runtime())
     assert " passed" in out
