@@ -205,3 +205,158 @@ def test_direct_calls_match_prepared_calls(B, T, V):
             f(args[0].double(), *args[1:], **kw)
         with pytest.raises(ValueError):
             f(args[0].transpose(0, 1).contiguous().transpose(0, 1)[:, :, ::2], *args[1:], **kw)
+
+
+class _Both:
+    """Runs a call natively (and sees that it did go there) and by ctypes; everything it returns or writes is equal."""
+
+    def __init__(self, b, monkeypatch):
+        self.b, self.taken = b, 0
+        real, outer = b._native, self
+
+        class Spy:
+            def __getattr__(self, name):
+                def call(*args):
+                    got = getattr(real, name)(*args)
+                    outer.taken += got is not None
+                    return got
+                return call
+        monkeypatch.setattr(b, "_direct", lambda prepared: None if prepared or not self.native else Spy())
+
+    def __call__(self, what, call):
+        """call() -> tensors; made twice, on buffers of its own each time."""
+        self.native, before = True, self.taken
+        direct = call()
+        assert self.taken == before + 1, f"{what}: the native half refused it"
+        self.native = False
+        other = call()
+        torch.cuda.synchronize()
+        assert len(direct) == len(other)
+        for i, (x, y) in enumerate(zip(direct, other)):
+            assert x.shape == y.shape and x.dtype == y.dtype and torch.equal(x, y), (what, i)
+
+
+@pytest.mark.parametrize("D,S,kps", [(64, 150, 0), (128, 150, 64), (64, 1300, 1024), (128, 20000, 0)])
+def test_native_attention_calls_match_ctypes(monkeypatch, D, S, kps):
+    """Every form of an attention call that the native half reads by itself: log-sum-exp, scale, rows taken from a
+    fused projection and caches with a row pitch, trees of the full size, outputs of the caller's."""
+    from paper_2512_14069_amd import binding as b
+    b.load()
+    both = _Both(b, monkeypatch)
+    g = torch.Generator(device="cuda").manual_seed(S)
+    B, T, Hq, Hkv = 2, 33, 4, 2
+    fused = torch.randn((B, T, 3 * Hq, D), generator=g, device="cuda").to(torch.bfloat16)
+    kbuf, vbuf = (torch.randn((B, Hkv, S + T + 3, D + 8), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    par = dev(np.stack([synth.chain_tree(T), synth.star_tree(T)]).astype(np.int32))
+    ctx, nn = dev(np.array([S, S // 3], np.int32)), dev(np.array([T, 9], np.int32))
+    q, k, v = fused[:, :, Hq:2 * Hq], kbuf[:, :, :S + T, :D], vbuf[:, :, :S + T, :D]
+    for dense in (False, True):
+        if dense:
+            q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
+        ws = b.new_workspace(b.radar_tree_attention_workspace_bytes(b.attn_desc(q, k, kps)))
+        for nodes in (nn, None):
+            for scale in (0.0, 0.04):
+                for given in (False, True):
+                    def call():
+                        lse = torch.full((B, T, Hq), 5.0, device="cuda")
+                        out = torch.full((B, T, Hq, D), 5.0, dtype=torch.bfloat16, device="cuda") if given else None
+                        return b.radar_tree_attention(q, k, v, par, ctx, nodes, out=out, lse_out=lse, workspace=ws, keys_per_split=kps,
+                                                      softmax_scale=scale), lse
+                    both((dense, nodes is None, scale, given), call)
+
+
+@pytest.mark.parametrize("V,k", [(1000, 4), (32000, 10)])
+def test_native_drafting_calls_match_ctypes(monkeypatch, V, k):
+    """Expansion alone, with the prediction model, with a cycle's state and for a batch, with and without a hidden state and
+    a uniform; the reranks over what they left; the model's step by itself."""
+    from paper_2512_14069_amd import binding as b
+    b.load()
+    both = _Both(b, monkeypatch)
+    rng = np.random.default_rng(V + k)
+    F, B, N, cap = 3, 2, 7, 4 * 3 * k
+    pp = b.policy_params({n: dev(v) for n, v in synth.policy_params(rng, k).items()})
+    H = synth.POLICY_H
+    f32 = lambda *shape: dev(rng.standard_normal(shape).astype(np.float32))    # noqa: E731
+    logits, ps, pi = f32(B, F, V), -f32(B, F).abs(), torch.full((B, F), -1, dtype=torch.int32, device="cuda")
+    h, c, uni = f32(B, H), f32(B, H), dev(rng.random(B, dtype=np.float32))
+    desc = b.expand_desc(F, V, k, 0, cap)
+    ws = b.new_workspace(b.radar_draft_expand_batch_workspace_bytes(desc, B))
+    fields = lambda o: [getattr(o, n).clone() for n in (getattr(o, "__slots__", None) or vars(o)) if isinstance(getattr(o, n), torch.Tensor)]   # noqa: E731
+    states = ((None, None, None), (h, c, None), (h, c, uni), (None, None, uni))
+
+    def draft(fn, batch, state=False, params=None, hcu=(None, None, None)):
+        def call():
+            b.radar_workspace_init(ws)
+            pool = b.DraftPool(cap, B=B if batch else None)
+            for t in (pool.tokens, pool.scores, pool.parents):
+                t.zero_()
+            out = b.ExpandOut(F, k, "cuda", B=B if batch else None)
+            pout = b.PolicyOut(B if batch else 1, H, "cuda") if params else None
+            st = (torch.zeros((B, 4), dtype=torch.int32, device="cuda") if batch else b.new_cycle_state()) if state else None
+            lg, s, i = (logits, ps, pi) if batch else (logits[0], ps[0], pi[0])
+            own = [None if t is None else t if batch else t[:1] for t in hcu]
+            kw = dict(out=out, workspace=ws)
+            if params:
+                kw.update(params=params, h=own[0], c=own[1], uniform=own[2], policy_out=pout)
+            if batch:
+                fn(lg, s, i, k, pool, states=st, pool_count_max=0 if state else None, **kw)
+            elif state:
+                fn(lg, s, i, k, pool, 0, st, **kw)
+            else:
+                fn(lg, s, i, k, pool, **kw)
+            return fields(out) + fields(pool) + (fields(pout) if params else []) + ([st] if state else [])
+        return call
+
+    both("expand", draft(b.radar_draft_expand, False))
+    both("cycle", draft(b.radar_draft_expand_cycle, False, state=True))
+    both("batch", draft(b.radar_draft_expand_batch, True))
+    both("batch, states", draft(b.radar_draft_expand_batch, True, state=True))
+    for hcu in states:
+        given = tuple(t is not None for t in hcu)
+        both(("policy", given), draft(b.radar_draft_expand_policy, False, params=pp, hcu=hcu))
+        both(("cycle, policy", given), draft(b.radar_draft_expand_cycle, False, state=True, params=pp, hcu=hcu))
+        both(("batch, policy", given), draft(b.radar_draft_expand_batch, True, params=pp, hcu=hcu))
+        both(("batch, states, policy", given), draft(b.radar_draft_expand_batch, True, state=True, params=pp, hcu=hcu))
+        both(("step", given), lambda: fields(b.radar_policy_step(ps[:, :1].exp().repeat(1, k).contiguous(), pp, hcu[0], hcu[1], hcu[2])))
+
+    pool1, poolB = b.DraftPool(cap), b.DraftPool(cap, B=B)
+    b.radar_draft_expand(logits[0], ps[0], pi[0], k, pool1)
+    b.radar_draft_expand_batch(logits, ps, pi, k, poolB)
+    st1, stB = (torch.tensor([0, F * k, 1, 0] * n, dtype=torch.int32, device="cuda") for n in (1, B))
+    roots = dev(np.arange(B, dtype=np.int32))
+    both("rerank", lambda: fields(b.radar_draft_rerank(pool1, N, 5)))
+    both("rerank, state", lambda: fields(b.radar_draft_rerank_cycle(pool1, st1, cap, N, 5)))
+    both("rerank, batch", lambda: fields(b.radar_draft_rerank_batch(poolB, N, roots)))
+    both("rerank, batch, states", lambda: fields(b.radar_draft_rerank_batch(poolB, N, roots, states=stB.view(B, 4), pool_count_max=cap)))
+
+
+@pytest.mark.parametrize("B,T,V", [(1, 1, 17), (3, 24, 5000)])
+def test_native_verification_calls_match_ctypes(monkeypatch, B, T, V):
+    """Greedy and sampled walks, the length distribution and the walk with draft distributions, with whole and ragged
+    trees, outputs of the caller's and fresh ones, a row map and none, depths and temperatures."""
+    from paper_2512_14069_amd import binding as b
+    b.load()
+    both = _Both(b, monkeypatch)
+    rng = np.random.default_rng(B + T + V)
+    x, y = (dev(synth.normal_logits(rng, (B, T, V), 2.0)) for _ in range(2))
+    uni, par = dev(rng.random((B, T + 1), dtype=np.float32)), dev(np.tile(synth.chain_tree(T), (B, 1)).astype(np.int32))
+    tok, nn = dev(rng.integers(0, V, size=(B, T)).astype(np.int32)), dev(rng.integers(1, T + 1, size=B).astype(np.int32))
+    rows = dev(rng.integers(0, T, size=(B, T)).astype(np.int32))
+    for D_max in {T - 1, T // 2}:
+        ws = b.new_workspace(b.radar_verify_accept_workspace_bytes(b.accept_desc(B, T, V, D_max, b.RADAR_ACCEPT_SAMPLE, 1.0)))
+        wsq = b.new_workspace(b.radar_verify_accept_q_workspace_bytes(b.accept_q_desc(B, T, T, V, D_max)))
+        for given in (False, True):
+            def fresh():
+                return tuple(torch.full(s, 9, dtype=torch.int32, device="cuda") for s in ((B,), (B, D_max + 1), (B,))) if given else None
+            for nodes in (nn, None):
+                for temp in (1.0, 0.7):
+                    kw = dict(D_max=D_max, temperature=temp, workspace=ws)
+                    what = (D_max, given, nodes is None, temp)
+                    both(("greedy",) + what, lambda: b.radar_verify_accept(x, tok, par, nodes, mode=b.RADAR_ACCEPT_GREEDY, out=fresh(), **kw))
+                    both(("sample",) + what, lambda: b.radar_verify_accept(x, tok, par, nodes, uni, mode=b.RADAR_ACCEPT_SAMPLE, out=fresh(), **kw))
+                    dist = torch.full((B, D_max + 1), 9.0, dtype=torch.float64, device="cuda") if given else None
+                    both(("length",) + what, lambda: (b.radar_accept_length_distribution(x, tok, par, nodes, out=dist, **kw).clone(),))
+                    for qr in (rows, None):
+                        for limit in (0, -1):
+                            both(("q", qr is None, limit) + what, lambda: b.radar_verify_accept_q(
+                                x, y, tok, par, nodes, uni, qr, draft_temperature=1.2, out=fresh(), walk_spin_limit=limit, **dict(kw, workspace=wsq)))
