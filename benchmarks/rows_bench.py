@@ -126,7 +126,7 @@ def main():
         call = b.radar_verify_accept_q(d["target_logits"], d["draft_logits"], d["draft_tokens"], d["parents"], d["n_nodes"],
                                        d["uniforms"], d["q_rows"], workspace=qws, prepared=True, walk_spin_limit=limit)
         used = len(set(x["q_rows"][0, 1:T].tolist()))
-        timed("radar_verify_accept_q", [call], (T + used) * V * 4, label + "; %d target rows and %d draft rows read once by the statistics launch" % (T, used))
+        timed("radar_verify_accept_q", [call], (T + used) * V * 4, label + "; bytes: %d target rows and %d draft rows, of which the shared walk reads those it visits" % (T, used))
 
 
 if __name__ == "__main__":

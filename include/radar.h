@@ -311,7 +311,8 @@ radar_status radar_accept_length_distribution(const float *target_logits, const 
  * [B,T_max+1].  Nodes whose token or draft row is out of range are skipped.
  * Limits: T_max <= RADAR_T_MAX; V <= 1048576; B * (T_max + Tq) <= 65535;
  *         both temperatures > 0.  One kernel is enqueued, which reads the rows that
- *         the walk visits and no others.  The shared walk needs its
+ *         the walk visits and no others (a single-workgroup walk over few rows of a large vocabulary:
+ *         two kernels, the first of which reads every row once).  The shared walk needs its
  *         B * G workgroups resident together; the library sizes G from the occupancy the runtime
  *         reports for the device (CUs x workgroups per CU) and bounds every wait (about 100 us by
  *         default, up to 0.7 ms where rows are too long for the workgroups' registers): where other work keeps some of them from running, the wait ends and the

@@ -12,9 +12,10 @@
 // bounds a call is that chain: rows from HBM (about 2 us, requested one node ahead) and a meeting (about
 // 1.5 us) per node and per rejection.  Slices that do not fit into registers are walked over in laps.  Where
 // there are more sequences than pairs of workgroups, where a row fits one workgroup's first float4,
-// and where workgroups of a sequence could not meet, one workgroup walks alone: every rejection is then a
-// vocabulary-wide pass that turns the unnormalised residual u into max(0, u - W q) (W = sum u), keeps it
-// in a workspace row and leaves sums per 256 tokens in LDS, from which the bonus token is found.
+// and where workgroups of a sequence could not meet or the caller wants none that wait, one workgroup walks alone:
+// every rejection is then a vocabulary-wide pass that turns the unnormalised residual u into max(0, u - W q)
+// (W = sum u), keeps it in a workspace row and leaves sums per 256 tokens in LDS, from which the bonus token is
+// found.  Where such a call has few rows, the whole chip takes their statistics in a launch before it.
 #include <type_traits>
 
 #include "radar_device.h"
@@ -25,10 +26,11 @@ namespace radar {
 constexpr int kAqWaves = 8;                           // wavefronts that hold the vocabulary
 constexpr int kAqStream = kAqWaves * kWave;
 constexpr int kAqThreads = kAqStream + kWave;         // and one that meets the other workgroups and decides
-constexpr int kAqAllWaves = kAqWaves + 1;
+constexpr int kAqLone = 1024;                         // a lone walk that was launched as one: more loads in flight
 constexpr int kAqMaxV = 1 << 20;
 constexpr int kAqGran = 4 * kWave;                    // tokens per partial sum in the lone walk (one wavefront x 16 B)
 constexpr int kAqMaxGran = kAqMaxV / kAqGran;         // 4096
+constexpr int kAqChunk = 16384;                       // tokens per workgroup of the statistics launch
 constexpr int kCoG = 32;                              // most workgroups per sequence
 constexpr int kCoR = 8;                               // most float4 per lane that a row's slice may take in registers
 constexpr int kCoLapR = 4;                            // and what is taken at a time where a slice is longer
@@ -44,6 +46,9 @@ struct AqArgs {
     int32_t *accept_len, *accept_path, *bonus;
     int B, T, Tq, V, D_max;
     double inv_t, inv_td;
+    float *part_m;              // statistics launch: [B*T + B*Tq][nchunks] maximum per chunk
+    double *part_l;             // and its sum of exponentials
+    int nchunks;
     float *ubuf;                // [B][V] unnormalised residual of the node being verified (lone walk, long slices)
     int co_laps;                // long slices: how often R float4 per lane go into one
     unsigned int *co_ctl;       // [B][32]
@@ -64,7 +69,8 @@ __device__ __forceinline__ float exp_rel_f32(float x, float m, float inv_temp) {
 // a value that is the same in every lane (read from LDS, say), kept in a scalar register
 __device__ __forceinline__ int uniform_of(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// sum over the workgroup of one double per thread, fixed order; every thread gets it
+// sum over the workgroup of N threads of one double per thread, fixed order; every thread gets it
+template <int N>
 __device__ __forceinline__ double block_sum_f64(double v, double *wred) {
     const double ws = wave_sum_f64(v);
     __syncthreads();
@@ -72,15 +78,15 @@ __device__ __forceinline__ double block_sum_f64(double v, double *wred) {
     __syncthreads();
     double t = 0.0;
 #pragma unroll
-    for (int i = 0; i < kAqAllWaves; ++i) t += wred[i];
+    for (int i = 0; i < N / kWave; ++i) t += wred[i];
     return t;
 }
 
 // ------------------------------------------------------------------------ walk by one workgroup
 struct AqSmem {
     double gsum[kAqMaxGran];     // residual mass per 256 tokens (of the last pass)
-    double wred[kAqAllWaves];
-    float wmax[kAqAllWaves];
+    double wred[kAqLone / kWave];
+    float wmax[kAqLone / kWave];
     double px[kWave];            // per node: residual at its token under its parent
     float qx[kWave];             // draft logit of its token
     int par[kWave], tok[kWave], qrow[kWave];
@@ -88,25 +94,38 @@ struct AqSmem {
     double W;                    // mass of the residual
     unsigned long long kids;     // untried children of the current node
     int cur, len, next, have_u;
+    int chunk;                   // where the bonus token lies, and the mass in front of it
+    double before;
 };
 
-// maximum of a row and sum of exp((x - maximum) * inv) (all threads call it)
-template <bool VEC4>
-__device__ __forceinline__ void row_stats(const AqArgs &a, AqSmem &s, const float *row, double inv, float *m_out, double *l_out) {
+// maximum of a row and sum of exp((x - maximum) * inv) (all threads call it): row number `id` of the call, from the
+// statistics launch if there was one, else from the row itself
+template <bool VEC4, int N, bool PARTS>
+__device__ __forceinline__ void row_stats(const AqArgs &a, AqSmem &s, const float *row, int id, double inv, float *m_out, double *l_out) {
     const int tid = threadIdx.x;
     float m = -INFINITY;
     double l = 0.0;
+    if constexpr (PARTS) {                                           // at most 64 chunks, one per lane, in every wavefront
+        const bool has = lane_id() < a.nchunks;
+        const size_t at = (size_t)id * a.nchunks + min(lane_id(), a.nchunks - 1);
+        const float mc = has ? a.part_m[at] : -INFINITY;
+        const double lc = a.part_l[at];
+        m = wave_max_f32(mc);
+        *m_out = m;
+        *l_out = wave_sum_f64(mc > -INFINITY ? lc * exp(((double)mc - (double)m) * inv) : 0.0);
+        return;
+    }
     for (int pass = 0; pass < 2; ++pass) {
         if (VEC4) {
 #pragma unroll 4
-            for (int i = tid * 4; i < a.V; i += kAqThreads * 4) {
+            for (int i = tid * 4; i < a.V; i += N * 4) {
                 const float4 v = *reinterpret_cast<const float4 *>(row + i);
                 if (pass == 0) m = fmaxf(fmaxf(fmaxf(m, v.x), fmaxf(v.y, v.z)), v.w);
                 else l += (exp_rel(v.x, m, inv) + exp_rel(v.y, m, inv)) + (exp_rel(v.z, m, inv) + exp_rel(v.w, m, inv));
             }
         } else {
 #pragma unroll 4
-            for (int i = tid; i < a.V; i += kAqThreads) {
+            for (int i = tid; i < a.V; i += N) {
                 if (pass == 0) m = fmaxf(m, row[i]);
                 else l += exp_rel(row[i], m, inv);
             }
@@ -117,32 +136,32 @@ __device__ __forceinline__ void row_stats(const AqArgs &a, AqSmem &s, const floa
             if (lane_id() == 0) s.wmax[wave_id()] = m;
             __syncthreads();
 #pragma unroll
-            for (int i = 0; i < kAqAllWaves; ++i) m = fmaxf(m, s.wmax[i]);
+            for (int i = 0; i < N / kWave; ++i) m = fmaxf(m, s.wmax[i]);
         }
     }
     *m_out = m;
-    *l_out = block_sum_f64(l, s.wred);
+    *l_out = block_sum_f64<N>(l, s.wred);
 }
 
-// One pass over tokens [0, hi) of sequence b:
+// One pass over tokens [lo, hi) of sequence b (lo a multiple of 256):
 //   u(i) = have_u ? ubuf[i] : softmax(target row)[i];   u(i) <- max(0, u(i) - W * q(i)) when q is given;
-// u is written to ubuf (as fp32), its sums per 256 tokens to s.gsum[i / 256]; returns the total
+// u is written to ubuf (as fp32), its sums per 256 tokens to s.gsum[(i - lo) / 256]; returns the total
 // of the stored values.  All threads call it.
-template <bool VEC4>
+template <bool VEC4, int N>
 __device__ __forceinline__ double residual_pass(const AqArgs &a, AqSmem &s, int b, const float *prow, float pm, double pinv_l,
-                                                const float *qrow, float qm, double qinv_l, double W, int hi) {
+                                                const float *qrow, float qm, double qinv_l, double W, int lo, int hi) {
     const int tid = threadIdx.x, lane = lane_id();
     float *ub = a.ubuf + (size_t)b * a.V;
-    const int ngran = (hi + kAqGran - 1) / kAqGran;
+    const int ngran = (hi - lo + kAqGran - 1) / kAqGran;
     const float it_f = (float)a.inv_t, itd_f = (float)a.inv_td, pinv_l_f = (float)pinv_l, qinv_l_f = (float)qinv_l, W_f = (float)W;
-    constexpr int U = 4;                                             // 2304-token steps whose loads are in flight together
-    for (int base0 = tid * 4; base0 - lane * 4 < hi; base0 += U * kAqThreads * 4) {
+    constexpr int U = VEC4 ? 4 : 3;                                  // steps of 4 N tokens whose loads are in flight together (word by word a fourth spills)
+    for (int base0 = lo + tid * 4; base0 - lane * 4 < hi; base0 += U * N * 4) {
         float u4[U][4], q4[U][4];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const int base = base0 + k * kAqThreads * 4;
+            const int base = base0 + k * N * 4;
             if (VEC4) {                                              // V % 4 == 0: a float4 is all in or all out
-                const int i0 = base < hi ? base : 0;                 // out of range: any legal address, masked below
+                const int i0 = base < hi ? base : lo;                // out of range: any legal address, masked below
                 const float4 v = *reinterpret_cast<const float4 *>((prow ? prow : ub) + i0);
                 u4[k][0] = v.x; u4[k][1] = v.y; u4[k][2] = v.z; u4[k][3] = v.w;
                 if (qrow) {
@@ -160,7 +179,7 @@ __device__ __forceinline__ double residual_pass(const AqArgs &a, AqSmem &s, int 
         }
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const int base = base0 + k * kAqThreads * 4;
+            const int base = base0 + k * N * 4;
             if (base - lane * 4 >= hi) break;                        // wave-uniform
             // fp32 per token (one workgroup's vector ALUs, not its memory path, bound this loop), fp64 sums
             float out[4];
@@ -179,23 +198,23 @@ __device__ __forceinline__ double residual_pass(const AqArgs &a, AqSmem &s, int 
                     if (base + j < hi) ub[base + j] = out[j];
             }
             sum = wave_sum_f64(sum);
-            if (lane == 0) s.gsum[base / kAqGran] = sum;
+            if (lane == 0) s.gsum[(base - lo) / kAqGran] = sum;
         }
     }
     __syncthreads();
     double part = 0.0;
-    for (int g = tid; g < ngran; g += kAqThreads) part += s.gsum[g];
-    return block_sum_f64(part, s.wred);
+    for (int g = tid; g < ngran; g += N) part += s.gsum[g];
+    return block_sum_f64<N>(part, s.wred);
 }
 
-// Inverse CDF by wavefront 0: first token i in [0, hi) with sum_{0..i} u > target, or, if
+// Inverse CDF by wavefront 0: first token i in [lo, hi) with before0 + sum_{lo..i} u > target, or, if
 // the sums never get there (rounding), the last token with u > 0; -1 if there is none.  The sums per
 // 256 tokens are in s.gsum, u itself in ubuf.  Returns the token to every lane of wavefront 0.
 template <bool VEC4>
-__device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, double target, int hi) {
+__device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, double before0, double target, int lo, int hi) {
     const int lane = lane_id();
     const float *ub = a.ubuf + (size_t)b * a.V;
-    const int ngran = (hi + kAqGran - 1) / kAqGran;
+    const int ngran = (hi - lo + kAqGran - 1) / kAqGran;
     const int per = (ngran + kWave - 1) / kWave;
     // each lane owns `per` consecutive granules
     double mine = 0.0;
@@ -205,14 +224,14 @@ __device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, dou
         if (s.gsum[g] > 0.0) last_pos = g;
     }
     const double incl = wave_scan_f64(mine);
-    const uint64_t cross = __ballot(incl > target);
+    const uint64_t cross = __ballot(before0 + incl > target);
     int g_pick;
     double before;
     if (cross != 0) {
         const int owner = __ffsll((long long)cross) - 1;
         // the owner walks its granules
         int g_loc = -1;
-        double acc = incl - mine, bef = acc;
+        double acc = before0 + incl - mine, bef = acc;
         for (int g = lane * per; g < min((lane + 1) * per, ngran); ++g) {
             if (g_loc < 0) {
                 bef = acc;
@@ -236,7 +255,7 @@ __device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, dou
         before = -1.0;                                               // marks "take the last positive token"
     }
     // the 256 tokens of the granule, 4 per lane in token order
-    const int i0 = g_pick * kAqGran + lane * 4;
+    const int i0 = lo + g_pick * kAqGran + lane * 4;
     double v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = (i0 + j < hi) ? (double)ub[i0 + j] : 0.0;
@@ -272,13 +291,13 @@ __device__ __forceinline__ int pick_token(const AqArgs &a, AqSmem &s, int b, dou
     return __shfl(pick, owner2);
 }
 
-// The whole walk of sequence b by one workgroup (every thread calls it).
-template <bool VEC4>
+// The whole walk of sequence b by one workgroup of N threads (all of them call it).
+template <bool VEC4, int N, bool PARTS>
 __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int nn = a.n_nodes ? min(max(a.n_nodes[b], 0), a.T) : a.T;
     int32_t *path = a.accept_path + (size_t)b * (a.D_max + 1);
-    for (int d = tid; d <= a.D_max; d += kAqThreads) path[d] = d == 0 && nn >= 1 ? 0 : -1;
+    for (int d = tid; d <= a.D_max; d += N) path[d] = d == 0 && nn >= 1 ? 0 : -1;
     if (nn < 1) {
         if (tid == 0) { a.accept_len[b] = 0; a.bonus[b] = -1; }
         return;
@@ -299,7 +318,7 @@ __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
         float pm, qm = 0.f;
         double pl, ql = 1.0;
         int q_have = -1;                                             // the draft row whose statistics are at hand
-        row_stats<VEC4>(a, s, prow, a.inv_t, &pm, &pl);
+        row_stats<VEC4, N, PARTS>(a, s, prow, b * a.T + cur, a.inv_t, &pm, &pl);
         const double pinv_l = 1.0 / pl;
         // ---- children of cur (ascending node index) and, for each, p(token) and its draft logit
         if (w == 0) {
@@ -317,14 +336,14 @@ __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
         while (s.kids != 0 && s.next < 0 && s.W > 0.0) {
             const int c = __ffsll((long long)s.kids) - 1, qr = s.qrow[c];
             const float *qrow = a.draft + ((size_t)b * a.Tq + qr) * a.V;
-            if (qr != q_have) { row_stats<VEC4>(a, s, qrow, a.inv_td, &qm, &ql); q_have = qr; }
+            if (qr != q_have) { row_stats<VEC4, N, PARTS>(a, s, qrow, a.B * a.T + b * a.Tq + qr, a.inv_td, &qm, &ql); q_have = qr; }
             const double W = s.W;
             const bool accept = (double)s.uni[c] * W * (exp_rel(s.qx[c], qm, a.inv_td) / ql) < s.px[c];
             __syncthreads();                                         // everyone has read the state of this test
             if (accept) {
                 if (tid == 0) s.next = c;
             } else {
-                const double total = residual_pass<VEC4>(a, s, b, s.have_u ? nullptr : prow, pm, pinv_l, qrow, qm, 1.0 / ql, W, a.V);
+                const double total = residual_pass<VEC4, N>(a, s, b, s.have_u ? nullptr : prow, pm, pinv_l, qrow, qm, 1.0 / ql, W, 0, a.V);
                 // the residual at the tokens of the children still to be tried (written by this workgroup)
                 const unsigned long long rest = s.kids & ~(1ull << c);
                 if (w == 0 && ((rest >> lane) & 1)) s.px[lane] = (double)a.ubuf[(size_t)b * a.V + s.tok[lane]];
@@ -345,12 +364,33 @@ __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
         }
         // ---- bonus token from the residual (or from p itself when nothing was rejected, or when
         // the residual vanished)
-        double W = s.W;
+        double W = s.W, before0 = 0.0;
+        int lo = 0, hi = a.V;
         const bool use_u = s.have_u && W > 0.0;
         __syncthreads();
-        if (!use_u) W = residual_pass<VEC4>(a, s, b, prow, pm, pinv_l, nullptr, 0.f, 0.0, 0.0, a.V);
+        if (PARTS && !use_u) {
+            // the chunk that the token lies in, from the row's partials; u = p is then made on that chunk only
+            W = 1.0;
+            if (w == 0) {
+                const float mc = lane < a.nchunks ? a.part_m[((size_t)b * a.T + cur) * a.nchunks + lane] : -INFINITY;
+                const double mass = mc > -INFINITY ? a.part_l[((size_t)b * a.T + cur) * a.nchunks + lane] * exp(((double)mc - (double)pm) * a.inv_t) * pinv_l : 0.0;
+                const double incl = wave_scan_f64(mass);
+                const uint64_t cross = __ballot(lane < a.nchunks && incl > (double)s.uni[a.T]), has = __ballot(mass > 0.0);
+                const int ch = cross ? __ffsll((long long)cross) - 1 : has ? 63 - __clzll((long long)has) : 0;
+                const double bef = readlane_f64(incl - mass, ch);
+                if (lane == 0) { s.chunk = ch; s.before = bef; }
+            }
+            __syncthreads();
+            lo = s.chunk * kAqChunk;
+            hi = min(a.V, lo + kAqChunk);
+            before0 = s.before;
+        }
+        if (!use_u) {
+            const double mass = residual_pass<VEC4, N>(a, s, b, prow, pm, pinv_l, nullptr, 0.f, 0.0, 0.0, lo, hi);
+            if (!PARTS) W = mass;
+        }
         if (w == 0) {
-            const int pick = pick_token<VEC4>(a, s, b, (double)s.uni[a.T] * W, a.V);
+            const int pick = pick_token<VEC4>(a, s, b, before0, (double)s.uni[a.T] * W, lo, hi);
             if (lane == 0) {
                 a.bonus[b] = pick;
                 a.accept_len[b] = len;
@@ -360,10 +400,73 @@ __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
     }
 }
 
+// Statistics of every row that a lone walk may visit, taken by the whole chip beforehand: one workgroup per 16384
+// logits of a row leaves its maximum and sum; the walk merges a row's when it gets there.  (Where that
+// pays: aq_take_statistics.)
 template <bool VEC4>
-__global__ __launch_bounds__(kAqThreads) void accept_q_walk_kernel(AqArgs a) {
+__global__ __launch_bounds__(kAqStream) void accept_q_stats_kernel(AqArgs a) {
+    __shared__ float wm[kAqWaves];
+    __shared__ double wl[kAqWaves];
+    const int tid = threadIdx.x, lane = lane_id(), id = blockIdx.y, lo = blockIdx.x * kAqChunk;
+    const bool is_target = id < a.B * a.T;
+    const int b = is_target ? id / a.T : (id - a.B * a.T) / a.Tq, r = is_target ? id % a.T : (id - a.B * a.T) % a.Tq;
+    const int nn = a.n_nodes ? min(max(a.n_nodes[b], 0), a.T) : a.T;
+    if (is_target) {
+        if (r >= nn) return;
+    } else {                                                         // the rows of live nodes other than the root
+        const int qr = lane >= 1 && lane < nn ? (a.q_rows ? a.q_rows[(size_t)b * a.T + lane] : lane) : -1;
+        if (__ballot(qr == r) == 0) return;
+    }
+    const float *row = is_target ? a.target + (size_t)id * a.V : a.draft + (size_t)(id - a.B * a.T) * a.V;
+    const double inv = is_target ? a.inv_t : a.inv_td;
+    constexpr int R = kAqChunk / (kAqStream * 4);
+    float x[R][4], m = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int i0 = lo + (k * kAqStream + tid) * 4;
+        if (VEC4) {
+            const float4 v = *reinterpret_cast<const float4 *>(row + (i0 < a.V ? i0 : 0));
+            x[k][0] = v.x; x[k][1] = v.y; x[k][2] = v.z; x[k][3] = v.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[k][j] = row[min(i0 + j, a.V - 1)];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            x[k][j] = lo + (k * kAqStream + tid) * 4 + j < a.V ? x[k][j] : -INFINITY;
+            m = fmaxf(m, x[k][j]);
+        }
+    m = wave_max_f32(m);
+    if (lane == 0) wm[wave_id()] = m;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kAqWaves; ++i) m = fmaxf(m, wm[i]);
+    double l = 0.0;
+    if (m > -INFINITY) {
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) l += inv == 1.0 ? (double)exp_rel_f32(x[k][j], m, 1.f) : exp_rel(x[k][j], m, inv);   // (the same value)
+    }
+    l = wave_sum_f64(l);
+    if (lane == 0) wl[wave_id()] = l;
+    __syncthreads();
+    if (tid == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < kAqWaves; ++i) t += wl[i];
+        a.part_m[(size_t)id * a.nchunks + blockIdx.x] = m;
+        a.part_l[(size_t)id * a.nchunks + blockIdx.x] = t;
+    }
+}
+
+template <bool VEC4, bool PARTS>
+__global__ __launch_bounds__(kAqLone) void accept_q_walk_kernel(AqArgs a) {
     __shared__ AqSmem s;
-    walk_single<VEC4>(a, s, blockIdx.x);
+    walk_single<VEC4, kAqLone, PARTS>(a, s, blockIdx.x);
 }
 
 // ------------------------------------------------------------------- walk by several workgroups
@@ -941,7 +1044,7 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
     }
     if (!redo) return;
     __syncthreads();
-    walk_single<VEC4>(a, lds.alone, b);
+    walk_single<VEC4, kAqThreads, false>(a, lds.alone, b);
 }
 
 }  // namespace radar
@@ -985,12 +1088,29 @@ static void aq_coop_plan(const radar_accept_q_desc *d, int *G, int *R, int *laps
     *G = g; *R = r; *laps = n;
 }
 
+// Whether a lone walk's rows have their statistics taken beforehand.  Inside the walk a row costs its workgroup two
+// passes at 64 KB/us, however many sequences walk beside it; beforehand every row of the call costs the chip one pass,
+// and a launch.  Measured (us, inside / beforehand): one sequence, 122 rows, V = 8192 12.3 / 14.9, 16000 21.9 / 20.5,
+// 32000 23.5 / 15.8, 128256 184 / 146, 1048576 1022 / 714; 488 rows of 128256 217 / 200, 732 264 / 289, 1464 261 / 338;
+// 976 rows of 32000, which the memory-side cache holds, 126 / 105, of 128256 270 / 304; 2240 of 32000 76 / 89.
+static bool aq_take_statistics(const radar_accept_q_desc *d) {
+    const int64_t rows = (int64_t)d->B * ((int64_t)d->T_max + d->Tq);
+    return d->V >= 12288 && (rows <= 600 || (rows <= 1000 && rows * d->V <= (int64_t(1) << 26)));
+}
+
+static int aq_chunks(const radar_accept_q_desc *d) { return (d->V + kAqChunk - 1) / kAqChunk; }
+
 extern "C" size_t radar_verify_accept_q_workspace_bytes(const radar_accept_q_desc *d) {
     if (!d || d->B < 1 || d->T_max < 1 || d->Tq < 1 || d->V < 1) return 0;
     size_t bytes = ((size_t)d->B * d->V * sizeof(float) + 255) & ~size_t(255);
     bytes += ((size_t)d->B * kCoCtl * sizeof(unsigned int) + 255) & ~size_t(255);
     bytes += ((size_t)d->B * 2 * kCoG * kCoWords * sizeof(uint64_t) + 255) & ~size_t(255);
     bytes += ((size_t)d->B * 2 * kWave * sizeof(uint64_t) + 255) & ~size_t(255);
+    if (aq_take_statistics(d)) {
+        const size_t parts = (size_t)d->B * ((size_t)d->T_max + d->Tq) * aq_chunks(d);
+        bytes += (parts * sizeof(float) + 255) & ~size_t(255);
+        bytes += (parts * sizeof(double) + 255) & ~size_t(255);
+    }
     return bytes;
 }
 
@@ -1035,8 +1155,23 @@ extern "C" radar_status radar_verify_accept_q(const float *target_logits, const 
     const dim3 grid((unsigned)G, (unsigned)d->B), block(kAqThreads);
     hipError_t e;
     if (G == 1) {
-        e = vec4 ? launch("accept_q_walk", accept_q_walk_kernel<true>, dim3((unsigned)d->B), block, 0, st, a)
-                 : launch("accept_q_walk", accept_q_walk_kernel<false>, dim3((unsigned)d->B), block, 0, st, a);
+        const bool parts = aq_take_statistics(d);
+        if (parts) {
+            const size_t rows = (size_t)d->B * ((size_t)d->T_max + d->Tq);
+            a.nchunks = aq_chunks(d);
+            a.part_m = reinterpret_cast<float *>(take(rows * a.nchunks * sizeof(float)));
+            a.part_l = reinterpret_cast<double *>(take(rows * a.nchunks * sizeof(double)));
+            const dim3 all((unsigned)a.nchunks, (unsigned)rows);
+            e = vec4 ? launch("accept_q_stats", accept_q_stats_kernel<true>, all, dim3(kAqStream), 0, st, a)
+                     : launch("accept_q_stats", accept_q_stats_kernel<false>, all, dim3(kAqStream), 0, st, a);
+            if (e != hipSuccess) return RADAR_HIP_ERROR;
+        }
+        auto go = [&](auto has) {
+            constexpr bool P = decltype(has)::value;
+            return vec4 ? launch("accept_q_walk", accept_q_walk_kernel<true, P>, dim3((unsigned)d->B), dim3(kAqLone), 0, st, a)
+                        : launch("accept_q_walk", accept_q_walk_kernel<false, P>, dim3((unsigned)d->B), dim3(kAqLone), 0, st, a);
+        };
+        e = parts ? go(std::true_type{}) : go(std::false_type{});
     } else {
         auto go = [&](auto r, auto laps) {
             constexpr int RR = decltype(r)::value;
