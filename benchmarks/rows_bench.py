@@ -59,7 +59,7 @@ def main():
     ws = b.new_workspace(b.radar_verify_accept_workspace_bytes(desc))
     call = b.radar_accept_length_distribution(d["target_logits"], d["draft_tokens"], d["parents"], d["n_nodes"],
                                               workspace=ws, prepared=True)
-    timed("radar_accept_length_distribution", [call], T * V * 4, "61 target rows read once")
+    timed("radar_accept_length_distribution", [call], T * V * 4, "bytes: 61 target rows, of which those of leaves are left unread")
 
     pw = synth.policy_params(rng, k)
     pp = b.policy_params({n: to(v) for n, v in pw.items()})

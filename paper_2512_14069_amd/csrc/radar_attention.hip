@@ -43,7 +43,7 @@ constexpr int kAttnWaves = 4;
 constexpr int kKT = 64;                    // cache rows per LDS tile
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr float kMaxSlack = 8.0f;          // how far a row's maximum may pass its reference (log2 units)
+constexpr float kMaxSlack = 8.0f;          // how far a row's maximum may pass its reference (log2 units; tile_softmax)
 constexpr float kNegBig = -1.0e30f;        // finite stand-in for "no score yet" (log2 units)
 
 struct AttnArgs {
@@ -183,9 +183,13 @@ __device__ __forceinline__ void tile_softmax(floatx16 (&sacc)[2], floatx16 (&oac
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[sub][r]);
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     // The reference the exponentials are taken against follows the maximum only when that has risen by
-    // more than 8 (a factor of 256 in a probability, which neither bf16 nor the fp32 sums notice): the
-    // maxima of 32 rows keep moving a little in most tiles, and each move would cost rescaling the
-    // accumulators, a sixth of a tile's vector instructions.
+    // more than 8 (a factor of 256 in a probability): the maxima of 32 rows keep moving a little in most
+    // tiles, and each move would cost rescaling the accumulators, a sixth of a tile's vector instructions.
+    // Probabilities keep their eight bits and sums their fp32, but a row's largest probability is no longer
+    // exactly 1: against 64 bits the output is off by 2.24e-3 (2-norm, N(0,1) scores, 2048 rows) instead of
+    // 2.15e-3, by 1.86e-3 instead of 1.68e-3 with scores four times as wide, both mostly the output's own
+    // rounding to bf16.  Time with / without the slack: 2048 rows 14.5 / 14.7 us, ragged 16 79.4 / 81.2,
+    // 4 x 16384 rows with 64 heads 148.5 / 155.8.
     const float mt = mx * scale_log2;                                // scale_log2 > 0; -inf stays -inf
     const float m_new = mt > m_run + kMaxSlack ? mt : m_run;
     if (!first && __any(m_new != m_run)) {                           // wave-uniform
