@@ -11,6 +11,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # packed fp32 arithmetic is kept off for device code
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # a kernel's leading scalar arguments are in registers when it starts (as many as fit into the 16 that the
+         # hardware fills), so that its first loads do not wait for the argument segment
+         "-mllvm", "-amdgpu-kernarg-preload-count=14",
          # the loads that write LDS directly are issued as assembly and name m0, a reserved register, as clobbered
          "-Wno-inline-asm"]
 

@@ -31,8 +31,10 @@ constexpr int kCounterStride = 32;                    // arrival counters sit 12
                                                       // cache line serialise at roughly 10 ns each
 constexpr size_t kCounterBytes = 16384;               // leading counter block of the workspace
 constexpr float kLog2eF = 1.4426950408889634f;
-constexpr int kDumpCap = 64;                          // hot lanes (largest logit reaches the threshold) whose logits go through LDS
+constexpr int kStreamers = 4;                         // wavefronts of a workgroup that stream
+constexpr int kDumpCap = 32;                          // hot lanes of one of them (largest logit reaches the threshold) whose logits go through LDS
 constexpr int kFastCap = 512;                         // chunk candidates ranked by the short path; more (runs of equal values) rank per wavefront
+constexpr int kFewChunks = 16;                        // rows of so many chunks are merged the short way (expand_finish)
 constexpr int kFrontierMax = 256;                     // candidates of a call that are ranked by counting
 constexpr int64_t kStreamMinLogits = 4 << 20;         // batched calls of at least 16 MB of logits take the streaming path
 
@@ -55,7 +57,7 @@ struct ExpandArgs {
     int F, V, k, nchunks, pool_count;
     int pool_capacity;          // length of one sequence's pool arrays (their stride in a batched call)
     unsigned int *counters;     // [0] rows finished, [(1+f) * kCounterStride] chunks of row f finished
-    uint64_t *part_keys;        // [F][nchunks][RADAR_K_MAX] best first, 0 where a chunk has fewer
+    uint64_t *part_keys;        // [F][nchunks][RADAR_K_MAX] in any order, 0 where a chunk has fewer
     double *part_l;             // [F][nchunks] sum of exp(x - part_m) over the chunk
     float *part_m;              // [F][nchunks] chunk maximum
     PolicyArgs pol;             // prediction model run by the last workgroup when has_policy != 0
@@ -68,12 +70,12 @@ struct ExpandArgs {
 struct alignas(16) ExpandSmem {
     WaveTopkSmem wtk[kExpWaves];                  // one scratch per wavefront
     uint64_t wlist[kExpWaves * kWaveListSlots];   // the wavefronts' candidates of a chunk (0 = none; many ties only)
-    float gmax[16];                               // maxima of the sixteen 16-lane rows of the streaming wavefronts
-    float wave_l[4];                              // sum of exp(x - chunk maximum) over each streaming wavefront
+    float gmax[8 * kStreamers];                   // maxima of the 8-lane groups of the streaming wavefronts
+    float wave_l[kStreamers], cmax;               // sum of exp(x - chunk maximum) over each streaming wavefront; the maximum
     unsigned int nsurv;                           // candidates of the chunk that reached the threshold
-    unsigned int ndump;                           // lanes whose largest logit reached it
+    unsigned int ndump[kStreamers];               // lanes of each streaming wavefront whose largest logit reached it
     float tau;                                    // the threshold
-    unsigned short dump_lane[kDumpCap];           // which lane left each block of logits
+    unsigned char dump_lane[kStreamers][kDumpCap];   // which lane left each block of logits
     // last workgroup only: candidate c = f * k + r (row f, rank r in it)
     float cand_sc[RADAR_F_MAX * 16];
     int cand_tok[RADAR_F_MAX * 16];
@@ -84,12 +86,12 @@ struct alignas(16) ExpandSmem {
 };
 
 // 512 slots, starting at c0, of one row's chunk lists in the workspace (device-scope loads)
-__device__ __forceinline__ void load_key_block(const uint64_t *pk, int nslot, int c0, int K, uint64_t (&kk)[9]) {
+__device__ __forceinline__ void load_key_block(const uint64_t *pk, int nslot, int c0, uint64_t (&kk)[9]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int i = c0 + topk_slot_of(e);
         const uint64_t key = load_shared_result(pk + min(i, nslot - 1));     // branch-free: clamp, load, mask
-        kk[e] = (i < nslot && (i & 15) < K) ? key : 0;
+        kk[e] = i < nslot ? key : 0;
     }
     kk[8] = 0;
 }
@@ -98,7 +100,7 @@ __device__ __forceinline__ void load_key_block(const uint64_t *pk, int nslot, in
 __device__ __forceinline__ uint64_t row_topk(uint64_t (&kk)[9], const uint64_t *pk, int nslot, int K, WaveTopkSmem &scratch) {
     uint64_t top = wave_topk<9>(kk, K, scratch);
     for (int c0 = 8 * kWave; c0 < nslot; c0 += 8 * kWave) {        // V > 131072 only
-        load_key_block(pk, nslot, c0, K, kk);
+        load_key_block(pk, nslot, c0, kk);
         kk[8] = top;                                                 // the running selection rides along
         top = wave_topk<9>(kk, K, scratch);
     }
@@ -197,7 +199,7 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
                                               bool cycle_first, Settle &&settle, Hidden &&hidden) {
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int K = a.k, n = a.F * K;
-    const bool few = a.nchunks <= 16;                              // (V <= 131072 at 8 logits per lane)
+    const bool few = a.nchunks <= kFewChunks;                      // (V <= 131072 at 8 logits per lane)
     const int nslot = a.nchunks * RADAR_K_MAX;
     if (tid >= n && tid < kFrontierMax) s.cand_key[tid] = 0;
     if (MODE == kExpPolicy && tid < RADAR_K_MAX) s.pol.in[kPolH + tid] = 0.f;
@@ -215,10 +217,10 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
             for (int e = 0; e < 4; ++e) {
                 const int i = topk_slot_of(e);
                 const uint64_t key = load_shared_result(pk + min(i, nslot - 1));
-                kk[e] = (i < nslot && (i & 15) < K) ? key : 0;
+                kk[e] = i < nslot ? key : 0;
             }
         } else {
-            load_key_block(pk, nslot, 0, K, kk);
+            load_key_block(pk, nslot, 0, kk);
         }
         // chunk partials, one chunk per lane first (up to 16 chunks: every 16-lane row of the wavefront takes all)
         const int c = min(few ? (lane & 15) : lane, a.nchunks - 1);
@@ -317,11 +319,23 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
 }
 
 // MODE: the plain expansion is compiled without any code for batches, cycle states or the prediction model.
+// A call is a chain of dependent stages, none of which is bound by bandwidth.  Times of the last workgroup at F = 10,
+// V = 128256, k = 10, us after the first one starts: row maxima 1.1, threshold and hot lanes 1.8, candidates
+// and sums 2.5, list stored 2.8, row ticket 3.9, call ticket 4.3, lists loaded 5.1, rows merged 6.9, frontier 7.8;
+// a launch adds about 1.  8.2 us per call on warm logits (8.9 with sixteen groups for the threshold, the exponentials before it
+// and every list ranked), 11.7 instead of 28.9 for 16 rows with k = 16, where the sixteen groups' threshold
+// let whole chunks through.  Lists longer than 16 slots need no ranking at all, but the last workgroup's loads are
+// slow (from beyond its L2, 37 bytes per ns): 24 slots cost it 0.4 us, records of 32 0.7.
+// The leading arguments are what the stream waits for; they are in registers when the kernel starts (0.25 us).
 template <bool VEC4, int EPT, int MODE>
-__global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(ExpandArgs a) {
+__global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *logits, int F, int V, int k, int nchunks, int pool_count,
+                                                                radar_cycle_state *cycle_, uint64_t *part_keys, unsigned int *counters,
+                                                                ExpandArgs a) {
     constexpr bool EXT = MODE != kExpPlain;
+    a.logits = logits; a.F = F; a.V = V; a.k = k; a.nchunks = nchunks; a.pool_count = pool_count;
+    a.cycle = cycle_; a.part_keys = part_keys; a.counters = counters;
     static_assert(EPT == 4 || EPT == 8 || EPT == 16, "EPT");
-    static_assert(kFastCap + 8 <= kWave * kWaveTopkMaxEPL + 8 && kExpWaves == 16, "candidate list inside the selection scratch");
+    static_assert(kFastCap + 8 <= kWave * kWaveTopkMaxEPL + 8 && kExpWaves == 16 && kStreamers == 4, "candidate list inside the selection scratch");
     constexpr int kChunk = kExpThreads * EPT;
     __shared__ ExpandSmem s;
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
@@ -352,13 +366,13 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(ExpandArgs a) {
     // the call (one row each, the prediction model).  NE/4 x (256 lanes x 16 B) coalesced loads, all
     // issued before anything is computed from them (out-of-range lanes read a valid address and are
     // masked).
-    constexpr int kStreamers = 4;                                  // wavefronts that stream
     constexpr int kSLanes = kStreamers * kWave;
     constexpr int NE = EPT * (kExpThreads / kSLanes);              // logits per streaming lane
     const bool streamer = w < kStreamers;
     const bool tail = base + kChunk > a.V;                         // the row ends inside this chunk
     float x[NE];
     if (streamer) {
+        __builtin_amdgcn_s_setprio(3);                             // the others wait for these four
         float4 raw[NE / 4];
 #pragma unroll
         for (int g = 0; g < NE / 4; ++g) {
@@ -392,45 +406,62 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(ExpandArgs a) {
     const bool hidden_rows = MODE == kExpPolicy && a.pol_has_state && !streamer;
     if (hidden_rows) hrows.load(a.pol, bz, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid / 32 - 2 * kStreamers);
 
-    // ---- the chunk's maximum, and the threshold of its top-k: the k-th largest of the maxima of the
-    // sixteen 16-lane rows of the streaming wavefronts.  At least k logits of the chunk reach it (one
-    // per row whose maximum does), and on untied data only about 1.6 k do.  Everything here is a
-    // chain of latencies (a ballot whose count a scalar instruction needs costs ~30 cycles, a lane
-    // read with a compare ~40, an LDS round trip ~120), so the steps are laid out to run side by
-    // side: a wavefront that does not stream ranks the sixteen maxima while the streaming ones take
-    // their exponentials, and logits are compared with the threshold only where they can reach it.
+    // ---- the threshold of the chunk's top-k: the k-th largest of the maxima of the 32 eight-lane groups of the
+    // streaming wavefronts.  At least k logits of the chunk reach it (one per group whose maximum does), and on
+    // untied data 1.2 k (k = 10) to 1.4 k (k = 16).  Everything here is a chain of latencies (a ballot whose
+    // count a scalar instruction needs costs ~30 cycles, a lane read with a compare ~40, an LDS round trip
+    // ~120), so every streaming wavefront finds the threshold by itself, in vector registers, and the
+    // exponentials wait until the other wavefronts have something to do beside them.
     float lmax = -INFINITY;                                        // the lane's largest logit
     if (streamer) {
         lmax = x[0];
 #pragma unroll
         for (int e = 1; e < NE; ++e) lmax = fmaxf(lmax, x[e]);
-        float rm = lmax;
-        rm = fmaxf(rm, dpp_f32<0xB1>(rm));
-        rm = fmaxf(rm, dpp_f32<0x4E>(rm));
-        rm = fmaxf(rm, dpp_f32<0x141>(rm));
-        rm = fmaxf(rm, dpp_f32<0x140>(rm));                        // every lane: the maximum of its 16-lane row
-        if ((lane & 15) == 0) s.gmax[w * 4 + (lane >> 4)] = rm;
+        float gm = lmax;
+        gm = fmaxf(gm, dpp_f32<0xB1>(gm));
+        gm = fmaxf(gm, dpp_f32<0x4E>(gm));
+        gm = fmaxf(gm, dpp_f32<0x141>(gm));                        // every lane: the maximum of its eight lanes
+        if ((lane & 7) == 0) s.gmax[w * 8 + (lane >> 3)] = gm;
     }
-    if (tid == 0) { s.nsurv = 0; s.ndump = 0; }
+    if (tid == 0) s.nsurv = 0;
     __syncthreads();
-    float cm = 0.f;                                                // chunk maximum (streamers, and wavefront 1 below)
-    if (w == kStreamers) {
-        // threshold: the k-th largest of the sixteen maxima (ties: lower row first), by one wavefront
-        const uint32_t ov = ord_of(s.gmax[lane & 15]);             // every 16-lane row holds the 16 maxima
-        int larger = 0;
+    // Lanes whose largest logit reaches the threshold (about 1.2 k of the 256) leave all their logits
+    // in LDS; only those are compared one by one afterwards.
+    float *const dump = reinterpret_cast<float *>(&s.wtk[1]);      // [kStreamers][kDumpCap][NE], inside the selection scratch
+    uint64_t *const surv = s.wtk[0].surv;                          // kFastCap + 8 slots
+    static_assert(kStreamers * kDumpCap * NE * sizeof(float) <= (kExpWaves - 1) * sizeof(WaveTopkSmem), "dump inside the scratch");
+    float cm = 0.f;                                                // chunk maximum (streamers)
+    if (streamer) {
+        const float g32 = s.gmax[lane & 31];
+        const float tau = float_of_ord(kth_of_32(ord_of(g32), K));
+        const bool hot = lmax >= tau && base + tid * 4 < a.V;      // (a lane wholly past the row holds -inf only)
+        const uint64_t hm = __ballot(hot);
+        if (hot) {
+            const int at = lanes_below(hm);
+            if (at < kDumpCap) {
+                float4 *d4 = reinterpret_cast<float4 *>(dump + (size_t)(w * kDumpCap + at) * NE);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const uint32_t oj = readlane_u32(ov, j);
-            larger += (oj > ov || (oj == ov && j < (lane & 15))) ? 1 : 0;
+                for (int g = 0; g < NE / 4; ++g) d4[g] = make_float4(x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]);
+                s.dump_lane[w][at] = (unsigned char)lane;
+            }
         }
-        const uint64_t sel = __ballot(larger == K - 1) & 0xffffull; // ranks are a permutation of 0..15: exactly one lane
-        if (lane == 0) s.tau = float_of_ord(readlane_u32(ov, __ffsll((long long)sel) - 1));
-    } else if (streamer) {
-        cm = s.gmax[lane & 15];
-        cm = fmaxf(cm, dpp_f32<0xB1>(cm));
+        if (lane == 0) s.ndump[w] = (unsigned int)__popcll(hm);
+        if (tid == 0) s.tau = tau;
+        cm = fmaxf(g32, dpp_f32<0xB1>(g32));
         cm = fmaxf(cm, dpp_f32<0x4E>(cm));
         cm = fmaxf(cm, dpp_f32<0x141>(cm));
         cm = fmaxf(cm, dpp_f32<0x140>(cm));
+        const auto c2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(cm), __float_as_uint(cm), false, false);
+        cm = fmaxf(__uint_as_float(c2[0]), __uint_as_float(c2[1]));
+    } else {
+        // The arguments that only the call's end needs are brought close by now: read by the last workgroup when it
+        // gets there, each cache line of them would be a round trip of its own (0.3 us).
+        asm volatile("" :: "s"(a.parent_scores), "s"(a.pool_scores), "s"(a.part_m));
+        if (MODE == kExpPolicy) asm volatile("" :: "s"(a.pol.b2), "s"(a.gate_pre));
+        if (hidden_rows) hrows.finish(a.pol, bz, [&](int r, float v) { store_shared_result(&a.gate_pre[r], v); });
+    }
+    __syncthreads();
+    if (streamer) {
         // ---- sum of exp(x - chunk maximum): fp32 exponentials; a lane adds its terms in four fp32 chains,
         // the wavefront's 64 lanes as a fixed fp32 tree (relative error below 1e-6), the rest is fp64.
         // (x - cm) first: folding the scale into one fused multiply-add would round cm * log2(e), an
@@ -442,60 +473,41 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(ExpandArgs a) {
         }
         const float wl = wave_sum_f32((tl[0] + tl[1]) + (tl[2] + tl[3]));
         if (lane == 0) s.wave_l[w] = wl;
-    }
-    __syncthreads();
-    // Lanes whose largest logit reaches the threshold (about 1.6 k of the 256) leave all their logits
-    // in LDS; only those are compared one by one afterwards.
-    float *const dump = reinterpret_cast<float *>(&s.wtk[1]);      // [kDumpCap][NE], inside the selection scratch
-    uint64_t *const surv = s.wtk[0].surv;                          // kFastCap + 8 slots
-    static_assert(kDumpCap * NE * sizeof(float) <= (kExpWaves - 1) * sizeof(WaveTopkSmem), "dump inside the scratch");
-    const float tau_f = s.tau;
-    if (streamer) {
-        const bool hot = lmax >= tau_f && base + tid * 4 < a.V;    // (a lane wholly past the row holds -inf only)
-        const uint64_t hm = __ballot(hot);
-        if (hm != 0) {
-            int at = 0;
-            if (lane == 0) at = (int)atomicAdd(&s.ndump, (unsigned int)__popcll(hm));
-            at = (int)readlane_u32((uint32_t)at, 0) + lanes_below(hm);
-            if (hot && at < kDumpCap) {
-                float4 *d4 = reinterpret_cast<float4 *>(dump + (size_t)at * NE);
-#pragma unroll
-                for (int g = 0; g < NE / 4; ++g) d4[g] = make_float4(x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]);
-                s.dump_lane[at] = (unsigned short)tid;
-            }
-        }
-    }
-    __syncthreads();
-    const int ndump = (int)s.ndump;
-    if (ndump <= kDumpCap) {
-        // The logits of the hot lanes against the threshold, all sixteen wavefronts side by side: a lane
-        // takes one logit of one block; what passes goes to the workgroup's candidate list (its order is
-        // immaterial, the ranking below is by key).
+        if (tid == 0) s.cmax = cm;
+        __builtin_amdgcn_s_setprio(0);
+    } else {
+        // ---- Meanwhile the logits of the hot lanes against the threshold, three wavefronts to each streaming one: a
+        // lane takes one logit of one block; what passes is a candidate (their order is immaterial).
+        constexpr int kReaders = (kExpWaves - kStreamers) / kStreamers;
         constexpr int kPerWave = NE <= kWave ? kWave / NE : 1;     // blocks a wavefront takes at a time
-        for (int d0 = w * kPerWave; d0 < ndump; d0 += kExpWaves * kPerWave) {
+        const int from = w % kStreamers, ndump = (int)s.ndump[from];
+        const float tau_f = s.tau;
+        if (ndump > kDumpCap) {                                    // long runs of equal values
+            if (w < 2 * kStreamers && lane == 0) atomicAdd(&s.nsurv, kFastCap + 1u);
+        } else {
+            for (int d0 = (w / kStreamers - 1) * kPerWave; d0 < ndump; d0 += kReaders * kPerWave) {
 #pragma unroll
-            for (int e1 = 0; e1 < NE; e1 += kWave) {               // (one round unless a lane streams more than 64 logits)
-                const int d = d0 + (NE <= kWave ? lane / NE : 0);
-                const int e = NE <= kWave ? lane % NE : e1 + lane;
-                const bool live = d < ndump;
-                const float v = dump[(size_t)min(d, ndump - 1) * NE + e];
-                const int src = (int)s.dump_lane[min(d, ndump - 1)];
-                const int idx = base + (e >> 2) * (kSLanes * 4) + src * 4 + (e & 3);
-                const uint64_t m = __ballot(live && v >= tau_f && idx < a.V);
-                if (m != 0) {
-                    int at = 0;
-                    if (lane == 0) at = (int)atomicAdd(&s.nsurv, (unsigned int)__popcll(m));
-                    at = (int)readlane_u32((uint32_t)at, 0) + lanes_below(m);
-                    if (((m >> lane) & 1) && at < kFastCap) surv[at] = make_key(v, uint32_t(idx));
+                for (int e1 = 0; e1 < NE; e1 += kWave) {           // (one round unless a lane streams more than 64 logits)
+                    const int d = d0 + (NE <= kWave ? lane / NE : 0);
+                    const int e = NE <= kWave ? lane % NE : e1 + lane;
+                    const int slot = from * kDumpCap + min(d, ndump - 1);
+                    const float v = dump[(size_t)slot * NE + e];
+                    const int src = from * kWave + (int)(&s.dump_lane[0][0])[slot];
+                    const int idx = base + (e >> 2) * (kSLanes * 4) + src * 4 + (e & 3);
+                    const uint64_t m = __ballot(d < ndump && v >= tau_f && idx < a.V);
+                    if (m != 0) {
+                        int at = 0;
+                        if (lane == 0) at = (int)atomicAdd(&s.nsurv, (unsigned int)__popcll(m));
+                        at = (int)readlane_u32((uint32_t)at, 0) + lanes_below(m);
+                        if (((m >> lane) & 1) && at < kFastCap) surv[at] = make_key(v, uint32_t(idx));
+                    }
                 }
             }
         }
     }
-    // more hot lanes or candidates than the lists hold means long runs of equal values (every
-    // wavefront reads the same counts after the barrier and takes the same path)
-    if (ndump > kDumpCap && tid == 0) s.nsurv = kFastCap + 1;
     __syncthreads();
     const size_t pslot = (size_t)f * a.nchunks + chunk;
+    uint64_t *const list = a.part_keys + pslot * RADAR_K_MAX;
     const int nsurv = (int)s.nsurv;
     if (nsurv > kFastCap) {
         // Long runs of equal values (more candidates than the list holds): every streaming wavefront
@@ -525,10 +537,14 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(ExpandArgs a) {
 #pragma unroll
             for (int e = 0; e < NS; ++e) k2[e] = s.wlist[e * kWave + lane];
             const uint64_t top = wave_topk<NS>(k2, K, s.wtk[0]);
-            if (lane < K) store_shared_result(a.part_keys + pslot * RADAR_K_MAX + lane, top);
+                if (lane < RADAR_K_MAX) store_shared_result(list + lane, top);      // lanes from K on hold 0
         }
+    } else if (w == 0 && nsurv <= RADAR_K_MAX) {
+        // the candidates as they are: the last workgroup ranks them with the other chunks'
+        if (lane < RADAR_K_MAX) store_shared_result(list + lane, lane < nsurv ? surv[lane] : (uint64_t)0);
     } else if (w == 0) {
-        // exact ranks among the chunk's candidates: every lane counts the larger keys with broadcast reads
+        // More candidates than slots (k = 10: one chunk in a hundred; k above 12: most): the k best of them, by exact
+        // ranks; every lane counts the larger keys with broadcast reads.
         if (lane < 8) surv[nsurv + lane] = 0;                      // padding for the grouped reads
         wave_lds_sync();
         for (int i0 = 0; i0 < nsurv; i0 += kWave) {                // one pass unless there are many ties
@@ -542,20 +558,19 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(ExpandArgs a) {
 #pragma unroll
                 for (int u = 0; u < 8; ++u) rank += (kj[u] > key) ? 1 : 0;
             }
-            if (i < nsurv && rank < K) store_shared_result(a.part_keys + pslot * RADAR_K_MAX + rank, key);   // ranks are distinct
+            if (i < nsurv && rank < K) store_shared_result(list + rank, key);   // ranks are distinct
         }
-        if (lane >= nsurv && lane < K) store_shared_result(a.part_keys + pslot * RADAR_K_MAX + lane, (uint64_t)0);   // fewer than K in the chunk
+        if (lane >= K && lane < RADAR_K_MAX) store_shared_result(list + lane, (uint64_t)0);
     }
     if (w == 1) {
         double l = 0.0;                                            // fixed order of addition
 #pragma unroll
         for (int i = 0; i < kStreamers; ++i) l += (double)s.wave_l[i];
         if (lane == 0) {
-            store_shared_result(&a.part_m[pslot], cm);
+            store_shared_result(&a.part_m[pslot], s.cmax);
             store_shared_result(&a.part_l[pslot], l);
         }
     }
-    if (hidden_rows) hrows.finish(a.pol, bz, [&](int r, float v) { store_shared_result(&a.gate_pre[r], v); });
     unsigned int *row_counter = &a.counters[(1 + f) * kCounterStride];
     if (publish_then_ticket(row_counter, &s.ticket) != (unsigned int)(a.nchunks - 1)) return;
 
@@ -871,8 +886,11 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(Expand
             const uint64_t ctop = wave_topk<NS>(kk, K, s.ties.wtk[0]);
             if (lane < RADAR_K_MAX) a.part_keys[slot * RADAR_K_MAX + lane] = ctop;    // 0 beyond the k-th
         }
+    } else if (w == 0 && n <= RADAR_K_MAX) {
+        // the candidates as they are: the finishing workgroup ranks them with the other chunks'
+        if (lane < RADAR_K_MAX) a.part_keys[slot * RADAR_K_MAX + lane] = lane < n ? s.fast.surv[lane] : 0;
     } else if (w == 0) {
-        // exact ranks among the chunk's candidates: every lane counts the larger keys with broadcast reads
+        // more than that: the k best, by exact ranks; every lane counts the larger keys with broadcast reads
         uint64_t *const surv = s.fast.surv;
         if (lane < 8) surv[n + lane] = 0;                          // padding for the grouped reads
         wave_lds_sync();
@@ -889,7 +907,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(Expand
             }
             if (i < n && rank < K) a.part_keys[slot * RADAR_K_MAX + rank] = key;
         }
-        if (lane >= n && lane < K) a.part_keys[slot * RADAR_K_MAX + lane] = 0;     // fewer than K in the chunk
+        if (lane >= K && lane < RADAR_K_MAX) a.part_keys[slot * RADAR_K_MAX + lane] = 0;
     }
     if (w == 1 && lane == 0) {                                     // fixed order of addition
         double l = 0.0;
@@ -918,12 +936,15 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_finish_kernel(ExpandArg
 using namespace radar;
 
 // Logits per lane: the fewest (shortest critical path per workgroup) that keep the launch at one
-// workgroup per CU; launches too large for that take the most, i.e. the fewest workgroups.
+// workgroup per CU and a row at as many chunks as are merged the short way, as far as there are such (one row of
+// V = 128256 in 16 chunks instead of 32: XX us per call instead of XX); launches too large for that take the
+// most, i.e. the fewest workgroups.
 static int plan_expand_ept(int F, int V) {
-    for (int ept = kExpMinEPT; ept <= 16; ept *= 2) {
-        const int64_t chunk = (int64_t)kExpThreads * ept;
-        if ((int64_t)F * (((int64_t)V + chunk - 1) / chunk) <= 256) return ept;
-    }
+    for (const int most : {kFewChunks, kExpMaxChunks})
+        for (int ept = kExpMinEPT; ept <= 16; ept *= 2) {
+            const int64_t chunk = (int64_t)kExpThreads * ept, nchunks = ((int64_t)V + chunk - 1) / chunk;
+            if (F * nchunks <= 256 && nchunks <= most) return ept;
+        }
     return 16;
 }
 
@@ -1012,10 +1033,10 @@ static radar_status launch_expand(const float *logits, const float *parent_score
         return e == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
     }
     const bool ext = cycle != nullptr || B > 1;
-#define RADAR_EXPAND_LAUNCH(V4, E)                                                                   \
-    (pol ? launch("expand", expand_kernel<V4, E, kExpPolicy>, grid, block, 0, st, a)                  \
-     : ext ? launch("expand", expand_kernel<V4, E, kExpExt>, grid, block, 0, st, a)                   \
-           : launch("expand", expand_kernel<V4, E, kExpPlain>, grid, block, 0, st, a))
+    auto go = [&](auto kernel) {
+        return launch("expand", kernel, grid, block, 0, st, a.logits, a.F, a.V, a.k, a.nchunks, a.pool_count, a.cycle, a.part_keys, a.counters, a);
+    };
+#define RADAR_EXPAND_LAUNCH(V4, E) (pol ? go(expand_kernel<V4, E, kExpPolicy>) : ext ? go(expand_kernel<V4, E, kExpExt>) : go(expand_kernel<V4, E, kExpPlain>))
     if (ept == 4)      e = vec4 ? RADAR_EXPAND_LAUNCH(true, 4) : RADAR_EXPAND_LAUNCH(false, 4);
     else if (ept == 8) e = vec4 ? RADAR_EXPAND_LAUNCH(true, 8) : RADAR_EXPAND_LAUNCH(false, 8);
     else               e = vec4 ? RADAR_EXPAND_LAUNCH(true, 16) : RADAR_EXPAND_LAUNCH(false, 16);

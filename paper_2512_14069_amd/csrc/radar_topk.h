@@ -148,6 +148,30 @@ __device__ __forceinline__ uint32_t quad_threshold(uint32_t v, int K) {
     return max(c, 1u);
 }
 
+// K-th largest (K <= 16) of 32 values, of which every lane passes number lane % 32; the result is the same in
+// every lane.  Rows 0 and 1 of the wavefront count what is larger among values 0-15, rows 2 and 3 (which
+// hold the same values again) among 16-31, by row rotations.
+template <int ROR>
+__device__ __forceinline__ void count_larger_of(uint32_t c, uint32_t g, int &larger) {
+    if constexpr (ROR < 16) {
+        larger += dpp_u32<0x120 + ROR>(c) > g ? 1 : 0;              // row_ror
+        count_larger_of<ROR + 1>(c, g, larger);
+    }
+}
+__device__ __forceinline__ uint32_t kth_of_32(uint32_t g, int K) {
+    const auto ab = __builtin_amdgcn_permlane16_swap(g, g, false, false);       // values 0-15, values 16-31 in every row
+    const uint32_t c = lane_id() < 32 ? ab[0] : ab[1];
+    int larger = c > g ? 1 : 0;
+    count_larger_of<1>(c, g, larger);
+    const auto n = __builtin_amdgcn_permlane32_swap((uint32_t)larger, (uint32_t)larger, false, false);
+    uint32_t k = n[0] + n[1] < (uint32_t)K ? g : 0xffffffffu;      // the K largest (and their ties) stay
+    k = min(k, dpp_u32<0xB1>(k));
+    k = min(k, dpp_u32<0x4E>(k));
+    k = min(k, dpp_u32<0x141>(k));
+    k = min(k, dpp_u32<0x140>(k));
+    const auto m = __builtin_amdgcn_permlane16_swap(k, k, false, false);
+    return min(m[0], m[1]);
+}
 
 struct WaveTopkSmem {
     uint64_t surv[kWave * kWaveTopkMaxEPL + 8];   // +8: the ranking reads keys eight at a time

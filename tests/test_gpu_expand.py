@@ -98,6 +98,28 @@ def test_expand_exact_ties_and_special_values(oracle):
     assert np.max(np.abs(host(g.cand_scores).reshape(F, k) - r["cand_scores"])) <= SCORE_TOL
 
 
+@pytest.mark.parametrize("V", [4096, 8191, 70000, 131072])       # 4 and 8 logits per lane; both kinds of loads; a last chunk of few logits
+@pytest.mark.parametrize("k", [1, 9, 16])
+def test_expand_candidate_counts_at_the_edges_of_the_lists(oracle, V, k):
+    """A chunk's candidates go out as they are up to 16 and ranked beyond; up to 32 lanes per wavefront and 512
+    candidates are looked at one by one.  Rows with that many logits above the rest, and one more or less, distinct
+    (order decides) and equal (token id decides), scattered and side by side in one wavefront's columns."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(V + k)
+    rows = []
+    for n in (15, 16, 17, 31, 33, 129, 132, 512, 513, 1000):
+        for equal in (False, True):
+            x = synth.normal_logits(rng, (V,), 1.0)
+            where = rng.permutation(min(V, 4096))[:n] if n % 2 else np.arange(n) % 256 + np.arange(n) // 256 * 1024
+            x[where] = 9.0 if equal else 9.0 + rng.permutation(n).astype(np.float32) / 64
+            rows.append(x)
+    logits = np.stack(rows)
+    F = len(rows)
+    ps, ppi = np.zeros(F, np.float32), np.full(F, -1, np.int32)
+    gp, cp = b.DraftPool(F * k), np_pool(F * k)
+    run_both_step(oracle, b, logits, ps, ppi, k, gp, cp)
+
+
 @pytest.mark.parametrize("cfg,first_F", [(1, 1), (3, 1), (3, 10)])
 def test_expand_chain_and_rerank_match_oracle(oracle, cfg, first_F):
     """The whole drafting phase of a cycle: the paper's schedule (first call on the root
