@@ -67,10 +67,12 @@ struct AttnArgs {
 // (sixteen consecutive rows, the same chunk) cover all 64 banks: 16 distinct chunk slots at D = 128
 // (256-byte rows), 8 slots times the two rows of a 256-byte bank period at D = 64.
 template <int D>
-__device__ __forceinline__ int ks_off(int key, int chunk) {
+__device__ __forceinline__ int ks_swz(int key) {
     constexpr int CH = D / 8;
-    return key * (D * 2) + ((chunk ^ ((key >> (CH == 16 ? 0 : 1)) & (CH - 1))) << 4);
+    return (key >> (CH == 16 ? 0 : 1)) & (CH - 1);
 }
+template <int D>
+__device__ __forceinline__ int ks_off(int key, int chunk) { return key * (D * 2) + ((chunk ^ ks_swz<D>(key)) << 4); }
 // byte offset of element (d, pos) of a transposed V tile; pos = permuted key slot.
 // 16-byte groups of a row are XOR-swizzled so that both the transposing writes
 // (lanes differ in d/8) and the operand reads (lanes differ in d) spread over banks.
@@ -86,13 +88,12 @@ __device__ __forceinline__ int key_slot(int kappa) {
 
 // byte offset of 16-byte chunk `chunk` of row `row` in a row-major V tile that is read by transposing
 // LDS reads: one pass of such a read (32 lanes) touches 64 consecutive bytes of four consecutive rows,
-// and with 256-byte rows these would meet in the same banks; the row's two low bits move its 64-byte
-// windows apart.  (8 rows + 8 keeps the swizzle: the second read of a pair differs by a constant.)
+// and rows 256 bytes apart would meet in the same banks; the row's two low bits (128-byte rows: the second) move its
+// 64-byte windows apart.  (8 rows + 8 keeps the swizzle: the second read of a pair differs by a constant.)
 template <int D>
-__device__ __forceinline__ int vs_off(int row, int chunk) {
-    static_assert(D == 128, "row-major V tiles are built for 256-byte rows");
-    return row * (D * 2) + ((chunk ^ ((row & 3) << 2)) << 4);
-}
+__device__ __forceinline__ int vs_swz(int row) { return D == 128 ? (row & 3) << 2 : ((row >> 1) & 1) << 2; }
+template <int D>
+__device__ __forceinline__ int vs_off(int row, int chunk) { return row * (D * 2) + ((chunk ^ vs_swz<D>(row)) << 4); }
 
 // Rows of the prefix: at most the cache's, so that the tree's rows can be added in 32 bits for any content of
 // ctx_lens (a length near 2^31 would wrap, and the sequence seem empty to one kernel and not to the next).
@@ -105,17 +106,30 @@ __device__ __forceinline__ void and_mask(u32x4 &v, bool keep) {
     v &= 0u - (uint32_t)keep;
 }
 
-// Ancestor word of tree row i (bit a set <=> a is i or an ancestor of i).  par[] holds the
-// sequence's parents in LDS.  Terminates and stays in bounds for any content: the chain is
-// followed only while it strictly decreases.
-__device__ __forceinline__ uint64_t ancestor_word(const int *par, int i) {
-    uint64_t m = 1ull << i;
-    int guard = i, p = par[i];
-    while (p >= 0 && p < guard) { m |= 1ull << p; guard = p; p = par[p];}
-    return m;
+// Ancestor word of this lane's tree row (bit a set <=> a is the row or an ancestor of it), lane = row; p: the
+// row's parent.  Valid and in bounds for any content: a parent counts only if it is an earlier row.  By
+// doubling: after r rounds a lane holds the 2^r nearest ancestors (itself included) and the next one's
+// number, so a tree of depth 8 takes four rounds of lane gathers (walking up through LDS took eight dependent reads
+// and a barrier; a chain of 60 rows 3 us).  All lanes call.
+__device__ __forceinline__ uint64_t ancestor_words(int p, int nn) {
+    const int lane = lane_id();
+    uint32_t lo = lane < 32 ? 1u << lane : 0u, hi = lane < 32 ? 0u : 1u << (lane - 32);
+    p = (lane < nn && p < lane) ? p : -1;
+    while (__ballot(p >= 0) != 0ull) {
+        const int src = max(p, 0);
+        const uint32_t l2 = (uint32_t)__shfl((int)lo, src), h2 = (uint32_t)__shfl((int)hi, src);
+        const int p2 = __shfl(p, src);
+        if (p >= 0) { lo |= l2; hi |= h2; p = p2; }
+    }
+    return (uint64_t)hi << 32 | lo;
+}
+// the word of row i, whose lane it is; rows past the tree have none
+__device__ __forceinline__ uint64_t ancestor_word_of(uint64_t words, int i, int nn) {
+    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)words, i), hi = (uint32_t)__shfl((int)(uint32_t)(words >> 32), i);
+    return i < nn ? (uint64_t)hi << 32 | lo : 0ull;
 }
 
-// One wavefront, one 64-row tile that sits in LDS, in three phases: scores into
+// One wavefront, one tile of SUBS x 32 rows that sits in LDS, in three phases: scores into
 // `sacc` (register r of sub-tile `sub` is row 32*sub + 8*(r/4) + 4*g2 + r%4), masked online softmax
 // from `sacc` into the bf16 operand `pk` (rescaling the output accumulators when the maximum moved far),
 // and the update of the transposed output accumulators, from a transposed V tile (vt_off) or, with
@@ -130,12 +144,12 @@ __device__ __forceinline__ uint64_t ancestor_word(const int *par, int i) {
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 typedef const __attribute__((address_space(3))) u32x4 *lds_u32x4;
 
-// kaddr(k): where step k's K operand sits in LDS (sub-tile k % 2, 16-byte chunk 2 * (k / 2) + g2 of row j32)
-template <int D, typename KAddr>
-__device__ __forceinline__ void tile_scores(KAddr kaddr, const bf16x8 (&qop)[D / 16], floatx16 (&sacc)[2]) {
-    constexpr int KSTEPS = D / 16, NS = 2 * KSTEPS, kAhead = 4;
+// kaddr(k): where step k's K operand sits in LDS (sub-tile k % SUBS, 16-byte chunk 2 * (k / SUBS) + g2 of row j32)
+template <int D, int SUBS, typename KAddr>
+__device__ __forceinline__ void tile_scores(KAddr kaddr, const bf16x8 (&qop)[D / 16], floatx16 (&sacc)[SUBS]) {
+    constexpr int KSTEPS = D / 16, NS = SUBS * KSTEPS, kAhead = 4;
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub)
+    for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
         for (int r = 0; r < 16; ++r) sacc[sub][r] = 0.f;
     auto kread = [&](int k) { return *kaddr(k); };
@@ -146,7 +160,7 @@ __device__ __forceinline__ void tile_scores(KAddr kaddr, const bf16x8 (&qop)[D /
     for (int k = 0; k < NS; ++k) {
         const u32x4 cur = kf[k % kAhead];
         if (k + kAhead < NS) kf[k % kAhead] = kread(k + kAhead);
-        sacc[k & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, cur), qop[k >> 1], sacc[k & 1], 0, 0, 0);
+        sacc[k % SUBS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, cur), qop[k / SUBS], sacc[k % SUBS], 0, 0, 0);
     }
     __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);          // the order written above, for the scheduler
 #pragma unroll
@@ -156,13 +170,13 @@ __device__ __forceinline__ void tile_scores(KAddr kaddr, const bf16x8 (&qop)[D /
     }
 }
 
-template <int D>
-__device__ __forceinline__ void tile_softmax(floatx16 (&sacc)[2], floatx16 (&oacc)[D / 32][1], float &m_run, float &l_run,
-                                           uint64_t anc, int t0, int L, int kend, bool first, float scale_log2,
-                                           bf16x8 (&pk)[2][2]) {
-    constexpr int DB = D / 32;
+template <int D, int SUBS>
+__device__ __forceinline__ void tile_softmax(floatx16 (&sacc)[SUBS], floatx16 (&oacc)[D / 32][1], float &m_run, float &l_run,
+                                           uint64_t anc, int t0, int L, int kend, bool first, float scale_log2, float slack,
+                                           bf16x8 (&pk)[SUBS][2]) {
+    constexpr int DB = D / 32, ROWS = 32 * SUBS;
     const int g2 = lane_id() >> 5;
-    if ((t0 + kKT > L) || (t0 + kKT > kend)) {                       // wave-uniform; prefix tiles skip it
+    if ((t0 + ROWS > L) || (t0 + ROWS > kend)) {                     // wave-uniform; prefix tiles skip it
         const int pre = L - t0;                                      // prefix keys in this tile (may be <= 0 or >= 64)
         uint64_t allow = pre >= 64 ? ~0ull : (pre > 0 ? ((1ull << pre) - 1) : 0ull);
         if (pre > -64 && pre < 64) allow |= pre >= 0 ? (anc << pre) : (anc >> (-pre));
@@ -171,14 +185,14 @@ __device__ __forceinline__ void tile_softmax(floatx16 (&sacc)[2], floatx16 (&oac
         allow >>= 4 * g2;
         const uint32_t aw[2] = {(uint32_t)allow, (uint32_t)(allow >> 32)};
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
+        for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 sacc[sub][r] = ((aw[sub] >> (8 * (r >> 2) + (r & 3))) & 1u) ? sacc[sub][r] : -INFINITY;
     }
     float mx = -INFINITY;
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub)
+    for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[sub][r]);
     mx = fmaxf(mx, __shfl_xor(mx, 32));
@@ -189,9 +203,9 @@ __device__ __forceinline__ void tile_softmax(floatx16 (&sacc)[2], floatx16 (&oac
     // exactly 1: against 64 bits the output is off by 2.24e-3 (2-norm, N(0,1) scores, 2048 rows) instead of
     // 2.15e-3, by 1.86e-3 instead of 1.68e-3 with scores four times as wide, both mostly the output's own
     // rounding to bf16.  Time with / without the slack: 2048 rows 14.5 / 14.7 us, ragged 16 79.4 / 81.2,
-    // 4 x 16384 rows with 64 heads 148.5 / 155.8.
+    // 4 x 16384 rows with 64 heads 148.5 / 155.8.  (Short contexts in one launch take no slack: a wavefront has few steps.)
     const float mt = mx * scale_log2;                                // scale_log2 > 0; -inf stays -inf
-    const float m_new = mt > m_run + kMaxSlack ? mt : m_run;
+    const float m_new = mt > m_run + slack ? mt : m_run;
     if (!first && __any(m_new != m_run)) {                           // wave-uniform
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         l_run *= alpha;
@@ -205,7 +219,7 @@ __device__ __forceinline__ void tile_softmax(floatx16 (&sacc)[2], floatx16 (&oac
     m_run = m_new;
     float rs = 0.f;
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub)
+    for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[sub][r], scale_log2, -m_new));
@@ -217,9 +231,9 @@ __device__ __forceinline__ void tile_softmax(floatx16 (&sacc)[2], floatx16 (&oac
 
 // vaddr(k, hi): VTR = false: where step k's V^T operand sits (16 bytes; hi unused); VTR = true: the 8-byte
 // piece this lane names for the first (hi = 0) or second (hi = 1) transposing read of step k
-template <int D, bool VTR, typename VAddr>
-__device__ __forceinline__ void tile_pv(VAddr vaddr, const bf16x8 (&pk)[2][2], floatx16 (&oacc)[D / 32][1]) {
-    constexpr int DB = D / 32, NP = 4 * DB, kAhead = 4;
+template <int D, int SUBS, bool VTR, typename VAddr>
+__device__ __forceinline__ void tile_pv(VAddr vaddr, const bf16x8 (&pk)[SUBS][2], floatx16 (&oacc)[D / 32][1]) {
+    constexpr int DB = D / 32, NP = 2 * SUBS * DB, kAhead = 4;
     // V^T operand straight from the row-major tile, by two transposing LDS reads.  In each block of 16
     // lanes, lane 4j+q names an 8-byte piece (row kv0+j, elements 4q..4q+3 of the block's 16) and lane l
     // receives element l%4 of the pieces named by lanes 4j + l/4, j = 0..3: its own d for four
@@ -388,8 +402,6 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(AttnArgs a) {
 
     constexpr int TILE = 2 * kKT * D * 2;   // one K tile ([64][D] bf16, swizzled) + one V^T tile ([D][64], swizzled)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    int *s_par = reinterpret_cast<int *>(smem + 2 * TILE);
-
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int sp = blockIdx.x;
     // The blocks of units that share a range of cache rows are ranges x KV heads apart in workgroup number:
@@ -440,13 +452,13 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(AttnArgs a) {
     const int nsplit = (total + a.kps - 1) / a.kps;
     const int ntiles = (kend - kbeg + kKT - 1) / kKT;
     if (DEEP) gs_load_tile<D>(regs1, kbase, vbase, kv_ss, kbeg + kKT, kend, tid);
-    if (tid < RADAR_T_MAX) s_par[tid] = a.parents[(size_t)b * a.T + min(tid, nn - 1)];
+    const int parent = a.parents[(size_t)b * a.T + min(lane, nn - 1)];
     gs_store_tile<D>(regs0, smem, smem + TILE / 2, kbeg, kend, tid);
     __syncthreads();
     if (DEEP) gs_load_tile<D>(regs0, kbase, vbase, kv_ss, kbeg + 2 * kKT, kend, tid);
     else if (ntiles > 1) gs_load_tile<D>(regs0, kbase, vbase, kv_ss, kbeg + kKT, kend, tid);
     uint64_t anc[1];
-    anc[0] = (kend > L && i < nn) ? ancestor_word(s_par, i) : 0ull;
+    anc[0] = kend > L ? ancestor_word_of(ancestor_words(parent, nn), i, nn) : 0ull;
 
     floatx16 oacc[DB][1];
 #pragma unroll
@@ -464,9 +476,9 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(AttnArgs a) {
             floatx16 sacc[2];
             bf16x8 pk[2][2];
             const unsigned char *Vt = cur + TILE / 2;
-            tile_scores<D>([&](int k) { return (lds_u32x4)(cur + ks_off<D>(32 * (k & 1) + j32, 2 * (k >> 1) + g2)); }, qop, sacc);
-            tile_softmax<D>(sacc, oacc, m_run[0], l_run[0], anc[0], kbeg + t * kKT, L, kend, t == 0, a.scale_log2, pk);
-            tile_pv<D, false>([&](int k, int) { return (const lds_byte *)(Vt + vt_off(32 * (k % DB) + j32, 16 * (k / DB) + 8 * g2)); },
+            tile_scores<D, 2>([&](int k) { return (lds_u32x4)(cur + ks_off<D>(32 * (k & 1) + j32, 2 * (k >> 1) + g2)); }, qop, sacc);
+            tile_softmax<D, 2>(sacc, oacc, m_run[0], l_run[0], anc[0], kbeg + t * kKT, L, kend, t == 0, a.scale_log2, kMaxSlack, pk);
+            tile_pv<D, 2, false>([&](int k, int) { return (const lds_byte *)(Vt + vt_off(32 * (k % DB) + j32, 16 * (k / DB) + 8 * g2)); },
                               pk, oacc);
         }
         if (t + 1 < ntiles) {
@@ -673,8 +685,6 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
     constexpr int DB = D / 32;
     constexpr int TILE = 2 * kKT * D * 2;   // one K tile ([64][D] bf16, swizzled) + one V tile (row-major, swizzled)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    int *s_par = reinterpret_cast<int *>(smem + kLdBufs * TILE);
-
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int j32 = lane & 31, g2 = lane >> 5;
     const int kv_ss = (int)a.kv_ss;          // 32-bit offsets inside one head's cache (checked on the host)
@@ -794,7 +804,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
         const int i = 32 * qb + j32;                      // this lane's tree row
         const int L = pc.L, nn = pc.nn, kend = pc.kend;
 
-        if (tid < RADAR_T_MAX) s_par[tid] = a.parents[(size_t)pc.b * a.T + min(tid, max(nn, 1) - 1)];
+        const int parent = a.parents[(size_t)pc.b * a.T + min(lane, max(nn, 1) - 1)];
         bf16x8 qop[D / 16];                               // row i, d = 16*st + 8*g2 .. +8, for the whole piece
         {
             const __bf16 *qrow = a.q + (size_t)pc.b * a.q_sb + (size_t)h * a.q_sh + (uint32_t)(min(i, a.T - 1) * (int)a.q_st);
@@ -822,9 +832,8 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
                                                           (uint32_t)(row * (int)a.q_st + (D / 2) * g2));
             touched ^= (uint32_t)a.parents[(size_t)nx.b * a.T + min(lane, a.T - 1)];
         }
-        __syncthreads();                                  // the parents are in LDS
         uint64_t anc[1];
-        anc[0] = (kend > L && i < nn) ? ancestor_word(s_par, i) : 0ull;
+        anc[0] = kend > L ? ancestor_word_of(ancestor_words(parent, nn), i, nn) : 0ull;
 
         floatx16 oacc[DB][1];
 #pragma unroll
@@ -848,10 +857,10 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
         auto run_tile = [&](auto second, int t0) {
             constexpr int TOFF = decltype(second)::value ? TILE : 0;
             // sub-tile k % 2: 32 rows on, the same swizzle (32 is a multiple of 16)
-            tile_scores<D>([&](int k) { return (lds_u32x4)(ka[k >> 1] + TOFF + (k & 1) * (32 * D * 2)); }, qop, sacc);
-            tile_softmax<D>(sacc, oacc, m_run[0], l_run[0], anc[0], t0, L, kend, false, a.scale_log2, pk);   // (zeros rescaled once: no second copy of the loop for the first pair)
+            tile_scores<D, 2>([&](int k) { return (lds_u32x4)(ka[k >> 1] + TOFF + (k & 1) * (32 * D * 2)); }, qop, sacc);
+            tile_softmax<D, 2>(sacc, oacc, m_run[0], l_run[0], anc[0], t0, L, kend, false, a.scale_log2, kMaxSlack, pk);   // (zeros rescaled once: no second copy of the loop for the first pair)
             // step k: output block k % DB, rows 16 * (k / DB) on (a multiple of 4: the same swizzle), hi: 8 rows on
-            tile_pv<D, true>([&](int k, int hi) { return va[k % DB] + TOFF + (k / DB) * (16 * D * 2) + hi * (8 * D * 2); }, pk, oacc);
+            tile_pv<D, 2, true>([&](int k, int hi) { return va[k % DB] + TOFF + (k / DB) * (16 * D * 2) + hi * (8 * D * 2); }, pk, oacc);
         };
         const int fav = w < kGsWaves / 2 ? 1 : 0;
         for (int t = pc.t0; t < pc.t1; t += 2) {
@@ -880,6 +889,137 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
         if (!more) return;
         pc = nx;
     }
+}
+
+// ===================================================================== one launch, short contexts
+// A call over a few hundred rows is two launches of about four dependent round trips each; what it computes would take
+// a microsecond.  Here a workgroup takes one unit (query head, block of 32 tree rows) over all rows, its eight
+// wavefronts 32 rows each in turn, and merges their results in LDS: one launch, no partials in memory.  A
+// wavefront stages its own rows straight into its own part of LDS and waits for nobody until the merge.  The
+// price is that every unit's CU reads all of its KV head's rows: what bounds it is that CU's port, about 1 us per
+// 64 KB, after 5 us of launch and round trips (32 heads, D = 128: 76 rows 5.8 us, 256 rows 8.3, 572 rows 9.9; with ranges
+// and a merge 10.9, 9.9 and 11.7.  One layer of 4 heads with D = 64 over 272 rows 6.0 instead of 7.8).
+constexpr int kOneRows = 32;                             // cache rows of a wavefront's step
+
+template <int D>
+__global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 *k_, const __bf16 *v_, const int32_t *ctx_lens, const int32_t *n_nodes,
+                                                                  int64_t kv_sb, int64_t kv_sh, AttnArgs a) {
+    constexpr int DB = D / 32, ROW = D * 2, SUB = kOneRows * ROW;           // bytes of a row, of a step's K or V rows
+    constexpr int LOADS = SUB / 1024, RPL = 1024 / ROW, CPR = ROW / 16;     // 1 KB loads; rows of one; 16-byte chunks of a row
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    float *const s_m = reinterpret_cast<float *>(smem + kGsWaves * 2 * SUB), *const s_l = s_m + kGsWaves * 32;
+    a.k = k_; a.v = v_; a.ctx_lens = ctx_lens; a.n_nodes = n_nodes; a.kv_sb = kv_sb; a.kv_sh = kv_sh;
+
+    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    const int j32 = lane & 31, g2 = lane >> 5;
+    // Units of a KV head are a multiple of Hkv apart in workgroup number: with eight KV heads on one XCD, whose L2 then
+    // holds that head's rows for all of them (32 heads x 3 sequences over 572 rows 13.9 -> 10.7 us).
+    const int hk = blockIdx.x, unit = blockIdx.y, b = blockIdx.z, qb = unit & (a.nqb - 1), h = hk * a.G + (unit >> (a.nqb - 1));
+    const int L = prefix_rows(a, b);
+    int nn = a.n_nodes ? a.n_nodes[b] : a.T;
+    nn = max(1, min(nn, a.T));
+    const int total = min(L + nn, a.S);                  // never read past the cache the caller described
+    if (L < 0 || total < 1) return;
+    const int nsub = (total + kOneRows - 1) / kOneRows, nact = min(nsub, kGsWaves);
+    const __bf16 *const kbase = a.k + (size_t)b * a.kv_sb + (size_t)hk * a.kv_sh;
+    const __bf16 *const vbase = a.v + (size_t)b * a.kv_sb + (size_t)hk * a.kv_sh;
+    const int kv_ss = (int)a.kv_ss;                      // 32-bit offsets inside one head's cache (checked on the host)
+
+    // This wavefront's rows of a step: K [32][D], then V [32][D], both row-major with their own swizzle (ks_off, vs_off); a
+    // lane's 16 bytes land at the load's LDS base + 16 * lane, so it fetches the chunk that belongs there.  Rows past
+    // the end re-read the last one: their scores are masked, and 0 * finite = 0.
+    unsigned char *const mine = smem + w * 2 * SUB;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)mine);
+    auto issue = [&](const __bf16 *base, auto is_v, int sub) {
+        constexpr bool V = decltype(is_v)::value;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int row = RPL * i + lane / CPR, slot = lane % CPR;
+            const int chunk = V ? slot ^ vs_swz<D>(row) : slot ^ ks_swz<D>(row);
+            const __bf16 *src = base + (uint32_t)(min(sub * kOneRows + row, total - 1) * kv_ss) + chunk * 8;
+            const uint32_t dst = lds0 + (V ? SUB : 0) + i * 1024;
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
+        }
+    };
+    constexpr std::false_type kK{};
+    constexpr std::true_type kV{};
+    const int i = 32 * qb + j32;                         // this lane's tree row
+    bf16x8 qop[D / 16];                                  // its query operands: d = 16*st + 8*g2 .. +8
+    floatx16 oacc[DB][1];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[db][0][r] = 0.f;
+    float m_run = kNegBig, l_run = 0.f;
+    if (w < nact) {
+        issue(kbase, kK, w);
+        issue(vbase, kV, w);
+        const __bf16 *qrow = a.q + (size_t)b * a.q_sb + (size_t)h * a.q_sh + (uint32_t)(min(i, a.T - 1) * (int)a.q_st);
+#pragma unroll
+        for (int st = 0; st < D / 16; ++st) {
+            u32x4 raw = *reinterpret_cast<const u32x4 *>(qrow + 16 * st + 8 * g2);
+            and_mask(raw, i < a.T);
+            qop[st] = __builtin_bit_cast(bf16x8, raw);
+        }
+        uint64_t anc = 0;
+        // (only wavefronts that meet rows of the tree need the ancestors: the last steps')
+        const int last = w + (nsub - 1 - w) / kGsWaves * kGsWaves;
+        if (last * kOneRows + kOneRows > L)
+            anc = ancestor_word_of(ancestor_words(a.parents[(size_t)b * a.T + min(lane, nn - 1)], nn), i, nn);
+        const lds_byte *const kl = (const lds_byte *)mine, *const vl = kl + SUB;
+        for (int sub = w; sub < nsub; sub += kGsWaves) {
+            const bool more = sub + kGsWaves < nsub;
+            floatx16 sacc[1];
+            bf16x8 pk[1][2];
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            tile_scores<D, 1>([&](int k) { return (lds_u32x4)(kl + ks_off<D>(j32, 2 * k + g2)); }, qop, sacc);
+            if (more) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // the K rows have been read: the next may land there
+                issue(kbase, kK, sub + kGsWaves);
+            }
+            tile_softmax<D, 1>(sacc, oacc, m_run, l_run, anc, sub * kOneRows, L, total, sub == w, a.scale_log2, 0.f, pk);
+            tile_pv<D, 1, true>([&](int k, int hi) {
+                const int d0 = 32 * (k % DB) + (j32 & 16) + 4 * (lane & 3), kv0 = 4 * g2 + ((lane >> 2) & 3);
+                return vl + vs_off<D>(kv0, d0 >> 3) + (d0 & 7) * 2 + (k / DB) * (16 * ROW) + hi * (8 * ROW);   // (8 rows on: the same swizzle)
+            }, pk, oacc);
+            if (more) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                issue(vbase, kV, sub + kGsWaves);
+            }
+        }
+        const float l_tot = l_run + __shfl_xor(l_run, 32);
+        if (g2 == 0) { s_m[w * 32 + j32] = m_run; s_l[w * 32 + j32] = l_tot; }
+    }
+    __syncthreads();                                     // every wavefront is done with its rows; maxima and sums are in LDS
+    float *const s_o = reinterpret_cast<float *>(smem);  // [wavefront][d][32], over the rows
+    if (w < nact) {
+        float M = kNegBig;
+        for (int v = 0; v < nact; ++v) M = fmaxf(M, s_m[v * 32 + j32]);
+        const float scl = __builtin_amdgcn_exp2f(m_run - M);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s_o[(w * D + 32 * db + 8 * (r >> 2) + 4 * g2 + (r & 3)) * 32 + j32] = oacc[db][0][r] * scl;
+    }
+    __syncthreads();
+    const int row = tid & 31, d8 = tid >> 5, ti = 32 * qb + row;            // eight outputs of one row
+    if (d8 * 8 >= D || ti >= a.T) return;
+    const bool live = ti < nn;
+    float M = kNegBig, l = 0.f, acc[8];
+    for (int v = 0; v < nact; ++v) M = fmaxf(M, s_m[v * 32 + row]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+    for (int v = 0; v < nact; ++v) {
+        l += s_l[v * 32 + row] * __builtin_amdgcn_exp2f(s_m[v * 32 + row] - M);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] += s_o[(v * D + d8 * 8 + e) * 32 + row];
+    }
+    const float inv = (live && l > 0.f) ? 1.0f / l : 0.f;
+    bf16x8 o8;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o8[e] = (__bf16)(live ? acc[e] * inv : 0.f);             // rows past the tree are zeroed
+    *reinterpret_cast<bf16x8 *>(a.out + (size_t)b * a.o_sb + (size_t)ti * a.o_st + (size_t)h * a.o_sh + d8 * 8) = o8;
+    if (a.lse && d8 == 0) a.lse[((size_t)b * a.T + ti) * a.Hq + h] = live ? (M + __builtin_amdgcn_logf(l)) * kLn2 : 0.f;
 }
 
 // Merges the group-share kernels' partials.  A workgroup takes one (sequence, query head, 32-wide slice
@@ -998,8 +1138,32 @@ __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(AttnA
 // ------------------------------------------------------------------ host-side planning
 struct AttnPlan {
     int kps, max_splits, n_ublk, nqb, shares;
+    bool one;                                              // one launch, no ranges
     size_t off_part_o, off_part_ml, off_tab, bytes;
 };
+
+// Up to how many cache rows a call is one launch of whole units (tree_attn_one_kernel): as long as the units are no more
+// than the chip holds at once (one per CU with D = 128, two with D = 64), to where a unit's CU takes as long to read all
+// rows as ranges and their merge take.  That is later the more units there are, because ranges then wait for each other,
+// and earlier where a KV head has few (two blocks of rows, at most two heads): half of a range's wavefronts are idle then.
+// Both sides measured at 32 ... 1860 rows for 41 combinations of batch, heads and tree; one launch / ranges in us, at
+// D = 128, 60 tree rows: 32 heads 8.6 / 10.3 over 380 rows, 9.9 / 11.7 over 572, 13.0 / 14.1 over 1060, 17.7 / 15.1 over 1860;
+// four such sequences 10.8 / 15.3 over 500, 14.3 / 16.9 over 1060, 17.7 / 20.4 over 1560; 16 heads on 8 KV heads 8.5 / 9.5
+// over 380, 9.8 / 9.6 over 500; 16 tree rows, 32 heads 9.4 / 10.2 over 616, 10.8 / 10.1 over 716.  D = 64, 8 heads on 4: 7.2 / 8.6 over
+// 500, 8.9 / 10.1 over 1060, 32 sequences of it 12.0 / 13.2 over 572; with 16 tree rows 64 sequences 7.7 / 7.9 over 212, 11.5 / 9.9 over 336.
+static int one_launch_rows(const radar_attn_desc *d, int nqb) {
+    const long units = (long)d->B * d->Hq * nqb;
+    const int G = d->Hq / d->Hkv;
+    if (d->D == 64) {
+        if (units > 512) return 0;
+        if (nqb == 1 && units > 256) return units <= 384 ? 640 : 224;
+        return units >= 128 ? 1600 : 1024;
+    }
+    if (units > 256) return 0;
+    if (nqb == 2 && G <= 2) return units > 64 ? 800 : 384;
+    if (nqb == 2 && units >= 128) return units >= 192 ? 1600 : 1100;
+    return units >= 192 ? 1100 : units >= 96 ? 800 : 640;
+}
 
 static AttnPlan plan_attention(const radar_attn_desc *d) {
     AttnPlan p;
@@ -1007,6 +1171,8 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
     p.nqb = d->T_max <= 32 ? 1 : 2;
     p.n_ublk = (G * p.nqb + kGsWaves - 1) / kGsWaves;
     long kps = d->keys_per_split;
+    p.one = kps <= 0 && d->S_max <= one_launch_rows(d, p.nqb);
+    if (p.one) kps = ((long)d->S_max + kKT - 1) / kKT * kKT;
     if (kps <= 0) {
         // Number of key ranges: the one that minimises a small cost model, in units of one tile of
         // one workgroup (measured ~2.7 us): rounds of 256 resident workgroups x (tiles per range +
@@ -1034,7 +1200,7 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
     // workgroups are many rounds, and the hardware's dispatch evens them out.)
     p.shares = 0;
     const long pairs = ((long)d->S_max + 2 * kKT - 1) / (2 * kKT), heads = (long)d->B * d->Hkv;
-    if (d->keys_per_split == 0 && kps >= kLongTiles * kKT && d->D == 128 && d->B <= kFlatMaxB && d->Hkv <= kWave && p.n_ublk <= 16 &&
+    if (!p.one && d->keys_per_split == 0 && kps >= kLongTiles * kKT && d->D == 128 && d->B <= kFlatMaxB && d->Hkv <= kWave && p.n_ublk <= 16 &&
         heads * (2 * pairs * kTileCost + kUnitCost) < (1l << 30))
         p.shares = 256 / p.n_ublk;
     size_t off = 0;
@@ -1071,11 +1237,11 @@ extern "C" size_t radar_tree_attention_workspace_bytes(const radar_attn_desc *d)
 }
 
 template <int D>
-constexpr int gs_smem_bytes() { return 2 * (2 * kKT * D * 2) + RADAR_T_MAX * 4; }
+constexpr int gs_smem_bytes() { return 2 * (2 * kKT * D * 2); }
 
 template <int D, bool FLAT>
 static hipError_t launch_ld(const AttnArgs &a, dim3 grid, hipStream_t s) {
-    constexpr int bytes = kLdBufs * (2 * kKT * D * 2) + RADAR_T_MAX * 4;
+    constexpr int bytes = kLdBufs * (2 * kKT * D * 2);
     static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_ld_kernel<D, FLAT>),
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (configured != hipSuccess) return configured;
@@ -1090,6 +1256,15 @@ static hipError_t launch_gs(const AttnArgs &a, dim3 grid, hipStream_t s) {
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, gs_smem_bytes<D>());
     if (configured != hipSuccess) return configured;
     return launch("tree_attn_group_share", tree_attn_gs_kernel<D, DEEP>, grid, dim3(kGsThreads), gs_smem_bytes<D>(), s, a);
+}
+
+template <int D>
+static hipError_t launch_one(const AttnArgs &a, dim3 grid, hipStream_t s) {
+    constexpr int bytes = kGsWaves * (2 * kOneRows * D * 2 + 2 * 32 * (int)sizeof(float));
+    static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_one_kernel<D>),
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (configured != hipSuccess) return configured;
+    return launch("tree_attn_one", tree_attn_one_kernel<D>, grid, dim3(kGsThreads), bytes, s, a.k, a.v, a.ctx_lens, a.n_nodes, a.kv_sb, a.kv_sh, a);
 }
 
 extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache, const void *v_cache,
@@ -1140,6 +1315,10 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
     hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 block(kAttnThreads);
     if ((long)a.B * a.n_ublk > 65535) return RADAR_UNSUPPORTED_SHAPE;
+    if (p.one) {
+        const dim3 ogrid((unsigned)a.Hkv, (unsigned)(a.G * a.nqb), (unsigned)a.B);
+        return (d->D == 128 ? launch_one<128>(a, ogrid, s) : launch_one<64>(a, ogrid, s)) == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
+    }
     const dim3 grid = p.shares > 0 ? dim3((unsigned)p.shares, 1, (unsigned)p.n_ublk)
                                    : dim3((unsigned)a.max_splits, (unsigned)a.Hkv, (unsigned)(a.B * a.n_ublk));
     {

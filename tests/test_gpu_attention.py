@@ -180,6 +180,30 @@ def test_context_lengths_past_the_cache_are_cut_to_it(D, S, kps):
         assert torch.all(err <= ABS_TIGHT + REL_TIGHT * want[i, :n].abs())
 
 
+@pytest.mark.parametrize("D,ctx,nn,T", [
+    (128, 0, 1, 1), (128, 0, 2, 64), (64, 0, 1, 33),                       # one row, two; a block of rows past the tree
+    (128, 30, 1, 5), (128, 31, 1, 32), (64, 32, 1, 33),                     # 31, 32 and 33 rows: one wavefront or two
+    (128, 223, 32, 32), (128, 200, 57, 60), (64, 255, 2, 2),                # 255, 257 and 257 rows: the second step's first
+    (128, 320, 64, 64), (128, 608, 32, 32), (64, 960, 64, 64), (64, 991, 1, 33),   # the most rows that go in one launch
+    (128, 321, 64, 64), (128, 609, 32, 32), (64, 961, 64, 64),              # one row more: ranges
+])
+def test_one_launch_over_whole_units(oracle, D, ctx, nn, T):
+    """Short contexts take one launch in which eight wavefronts share a unit's rows; every count of rows around 32 (one
+    wavefront's step) and 256 (the workgroup's), and the last ones that go this way.  The second sequence is shorter."""
+    from paper_2512_14069_amd import binding as b
+    nodes = [nn, (nn + 1) // 2]
+    a = shape(2, 4, 2, D, T, [ctx, ctx // 3], nodes, [max(1, min(6, n - 1)) for n in nodes], k=64)
+    x = synth.attention_inputs(a, seed=synth.seed_for(1, ctx * 64 + nn), shuffle=True)
+    ref, ref_lse = oracle.tree_attention(x["q"], x["k_cache"], x["v_cache"], x["parents"], x["ctx_lens"],
+                                         x["n_nodes"], want_lse=True)
+    got, lse = run_gpu(b, x, want_lse=True)
+    for bb in range(2):
+        n = nodes[bb]
+        check_close(got[bb, :n], ref[bb, :n], f"b={bb}")
+        assert np.max(np.abs(lse[bb, :n] - ref_lse[bb, :n])) < LSE_TOL
+        assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)     # unused rows are zeroed
+
+
 def test_chain_and_star_trees_depth_63(oracle):
     from paper_2512_14069_amd import binding as b
     a = shape(2, 4, 1, 128, 64, [100, 31], [64, 64], [8, 8], k=10)
