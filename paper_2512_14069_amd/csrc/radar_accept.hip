@@ -23,8 +23,9 @@
 // (trees are numbered from the root), so that the roots' decisions come first.
 // What bounds a call is then the chain of decisions (about 2.5 us per level) and
 // the starting of workgroups, not the logits' bytes: 61 rows of V = 128256, sampled,
-// 8 / 16 sequences 24.8 / 30.9 us, against 70 / 129 us when every row is read; one
-// sequence 13.5 us against 15.7 (its walk no longer waits for the last row).
+// 8 / 16 sequences 16 ... 31 / 23 ... 43 us for paths of 0 ... 8 nodes, against 70 / 129 us
+// when every row is read; one sequence 11 ... 14 us.  In a large launch the
+// workgroups behind the roots' rows hold back until the roots are decided (below).
 #include "radar_device.h"
 #include "radar_host.h"
 
@@ -40,6 +41,7 @@ constexpr int kAccCounterStride = 16;   // counters 64 B apart (same-line fetch-
 constexpr int64_t kAccManyBlocks = 49152;
 constexpr int64_t kAccWalkLast = 3072;  // greedy launches up to this many workgroups leave the walk to the last row
 constexpr int kAccUnchecked = 1024;     // workgroups the chip starts first: nothing is decided yet when they do
+constexpr int kAccPolls = 3;            // how often a waiting workgroup looks (1 us apart)
 constexpr float kAccLog2e = 1.4426950408889634f;
 constexpr unsigned int kAccDone = 1u << 30, kAccReached = 1u << 29;   // marks beside a row's count of arrivals
 constexpr int kAccEnded = RADAR_T_MAX;  // "node arrived at" once the walk has ended
@@ -57,6 +59,8 @@ struct AcceptArgs {
     double *dist;               // mode kAccDistribution: [B][D_max+1]
     int B, T, V, D_max, nwg, nsub;   // nwg workgroups and nsub 1024-logit blocks per row
     int check_from;             // workgroups from this number on ask whether their row can still be on the path
+    int wait;                   // > 0 (units of 10 ns): those of them that start with the launch wait so long for the roots' decisions
+    int wait_until;             // those before this number
     int exact_scale;            // 1/temperature is exactly representable in fp32
     float inv_temp_f;
     double inv_temp;
@@ -73,26 +77,29 @@ struct AcceptArgs {
 
 struct AcceptSmem {
     unsigned int ticket;
-    double row_lse[RADAR_T_MAX];                  // rows whose results this wavefront holds
-    int row_arg[RADAR_T_MAX];
+    int row_arg[RADAR_T_MAX];                     // rows whose results this wavefront holds
     float row_M[RADAR_T_MAX];
     double row_L[RADAR_T_MAX];
     int rej_tok[RADAR_T_MAX];
+    float rej_x[RADAR_T_MAX];                     // their logits
     int internal[RADAR_T_MAX];                    // distribution: nodes with children,
     unsigned long long kid_mask[RADAR_T_MAX], depth_mask[RADAR_T_MAX];   // the children of each node, the nodes at each depth
     double rej_e[RADAR_T_MAX];                    // what each rejected token carries, and the block it lies in
     int rej_sub[RADAR_T_MAX];
     unsigned int rej_bits[kWave];                 // pass (b): which of a lane's 16 tokens are rejected ones
-    unsigned char seen[4096];                     // sibling tokens, hashed
+    union alignas(16) {
+        unsigned char seen[4096];                 // sibling tokens, hashed
+        float mass[kAccSub];                      // pass (b): the block's exponentials
+    };
 };
 
-// exp(x / temperature - ref) for one logit, as a double.  The exponent difference is rounded to
+// exp(x / temperature - ref) for one logit.  The exponent difference is rounded to
 // fp32 once (an fp32 FMA does that when the scale is exact in fp32, else it is formed in fp64);
 // the exponential itself is the fp32 one.  The sums that use it are kept in fp64.
 template <bool EXACT>
-__device__ __forceinline__ double scaled_exp(float x, const AcceptArgs &a, float ref) {
-    if (EXACT) return (double)__builtin_amdgcn_exp2f(__builtin_fmaf(x, a.inv_temp_f, -ref) * kAccLog2e);
-    return (double)expf((float)((double)x * a.inv_temp - (double)ref));
+__device__ __forceinline__ float scaled_exp(float x, const AcceptArgs &a, float ref) {
+    if (EXACT) return __builtin_amdgcn_exp2f(__builtin_fmaf(x, a.inv_temp_f, -ref) * kAccLog2e);
+    return expf((float)((double)x * a.inv_temp - (double)ref));
 }
 
 // 16 logits per lane of one 1024-logit block: lane l takes [16 * l, 16 * l + 16) when CONTIG (pass
@@ -165,9 +172,19 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
     // row, may see the walk at different nodes: one that finds the row off the path is right, the walk
     // only moves down, and then nobody will ask for the row's results.)
     bool needed = true;
-    if (distribution || (!LAST && (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x >= (unsigned int)a.check_from)) {
+    const unsigned int number = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    if (distribution || (!LAST && number >= (unsigned int)a.check_from)) {
         unsigned int at = 0;
-        if (!distribution) at = load_shared_result(arrived_at);
+        if (!distribution && (int)number < a.wait_until) {
+            // By the clock, not by anything another workgroup does: whatever happens elsewhere, this ends.
+            const uint64_t t0 = wall_clock64();
+            for (int k = 0; k < kAccPolls && at == 0; ++k) {
+                for (int i = 0; i < 400 && wall_clock64() - t0 < (uint64_t)(a.wait + 100 * k); ++i) __builtin_amdgcn_s_sleep(8);
+                at = load_shared_result(arrived_at);
+            }
+        } else if (!distribution) {
+            at = load_shared_result(arrived_at);
+        }
         int par = lane < nn ? a.parents[(size_t)b * a.T + lane] : -1;
         par = par < lane ? par : -1;
         if (distribution) {
@@ -210,10 +227,10 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
                 if (wm > -INFINITY) {
                     if (a.exact_scale) {
 #pragma unroll
-                        for (int e = 0; e < kAccEPT; ++e) tl += scaled_exp<true>(x[i][e], a, wm);
+                        for (int e = 0; e < kAccEPT; ++e) tl += (double)scaled_exp<true>(x[i][e], a, wm);
                     } else {
 #pragma unroll
-                        for (int e = 0; e < kAccEPT; ++e) tl += scaled_exp<false>(x[i][e], a, wm);
+                        for (int e = 0; e < kAccEPT; ++e) tl += (double)scaled_exp<false>(x[i][e], a, wm);
                     }
                 }
                 const double wl = wave_sum_f64(tl);
@@ -225,6 +242,20 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
             if (lane == 0 && live) store_shared_result(&a.part_key[pslot], best);
         }
     }
+    // What the walk needs to know of the tree is fetched beside the stream's last results: behind the ticket it was a round
+    // trip before the gather of the tokens' logits could be asked for.
+    const int c = lane;
+    int p = -1, t = -1;
+    float uc = 0.f, ubonus = 0.f;
+    if (w == 0) {
+        if (c < nn) { p = a.parents[(size_t)b * a.T + c]; t = a.tokens[(size_t)b * a.T + c]; }
+        if (MODE == RADAR_ACCEPT_SAMPLE) {
+            const float *u = a.uniforms + (size_t)b * (a.T + 1);
+            uc = u[min(c, a.T)];
+            ubonus = u[a.T];
+        }
+    }
+    const bool tree_ok = (c > 0 && c < nn && p >= 0 && p < c);
     if ((publish_then_ticket(&words[r * kAccCounterStride], &s.ticket) & (kAccReached - 1)) != (unsigned int)(a.nwg - 1)) return;
     if (w != 0) return;                                      // one wavefront does the rest
 
@@ -239,26 +270,13 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
     if (!needed) { finish_row(wave_fetch_add(seq_counter, 1u)); return; }
 
     // ---------------- phase 2: last workgroup of row r -- merge the row's partials.
-    // What only the walk needs (lane c is tree node c) is fetched here, so that it has arrived by
-    // the time the walk starts.
-    const int c = lane;
-    int p = -1, t = -1;
-    float xg = 0.f, uc = 0.f, ubonus = 0.f;
-    bool tree_ok = false;
+    // The logits that only the walk needs (lane c is tree node c) are asked for together with the partials.
+    float xg = 0.f;
     uint64_t kb = 0;
     float M;
     double L, mass_[2] = {0.0, 0.0};                         // this row's first 128 block masses
     {
-        if (c < nn) { p = a.parents[(size_t)b * a.T + c]; t = a.tokens[(size_t)b * a.T + c]; }
-        tree_ok = (c > 0 && c < nn && p >= 0 && p < c);
-        if (sampling) {
-            if (a.uniforms) {                                // none in distribution mode
-                const float *u = a.uniforms + (size_t)b * (a.T + 1);
-                uc = u[min(c, a.T)];
-                ubonus = u[a.T];
-            }
-            if (tree_ok && t >= 0 && t < a.V) xg = a.logits[((size_t)b * a.T + p) * a.V + t];
-        }
+        if (sampling && tree_ok && t >= 0 && t < a.V) xg = a.logits[((size_t)b * a.T + p) * a.V + t];
         const size_t p0 = ((size_t)b * a.T + r) * a.nsub;
         // the first 128 partials (all of them up to V = 131072) are taken in one round trip
         float m_[2];
@@ -325,10 +343,10 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         if (wave_fetch_add(seq_counter, 1u) != (unsigned int)(__popcll(__ballot(inner)) - 1)) return;
         if (lane == 0) store_shared_result(seq_counter, 0u);
         const size_t rs = (size_t)b * a.T + min(c, nn - 1);
-        if (inner) s.row_lse[c] = (double)load_shared_result(&a.row_M[rs]) + log(load_shared_result(&a.row_L[rs]));
+        if (inner) { s.row_M[c] = load_shared_result(&a.row_M[rs]); s.row_L[c] = load_shared_result(&a.row_L[rs]); }
         wave_lds_sync();
         double pc = 0.0;                                     // probability of each node's token under its parent's row
-        if (tree_ok && t >= 0 && t < a.V) pc = exp((double)xg * a.inv_temp - s.row_lse[p]);
+        if (tree_ok && t >= 0 && t < a.V) pc = exp((double)xg * a.inv_temp - (double)s.row_M[p]) / s.row_L[p];
         // Sec. 4.3, Eq. 11-13, one lane per node.
         // Children of each node as a bit mask; the sums below run over the bits, in node order.
         s.kid_mask[lane] = 0;
@@ -401,7 +419,6 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
                 const double Lr = own ? L : load_shared_result(&a.row_L[rs]);
                 s.row_M[lane] = Mr;
                 s.row_L[lane] = Lr;
-                s.row_lse[lane] = (double)Mr + log(Lr);
             }
             s.row_arg[lane] = (int)key_index(key);
         }
@@ -410,7 +427,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         wave_lds_sync();
         if (tree_ok && ((fresh >> p) & 1)) {
             if (!sampling) match = s.row_arg[p] == t;
-            else if (t >= 0 && t < a.V) pc = exp((double)xg * a.inv_temp - s.row_lse[p]);
+            else if (t >= 0 && t < a.V) pc = exp((double)xg * a.inv_temp - (double)s.row_M[p]) / s.row_L[p];   // (no logarithm on the way)
         }
     };
     const int up = tree_ok ? p : -1;
@@ -426,7 +443,8 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
             if (lane == d) mypath = x;
     }
     double R = 0.0;
-    int nrej = 0, rejtok = -1;                               // lane j keeps the j-th rejected token
+    int nrej = 0, rejtok = -1;                               // lane j keeps the j-th rejected token and its logit
+    float rejx = 0.f;
     for (;;) {
         uint64_t kids = (len < a.D_max) ? __ballot(tree_ok && p == cur) : 0ull;
         R = 0.0; nrej = 0;
@@ -465,9 +483,13 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
             nrej = __popcll(rejected);
             R = nrej ? readlane_f64(before + mine, 63 - __clzll((long long)rejected)) : 0.0;
             // lane j takes the token of the j-th rejected child
-            if ((rejected >> lane) & 1) s.rej_tok[lanes_below(rejected)] = t;
+            if ((rejected >> lane) & 1) {
+                s.rej_tok[lanes_below(rejected)] = t;
+                s.rej_x[lanes_below(rejected)] = xg;
+            }
             wave_lds_sync();
             rejtok = lane < nrej ? s.rej_tok[lane] : -1;
+            rejx = s.rej_x[lane];
             wave_lds_sync();
         } else {
             while (kids) {
@@ -479,7 +501,8 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
                 const float ucc = readlane_f32(uc, cc);
                 if ((double)ucc * (1.0 - R) < pcc) { next = cc; break; }
                 R += pcc;
-                if (lane == nrej) rejtok = tcc;
+                const float xcc = readlane_f32(xg, cc);
+                if (lane == nrej) { rejtok = tcc; rejx = xcc; }
                 ++nrej;
             }
         }
@@ -517,8 +540,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
     L = s.row_L[cur];
     const size_t p0 = ((size_t)b * a.T + cur) * a.nsub;
     const float *xr = a.logits + ((size_t)b * a.T + cur) * a.V;
-    // masses of the first 128 blocks: requested together with the rejected tokens' logits
-    // (a row this wavefront has just merged still has them in registers)
+    // masses of the first 128 blocks (a row this wavefront has just merged still has them in registers)
     double mass0 = mass_[0], mass1 = mass_[1];
     if (cur != r) {
         mass0 = (lane < a.nsub) ? load_shared_result(&a.part_l[p0 + lane]) : 0.0;
@@ -528,10 +550,10 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         float xj = -INFINITY;
         int sj = -1;
         if (lane < nrej && rejtok >= 0 && rejtok < a.V) {
-            xj = xr[rejtok];
+            xj = rejx;
             sj = rejtok / kAccSub;
         }
-        s.rej_e[lane] = sj < 0 ? 0.0 : a.exact_scale ? scaled_exp<true>(xj, a, M) : scaled_exp<false>(xj, a, M);
+        s.rej_e[lane] = sj < 0 ? 0.0 : (double)(a.exact_scale ? scaled_exp<true>(xj, a, M) : scaled_exp<false>(xj, a, M));
         s.rej_sub[lane] = sj;
         wave_lds_sync();
     }
@@ -539,28 +561,39 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
     double before = 0.0;                                     // mass of the blocks before this group of 64
     int pick = -1, lastc = -1;
     double resid = 0.0;
-    for (int c0 = 0; c0 < a.nsub && pick < 0; c0 += kWave) {
-        const int cs = c0 + lane;
-        double mass = c0 == 0 ? mass0 : mass1;
-        if (c0 >= 2 * kWave) mass = (cs < a.nsub) ? load_shared_result(&a.part_l[p0 + cs]) : 0.0;
+    // what the blocks' masses are without the rejected tokens; two groups of 64 blocks at a time
+    for (int c0 = 0; c0 < a.nsub && pick < 0; c0 += 2 * kWave) {
+        double mass[2] = {mass0, mass1};
+        if (c0 > 0) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) mass[i] = (c0 + i * kWave + lane < a.nsub) ? load_shared_result(&a.part_l[p0 + c0 + i * kWave + lane]) : 0.0;
+        }
         for (int j0 = 0; j0 < nrej; j0 += 8) {                // broadcast LDS reads, eight in flight; entries
 #pragma unroll                                                 // past nrej name no block
             for (int j = j0; j < j0 + 8; ++j) {
                 const double e = s.rej_e[j];                 // read unconditionally: no branch per entry
-                mass -= (s.rej_sub[j] == cs) ? e : 0.0;
+                const int sub = s.rej_sub[j] - c0;
+                mass[0] -= (sub == lane) ? e : 0.0;
+                mass[1] -= (sub == kWave + lane) ? e : 0.0;
             }
         }
-        mass = mass > 0.0 ? mass : 0.0;
-        const double incl = before + wave_scan_f64(mass);
-        const uint64_t hit = __ballot(cs < a.nsub && incl > target);
-        const uint64_t pos = __ballot(cs < a.nsub && mass > 0.0);
-        if (pos) lastc = c0 + 63 - __clzll((long long)pos);
-        if (hit) {
-            const int hl = __ffsll((long long)hit) - 1;
-            pick = c0 + hl;
-            resid = target - (readlane_f64(incl, hl) - readlane_f64(mass, hl));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int cs = c0 + i * kWave + lane;
+            const double m = mass[i] > 0.0 ? mass[i] : 0.0;
+            const double incl = before + wave_scan_f64(m);
+            const uint64_t hit = __ballot(cs < a.nsub && incl > target);
+            const uint64_t pos = __ballot(cs < a.nsub && m > 0.0);
+            if (pick < 0) {
+                if (pos) lastc = c0 + i * kWave + 63 - __clzll((long long)pos);
+                if (hit) {
+                    const int hl = __ffsll((long long)hit) - 1;
+                    pick = c0 + i * kWave + hl;
+                    resid = target - (readlane_f64(incl, hl) - readlane_f64(m, hl));
+                }
+                before = readlane_f64(incl, kWave - 1);
+            }
         }
-        before = readlane_f64(incl, kWave - 1);
     }
     if (pick < 0) {                                          // rounding pushed the target past the total:
         pick = lastc >= 0 ? lastc : 0;                       // the last token with mass is taken
@@ -574,50 +607,52 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         const int off = rejtok - pick * kAccSub;
         atomicOr(&s.rej_bits[off / kAccEPT], 1u << (off % kAccEPT));
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (everything asked for has been used by now)
-    const unsigned int rows_before = wave_fetch_add(seq_counter, 1u);
+    // The block is asked for first, then this row counted (everything else asked for has been used by now, and the stores are
+    // acknowledged while the block is on its way); the count is looked at when the token is out.
     float xv[kAccEPT];
     int first[kAccEPT / 4];
     load_block<VEC4, true>(xr, pick * kAccSub, a.V, xv, first);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    unsigned int rows_before = 0;
+    if (lane == 0) rows_before = __hip_atomic_fetch_add(seq_counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     wave_lds_sync();
     const unsigned int rejected = s.rej_bits[lane];
     const int i0 = pick * kAccSub + lane * kAccEPT;
-    double pv[kAccEPT];
+    // (Every lane adds up its sixteen exponentials and leaves them in LDS, from where the sixteen of the lane that the target
+    // falls into are taken one per lane.)
     if (a.exact_scale) {
 #pragma unroll
-        for (int e = 0; e < kAccEPT; ++e) pv[e] = scaled_exp<true>(xv[e], a, M);
+        for (int e = 0; e < kAccEPT; ++e) xv[e] = scaled_exp<true>(xv[e], a, M);
     } else {
 #pragma unroll
-        for (int e = 0; e < kAccEPT; ++e) pv[e] = scaled_exp<false>(xv[e], a, M);
+        for (int e = 0; e < kAccEPT; ++e) xv[e] = scaled_exp<false>(xv[e], a, M);
     }
     double sum = 0.0;
     int lastpos = -1;
 #pragma unroll
     for (int e = 0; e < kAccEPT; ++e) {
-        const int i = i0 + e;
-        pv[e] = (i < a.V && !((rejected >> e) & 1)) ? pv[e] : 0.0;
-        sum += pv[e];
-        if (pv[e] > 0.0) lastpos = i;
+        xv[e] = (i0 + e < a.V && !((rejected >> e) & 1)) ? xv[e] : 0.f;
+        sum += (double)xv[e];
+        if (xv[e] > 0.f) lastpos = i0 + e;
     }
+#pragma unroll
+    for (int g = 0; g < kAccEPT / 4; ++g)
+        reinterpret_cast<float4 *>(s.mass)[lane * (kAccEPT / 4) + g] = make_float4(xv[4 * g], xv[4 * g + 1], xv[4 * g + 2], xv[4 * g + 3]);
+    wave_lds_sync();
     const double incl = wave_scan_f64(sum);
     const uint64_t hit = __ballot(incl > resid);
-    const int lp = (int)wave_max_u32((uint32_t)(lastpos + 1)) - 1;      // last token of the block with mass
-    int bonus = lp;
+    int bonus = (int)wave_max_u32((uint32_t)(lastpos + 1)) - 1;          // last token of the block with mass
     if (hit) {
         const int owner = __ffsll((long long)hit) - 1;
-        int mine = -1;
-        double cdf = incl - sum;
-#pragma unroll
-        for (int e = 0; e < kAccEPT; ++e) {
-            cdf += pv[e];
-            if (mine < 0 && pv[e] > 0.0 && cdf > resid) mine = i0 + e;
-        }
-        if (mine < 0) mine = lastpos;
-        const int got = (int)readlane_u32((uint32_t)mine, owner);
-        if (got >= 0) bonus = got;
+        const float pe = lane < kAccEPT ? s.mass[owner * kAccEPT + lane] : 0.f;
+        const double cdf = (readlane_f64(incl, owner) - readlane_f64(sum, owner)) + wave_scan_f64((double)pe);
+        const uint64_t with_mass = __ballot(pe > 0.f), past = with_mass & __ballot(cdf > resid);
+        // (rounding may leave none past the target: the owner's last token with mass)
+        const int e = past ? __ffsll((long long)past) - 1 : with_mass ? 63 - __clzll((long long)with_mass) : -1;
+        if (e >= 0) bonus = pick * kAccSub + owner * kAccEPT + e;
     }
     if (lane == 0) a.bonus[b] = bonus;
-    finish_row(rows_before);
+    finish_row(readlane_u32(rows_before, 0));
 }
 
 __global__ void validate_tree_kernel(const int32_t *parents, const int32_t *n_nodes, int B, int T, int32_t *bad) {
@@ -703,7 +738,18 @@ static radar_status launch_accept(const float *target_logits, const int32_t *dra
     a.inv_temp_f = (float)a.inv_temp;
     a.exact_scale = ((double)a.inv_temp_f == a.inv_temp) ? 1 : 0;
     accept_layout(d->B, d->T_max, (size_t)nsub, static_cast<char *>(workspace), &a);
-    a.check_from = kAccUnchecked;
+    // Large launches: the roots' rows are read first and alone, the workgroups behind them wait for the roots' decisions (the
+    // memory's queue is first come, first served: 2048 workgroups that read at once are 64 MB ahead of the roots' results, whose
+    // rows were complete after 9.5 us instead of 6.7).  Greedy 2.5 us, sampled 4.5 (its decisions are later); the chip holds eight
+    // workgroups per CU of the greedy kernel, six of the sampled one, and later ones find the decisions made.
+    // us without / with it, 61 rows of V = 128256 and paths of 0, 2 and 8 nodes: greedy, 4 sequences 13.8 / 11.5, 15.7 / 14.5, 21.0 / 18.2;
+    // 16 sequences 22.2 / 17.5, 25.5 / 23.5, 40.3 / 35.7; sampled, 8 sequences 20 / 15.6, 22.5 / 22.3, 34 / 30.8.  Smaller launches
+    // lose by it (one sequence, sampled, 2 nodes 11.1 / 14.1; two 13.2 / 14.9; greedy, 8 sequences of V = 32000 10.3 / 10.7).
+    const int64_t blocks = (int64_t)d->B * d->T_max * nsub;
+    const bool wait = mode == RADAR_ACCEPT_GREEDY ? blocks >= kAccManyBlocks / 2 : mode == RADAR_ACCEPT_SAMPLE && blocks >= kAccManyBlocks;
+    a.check_from = wait ? (int)(d->B * nwg) : kAccUnchecked;
+    a.wait = mode == RADAR_ACCEPT_GREEDY ? 250 : 450;
+    a.wait_until = wait ? (mode == RADAR_ACCEPT_GREEDY ? 2048 : 1536) : 0;
     // A greedy walk is shortest at the end of the launch, in registers over all rows' results, as long as the launch
     // is not much more than the chip holds at once (one sequence of 16 rows, V = 32000: 5.6 us against 7.1; two of
     // 61 rows, V = 128256, 3904 workgroups: 13.9 against 13.3).  A sampled one is not: its exponentials and the

@@ -184,7 +184,8 @@ def test_large_vocabulary_many_blocks(oracle, mode):
 
 
 @pytest.mark.parametrize("mode", [0, 1])
-@pytest.mark.parametrize("B,T,V,chain", [(3, 64, 40000, True), (6, 64, 34000, False), (12, 64, 65539, False)])
+@pytest.mark.parametrize("B,T,V,chain", [(3, 64, 40000, True), (6, 64, 34000, False), (12, 64, 65539, False),
+                                          (13, 64, 61001, True)])       # the rows behind the roots wait for the walk
 def test_walk_carried_from_row_to_row(oracle, mode, B, T, V, chain):
     """The walk that goes on with whichever row completes next: trees as deep as they get, launches with more workgroups
     than start at once (rows off the path are left unread), two blocks per wavefront with odd row lengths, and one
