@@ -46,6 +46,8 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kMaxSlack = 8.0f;          // how far a row's maximum may pass its reference (log2 units; tile_softmax)
 constexpr float kNegBig = -1.0e30f;        // finite stand-in for "no score yet" (log2 units)
 
+// (Each kernel takes what its first loads wait for as leading scalar arguments beside this: those are in registers when it
+// starts, the rest is a round trip of 0.25 us.)
 struct AttnArgs {
     const __bf16 *q, *k, *v;
     const int32_t *parents, *ctx_lens, *n_nodes;
@@ -397,7 +399,9 @@ __device__ __forceinline__ void gs_finish(const AttnArgs &a, Acc O, float m_run,
 }
 
 template <int D, bool DEEP>
-__global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(const __bf16 *k_, const __bf16 *v_, int64_t kv_sb, int64_t kv_sh, int kv_ss_, int kps,
+                                                                 int S, int n_ublk, const __bf16 *q_, AttnArgs a) {
+    a.k = k_; a.v = v_; a.kv_sb = kv_sb; a.kv_sh = kv_sh; a.kv_ss = kv_ss_; a.kps = kps; a.S = S; a.n_ublk = n_ublk; a.q = q_;
     constexpr int DB = D / 32;              // 32-row blocks of O^T
 
     constexpr int TILE = 2 * kKT * D * 2;   // one K tile ([64][D] bf16, swizzled) + one V^T tile ([D][64], swizzled)
@@ -681,7 +685,10 @@ __device__ __forceinline__ void ld_issue_tile(unsigned char *buf, const __bf16 *
 
 // FLAT: the rows are dealt out on the device; otherwise one fixed range of kps rows per workgroup.
 template <int D, bool FLAT>
-__global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(const int32_t *ctx_lens, const int32_t *n_nodes, int T, int S, int B, int Hkv, int G,
+                                                                 int n_ublk, int nqb, int shares, uint32_t shares_inv, int per_unit, AttnArgs a) {
+    a.ctx_lens = ctx_lens; a.n_nodes = n_nodes; a.T = T; a.S = S; a.B = B; a.Hkv = Hkv; a.G = G;
+    a.n_ublk = n_ublk; a.nqb = nqb; a.shares = shares; a.shares_inv = shares_inv; a.per_unit = per_unit;
     constexpr int DB = D / 32;
     constexpr int TILE = 2 * kKT * D * 2;   // one K tile ([64][D] bf16, swizzled) + one V tile (row-major, swizzled)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1031,10 +1038,12 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
 // 0.1 us more than it gives, and four groups cost more than two nearly everywhere: a workgroup of 1024 lanes starts
 // late).  Ranges cut on the host are merged by one group, however many they are.
 template <int D, int E>
-__global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(const int32_t *ctx_lens, const int32_t *n_nodes, const uint64_t *part_o,
+                                                                          const float *part_ml, int T, int kps, int S, int max_splits, int shares, int G, AttnArgs a) {
     __shared__ float red[E > 1 ? E - 1 : 1][10][kAttnThreads];
     constexpr int SL = 32, DQ = 8;                          // slice width, floats per lane
-    const int slice = blockIdx.x % (D / SL), h = blockIdx.x / (D / SL), b = blockIdx.y;
+    a.ctx_lens = ctx_lens; a.n_nodes = n_nodes; a.T = T; a.kps = kps; a.S = S; a.max_splits = max_splits; a.shares = shares; a.G = G;
+    const int slice = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int L = prefix_rows(a, b);
     int nn = a.n_nodes ? a.n_nodes[b] : a.T;
     nn = max(1, min(nn, a.T));
@@ -1077,10 +1086,10 @@ __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(AttnA
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             const size_t en = entry_of(min(s0 + j * E, count - 1));
-            ms[j] = a.part_ml[en * 96 + j32];
-            l0[j] = a.part_ml[en * 96 + 32 + j32];
-            ls[j] = l0[j] * a.part_ml[en * 96 + 64 + j32];   // l x magnitude
-            ow[j] = *reinterpret_cast<const u32x4 *>(a.part_o + en * (size_t)(D / 4 * 32) + ((d0 >> 3) * 32 + j32) * 2);
+            ms[j] = part_ml[en * 96 + j32];
+            l0[j] = part_ml[en * 96 + 32 + j32];
+            ls[j] = l0[j] * part_ml[en * 96 + 64 + j32];   // l x magnitude
+            ow[j] = *reinterpret_cast<const u32x4 *>(part_o + en * (size_t)(D / 4 * 32) + ((d0 >> 3) * 32 + j32) * 2);
         }
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
@@ -1245,7 +1254,8 @@ static hipError_t launch_ld(const AttnArgs &a, dim3 grid, hipStream_t s) {
     static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_ld_kernel<D, FLAT>),
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (configured != hipSuccess) return configured;
-    return launch("tree_attn_group_share", tree_attn_ld_kernel<D, FLAT>, grid, dim3(kGsThreads), bytes, s, a);
+    return launch("tree_attn_group_share", tree_attn_ld_kernel<D, FLAT>, grid, dim3(kGsThreads), bytes, s, a.ctx_lens, a.n_nodes, a.T, a.S, a.B, a.Hkv, a.G,
+                  a.n_ublk, a.nqb, a.shares, a.shares_inv, a.per_unit, a);
 }
 
 template <int D, bool DEEP>
@@ -1255,7 +1265,8 @@ static hipError_t launch_gs(const AttnArgs &a, dim3 grid, hipStream_t s) {
     static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_gs_kernel<D, DEEP>),
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, gs_smem_bytes<D>());
     if (configured != hipSuccess) return configured;
-    return launch("tree_attn_group_share", tree_attn_gs_kernel<D, DEEP>, grid, dim3(kGsThreads), gs_smem_bytes<D>(), s, a);
+    return launch("tree_attn_group_share", tree_attn_gs_kernel<D, DEEP>, grid, dim3(kGsThreads), gs_smem_bytes<D>(), s, a.k, a.v, a.kv_sb, a.kv_sh,
+                  (int)a.kv_ss, a.kps, a.S, a.n_ublk, a.q, a);
 }
 
 template <int D>
@@ -1313,7 +1324,6 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
     a.unit_tab = reinterpret_cast<uint64_t *>(ws + p.off_tab);
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const dim3 block(kAttnThreads);
     if ((long)a.B * a.n_ublk > 65535) return RADAR_UNSUPPORTED_SHAPE;
     if (p.one) {
         const dim3 ogrid((unsigned)a.Hkv, (unsigned)(a.G * a.nqb), (unsigned)a.B);
@@ -1329,13 +1339,14 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
         if (e != hipSuccess) return RADAR_HIP_ERROR;
     }
     if (a.max_splits > 1 || p.shares > 0) {
-        const dim3 mgrid((unsigned)(a.Hq * (d->D / 32)), (unsigned)a.B);
         const bool many = p.shares >= 16l * d->B * d->Hkv;          // sixteen shares per KV head or more (dealt-out rows only)
-        const dim3 block2(kAttnThreads * 2);
-        const hipError_t e = d->D == 128 ? (many ? launch("tree_attn_merge", tree_attn_merge_kernel<128, 2>, mgrid, block2, 0, s, a)
-                                                 : launch("tree_attn_merge", tree_attn_merge_kernel<128, 1>, mgrid, block, 0, s, a))
-                                         : (many ? launch("tree_attn_merge", tree_attn_merge_kernel<64, 2>, mgrid, block2, 0, s, a)
-                                                 : launch("tree_attn_merge", tree_attn_merge_kernel<64, 1>, mgrid, block, 0, s, a));
+        const dim3 mgrid((unsigned)(d->D / 32), (unsigned)a.Hq, (unsigned)a.B);
+        auto go = [&](auto kernel, int groups) {
+            return launch("tree_attn_merge", kernel, mgrid, dim3((unsigned)(kAttnThreads * groups)), 0, s, a.ctx_lens, a.n_nodes, a.part_o, a.part_ml, a.T, a.kps,
+                          a.S, a.max_splits, a.shares, a.G, a);
+        };
+        const hipError_t e = d->D == 128 ? (many ? go(tree_attn_merge_kernel<128, 2>, 2) : go(tree_attn_merge_kernel<128, 1>, 1))
+                                         : (many ? go(tree_attn_merge_kernel<64, 2>, 2) : go(tree_attn_merge_kernel<64, 1>, 1));
         if (e != hipSuccess) return RADAR_HIP_ERROR;
     }
     return RADAR_OK;
