@@ -712,11 +712,14 @@ __global__ __launch_bounds__(kTopkThreads) void rerank_kernel(RerankArgs a) {
 // its share of the stream (one workgroup per CU, hand-over and ticket per chunk).  Two launches
 // instead: a streaming kernel of small workgroups (several per CU, out of step with each other)
 // without tickets or hand-over, each of which leaves one top-k list, maximum and sum of exponentials per
-// 4096 logits in the workspace, then one workgroup per sequence that does what the last workgroup of the single
-// launch does.
+// 8192 logits in the workspace, then one workgroup per sequence that does what the last workgroup of the single
+// launch does.  (Per 4096 logits the stream paid for its barriers and bookkeeping twice as often, and rows of more than
+// 65536 logits were merged the long way: F = 10, V = 128256, 4 / 16 / 64 sequences 12.1 / 21.7 / 61.7 us, now 10.6 /
+// 20.3 / 59.5, the last 5.5 TB/s.)
 constexpr int kStreamThreads = 256;
 constexpr int kStreamWaves = kStreamThreads / kWave;
-constexpr int kStreamChunk = kStreamThreads * 16;
+constexpr int kStreamEPT = 32;                                     // logits per lane
+constexpr int kStreamChunk = kStreamThreads * kStreamEPT;
 
 // true: the sequence's cycle has stopped (or its state is out of range) and the call leaves it alone
 __device__ __forceinline__ bool cycle_skips(const radar_cycle_state *st, int pool_count_max, int *pool_count) {
@@ -731,13 +734,17 @@ constexpr int kStreamHot = 16;                                     // lanes of a
 constexpr int kStreamCap = 128;                                    // candidates of a chunk; more (runs of equal values) rank per wavefront
 
 struct StreamFast {
-    alignas(16) float dump[kStreamWaves][kStreamHot * 16];
+    alignas(16) float dump[kStreamWaves][kStreamHot * kStreamEPT];
     uint64_t surv[kStreamCap + 8];
     unsigned char lane_of[kStreamWaves][kStreamHot];
 };
 
 template <bool VEC4>
-__global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(ExpandArgs a) {
+__global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const float *logits, int F, int V, int k, int nchunks, int pool_count,
+                                                                         radar_cycle_state *cycle, int has_policy, int pol_has_state, ExpandArgs a) {
+    a.logits = logits; a.F = F; a.V = V; a.k = k; a.nchunks = nchunks; a.pool_count = pool_count; a.cycle = cycle;
+    a.has_policy = has_policy; a.pol_has_state = pol_has_state;
+    constexpr int EPT = kStreamEPT;
     __shared__ union {
         StreamFast fast;
         struct {
@@ -745,14 +752,14 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(Expand
             uint64_t wlists[kStreamWaves][kWaveListSlots];
         } ties;
     } s;
-    __shared__ float gmax[4 * kStreamWaves];                       // maxima of the sixteen 16-lane rows
+    __shared__ float gmax[8 * kStreamWaves];                       // maxima of the 32 eight-lane groups
     __shared__ double wave_l[kStreamWaves];
     __shared__ unsigned int nsurv;
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int row = blockIdx.y;                                    // sequence * F + frontier row
     int unused;
     if (cycle_skips(a.cycle ? a.cycle + row / a.F : nullptr, a.pool_count, &unused)) return;   // the whole workgroup
-    // sixteen logits per lane, four at a time and all wavefronts side by side: where a row ends inside the chunk,
+    // EPT logits per lane, four at a time and all wavefronts side by side: where a row ends inside the chunk,
     // every wavefront still has some of it
     const int base = blockIdx.x * kStreamChunk;
     const float *rowp = a.logits + (size_t)row * a.V;
@@ -767,9 +774,9 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(Expand
         hrows.finish(a.pol, bz, [&](int r, float v) { gate[r] = v; });
     }
 
-    float4 raw[4];
+    float4 raw[EPT / 4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < EPT / 4; ++g) {
         const int idx0 = base + g * (kStreamThreads * 4) + tid * 4;
         if (VEC4) {
             raw[g] = *reinterpret_cast<const float4 *>(rowp + (idx0 < a.V ? idx0 : 0));
@@ -780,54 +787,47 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(Expand
             raw[g].w = rowp[min(idx0 + 3, a.V - 1)];
         }
     }
-    float x[16];
+    float x[EPT];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < EPT / 4; ++g) {
         x[4 * g + 0] = raw[g].x; x[4 * g + 1] = raw[g].y; x[4 * g + 2] = raw[g].z; x[4 * g + 3] = raw[g].w;
     }
     if (base + kStreamChunk > a.V) {                               // the row's last chunk only
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
+        for (int e = 0; e < EPT; ++e) {
             const int idx = base + (e >> 2) * (kStreamThreads * 4) + tid * 4 + (e & 3);
             x[e] = idx < a.V ? x[e] : -INFINITY;
         }
     }
-    // ---- the maxima of the sixteen 16-lane rows: the chunk's maximum, and as threshold of its top-k their k-th
-    // largest (at least k logits of the chunk reach it, one per row whose maximum does; on untied data
-    // only about 1.6 k do)
+    // ---- the maxima of the 32 eight-lane groups: the chunk's maximum, and as threshold of its top-k their k-th
+    // largest (at least k logits of the chunk reach it, one per group whose maximum does; on untied data 1.2 k to 1.4 k.
+    // Of sixteen groups the 16th largest is the smallest, which lets the whole chunk through: 64 sequences of 16 rows, V = 32000, k = 16 took 57 us instead of 30.)
     float tm = x[0];
 #pragma unroll
-    for (int e = 1; e < 16; ++e) tm = fmaxf(tm, x[e]);
-    float rm = tm;
-    rm = fmaxf(rm, dpp_f32<0xB1>(rm));
-    rm = fmaxf(rm, dpp_f32<0x4E>(rm));
-    rm = fmaxf(rm, dpp_f32<0x141>(rm));
-    rm = fmaxf(rm, dpp_f32<0x140>(rm));
-    if ((lane & 15) == 0) gmax[w * 4 + (lane >> 4)] = rm;
+    for (int e = 1; e < EPT; ++e) tm = fmaxf(tm, x[e]);
+    float gm = tm;
+    gm = fmaxf(gm, dpp_f32<0xB1>(gm));
+    gm = fmaxf(gm, dpp_f32<0x4E>(gm));
+    gm = fmaxf(gm, dpp_f32<0x141>(gm));
+    if ((lane & 7) == 0) gmax[w * 8 + (lane >> 3)] = gm;
     if (threadIdx.x == 0) nsurv = 0;
     __syncthreads();
-    const float g16 = gmax[lane & 15];
-    float cm = g16;
+    const float g32 = gmax[lane & 31];
+    float cm = g32;
     cm = fmaxf(cm, dpp_f32<0xB1>(cm));
     cm = fmaxf(cm, dpp_f32<0x4E>(cm));
     cm = fmaxf(cm, dpp_f32<0x141>(cm));
     cm = fmaxf(cm, dpp_f32<0x140>(cm));
-    float tl = 0.f;
+    const auto c2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(cm), __float_as_uint(cm), false, false);
+    cm = fmaxf(__uint_as_float(c2[0]), __uint_as_float(c2[1]));
+    float tl[4] = {0.f, 0.f, 0.f, 0.f};                            // four fp32 chains of eight terms, fp64 from there on
     if (cm > -INFINITY) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) tl += __builtin_amdgcn_exp2f((x[e] - cm) * kLog2eF);
+        for (int e = 0; e < EPT; ++e) tl[e & 3] += __builtin_amdgcn_exp2f((x[e] - cm) * kLog2eF);
     }
-    const double wl = wave_sum_f64((double)tl);
+    const double wl = wave_sum_f64(((double)tl[0] + (double)tl[1]) + ((double)tl[2] + (double)tl[3]));
     if (lane == 0) wave_l[w] = wl;
-    const uint32_t ov = ord_of(g16);
-    int larger = 0;                                                // ties: all of them rank with the first
-    count_larger<1>(ov, larger);
-    uint32_t c = larger < K ? ov : 0xffffffffu;
-    c = min(c, dpp_u32<0xB1>(c));
-    c = min(c, dpp_u32<0x4E>(c));
-    c = min(c, dpp_u32<0x141>(c));
-    c = min(c, dpp_u32<0x140>(c));
-    const float tau = float_of_ord(c);
+    const float tau = float_of_ord(kth_of_32(ord_of(g32), K));
 
     // ---- Lanes whose largest logit reaches the threshold (about 1.6 k of the 256) leave all their logits in
     // LDS; their wavefront compares those one per lane and appends what passes to the chunk's list.  (A
@@ -841,16 +841,16 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(Expand
         float *const dump = s.fast.dump[w];
         if (hot) {
             const int at = lanes_below(hm);
-            float4 *d4 = reinterpret_cast<float4 *>(dump + at * 16);
+            float4 *d4 = reinterpret_cast<float4 *>(dump + at * EPT);
 #pragma unroll
-            for (int g = 0; g < 4; ++g) d4[g] = make_float4(x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]);
+            for (int g = 0; g < EPT / 4; ++g) d4[g] = make_float4(x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]);
             s.fast.lane_of[w][at] = (unsigned char)lane;
         }
         wave_lds_sync();
-        for (int d0 = 0; d0 < nhot; d0 += 4) {                     // four lanes' logits at a time
-            const int d = d0 + (lane >> 4), e = lane & 15;
+        for (int d0 = 0; d0 < nhot; d0 += kWave / EPT) {           // two or four lanes' logits at a time
+            const int d = d0 + lane / EPT, e = lane % EPT;
             const bool live = d < nhot;
-            const float v = dump[min(d, nhot - 1) * 16 + e];
+            const float v = dump[min(d, nhot - 1) * EPT + e];
             const int idx = base + (e >> 2) * (kStreamThreads * 4) + (w * kWave + (int)s.fast.lane_of[w][min(d, nhot - 1)]) * 4 + (e & 3);
             const uint64_t m = __ballot(live && v >= tau && idx < a.V);
             if (m != 0) {
@@ -867,15 +867,19 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(Expand
     if (n > kStreamCap) {
         // Long runs of equal values: every wavefront ranks its own logits exactly, then one ranks the four lists.
         __syncthreads();                                           // the short path's LDS is overlaid
-        uint64_t k1[8], k2[9];
+        uint64_t wt = 0;
+#pragma unroll 1
+        for (int g0 = 0; g0 < EPT / 4; g0 += 2) {                  // (read again: a rolled loop would index the registers dynamically)
+            uint64_t kk[9];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int idx = base + (e >> 2) * (kStreamThreads * 4) + tid * 4 + (e & 3);
-            const uint64_t key = idx < a.V ? make_key(x[e], uint32_t(idx)) : 0;
-            if (e < 8) k1[e] = key; else k2[e - 8] = key;
+            for (int u = 0; u < 8; ++u) {
+                const int idx = base + (g0 + (u >> 2)) * (kStreamThreads * 4) + tid * 4 + (u & 3);
+                const float v = rowp[min(idx, a.V - 1)];
+                kk[u] = idx < a.V ? make_key(v, uint32_t(idx)) : 0;
+            }
+            kk[8] = wt;
+            wt = wave_topk<9>(kk, K, s.ties.wtk[w]);
         }
-        k2[8] = wave_topk<8>(k1, K, s.ties.wtk[w]);
-        const uint64_t wt = wave_topk<9>(k2, K, s.ties.wtk[w]);
         if (lane < kWaveListSlots) s.ties.wlists[w][lane] = wt;    // lanes 16.. hold 0
         __syncthreads();
         if (w == 0) {
@@ -920,7 +924,10 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(Expand
 
 // one workgroup per sequence, after expand_stream_kernel
 template <int MODE>
-__global__ __launch_bounds__(kExpThreads, 1) void expand_finish_kernel(ExpandArgs a) {
+__global__ __launch_bounds__(kExpThreads, 1) void expand_finish_kernel(const uint64_t *part_keys, const double *part_l, const float *part_m, int F, int nchunks,
+                                                                       int k, int pool_count, radar_cycle_state *cycle_, ExpandArgs a) {
+    a.part_keys = const_cast<uint64_t *>(part_keys); a.part_l = const_cast<double *>(part_l); a.part_m = const_cast<float *>(part_m);
+    a.F = F; a.nchunks = nchunks; a.k = k; a.pool_count = pool_count; a.cycle = cycle_;
     __shared__ ExpandSmem s;
     const int bz = blockIdx.x;
     if (bz != 0) sequence_view(a, bz);
@@ -936,9 +943,9 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_finish_kernel(ExpandArg
 using namespace radar;
 
 // Logits per lane: the fewest (shortest critical path per workgroup) that keep the launch at one
-// workgroup per CU and a row at as many chunks as are merged the short way, as far as there are such (one row of
-// V = 128256 in 16 chunks instead of 32: XX us per call instead of XX); launches too large for that take the
-// most, i.e. the fewest workgroups.
+// workgroup per CU and a row at as many chunks as are merged the short way, as far as there are such (a call over one row
+// of V = 128256 in 16 chunks takes 7.0 us, of V = 262144 in 16 instead of 64 chunks 7.5 instead of 9.4); launches too
+// large for that take the most, i.e. the fewest workgroups.
 static int plan_expand_ept(int F, int V) {
     for (const int most : {kFewChunks, kExpMaxChunks})
         for (int ept = kExpMinEPT; ept <= 16; ept *= 2) {
@@ -954,7 +961,7 @@ static size_t expand_gate_bytes(size_t B) { return (B * 4 * kPolH * sizeof(float
 
 static size_t expand_workspace_bytes(const radar_expand_desc *d, size_t B) {
     if (!d || d->F < 1 || d->V < 1 || B < 1) return 0;
-    static_assert(kStreamChunk == kExpThreads * kExpMinEPT, "both paths' smallest chunk");
+    static_assert(kStreamChunk >= kExpThreads * kExpMinEPT, "the single launch has the smallest chunk");
     const size_t per_chunk = (size_t)kExpThreads * kExpMinEPT;                // most chunks any plan uses
     const size_t nchunks = ((size_t)d->V + per_chunk - 1) / per_chunk;
     size_t bytes = B * kCounterBytes;
@@ -1025,11 +1032,16 @@ static radar_status launch_expand(const float *logits, const float *parent_score
     hipError_t e;
     if (stream) {
         const dim3 sgrid((unsigned)nchunks, (unsigned)(B * d->F));
-        e = vec4 ? launch("expand_stream", expand_stream_kernel<true>, sgrid, dim3(kStreamThreads), 0, st, a)
-                 : launch("expand_stream", expand_stream_kernel<false>, sgrid, dim3(kStreamThreads), 0, st, a);
+        auto go = [&](auto kernel) {
+            return launch("expand_stream", kernel, sgrid, dim3(kStreamThreads), 0, st, a.logits, a.F, a.V, a.k, a.nchunks, a.pool_count, a.cycle, a.has_policy,
+                          a.pol_has_state, a);
+        };
+        e = vec4 ? go(expand_stream_kernel<true>) : go(expand_stream_kernel<false>);
         if (e != hipSuccess) return RADAR_HIP_ERROR;
-        e = pol ? launch("expand_finish", expand_finish_kernel<kExpPolicy>, dim3((unsigned)B), block, 0, st, a)
-                : launch("expand_finish", expand_finish_kernel<kExpExt>, dim3((unsigned)B), block, 0, st, a);
+        auto fin = [&](auto kernel) {
+            return launch("expand_finish", kernel, dim3((unsigned)B), block, 0, st, a.part_keys, a.part_l, a.part_m, a.F, a.nchunks, a.k, a.pool_count, a.cycle, a);
+        };
+        e = pol ? fin(expand_finish_kernel<kExpPolicy>) : fin(expand_finish_kernel<kExpExt>);
         return e == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
     }
     const bool ext = cycle != nullptr || B > 1;
