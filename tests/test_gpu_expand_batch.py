@@ -59,6 +59,34 @@ def test_batched_call_matches_oracle_per_sequence(oracle, B, F, V, k, pre):
         assert np.max(np.abs(host(gp.scores)[s, pre:cap].astype(np.float64) - cp["scores"][pre:cap])) <= SCORE_TOL
 
 
+@pytest.mark.parametrize("V,k", [(70000, 16), (70001, 16), (65536, 5)])   # both kinds of loads; a last chunk of 4464 logits, none
+def test_streamed_candidate_counts_at_the_edges_of_the_lists(oracle, V, k):
+    """From 4 Mi logits on a call streams chunks of 8192: up to 16 lanes of a wavefront and 128 candidates go through LDS
+    and up to 16 candidates out unranked.  Rows with that many logits above the rest, and one more or less, distinct
+    (order decides) and equal (token id decides), scattered and side by side in one wavefront's columns."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(V + k)
+    rows = []
+    for n in (15, 16, 17, 63, 64, 65, 127, 128, 129, 999):
+        for equal in (False, True):
+            x = synth.normal_logits(rng, (V,), 1.0)
+            where = rng.permutation(8192)[:n] if n % 2 else np.arange(n) % 64 + np.arange(n) // 64 * 1024
+            x[where + (8192 if equal else V - 8192)] = 9.0 if equal else 9.0 + rng.permutation(n).astype(np.float32) / 64
+            rows.append(x)
+    F, B = len(rows), 4
+    logits = np.stack([np.stack(rows[s:] + rows[:s]) for s in range(B)])
+    assert logits.size >= 4 << 20
+    ps, ppi = np.zeros((B, F), np.float32), np.full((B, F), -1, np.int32)
+    gp = b.DraftPool(F * k, B=B)
+    g, _ = b.radar_draft_expand_batch(dev(logits), dev(ps), dev(ppi), k, gp)
+    torch.cuda.synchronize()
+    for s in range(B):
+        cp = dict(tokens=np.zeros(F * k, np.int32), scores=np.zeros(F * k, np.float32), parents=np.zeros(F * k, np.int32))
+        r = oracle.draft_expand(logits[s], ps[s], ppi[s], k, cp, 0)
+        assert np.array_equal(host(g.cand_tokens)[s].reshape(F, k), r["cand_tokens"]), s
+        assert np.max(np.abs(host(g.cand_scores)[s].reshape(F, k).astype(np.float64) - r["cand_scores"])) <= SCORE_TOL
+
+
 @pytest.mark.parametrize("V,stops", [
     (32000, (1, 3, 8, 5, 2, 8)),       # single-launch form throughout
     (128256, (4, 8, 1)),
