@@ -1032,12 +1032,14 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
 // Merges the group-share kernels' partials.  A workgroup takes one (sequence, query head, 32-wide slice
 // of the head dimension): lane = (8 consecutive d, tree row i), rows rounded up to 16, 32 or 64, so that a
 // small tree's rows sit in few wavefronts (four rows, 48 partials: 31 us for the call with 64 lanes per
-// d, 22 with 16).  The time is that of dependent rounds of loads, so a lane asks for four or eight
-// partials at once; where the rows are dealt out on the device into sixteen shares or more per KV head, two groups
+// d, 22 with 16).  The time is that of dependent rounds of loads, so a lane asks for NB partials at once, or for
+// as many as there are in steps of four (17 of them in rounds of 8, 8 and 1, which the compiler made five rounds to save
+// registers: 16.0 us for a call over 2048 rows, 15.0 in one), and weighs them by their common maximum.  Where the rows
+// are dealt out on the device into sixteen shares or more per KV head, two groups
 // of lanes take every other partial and meet in LDS (3 heads of 16000 rows 26.5 -> 24.8 us; with 11 pieces it costs
 // 0.1 us more than it gives, and four groups cost more than two nearly everywhere: a workgroup of 1024 lanes starts
 // late).  Ranges cut on the host are merged by one group, however many they are.
-template <int D, int E>
+template <int D, int E, int NB>
 __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(const int32_t *ctx_lens, const int32_t *n_nodes, const uint64_t *part_o,
                                                                           const float *part_ml, int T, int kps, int S, int max_splits, int shares, int G, AttnArgs a) {
     __shared__ float red[E > 1 ? E - 1 : 1][10][kAttnThreads];
@@ -1071,48 +1073,68 @@ __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(const
     const bool live = i < nn && part < SL / DQ;
     const int d0 = slice * SL + part * DQ;
     const int units = a.G * nqb, j32 = i & 31;
-    const int entry0 = slot0 * a.n_ublk * kGsWaves + g * nqb + (nqb == 1 ? 0 : i >> 5);
-    auto entry_of = [&](int n) { return (size_t)(entry0 + (n >> shared) * a.n_ublk * kGsWaves + ((n & shared) ? units : 0)); };
+    // an entry's address: a uniform part, kept in scalar registers, and the lane's offset in the entries of its block
+    const int entry0 = slot0 * a.n_ublk * kGsWaves + g * nqb;
+    const uint32_t block = nqb == 1 ? 0 : i >> 5;
+    const uint32_t lane_ml = block * 96 + j32, lane_o = block * (D / 4 * 32) + ((d0 >> 3) * 32 + j32) * 2;
+    auto entry_of = [&](int n) { return (size_t)__builtin_amdgcn_readfirstlane(entry0 + (n >> shared) * a.n_ublk * kGsWaves + ((n & shared) ? units : 0)); };
     __bf16 *orow = a.out + (size_t)b * a.o_sb + (size_t)i * a.o_st + (size_t)h * a.o_sh + d0;
     const bool lse_lane = a.lse && slice == 0 && part == 0;
     float M = kNegBig, lsum = 0.f;
     float acc[DQ];
 #pragma unroll
     for (int d = 0; d < DQ; ++d) acc[d] = 0.f;
-    auto take = [&](auto batch, int s0) {                   // so many partials at a time, all of their loads in flight
-        constexpr int NB = decltype(batch)::value;
-        float ms[NB], l0[NB], ls[NB];
-        u32x4 ow[NB];
+    auto take = [&](auto batch, int s0) __attribute__((always_inline)) {   // so many partials at a time, their loads in flight together
+        constexpr int N = decltype(batch)::value;
+        float m[N], l[N], mag[N];
+        u32x4 o[N];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
+        for (int j = 0; j < N; ++j) {
             const size_t en = entry_of(min(s0 + j * E, count - 1));
-            ms[j] = part_ml[en * 96 + j32];
-            l0[j] = part_ml[en * 96 + 32 + j32];
-            ls[j] = l0[j] * part_ml[en * 96 + 64 + j32];   // l x magnitude
-            ow[j] = *reinterpret_cast<const u32x4 *>(part_o + en * (size_t)(D / 4 * 32) + ((d0 >> 3) * 32 + j32) * 2);
+            const float *const ml = part_ml + en * 96;
+            m[j] = ml[lane_ml];
+            l[j] = ml[lane_ml + 32];
+            mag[j] = ml[lane_ml + 64];
+            o[j] = *reinterpret_cast<const u32x4 *>(part_o + en * (size_t)(D / 4 * 32) + lane_o);
         }
+        if constexpr (NB > 8) __builtin_amdgcn_sched_barrier(0);    // (else loads follow the arithmetic, to save registers)
+        float Mn = M;
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const bool valid = s0 + j * E < count;
-            const float m = valid ? ms[j] : kNegBig;
-            const float Mn = fmaxf(M, m);
-            const float aold = __builtin_amdgcn_exp2f(M - Mn);
-            const float wnew = valid ? __builtin_amdgcn_exp2f(m - Mn) : 0.f;
-            lsum = lsum * aold + wnew * l0[j];
-            const float wo = wnew * ls[j];                        // the stored rows are o / (l x magnitude)
+        for (int j = 0; j < N; ++j) {
+            if (s0 + j * E >= count) m[j] = kNegBig;
+            Mn = fmaxf(Mn, m[j]);
+        }
+        const float aold = __builtin_amdgcn_exp2f(M - Mn);
+        M = Mn;
+        lsum *= aold;
+#pragma unroll
+        for (int d = 0; d < DQ; ++d) acc[d] *= aold;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const float wl = s0 + j * E < count ? __builtin_amdgcn_exp2f(m[j] - Mn) * l[j] : 0.f;
+            lsum += wl;
+            const float wo = wl * mag[j];                     // the stored rows are o / (l x magnitude)
 #pragma unroll
             for (int d = 0; d < DQ / 2; ++d) {
-                const float lo = (float)__builtin_bit_cast(_Float16, (uint16_t)(ow[j][d] & 0xffffu));
-                const float hi = (float)__builtin_bit_cast(_Float16, (uint16_t)(ow[j][d] >> 16));
-                acc[2 * d] = acc[2 * d] * aold + wo * lo;
-                acc[2 * d + 1] = acc[2 * d + 1] * aold + wo * hi;
+                acc[2 * d] = fmaf(wo, (float)__builtin_bit_cast(_Float16, (uint16_t)(o[j][d] & 0xffffu)), acc[2 * d]);
+                acc[2 * d + 1] = fmaf(wo, (float)__builtin_bit_cast(_Float16, (uint16_t)(o[j][d] >> 16)), acc[2 * d + 1]);
             }
-            M = Mn;
         }
     };
+    auto take_all = [&](auto batch) __attribute__((always_inline)) {
+        constexpr int N = decltype(batch)::value;
+        for (int s0 = eg; s0 < count; s0 += N * E) take(batch, s0);
+    };
     if (live) {
-        if (E > 1 || count <= 4) for (int s0 = eg; s0 < count; s0 += 4 * E) take(std::integral_constant<int, 4>{}, s0);
-        else for (int s0 = 0; s0 < count; s0 += 8) take(std::integral_constant<int, 8>{}, s0);
+        const int each = (count + E - 1) / E;
+        if (NB == 4 || each <= 4) take_all(std::integral_constant<int, 4>{});
+        else if (NB == 8 || each <= 8) take_all(std::integral_constant<int, 8>{});
+        else {
+            const int rounds = (each + NB - 1) / NB, most = (each + rounds - 1) / rounds;
+            if (most <= 12) take_all(std::integral_constant<int, 12>{});
+            else if (most <= 16) take_all(std::integral_constant<int, 16>{});
+            else take_all(std::integral_constant<int, NB>{});
+        }
     }
     if constexpr (E > 1) {
         if (live && eg > 0) {
@@ -1340,13 +1362,18 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
     }
     if (a.max_splits > 1 || p.shares > 0) {
         const bool many = p.shares >= 16l * d->B * d->Hkv;          // sixteen shares per KV head or more (dealt-out rows only)
+        // Many partials at once take registers that a launch of more wavefronts needs to have all of them on the chip: up to 640
+        // (40 heads of 60 rows, 160 of 16 rows).  One sequence of 2048 rows: 32 heads 16.0 -> 15.0 us (8 -> 18 partials at
+        // a time), 16 tree rows 11.7 -> 10.6, 8 heads on 2 13.7 -> 12.4, D = 64 on 4 10.6 -> 9.5; with 48 or 64 heads
+        // 3000 rows would go from 17.6 to 17.8 and from 19.4 to 19.9.
+        const bool wide = (long)d->D / 32 * a.Hq * a.B * (d->T_max > 32 ? 4 : d->T_max > 16 ? 2 : 1) <= 640;
         const dim3 mgrid((unsigned)(d->D / 32), (unsigned)a.Hq, (unsigned)a.B);
         auto go = [&](auto kernel, int groups) {
             return launch("tree_attn_merge", kernel, mgrid, dim3((unsigned)(kAttnThreads * groups)), 0, s, a.ctx_lens, a.n_nodes, a.part_o, a.part_ml, a.T, a.kps,
                           a.S, a.max_splits, a.shares, a.G, a);
         };
-        const hipError_t e = d->D == 128 ? (many ? go(tree_attn_merge_kernel<128, 2>, 2) : go(tree_attn_merge_kernel<128, 1>, 1))
-                                         : (many ? go(tree_attn_merge_kernel<64, 2>, 2) : go(tree_attn_merge_kernel<64, 1>, 1));
+        const hipError_t e = d->D == 128 ? (wide ? (many ? go(tree_attn_merge_kernel<128, 2, 18>, 2) : go(tree_attn_merge_kernel<128, 1, 18>, 1)) : (many ? go(tree_attn_merge_kernel<128, 2, 4>, 2) : go(tree_attn_merge_kernel<128, 1, 8>, 1)))
+                                         : (wide ? (many ? go(tree_attn_merge_kernel<64, 2, 18>, 2) : go(tree_attn_merge_kernel<64, 1, 18>, 1)) : (many ? go(tree_attn_merge_kernel<64, 2, 4>, 2) : go(tree_attn_merge_kernel<64, 1, 8>, 1)));
         if (e != hipSuccess) return RADAR_HIP_ERROR;
     }
     return RADAR_OK;

@@ -204,6 +204,24 @@ def test_one_launch_over_whole_units(oracle, D, ctx, nn, T):
         assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)     # unused rows are zeroed
 
 
+@pytest.mark.parametrize("parts", [2, 4, 5, 8, 9, 12, 13, 16, 17, 18, 19, 24, 25, 33, 36, 37])
+def test_merge_takes_any_number_of_partials(oracle, parts):
+    """The merge asks for up to 18 partials at a time, in steps of four, and for as few rounds as that allows: numbers of
+    ranges at the edges of both, the second sequence with about a third of them."""
+    from paper_2512_14069_amd import binding as b
+    D, nn = (128, 64)[parts & 1], (20, 37)[parts >> 1 & 1]
+    a = shape(2, 4, 2, D, 40, [parts * 64 - nn, parts * 64 // 3], [nn, 9], [5, 3])
+    x = synth.attention_inputs(a, seed=synth.seed_for(1, parts), shuffle=True)
+    ref, ref_lse = oracle.tree_attention(x["q"], x["k_cache"], x["v_cache"], x["parents"], x["ctx_lens"],
+                                         x["n_nodes"], want_lse=True)
+    got, lse = run_gpu(b, x, keys_per_split=64, want_lse=True)
+    for bb in range(2):
+        n = a.n_nodes[bb]
+        check_close(got[bb, :n], ref[bb, :n], f"b={bb}")
+        assert np.max(np.abs(lse[bb, :n] - ref_lse[bb, :n])) < LSE_TOL
+        assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)     # unused rows are zeroed
+
+
 def test_chain_and_star_trees_depth_63(oracle):
     from paper_2512_14069_amd import binding as b
     a = shape(2, 4, 1, 128, 64, [100, 31], [64, 64], [8, 8], k=10)
