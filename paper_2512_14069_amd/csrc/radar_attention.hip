@@ -28,6 +28,7 @@
 // deal the batch's cache rows out among themselves, so that a batch of unlike sequences keeps every
 // CU busy to the end.
 #include "radar_device.h"
+#include <algorithm>
 #include <type_traits>
 #include "radar_host.h"
 
@@ -1176,23 +1177,24 @@ struct AttnPlan {
 // Up to how many cache rows a call is one launch of whole units (tree_attn_one_kernel): as long as the units are no more
 // than the chip holds at once (one per CU with D = 128, two with D = 64), to where a unit's CU takes as long to read all
 // rows as ranges and their merge take.  That is later the more units there are, because ranges then wait for each other,
-// and earlier where a KV head has few (two blocks of rows, at most two heads): half of a range's wavefronts are idle then.
-// Both sides measured at 32 ... 1860 rows for 41 combinations of batch, heads and tree; one launch / ranges in us, at
-// D = 128, 60 tree rows: 32 heads 8.6 / 10.3 over 380 rows, 9.9 / 11.7 over 572, 13.0 / 14.1 over 1060, 17.7 / 15.1 over 1860;
-// four such sequences 10.8 / 15.3 over 500, 14.3 / 16.9 over 1060, 17.7 / 20.4 over 1560; 16 heads on 8 KV heads 8.5 / 9.5
-// over 380, 9.8 / 9.6 over 500; 16 tree rows, 32 heads 9.4 / 10.2 over 616, 10.8 / 10.1 over 716.  D = 64, 8 heads on 4: 7.2 / 8.6 over
-// 500, 8.9 / 10.1 over 1060, 32 sequences of it 12.0 / 13.2 over 572; with 16 tree rows 64 sequences 7.7 / 7.9 over 212, 11.5 / 9.9 over 336.
+// and earlier where a KV head has at most four: half of a range's wavefronts are idle then, and it takes a tile the faster.
+// Both sides measured at 200 ... 1560 rows for 27 combinations of batch, heads and tree; one launch / ranges in us, at
+// D = 128, 60 tree rows: 32 heads 8.3 / 10.7 over 260 rows, 9.9 / 11.2 over 540, 11.6 / 12.1 over 820, 13.1 / 13.1 over 1050; 64
+// heads 10.3 / 13.6 over 620, 13.1 / 15.2 over 1050, 14.8 / 16.2 over 1360, 17.5 / 17.4 over 1560; four sequences of 32 heads
+// 10.6 / 15.2 over 540, 17.5 / 19.5 over 1560; 16 heads on 8 KV heads 8.6 / 9.3 over 360, 9.8 / 9.9 over 540; 16 tree rows, 32
+// heads 8.0 / 8.6 over 316, 9.2 / 8.6 over 496, three sequences 9.6 / 10.3 over 626.  D = 64, 8 heads on 4: 8.1 / 8.6 over 820, 9.1 / 8.5 over
+// 960; eight sequences of 16 heads 8.6 / 11.8 over 820, 11.7 / 18.3 over 1560.
 static int one_launch_rows(const radar_attn_desc *d, int nqb) {
     const long units = (long)d->B * d->Hq * nqb;
     const int G = d->Hq / d->Hkv;
     if (d->D == 64) {
         if (units > 512) return 0;
         if (nqb == 1 && units > 256) return units <= 384 ? 640 : 224;
-        return units >= 128 ? 1600 : 1024;
+        return units >= 128 ? 1600 : G * nqb <= 4 || nqb == 1 ? 832 : 1024;
     }
     if (units > 256) return 0;
-    if (nqb == 2 && G <= 2) return units > 64 ? 800 : 384;
-    if (nqb == 2 && units >= 128) return units >= 192 ? 1600 : 1100;
+    if (G * nqb <= 4) return units >= 96 ? 800 : units >= 64 && nqb == 2 ? 700 : 384;
+    if (nqb == 2 && units >= 64) return units >= 192 ? 1600 : units >= 128 ? 1400 : 900;
     return units >= 192 ? 1100 : units >= 96 ? 800 : 640;
 }
 
@@ -1206,12 +1208,13 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
     if (p.one) kps = ((long)d->S_max + kKT - 1) / kKT * kKT;
     if (kps <= 0) {
         // Number of key ranges: the one that minimises a small cost model, in units of one tile of
-        // one workgroup (measured ~2.7 us): rounds of 256 resident workgroups x (tiles per range +
+        // one workgroup (1.45 us): rounds of 256 resident workgroups x (tiles per range +
         // 3 for prologue and epilogue), plus what the merge of the ranges costs: the launch, and every
         // range's partials written and read again.  Counting whole rounds matters: 576 workgroups take
-        // as long as 768.  The two merge terms were fitted over 29 shapes of 90 ... 16000 rows (0.3 per
-        // range, from when a lane read its partials 4 bytes at a time, cost 5-15 % on most of them: one layer of
-        // 2048 rows 15.4 us with 11 ranges, 14.6 with 17; 8000 rows 22.1 and 20.4).
+        // as long as 768.  What a range costs was fitted over 164 shapes of 700 ... 16000 rows, every number of tiles:
+        // it grows with the bytes of its partials (with 0.08 for any, 1300 rows of 32 heads were cut into 22 ranges of one tile, 15.4 us;
+        // 11 of two take 13.7; 3000 rows 24 of two and 17.6, 16 of three take 16.9).
+        const double per_range = std::max(0.078, 0.045 + 4e-7 * (double)d->B * d->Hq * d->T_max * d->D);
         const long units = (long)d->B * d->Hkv * p.n_ublk;
         const long tiles_all = ((long)d->S_max + kKT - 1) / kKT;
         double best = 1e30;
@@ -1219,7 +1222,7 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
         for (long ns = 1; ns <= 64 && ns <= tiles_all; ++ns) {
             const long tiles = (tiles_all + ns - 1) / ns;
             const long rounds = (units * ns + 255) / 256;
-            const double cost = (double)rounds * (double)(tiles + 3) + (ns > 1 ? 1.2 + 0.08 * (double)ns : 0.0);
+            const double cost = (double)rounds * (double)(tiles + 3) + (ns > 1 ? 1.2 + per_range * (double)ns : 0.0);
             if (cost < best) { best = cost; best_ns = ns; }
         }
         kps = (tiles_all + best_ns - 1) / best_ns * kKT;

@@ -184,8 +184,9 @@ def test_context_lengths_past_the_cache_are_cut_to_it(D, S, kps):
     (128, 0, 1, 1), (128, 0, 2, 64), (64, 0, 1, 33),                       # one row, two; a block of rows past the tree
     (128, 30, 1, 5), (128, 31, 1, 32), (64, 32, 1, 33),                     # 31, 32 and 33 rows: one wavefront or two
     (128, 223, 32, 32), (128, 200, 57, 60), (64, 255, 2, 2),                # 255, 257 and 257 rows: the second step's first
-    (128, 320, 64, 64), (128, 608, 32, 32), (64, 960, 64, 64), (64, 991, 1, 33),   # the most rows that go in one launch
-    (128, 321, 64, 64), (128, 609, 32, 32), (64, 961, 64, 64),              # one row more: ranges
+    (128, 320, 64, 64), (128, 352, 32, 32), (64, 768, 64, 64), (64, 799, 1, 33),   # the most rows that go in one launch
+    (128, 321, 64, 64), (128, 353, 32, 32), (64, 769, 64, 64),              # one row more: ranges
+    (128, 608, 32, 32), (64, 960, 64, 64),
 ])
 def test_one_launch_over_whole_units(oracle, D, ctx, nn, T):
     """Short contexts take one launch in which eight wavefronts share a unit's rows; every count of rows around 32 (one
