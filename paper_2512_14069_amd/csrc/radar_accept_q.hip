@@ -476,6 +476,12 @@ __global__ __launch_bounds__(kAqLone) void accept_q_walk_kernel(AqArgs a) {
 // ahead, the rows that will be asked for if that child is accepted.  The ninth wavefront does everything
 // that is said and decided: it merges the wavefronts' results, meets the other workgroups and tests the
 // next child.  (It loads no rows: a wavefront's loads return in order, and a poll would wait for them.)
+// While it does, the others take the statistics of the rows one node ahead: an accepted first child's meeting
+// begins with the decision.  (Taken after it, a node cost 3.6 us where it costs 2.6 now; in a call of one sequence,
+// V = 128256, a meeting's words are 1.1 us on their way, merging them and deciding takes 0.7, rows that are not
+// ahead 0.75 + their load.  Calls of one / four sequences 19.0 / 37.7 -> 17.6 / 37.3 us, on cold rows 26.4 / 31.2 -> 25.4 / 30.3.  Rows too
+// long to be held one ahead gain from the two rows' chains side by side: 32 sequences 65.4 -> 59.3.  Having the last of the
+// eight merge their results at once (18.0 instead of 17.6) and two polls in flight (2 % slower) were taken out again.)
 //
 // Every workgroup takes the same decisions from the same numbers, added in the same order.  At a meeting
 // a workgroup stores two or four 8-byte words, each with the meeting's number in its low byte, and polls
@@ -488,12 +494,14 @@ __global__ __launch_bounds__(kAqLone) void accept_q_walk_kernel(AqArgs a) {
 enum { kCoAccept, kCoReject, kCoBonusP, kCoBonusU, kCoAbort };
 
 struct CoSmem {
-    float wm[2][kAqWaves];       // per wavefront: maximum and sum of exponentials of its part of the target / draft row
-    double wl[2][kAqWaves];
+    // statistics and children's logits: of the node at hand, and of the one that is next if its first child is accepted
+    float wm[2][2][kAqWaves];    // per wavefront: maximum and sum of exponentials of its part of the target / draft row
+    double wl[2][2][kAqWaves];
     double wsum[kAqWaves];       // residual mass of its part
-    float gx[kWave], gq[kWave];  // per child of the current node: target and draft logit of its token
+    float gx[2][kWave], gq[2][kWave];   // per child of the node: target and draft logit of its token
     float pm, pinv_l, qm, qinv_l, W;
-    int cmd, arg;
+    uint64_t order[2];           // command and node of the last two decisions: the next may be taken while one is read
+    int gave_up;
     int owner, take_last, pick, wlast[kAqWaves];
     double before, goal;
     double wtot[2][kCoR][kAqWaves];
@@ -519,7 +527,9 @@ __device__ __forceinline__ float f32_of_word(uint64_t w) { return __uint_as_floa
 // float4 per lane: rows are read from memory as often as they are needed (one read for the statistics, one per
 // rejection), and the residual is kept in the workspace.  What bounds it is one CU's path to memory, some 64 KB/us.
 template <bool VEC4, int R, bool LAPS>
-__global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
+__global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(const int32_t *parents, const int32_t *tokens, const int32_t *q_rows, const int32_t *n_nodes,
+                                                                    const float *target_rows, int T, int V, int D_max, AqArgs a) {
+    a.parents = parents; a.tokens = tokens; a.q_rows = q_rows; a.n_nodes = n_nodes; a.target = target_rows; a.T = T; a.V = V; a.D_max = D_max;
     __shared__ CoLds lds;
     CoSmem &s = lds.s;
     const int tid = threadIdx.x, lane = lane_id(), w = uniform_of(wave_id());
@@ -534,30 +544,6 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
     int32_t *path = a.accept_path + (size_t)b * (a.D_max + 1);
     const float *target = a.target + (size_t)b * a.T * a.V, *draft = a.draft + (size_t)b * a.Tq * a.V;
 
-    // the tree, one node per lane, in every wavefront
-    const bool live = lane < nn;
-    const int nl = min(lane, a.T - 1);
-    int par = a.parents[(size_t)b * a.T + nl], tok = a.tokens[(size_t)b * a.T + nl];
-    int qrow = a.q_rows ? a.q_rows[(size_t)b * a.T + nl] : lane;
-    const float uni = control ? a.uniforms[(size_t)b * (a.T + 1) + min(lane, a.T)] : 0.f;
-    const float uni_bonus = control ? a.uniforms[(size_t)b * (a.T + 1) + a.T] : 0.f;
-    if (!live) { par = -2; tok = -1; qrow = -1; }
-    const bool usable = live && tok >= 0 && tok < a.V && qrow >= 0 && qrow < a.Tq;
-    auto kids_of = [&](int node, int depth) -> uint64_t {
-        return depth < a.D_max ? __ballot(usable && lane > node && par == node) : 0ull;
-    };
-    auto first_of = [](uint64_t m) { return __ffsll((long long)m) - 1; };
-    auto qrow_of = [&](int node) { return (int)readlane_u32((uint32_t)qrow, node); };
-
-    // Outputs are written through (agent-scope stores): should the sequence be redone by another
-    // workgroup, on another die, no older copy of them may linger in this die's L2 to be written back later.
-    if (g == 0) for (int d = tid; d <= a.D_max; d += kAqThreads) store_shared_result(&path[d], d == 0 && nn >= 1 ? 0 : -1);
-    if (nn < 1) {                                         // nobody meets on this path
-        if (g == 0 && tid == 0) { store_shared_result(&a.accept_len[b], 0); store_shared_result(&a.bonus[b], -1); }
-        return;
-    }
-
-    const float it_f = (float)a.inv_t, itd_f = (float)a.inv_td;
     // this lane's tokens: float4 r of a lap covers lo + lap * lap_tokens + (r * 512 + tid) * 4 .. + 3
     // (made anew for every row: the offsets and end-of-row masks of 4 R tokens are not worth keeping through the walk)
     auto first_token = [&](int lap) { int i = lo + lap * lap_tokens + tid * 4; asm volatile("" : "+v"(i)); return i; };
@@ -576,6 +562,34 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
             }
         }
     };
+    constexpr bool kAhead = R <= 2 && !LAPS;              // rows are requested one node ahead (wider slices have no registers left)
+    float nx[kAhead ? R : 1][4], nq[kAhead ? R : 1][4], ngx = 0.f, ngq = 0.f;   // one ahead; its children's logits (wavefront 0)
+    // the tree, one node per lane, in every wavefront
+    const bool live = lane < nn;
+    const int nl = min(lane, a.T - 1);
+    int par = a.parents[(size_t)b * a.T + nl], tok = a.tokens[(size_t)b * a.T + nl];
+    int qrow = a.q_rows ? a.q_rows[(size_t)b * a.T + nl] : lane;
+    const float uni = control ? a.uniforms[(size_t)b * (a.T + 1) + min(lane, a.T)] : 0.f;
+    const float uni_bonus = control ? a.uniforms[(size_t)b * (a.T + 1) + a.T] : 0.f;
+    if constexpr (kAhead) if (!control) load_row(target, nx);     // the root's row does not wait for the tree
+    __builtin_amdgcn_sched_barrier(0);
+    if (!live) { par = -2; tok = -1; qrow = -1; }
+    const bool usable = live && tok >= 0 && tok < a.V && qrow >= 0 && qrow < a.Tq;
+    auto kids_of = [&](int node, int depth) -> uint64_t {
+        return depth < a.D_max ? __ballot(usable && lane > node && par == node) : 0ull;
+    };
+    auto first_of = [](uint64_t m) { return __ffsll((long long)m) - 1; };
+    auto qrow_of = [&](int node) { return (int)readlane_u32((uint32_t)qrow, node); };
+
+    // Outputs are written through (agent-scope stores): should the sequence be redone by another
+    // workgroup, on another die, no older copy of them may linger in this die's L2 to be written back later.
+    if (g == 0) for (int d = tid; d <= a.D_max; d += kAqThreads) store_shared_result(&path[d], d == 0 && nn >= 1 ? 0 : -1);
+    if (nn < 1) {                                         // nobody meets on this path
+        if (g == 0 && tid == 0) { store_shared_result(&a.accept_len[b], 0); store_shared_result(&a.bonus[b], -1); }
+        return;
+    }
+
+    const float it_f = (float)a.inv_t, itd_f = (float)a.inv_td;
     // tokens past the vocabulary (at the end of the last slice only) are -inf from here on: no mass in a row, none in
     // a residual (a residual read back: 0)
     auto settle = [&](float (&x)[R][4], int lap = 0, float none = -INFINITY) {
@@ -605,14 +619,47 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
         *l_out = l;
         return m;
     };
-    auto put_stats = [&](float m, double l, int which) {
+    int at = 0;                                           // which of the two statistics is the current node's
+    auto put_stats = [&](float m, double l, int which, int buf) {
         l = wave_sum_f64(l);
-        if (lane == 0) { s.wm[which][w] = m; s.wl[which][w] = l; }
+        if (lane == 0) { s.wm[buf][which][w] = m; s.wl[buf][which][w] = l; }
     };
-    auto wave_stats = [&](const float (&x)[R][4], double inv, int which) {
+    auto wave_stats = [&](const float (&x)[R][4], double inv, int which, int buf) {
         double l;
         const float m = lane_stats(x, inv, &l);
-        put_stats(m, l, which);
+        put_stats(m, l, which, buf);
+    };
+    // wave_stats of a target row and a draft row, their chains of dependent steps side by side
+    auto both_stats = [&](const float (&x)[R][4], const float (&y)[R][4], int buf) {
+        float mx = -INFINITY, my = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { mx = fmaxf(mx, x[r][j]); my = fmaxf(my, y[r][j]); }
+        mx = wave_max_f32(mx);
+        my = wave_max_f32(my);
+        const float rx = mx > -INFINITY ? mx : 0.f, ry = my > -INFINITY ? my : 0.f;   // (nothing but -inf: a sum of 0)
+        double lx = 0.0, ly = 0.0;
+        if (a.inv_t == 1.0 && a.inv_td == 1.0) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    lx += (double)exp_rel_f32(x[r][j], rx, 1.f);
+                    ly += (double)exp_rel_f32(y[r][j], ry, 1.f);
+                }
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    lx += exp_rel(x[r][j], rx, a.inv_t);
+                    ly += exp_rel(y[r][j], ry, a.inv_td);
+                }
+        }
+        lx = wave_sum_f64(lx);
+        ly = wave_sum_f64(ly);
+        if (lane == 0) { s.wm[buf][0][w] = mx; s.wl[buf][0][w] = lx; s.wm[buf][1][w] = my; s.wl[buf][1][w] = ly; }
     };
     auto lane_mass = [&](const float (&u)[R][4]) {
         double t = 0.0;
@@ -655,7 +702,7 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
                 l += m1 == m ? l1 : l1 * exp(((double)m1 - (double)m) * inv);
             }
         }
-        put_stats(m, l, which);
+        put_stats(m, l, which, at);
     };
     float *ub = a.ubuf + (size_t)b * a.V;                 // long slices: the residual; a lane reads back what it wrote
     auto store_residual = [&](const float (&u)[R][4], int lap) {
@@ -680,19 +727,33 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
     };
 
     // ---- streaming wavefronts' state
-    constexpr bool kAhead = R <= 2 && !LAPS;              // rows are requested one node ahead (wider slices have no registers left)
     float x[R][4], q[R][4];                               // target row (logits; after a rejection the residual), draft row
     bool q_ready = false;                                 // q holds probabilities (else logits)
-    float nx[kAhead ? R : 1][4], nq[kAhead ? R : 1][4], ngx = 0.f, ngq = 0.f;   // one ahead; its children's logits (wavefront 0)
-    auto look_ahead = [&](int node, int depth) {
+    auto look_ahead = [&](int node, int depth) -> uint64_t {
         const uint64_t k = kids_of(node, depth);
         if constexpr (kAhead) {
-            load_row(target + (size_t)node * a.V, nx);
+            if (depth > 0) load_row(target + (size_t)node * a.V, nx);
             if (k != 0) load_row(draft + (size_t)qrow_of(first_of(k)) * a.V, nq);
         }
         if (w == 0 && ((k >> lane) & 1)) {
             ngx = target[(size_t)node * a.V + tok];
             ngq = draft[(size_t)qrow * a.V + tok];
+        }
+        return k;
+    };
+    auto put_logits = [&](int buf) { if (w == 0) { s.gx[buf][lane] = ngx; s.gq[buf][lane] = ngq; } };
+    // Statistics of the rows that were requested one node ahead, taken while the control wavefront meets the others about
+    // the node at hand: if the child is accepted its meeting begins at once (k: its children).
+    auto stage = [&](uint64_t k, int buf) {
+        if constexpr (kAhead) {
+            settle(nx);
+            if (k != 0) {
+                settle(nq);
+                both_stats(nx, nq, buf);
+            } else {
+                wave_stats(nx, a.inv_t, 0, buf);
+            }
+            put_logits(buf);
         }
     };
     unsigned int meetings = 0;                            // so far
@@ -719,7 +780,8 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
 
     // Maximum and sum of exponentials over the eight wavefronts (lanes 0-7 the target row's, 32-39 the draft
     // row's), then over the workgroups (lane, lane - 32 = workgroup).  m: -inf where a lane has none.
-    auto half_merge = [&](float m, double l, double inv, float *mo, double *lo_) {
+    // at_max(Mp, Mq) runs once the maxima are known, beside the sums.
+    auto half_merge = [&](float m, double l, double inv, auto &&at_max, float *mo, double *lo_) {
         float M = m;
         M = fmaxf(M, dpp_f32<0xB1>(M));
         M = fmaxf(M, dpp_f32<0x4E>(M));
@@ -727,6 +789,7 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
         M = fmaxf(M, dpp_f32<0x140>(M));                  // every lane: the maximum of its 16-lane row
         const float Mp = fmaxf(readlane_f32(M, 0), readlane_f32(M, 16)), Mq = fmaxf(readlane_f32(M, 32), readlane_f32(M, 48));
         M = lane < 32 ? Mp : Mq;
+        at_max(Mp, Mq);
         double t = m > -INFINITY ? l * exp(((double)m - (double)M) * inv) : 0.0;
         auto add = [](double v, uint64_t moved) { return v + __longlong_as_double((long long)moved); };
         t = add(t, dpp_u64<0xB1>((uint64_t)__double_as_longlong(t)));
@@ -746,11 +809,11 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
         if (with_p || with_q) {
             const int which = lane >> 5, i = lane & 31;
             const bool has = i < kAqWaves && (which ? with_q : with_p);
-            const float m0 = s.wm[which][i & (kAqWaves - 1)];
-            const double l0 = s.wl[which][i & (kAqWaves - 1)];
+            const float m0 = s.wm[at][which][i & (kAqWaves - 1)];
+            const double l0 = s.wl[at][which][i & (kAqWaves - 1)];
             float m;
             double l;
-            half_merge(has ? m0 : -INFINITY, has ? l0 : 0.0, inv_half, &m, &l);
+            half_merge(has ? m0 : -INFINITY, has ? l0 : 0.0, inv_half, [](float, float) {}, &m, &l);
             if (i == 0 && (which ? with_q : with_p)) {
                 store_shared_result(&mine[2 * which], word_of_f64(l, tag));
                 store_shared_result(&mine[2 * which + 1], word_of_rest(l, m, tag));
@@ -765,33 +828,46 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
                 store_shared_result(&mine[1], word_of_rest(t, 0.f, tag));
             }
         }
+        const float gx = s.gx[at][lane], gq = s.gq[at][lane];
         int from = lane & 31;
         const int which = lane >> 5;
         asm volatile("" : "+v"(from));                    // addresses made here and not kept through the walk
         const uint64_t *theirs = words + ((size_t)set * kCoG + min(from, G - 1)) * kCoWords + 2 * which;
         const bool has_theirs = from < G && (which ? with_q : (with_p || with_u));
         const bool sib = (rest >> lane) & 1;
-        uint64_t a0, a1, as;
+        struct Poll { uint64_t a0, a1, as; unsigned int given_up; };
+        auto look = [&](Poll &p) {
+            p.a0 = load_shared_result(&theirs[0]);
+            p.a1 = load_shared_result(&theirs[1]);
+            p.as = load_shared_result(&sibs[set * kWave + lane]);
+            p.given_up = load_shared_result(&ctl[16]);
+        };
+        auto there = [&](const Poll &p) {
+            const bool ok = (!has_theirs || ((p.a0 & 0xff) == tag && (p.a1 & 0xff) == tag)) && (!sib || (p.as & 0xff) == tag);
+            return __ballot(!ok) == 0;
+        };
+        Poll p;
         for (unsigned int spins = 0;;) {
-            a0 = load_shared_result(&theirs[0]);
-            a1 = load_shared_result(&theirs[1]);
-            as = load_shared_result(&sibs[set * kWave + lane]);
-            const unsigned int given_up = load_shared_result(&ctl[16]);
-            const bool ok = (!has_theirs || ((a0 & 0xff) == tag && (a1 & 0xff) == tag)) && (!sib || (as & 0xff) == tag);
-            if (__ballot(!ok) == 0) break;
-            if (++spins > a.co_spin_limit || given_up != 0u) {
+            look(p);
+            if (there(p)) break;
+            if (++spins > a.co_spin_limit || p.given_up != 0u) {
                 if (lane == 0) store_shared_result(&ctl[16], 1u);
                 return false;
             }
             __builtin_amdgcn_s_sleep(1);
         }
+        const uint64_t a0 = p.a0, a1 = p.a1, as = p.as;
         if (with_p || with_q) {
             float m;
             double l;
             const bool row = from < G && (which ? with_q : with_p);
-            half_merge(row ? f32_of_word(a1) : -INFINITY, row ? f64_of_words(a0, a1) : 0.0, inv_half, &m, &l);
-            if (with_p) { pm = readlane_f32(m, 0); pl = readlane_f64(l, 0); }
-            if (with_q) { qm = readlane_f32(m, 32); ql = readlane_f64(l, 32); }
+            double ex = 0.0, eq = 0.0;                    // this child's numerators
+            half_merge(row ? f32_of_word(a1) : -INFINITY, row ? f64_of_words(a0, a1) : 0.0, inv_half, [&](float Mp, float Mq) {
+                ex = exp_rel(gx, Mp, a.inv_t);
+                eq = exp_rel(gq, Mq, a.inv_td);
+            }, &m, &l);
+            if (with_p) { pm = readlane_f32(m, 0); pl = readlane_f64(l, 0); px = ex * (1.0 / pl); }
+            if (with_q) { qm = readlane_f32(m, 32); ql = readlane_f64(l, 32); qx = eq / ql; }
         }
         if (with_u) {
             psum = lane < G ? f64_of_words(a0, a1) : 0.0;
@@ -800,48 +876,54 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
         if (sib) px = (double)f32_of_word(as);
         return true;
     };
-    // Eq. 1 for the next child (qx: used at the child's lane).  What a meeting about rows has changed is passed on
+    // Eq. 1 for the next child (px, qx: used at the child's lane).  What a meeting about rows has changed is passed on
     // to the streaming wavefronts.
     auto decide = [&](uint64_t kids, bool was_rejected, bool new_p, bool new_q) {
         int cmd = was_rejected && W > 0.0 ? kCoBonusU : kCoBonusP, arg = -1;
-        if (new_q) qx = exp_rel(s.gq[lane], qm, a.inv_td) / ql;
         if (kids != 0 && W > 0.0) {
             arg = first_of(kids);
             const uint64_t yes = __ballot((double)uni * W * qx < px);
             cmd = (yes >> arg) & 1 ? kCoAccept : kCoReject;
         }
         if (lane == 0) {
-            s.cmd = cmd; s.arg = arg; s.W = (float)W;
+            s.order[meetings & 1] = (uint64_t)(uint32_t)arg << 32 | (uint32_t)cmd;
+            s.W = (float)W;
             if (new_p) { s.pm = pm; s.pinv_l = (float)(1.0 / pl); }
             if (new_q) { s.qm = qm; s.qinv_l = (float)(1.0 / ql); }
         }
     };
-    auto give_up = [&]() { if (lane == 0) s.cmd = kCoAbort; };
+    auto give_up = [&]() { if (lane == 0) { s.order[meetings & 1] = kCoAbort; s.gave_up = 1; } };
+    int cur = 0, len = 0, cmd = kCoAbort, arg = 0;
+    // The decision of the last meeting, after the barrier that follows it.  What a decision leaves in LDS beside this is read before
+    // a barrier that the control wavefront passes before its next decision, but nothing holds that one back after an acceptance.
+    auto read_order = [&]() {
+        const uint64_t o = s.order[(meetings - 1) & 1];
+        cmd = uniform_of((int)(uint32_t)o);
+        arg = uniform_of((int)(uint32_t)(o >> 32));
+    };
 
     // The control wavefront and the streaming ones run loops of their own with the same barriers, command by
     // command: the registers of a row and the state of the tests are never held by the same code.  (In one loop, with
     // a row's addresses and end-of-row masks kept through the walk as well, eight float4 per lane spilled 69 registers,
     // 154 without 16-byte loads: 24 sequences of V = 128256 70 us and now 54, 20 of 128257 110 and 72.)
-    int cur = 0, len = 0, cmd;
     bool rejected = false;
+    if (tid == 0) s.gave_up = 0;
     if (control) {
         for (;;) {                                        // one iteration per visited node
             uint64_t kids = kids_of(cur, len);
             rejected = false;
-            __syncthreads();
+            if (!kAhead || len == 0) __syncthreads();
             if (meet(true, kids != 0, false, 0)) {
                 W = 1.0;
-                px = exp_rel(s.gx[lane], pm, a.inv_t) * (1.0 / pl);
                 decide(kids, false, true, kids != 0);
             } else {
                 give_up();
             }
             ++meetings;
             __syncthreads();
-            while ((cmd = uniform_of(s.cmd)) == kCoReject) {
-                const int c = uniform_of(s.arg);
-                kids &= ~(1ull << c);
-                const bool other_q = kids != 0 && qrow_of(first_of(kids)) != qrow_of(c);
+            for (read_order(); cmd == kCoReject; read_order()) {
+                kids &= ~(1ull << arg);
+                const bool other_q = kids != 0 && qrow_of(first_of(kids)) != qrow_of(arg);
                 rejected = true;
                 __syncthreads();
                 if (meet(false, other_q, true, kids)) decide(kids, true, false, other_q);
@@ -850,44 +932,49 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
                 __syncthreads();
             }
             if (cmd != kCoAccept) break;
-            cur = uniform_of(s.arg);
+            cur = arg;
             ++len;
+            at ^= 1;
         }
     } else {
-        look_ahead(0, 0);
+        const uint64_t k0 = look_ahead(0, 0);
+        stage(k0, 0);
         for (;;) {
             uint64_t kids = kids_of(cur, len);
             rejected = false;
             const float *prow = target + (size_t)cur * a.V;
-            if (w == 0) { s.gx[lane] = ngx; s.gq[lane] = ngq; }
-            if constexpr (LAPS) {
-                long_stats(prow, a.inv_t, 0);
-                if (kids != 0) long_stats(draft + (size_t)qrow_of(first_of(kids)) * a.V, a.inv_td, 1);
+            if constexpr (kAhead) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) { x[r][j] = nx[r][j]; q[r][j] = nq[r][j]; }
+                q_ready = false;
+                if (len == 0) __syncthreads();
             } else {
-                if constexpr (kAhead) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) { x[r][j] = nx[r][j]; q[r][j] = nq[r][j]; }
+                put_logits(at);
+                if constexpr (LAPS) {
+                    long_stats(prow, a.inv_t, 0);
+                    if (kids != 0) long_stats(draft + (size_t)qrow_of(first_of(kids)) * a.V, a.inv_td, 1);
                 } else {
                     load_row(prow, x);
                     if (kids != 0) load_row(draft + (size_t)qrow_of(first_of(kids)) * a.V, q);
+                    q_ready = false;
+                    settle(x);
+                    if (kids != 0) {
+                        settle(q);
+                        both_stats(x, q, at);
+                    } else {
+                        wave_stats(x, a.inv_t, 0, at);
+                    }
                 }
-                q_ready = false;
-                settle(x);
-                wave_stats(x, a.inv_t, 0);
-                if (kids != 0) {
-                    settle(q);
-                    wave_stats(q, a.inv_td, 1);
-                }
+                __syncthreads();
             }
-            __syncthreads();
-            if (kids != 0) look_ahead(first_of(kids), len + 1);
+            if (kids != 0) stage(look_ahead(first_of(kids), len + 1), at ^ 1);
             ++meetings;
             __syncthreads();
-            while ((cmd = uniform_of(s.cmd)) == kCoReject) {
+            for (read_order(); cmd == kCoReject; read_order()) {
                 // Eq. 2, then the next child (whose draft row may be another one)
-                const int c = uniform_of(s.arg);
+                const int c = arg;
                 kids &= ~(1ull << c);
                 const int next = kids != 0 ? first_of(kids) : -1;
                 const bool other_q = next >= 0 && qrow_of(next) != qrow_of(c);
@@ -916,17 +1003,18 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
                     if (other_q) load_row(draft + (size_t)qrow_of(next) * a.V, q);
                     publish(x, kids, 0);
                     put_mass(lane_mass(x));
-                    if (other_q) { settle(q); wave_stats(q, a.inv_td, 1); }
+                    if (other_q) { settle(q); wave_stats(q, a.inv_td, 1, at); }
                 }
                 rejected = true;
                 __syncthreads();
-                if (next >= 0) look_ahead(next, len + 1);
+                if (next >= 0) stage(look_ahead(next, len + 1), at ^ 1);
                 ++meetings;
                 __syncthreads();
             }
             if (cmd != kCoAccept) break;
-            cur = uniform_of(s.arg);
+            cur = arg;
             ++len;
+            at ^= 1;
             if (g == 0 && tid == 0) store_shared_result(&path[len], cur);
         }
     }
@@ -967,7 +1055,7 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(AqArgs a) {
             if (lane == max(owner, 0)) s.before = before;
         }
         __syncthreads();
-        if (s.cmd != kCoAbort && g == s.owner) {
+        if (s.gave_up == 0 && g == s.owner) {
             // token order inside the slice: lap, float4 row r, then thread, then element
             double run = s.before;
             int lastp = -1;
@@ -1176,8 +1264,10 @@ extern "C" radar_status radar_verify_accept_q(const float *target_logits, const 
         auto go = [&](auto r, auto laps) {
             constexpr int RR = decltype(r)::value;
             constexpr bool LL = decltype(laps)::value;
-            return vec4 ? launch("accept_q_walk_shared", accept_q_coop_kernel<true, RR, LL>, grid, block, 0, st, a)
-                        : launch("accept_q_walk_shared", accept_q_coop_kernel<false, RR, LL>, grid, block, 0, st, a);
+            return vec4 ? launch("accept_q_walk_shared", accept_q_coop_kernel<true, RR, LL>, grid, block, 0, st, a.parents, a.tokens, a.q_rows,
+                                 a.n_nodes, a.target, a.T, a.V, a.D_max, a)
+                        : launch("accept_q_walk_shared", accept_q_coop_kernel<false, RR, LL>, grid, block, 0, st, a.parents, a.tokens, a.q_rows,
+                                 a.n_nodes, a.target, a.T, a.V, a.D_max, a);
         };
         using std::integral_constant;
         using std::false_type;

@@ -102,6 +102,19 @@ def test_batches_that_leave_few_workgroups_per_sequence(oracle, V, B):
     compare(ref, got)
 
 
+@pytest.mark.parametrize("V", [2052, 65536, 65540, 131071])      # slices of one and two float4 per lane, their longest, and scalar loads
+@pytest.mark.parametrize("noise", [0.3, 1.5])
+def test_runs_of_acceptances_and_rejections(oracle, V, noise):
+    """The statistics of the rows that an accepted first child needs are taken before the decision: chains and bushy
+    trees in which acceptances follow each other, and rejections come between (another child's rows then take that place)."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(synth.seed_for(32, V % 1000 + int(noise * 10)))
+    par = [synth.chain_tree(12) if i % 2 else synth.make_tree(rng, 12, 4, 3, V)[0] for i in range(4)]
+    x = synth.sampled_draft_inputs(rng, par, V, 12, std=2.0, noise=noise, shared_rows=V % 2 == 0)
+    ref, got = run_both(oracle, b, x, temperature=0.7 if V == 65540 else 1.0)
+    compare(ref, got)
+
+
 @pytest.mark.parametrize("V,B", [(1048576, 2), (600001, 3), (128256, 45), (40001, 110)])
 def test_slices_too_long_for_registers(oracle, V, B):
     """Rows walked over in laps, with the residual in the workspace: the largest vocabulary, two to four workgroups per
