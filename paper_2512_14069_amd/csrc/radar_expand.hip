@@ -611,7 +611,6 @@ constexpr int kRerankStaged = 4 * kTopkThreads;       // pools up to this size a
 struct RerankSmem {
     TopkSmem topk;
     int16_t node_of[RADAR_POOL_MAX];     // pool index -> node number, -1 if dropped
-    int32_t parent[RADAR_T_MAX];
     // small pools: tokens, parents and scores ride along with the first loads, so that the kept
     // entries are read from LDS instead of a second round trip to memory
     int32_t tok[kRerankStaged], par[kRerankStaged];
@@ -619,7 +618,10 @@ struct RerankSmem {
 };
 
 template <int EPT>                       // pool entries per lane: 4 (pools up to 1024) or 16
-__global__ __launch_bounds__(kTopkThreads) void rerank_kernel(RerankArgs a) {
+__global__ __launch_bounds__(kTopkThreads) void rerank_kernel(const float *pool_scores, const int32_t *pool_tokens, const int32_t *pool_parents,
+                                                              const radar_cycle_state *cycle, int pool_count, int N, int pool_capacity, int root_token, RerankArgs a) {
+    a.pool_scores = pool_scores; a.pool_tokens = pool_tokens; a.pool_parents = pool_parents; a.cycle = cycle;
+    a.pool_count = pool_count; a.N = N; a.pool_capacity = pool_capacity; a.root_token = root_token;
     __shared__ RerankSmem s;
     const int tid = threadIdx.x;
     if (blockIdx.x != 0) {                               // sequence b of a batched call: every array has a leading batch dimension
@@ -630,33 +632,29 @@ __global__ __launch_bounds__(kTopkThreads) void rerank_kernel(RerankArgs a) {
         a.n_nodes_out += b;
         if (a.cycle) a.cycle += b;
     }
-    if (a.root_tokens) a.root_token = a.root_tokens[blockIdx.x];
-    if (a.cycle) a.pool_count = min(max(a.cycle->pool_count, 0), a.pool_count);
-    const int keep = min(a.N, a.pool_count);
-
+    // All loads first, one round trip.  A cycle's own count comes with them where the pool is known to reach to the
+    // host's (a batched call's capacity), else before them: the host's count only bounds the state's then.
+    const bool late_count = a.cycle != nullptr && a.pool_capacity > 0;
+    if (a.cycle && !late_count) a.pool_count = min(max(a.cycle->pool_count, 0), a.pool_count);
     constexpr bool kStaged = EPT * kTopkThreads <= kRerankStaged;
     uint64_t keys[EPT];
-    if constexpr (kStaged) {
-        float sc[EPT];
-        int tk[EPT], pr[EPT];
+    float sc0[EPT];
+    int tk[EPT], pr[EPT];
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) {                      // all loads first: one round trip
-            const int i = max(0, min(tid + e * kTopkThreads, a.pool_count - 1));
-            sc[e] = a.pool_scores[i]; tk[e] = a.pool_tokens[i]; pr[e] = a.pool_parents[i];
-        }
+    for (int e = 0; e < EPT; ++e) {
+        const int i = max(0, min(tid + e * kTopkThreads, a.pool_count - 1));
+        sc0[e] = a.pool_scores[i];
+        if constexpr (kStaged) { tk[e] = a.pool_tokens[i]; pr[e] = a.pool_parents[i]; }
+    }
+    if (a.root_tokens) a.root_token = a.root_tokens[blockIdx.x];
+    if (late_count) a.pool_count = min(max(a.cycle->pool_count, 0), a.pool_count);
+    const int keep = min(a.N, a.pool_count);
+    asm volatile("" :: "s"(a.tree_tokens), "s"(a.n_nodes_out));
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const int i = tid + e * kTopkThreads;
-            keys[e] = (i < a.pool_count) ? make_key(sc[e], uint32_t(i)) : 0;
-            s.sc[i] = sc[e]; s.tok[i] = tk[e]; s.par[i] = pr[e];
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const int i = tid + e * kTopkThreads;
-            const float sc = a.pool_scores[max(0, min(i, a.pool_count - 1))];
-            keys[e] = (i < a.pool_count) ? make_key(sc, uint32_t(i)) : 0;
-        }
+    for (int e = 0; e < EPT; ++e) {
+        const int i = tid + e * kTopkThreads;
+        keys[e] = (i < a.pool_count) ? make_key(sc0[e], uint32_t(i)) : 0;
+        if constexpr (kStaged) { s.sc[i] = sc0[e]; s.tok[i] = tk[e]; s.par[i] = pr[e]; }
     }
     for (int i = tid; i < a.pool_count; i += kTopkThreads) s.node_of[i] = -1;
     if (keep > 0) block_topk<EPT>(keys, keep, s.topk);
@@ -670,39 +668,36 @@ __global__ __launch_bounds__(kTopkThreads) void rerank_kernel(RerankArgs a) {
         s.node_of[my_pool] = (int16_t)tid;
     }
     __syncthreads();
+    if (tid >= kWave) return;                            // the tree has at most 64 nodes: one per lane of one wavefront
+    int tok = -1, par = -1, pidx = -1;
+    float sc = 0.f;
+    if (tid == 0) { tok = a.root_token; }
+    else if (tid <= keep) {
+        tok = kStaged ? s.tok[my_pool] : a.pool_tokens[my_pool];
+        sc = kStaged ? s.sc[my_pool] : a.pool_scores[my_pool];
+        pidx = my_pool;
+        const int pp = kStaged ? s.par[my_pool] : a.pool_parents[my_pool];
+        if (pp < 0) par = 0;
+        else if (pp < a.pool_count && s.node_of[pp] >= 0 && s.node_of[pp] < tid) par = s.node_of[pp];
+        else par = -2;
+    }
+    // Depths by doubling: an ancestor's distance to its own ancestor is added until all have reached the root, or a
+    // node without a parent in the tree (which has depth 0, and so have all below it).
+    int up = par >= 0 ? par : tid, depth = par >= 0 ? 1 : 0, lost = par == -2 ? 1 : 0;
+    for (int r = 1; r < RADAR_T_MAX; r *= 2) {
+        const int there = __shfl(up | depth << 8 | lost << 16, up);
+        const bool moved = (there & 0xff) != up;
+        depth += there >> 8 & 0xff;
+        lost |= there >> 16;
+        up = there & 0xff;
+        if (__ballot(moved) == 0) break;
+    }
     if (tid <= a.N) {
-        int tok = -1, par = -1, pidx = -1;
-        float sc = 0.f;
-        if (tid == 0) { tok = a.root_token; }
-        else if (tid <= keep) {
-            tok = kStaged ? s.tok[my_pool] : a.pool_tokens[my_pool];
-            sc = kStaged ? s.sc[my_pool] : a.pool_scores[my_pool];
-            pidx = my_pool;
-            const int pp = kStaged ? s.par[my_pool] : a.pool_parents[my_pool];
-            if (pp < 0) par = 0;
-            else if (pp < a.pool_count && s.node_of[pp] >= 0 && s.node_of[pp] < tid) par = s.node_of[pp];
-            else par = -2;
-        }
-        s.parent[tid] = par;
         a.tree_tokens[tid] = tok;
         a.tree_parents[tid] = par;
         a.tree_scores[tid] = sc;
         a.tree_pool_idx[tid] = pidx;
-    }
-    __syncthreads();
-    if (tid <= a.N) {
-        int depth = 0;
-        if (tid >= 1 && tid <= keep && s.parent[tid] >= 0) {
-            int cur = tid;
-            // parents are strictly smaller node numbers, so this ends within tid steps
-            while (cur > 0 && depth < RADAR_T_MAX) {
-                const int p = s.parent[cur];
-                if (p < 0 || p >= cur) { depth = 0; break; }
-                cur = p;
-                ++depth;
-            }
-        }
-        a.tree_depth[tid] = depth;
+        a.tree_depth[tid] = lost ? 0 : depth;
     }
     if (tid == 0) *a.n_nodes_out = 1 + keep;
 }
@@ -1241,9 +1236,13 @@ static radar_status launch_rerank(const int32_t *pool_tokens, const float *pool_
     a.pool_count = pool_count; a.N = N; a.root_token = root_token; a.cycle = cycle;
     a.tree_tokens = tree_tokens; a.tree_parents = tree_parents; a.tree_scores = tree_scores;
     a.tree_depth = tree_depth; a.tree_pool_idx = tree_pool_idx; a.n_nodes_out = n_nodes_out;
+    auto go = [&](auto kernel) {
+        return launch("rerank", kernel, dim3((unsigned)B), dim3(kTopkThreads), 0, static_cast<hipStream_t>(stream), a.pool_scores, a.pool_tokens,
+                      a.pool_parents, a.cycle, a.pool_count, a.N, a.pool_capacity, a.root_token, a);
+    };
     const hipError_t e = pool_count <= 4 * kTopkThreads
-        ? launch("rerank", rerank_kernel<4>, dim3((unsigned)B), dim3(kTopkThreads), 0, static_cast<hipStream_t>(stream), a)
-        : launch("rerank", rerank_kernel<16>, dim3((unsigned)B), dim3(kTopkThreads), 0, static_cast<hipStream_t>(stream), a);
+        ? go(rerank_kernel<4>)
+        : go(rerank_kernel<16>);
     return e == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
 }
 

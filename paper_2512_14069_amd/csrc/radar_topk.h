@@ -21,40 +21,50 @@ constexpr int kTopkMaxK = 64;
 constexpr int kTopkMaxEPT = 16;
 
 struct TopkSmem {
-    uint64_t surv[kTopkThreads * kTopkMaxEPT + 8];    // compacted survivors (+8: grouped reads past the end)
+    alignas(16) uint64_t surv[kTopkThreads * kTopkMaxEPT + 32];   // compacted survivors (+32: grouped reads past the end)
     uint64_t top[kTopkMaxK];                          // result, best first; 0 where fewer than K exist
-    uint32_t lmax[kTopkThreads];                      // largest value of each lane
+    alignas(16) uint32_t lmax[kTopkThreads / 2 + 4];  // largest value of each pair of lanes, a gap between the halves
     uint32_t tau;
     int count;                                        // number of survivors
 };
+constexpr int kTopkCleared = 512;                     // survivors' slots that are cleared beforehand
 
-// Workgroup version, 256 lanes, 1 <= K <= 64, EPT <= 16 keys per lane.  tau = the K-th largest
-// of the 256 lane maxima (each lane ranks its maximum against all of them).  keys[e] == 0 marks
-// an absent element.  All 256 threads must call this (it synchronises the workgroup).  On
+// Workgroup version, 256 lanes, 1 <= K <= 64, EPT <= 16 keys per lane.  tau = the K-th largest of the 128 maxima of
+// pairs of lanes; the two lanes of a pair count half of the others each, and so they do when the survivors (about
+// 1.4 K) are ranked.  (256 lane maxima leave fewer survivors, 1.15 K, but ranking them is 2000 cycles of comparisons
+// where this is 500: a rerank of 710 candidates 5.6 us and now, with the arguments in registers at the start and depths by
+// doubling, 4.0; 4096 candidates 8.2 and 5.4.)  keys[e] == 0 marks an absent element.  All 256 threads must call this (it synchronises the workgroup).  On
 // return s.top[0..K) is valid for every thread.
 template <int EPT>
 __device__ __forceinline__ void block_topk(const uint64_t (&keys)[EPT], int K, TopkSmem &s) {
     const int tid = threadIdx.x, lane = lane_id();
+    constexpr int kPairs = kTopkThreads / 2, kHalf = kPairs / 2;
 
     uint32_t tmax = 0;
 #pragma unroll
     for (int e = 0; e < EPT; ++e) tmax = max(tmax, uint32_t(keys[e] >> 32));
-    s.lmax[tid] = tmax;
+    tmax = max(tmax, dpp_u32<0xB1>(tmax));
+    const int pair = tid >> 1, half = tid & 1;
+    if (half == 0) s.lmax[pair < kHalf ? pair : pair + 4] = tmax;
     if (tid == 0) { s.count = 0; s.tau = 0xffffffffu; }
     if (tid < kTopkMaxK) s.top[tid] = 0;
+    for (int i = tid; i < kTopkCleared; i += kTopkThreads) s.surv[i] = 0;
     __syncthreads();
 
-    // ---- tau: smallest lane maximum that fewer than K lane maxima exceed
+    // ---- tau: smallest pair maximum that fewer than K pair maxima exceed
     {
-        int larger = 0;
-        for (int j = 0; j < kTopkThreads; j += 16) {              // broadcast reads, 16 values in flight
+        const uint32_t *const theirs = s.lmax + half * (kHalf + 4);
+        uint32_t larger = 0;
+#pragma unroll
+        for (int j = 0; j < kHalf; j += 16) {                     // broadcast reads, 16 values in flight
             uint32_t v[16];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = s.lmax[j + u];
+            for (int u = 0; u < 16; ++u) v[u] = theirs[j + u];
 #pragma unroll
             for (int u = 0; u < 16; ++u) larger += (v[u] > tmax) ? 1 : 0;
         }
-        uint32_t c = larger < K ? tmax : 0xffffffffu;
+        larger += dpp_u32<0xB1>(larger);
+        uint32_t c = larger < (uint32_t)K ? tmax : 0xffffffffu;
         c = min(c, dpp_u32<0xB1>(c));
         c = min(c, dpp_u32<0x4E>(c));
         c = min(c, dpp_u32<0x141>(c));
@@ -83,21 +93,24 @@ __device__ __forceinline__ void block_topk(const uint64_t (&keys)[EPT], int K, T
     }
     __syncthreads();
     const int n = s.count;
-    if (tid < 8) s.surv[n + tid] = 0;                             // padding for the grouped reads
-    __syncthreads();
+    if (n > kTopkCleared - 32) {                                  // long runs of equal values
+        if (tid < 32) s.surv[n + tid] = 0;                        // padding for the grouped reads
+        __syncthreads();
+    }
 
-    // ---- exact ranks among the n survivors; all lanes read the same LDS words (broadcast)
-    for (int i = tid; i < n; i += kTopkThreads) {
-        const uint64_t key = s.surv[i];
-        int rank = 0;
-        for (int j = 0; j < n; j += 8) {
-            uint64_t kj[8];
+    // ---- exact ranks among the n survivors, two lanes each: every other two of the survivors
+    for (int i = pair; i - pair < n; i += kPairs) {
+        const uint64_t key = s.surv[min(i, n - 1)];
+        uint32_t rank = 0;
+        for (int j = 2 * half; j < n; j += 32) {
+            uint64_t kj[16];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) kj[u] = s.surv[j + u];
+            for (int u = 0; u < 16; ++u) kj[u] = s.surv[j + (u >> 1) * 4 + (u & 1)];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) rank += (kj[u] > key) ? 1 : 0;
+            for (int u = 0; u < 16; ++u) rank += (kj[u] > key) ? 1 : 0;
         }
-        if (rank < K) s.top[rank] = key;
+        rank += dpp_u32<0xB1>(rank);
+        if (half == 0 && i < n && rank < (uint32_t)K) s.top[rank] = key;
     }
     __syncthreads();
 }

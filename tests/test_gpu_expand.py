@@ -175,6 +175,29 @@ def test_rerank_sizes_and_ties(oracle, count, N):
         assert np.array_equal(host(getattr(t, name)), tree[name]), name
 
 
+@pytest.mark.parametrize("count", [1, 127, 128, 129, 480, 481, 512, 1024, 1025, 4096])
+@pytest.mark.parametrize("shape", ["equal", "two_lanes", "chain"])
+def test_rerank_survivors_and_depths_at_their_edges(oracle, count, shape):
+    """All scores equal (everything survives the threshold: up to 128 are ranked in one pass, up to 480 in slots that are cleared
+    beforehand), the largest scores in one pair of lanes, and a chain as deep as the tree can be."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(count)
+    gp, cp = b.DraftPool(count), np_pool(count)
+    i = np.arange(count)
+    cp["parents"][:] = i - 1 if shape == "chain" else -1 if shape == "two_lanes" else np.where(i < 10, -1, i // 7 - 1)
+    cp["scores"][:] = 0.0 if shape == "equal" else -0.125 * i if shape == "chain" else np.where(i % 256 < 2, -0.5, -1.0 - 0.001 * i)
+    cp["tokens"][:] = rng.integers(0, 1000, count)
+    gp.tokens.copy_(dev(cp["tokens"])); gp.scores.copy_(dev(cp["scores"])); gp.parents.copy_(dev(cp["parents"]))
+    gp.count = count
+    for N in (1, 63):
+        tree = oracle.draft_rerank(cp, count, N, root_token=7)
+        t = b.radar_draft_rerank(gp, N, 7)
+        torch.cuda.synchronize()
+        assert int(host(t.n_nodes)[0]) == tree["n_nodes"]
+        for name in ("tokens", "parents", "depth", "pool_idx", "scores"):
+            assert np.array_equal(host(getattr(t, name)), tree[name]), (name, N)
+
+
 def test_expand_is_deterministic_and_workspace_reusable(oracle):
     from paper_2512_14069_amd import binding as b
     rng = np.random.default_rng(1)
