@@ -1034,7 +1034,8 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
 // of the head dimension): lane = (8 consecutive d, tree row i), rows rounded up to 16, 32 or 64, so that a
 // small tree's rows sit in few wavefronts (four rows, 48 partials: 31 us for the call with 64 lanes per
 // d, 22 with 16).  The time is that of dependent rounds of loads, so a lane asks for NB partials at once, or for
-// as many as there are in steps of four (17 of them in rounds of 8, 8 and 1, which the compiler made five rounds to save
+// as many as there are, two or in steps of four (12 sequences of 64 heads, a head's rows in one or two pieces: 55.0 us for the call with four,
+// 54.3 with two; 17 of them in rounds of 8, 8 and 1, which the compiler made five rounds to save
 // registers: 16.0 us for a call over 2048 rows, 15.0 in one), and weighs them by their common maximum.  Where the rows
 // are dealt out on the device into sixteen shares or more per KV head, two groups
 // of lanes take every other partial and meet in LDS (3 heads of 16000 rows 26.5 -> 24.8 us; with 11 pieces it costs
@@ -1128,7 +1129,8 @@ __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(const
     };
     if (live) {
         const int each = (count + E - 1) / E;
-        if (NB == 4 || each <= 4) take_all(std::integral_constant<int, 4>{});
+        if (each <= 2) take_all(std::integral_constant<int, 2>{});
+        else if (NB == 4 || each <= 4) take_all(std::integral_constant<int, 4>{});
         else if (NB == 8 || each <= 8) take_all(std::integral_constant<int, 8>{});
         else {
             const int rounds = (each + NB - 1) / NB, most = (each + rounds - 1) / rounds;
