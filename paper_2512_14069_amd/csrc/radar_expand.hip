@@ -327,6 +327,12 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
 // let whole chunks through.  Lists longer than 16 slots need no ranking at all, but the last workgroup's loads are
 // slow (from beyond its L2, 37 bytes per ns): 24 slots cost it 0.4 us, records of 32 0.7.
 // The leading arguments are what the stream waits for; they are in registers when the kernel starts (0.25 us).
+//
+// Up to how many workgroups all count on one counter: they wait for each other there, some 10 ns each, but the last one is
+// spared a second counter's round trip (by row first, then the rows).  16 arrivals (one row of V = 128256) 6.9 us by rows,
+// 6.5 on one; 64 (four) 7.0 and 6.6; 80 (ten of 32000) 7.7 and 7.5; 128 7.8 and 7.9; 160 8.4 and 8.8.
+constexpr int kDirectArrivals = 96;
+
 template <bool VEC4, int EPT, int MODE>
 __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *logits, int F, int V, int k, int nchunks, int pool_count,
                                                                 radar_cycle_state *cycle_, uint64_t *part_keys, unsigned int *counters,
@@ -571,17 +577,20 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
             store_shared_result(&a.part_l[pslot], l);
         }
     }
-    unsigned int *row_counter = &a.counters[(1 + f) * kCounterStride];
-    if (publish_then_ticket(row_counter, &s.ticket) != (unsigned int)(a.nchunks - 1)) return;
+    const bool direct = a.F * a.nchunks <= kDirectArrivals;
+    unsigned int *const counter = direct ? &a.counters[0] : &a.counters[(1 + f) * kCounterStride];
+    if (publish_then_ticket(counter, &s.ticket) != (unsigned int)((direct ? a.F : 1) * a.nchunks - 1)) return;
 
     // ---- last chunk of row f: the row is complete; count it.  Only the workgroup that completes
     // the last row goes on (its predecessors' partials were all acknowledged before their tickets).
-    if (tid == 0) {
-        store_shared_result(row_counter, 0u);                      // leave the row counter clean
-        s.ticket2 = __hip_atomic_fetch_add(&a.counters[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!direct) {
+        if (tid == 0) {
+            store_shared_result(counter, 0u);                      // leave the row counter clean
+            s.ticket2 = __hip_atomic_fetch_add(&a.counters[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (s.ticket2 != (unsigned int)(a.F - 1)) return;
     }
-    __syncthreads();
-    if (s.ticket2 != (unsigned int)(a.F - 1)) return;
     if (tid == 0) store_shared_result(&a.counters[0], 0u);
 
     // ================= last workgroup of the call

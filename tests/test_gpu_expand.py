@@ -198,6 +198,20 @@ def test_rerank_survivors_and_depths_at_their_edges(oracle, count, shape):
             assert np.array_equal(host(getattr(t, name)), tree[name]), (name, N)
 
 
+def test_expand_counts_on_one_counter_or_by_rows(oracle):
+    """Up to 96 workgroups count on one counter, more of them by rows: both sides of that line in turn on one
+    workspace, each call starting from what the one before it left."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(96)
+    k, V = 8, 32000                                                # eight chunks per row
+    ws = b.new_workspace(b.radar_draft_expand_workspace_bytes(b.expand_desc(13, V, k, 0, 4096)))
+    for F in (12, 13, 1, 13, 12, 11):
+        logits = synth.expand_logits(rng, F, V, 2.0)
+        gp, cp = b.DraftPool(F * k), np_pool(F * k)
+        run_both_step(oracle, b, logits, (-rng.random(F)).astype(np.float32), np.full(F, -1, np.int32), k, gp, cp, ws=ws)
+        assert int(ws[:4096].view(torch.int32).abs().sum().item()) == 0   # counters left clean
+
+
 def test_expand_is_deterministic_and_workspace_reusable(oracle):
     from paper_2512_14069_amd import binding as b
     rng = np.random.default_rng(1)
