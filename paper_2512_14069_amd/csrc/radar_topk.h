@@ -191,8 +191,10 @@ struct WaveTopkSmem {
     uint64_t top[16];
 };
 
-template <int EPL>
-__device__ __forceinline__ uint64_t wave_topk(const uint64_t (&keys)[EPL], int K, WaveTopkSmem &s) {
+// between() runs once the keys are in LDS and their registers free.
+struct Nothing { __device__ __forceinline__ void operator()() const {} };
+template <int EPL, typename Between = Nothing>
+__device__ __forceinline__ uint64_t wave_topk(const uint64_t (&keys)[EPL], int K, WaveTopkSmem &s, Between &&between = Between()) {
     static_assert(EPL <= kWaveTopkMaxEPL, "scratch too small");
     const int lane = lane_id();
     uint32_t tmax = 0;
@@ -210,6 +212,7 @@ __device__ __forceinline__ uint64_t wave_topk(const uint64_t (&keys)[EPL], int K
     }
     if (lane < 8) s.surv[n + lane] = 0;           // padding for the grouped reads
     if (lane < 16) s.top[lane] = 0;
+    between();
     wave_lds_sync();
     for (int i0 = 0; i0 < n; i0 += kWave) {       // one pass unless nearly everything survived
         const int i = i0 + lane;

@@ -121,7 +121,8 @@ def test_prepared_call_and_argument_errors(oracle):
 
 
 @pytest.mark.parametrize("F,V,k,with_state", [(1, 128256, 10, False), (10, 128256, 10, True), (10, 32000, 10, True),
-                                              (3, 5000, 4, True), (64, 4099, 16, True), (2, 300000, 10, False)])
+                                              (3, 5000, 4, True), (64, 4099, 16, True), (2, 300000, 10, False),
+                                              (16, 20000, 16, True), (17, 8192, 5, True)])   # as many rows as wavefronts, one more
 def test_expansion_with_policy_equals_the_two_calls(oracle, F, V, k, with_state):
     """One launch (expansion, then the model on the confidences still on chip) gives bit for bit what
     radar_draft_expand followed by radar_policy_step gives, and agrees with the oracle chain."""
