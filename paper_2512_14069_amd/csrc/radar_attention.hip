@@ -905,8 +905,8 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(const int32_t 
 // wavefronts 32 rows each in turn, and merges their results in LDS: one launch, no partials in memory.  A
 // wavefront stages its own rows straight into its own part of LDS and waits for nobody until the merge.  The
 // price is that every unit's CU reads all of its KV head's rows: what bounds it is that CU's port, about 1 us per
-// 64 KB, after 5 us of launch and round trips (32 heads, D = 128: 76 rows 5.8 us, 256 rows 8.3, 572 rows 9.9; with ranges
-// and a merge 10.9, 9.9 and 11.7.  One layer of 4 heads with D = 64 over 272 rows 6.0 instead of 7.8).
+// 64 KB, after 5 us of launch and round trips (32 heads, D = 128: 260 rows 8.3 us, 540 rows 9.9; with ranges
+// and a merge 10.7 and 11.2.  One layer of 4 heads with D = 64 over 272 rows 6.0 instead of 7.8).
 constexpr int kOneRows = 32;                             // cache rows of a wavefront's step
 
 template <int D>
