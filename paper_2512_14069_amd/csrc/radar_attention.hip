@@ -98,6 +98,10 @@ __device__ __forceinline__ int vs_swz(int row) { return D == 128 ? (row & 3) << 
 template <int D>
 __device__ __forceinline__ int vs_off(int row, int chunk) { return row * (D * 2) + ((chunk ^ vs_swz<D>(row)) << 4); }
 
+// What loads that write LDS directly read for V rows past the end: a masked row's probability is 0, and 0 * Inf would be NaN.
+// (Clearing the rows in LDS afterwards cost a call over 272 rows 2 %.)
+__device__ __attribute__((aligned(16))) const uint32_t kZeroChunk[4] = {0, 0, 0, 0};
+
 // Rows of the prefix: at most the cache's, so that the tree's rows can be added in 32 bits for any content of
 // ctx_lens (a length near 2^31 would wrap, and the sequence seem empty to one kernel and not to the next).
 // Where the prefix fills the cache nothing is left for the tree, as before.  Negative: no such sequence.
@@ -935,7 +939,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
 
     // This wavefront's rows of a step: K [32][D], then V [32][D], both row-major with their own swizzle (ks_off, vs_off); a
     // lane's 16 bytes land at the load's LDS base + 16 * lane, so it fetches the chunk that belongs there.  Rows past
-    // the end re-read the last one: their scores are masked, and 0 * finite = 0.
+    // the end re-read the last one in K, whose scores are masked, and are zeros in V.
     unsigned char *const mine = smem + w * 2 * SUB;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)mine);
     auto issue = [&](const __bf16 *base, auto is_v, int sub) {
@@ -944,7 +948,9 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
         for (int i = 0; i < LOADS; ++i) {
             const int row = RPL * i + lane / CPR, slot = lane % CPR;
             const int chunk = V ? slot ^ vs_swz<D>(row) : slot ^ ks_swz<D>(row);
-            const __bf16 *src = base + (uint32_t)(min(sub * kOneRows + row, total - 1) * kv_ss) + chunk * 8;
+            const int at = sub * kOneRows + row;
+            const __bf16 *src = base + (uint32_t)(min(at, total - 1) * kv_ss) + chunk * 8;
+            if (V) src = at < total ? src : (const __bf16 *)kZeroChunk;
             const uint32_t dst = lds0 + (V ? SUB : 0) + i * 1024;
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
         }

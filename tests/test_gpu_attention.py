@@ -205,6 +205,23 @@ def test_one_launch_over_whole_units(oracle, D, ctx, nn, T):
         assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)     # unused rows are zeroed
 
 
+@pytest.mark.parametrize("D,ctx,nn,kps", [(128, 30, 3, 0), (128, 224, 33, 0), (128, 256, 1, 0), (64, 256, 16, 0), (64, 700, 60, 0), (128, 256, 32, 0)])
+def test_infinite_values_in_the_last_row(oracle, D, ctx, nn, kps):
+    """The last node's V row holds +Inf and -Inf in two columns: its own output is the infinity there, whatever the count of rows
+    leaves of a tile (rows past the end count for nothing, also as copies of the last one), and every other column is as without them.
+    (The other nodes' products 0 * Inf in the two columns are not defined.)"""
+    from paper_2512_14069_amd import binding as b
+    a = shape(1, 4, 2, D, max(nn, 2), [ctx], [nn], [max(1, min(6, nn - 1))], k=64)
+    x = synth.attention_inputs(a, seed=synth.seed_for(1, ctx + nn), shuffle=True)
+    ref = oracle.tree_attention(x["q"], x["k_cache"], x["v_cache"], x["parents"], x["ctx_lens"], x["n_nodes"])
+    x["v_cache"][0, :, ctx + nn - 1, 5], x["v_cache"][0, :, ctx + nn - 1, D - 3] = 0x7f80, 0xff80
+    x["v_cache"][0, :, ctx + nn:] = 0x7fc0
+    got = run_gpu(b, x, keys_per_split=kps)
+    finite = [d for d in range(D) if d not in (5, D - 3)]
+    check_close(got[0, :nn, :, finite], ref[0, :nn, :, finite], "columns without an infinity")
+    assert np.all(f64(got[0, nn - 1, :, 5]) == np.inf) and np.all(f64(got[0, nn - 1, :, D - 3]) == -np.inf)
+
+
 @pytest.mark.parametrize("parts", [2, 4, 5, 8, 9, 12, 13, 16, 17, 18, 19, 24, 25, 33, 36, 37])
 def test_merge_takes_any_number_of_partials(oracle, parts):
     """The merge asks for up to 18 partials at a time, in steps of four, and for as few rounds as that allows: numbers of
