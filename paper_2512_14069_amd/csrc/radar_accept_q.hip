@@ -373,7 +373,9 @@ __device__ __forceinline__ void walk_single(const AqArgs &a, AqSmem &s, int b) {
             W = 1.0;
             if (w == 0) {
                 const float mc = lane < a.nchunks ? a.part_m[((size_t)b * a.T + cur) * a.nchunks + lane] : -INFINITY;
-                const double mass = mc > -INFINITY ? a.part_l[((size_t)b * a.T + cur) * a.nchunks + lane] * exp(((double)mc - (double)pm) * a.inv_t) * pinv_l : 0.0;
+                // (a chunk counts if its largest probability is above zero in fp32, in which u is made: others have no token to find)
+                const bool any = mc > -INFINITY && exp_rel_f32(mc, pm, (float)a.inv_t) * (float)pinv_l > 0.f;
+                const double mass = any ? a.part_l[((size_t)b * a.T + cur) * a.nchunks + lane] * exp(((double)mc - (double)pm) * a.inv_t) * pinv_l : 0.0;
                 const double incl = wave_scan_f64(mass);
                 const uint64_t cross = __ballot(lane < a.nchunks && incl > (double)s.uni[a.T]), has = __ballot(mass > 0.0);
                 const int ch = cross ? __ffsll((long long)cross) - 1 : has ? 63 - __clzll((long long)has) : 0;

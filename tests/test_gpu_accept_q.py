@@ -204,6 +204,28 @@ def test_sums_pass_between_workgroups_whole(oracle):
         assert host(got[2])[1] == 5, limit
 
 
+@pytest.mark.parametrize("B,V", [(1, 40000), (1, 40002), (1, 1048576), (140, 16388)])
+def test_bonus_of_a_zero_uniform_over_chunks_of_little_mass(B, V):
+    """A uniform of zero takes the first token that has mass in fp32.  Where the statistics are taken beforehand it is looked for
+    chunk by chunk: chunks whose mass fp64 holds and fp32 does not (exp(-105) ... exp(-740) of the maximum) are passed over."""
+    from paper_2512_14069_amd import binding as b
+    gaps = [60.0, 104.5, 110.0, 300.0, 700.0, 800.0]
+    first = 16384 + 3                                            # the first token of the second chunk that has mass
+    x = np.full((len(gaps), 1, V), -2000.0, np.float32)
+    for i, gap in enumerate(gaps):
+        x[i, 0, 7:5000] = -gap
+        x[i, 0, [first, V - 1]] = 0.0
+    y = np.zeros((B, 1, V), np.float32)
+    for i, gap in enumerate(gaps):
+        args = [dev(np.repeat(x[i:i + 1], B, 0)), dev(y), dev(np.zeros((B, 1), np.int32)), dev(np.full((B, 1), -1, np.int32)),
+                dev(np.ones(B, np.int32)), dev(np.zeros((B, 2), np.float32))]
+        want = 7 if gap == 60.0 else first
+        for limit in (0, -1, 1):
+            length, path, bonus = [host(t) for t in b.radar_verify_accept_q(*args, walk_spin_limit=limit)]
+            assert np.all(length == 0) and np.all(path[:, 0] == 0), (gap, limit)
+            assert np.all(bonus == want), (gap, limit, bonus[:4])
+
+
 def test_workspace_reuse_prepared_call_and_errors(oracle):
     from paper_2512_14069_amd import binding as b
     V, T, B = 9000, 12, 5
