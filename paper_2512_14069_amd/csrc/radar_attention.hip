@@ -615,8 +615,7 @@ __device__ __forceinline__ int flat_pair_at(const FlatUnit &u, int pos) {
 // the row the lane fetches), a pair of tiles ahead of the pair being consumed, four tile buffers.  V
 // stays row-major and is transposed by the LDS reads that fetch the operands.  No staging registers,
 // no vector instructions for the transposition, one barrier per pair of tiles.  Rows past the end
-// of a range re-read its last row: their scores are masked, and the row they repeat is a cache row
-// whose values the result depends on anyway (0 * finite = 0).
+// of a range re-read its last row in K, whose scores are masked, and are zeros in V.
 constexpr int kLdBufs = 4;
 // Ranges of so many tiles take it.  At eight the compact one-ahead loop still wins (16 sequences of up to 900
 // rows 20.3 us against 22.0), at nine the long-range kernel (8 of up to 2000 rows 26.6 against 28.6).
@@ -653,7 +652,7 @@ __device__ __forceinline__ LdLane ld_lane_offsets(int kv_ss, int w, int lane) {
 // these loads are the explicit ones in the kernel's loop.  (m0 is a reserved register: the compiler
 // sets it right before each of its own uses and warns about the clobber.)  A tile inside the range
 // takes a scalar base and the lane's fixed offsets, no vector arithmetic; a tile that reaches past the
-// end of the range clamps every row to the range's last one.
+// end of the range clamps every row to the range's last one in K and reads zeros in V.
 template <int D>
 __device__ __forceinline__ void ld_issue_tile(unsigned char *buf, const __bf16 *kbase, const __bf16 *vbase, int kv_ss, int t0,
                                               int kend, int w, int lane, const LdLane &o) {
@@ -678,9 +677,9 @@ __device__ __forceinline__ void ld_issue_tile(unsigned char *buf, const __bf16 *
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int row = 4 * (2 * w + i) + (lane >> 4), slot = lane & 15;
-            const uint32_t rowoff = (uint32_t)(min(t0 + row, kend - 1) * kv_ss);
+            const uint32_t rowoff = (uint32_t)(min(t0 + row, max(kend, 1) - 1) * kv_ss);
             const __bf16 *gk = kbase + rowoff + ((slot ^ (row & 15)) << 3);
-            const __bf16 *gv = vbase + rowoff + ((slot ^ ((row & 3) << 2)) << 3);
+            const __bf16 *gv = t0 + row < kend ? vbase + rowoff + ((slot ^ ((row & 3) << 2)) << 3) : (const __bf16 *)kZeroChunk;
             const uint32_t ldsk = lds0 + i * 1024, ldsv = ldsk + kKT * D * 2;
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(ldsk), "v"(gk) : "memory", "m0");
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(ldsv), "v"(gv) : "memory", "m0");
@@ -767,11 +766,11 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(const int32_t 
     };
     // where the loads are, one pair ahead of the arithmetic
     const __bf16 *kb, *vb;
-    int lt, lt1, lend;                                    // next tile, the piece's end, the row that loads are clamped to
+    int lt, lt1, lend;                                    // next tile, the piece's end, the end of the rows that count
     auto load_from = [&](const Piece &p) {
         const size_t at = (size_t)p.b * a.kv_sb + (size_t)p.hk * a.kv_sh;
         kb = a.k + at; vb = a.v + at;
-        lt = p.t0; lt1 = p.t1; lend = max(p.kend, 1);
+        lt = p.t0; lt1 = p.t1; lend = p.kend;
     };
 
     // the first two tiles are requested before anything else: the query rows below are consumed as soon as

@@ -206,7 +206,8 @@ def test_one_launch_over_whole_units(oracle, D, ctx, nn, T):
 
 
 @pytest.mark.parametrize("D,ctx,nn,kps", [(128, 30, 3, 0), (128, 224, 33, 0), (128, 256, 1, 0), (64, 256, 16, 0), (64, 700, 60, 0), (128, 256, 32, 0),
-                                          (128, 224, 33, 64), (64, 256, 16, 64), (128, 1000, 40, 64), (128, 2000, 17, 64)])
+                                          (128, 224, 33, 64), (64, 256, 16, 64), (128, 1000, 40, 64), (128, 2000, 17, 64),
+                                          (128, 1000, 33, 576), (128, 1000, 33, 1088), (64, 1000, 33, 576), (128, 36000, 33, 0)])
 def test_infinite_values_in_the_last_row(oracle, D, ctx, nn, kps):
     """The last node's V row holds +Inf and -Inf in two columns: its own output is the infinity there, whatever the count of rows
     leaves of a tile (rows past the end count for nothing, also as copies of the last one), and every other column is as without them.
