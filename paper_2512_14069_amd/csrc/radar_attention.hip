@@ -1383,7 +1383,7 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
         if (e != hipSuccess) return RADAR_HIP_ERROR;
     }
     if (a.max_splits > 1 || p.shares > 0) {
-        const bool many = p.shares >= 16l * d->B * d->Hkv;          // sixteen shares per KV head or more (dealt-out rows only)
+        const bool many = p.shares >= 16l * d->B * d->Hkv;          // sixteen shares per KV head or more (dealt-out rows only: D = 128)
         // Many partials at once take registers that a launch of more wavefronts needs to have all of them on the chip: up to 640
         // (40 heads of 60 rows, 160 of 16 rows).  One sequence of 2048 rows: 32 heads 16.0 -> 15.0 us (8 -> 18 partials at
         // a time), 16 tree rows 11.7 -> 10.6, 8 heads on 2 13.7 -> 12.4, D = 64 on 4 10.6 -> 9.5; with 48 or 64 heads
@@ -1394,8 +1394,9 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
             return launch("tree_attn_merge", kernel, mgrid, dim3((unsigned)(kAttnThreads * groups)), 0, s, a.ctx_lens, a.n_nodes, a.part_o, a.part_ml, a.T, a.kps,
                           a.S, a.max_splits, a.shares, a.G, a);
         };
-        const hipError_t e = d->D == 128 ? (wide ? (many ? go(tree_attn_merge_kernel<128, 2, 18>, 2) : go(tree_attn_merge_kernel<128, 1, 18>, 1)) : (many ? go(tree_attn_merge_kernel<128, 2, 4>, 2) : go(tree_attn_merge_kernel<128, 1, 8>, 1)))
-                                         : (wide ? (many ? go(tree_attn_merge_kernel<64, 2, 18>, 2) : go(tree_attn_merge_kernel<64, 1, 18>, 1)) : (many ? go(tree_attn_merge_kernel<64, 2, 4>, 2) : go(tree_attn_merge_kernel<64, 1, 8>, 1)));
+        const hipError_t e = d->D == 64 ? (wide ? go(tree_attn_merge_kernel<64, 1, 18>, 1) : go(tree_attn_merge_kernel<64, 1, 8>, 1))
+                           : many       ? (wide ? go(tree_attn_merge_kernel<128, 2, 18>, 2) : go(tree_attn_merge_kernel<128, 2, 4>, 2))
+                                        : (wide ? go(tree_attn_merge_kernel<128, 1, 18>, 1) : go(tree_attn_merge_kernel<128, 1, 8>, 1));
         if (e != hipSuccess) return RADAR_HIP_ERROR;
     }
     return RADAR_OK;
