@@ -126,13 +126,25 @@ def _ragged(seed, B, hi, T):
 
 DEALT_CASES = {                                   # name: B, Hq, Hkv, T, longest prefix, equal lengths
     "group_of_4": (32, 32, 8, 60, 700, False),                # trees on both sides of one block of 32 rows
-    "one_head_per_kv_head": (64, 4, 4, 20, 640, False),       # one unit
+    "one_head_per_kv_head": (64, 4, 4, 20, 1500, False),      # one unit
     "group_of_8_two_unit_blocks": (16, 64, 8, 64, 900, False),    # small trees: the unit blocks share a piece
     "group_of_12_three_unit_blocks": (21, 48, 4, 40, 520, False),
     "many_pieces_per_head": (2, 4, 2, 33, 36000, False),      # more partials than one batch of the merge
-    "equal_lengths": (5, 16, 8, 40, 3000, True),              # whole pieces
+    "equal_lengths": (5, 16, 8, 40, 4200, True),              # whole pieces, six per head
     "one_sequence": (1, 8, 8, 60, 17000, True),
 }
+
+
+def scratch_bytes(b, B, Hq, Hkv, D, T, S):
+    return b.radar_tree_attention_workspace_bytes(b.attn_desc(torch.empty((B, T, Hq, D), device="meta"), torch.empty((B, Hkv, S, D), device="meta")))
+
+
+def dealt_bytes(B, Hq, Hkv, D, T):
+    """What the workspace of a call whose rows are dealt out holds: a partial per unit for every share and every KV head, and
+    the table for the merge."""
+    blocks = -(-(Hq // Hkv) * (1 if T <= 32 else 2) // 8)
+    entries = (256 // blocks + B * Hkv) * blocks * 8
+    return 256 + sum(-(-n // 256) * 256 for n in (entries * 32 * (D // 2) * 4, entries * 96 * 4, B * Hkv * 8))
 
 
 @pytest.mark.parametrize("name", list(DEALT_CASES))
@@ -144,6 +156,7 @@ def test_rows_dealt_out_on_the_device(oracle, name):
     B, Hq, Hkv, T, hi, equal = DEALT_CASES[name]
     ctx, nodes, depth = ([hi] * B, [T] * B, [8] * B) if equal else _ragged(len(name), B, hi, T)
     a = shape(B, Hq, Hkv, 128, T, ctx, nodes, depth, k=10)
+    assert scratch_bytes(b, B, Hq, Hkv, 128, T, a.S) == dealt_bytes(B, Hq, Hkv, 128, T)
     x = synth.attention_inputs(a, seed=synth.seed_for(1, 11 * len(name)), shuffle=True)
     ref, ref_lse = oracle.tree_attention(x["q"], x["k_cache"], x["v_cache"], x["parents"], x["ctx_lens"],
                                          x["n_nodes"], want_lse=True)
@@ -199,6 +212,31 @@ def test_one_launch_over_whole_units(oracle, D, ctx, nn, T):
                                          x["n_nodes"], want_lse=True)
     got, lse = run_gpu(b, x, want_lse=True)
     for bb in range(2):
+        n = nodes[bb]
+        check_close(got[bb, :n], ref[bb, :n], f"b={bb}")
+        assert np.max(np.abs(lse[bb, :n] - ref_lse[bb, :n])) < LSE_TOL
+        assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)     # unused rows are zeroed
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T,rows", [
+    (1, 32, 8, 64, 513), (1, 32, 8, 60, 900),                               # 64 units: the third step's first row, and the line
+    (2, 32, 8, 64, 769), (1, 64, 8, 64, 1400), (3, 32, 8, 60, 1280),        # 128 and 192 units
+    (4, 32, 8, 40, 1600), (2, 64, 8, 60, 1569), (8, 16, 4, 33, 1025),       # 256 units: seven steps, full and begun
+    (1, 32, 16, 64, 700), (3, 32, 8, 20, 800), (4, 48, 4, 32, 1100), (4, 64, 8, 17, 1057),
+])
+def test_one_launch_of_many_units_and_steps(oracle, B, Hq, Hkv, T, rows):
+    """The longest calls that go in one launch at D = 128: 64 to 256 units, three to seven steps per wavefront, each of which
+    lands where the one before it has been read.  The other sequences are shorter."""
+    from paper_2512_14069_amd import binding as b
+    nodes = [T] + [(T + 1) // 2] * (B - 1)
+    ctx = [rows - T] + [(rows - T) * (i + 1) // (B + 1) for i in range(1, B)]
+    a = shape(B, Hq, Hkv, 128, T, ctx, nodes, [max(1, min(6, n - 1)) for n in nodes], k=64)
+    assert a.S == rows and scratch_bytes(b, B, Hq, Hkv, 128, T, rows) == 256          # no partials
+    x = synth.attention_inputs(a, seed=synth.seed_for(1, rows + Hq), shuffle=True)
+    ref, ref_lse = oracle.tree_attention(x["q"], x["k_cache"], x["v_cache"], x["parents"], x["ctx_lens"],
+                                         x["n_nodes"], want_lse=True)
+    got, lse = run_gpu(b, x, want_lse=True)
+    for bb in range(B):
         n = nodes[bb]
         check_close(got[bb, :n], ref[bb, :n], f"b={bb}")
         assert np.max(np.abs(lse[bb, :n] - ref_lse[bb, :n])) < LSE_TOL
