@@ -26,6 +26,8 @@
 // 8 / 16 sequences 16 ... 31 / 23 ... 43 us for paths of 0 ... 8 nodes, against 70 / 129 us
 // when every row is read; one sequence 11 ... 14 us.  In a large launch the
 // workgroups behind the roots' rows hold back until the roots are decided (below).
+#include <algorithm>
+
 #include "radar_device.h"
 #include "radar_host.h"
 
@@ -42,6 +44,7 @@ constexpr int64_t kAccManyBlocks = 49152;
 constexpr int64_t kAccWalkLast = 3072;  // greedy launches up to this many workgroups leave the walk to the last row
 constexpr int kAccUnchecked = 1024;     // workgroups the chip starts first: nothing is decided yet when they do
 constexpr int kAccPolls = 3;            // how often a waiting workgroup looks (1 us apart)
+constexpr int kAccWaitNodes = 12;       // trees of fewer nodes never wait (launch_accept; 32 of 9, V = 128256, would gain 2 us at the root and lose 1-2 elsewhere)
 constexpr float kAccLog2e = 1.4426950408889634f;
 constexpr unsigned int kAccDone = 1u << 30, kAccReached = 1u << 29;   // marks beside a row's count of arrivals
 constexpr int kAccEnded = RADAR_T_MAX;  // "node arrived at" once the walk has ended
@@ -59,8 +62,8 @@ struct AcceptArgs {
     double *dist;               // mode kAccDistribution: [B][D_max+1]
     int B, T, V, D_max, nwg, nsub;   // nwg workgroups and nsub 1024-logit blocks per row
     int check_from;             // workgroups from this number on ask whether their row can still be on the path
-    int wait;                   // > 0 (units of 10 ns): those of them that start with the launch wait so long for the roots' decisions
-    int wait_until;             // those before this number
+    int wait;                   // (units of 10 ns) those of them that start with the launch wait so long for the roots' decisions:
+    int wait_until, wait_nodes; // those before this number, of trees of so many nodes
     int exact_scale;            // 1/temperature is exactly representable in fp32
     float inv_temp_f;
     double inv_temp;
@@ -175,7 +178,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
     const unsigned int number = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     if (distribution || (!LAST && number >= (unsigned int)a.check_from)) {
         unsigned int at = 0;
-        if (!distribution && (int)number < a.wait_until) {
+        if (!distribution && (int)number < a.wait_until && nn >= a.wait_nodes) {
             // By the clock, not by anything another workgroup does: whatever happens elsewhere, this ends.
             const uint64_t t0 = wall_clock64();
             for (int k = 0; k < kAccPolls && at == 0; ++k) {
@@ -740,16 +743,26 @@ static radar_status launch_accept(const float *target_logits, const int32_t *dra
     accept_layout(d->B, d->T_max, (size_t)nsub, static_cast<char *>(workspace), &a);
     // Large launches: the roots' rows are read first and alone, the workgroups behind them wait for the roots' decisions (the
     // memory's queue is first come, first served: 2048 workgroups that read at once are 64 MB ahead of the roots' results, whose
-    // rows were complete after 9.5 us instead of 6.7).  Greedy 2.5 us, sampled 4.5 (its decisions are later); the chip holds eight
-    // workgroups per CU of the greedy kernel, six of the sampled one, and later ones find the decisions made.
-    // us without / with it, 61 rows of V = 128256 and paths of 0, 2 and 8 nodes: greedy, 4 sequences 13.8 / 11.5, 15.7 / 14.5, 21.0 / 18.2;
-    // 16 sequences 22.2 / 17.5, 25.5 / 23.5, 40.3 / 35.7; sampled, 8 sequences 20 / 15.6, 22.5 / 22.3, 34 / 30.8.  Smaller launches
-    // lose by it (one sequence, sampled, 2 nodes 11.1 / 14.1; two 13.2 / 14.9; greedy, 8 sequences of V = 32000 10.3 / 10.7).
+    // rows were complete after 9.5 us instead of 6.7).  Greedy 2.5 us, sampled 4.5 (its decisions are later).  Those wait that start
+    // with the launch, by their number (rows past the end of a tree count too): eight workgroups per CU of the greedy kernel, six
+    // of the sampled one.  Of the greedy kernel for rows of any length and two blocks the chip holds seven: ending at 1792
+    // there is slower all the same (16 sequences of 61 rows, V = 128257, paths of 0, 2 and 8 nodes 22.1, 34.6, 56.7 us; 21.0, 33.6, 55.3 at 2048).
+    // Looking once before the wait changes nothing (1 %); with every workgroup waiting until the roots are decided V = 1048576 gains
+    // 4-9 % (4 sequences 46.6, 56.1, 96.8 -> 44.8, 52.7, 88.2) and V = 128256 loses as much (16 sequences 17.4, 24.6, 35.3 -> 19.2, 25.6, 35.9).
+    // us without / with the wait, trees of 61 rows, paths of 0, 2 and 8 nodes: greedy, V = 128256, 4 sequences 14.4 / 11.4, 16.6 / 16.3, 21.6 / 19.8;
+    // 16 sequences 23.6 / 17.5, 27.4 / 24.6, 39.6 / 35.0; V = 1048576, 4 sequences 50.3 / 47.7, 59.0 / 56.3, 99 / 96.5; sampled, V = 128256, 8
+    // sequences 20.2 / 15.5, 24.3 / 24.7, 36.2 / 32.3; 16 sequences 27.8 / 23.3, 31.3 / 30.0, 46.2 / 43.8.  Smaller launches lose
+    // by it (one sequence, sampled, 2 nodes 11.1 / 14.1; two 13.2 / 14.9; greedy, 8 sequences of V = 32000 10.3 / 10.7).
+    // So do small trees in a launch that is large by T_max alone, once the path leaves the root (16 trees of 6 nodes, T_max = 64, paths of
+    // 0, 2 and 5 nodes: greedy, V = 32000 6.0 / 7.2, 7.5 / 11.2, 8.0 / 11.6; sampled, V = 128256 14.7 / 10.4, 15.3 / 20.9, 18.1 / 22.5).  Only trees
+    // wait with which the launch would be a large one if all were like them: what is known of the others is not worth reading the
+    // batch's sizes (every workgroup starts later then: 16 x 61 rows 17.5 -> 22.4).  16 trees of 12 nodes, greedy, V = 128256 16.8 / 9.9, 19.9 / 21.2, 20.2 / 21.1.
     const int64_t blocks = (int64_t)d->B * d->T_max * nsub;
     const bool wait = mode == RADAR_ACCEPT_GREEDY ? blocks >= kAccManyBlocks / 2 : mode == RADAR_ACCEPT_SAMPLE && blocks >= kAccManyBlocks;
     a.check_from = wait ? (int)(d->B * nwg) : kAccUnchecked;
     a.wait = mode == RADAR_ACCEPT_GREEDY ? 250 : 450;
     a.wait_until = wait ? (mode == RADAR_ACCEPT_GREEDY ? 2048 : 1536) : 0;
+    a.wait_nodes = (int)std::max<int64_t>(kAccWaitNodes, (mode == RADAR_ACCEPT_GREEDY ? kAccManyBlocks / 2 : kAccManyBlocks) / (d->B * nsub));
     // A greedy walk is shortest at the end of the launch, in registers over all rows' results, as long as the launch
     // is not much more than the chip holds at once (one sequence of 16 rows, V = 32000: 5.6 us against 7.1; two of
     // 61 rows, V = 128256, 3904 workgroups: 13.9 against 13.3).  A sampled one is not: its exponentials and the

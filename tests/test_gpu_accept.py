@@ -211,3 +211,16 @@ def test_walk_carried_from_row_to_row(oracle, mode, B, T, V, chain):
         assert all(np.array_equal(p, q) for p, q in zip(ref, run_gpu(b, x, mode, ws=ws)))
         assert not chain or ref[0].max() == T - 1
     assert counters_are_clean(ws, B, T)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("nodes", [(6,), (11, 12, 13, 24, 25), (1, 64, 2, 40)])
+def test_small_trees_in_a_large_launch(oracle, mode, nodes):
+    """A launch that is large by T_max: trees too small to wait for the roots, trees on both sides of that line (12 nodes
+    greedy, 24 sampled), and both in one batch."""
+    from paper_2512_14069_amd import binding as b
+    B, T, V = 16, 64, 125001 if nodes[0] == 11 else 50001
+    nn = tuple(nodes[i % len(nodes)] for i in range(B))
+    x = synth.accept_inputs(small_shape(B, T, nn, tuple(max(1, min(5, n - 1)) for n in nn), k=10), V, seed=81 + nodes[0], plant=0.9, shuffle=True)
+    ref, _ = compare(oracle, b, x, mode)
+    assert mode == 1 or ref[0].max() >= 2
