@@ -911,10 +911,11 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(const int32_t 
 // 64 KB, after 5 us of launch and round trips (32 heads, D = 128: 260 rows 8.3 us, 540 rows 9.9; with ranges
 // and a merge 10.7 and 11.2.  One layer of 4 heads with D = 64 over 272 rows 6.0 instead of 7.8).
 constexpr int kOneRows = 32;                             // cache rows of a wavefront's step
+constexpr int kInvShift = 20;                            // a KV head's number times its sequence's share of 2^20
 
-template <int D>
+template <int D, bool EIGHTS>
 __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 *k_, const __bf16 *v_, const int32_t *ctx_lens, const int32_t *n_nodes,
-                                                                  int64_t kv_sb, int64_t kv_sh, AttnArgs a) {
+                                                                  int64_t kv_sb, int64_t kv_sh, int hkv, uint32_t hkv_inv, AttnArgs a) {
     constexpr int DB = D / 32, ROW = D * 2, SUB = kOneRows * ROW;           // bytes of a row, of a step's K or V rows
     constexpr int LOADS = SUB / 1024, RPL = 1024 / ROW, CPR = ROW / 16;     // 1 KB loads; rows of one; 16-byte chunks of a row
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -923,9 +924,15 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
 
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int j32 = lane & 31, g2 = lane >> 5;
-    // Units of a KV head are a multiple of Hkv apart in workgroup number: with eight KV heads on one XCD, whose L2 then
-    // holds that head's rows for all of them (32 heads x 3 sequences over 572 rows 13.9 -> 10.7 us).
-    const int hk = blockIdx.x, unit = blockIdx.y, b = blockIdx.z, qb = unit & (a.nqb - 1), h = hk * a.G + (unit >> (a.nqb - 1));
+    // Which workgroups share a KV head's rows, and whether they share an XCD: plan_attention.
+    int b = blockIdx.z, hk = blockIdx.x;
+    if (EIGHTS) {
+        const int number = 8 * b + hk;                   // the batch's KV heads, counted through
+        b = (int)((uint32_t)number * hkv_inv >> kInvShift);
+        if (b >= a.B) return;
+        hk = number - b * hkv;
+    }
+    const int unit = blockIdx.y, qb = unit & (a.nqb - 1), h = hk * a.G + (unit >> (a.nqb - 1));
     const int L = prefix_rows(a, b);
     int nn = a.n_nodes ? a.n_nodes[b] : a.T;
     nn = max(1, min(nn, a.T));
@@ -949,7 +956,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
             const int chunk = V ? slot ^ vs_swz<D>(row) : slot ^ ks_swz<D>(row);
             const int at = sub * kOneRows + row;
             const __bf16 *src = base + (uint32_t)(min(at, total - 1) * kv_ss) + chunk * 8;
-            if (V) src = at < total ? src : (const __bf16 *)kZeroChunk;
+            if (V) src = at < total ? src : (const __bf16 *)kZeroChunk;      // (in every step: a branch around it costs 0.1 us more)
             const uint32_t dst = lds0 + (V ? SUB : 0) + i * 1024;
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
         }
@@ -1189,7 +1196,7 @@ __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(const
 // ------------------------------------------------------------------ host-side planning
 struct AttnPlan {
     int kps, max_splits, n_ublk, nqb, shares;
-    bool one;                                              // one launch, no ranges
+    bool one, by_eights;                                   // one launch, no ranges; its KV heads taken eight at a time
     size_t off_part_o, off_part_ml, off_tab, bytes;
 };
 
@@ -1202,19 +1209,41 @@ struct AttnPlan {
 // heads 10.3 / 13.6 over 620, 13.1 / 15.2 over 1050, 14.8 / 16.2 over 1360, 17.5 / 17.4 over 1560; four sequences of 32 heads
 // 10.6 / 15.2 over 540, 17.5 / 19.5 over 1560; 16 heads on 8 KV heads 8.6 / 9.3 over 360, 9.8 / 9.9 over 540; 16 tree rows, 32
 // heads 8.0 / 8.6 over 316, 9.2 / 8.6 over 496, three sequences 9.6 / 10.3 over 626.  D = 64, 8 heads on 4: 8.1 / 8.6 over 820, 9.1 / 8.5 over
-// 960; eight sequences of 16 heads 8.6 / 11.8 over 820, 11.7 / 18.3 over 1560.
+// 960; eight sequences of 16 heads 8.6 / 11.8 over 820, 11.7 / 18.3 over 1560.  Two units of at
+// most 32 tree rows per CU (D = 64, more than 256) take longer over a row: 16 tree rows, 32 sequences of 16 heads on 2 10.3 / 11.1 over
+// 640, 13.0 / 12.8 over 900; 64 of 8 on 8 22.3 / 35.1 over 900, 33.0 / 52.2 over 1600; 32 of 12 on 3 13.7 / 15.6 over 1100, 17.7 / 18.5 over 1600.
 static int one_launch_rows(const radar_attn_desc *d, int nqb) {
     const long units = (long)d->B * d->Hq * nqb;
     const int G = d->Hq / d->Hkv;
     if (d->D == 64) {
         if (units > 512) return 0;
-        if (nqb == 1 && units > 256) return units <= 384 ? 640 : 224;
-        return units >= 128 ? 1600 : G * nqb <= 4 || nqb == 1 ? 832 : 1024;
+        if (units > 256 && nqb == 1) return G <= 4 ? 1600 : 832;
+        if (units >= 128) return nqb == 1 && G >= 4 && units < 192 ? 1300 : 1600;
+        return G * nqb <= 4 || nqb == 1 ? 832 : 1024;
     }
     if (units > 256) return 0;
     if (G * nqb <= 4) return units >= 96 ? 800 : units >= 64 && nqb == 2 ? 700 : 384;
     if (nqb == 2 && units >= 64) return units >= 192 ? 1600 : units >= 128 ? 1400 : 900;
     return units >= 192 ? 1100 : units >= 96 ? 800 : 640;
+}
+
+// The units of a KV head read the same rows.  Workgroups go to the eight XCDs in turn, and where grid x is the KV head and Hkv a
+// multiple of eight, a head's are all on one, whose L2 then holds the rows for them (32 heads x 3 sequences over 572 rows
+// 13.9 -> 10.7 us).  With another Hkv they are on two, four or eight XCDs, each of which fetches the rows: that
+// is as good while the L2s (32 MB together) hold all of it.  From 28 MB on the batch's KV heads are taken eight at a
+// time instead, if every XCD gets as few units as its CUs can take (one each, or two with D = 64 if there are more units than CUs);
+// elsewhere the call goes in ranges from 42 MB on.  Over 900 rows, us, grid x the KV head / by eights (finding the head costs 0.15): D = 64, 60
+// tree rows, 8 sequences of 8 heads on 4 (15 MB) 9.3 / 9.5, 16 (29 MB) 9.9 / 9.8, 32 (59 MB) 16.0 / 14.2, 32 of 4 on one (59 MB)
+// 13.8 / 9.8, 64 (118 MB) 22.0 / 13.5 (in ranges 16.1); D = 128, 16 tree rows, 32 of 8 on one (118 MB) 22.6 / 13.0 (14.8).  More units than
+// CUs on an XCD, 16 tree rows: D = 64, 18 of 14 heads on 2 (33 MB) 9.7 / 12.0 (11.3), D = 128 over 900 rows (66 MB) 16.2 and 15.0 in
+// ranges, 36 of 7 on one (116 MB) 22.9 and 17.3.
+static bool one_launch_by_eights_fits(const radar_attn_desc *d, int nqb) {
+    const int64_t heads = (int64_t)d->B * d->Hkv, units = (int64_t)(d->Hq / d->Hkv) * nqb;
+    return (heads + 7) / 8 * units <= (d->D == 64 && heads * units > 256 ? 64 : 32);
+}
+static int64_t one_launch_fetches(const radar_attn_desc *d, int nqb) {          // megabytes, with grid x the KV head
+    const int64_t xcds = d->Hkv % 8 == 0 ? 1 : d->Hkv % 4 == 0 ? 2 : d->Hkv % 2 == 0 ? 4 : 8, units = (int64_t)(d->Hq / d->Hkv) * nqb;
+    return (int64_t)d->B * d->Hkv * d->S_max * d->D * 4 * std::min(xcds, units) / 1000000;
 }
 
 static AttnPlan plan_attention(const radar_attn_desc *d) {
@@ -1224,6 +1253,11 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
     p.n_ublk = (G * p.nqb + kGsWaves - 1) / kGsWaves;
     long kps = d->keys_per_split;
     p.one = kps <= 0 && d->S_max <= one_launch_rows(d, p.nqb);
+    p.by_eights = p.one && d->Hkv % 8 != 0 && one_launch_fetches(d, p.nqb) >= 28;
+    if (p.by_eights && !one_launch_by_eights_fits(d, p.nqb)) {
+        p.by_eights = false;
+        p.one = one_launch_fetches(d, p.nqb) < 42;
+    }
     if (p.one) kps = ((long)d->S_max + kKT - 1) / kKT * kKT;
     if (kps <= 0) {
         // Number of key ranges: the one that minimises a small cost model, in units of one tile of
@@ -1313,13 +1347,17 @@ static hipError_t launch_gs(const AttnArgs &a, dim3 grid, hipStream_t s) {
                   (int)a.kv_ss, a.kps, a.S, a.n_ublk, a.q, a);
 }
 
-template <int D>
-static hipError_t launch_one(const AttnArgs &a, dim3 grid, hipStream_t s) {
+template <int D, bool EIGHTS>
+static hipError_t launch_one(const AttnArgs &a, hipStream_t s) {
+    const int heads = a.B * a.Hkv;                         // at most the 512 units of one launch: exact with the share rounded up
+    const dim3 grid((unsigned)(EIGHTS ? 8 : a.Hkv), (unsigned)(a.G * a.nqb), (unsigned)(EIGHTS ? (heads + 7) / 8 : a.B));
+    const uint32_t inv = ((1u << kInvShift) + a.Hkv - 1) / a.Hkv;
     constexpr int bytes = kGsWaves * (2 * kOneRows * D * 2 + 2 * 32 * (int)sizeof(float));
-    static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_one_kernel<D>),
+    static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_one_kernel<D, EIGHTS>),
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (configured != hipSuccess) return configured;
-    return launch("tree_attn_one", tree_attn_one_kernel<D>, grid, dim3(kGsThreads), bytes, s, a.k, a.v, a.ctx_lens, a.n_nodes, a.kv_sb, a.kv_sh, a);
+    return launch("tree_attn_one", tree_attn_one_kernel<D, EIGHTS>, grid, dim3(kGsThreads), bytes, s, a.k, a.v, a.ctx_lens, a.n_nodes, a.kv_sb, a.kv_sh, a.Hkv,
+                  inv, a);
 }
 
 extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache, const void *v_cache,
@@ -1370,8 +1408,9 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((long)a.B * a.n_ublk > 65535) return RADAR_UNSUPPORTED_SHAPE;
     if (p.one) {
-        const dim3 ogrid((unsigned)a.Hkv, (unsigned)(a.G * a.nqb), (unsigned)a.B);
-        return (d->D == 128 ? launch_one<128>(a, ogrid, s) : launch_one<64>(a, ogrid, s)) == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
+        const hipError_t e = p.by_eights ? (d->D == 128 ? launch_one<128, true>(a, s) : launch_one<64, true>(a, s))
+                                         : (d->D == 128 ? launch_one<128, false>(a, s) : launch_one<64, false>(a, s));
+        return e == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
     }
     const dim3 grid = p.shares > 0 ? dim3((unsigned)p.shares, 1, (unsigned)p.n_ublk)
                                    : dim3((unsigned)a.max_splits, (unsigned)a.Hkv, (unsigned)(a.B * a.n_ublk));

@@ -243,6 +243,31 @@ def test_one_launch_of_many_units_and_steps(oracle, B, Hq, Hkv, T, rows):
         assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)     # unused rows are zeroed
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,rows", [
+    (15, 8, 1, 64, 60, 1000), (16, 8, 1, 64, 16, 900), (17, 4, 1, 64, 60, 900),   # fifteen KV heads, sixteen, seventeen
+    (11, 14, 7, 128, 17, 370), (9, 12, 3, 64, 33, 700), (8, 12, 3, 128, 60, 300), (25, 10, 5, 128, 5, 240),
+    (64, 4, 1, 64, 60, 260), (32, 8, 1, 128, 20, 260),                      # as many units as an XCD holds
+    (9, 28, 4, 128, 32, 900), (17, 14, 2, 64, 40, 900),                     # more than that on one of them: taken in order
+])
+def test_one_launch_of_kv_heads_by_eights(oracle, B, Hq, Hkv, D, T, rows):
+    """One launch over many rows of a batch whose KV heads are no multiple of eight: its workgroups go through the heads of all
+    sequences eight at a time, and find sequence and head from their number."""
+    from paper_2512_14069_amd import binding as b
+    nodes = [max(1, T - i % 3) for i in range(B)]
+    ctx = [(rows - T) * (B - i) // B for i in range(B)]
+    a = shape(B, Hq, Hkv, D, T, ctx, nodes, [max(1, min(6, n - 1)) for n in nodes], k=64)
+    assert a.S == rows and scratch_bytes(b, B, Hq, Hkv, D, T, rows) == 256            # no partials
+    x = synth.attention_inputs(a, seed=synth.seed_for(1, rows + Hq), shuffle=True)
+    ref, ref_lse = oracle.tree_attention(x["q"], x["k_cache"], x["v_cache"], x["parents"], x["ctx_lens"],
+                                         x["n_nodes"], want_lse=True)
+    got, lse = run_gpu(b, x, want_lse=True)
+    for bb in range(B):
+        n = nodes[bb]
+        check_close(got[bb, :n], ref[bb, :n], f"b={bb}")
+        assert np.max(np.abs(lse[bb, :n] - ref_lse[bb, :n])) < LSE_TOL
+        assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)     # unused rows are zeroed
+
+
 @pytest.mark.parametrize("D,ctx,nn,kps", [(128, 30, 3, 0), (128, 224, 33, 0), (128, 256, 1, 0), (64, 256, 16, 0), (64, 700, 60, 0), (128, 256, 32, 0),
                                           (128, 224, 33, 64), (64, 256, 16, 64), (128, 1000, 40, 64), (128, 2000, 17, 64),
                                           (128, 1000, 33, 576), (128, 1000, 33, 1088), (64, 1000, 33, 576), (128, 36000, 33, 0)])
