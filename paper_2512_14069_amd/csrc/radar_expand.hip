@@ -960,11 +960,13 @@ using namespace radar;
 
 // Logits per lane: the fewest (shortest critical path per workgroup) that keep the launch at one
 // workgroup per CU and a row at as many chunks as are merged the short way, as far as there are such (a call over one row
-// of V = 128256 in 16 chunks takes 7.0 us, of V = 262144 in 16 instead of 64 chunks 7.5 instead of 9.4); launches too
-// large for that take the most, i.e. the fewest workgroups.
-static int plan_expand_ept(int F, int V) {
+// of V = 128256 in 16 chunks takes 7.0 us, of V = 262144 in 16 instead of 64 chunks 7.0 instead of 8.0); launches too
+// large for that take the most, i.e. the fewest workgroups.  Rows without 16-byte loads do not go to the most for the
+// sake of the short way: its 64 addresses per lane do not fit the registers (V = 262143, k = 10, one row in 16 / 64 chunks 10.6 / 8.8 us, eight
+// rows in 16 / 32 chunks each 11.7 / 10.2; V = 200001, k = 16, eight rows 19.0 / 12.1).
+static int plan_expand_ept(int F, int V, bool vec4) {
     for (const int most : {kFewChunks, kExpMaxChunks})
-        for (int ept = kExpMinEPT; ept <= 16; ept *= 2) {
+        for (int ept = kExpMinEPT; ept <= (vec4 || most > kFewChunks ? 16 : 8); ept *= 2) {
             const int64_t chunk = (int64_t)kExpThreads * ept, nchunks = ((int64_t)V + chunk - 1) / chunk;
             if (F * nchunks <= 256 && nchunks <= most) return ept;
         }
@@ -1013,7 +1015,8 @@ static radar_status launch_expand(const float *logits, const float *parent_score
     // Batches large enough to fill the chip several times over take the two-launch streaming path.
     const bool stream = B > 1 && (int64_t)B * d->F <= 65535 &&
                         (int64_t)B * d->F * d->V >= kStreamMinLogits;
-    const int ept = plan_expand_ept((int)std::min<int64_t>((int64_t)d->F * B, 1 << 20), d->V);
+    const bool vec4 = (d->V % 4 == 0) && (((uintptr_t)logits & 15) == 0);
+    const int ept = plan_expand_ept((int)std::min<int64_t>((int64_t)d->F * B, 1 << 20), d->V, vec4);
     const int64_t chunk = stream ? kStreamChunk : (int64_t)kExpThreads * ept;
     const int64_t nchunks = ((int64_t)d->V + chunk - 1) / chunk;
     if (d->F > RADAR_F_MAX || d->k > RADAR_K_MAX || nchunks > kExpMaxChunks) return RADAR_UNSUPPORTED_SHAPE;
@@ -1043,7 +1046,6 @@ static radar_status launch_expand(const float *logits, const float *parent_score
     a.pol_has_state = (pol && pol->h_in) ? 1 : 0;
 
     const dim3 grid((unsigned)nchunks, (unsigned)d->F, (unsigned)B), block(kExpThreads);
-    const bool vec4 = (d->V % 4 == 0) && (((uintptr_t)logits & 15) == 0);
     hipStream_t st = static_cast<hipStream_t>(stream_);
     hipError_t e;
     if (stream) {

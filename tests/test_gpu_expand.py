@@ -98,7 +98,7 @@ def test_expand_exact_ties_and_special_values(oracle):
     assert np.max(np.abs(host(g.cand_scores).reshape(F, k) - r["cand_scores"])) <= SCORE_TOL
 
 
-@pytest.mark.parametrize("V", [4096, 8191, 70000, 131072])       # 4 and 8 logits per lane; both kinds of loads; a last chunk of few logits
+@pytest.mark.parametrize("V", [4096, 8191, 70000, 131071, 131072])       # 4, 8 and 16 logits per lane, the last with both kinds of loads; a last chunk of few logits
 @pytest.mark.parametrize("k", [1, 9, 16])
 def test_expand_candidate_counts_at_the_edges_of_the_lists(oracle, V, k):
     """A chunk's candidates go out as they are up to 16 and ranked beyond; up to 32 lanes per wavefront and 512
@@ -118,6 +118,19 @@ def test_expand_candidate_counts_at_the_edges_of_the_lists(oracle, V, k):
     ps, ppi = np.zeros(F, np.float32), np.full(F, -1, np.int32)
     gp, cp = b.DraftPool(F * k), np_pool(F * k)
     run_both_step(oracle, b, logits, ps, ppi, k, gp, cp)
+
+
+@pytest.mark.parametrize("V", [131071, 131073, 200001, 262143, 262144, 262145])
+@pytest.mark.parametrize("F,k", [(1, 10), (4, 16), (8, 10), (10, 3)])
+def test_expand_rows_of_many_chunks(oracle, V, F, k):
+    """Rows of more than 131072 logits: 16 chunks of the most logits per lane where they take 16-byte loads, more chunks of fewer
+    where they do not, or both if there are many rows."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(V + F)
+    logits = np.stack([synth.normal_logits(rng, (V,), 3.0) for _ in range(F)])
+    logits[:, -1] = logits.max(axis=1) - 0.25                    # the last chunk's few logits count
+    ps, ppi = rng.standard_normal(F).astype(np.float32), np.full(F, -1, np.int32)
+    run_both_step(oracle, b, logits, ps, ppi, k, b.DraftPool(F * k), np_pool(F * k))
 
 
 @pytest.mark.parametrize("cfg,first_F", [(1, 1), (3, 1), (3, 10)])
