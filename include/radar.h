@@ -104,6 +104,9 @@ radar_status radar_workspace_init(void *workspace, size_t bytes, void *stream);
  * Strides are in elements; the innermost (D) axis is contiguous; a stride of
  * 0 means "dense" ([B,T_max,Hq,D] for q / out, [B,Hkv,S_max,D] for caches).
  * All bf16 base pointers and strides must keep rows 16-byte aligned.
+ * S_max is what the call is planned for: how many rows it is split into ranges for, or
+ * whether it is one launch.  Where the cache is allocated for longer sequences, pass the rows in
+ * use (the longest ctx_lens[b] + T_max) as S_max and the allocation's strides.
  */
 typedef struct radar_attn_desc {
     int32_t B, T_max, Hq, Hkv, D, S_max;

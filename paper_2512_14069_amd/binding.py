@@ -280,7 +280,8 @@ def radar_tree_attention_workspace_bytes(desc):
 def radar_tree_attention(q, k_cache, v_cache, parents, ctx_lens, n_nodes=None, out=None, lse_out=None,
                          desc=None, workspace=None, keys_per_split=0, softmax_scale=0.0, prepared=False):
     """q bf16 [B,T,Hq,D]; k_cache, v_cache bf16 [B,Hkv,S,D] (same strides, D contiguous);
-    parents i32 [B,T]; ctx_lens i32 [B]; n_nodes i32 [B] or None.  Returns out bf16 [B,T,Hq,D]."""
+    parents i32 [B,T]; ctx_lens i32 [B]; n_nodes i32 [B] or None.  Returns out bf16 [B,T,Hq,D].
+    The call is planned for S rows: of caches allocated for longer sequences pass views of the rows in use (cache[:, :, :n])."""
     if desc is None and workspace is not None and (native := _direct(prepared)):
         done = native.tree_attention(q, k_cache, v_cache, parents, ctx_lens, n_nodes, out, lse_out, keys_per_split, softmax_scale, workspace)
         if done is not None:

@@ -21,10 +21,10 @@
 // node it has arrived at, and a workgroup whose row does not descend from it leaves
 // its logits unread.  Rows go through the grid level by level over all sequences
 // (trees are numbered from the root), so that the roots' decisions come first.
-// What bounds a call is then the chain of decisions (about 2.5 us per level) and
-// the starting of workgroups, not the logits' bytes: 61 rows of V = 128256, sampled,
-// 8 / 16 sequences 16 ... 31 / 23 ... 43 us for paths of 0 ... 8 nodes, against 70 / 129 us
-// when every row is read; one sequence 11 ... 14 us.  In a large launch the
+// What bounds a call is then the chain of decisions and the starting of workgroups, not
+// the logits' bytes: 61 rows of V = 128256, 16 sequences, paths of 0, 1, 2, 4 and 8 nodes 17.6, 23.3,
+// 25.1, 27.7 and 32.6 us greedy and 23.3, 29.1, 31.5, 34.5 and 42.6 sampled (129 when every row is
+// read); one sequence 7.5 ... 8.0 and 10.9 ... 14.4 us.  In a large launch the
 // workgroups behind the roots' rows hold back until the roots are decided (below).
 #include <algorithm>
 

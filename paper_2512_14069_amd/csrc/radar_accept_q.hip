@@ -481,8 +481,9 @@ __global__ __launch_bounds__(kAqLone) void accept_q_walk_kernel(AqArgs a) {
 // While it does, the others take the statistics of the rows one node ahead: an accepted first child's meeting
 // begins with the decision.  (Taken after it, a node cost 3.6 us where it costs 2.6 now; in a call of one sequence,
 // V = 128256, a meeting's words are 1.1 us on their way, merging them and deciding takes 0.7, rows that are not
-// ahead 0.75 + their load.  Calls of one / four sequences 19.0 / 37.7 -> 17.6 / 37.3 us, on cold rows 26.4 / 31.2 -> 25.4 / 30.3.  Rows too
-// long to be held one ahead gain from the two rows' chains side by side: 32 sequences 65.4 -> 59.3.  Having the last of the
+// ahead 0.75 + their load.  Calls of one / four sequences that replay one tree 28.3 / 31.0 -> 26.4 / 26.7 us, over twelve / four trees in
+// turn (their rows cold) 20.8 / 28.1 -> 20.0 / 26.7.  Rows too
+// long to be held one ahead gain from the two rows' chains side by side: 16 / 32 sequences 61.2 / 79.5 -> 57.1 / 72.0.  Having the last of the
 // eight merge their results at once (18.0 instead of 17.6) and two polls in flight (2 % slower) were taken out again.)
 //
 // Every workgroup takes the same decisions from the same numbers, added in the same order.  At a meeting

@@ -11,9 +11,9 @@
 // P^T and V^T, which a contraction does not care about).  The running output is
 // rescaled only when some lane's maximum has risen past its reference by a factor of 256.
 //
-// The ancestor mask is never materialised in memory: each lane walks parents[]
-// once for its query row and keeps the ancestor set as one 64-bit word; a tile
-// that lies entirely in the prefix skips masking altogether.
+// The ancestor mask is never materialised in memory: a wavefront finds the ancestor
+// sets of all rows by doubling over parents[], and each lane keeps its query row's as one
+// 64-bit word; a tile that lies entirely in the prefix skips masking altogether.
 //
 // Work decomposition.  A workgroup of eight wavefronts owns (sequence, KV head,
 // range of cache rows, block of eight (query head, 32 tree rows) units); each
@@ -26,7 +26,7 @@
 // ranges: how many to cut is decided on the host from a cost model that counts whole rounds of
 // resident workgroups and the partial traffic.  Long ranges: the workgroups read the lengths and
 // deal the batch's cache rows out among themselves, so that a batch of unlike sequences keeps every
-// CU busy to the end.
+// CU busy to the end.  Short contexts: one launch, a workgroup per unit over all rows, merged in LDS.
 #include "radar_device.h"
 #include <algorithm>
 #include <type_traits>
@@ -1204,14 +1204,17 @@ struct AttnPlan {
 // than the chip holds at once (one per CU with D = 128, two with D = 64), to where a unit's CU takes as long to read all
 // rows as ranges and their merge take.  That is later the more units there are, because ranges then wait for each other,
 // and earlier where a KV head has at most four: half of a range's wavefronts are idle then, and it takes a tile the faster.
-// Both sides measured at 200 ... 1560 rows for 27 combinations of batch, heads and tree; one launch / ranges in us, at
+// Both sides measured for 633 combinations of batch, heads and tree at ten contexts of 150 ... 1850 rows; one launch / ranges in us, at
 // D = 128, 60 tree rows: 32 heads 8.3 / 10.7 over 260 rows, 9.9 / 11.2 over 540, 11.6 / 12.1 over 820, 13.1 / 13.1 over 1050; 64
 // heads 10.3 / 13.6 over 620, 13.1 / 15.2 over 1050, 14.8 / 16.2 over 1360, 17.5 / 17.4 over 1560; four sequences of 32 heads
 // 10.6 / 15.2 over 540, 17.5 / 19.5 over 1560; 16 heads on 8 KV heads 8.6 / 9.3 over 360, 9.8 / 9.9 over 540; 16 tree rows, 32
-// heads 8.0 / 8.6 over 316, 9.2 / 8.6 over 496, three sequences 9.6 / 10.3 over 626.  D = 64, 8 heads on 4: 8.1 / 8.6 over 820, 9.1 / 8.5 over
-// 960; eight sequences of 16 heads 8.6 / 11.8 over 820, 11.7 / 18.3 over 1560.  Two units of at
+// heads 8.0 / 8.6 over 316, 9.2 / 8.6 over 496, three sequences 9.6 / 10.3 over 626.  D = 64, 8 heads on 4: 8.1 / 8.6 over 820, 9.1 / 8.5 over 960; 16 on 4 over 1000 rows, 60 tree
+// rows, one / four / eight sequences 9.4 / 9.8, 9.8 / 11.0, 10.2 / 15.3; eight of 16 heads 8.6 / 11.8 over 820, 11.7 / 18.3 over 1560.  Two units of at
 // most 32 tree rows per CU (D = 64, more than 256) take longer over a row: 16 tree rows, 32 sequences of 16 heads on 2 10.3 / 11.1 over
 // 640, 13.0 / 12.8 over 900; 64 of 8 on 8 22.3 / 35.1 over 900, 33.0 / 52.2 over 1600; 32 of 12 on 3 13.7 / 15.6 over 1100, 17.7 / 18.5 over 1600.
+// Over all of these the better side is missed by 0.8 % in the geometric mean, as by a line between the two sides' estimated times.  Trees just
+// past 32 rows in ragged batches would have it earlier (33 tree rows, three sequences of 32 heads, the longest 1533 16.8 / 14.7), in even ones not
+// (four of 32 heads over 1400 15.6 / 16.9, eight of 8 on 8 with D = 64 over 1600 11.2 / 13.4), and the host does not know which they are.
 static int one_launch_rows(const radar_attn_desc *d, int nqb) {
     const long units = (long)d->B * d->Hq * nqb;
     const int G = d->Hq / d->Hkv;
@@ -1264,9 +1267,9 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
         // one workgroup (1.45 us): rounds of 256 resident workgroups x (tiles per range +
         // 3 for prologue and epilogue), plus what the merge of the ranges costs: the launch, and every
         // range's partials written and read again.  Counting whole rounds matters: 576 workgroups take
-        // as long as 768.  What a range costs was fitted over 164 shapes of 700 ... 16000 rows, every number of tiles:
-        // it grows with the bytes of its partials (with 0.08 for any, 1300 rows of 32 heads were cut into 22 ranges of one tile, 15.4 us;
-        // 11 of two take 13.7; 3000 rows 24 of two and 17.6, 16 of three take 16.9).
+        // as long as 768.  What a range costs grows with the bytes of its partials (with 0.08 for any, 1300 rows of 32 heads were cut
+        // into 22 ranges of one tile, 15.4 us; 11 of two take 13.7).  Over 753 calls of 900 ... 6500 rows, each timed with one to
+        // eight tiles per range, this choice is 1.1 % slower than the best one in the geometric mean; 0.08 for any is 1.7 %.
         const double per_range = std::max(0.078, 0.045 + 4e-7 * (double)d->B * d->Hq * d->T_max * d->D);
         const long units = (long)d->B * d->Hkv * p.n_ublk;
         const long tiles_all = ((long)d->S_max + kKT - 1) / kKT;

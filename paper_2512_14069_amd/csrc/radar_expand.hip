@@ -4,9 +4,9 @@
 // radar_draft_expand: grid (chunks of 4096, 8192 or 16384 logits, frontier rows).
 // Every workgroup streams its chunk once from HBM with 16-byte loads (the whole
 // step is one read of F*V*4 bytes), keeps its 4, 8 or 16 values per lane in registers,
-// and leaves (chunk top-k keys, chunk max, chunk sum of exp) in the workspace.
-// Arrival tickets (one counter per row, then one per call) single out the
-// workgroup that finishes last; it merges every row, one wavefront per row
+// and leaves (a list with the chunk's top-k keys in any order, chunk max, chunk sum of exp) in the workspace.
+// Arrival tickets (one counter for a call of few workgroups; else one per row, then one per call) single
+// out the workgroup that finishes last; it merges every row, one wavefront per row
 // (top-k of the chunk lists, log-sum-exp in fp64, cumulative scores, pool
 // append), and picks the next frontier.  There is no second launch and no
 // host round trip.  radar_draft_expand_policy lets the same workgroup go on to
@@ -845,7 +845,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
     if (lane == 0) wave_l[w] = wl;
     const float tau = float_of_ord(kth_of_32(ord_of(g32), K));
 
-    // ---- Lanes whose largest logit reaches the threshold (about 1.6 k of the 256) leave all their logits in
+    // ---- Lanes whose largest logit reaches the threshold (1.2 k to 1.4 k of the 256) leave all their logits in
     // LDS; their wavefront compares those one per lane and appends what passes to the chunk's list.  (A
     // threshold per wavefront and a comparison of every logit with it were 150 instructions, a sixth of the time.)
     const bool hot = tm >= tau && base + tid * 4 < a.V;           // (a lane wholly past the row holds -inf only)

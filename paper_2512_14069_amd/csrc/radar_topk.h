@@ -235,9 +235,9 @@ __device__ __forceinline__ uint64_t wave_topk(const uint64_t (&keys)[EPL], int K
 
 constexpr int kWaveListSlots = 32;               // a wavefront's list in LDS
 
-// Lists of 16 slots of which the first K are used (slot i: list i / 16, rank i % 16), taken 64
-// slots per step: which slot a lane takes at step e.  Lanes rotate by 4 per step, so a lane
-// meets slots of different ranks and every quad of lanes holds used slots.
+// Lists of 16 slots, at least K of them used unless the chunk is shorter, in any order and from the first on (slot i: list
+// i / 16), taken 64 slots per step: which slot a lane takes at step e.  Lanes rotate by 4 per step, so a lane
+// meets slots of different places and every quad of lanes holds used slots.
 __device__ __forceinline__ int topk_slot_of(int e) {
     return e * kWave + ((lane_id() + 4 * e) & (kWave - 1));
 }
