@@ -44,7 +44,7 @@ constexpr int64_t kAccManyBlocks = 49152;
 constexpr int64_t kAccWalkLast = 3072;  // greedy launches up to this many workgroups leave the walk to the last row
 constexpr int kAccUnchecked = 1024;     // workgroups the chip starts first: nothing is decided yet when they do
 constexpr int kAccPolls = 3;            // how often a waiting workgroup looks (1 us apart)
-constexpr int kAccWaitNodes = 12;       // trees of fewer nodes never wait (launch_accept; 32 of 9, V = 128256, would gain 2 us at the root and lose 1-2 elsewhere)
+constexpr int kAccWaitNodes = 8;        // trees of fewer nodes never wait (launch_accept)
 constexpr float kAccLog2e = 1.4426950408889634f;
 constexpr unsigned int kAccDone = 1u << 30, kAccReached = 1u << 29;   // marks beside a row's count of arrivals
 constexpr int kAccEnded = RADAR_T_MAX;  // "node arrived at" once the walk has ended
@@ -755,14 +755,16 @@ static radar_status launch_accept(const float *target_logits, const int32_t *dra
     // by it (one sequence, sampled, 2 nodes 11.1 / 14.1; two 13.2 / 14.9; greedy, 8 sequences of V = 32000 10.3 / 10.7).
     // So do small trees in a launch that is large by T_max alone, once the path leaves the root (16 trees of 6 nodes, T_max = 64, paths of
     // 0, 2 and 5 nodes: greedy, V = 32000 6.0 / 7.2, 7.5 / 11.2, 8.0 / 11.6; sampled, V = 128256 14.7 / 10.4, 15.3 / 20.9, 18.1 / 22.5).  Only trees
-    // wait with which the launch would be a large one if all were like them: what is known of the others is not worth reading the
-    // batch's sizes (every workgroup starts later then: 16 x 61 rows 17.5 -> 22.4).  16 trees of 12 nodes, greedy, V = 128256 16.8 / 9.9, 19.9 / 21.2, 20.2 / 21.1.
+    // wait with which the launch would be half a large one if all were like them; reading the others' sizes is not worth it
+    // (every workgroup starts later then: 16 x 61 rows 17.5 -> 22.4).  16 trees of 12 nodes, T_max = 64, paths of 0, 2 and 4 nodes, greedy,
+    // V = 32000 8.7 / 7.6, 9.5 / 12.3, 10.5 / 12.7, of 24 nodes 12.6 / 8.5, 13.3 / 12.6, 13.6 / 13.1.  With a whole large one instead of half, batches of
+    // unlike trees lose: 16 of 2 to 60 nodes (377 rows), sampled, V = 128256 15.5 us when all wait, 16.2 with half, 17.2 with a whole.
     const int64_t blocks = (int64_t)d->B * d->T_max * nsub;
     const bool wait = mode == RADAR_ACCEPT_GREEDY ? blocks >= kAccManyBlocks / 2 : mode == RADAR_ACCEPT_SAMPLE && blocks >= kAccManyBlocks;
     a.check_from = wait ? (int)(d->B * nwg) : kAccUnchecked;
     a.wait = mode == RADAR_ACCEPT_GREEDY ? 250 : 450;
     a.wait_until = wait ? (mode == RADAR_ACCEPT_GREEDY ? 2048 : 1536) : 0;
-    a.wait_nodes = (int)std::max<int64_t>(kAccWaitNodes, (mode == RADAR_ACCEPT_GREEDY ? kAccManyBlocks / 2 : kAccManyBlocks) / (d->B * nsub));
+    a.wait_nodes = (int)std::max<int64_t>(kAccWaitNodes, (mode == RADAR_ACCEPT_GREEDY ? kAccManyBlocks / 4 : kAccManyBlocks / 2) / (d->B * nsub));
     // A greedy walk is shortest at the end of the launch, in registers over all rows' results, as long as the launch
     // is not much more than the chip holds at once (one sequence of 16 rows, V = 32000: 5.6 us against 7.1; two of
     // 61 rows, V = 128256, 3904 workgroups: 13.9 against 13.3).  A sampled one is not: its exponentials and the

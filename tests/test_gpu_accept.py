@@ -214,12 +214,12 @@ def test_walk_carried_from_row_to_row(oracle, mode, B, T, V, chain):
 
 
 @pytest.mark.parametrize("mode", [0, 1])
-@pytest.mark.parametrize("nodes", [(6,), (11, 12, 13, 24, 25), (1, 64, 2, 40)])
+@pytest.mark.parametrize("nodes", [(6,), (11, 12, 13, 24, 25), (7, 8, 9, 11, 12), (1, 64, 2, 40)])
 def test_small_trees_in_a_large_launch(oracle, mode, nodes):
-    """A launch that is large by T_max: trees too small to wait for the roots, trees on both sides of that line (12 nodes
-    greedy, 24 sampled), and both in one batch."""
+    """A launch that is large by T_max: trees too small to wait for the roots, trees on both sides of that line (8 nodes
+    greedy, 12 sampled), and both in one batch."""
     from paper_2512_14069_amd import binding as b
-    B, T, V = 16, 64, 125001 if nodes[0] == 11 else 50001
+    B, T, V = 16, 64, 125001 if nodes[0] in (7, 11) else 50001
     nn = tuple(nodes[i % len(nodes)] for i in range(B))
     x = synth.accept_inputs(small_shape(B, T, nn, tuple(max(1, min(5, n - 1)) for n in nn), k=10), V, seed=81 + nodes[0], plant=0.9, shuffle=True)
     ref, _ = compare(oracle, b, x, mode)
