@@ -5,15 +5,16 @@
 // Every workgroup streams its chunk once from HBM with 16-byte loads (the whole
 // step is one read of F*V*4 bytes), keeps its 4, 8 or 16 values per lane in registers,
 // and leaves (a list with the chunk's top-k keys in any order, chunk max, chunk sum of exp) in the workspace.
-// Arrival tickets (one counter for a call of few workgroups; else one per row, then one per call) single
-// out the workgroup that finishes last; it merges every row, one wavefront per row
+// Counters (one for a call of few workgroups; else one per row, then one per call) single
+// out the workgroup that comes last, which takes the others' words as they arrive (each says itself that
+// it is there) and merges every row, one wavefront per row
 // (top-k of the chunk lists, log-sum-exp in fp64, cumulative scores, pool
 // append), and picks the next frontier.  There is no second launch and no
 // host round trip.  radar_draft_expand_policy lets the same workgroup go on to
 // the prediction model's step on the k confidences it has just produced
 // (Sec. 4.2), so the continue / stop decision costs no launch of its own.
 // radar_draft_expand_batch adds a grid dimension: one such call per sequence,
-// B sequences in one launch, each with its own arrays, tickets and last workgroup.
+// B sequences in one launch, each with its own arrays, counters and last workgroup.
 #include <algorithm>
 #include <mutex>
 
@@ -38,6 +39,17 @@ constexpr int kFewChunks = 16;                        // rows of so many chunks 
 constexpr int kFrontierMax = 256;                     // candidates of a call that are ranked by counting
 constexpr int64_t kStreamMinLogits = 4 << 20;         // batched calls of at least 16 MB of logits take the streaming path
 
+// What the workgroups of a single launch hand over vouches for itself: the reader looks until every word is there.  A key there
+// has bits 31 and 30 of its lower half as 01 (as 11 where the two-launch form left it), a sum its sign bit set and a maximum 1 in its
+// upper half; the reader clears what it has read, and nothing else that a workspace can hold looks like that.
+constexpr uint64_t kKeyMark = uint64_t(1) << 31, kSumMark = uint64_t(1) << 63;
+constexpr uint64_t kNoKey = uint64_t(1) << 30;        // an empty slot of a list: below every key
+constexpr uint32_t kKeyIndexMask = (1u << 30) - 1;
+constexpr size_t kGateOffset = 12288, kStreamGateOffset = 14336;   // the prediction model's w_hh h (of which no value is 0 in a single launch), in the counter block
+static_assert((1 + RADAR_F_MAX) * kCounterStride * sizeof(unsigned int) <= kGateOffset && kGateOffset + 4 * kPolH * sizeof(float) <= kStreamGateOffset &&
+              kStreamGateOffset + 4 * kPolH * sizeof(float) <= kCounterBytes, "counter block");
+constexpr unsigned int kPollLimit = 1u << 22;         // looks (0.5 us and more each) at what is always on its way: only memory that was never cleared gets there
+
 // what a launch carries beside the expansion itself: nothing; a batch or a cycle state; a prediction model, too
 enum { kExpPlain, kExpExt, kExpPolicy };
 
@@ -57,9 +69,8 @@ struct ExpandArgs {
     int F, V, k, nchunks, pool_count;
     int pool_capacity;          // length of one sequence's pool arrays (their stride in a batched call)
     unsigned int *counters;     // [0] rows finished, [(1+f) * kCounterStride] chunks of row f finished
-    uint64_t *part_keys;        // [F][nchunks][RADAR_K_MAX] in any order, 0 where a chunk has fewer
-    double *part_l;             // [F][nchunks] sum of exp(x - part_m) over the chunk
-    float *part_m;              // [F][nchunks] chunk maximum
+    uint64_t *part_keys;        // [F][nchunks][RADAR_K_MAX] in any order, kNoKey (two launches: 0) where a chunk has fewer
+    uint64_t *part_lm;          // [F][nchunks][2] sum of exp(x - m) over the chunk, and its maximum m in the lower half
     PolicyArgs pol;             // prediction model run by the last workgroup when has_policy != 0
     float *gate_pre;            // [4H] w_hh h of that model, computed by the first workgroups of the launch
     radar_cycle_state *cycle;   // device-side state of the drafting cycle, or null: when set, pool_count above is
@@ -82,25 +93,47 @@ struct alignas(16) ExpandSmem {
     alignas(16) uint64_t cand_key[kFrontierMax];
     int rank[kExpThreads];                        // larger keys in each part of cand_key
     PolicySmem pol;
-    unsigned int ticket, ticket2;
+    int last;                                     // this workgroup finishes the call
 };
 
+__device__ __forceinline__ bool key_there(uint64_t w) { return ((uint32_t)w >> 30) == 1u; }
+__device__ __forceinline__ bool sum_there(uint64_t w) { return (int64_t)w < 0; }
+__device__ __forceinline__ bool max_there(uint64_t w) { return (uint32_t)(w >> 32) == 1u; }
+__device__ __forceinline__ double sum_of_word(uint64_t w) { return __longlong_as_double((long long)(w & ~kSumMark)); }   // (sums are not negative)
+__device__ __forceinline__ float max_of_word(uint64_t w) { return __uint_as_float((uint32_t)w); }
+
+// A word of the hand-over, of which w is what the first look saw.
+template <bool POLL, typename There>
+__device__ __forceinline__ uint64_t settled(uint64_t w, const uint64_t *p, There &&there) {
+    if (POLL) for (unsigned int looks = 0; !there(w) && looks < kPollLimit; ++looks) w = load_shared_result(p);
+    return w;
+}
+
 // 512 slots, starting at c0, of one row's chunk lists in the workspace (device-scope loads)
+template <bool POLL>
 __device__ __forceinline__ void load_key_block(const uint64_t *pk, int nslot, int c0, uint64_t (&kk)[9]) {
+    auto slot = [&](int e) { return min(c0 + topk_slot_of(e), nslot - 1); };     // branch-free: clamp, load, mask
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int i = c0 + topk_slot_of(e);
-        const uint64_t key = load_shared_result(pk + min(i, nslot - 1));     // branch-free: clamp, load, mask
-        kk[e] = i < nslot ? key : 0;
+    for (int e = 0; e < 8; ++e) kk[e] = load_shared_result(pk + slot(e));
+    for (unsigned int looks = 0; POLL && looks < kPollLimit; ++looks) {            // a look asks only for what the one before did not see
+        bool all = true;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) all = all && key_there(kk[e]);
+        if (__ballot(!all) == 0) break;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) if (!key_there(kk[e])) kk[e] = load_shared_result(pk + slot(e));
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) kk[e] = c0 + topk_slot_of(e) < nslot ? kk[e] : 0;
     kk[8] = 0;
 }
 
 // top-K of one row's chunk lists by one wavefront; kk holds the first 512 slots already
+template <bool POLL>
 __device__ __forceinline__ uint64_t row_topk(uint64_t (&kk)[9], const uint64_t *pk, int nslot, int K, WaveTopkSmem &scratch) {
     uint64_t top = wave_topk<9>(kk, K, scratch);
     for (int c0 = 8 * kWave; c0 < nslot; c0 += 8 * kWave) {        // V > 131072 only
-        load_key_block(pk, nslot, c0, kk);
+        load_key_block<POLL>(pk, nslot, c0, kk);
         kk[8] = top;                                                 // the running selection rides along
         top = wave_topk<9>(kk, K, scratch);
     }
@@ -181,8 +214,8 @@ __device__ __forceinline__ void sequence_view(ExpandArgs &a, int bz) {
     a.frontier_scores += b * a.k; a.frontier_conf += b * a.k;
     a.pool_tokens += b * a.pool_capacity; a.pool_scores += b * a.pool_capacity; a.pool_parents += b * a.pool_capacity;
     a.counters += b * (kCounterBytes / sizeof(unsigned int));
-    a.part_keys += b * fc * RADAR_K_MAX; a.part_l += b * fc; a.part_m += b * fc;
-    a.gate_pre += b * (4 * kPolH);
+    a.part_keys += b * fc * RADAR_K_MAX; a.part_lm += b * fc * 2;
+    a.gate_pre += b * (kCounterBytes / sizeof(float));
     if (a.cycle) a.cycle += b;
 }
 
@@ -194,7 +227,9 @@ __device__ __forceinline__ void sequence_view(ExpandArgs &a, int bz) {
 // batched call learns here that the sequence's cycle has stopped, and its pool count).
 // hidden(row) returns row `row` of w_hh h (complete before the call; only used with a prediction
 // model that has a state).
-template <int MODE, typename Settle, typename Hidden>
+// POLL: what the other workgroups hand over may still be on its way (all of them have begun, and wait for nobody), and is cleared
+// once it has been read.  Without, it is all there.
+template <int MODE, bool POLL, typename Settle, typename Hidden>
 __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int bz, radar_cycle_state *cycle,
                                               bool cycle_first, Settle &&settle, Hidden &&hidden) {
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
@@ -211,27 +246,51 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
     double ll = 0.0;
     int ppool = 0;
     auto load_row = [&](int fr) {
-        const uint64_t *pk = a.part_keys + (size_t)fr * nslot;
-        if (few) {
-            // Four slots per lane, two to a load (device scope, as load_shared_result's; slots past the lists read 0).  What the call's last
-            // workgroup waits for here is requests: with loads of one slot a call took 8.1 us, 7.9 now, ten rows of 32000 7.5 and 7.3.
-            const auto lists = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(a.part_keys) + (size_t)__builtin_amdgcn_readfirstlane(fr) * nslot,
-                                                                 0, nslot * (int)sizeof(uint64_t), 0x00027000);
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const auto v = __builtin_amdgcn_raw_buffer_load_b128(lists, e * (kWave * 16) + ((lane + 4 * e) & (kWave - 1)) * 16, 0, 16);
-                kk[2 * e] = (uint64_t)v[0] | (uint64_t)v[1] << 32;
-                kk[2 * e + 1] = (uint64_t)v[2] | (uint64_t)v[3] << 32;
-            }
-        } else {
-            load_key_block(pk, nslot, 0, kk);
-        }
+        const uint64_t *pk = a.part_keys + (size_t)fr * nslot, *plm = a.part_lm + (size_t)fr * a.nchunks * 2;
         // chunk partials, one chunk per lane first (up to 16 chunks: every 16-lane row of the wavefront takes all)
         const int c = min(few ? (lane & 15) : lane, a.nchunks - 1);
-        ml = load_shared_result(&a.part_m[(size_t)fr * a.nchunks + c]);
-        ll = load_shared_result(&a.part_l[(size_t)fr * a.nchunks + c]);
-        pscore = a.parent_scores[fr];
-        ppool = a.parent_pool_idx[fr];
+        if (few) {
+            // Four slots per lane, two to a load (device scope, as load_shared_result's; slots past the lists read 0).  What is waited for
+            // here is requests: with loads of one slot a call took 8.1 us, 7.9 with two, ten rows of 32000 7.5 and 7.3.  A
+            // look asks only for what the one before did not see.
+            const int urow = __builtin_amdgcn_readfirstlane(fr);
+            const auto lists = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(a.part_keys) + (size_t)urow * nslot,
+                                                                 0, nslot * (int)sizeof(uint64_t), 0x00027000);
+            const auto sums = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(a.part_lm) + (size_t)urow * a.nchunks * 2,
+                                                                0, a.nchunks * 16, 0x00027000);
+            const int at[3] = {lane * 16, kWave * 16 + ((lane + 4) & (kWave - 1)) * 16, c * 16};
+            uint64_t w2[3][2];
+            auto look = [&](int e) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(e == 2 ? sums : lists, at[e], 0, 16);
+                w2[e][0] = (uint64_t)v[0] | (uint64_t)v[1] << 32;
+                w2[e][1] = (uint64_t)v[2] | (uint64_t)v[3] << 32;
+            };
+            look(0); look(1); look(2);
+            pscore = a.parent_scores[fr];
+            ppool = a.parent_pool_idx[fr];
+            if (POLL) {
+                for (unsigned int looks = 0; looks < kPollLimit; ++looks) {
+                    bool missing[3];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) missing[e] = !(key_there(w2[e][0]) && key_there(w2[e][1])) && at[e] < nslot * (int)sizeof(uint64_t);
+                    missing[2] = !(sum_there(w2[2][0]) && max_there(w2[2][1]));
+                    if (__ballot(missing[0] || missing[1] || missing[2]) == 0) break;
+                    asm volatile("" ::: "memory");                 // (else the loads are the ones before)
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) if (missing[e]) look(e);
+                }
+            }
+            kk[0] = w2[0][0]; kk[1] = w2[0][1]; kk[2] = w2[1][0]; kk[3] = w2[1][1];
+            ll = sum_of_word(w2[2][0]);
+            ml = max_of_word(w2[2][1]);
+        } else {
+            const uint64_t wl = load_shared_result(plm + 2 * c), wm = load_shared_result(plm + 2 * c + 1);
+            pscore = a.parent_scores[fr];
+            ppool = a.parent_pool_idx[fr];
+            load_key_block<POLL>(pk, nslot, 0, kk);
+            ll = sum_of_word(settled<POLL>(wl, plm + 2 * c, sum_there));
+            ml = max_of_word(settled<POLL>(wm, plm + 2 * c + 1, max_there));
+        }
     };
     auto merge_row = [&](int fr, auto &&between) {
         const uint64_t *pk = a.part_keys + (size_t)fr * nslot;
@@ -240,12 +299,14 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
             const uint64_t k4[4] = {kk[0], kk[1], kk[2], kk[3]};
             top = wave_topk<4>(k4, K, s.wtk[w], between);
         } else {
-            top = row_topk(kk, pk, nslot, K, s.wtk[w]);
+            top = row_topk<POLL>(kk, pk, nslot, K, s.wtk[w]);
         }
         if ((few ? (lane & 15) : lane) >= a.nchunks) { ml = -INFINITY; ll = 0.0; }
         for (int c = lane + kWave; c < a.nchunks; c += kWave) {        // V > 262144 only
-            const float m2 = load_shared_result(&a.part_m[(size_t)fr * a.nchunks + c]);
-            const double l2 = load_shared_result(&a.part_l[(size_t)fr * a.nchunks + c]);
+            const uint64_t *p = a.part_lm + ((size_t)fr * a.nchunks + c) * 2;
+            const uint64_t wl = load_shared_result(p), wm = load_shared_result(p + 1);
+            const double l2 = sum_of_word(settled<POLL>(wl, p, sum_there));
+            const float m2 = max_of_word(settled<POLL>(wm, p + 1, max_there));
             const float mn = fmaxf(ml, m2);
             if (mn > -INFINITY)
                 ll = ll * (double)__builtin_amdgcn_exp2f((ml - mn) * kLog2eF) + l2 * (double)__builtin_amdgcn_exp2f((m2 - mn) * kLog2eF);
@@ -275,7 +336,7 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
         // fp64 routine costs 0.3 us on this serial path
         const double lse = (double)M + (double)logf((float)L);
         if (lane < K) {
-            const int tok = (int)key_index(top);
+            const int tok = (int)(key_index(top) & kKeyIndexMask);
             const double logp = (double)key_value(top) - lse;
             const float cum = (float)((double)pscore + logp);
             const int c = fr * K + lane;
@@ -322,27 +383,46 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
         else if (cycle_first) cycle->stopped = 0;
     };
     if constexpr (MODE == kExpPolicy) {
+        if (POLL && a.pol_has_state && w >= kPolWaves / 2)          // this lane's row of w_hh h
+            for (unsigned int looks = 0; __float_as_uint(pr.hid) == 0 && looks < kPollLimit; ++looks) pr.hid = hidden(policy_gate_row());
         // ---- prediction-model step on the new frontier's confidences
         __syncthreads();
         policy_decide<true>(a.pol, bz, a.pol_has_state != 0, s.pol, pr, hidden, advance);
     } else {
         if (tid == 0) advance(-1);
     }
+    if constexpr (POLL) {
+        // Everything that was handed over has been read: clear it, written through like the words themselves.  By wavefronts that have
+        // nothing else to do at the end, and where nothing loads any more (a wait for loads is one for these stores, too: 0.5 us
+        // of a call with the prediction model).
+        typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+        const u32x4 zeros = {0, 0, 0, 0};
+        const int idle = kExpThreads - kWave, from = MODE == kExpPolicy ? tid : tid - kWave, nlist = a.F * nslot * (int)sizeof(uint64_t), nsum = a.F * a.nchunks * 16;
+        const auto lists = __builtin_amdgcn_make_buffer_rsrc(a.part_keys, 0, nlist, 0x00027000);
+        const auto sums = __builtin_amdgcn_make_buffer_rsrc(a.part_lm, 0, nsum, 0x00027000);
+        if (from >= 0 && from < idle) {
+            for (int i = from * 16; i < nlist; i += idle * 16) __builtin_amdgcn_raw_buffer_store_b128(zeros, lists, i, 0, 16);
+            for (int i = from * 16; i < nsum; i += idle * 16) __builtin_amdgcn_raw_buffer_store_b128(zeros, sums, i, 0, 16);
+            if (MODE == kExpPolicy && a.pol_has_state && from < 4 * kPolH) store_shared_result(&a.gate_pre[from], 0.f);
+        }
+    }
 }
 
 // MODE: the plain expansion is compiled without any code for batches, cycle states or the prediction model.
 // A call is a chain of dependent stages, none of which is bound by bandwidth.  Times of the last workgroup at F = 10,
-// V = 128256, k = 10, us after the first one starts: row maxima 1.1, threshold and hot lanes 1.8, candidates
-// and sums 2.5, list stored 2.8, row ticket 3.9, call ticket 4.3, lists loaded 5.1, rows merged 6.9, frontier 7.8;
-// a launch adds about 1.  8.2 us per call on warm logits (8.9 with sixteen groups for the threshold, the exponentials before it
+// V = 128256, k = 10, us after the first one starts: row maxima 1.0, threshold and hot lanes 1.75, candidates
+// and sums 2.5, list stored 2.7, all lists there 3.5, rows merged 5.2, frontier 6.1;
+// a launch adds about 1.  (With lists announced by tickets once their stores were acknowledged they were there at 5.1: a call took 7.9 us, now 7.1;
+// F = 1 6.6 and 6.4, eight rows of 128257 9.2 and 8.1.)
+// 8.2 us per call on warm logits then (8.9 with sixteen groups for the threshold, the exponentials before it
 // and every list ranked), 11.7 instead of 28.9 for 16 rows with k = 16, where the sixteen groups' threshold
 // let whole chunks through.  Lists longer than 16 slots need no ranking at all, but the last workgroup's loads are
 // slow (from beyond its L2, 37 bytes per ns): 24 slots cost it 0.4 us, records of 32 0.7.
 // The leading arguments are what the stream waits for; they are in registers when the kernel starts (0.25 us).
 //
 // Up to how many workgroups all count on one counter: they wait for each other there, some 10 ns each, but the last one is
-// spared a second counter's round trip (by row first, then the rows).  16 arrivals (one row of V = 128256) 6.9 us by rows,
-// 6.5 on one; 64 (four) 7.0 and 6.6; 80 (ten of 32000) 7.7 and 7.5; 128 7.8 and 7.9; 160 8.4 and 8.8.
+// spared a second counter's round trip (by row first, then the rows).  Over 100 calls of 1 ... 10 rows, V = 32001 ... 400001, all on one counter costs
+// 2-8 % where they are more (80 of 81 ... 256 workgroups), up to 96 or up to 48 is the same within 0.5 %.
 constexpr int kDirectArrivals = 96;
 
 template <bool VEC4, int EPT, int MODE>
@@ -375,6 +455,12 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     const float *row = a.logits + (size_t)f * a.V;
     const int base = chunk * kChunk;
     const int K = a.k;
+    // Who finishes the call: the workgroup that is counted last.  The others are running by then, or done, and wait for nobody, so it may wait
+    // for what they hand over.  One lane of a wavefront that does not stream counts, beside the stream; few workgroups when their logits are
+    // there (counted at the start, one row of V = 200000 7.14 us, so 6.74; counted beside the candidates 6.93).
+    const bool direct = a.F * a.nchunks <= kDirectArrivals, counting = w == kExpWaves - 1 && lane == 0;
+    unsigned int before = 0;
+    if (counting && !direct) before = __hip_atomic_fetch_add(&a.counters[(1 + f) * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // ---- stream the chunk.  Only the first four wavefronts (one per SIMD) stream and select: a
     // 64-wide vector instruction occupies its SIMD for four cycles whichever wavefront issues it, so
@@ -472,11 +558,14 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
         const auto c2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(cm), __float_as_uint(cm), false, false);
         cm = fmaxf(__uint_as_float(c2[0]), __uint_as_float(c2[1]));
     } else {
+        if (counting && direct) before = __hip_atomic_fetch_add(&a.counters[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // The arguments that only the call's end needs are brought close by now: read by the last workgroup when it
         // gets there, each cache line of them would be a round trip of its own (0.3 us).
-        asm volatile("" :: "s"(a.parent_scores), "s"(a.pool_scores), "s"(a.part_m));
+        asm volatile("" :: "s"(a.parent_scores), "s"(a.pool_scores), "s"(a.part_lm));
         if (MODE == kExpPolicy) asm volatile("" :: "s"(a.pol.b2), "s"(a.gate_pre));
-        if (hidden_rows) hrows.finish(a.pol, bz, [&](int r, float v) { store_shared_result(&a.gate_pre[r], v); });
+        if (hidden_rows) hrows.finish(a.pol, bz, [&](int r, float v) { store_shared_result(&a.gate_pre[r], __float_as_uint(v) == 0 ? -0.f : v); });
+        if (counting && !direct)                                   // the last one of the row counts the row
+            before = before == (unsigned int)(a.nchunks - 1) ? __hip_atomic_fetch_add(&a.counters[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0u;
     }
     __syncthreads();
     if (streamer) {
@@ -522,6 +611,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
                 }
             }
         }
+        if (counting) s.last = before == (unsigned int)((direct ? a.F * a.nchunks : a.F) - 1);
     }
     __syncthreads();
     const size_t pslot = (size_t)f * a.nchunks + chunk;
@@ -555,11 +645,11 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
 #pragma unroll
             for (int e = 0; e < NS; ++e) k2[e] = s.wlist[e * kWave + lane];
             const uint64_t top = wave_topk<NS>(k2, K, s.wtk[0]);
-                if (lane < RADAR_K_MAX) store_shared_result(list + lane, top);      // lanes from K on hold 0
+            if (lane < RADAR_K_MAX) store_shared_result(list + lane, top != 0 ? top ^ kKeyMark : kNoKey);      // lanes from K on hold 0
         }
     } else if (w == 0 && nsurv <= RADAR_K_MAX) {
-        // the candidates as they are: the last workgroup ranks them with the other chunks'
-        if (lane < RADAR_K_MAX) store_shared_result(list + lane, lane < nsurv ? surv[lane] : (uint64_t)0);
+        // the candidates as they are: the finishing workgroup ranks them with the other chunks'
+        if (lane < RADAR_K_MAX) store_shared_result(list + lane, lane < nsurv ? surv[lane] ^ kKeyMark : kNoKey);
     } else if (w == 0) {
         // More candidates than slots (k = 10: one chunk in a hundred; k above 12: most): the k best of them, by exact
         // ranks; every lane counts the larger keys with broadcast reads.
@@ -576,37 +666,22 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
 #pragma unroll
                 for (int u = 0; u < 8; ++u) rank += (kj[u] > key) ? 1 : 0;
             }
-            if (i < nsurv && rank < K) store_shared_result(list + rank, key);   // ranks are distinct
+            if (i < nsurv && rank < K) store_shared_result(list + rank, key ^ kKeyMark);   // ranks are distinct
         }
-        if (lane >= K && lane < RADAR_K_MAX) store_shared_result(list + lane, (uint64_t)0);
+        if (lane >= K && lane < RADAR_K_MAX) store_shared_result(list + lane, kNoKey);
     }
     if (w == 1) {
         double l = 0.0;                                            // fixed order of addition
 #pragma unroll
         for (int i = 0; i < kStreamers; ++i) l += (double)s.wave_l[i];
-        if (lane == 0) {
-            store_shared_result(&a.part_m[pslot], s.cmax);
-            store_shared_result(&a.part_l[pslot], l);
-        }
+        if (lane < 2)
+            store_shared_result(&a.part_lm[pslot * 2 + lane], lane == 0 ? (uint64_t)__double_as_longlong(l) | kSumMark : uint64_t(1) << 32 | __float_as_uint(s.cmax));
     }
-    const bool direct = a.F * a.nchunks <= kDirectArrivals;
-    unsigned int *const counter = direct ? &a.counters[0] : &a.counters[(1 + f) * kCounterStride];
-    if (publish_then_ticket(counter, &s.ticket) != (unsigned int)((direct ? a.F : 1) * a.nchunks - 1)) return;
+    if (!s.last) return;
+    if (tid <= a.F) store_shared_result(&a.counters[tid * kCounterStride], 0u);      // (all have counted)
 
-    // ---- last chunk of row f: the row is complete; count it.  Only the workgroup that completes
-    // the last row goes on (its predecessors' partials were all acknowledged before their tickets).
-    if (!direct) {
-        if (tid == 0) {
-            store_shared_result(counter, 0u);                      // leave the row counter clean
-            s.ticket2 = __hip_atomic_fetch_add(&a.counters[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        if (s.ticket2 != (unsigned int)(a.F - 1)) return;
-    }
-    if (tid == 0) store_shared_result(&a.counters[0], 0u);
-
-    // ================= last workgroup of the call
-    expand_finish<MODE>(a, s, bz, cycle, cycle_first, [] { return true; },
+    // ================= the workgroup that finishes the call
+    expand_finish<MODE, true>(a, s, bz, cycle, cycle_first, [] { return true; },
                         [&](int row) { return load_shared_result(&a.gate_pre[row]); });
 }
 
@@ -784,7 +859,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
     // sequence's workgroups, eight rows each, as the single launch does; the finish kernel reads it.
     if (a.has_policy && a.pol_has_state) {
         const int bz = row / a.F;
-        float *gate = a.gate_pre + (size_t)bz * (4 * kPolH);
+        float *gate = a.gate_pre + (size_t)bz * (kCounterBytes / sizeof(float));
         HiddenRows<4, kStreamThreads / 32> hrows;
         hrows.load(a.pol, bz, (row - bz * a.F) * gridDim.x + blockIdx.x, a.F * gridDim.x, threadIdx.x / 32);
         hrows.finish(a.pol, bz, [&](int r, float v) { gate[r] = v; });
@@ -933,16 +1008,16 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
         double l = 0.0;
 #pragma unroll
         for (int i = 0; i < kStreamWaves; ++i) l += wave_l[i];
-        a.part_m[slot] = cm;
-        a.part_l[slot] = l;
+        a.part_lm[slot * 2] = (uint64_t)__double_as_longlong(l) & ~kSumMark;
+        a.part_lm[slot * 2 + 1] = __float_as_uint(cm);
     }
 }
 
 // one workgroup per sequence, after expand_stream_kernel
 template <int MODE>
-__global__ __launch_bounds__(kExpThreads, 1) void expand_finish_kernel(const uint64_t *part_keys, const double *part_l, const float *part_m, int F, int nchunks,
+__global__ __launch_bounds__(kExpThreads, 1) void expand_finish_kernel(uint64_t *part_keys, uint64_t *part_lm, int F, int nchunks,
                                                                        int k, int pool_count, radar_cycle_state *cycle_, ExpandArgs a) {
-    a.part_keys = const_cast<uint64_t *>(part_keys); a.part_l = const_cast<double *>(part_l); a.part_m = const_cast<float *>(part_m);
+    a.part_keys = part_keys; a.part_lm = part_lm;
     a.F = F; a.nchunks = nchunks; a.k = k; a.pool_count = pool_count; a.cycle = cycle_;
     __shared__ ExpandSmem s;
     const int bz = blockIdx.x;
@@ -950,7 +1025,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_finish_kernel(const uin
     radar_cycle_state *const cycle = a.cycle;
     const bool cycle_first = cycle != nullptr && a.pool_count == 0;
     // (the prediction model's input-free part was left in the workspace by the streaming kernel)
-    expand_finish<MODE>(a, s, bz, cycle, cycle_first, [&] { return !cycle_skips(cycle, a.pool_count, &a.pool_count); },
+    expand_finish<MODE, false>(a, s, bz, cycle, cycle_first, [&] { return !cycle_skips(cycle, a.pool_count, &a.pool_count); },
                         [&](int row) { return a.gate_pre[row]; });
 }
 
@@ -1037,9 +1112,8 @@ static radar_status launch_expand(const float *logits, const float *parent_score
     a.counters = reinterpret_cast<unsigned int *>(ws);
     a.part_keys = reinterpret_cast<uint64_t *>(ws + cbytes);
     const size_t nslots = nb * d->F * nchunks;
-    a.part_l = reinterpret_cast<double *>(ws + cbytes + nslots * RADAR_K_MAX * sizeof(uint64_t));
-    a.part_m = reinterpret_cast<float *>(ws + cbytes + nslots * (RADAR_K_MAX * sizeof(uint64_t) + sizeof(double)));
-    a.gate_pre = reinterpret_cast<float *>(ws + expand_workspace_bytes(d, nb) - expand_gate_bytes(nb));
+    a.part_lm = a.part_keys + nslots * RADAR_K_MAX;
+    a.gate_pre = reinterpret_cast<float *>(ws + (stream ? kStreamGateOffset : kGateOffset));
     a.cycle = cycle;
     a.pol = pol ? *pol : PolicyArgs{};
     a.has_policy = pol ? 1 : 0;
@@ -1057,7 +1131,7 @@ static radar_status launch_expand(const float *logits, const float *parent_score
         e = vec4 ? go(expand_stream_kernel<true>) : go(expand_stream_kernel<false>);
         if (e != hipSuccess) return RADAR_HIP_ERROR;
         auto fin = [&](auto kernel) {
-            return launch("expand_finish", kernel, dim3((unsigned)B), block, 0, st, a.part_keys, a.part_l, a.part_m, a.F, a.nchunks, a.k, a.pool_count, a.cycle, a);
+            return launch("expand_finish", kernel, dim3((unsigned)B), block, 0, st, a.part_keys, a.part_lm, a.F, a.nchunks, a.k, a.pool_count, a.cycle, a);
         };
         e = pol ? fin(expand_finish_kernel<kExpPolicy>) : fin(expand_finish_kernel<kExpExt>);
         return e == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;

@@ -138,6 +138,9 @@ struct HiddenRows {
     }
 };
 
+// Which of the 4H gate rows a thread of the upper half of the workgroup holds.
+__device__ __forceinline__ int policy_gate_row() { return (threadIdx.x & 3) * kPolH + (((int)threadIdx.x - kPolThreads / 2) >> 2); }
+
 // Request what the step for state b will need, the head's rows (policy_fetch_head) and the rest, by the
 // kPolThreads threads of one workgroup; nothing waits here.  Every load is from a clamped, valid address, taken or not (rows and columns that do not
 // exist are discarded where the values are used); only which kind of load a wavefront makes depends on
@@ -157,7 +160,7 @@ template <bool EARLY, typename Hidden>
 __device__ __forceinline__ void policy_fetch_rest(const PolicyArgs &p, int b, bool has_state, PolicyRegs &r, Hidden &&hidden) {
     const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
     if (w >= kPolWaves / 2) {
-        const int unit = (tid - kPolThreads / 2) >> 2, row = (tid & 3) * kPolH + unit;
+        const int unit = (tid - kPolThreads / 2) >> 2, row = policy_gate_row();
         const float *src = p.w_ih + (size_t)row * p.k;
 #pragma unroll
         for (int i4 = 0; i4 < RADAR_K_MAX; i4 += 4) {                // (the conditions are the same in every lane)

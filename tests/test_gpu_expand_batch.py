@@ -209,6 +209,42 @@ def test_streaming_path_with_cycle_states(oracle):
         assert np.max(np.abs(host(pool.scores)[q, lo:hi].astype(np.float64) - cp["scores"][lo:hi])) <= SCORE_TOL
 
 
+@pytest.mark.parametrize("B", [1, 4])
+def test_forms_of_the_call_follow_each_other_on_one_workspace(B):
+    """One launch and two, few chunks and many, with and without the model (a zero state among them: zeros are handed over,
+    too), in turn on one workspace and each on a fresh one: the same bits, and words of a single launch are cleared."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(synth.seed_for(9, 400 + B))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(400 + B)
+    shapes = [(1, 128256, 10), (10, 128256, 10), (7, 4097, 16), (1, 300000, 16), (64, 4096, 2), (10, 128256, 16), (3, 5, 5)]   # B = 4: the second and sixth in two launches
+    largest = max(b.radar_draft_expand_batch_workspace_bytes(b.expand_desc(F, V, k, 0, F * k), B) for F, V, k in shapes)
+    shared = b.new_workspace(largest)
+    params = {k: b.policy_params({n: dev(v) for n, v in synth.policy_params(rng, k).items()}) for _, _, k in shapes}
+    for turn in range(3):
+        for i, (F, V, k) in enumerate(shapes):
+            x = torch.randn((B, F, V), generator=gen, device="cuda")
+            x[0, 0] = 0.0 if turn == 1 else x[0, 0]                # a row of zeros
+            x[0, F - 1, V // 2:] = float("-inf") if turn == 2 else x[0, F - 1, V // 2:]
+            ps, ppi = torch.zeros((B, F), device="cuda"), torch.full((B, F), -1, dtype=torch.int32, device="cuda")
+            model = (i + turn) % 3                                 # none, without a state, with one
+            got = []
+            for ws in (shared, b.new_workspace(largest)):
+                kw = {}
+                if model:
+                    kw = dict(params=params[k], policy_out=b.PolicyOut(B, synth.POLICY_H, "cuda"))
+                if model == 2:
+                    kw.update(h=torch.zeros((B, synth.POLICY_H), device="cuda") if turn else torch.full((B, synth.POLICY_H), 0.25, device="cuda"),
+                              c=torch.ones((B, synth.POLICY_H), device="cuda"))
+                pool = b.DraftPool(F * k, B=B)
+                g, pol = b.radar_draft_expand_batch(x, ps, ppi, k, pool, out=b.ExpandOut(F, k, "cuda", B=B), workspace=ws, **kw)
+                got.append([host(t).copy() for t in list(vars(g).values()) + [pool.tokens, pool.scores, pool.parents] +
+                            ([getattr(pol, n) for n in b.PolicyOut.__slots__] if model else [])])
+            assert all(np.array_equal(p, q, equal_nan=True) for p, q in zip(*got)), (turn, F, V, k, model)
+            if B * F * V < 4 << 20:
+                assert int(ws.view(torch.int32).abs().sum().item()) == 0
+
+
 @pytest.mark.parametrize("B,count,cap,N", [(5, 810, 900, 60), (3, 4096, 4096, 63), (4, 3, 10, 7), (2, 0, 4, 5), (70, 64, 64, 0)])
 def test_batched_rerank_matches_oracle_per_sequence(oracle, B, count, cap, N):
     """radar_draft_rerank_batch without states: forests with exact score ties, every sequence its own."""
