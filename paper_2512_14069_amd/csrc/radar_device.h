@@ -36,7 +36,7 @@ __device__ __forceinline__ float key_value(uint64_t key) { return float_of_ord(u
 // the row's reduction; the four rows are then combined through scalar reads.
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
 template <int CTRL>
 __device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {

@@ -40,11 +40,9 @@ constexpr int kFrontierMax = 256;                     // candidates of a call th
 constexpr int64_t kStreamMinLogits = 4 << 20;         // batched calls of at least 16 MB of logits take the streaming path
 
 // What the workgroups of a single launch hand over vouches for itself: the reader looks until every word is there.  A key there
-// has bits 31 and 30 of its lower half as 01 (as 11 where the two-launch form left it), a sum its sign bit set and a maximum 1 in its
-// upper half; the reader clears what it has read, and nothing else that a workspace can hold looks like that.
-constexpr uint64_t kKeyMark = uint64_t(1) << 31, kSumMark = uint64_t(1) << 63;
-constexpr uint64_t kNoKey = uint64_t(1) << 30;        // an empty slot of a list: below every key
-constexpr uint32_t kKeyIndexMask = (1u << 30) - 1;
+// and a sum have bit 63 set (what the two-launch form leaves does not), a maximum has 1 in its upper half; the reader clears what it has
+// read, and nothing else that a workspace can hold looks like that.  An empty slot of a list is a mark without a key.
+constexpr uint64_t kThere = uint64_t(1) << 63;
 constexpr size_t kGateOffset = 12288, kStreamGateOffset = 14336;   // the prediction model's w_hh h (of which no value is 0 in a single launch), in the counter block
 static_assert((1 + RADAR_F_MAX) * kCounterStride * sizeof(unsigned int) <= kGateOffset && kGateOffset + 4 * kPolH * sizeof(float) <= kStreamGateOffset &&
               kStreamGateOffset + 4 * kPolH * sizeof(float) <= kCounterBytes, "counter block");
@@ -69,7 +67,7 @@ struct ExpandArgs {
     int F, V, k, nchunks, pool_count;
     int pool_capacity;          // length of one sequence's pool arrays (their stride in a batched call)
     unsigned int *counters;     // [0] rows finished, [(1+f) * kCounterStride] chunks of row f finished
-    uint64_t *part_keys;        // [F][nchunks][RADAR_K_MAX] in any order, kNoKey (two launches: 0) where a chunk has fewer
+    uint64_t *part_keys;        // [F][nchunks][RADAR_K_MAX] in any order, 0 where a chunk has fewer
     uint64_t *part_lm;          // [F][nchunks][2] sum of exp(x - m) over the chunk, and its maximum m in the lower half
     PolicyArgs pol;             // prediction model run by the last workgroup when has_policy != 0
     float *gate_pre;            // [4H] w_hh h of that model, computed by the first workgroups of the launch
@@ -91,15 +89,14 @@ struct alignas(16) ExpandSmem {
     float cand_sc[RADAR_F_MAX * 16];
     int cand_tok[RADAR_F_MAX * 16];
     alignas(16) uint64_t cand_key[kFrontierMax];
-    int rank[kExpThreads];                        // larger keys in each part of cand_key
     PolicySmem pol;
     int last;                                     // this workgroup finishes the call
 };
 
-__device__ __forceinline__ bool key_there(uint64_t w) { return ((uint32_t)w >> 30) == 1u; }
-__device__ __forceinline__ bool sum_there(uint64_t w) { return (int64_t)w < 0; }
+__device__ __forceinline__ bool word_there(uint64_t w) { return (int64_t)w < 0; }                   // a key's or a sum's
 __device__ __forceinline__ bool max_there(uint64_t w) { return (uint32_t)(w >> 32) == 1u; }
-__device__ __forceinline__ double sum_of_word(uint64_t w) { return __longlong_as_double((long long)(w & ~kSumMark)); }   // (sums are not negative)
+__device__ __forceinline__ uint64_t key_of_word(uint64_t w) { return w & ~kThere; }
+__device__ __forceinline__ double sum_of_word(uint64_t w) { return __longlong_as_double((long long)(w & ~kThere)); }   // (sums are not negative)
 __device__ __forceinline__ float max_of_word(uint64_t w) { return __uint_as_float((uint32_t)w); }
 
 // A word of the hand-over, of which w is what the first look saw.
@@ -118,13 +115,13 @@ __device__ __forceinline__ void load_key_block(const uint64_t *pk, int nslot, in
     for (unsigned int looks = 0; POLL && looks < kPollLimit; ++looks) {            // a look asks only for what the one before did not see
         bool all = true;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) all = all && key_there(kk[e]);
+        for (int e = 0; e < 8; ++e) all = all && word_there(kk[e]);
         if (__ballot(!all) == 0) break;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) if (!key_there(kk[e])) kk[e] = load_shared_result(pk + slot(e));
+        for (int e = 0; e < 8; ++e) if (!word_there(kk[e])) kk[e] = load_shared_result(pk + slot(e));
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) kk[e] = c0 + topk_slot_of(e) < nslot ? kk[e] : 0;
+    for (int e = 0; e < 8; ++e) kk[e] = c0 + topk_slot_of(e) < nslot ? key_of_word(kk[e]) : 0;
     kk[8] = 0;
 }
 
@@ -152,36 +149,19 @@ __device__ __forceinline__ void put_frontier(const ExpandArgs &a, const ExpandSm
 }
 
 // Next frontier: the k largest of n <= kFrontierMax candidates by cumulative score (candidate index breaks
-// ties), by the whole workgroup: a thread counts the keys in a part of the list (an eighth up to 128
-// candidates, else a quarter) that are larger than its candidate's, the counts of the parts add up to the
-// rank, and whoever has a rank below k writes that entry.  (By one wavefront with a threshold, a
-// compaction and a ranking it was a chain of 1.5 us.  What counting costs is LDS bandwidth: a broadcast
-// read takes as long as any other, so no wavefront reads for candidates that do not exist.)
-// s.cand_key holds zeros from n on; a barrier has passed since it was written.  All lanes call.
-template <int WIDE>                                                // candidates per part
-__device__ __forceinline__ void rank_frontier(const ExpandArgs &a, ExpandSmem &s, int n, float *conf_lds) {
-    constexpr int kParts = kExpThreads / WIDE;
-    const int tid = threadIdx.x, c = tid % WIDE, part = tid / WIDE;
-    const int per = (n + 2 * kParts - 1) / (2 * kParts) * 2;       // keys per part
-    if (c - lane_id() < n) {                                       // wave-uniform
-        const uint64_t mine = s.cand_key[c];
-        int larger = 0;
-        for (int j = part * per; j < (part + 1) * per; j += 2) {
-            const uint64_t k0 = s.cand_key[j], k1 = s.cand_key[j + 1];
-            larger += (k0 > mine ? 1 : 0) + (k1 > mine ? 1 : 0);
-        }
-        s.rank[tid] = larger;
-    }
-    __syncthreads();
-    if (tid < n) {
-        int at = 0;
+// ties), by one wavefront.  s.cand_key holds zeros from n on.  (By the whole workgroup, each candidate's larger ones counted in parts of the
+// list, it was bound by LDS: a broadcast read takes as long as any other, 0.4 us of them for 100 candidates.)
+template <int EPL>
+__device__ __forceinline__ void pick_frontier(const ExpandArgs &a, ExpandSmem &s, int n, float *conf_lds) {
+    const int lane = lane_id();
+    uint64_t kk[EPL];
 #pragma unroll
-        for (int i = 0; i < kParts; ++i) at += s.rank[i * WIDE + tid];
-        if (at < a.k) put_frontier(a, s, at, tid, conf_lds);
-    }
+    for (int e = 0; e < EPL; ++e) kk[e] = s.cand_key[e * kWave + (lane >> 1) + 32 * (lane & 1)];   // (the lanes of a pair far apart: a row's candidates are sorted)
+    const Picked p = wave_pick<EPL>(kk, a.k, s.wtk[0]);
+    if (p.rank < a.k) put_frontier(a, s, p.rank, min((int)pick_index(p.key), n - 1), conf_lds);   // (beyond n: only with NaN scores)
 }
 
-// The same for any number of candidates, by one wavefront.
+// The same for any number of candidates.
 __device__ __forceinline__ void select_frontier(const ExpandArgs &a, ExpandSmem &s, int n, float *conf_lds) {
     const int lane = lane_id(), K = a.k, nfs = a.F * 16;           // slot i: rank i % 16 of row i / 16
     uint64_t top = 0;
@@ -191,14 +171,14 @@ __device__ __forceinline__ void select_frontier(const ExpandArgs &a, ExpandSmem 
         for (int e = 0; e < 8; ++e) {
             const int i = c0 + topk_slot_of(e), c = (i >> 4) * K + (i & 15);
             const float sc = s.cand_sc[min(c, n - 1)];
-            kk[e] = (i < nfs && (i & 15) < K) ? make_key(sc, uint32_t(c)) : 0;
+            kk[e] = (i < nfs && (i & 15) < K) ? pick_key(sc, uint32_t(c)) : 0;
         }
         kk[8] = top;
         top = wave_topk<9>(kk, K, s.wtk[0]);
     }
     if (lane < K) {
-        int c = (int)key_index(top);
-        if (c < 0 || c >= n) c = 0;                               // only reachable with NaN scores
+        int c = (int)pick_index(top);
+        if (c >= n) c = 0;                                        // only reachable with NaN scores
         put_frontier(a, s, lane, c, conf_lds);
     }
 }
@@ -272,15 +252,16 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
                 for (unsigned int looks = 0; looks < kPollLimit; ++looks) {
                     bool missing[3];
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) missing[e] = !(key_there(w2[e][0]) && key_there(w2[e][1])) && at[e] < nslot * (int)sizeof(uint64_t);
-                    missing[2] = !(sum_there(w2[2][0]) && max_there(w2[2][1]));
+                    for (int e = 0; e < 2; ++e) missing[e] = !(word_there(w2[e][0]) && word_there(w2[e][1])) && at[e] < nslot * (int)sizeof(uint64_t);
+                    missing[2] = !(word_there(w2[2][0]) && max_there(w2[2][1]));
                     if (__ballot(missing[0] || missing[1] || missing[2]) == 0) break;
                     asm volatile("" ::: "memory");                 // (else the loads are the ones before)
 #pragma unroll
                     for (int e = 0; e < 3; ++e) if (missing[e]) look(e);
                 }
             }
-            kk[0] = w2[0][0]; kk[1] = w2[0][1]; kk[2] = w2[1][0]; kk[3] = w2[1][1];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) kk[e] = key_of_word(w2[e >> 1][e & 1]);
             ll = sum_of_word(w2[2][0]);
             ml = max_of_word(w2[2][1]);
         } else {
@@ -288,24 +269,25 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
             pscore = a.parent_scores[fr];
             ppool = a.parent_pool_idx[fr];
             load_key_block<POLL>(pk, nslot, 0, kk);
-            ll = sum_of_word(settled<POLL>(wl, plm + 2 * c, sum_there));
+            ll = sum_of_word(settled<POLL>(wl, plm + 2 * c, word_there));
             ml = max_of_word(settled<POLL>(wm, plm + 2 * c + 1, max_there));
         }
     };
     auto merge_row = [&](int fr, auto &&between) {
         const uint64_t *pk = a.part_keys + (size_t)fr * nslot;
-        uint64_t top;
+        Picked top;
         if (few) {
             const uint64_t k4[4] = {kk[0], kk[1], kk[2], kk[3]};
-            top = wave_topk<4>(k4, K, s.wtk[w], between);
+            top = wave_pick<4>(k4, K, s.wtk[w], between);
         } else {
-            top = row_topk<POLL>(kk, pk, nslot, K, s.wtk[w]);
+            top.key = row_topk<POLL>(kk, pk, nslot, K, s.wtk[w]);
+            top.rank = lane;
         }
         if ((few ? (lane & 15) : lane) >= a.nchunks) { ml = -INFINITY; ll = 0.0; }
         for (int c = lane + kWave; c < a.nchunks; c += kWave) {        // V > 262144 only
             const uint64_t *p = a.part_lm + ((size_t)fr * a.nchunks + c) * 2;
             const uint64_t wl = load_shared_result(p), wm = load_shared_result(p + 1);
-            const double l2 = sum_of_word(settled<POLL>(wl, p, sum_there));
+            const double l2 = sum_of_word(settled<POLL>(wl, p, word_there));
             const float m2 = max_of_word(settled<POLL>(wm, p + 1, max_there));
             const float mn = fmaxf(ml, m2);
             if (mn > -INFINITY)
@@ -335,14 +317,14 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
         // log in fp32 (1 ulp of a value below 14: 1e-6, a tenth of the tolerance on log-probabilities); the
         // fp64 routine costs 0.3 us on this serial path
         const double lse = (double)M + (double)logf((float)L);
-        if (lane < K) {
-            const int tok = (int)(key_index(top) & kKeyIndexMask);
-            const double logp = (double)key_value(top) - lse;
+        if (top.rank < K) {
+            const int tok = (int)pick_index(top.key);
+            const double logp = (double)pick_value(top.key) - lse;
             const float cum = (float)((double)pscore + logp);
-            const int c = fr * K + lane;
+            const int c = fr * K + top.rank;
             s.cand_sc[c] = cum;
             s.cand_tok[c] = tok;
-            if (n <= kFrontierMax) s.cand_key[c] = make_key(cum, uint32_t(c));
+            if (n <= kFrontierMax) s.cand_key[c] = pick_key(cum, uint32_t(c));
             a.cand_tokens[c] = tok;
             a.cand_scores[c] = cum;
             a.pool_tokens[a.pool_count + c] = tok;
@@ -371,9 +353,11 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
     }
     __syncthreads();
     float *const conf = MODE == kExpPolicy ? &s.pol.in[kPolH] : nullptr;
-    if (n <= kFrontierMax / 2) rank_frontier<kFrontierMax / 2>(a, s, n, conf);
-    else if (n <= kFrontierMax) rank_frontier<kFrontierMax>(a, s, n, conf);
-    else if (w == 0) select_frontier(a, s, n, conf);
+    if (w == 0) {
+        if (n <= kFrontierMax / 2) pick_frontier<2>(a, s, n, conf);
+        else if (n <= kFrontierMax) pick_frontier<4>(a, s, n, conf);
+        else select_frontier(a, s, n, conf);
+    }
     auto advance = [&](int action) {                               // by one lane
         if (!cycle) return;
         cycle->pool_count = a.pool_count + n;
@@ -409,15 +393,10 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
 }
 
 // MODE: the plain expansion is compiled without any code for batches, cycle states or the prediction model.
-// A call is a chain of dependent stages, none of which is bound by bandwidth.  Times of the last workgroup at F = 10,
-// V = 128256, k = 10, us after the first one starts: row maxima 1.0, threshold and hot lanes 1.75, candidates
-// and sums 2.5, list stored 2.7, all lists there 3.5, rows merged 5.2, frontier 6.1;
-// a launch adds about 1.  (With lists announced by tickets once their stores were acknowledged they were there at 5.1: a call took 7.9 us, now 7.1;
-// F = 1 6.6 and 6.4, eight rows of 128257 9.2 and 8.1.)
-// 8.2 us per call on warm logits then (8.9 with sixteen groups for the threshold, the exponentials before it
-// and every list ranked), 11.7 instead of 28.9 for 16 rows with k = 16, where the sixteen groups' threshold
-// let whole chunks through.  Lists longer than 16 slots need no ranking at all, but the last workgroup's loads are
-// slow (from beyond its L2, 37 bytes per ns): 24 slots cost it 0.4 us, records of 32 0.7.
+// A call is a chain of dependent stages, none of which is bound by bandwidth: F = 10, V = 128256, k = 10 takes 6.2 us per call on warm logits.
+// (With lists announced by tickets once their stores were acknowledged 7.9; then 7.1, until the selections compared by sign
+// bits and ranked what passes in parts, radar_topk.h: ten rows of 128257 with k = 16 12.2 -> 9.1, of 200000 16.8 -> 9.0.)  Lists longer than 16 slots need no ranking at all, but
+// the last workgroup's loads are slow (from beyond its L2, 37 bytes per ns): 24 slots cost it 0.4 us, records of 32 0.7.
 // The leading arguments are what the stream waits for; they are in registers when the kernel starts (0.25 us).
 //
 // Up to how many workgroups all count on one counter: they wait for each other there, some 10 ns each, but the last one is
@@ -433,7 +412,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     a.logits = logits; a.F = F; a.V = V; a.k = k; a.nchunks = nchunks; a.pool_count = pool_count;
     a.cycle = cycle_; a.part_keys = part_keys; a.counters = counters;
     static_assert(EPT == 4 || EPT == 8 || EPT == 16, "EPT");
-    static_assert(kFastCap + 8 <= kWave * kWaveTopkMaxEPL + 8 && kExpWaves == 16 && kStreamers == 4, "candidate list inside the selection scratch");
+    static_assert(kFastCap <= kWave * kWaveTopkMaxEPL && kExpWaves == 16 && kStreamers == 4, "candidate list inside the selection scratch");
     constexpr int kChunk = kExpThreads * EPT;
     __shared__ ExpandSmem s;
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
@@ -460,7 +439,8 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     // there (counted at the start, one row of V = 200000 7.14 us, so 6.74; counted beside the candidates 6.93).
     const bool direct = a.F * a.nchunks <= kDirectArrivals, counting = w == kExpWaves - 1 && lane == 0;
     unsigned int before = 0;
-    if (counting && !direct) before = __hip_atomic_fetch_add(&a.counters[(1 + f) * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    constexpr bool kCountFirst = VEC4 || EPT < 16;                 // (else there is no register to keep the count in)
+    if (kCountFirst && counting && !direct) before = __hip_atomic_fetch_add(&a.counters[(1 + f) * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // ---- stream the chunk.  Only the first four wavefronts (one per SIMD) stream and select: a
     // 64-wide vector instruction occupies its SIMD for four cycles whichever wavefront issues it, so
@@ -532,12 +512,12 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     // Lanes whose largest logit reaches the threshold (about 1.2 k of the 256) leave all their logits
     // in LDS; only those are compared one by one afterwards.
     float *const dump = reinterpret_cast<float *>(&s.wtk[1]);      // [kStreamers][kDumpCap][NE], inside the selection scratch
-    uint64_t *const surv = s.wtk[0].surv;                          // kFastCap + 8 slots
+    uint64_t *const surv = s.wtk[0].surv;                          // complements; room for kFastCap + kPickPad
     static_assert(kStreamers * kDumpCap * NE * sizeof(float) <= (kExpWaves - 1) * sizeof(WaveTopkSmem), "dump inside the scratch");
     float cm = 0.f;                                                // chunk maximum (streamers)
     if (streamer) {
         const float g32 = s.gmax[lane & 31];
-        const float tau = float_of_ord(kth_of_32(ord_of(g32), K));
+        const float tau = kth_threshold(g32, K);
         const bool hot = lmax >= tau && base + tid * 4 < a.V;      // (a lane wholly past the row holds -inf only)
         const uint64_t hm = __ballot(hot);
         if (hot) {
@@ -558,7 +538,8 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
         const auto c2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(cm), __float_as_uint(cm), false, false);
         cm = fmaxf(__uint_as_float(c2[0]), __uint_as_float(c2[1]));
     } else {
-        if (counting && direct) before = __hip_atomic_fetch_add(&a.counters[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (counting && (direct || !kCountFirst))
+            before = __hip_atomic_fetch_add(&a.counters[direct ? 0 : (1 + f) * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // The arguments that only the call's end needs are brought close by now: read by the last workgroup when it
         // gets there, each cache line of them would be a round trip of its own (0.3 us).
         asm volatile("" :: "s"(a.parent_scores), "s"(a.pool_scores), "s"(a.part_lm));
@@ -606,7 +587,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
                         int at = 0;
                         if (lane == 0) at = (int)atomicAdd(&s.nsurv, (unsigned int)__popcll(m));
                         at = (int)readlane_u32((uint32_t)at, 0) + lanes_below(m);
-                        if (((m >> lane) & 1) && at < kFastCap) surv[at] = make_key(v, uint32_t(idx));
+                        if (((m >> lane) & 1) && at < kFastCap) surv[at] = ~pick_key(v, uint32_t(idx));
                     }
                 }
             }
@@ -631,7 +612,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
                 for (int u = 0; u < 8; ++u) {
                     const int idx = base + (g0 + (u >> 2)) * (kSLanes * 4) + tid * 4 + (u & 3);
                     const float v = row[min(idx, a.V - 1)];
-                    kk[u] = idx < a.V ? make_key(v, uint32_t(idx)) : 0;
+                    kk[u] = idx < a.V ? pick_key(v, uint32_t(idx)) : 0;
                 }
                 kk[8] = wt;
                 wt = wave_topk<9>(kk, K, s.wtk[w]);
@@ -645,37 +626,23 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
 #pragma unroll
             for (int e = 0; e < NS; ++e) k2[e] = s.wlist[e * kWave + lane];
             const uint64_t top = wave_topk<NS>(k2, K, s.wtk[0]);
-            if (lane < RADAR_K_MAX) store_shared_result(list + lane, top != 0 ? top ^ kKeyMark : kNoKey);      // lanes from K on hold 0
+            if (lane < RADAR_K_MAX) store_shared_result(list + lane, top | kThere);      // lanes from K on hold 0
         }
     } else if (w == 0 && nsurv <= RADAR_K_MAX) {
         // the candidates as they are: the finishing workgroup ranks them with the other chunks'
-        if (lane < RADAR_K_MAX) store_shared_result(list + lane, lane < nsurv ? surv[lane] ^ kKeyMark : kNoKey);
+        if (lane < RADAR_K_MAX) store_shared_result(list + lane, lane < nsurv ? ~surv[lane] | kThere : kThere);
     } else if (w == 0) {
-        // More candidates than slots (k = 10: one chunk in a hundred; k above 12: most): the k best of them, by exact
-        // ranks; every lane counts the larger keys with broadcast reads.
-        if (lane < 8) surv[nsurv + lane] = 0;                      // padding for the grouped reads
-        wave_lds_sync();
-        for (int i0 = 0; i0 < nsurv; i0 += kWave) {                // one pass unless there are many ties
-            const int i = i0 + lane;
-            const uint64_t key = surv[min(i, nsurv - 1)];
-            int rank = 0;
-            for (int j = 0; j < nsurv; j += 8) {
-                uint64_t kj[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) kj[u] = surv[j + u];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) rank += (kj[u] > key) ? 1 : 0;
-            }
-            if (i < nsurv && rank < K) store_shared_result(list + rank, key ^ kKeyMark);   // ranks are distinct
-        }
-        if (lane >= K && lane < RADAR_K_MAX) store_shared_result(list + lane, kNoKey);
+        // more candidates than slots (k = 10: one chunk in a hundred; k above 12: most): the k best of them
+        const Picked p = rank_survivors(surv, s.wtk[0].top, nsurv, K);
+        if (p.rank < K) store_shared_result(list + p.rank, p.key | kThere);          // ranks are distinct
+        if (lane >= K && lane < RADAR_K_MAX) store_shared_result(list + lane, kThere);
     }
     if (w == 1) {
         double l = 0.0;                                            // fixed order of addition
 #pragma unroll
         for (int i = 0; i < kStreamers; ++i) l += (double)s.wave_l[i];
         if (lane < 2)
-            store_shared_result(&a.part_lm[pslot * 2 + lane], lane == 0 ? (uint64_t)__double_as_longlong(l) | kSumMark : uint64_t(1) << 32 | __float_as_uint(s.cmax));
+            store_shared_result(&a.part_lm[pslot * 2 + lane], lane == 0 ? (uint64_t)__double_as_longlong(l) | kThere : uint64_t(1) << 32 | __float_as_uint(s.cmax));
     }
     if (!s.last) return;
     if (tid <= a.F) store_shared_result(&a.counters[tid * kCounterStride], 0u);      // (all have counted)
@@ -826,7 +793,8 @@ constexpr int kStreamCap = 128;                                    // candidates
 
 struct StreamFast {
     alignas(16) float dump[kStreamWaves][kStreamHot * kStreamEPT];
-    uint64_t surv[kStreamCap + 8];
+    alignas(16) uint64_t surv[kStreamCap + kPickPad];              // complements
+    uint64_t top[16];
     unsigned char lane_of[kStreamWaves][kStreamHot];
 };
 
@@ -918,7 +886,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
     }
     const double wl = wave_sum_f64(((double)tl[0] + (double)tl[1]) + ((double)tl[2] + (double)tl[3]));
     if (lane == 0) wave_l[w] = wl;
-    const float tau = float_of_ord(kth_of_32(ord_of(g32), K));
+    const float tau = kth_threshold(g32, K);
 
     // ---- Lanes whose largest logit reaches the threshold (1.2 k to 1.4 k of the 256) leave all their logits in
     // LDS; their wavefront compares those one per lane and appends what passes to the chunk's list.  (A
@@ -948,7 +916,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
                 int at = 0;
                 if (lane == 0) at = (int)atomicAdd(&nsurv, (unsigned int)__popcll(m));
                 at = (int)readlane_u32((uint32_t)at, 0) + lanes_below(m);
-                if (((m >> lane) & 1) && at < kStreamCap) s.fast.surv[at] = make_key(v, uint32_t(idx));
+                if (((m >> lane) & 1) && at < kStreamCap) s.fast.surv[at] = ~pick_key(v, uint32_t(idx));
             }
         }
     }
@@ -966,7 +934,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
             for (int u = 0; u < 8; ++u) {
                 const int idx = base + (g0 + (u >> 2)) * (kStreamThreads * 4) + tid * 4 + (u & 3);
                 const float v = rowp[min(idx, a.V - 1)];
-                kk[u] = idx < a.V ? make_key(v, uint32_t(idx)) : 0;
+                kk[u] = idx < a.V ? pick_key(v, uint32_t(idx)) : 0;
             }
             kk[8] = wt;
             wt = wave_topk<9>(kk, K, s.ties.wtk[w]);
@@ -983,32 +951,18 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
         }
     } else if (w == 0 && n <= RADAR_K_MAX) {
         // the candidates as they are: the finishing workgroup ranks them with the other chunks'
-        if (lane < RADAR_K_MAX) a.part_keys[slot * RADAR_K_MAX + lane] = lane < n ? s.fast.surv[lane] : 0;
+        if (lane < RADAR_K_MAX) a.part_keys[slot * RADAR_K_MAX + lane] = lane < n ? ~s.fast.surv[lane] : 0;
     } else if (w == 0) {
-        // more than that: the k best, by exact ranks; every lane counts the larger keys with broadcast reads
-        uint64_t *const surv = s.fast.surv;
-        if (lane < 8) surv[n + lane] = 0;                          // padding for the grouped reads
-        wave_lds_sync();
-        for (int i0 = 0; i0 < n; i0 += kWave) {                    // one pass unless there are many ties
-            const int i = i0 + lane;
-            const uint64_t key = surv[min(i, n - 1)];
-            int rank = 0;
-            for (int q = 0; q < n; q += 8) {
-                uint64_t kj[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) kj[u] = surv[q + u];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) rank += (kj[u] > key) ? 1 : 0;
-            }
-            if (i < n && rank < K) a.part_keys[slot * RADAR_K_MAX + rank] = key;
-        }
+        // more than that: the k best
+        const Picked p = rank_survivors(s.fast.surv, s.fast.top, n, K);
+        if (p.rank < K) a.part_keys[slot * RADAR_K_MAX + p.rank] = p.key;
         if (lane >= K && lane < RADAR_K_MAX) a.part_keys[slot * RADAR_K_MAX + lane] = 0;
     }
     if (w == 1 && lane == 0) {                                     // fixed order of addition
         double l = 0.0;
 #pragma unroll
         for (int i = 0; i < kStreamWaves; ++i) l += wave_l[i];
-        a.part_lm[slot * 2] = (uint64_t)__double_as_longlong(l) & ~kSumMark;
+        a.part_lm[slot * 2] = (uint64_t)__double_as_longlong(l) & ~kThere;
         a.part_lm[slot * 2 + 1] = __float_as_uint(cm);
     }
 }

@@ -116,117 +116,148 @@ __device__ __forceinline__ void block_topk(const uint64_t (&keys)[EPT], int K, T
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same selection inside ONE wavefront, without workgroup barriers: K <= 16 largest of the
-// 64 * EPL keys its lanes hold.  The 16 quads of the wavefront are the groups (tau = K-th
-// largest quad maximum, so at least K keys pass; callers spread their keys over the quads, or
-// few quads hold anything and tau filters little), survivors are compacted into the
-// wavefront's private LDS scratch and ranked exactly.  Returns the r-th largest key in lane r
-// (r < 16; 0 where fewer exist, and in lanes >= 16).  Callers on different wavefronts pass
-// different scratch; all 64 lanes must call.
-constexpr int kWaveTopkMaxEPL = 9;
+// The same selection inside ONE wavefront, without workgroup barriers: the K <= 16 largest of the 64 * EPL keys its
+// lanes hold.  These keys have 63 bits (the index keeps 31), so that a difference of two has its sign in bit 63.
+//
+// How things are compared here: a vector compare leaves its result in scalar registers, and the instruction that counts it has to
+// wait for that (four issue slots in all, in a lone wavefront, whose every slot is on the critical path); a subtraction leaves
+// it in the sign bit, and one alignbit appends that bit to a mask, whose ones are counted at the end: two slots, no wait.
+// Values that are only grouped by a threshold are compared without their lowest bit, which leaves room for the sign; what the
+// threshold promises still holds.
+__device__ __forceinline__ uint64_t pick_key(float x, uint32_t idx) { return (uint64_t)ord_of(x) << 31 | (~idx & 0x7fffffffu); }
+__device__ __forceinline__ uint32_t pick_index(uint64_t key) { return ~(uint32_t)key & 0x7fffffffu; }
+__device__ __forceinline__ float pick_value(uint64_t key) { return float_of_ord((uint32_t)(key >> 31)); }
 
+__device__ __forceinline__ uint32_t append_sign(uint32_t mask, uint32_t v) { return __builtin_amdgcn_alignbit(mask, v, 31); }   // mask << 1 | v >> 31
+
+// K-th largest (K <= 16) of 32 values below 2^31, of which every lane passes number lane % 32; the result is the same in
+// every lane.  Rows 0 and 1 of the wavefront count what is not smaller among values 0-15, rows 2 and 3 (which
+// hold the same values again) among 16-31, by row rotations of the complements: g + ~c is negative if c >= g.
+// (An addition: subtracting a rotated operand came out with the other sign, v_subrev_u32 with a DPP operand.)
 template <int ROR>
-__device__ __forceinline__ void count_larger(uint32_t g, int &larger) {
+__device__ __forceinline__ void mark_not_smaller(uint32_t nc, uint32_t g, uint32_t &mask) {
     if constexpr (ROR < 16) {
-        larger += dpp_u32<0x120 + ROR>(g) > g ? 1 : 0;              // row_ror
-        count_larger<ROR + 1>(g, larger);
-    }
-}
-
-// Threshold for a selection of the K <= 16 largest values held by the lanes of one wavefront
-// (v = largest value of the lane, 0 if it holds none): the K-th largest of the 16 quad maxima.
-// At least K values are >= the result (one per quad that reaches it), and unlike the smallest
-// quad maximum it does not collapse when a few quads happen to hold only small values.
-// Never 0, so that absent entries (0) fail the test "value >= threshold".
-// All 16 maxima are brought into every 16-lane row by row swaps (lane 4 i + r of a row receives the
-// maximum of row r's quad i) and ranked there by rotations: vector instructions throughout, where sixteen
-// lane reads cross to the scalar side and back.
-__device__ __forceinline__ uint32_t quad_threshold(uint32_t v, int K) {
-    uint32_t g = v;
-    g = max(g, dpp_u32<0xB1>(g));
-    g = max(g, dpp_u32<0x4E>(g));                 // quad maximum in every lane of the quad
-    const int lane = lane_id();
-    g = (lane & 3) == (lane >> 4) ? g : 0;
-    const auto a = __builtin_amdgcn_permlane16_swap(g, g, false, false);        // rows 0 0 2 2, rows 1 1 3 3
-    g = max(a[0], a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap(g, g, false, false);
-    g = max(b[0], b[1]);
-    int larger = 0;                               // quads whose maximum is strictly larger than this lane's
-    count_larger<1>(g, larger);
-    uint32_t c = larger < K ? g : 0xffffffffu;    // the K largest quad maxima (and their ties) stay
-    c = min(c, dpp_u32<0xB1>(c));
-    c = min(c, dpp_u32<0x4E>(c));
-    c = min(c, dpp_u32<0x141>(c));
-    c = min(c, dpp_u32<0x140>(c));                // smallest of them; the same in every row
-    return max(c, 1u);
-}
-
-// K-th largest (K <= 16) of 32 values, of which every lane passes number lane % 32; the result is the same in
-// every lane.  Rows 0 and 1 of the wavefront count what is larger among values 0-15, rows 2 and 3 (which
-// hold the same values again) among 16-31, by row rotations.
-template <int ROR>
-__device__ __forceinline__ void count_larger_of(uint32_t c, uint32_t g, int &larger) {
-    if constexpr (ROR < 16) {
-        larger += dpp_u32<0x120 + ROR>(c) > g ? 1 : 0;              // row_ror
-        count_larger_of<ROR + 1>(c, g, larger);
+        mask = append_sign(mask, g + dpp_u32<0x120 + ROR>(nc));                 // row_ror
+        mark_not_smaller<ROR + 1>(nc, g, mask);
     }
 }
 __device__ __forceinline__ uint32_t kth_of_32(uint32_t g, int K) {
     const auto ab = __builtin_amdgcn_permlane16_swap(g, g, false, false);       // values 0-15, values 16-31 in every row
-    const uint32_t c = lane_id() < 32 ? ab[0] : ab[1];
-    int larger = c > g ? 1 : 0;
-    count_larger_of<1>(c, g, larger);
-    const auto n = __builtin_amdgcn_permlane32_swap((uint32_t)larger, (uint32_t)larger, false, false);
-    uint32_t k = n[0] + n[1] < (uint32_t)K ? g : 0xffffffffu;      // the K largest (and their ties) stay
-    k = min(k, dpp_u32<0xB1>(k));
-    k = min(k, dpp_u32<0x4E>(k));
-    k = min(k, dpp_u32<0x141>(k));
-    k = min(k, dpp_u32<0x140>(k));
+    const uint32_t nc = ~(lane_id() < 32 ? ab[0] : ab[1]);
+    uint32_t mask = append_sign(0, g + nc);
+    mark_not_smaller<1>(nc, g, mask);
+    const uint32_t n1 = (uint32_t)__popc(mask);
+    const auto n = __builtin_amdgcn_permlane32_swap(n1, n1, false, false);
+    uint32_t k = n[0] + n[1] >= (uint32_t)K ? g : 0;               // what at least K values reach; the largest of that
+    k = max(k, dpp_u32<0xB1>(k));
+    k = max(k, dpp_u32<0x4E>(k));
+    k = max(k, dpp_u32<0x141>(k));
+    k = max(k, dpp_u32<0x140>(k));
     const auto m = __builtin_amdgcn_permlane16_swap(k, k, false, false);
-    return min(m[0], m[1]);
+    return max(m[0], m[1]);
 }
+// The same for the maxima of groups of floats: a threshold that at least K of them reach (at least -inf, whose image is odd).
+__device__ __forceinline__ float kth_threshold(float g, int K) { return float_of_ord(max(kth_of_32(ord_of(g) >> 1, K) << 1, 0x007fffffu)); }
 
+constexpr int kWaveTopkMaxEPL = 9;
+constexpr int kPickPad = 8;                       // entries that survivors may be padded by, where they are more than 32
 struct WaveTopkSmem {
-    uint64_t surv[kWave * kWaveTopkMaxEPL + 8];   // +8: the ranking reads keys eight at a time
+    alignas(16) uint64_t surv[kWave * kWaveTopkMaxEPL + kPickPad];   // complements of the survivors
     uint64_t top[16];
 };
 
-// between() runs once the keys are in LDS and their registers free.
+struct Picked { uint64_t key; int rank; };        // a lane's key and how many are larger; rank kNoRank: none
+constexpr int kNoRank = 1 << 20;
+
+template <int PARTS>                              // up to 64 / PARTS survivors: each is compared in PARTS lanes
+__device__ __forceinline__ Picked rank_among_few(const uint64_t *surv, int n) {
+    constexpr int kMost = kWave / PARTS, kEach = kMost / PARTS;
+    const int lane = lane_id(), i = lane & (kMost - 1), part = lane / kMost;
+    Picked p;
+    p.key = ~surv[i];
+    uint64_t t[kEach];
+#pragma unroll
+    for (int u = 0; u < kEach; ++u) t[u] = surv[part * kEach + u];
+    uint32_t larger = 0;                          // (and the key itself, once)
+#pragma unroll
+    for (int u = 0; u < kEach; ++u) larger = append_sign(larger, (uint32_t)((p.key + t[u]) >> 32));
+    uint32_t c = (uint32_t)__popc(larger);
+    if (PARTS == 4) { const auto a = __builtin_amdgcn_permlane16_swap(c, c, false, false); c = a[0] + a[1]; }
+    const auto b = __builtin_amdgcn_permlane32_swap(c, c, false, false);
+    c = b[0] + b[1];
+    p.rank = lane < n && lane < kMost ? (int)c - 1 : kNoRank;
+    return p;
+}
+
+// The n survivors whose complements are in surv (room for 48 of them, and for kPickPad more), ranked: every one of the K largest is in one lane.
+__device__ __forceinline__ Picked rank_survivors(uint64_t *surv, uint64_t *top, int n, int K) {
+    const int lane = lane_id();
+    if (lane < (n <= 32 ? 16 : kPickPad)) surv[n + lane] = ~0ull;
+    wave_lds_sync();
+    if (n <= 16) return rank_among_few<4>(surv, n);
+    if (n <= 32) return rank_among_few<2>(surv, n);
+    if (lane < 16) top[lane] = 0;
+    wave_lds_sync();
+    for (int i0 = 0; i0 < n; i0 += kWave) {       // one pass unless many values are equal
+        const int i = i0 + lane;
+        const uint64_t key = ~surv[min(i, n - 1)];
+        int rank = -1;
+        for (int j = 0; j < n; j += 8) {          // broadcast reads (every lane reads the same keys), eight in flight
+            uint64_t t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = surv[j + u];
+            uint32_t larger = 0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) larger = append_sign(larger, (uint32_t)((key + t[u]) >> 32));
+            rank += __popc(larger);
+        }
+        if (i < n && rank < K) top[rank] = key;
+    }
+    wave_lds_sync();
+    Picked p;
+    p.key = top[lane & 15];
+    p.rank = lane < K && p.key != 0 ? lane : kNoRank;
+    wave_lds_sync();
+    return p;
+}
+
+// The K largest keys (0: none) and their ranks, each in some lane.  Threshold: the K-th largest of the maxima of the 32 pairs of lanes, so at
+// least K keys pass where there are as many, and of keys in no particular order 1.2 K to 1.4 K.  (Of the maxima of the 16 quads 1.5 K,
+// and all of them for K = 16.)  Survivors are compacted into the wavefront's private scratch.  Callers on different wavefronts pass different
+// scratch; all 64 lanes must call.  between() runs once the keys are in LDS and their registers free.
 struct Nothing { __device__ __forceinline__ void operator()() const {} };
 template <int EPL, typename Between = Nothing>
-__device__ __forceinline__ uint64_t wave_topk(const uint64_t (&keys)[EPL], int K, WaveTopkSmem &s, Between &&between = Between()) {
+__device__ __forceinline__ Picked wave_pick(const uint64_t (&keys)[EPL], int K, WaveTopkSmem &s, Between &&between = Between()) {
     static_assert(EPL <= kWaveTopkMaxEPL, "scratch too small");
     const int lane = lane_id();
     uint32_t tmax = 0;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) tmax = max(tmax, uint32_t(keys[e] >> 32));
-    const uint32_t tau = quad_threshold(tmax, K);
+    tmax = max(tmax, dpp_u32<0xB1>(tmax));
+    tmax = (lane & 1) == (lane >> 5) ? tmax : 0;  // even lanes of one half of the wavefront, odd lanes of the other ...
+    const auto h = __builtin_amdgcn_permlane32_swap(tmax, tmax, false, false);
+    const uint32_t tau = max(kth_of_32(max(h[0], h[1]), K), 1u);   // ... so that both halves hold all 32 (never 0: absent keys do not pass)
 
     int n = 0;                                    // survivors so far (wave-uniform)
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
         const bool keep = uint32_t(keys[e] >> 32) >= tau;
         const uint64_t m = __ballot(keep);
-        if (keep) s.surv[n + lanes_below(m)] = keys[e];
+        if (keep) s.surv[n + lanes_below(m)] = ~keys[e];
         n += __popcll(m);
     }
-    if (lane < 8) s.surv[n + lane] = 0;           // padding for the grouped reads
-    if (lane < 16) s.top[lane] = 0;
     between();
+    return rank_survivors(s.surv, s.top, n, K);
+}
+
+// The same in order: the r-th largest in lane r (r < 16; 0 where fewer exist, and in lanes >= 16).
+template <int EPL>
+__device__ __forceinline__ uint64_t wave_topk(const uint64_t (&keys)[EPL], int K, WaveTopkSmem &s) {
+    const int lane = lane_id();
+    const Picked p = wave_pick<EPL>(keys, K, s);
+    if (lane < 16) s.top[lane] = 0;
     wave_lds_sync();
-    for (int i0 = 0; i0 < n; i0 += kWave) {       // one pass unless nearly everything survived
-        const int i = i0 + lane;
-        const uint64_t key = s.surv[min(i, n - 1)];
-        int rank = 0;
-        for (int j = 0; j < n; j += 8) {          // broadcast reads (every lane reads the same keys),
-            uint64_t kj[8];                       // eight in flight so that their latencies overlap
-#pragma unroll
-            for (int u = 0; u < 8; ++u) kj[u] = s.surv[j + u];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) rank += (kj[u] > key) ? 1 : 0;
-        }
-        if (i < n && rank < K) s.top[rank] = key;
-    }
+    if (p.rank < K) s.top[p.rank] = p.key;
     wave_lds_sync();
     const uint64_t r = s.top[lane & 15];
     wave_lds_sync();                              // scratch may be reused right after the return

@@ -120,6 +120,35 @@ def test_expand_candidate_counts_at_the_edges_of_the_lists(oracle, V, k):
     run_both_step(oracle, b, logits, ps, ppi, k, gp, cp)
 
 
+@pytest.mark.parametrize("F,k", [(8, 16), (9, 15), (16, 16), (17, 16), (2, 1), (12, 10)])    # 128, 135, 256, 272, 2 and 120 candidates
+def test_expand_survivors_at_the_edges_of_the_rankings(oracle, F, k):
+    """What passes a wavefront's threshold is ranked in four parts up to 16 keys, in two up to 32, one by one beyond: rows with that
+    many logits above the rest over all chunks, equal or apart, and every second row like the one before it with the same parent score,
+    so that the frontier's candidates are equal in pairs (their number decides)."""
+    from paper_2512_14069_amd import binding as b
+    V = 60000
+    rng = np.random.default_rng(F * 100 + k)
+    counts = (15, 16, 17, 31, 32, 33, 64, 65, 200)
+    logits = np.empty((F, V), np.float32)
+    for f in range(F):
+        n = counts[(f // 2 + F) % len(counts)]
+        if f % 2 == 0:
+            logits[f] = synth.normal_logits(rng, (V,), 1.0)
+            logits[f, rng.permutation(V)[:n]] = 9.0 if n % 2 else 9.0 + rng.permutation(n).astype(np.float32) / 64
+        else:
+            logits[f] = logits[f - 1]
+    ps, ppi = -(np.arange(F) // 2).astype(np.float32) / 8, np.full(F, -1, np.int32)
+    cp = np_pool(F * k)
+    g = b.radar_draft_expand(dev(logits), dev(ps), dev(ppi), k, b.DraftPool(F * k))
+    r = oracle.draft_expand(logits, ps, ppi, k, cp, 0)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(g.cand_tokens).reshape(F, k), r["cand_tokens"])
+    got = host(g.cand_scores)
+    assert np.max(np.abs(got.reshape(F, k) - r["cand_scores"])) <= SCORE_TOL
+    best = np.lexsort((np.arange(F * k), -got.astype(np.float64)))[:k]           # of the device's own scores: score, then number
+    assert np.array_equal(host(g.frontier_pool_idx), best)
+
+
 @pytest.mark.parametrize("V", [131071, 131073, 200001, 262143, 262144, 262145])
 @pytest.mark.parametrize("F,k", [(1, 10), (4, 16), (8, 10), (10, 3)])
 def test_expand_rows_of_many_chunks(oracle, V, F, k):
