@@ -36,7 +36,7 @@ constexpr int kStreamers = 4;                         // wavefronts of a workgro
 constexpr int kDumpCap = 32;                          // hot lanes of one of them (largest logit reaches the threshold) whose logits go through LDS
 constexpr int kFastCap = 512;                         // chunk candidates ranked by the short path; more (runs of equal values) rank per wavefront
 constexpr int kFewChunks = 16;                        // rows of so many chunks are merged the short way (expand_finish)
-constexpr int kFrontierMax = 256;                     // candidates of a call that are ranked by counting
+constexpr int kFrontierBlock = 128;                   // candidates that are looked at together for the frontier
 constexpr int64_t kStreamMinLogits = 4 << 20;         // batched calls of at least 16 MB of logits take the streaming path
 
 // What the workgroups of a single launch hand over vouches for itself: the reader looks until every word is there.  A key there
@@ -78,7 +78,7 @@ struct ExpandArgs {
 
 struct alignas(16) ExpandSmem {
     WaveTopkSmem wtk[kExpWaves];                  // one scratch per wavefront
-    uint64_t wlist[kExpWaves * kWaveListSlots];   // the wavefronts' candidates of a chunk (0 = none; many ties only)
+    uint64_t wlist[kStreamers * RADAR_K_MAX];     // the streaming wavefronts' best (many ties only)
     float gmax[8 * kStreamers];                   // maxima of the 8-lane groups of the streaming wavefronts
     float wave_l[kStreamers], cmax;               // sum of exp(x - chunk maximum) over each streaming wavefront; the maximum
     unsigned int nsurv;                           // candidates of the chunk that reached the threshold
@@ -88,7 +88,7 @@ struct alignas(16) ExpandSmem {
     // last workgroup only: candidate c = f * k + r (row f, rank r in it)
     float cand_sc[RADAR_F_MAX * 16];
     int cand_tok[RADAR_F_MAX * 16];
-    alignas(16) uint64_t cand_key[kFrontierMax];
+    alignas(16) uint64_t cand_key[RADAR_F_MAX * 16];
     PolicySmem pol;
     int last;                                     // this workgroup finishes the call
 };
@@ -98,44 +98,6 @@ __device__ __forceinline__ bool max_there(uint64_t w) { return (uint32_t)(w >> 3
 __device__ __forceinline__ uint64_t key_of_word(uint64_t w) { return w & ~kThere; }
 __device__ __forceinline__ double sum_of_word(uint64_t w) { return __longlong_as_double((long long)(w & ~kThere)); }   // (sums are not negative)
 __device__ __forceinline__ float max_of_word(uint64_t w) { return __uint_as_float((uint32_t)w); }
-
-// A word of the hand-over, of which w is what the first look saw.
-template <bool POLL, typename There>
-__device__ __forceinline__ uint64_t settled(uint64_t w, const uint64_t *p, There &&there) {
-    if (POLL) for (unsigned int looks = 0; !there(w) && looks < kPollLimit; ++looks) w = load_shared_result(p);
-    return w;
-}
-
-// 512 slots, starting at c0, of one row's chunk lists in the workspace (device-scope loads)
-template <bool POLL>
-__device__ __forceinline__ void load_key_block(const uint64_t *pk, int nslot, int c0, uint64_t (&kk)[9]) {
-    auto slot = [&](int e) { return min(c0 + topk_slot_of(e), nslot - 1); };     // branch-free: clamp, load, mask
-#pragma unroll
-    for (int e = 0; e < 8; ++e) kk[e] = load_shared_result(pk + slot(e));
-    for (unsigned int looks = 0; POLL && looks < kPollLimit; ++looks) {            // a look asks only for what the one before did not see
-        bool all = true;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) all = all && word_there(kk[e]);
-        if (__ballot(!all) == 0) break;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) if (!word_there(kk[e])) kk[e] = load_shared_result(pk + slot(e));
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) kk[e] = c0 + topk_slot_of(e) < nslot ? key_of_word(kk[e]) : 0;
-    kk[8] = 0;
-}
-
-// top-K of one row's chunk lists by one wavefront; kk holds the first 512 slots already
-template <bool POLL>
-__device__ __forceinline__ uint64_t row_topk(uint64_t (&kk)[9], const uint64_t *pk, int nslot, int K, WaveTopkSmem &scratch) {
-    uint64_t top = wave_topk<9>(kk, K, scratch);
-    for (int c0 = 8 * kWave; c0 < nslot; c0 += 8 * kWave) {        // V > 131072 only
-        load_key_block<POLL>(pk, nslot, c0, kk);
-        kk[8] = top;                                                 // the running selection rides along
-        top = wave_topk<9>(kk, K, scratch);
-    }
-    return top;
-}
 
 // Entry `at` of the next frontier is candidate c.  conf_lds, when given, also receives the confidence.
 __device__ __forceinline__ void put_frontier(const ExpandArgs &a, const ExpandSmem &s, int at, int c, float *conf_lds) {
@@ -148,39 +110,28 @@ __device__ __forceinline__ void put_frontier(const ExpandArgs &a, const ExpandSm
     if (conf_lds) conf_lds[at] = conf;
 }
 
-// Next frontier: the k largest of n <= kFrontierMax candidates by cumulative score (candidate index breaks
+// Next frontier: the k largest of n candidates by cumulative score (candidate index breaks
 // ties), by one wavefront.  s.cand_key holds zeros from n on.  (By the whole workgroup, each candidate's larger ones counted in parts of the
 // list, it was bound by LDS: a broadcast read takes as long as any other, 0.4 us of them for 100 candidates.)
-template <int EPL>
+template <bool MANY>                                               // more than kFrontierBlock of them
 __device__ __forceinline__ void pick_frontier(const ExpandArgs &a, ExpandSmem &s, int n, float *conf_lds) {
     const int lane = lane_id();
-    uint64_t kk[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) kk[e] = s.cand_key[e * kWave + (lane >> 1) + 32 * (lane & 1)];   // (the lanes of a pair far apart: a row's candidates are sorted)
-    const Picked p = wave_pick<EPL>(kk, a.k, s.wtk[0]);
-    if (p.rank < a.k) put_frontier(a, s, p.rank, min((int)pick_index(p.key), n - 1), conf_lds);   // (beyond n: only with NaN scores)
-}
-
-// The same for any number of candidates.
-__device__ __forceinline__ void select_frontier(const ExpandArgs &a, ExpandSmem &s, int n, float *conf_lds) {
-    const int lane = lane_id(), K = a.k, nfs = a.F * 16;           // slot i: rank i % 16 of row i / 16
-    uint64_t top = 0;
-    for (int c0 = 0; c0 < nfs; c0 += 8 * kWave) {
-        uint64_t kk[9];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int i = c0 + topk_slot_of(e), c = (i >> 4) * K + (i & 15);
-            const float sc = s.cand_sc[min(c, n - 1)];
-            kk[e] = (i < nfs && (i & 15) < K) ? pick_key(sc, uint32_t(c)) : 0;
+    Picked p;
+    auto key = [&](int i) { return s.cand_key[i + (lane >> 1) + 32 * (lane & 1)]; };     // (the lanes of a pair far apart: a row's candidates are sorted)
+    if constexpr (MANY) {
+        uint64_t kk[3] = {0, 0, 0};
+#pragma unroll 1
+        for (int c0 = 0; c0 < n; c0 += kFrontierBlock) {
+            kk[0] = key(c0);
+            kk[1] = key(c0 + kWave);
+            p = wave_pick<3>(kk, a.k, s.wtk[0]);
+            kk[2] = carried(p, a.k);
         }
-        kk[8] = top;
-        top = wave_topk<9>(kk, K, s.wtk[0]);
+    } else {
+        const uint64_t kk[2] = {key(0), key(kWave)};
+        p = wave_pick<2>(kk, a.k, s.wtk[0]);
     }
-    if (lane < K) {
-        int c = (int)pick_index(top);
-        if (c >= n) c = 0;                                        // only reachable with NaN scores
-        put_frontier(a, s, lane, c, conf_lds);
-    }
+    if (p.rank < a.k) put_frontier(a, s, p.rank, min((int)pick_index(p.key), n - 1), conf_lds);   // (beyond n: only with NaN scores)
 }
 
 // Sequence bz of a batched call: every array of the call, the workspace parts and the cycle states
@@ -209,114 +160,102 @@ __device__ __forceinline__ void sequence_view(ExpandArgs &a, int bz) {
 // model that has a state).
 // POLL: what the other workgroups hand over may still be on its way (all of them have begun, and wait for nobody), and is cleared
 // once it has been read.  Without, it is all there.
-template <int MODE, bool POLL, typename Settle, typename Hidden>
+template <int MODE, bool POLL, bool GENERAL, typename Settle, typename Hidden>
 __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int bz, radar_cycle_state *cycle,
                                               bool cycle_first, Settle &&settle, Hidden &&hidden) {
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int K = a.k, n = a.F * K;
-    const bool few = a.nchunks <= kFewChunks;                      // (V <= 131072 at 8 logits per lane)
+    const bool few = !GENERAL || a.nchunks <= kFewChunks;                      // (V <= 131072 at 8 logits per lane)
     const int nslot = a.nchunks * RADAR_K_MAX;
-    if (tid >= n && tid < kFrontierMax) s.cand_key[tid] = 0;
+    if (tid >= n) s.cand_key[tid] = 0;
     if (MODE == kExpPolicy && tid < RADAR_K_MAX) s.pol.in[kPolH + tid] = 0.f;
 
     // One wavefront per row (rows w, w+16, ...):
     // top-k of the row's chunk lists, log-sum-exp of the row, cumulative scores, pool append.
-    uint64_t kk[9];
-    float ml = 0.f, pscore = 0.f;
-    double ll = 0.0;
+    // A look at 256 slots of the lists, four per lane and two to a load (device scope, as load_shared_result's; slots past the lists read 0),
+    // and one at the chunks' sums.  What is waited for here is requests: with loads of one slot a call took 8.1 us, 7.9 with two, ten
+    // rows of 32000 7.5 and 7.3.  A further look asks only for what the one before did not see.
+    uint64_t w2[3][2];
+    float pscore = 0.f;
     int ppool = 0;
-    auto load_row = [&](int fr) {
-        const uint64_t *pk = a.part_keys + (size_t)fr * nslot, *plm = a.part_lm + (size_t)fr * a.nchunks * 2;
-        // chunk partials, one chunk per lane first (up to 16 chunks: every 16-lane row of the wavefront takes all)
-        const int c = min(few ? (lane & 15) : lane, a.nchunks - 1);
-        if (few) {
-            // Four slots per lane, two to a load (device scope, as load_shared_result's; slots past the lists read 0).  What is waited for
-            // here is requests: with loads of one slot a call took 8.1 us, 7.9 with two, ten rows of 32000 7.5 and 7.3.  A
-            // look asks only for what the one before did not see.
-            const int urow = __builtin_amdgcn_readfirstlane(fr);
-            const auto lists = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(a.part_keys) + (size_t)urow * nslot,
-                                                                 0, nslot * (int)sizeof(uint64_t), 0x00027000);
-            const auto sums = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(a.part_lm) + (size_t)urow * a.nchunks * 2,
-                                                                0, a.nchunks * 16, 0x00027000);
-            const int at[3] = {lane * 16, kWave * 16 + ((lane + 4) & (kWave - 1)) * 16, c * 16};
-            uint64_t w2[3][2];
-            auto look = [&](int e) {
-                const auto v = __builtin_amdgcn_raw_buffer_load_b128(e == 2 ? sums : lists, at[e], 0, 16);
-                w2[e][0] = (uint64_t)v[0] | (uint64_t)v[1] << 32;
-                w2[e][1] = (uint64_t)v[2] | (uint64_t)v[3] << 32;
-            };
-            look(0); look(1); look(2);
-            pscore = a.parent_scores[fr];
-            ppool = a.parent_pool_idx[fr];
-            if (POLL) {
-                for (unsigned int looks = 0; looks < kPollLimit; ++looks) {
-                    bool missing[3];
+    const int sum_at = (few ? (lane & 15) : lane) * 16;            // up to 16 chunks: every 16-lane row of the wavefront takes all
+    auto look = [&](int fr, int c0, int e) {
+        const int urow = __builtin_amdgcn_readfirstlane(fr);
+        const auto from = e == 2 ? __builtin_amdgcn_make_buffer_rsrc(a.part_lm + (size_t)urow * a.nchunks * 2, 0, a.nchunks * 16, 0x00027000)
+                                 : __builtin_amdgcn_make_buffer_rsrc(a.part_keys + (size_t)urow * nslot, 0, nslot * (int)sizeof(uint64_t), 0x00027000);
+        const int at = e == 0 ? c0 * 8 + lane * 16 : e == 1 ? c0 * 8 + kWave * 16 + ((lane + 4) & (kWave - 1)) * 16 : c0 * 16 + sum_at;
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(from, at, 0, 16);
+        w2[e][0] = (uint64_t)v[0] | (uint64_t)v[1] << 32;
+        w2[e][1] = (uint64_t)v[2] | (uint64_t)v[3] << 32;
+    };
+    auto all_there = [&](int fr, int c0, bool keys, bool sums) {
+        if (!POLL) return;
+#pragma unroll 1
+        for (unsigned int looks = 0; looks < kPollLimit; ++looks) {
+            bool missing[3];
+            missing[0] = keys && !(word_there(w2[0][0]) && word_there(w2[0][1])) && c0 + lane * 2 < nslot;
+            missing[1] = keys && !(word_there(w2[1][0]) && word_there(w2[1][1])) && c0 + kWave * 2 + ((lane + 4) & (kWave - 1)) * 2 < nslot;
+            missing[2] = sums && !(word_there(w2[2][0]) && max_there(w2[2][1])) && c0 + (sum_at >> 4) < a.nchunks;
+            if (__ballot(missing[0] || missing[1] || missing[2]) == 0) break;
+            asm volatile("" ::: "memory");                         // (else the loads are the ones before)
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) missing[e] = !(word_there(w2[e][0]) && word_there(w2[e][1])) && at[e] < nslot * (int)sizeof(uint64_t);
-                    missing[2] = !(word_there(w2[2][0]) && max_there(w2[2][1]));
-                    if (__ballot(missing[0] || missing[1] || missing[2]) == 0) break;
-                    asm volatile("" ::: "memory");                 // (else the loads are the ones before)
-#pragma unroll
-                    for (int e = 0; e < 3; ++e) if (missing[e]) look(e);
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) kk[e] = key_of_word(w2[e >> 1][e & 1]);
-            ll = sum_of_word(w2[2][0]);
-            ml = max_of_word(w2[2][1]);
-        } else {
-            const uint64_t wl = load_shared_result(plm + 2 * c), wm = load_shared_result(plm + 2 * c + 1);
-            pscore = a.parent_scores[fr];
-            ppool = a.parent_pool_idx[fr];
-            load_key_block<POLL>(pk, nslot, 0, kk);
-            ll = sum_of_word(settled<POLL>(wl, plm + 2 * c, word_there));
-            ml = max_of_word(settled<POLL>(wm, plm + 2 * c + 1, max_there));
+            for (int e = 0; e < 3; ++e) if (missing[e]) look(fr, c0, e);
         }
     };
     auto merge_row = [&](int fr, auto &&between) {
-        const uint64_t *pk = a.part_keys + (size_t)fr * nslot;
-        Picked top;
-        if (few) {
-            const uint64_t k4[4] = {kk[0], kk[1], kk[2], kk[3]};
-            top = wave_pick<4>(k4, K, s.wtk[w], between);
-        } else {
-            top.key = row_topk<POLL>(kk, pk, nslot, K, s.wtk[w]);
-            top.rank = lane;
+        float ml = sum_at < a.nchunks * 16 ? max_of_word(w2[2][1]) : -INFINITY;
+        double ll = sum_of_word(w2[2][0]);
+#pragma unroll 1
+        for (int c = kWave; GENERAL && c < a.nchunks; c += kWave) {           // V > 262144 only
+            look(fr, c, 2);
+            all_there(fr, c, false, true);
+            if (c + lane < a.nchunks) {
+                const float m2 = max_of_word(w2[2][1]), mn = fmaxf(ml, m2);
+                if (mn > -INFINITY)
+                    ll = ll * (double)__builtin_amdgcn_exp2f((ml - mn) * kLog2eF) + sum_of_word(w2[2][0]) * (double)__builtin_amdgcn_exp2f((m2 - mn) * kLog2eF);
+                ml = mn;
+            }
         }
-        if ((few ? (lane & 15) : lane) >= a.nchunks) { ml = -INFINITY; ll = 0.0; }
-        for (int c = lane + kWave; c < a.nchunks; c += kWave) {        // V > 262144 only
-            const uint64_t *p = a.part_lm + ((size_t)fr * a.nchunks + c) * 2;
-            const uint64_t wl = load_shared_result(p), wm = load_shared_result(p + 1);
-            const double l2 = sum_of_word(settled<POLL>(wl, p, word_there));
-            const float m2 = max_of_word(settled<POLL>(wm, p + 1, max_there));
-            const float mn = fmaxf(ml, m2);
-            if (mn > -INFINITY)
-                ll = ll * (double)__builtin_amdgcn_exp2f((ml - mn) * kLog2eF) + l2 * (double)__builtin_amdgcn_exp2f((m2 - mn) * kLog2eF);
-            ml = mn;
-        }
-        float M;
-        double L;
-        if (few) {
-            // maximum and sum inside each 16-lane row by DPP steps alone (no lane reads: those cost a
-            // scalar round trip each); fixed order of addition, every lane ends up with the result
-            M = ml;
-            M = fmaxf(M, dpp_f32<0xB1>(M));
-            M = fmaxf(M, dpp_f32<0x4E>(M));
-            M = fmaxf(M, dpp_f32<0x141>(M));
-            M = fmaxf(M, dpp_f32<0x140>(M));
-            L = ml > -INFINITY ? ll * (double)__builtin_amdgcn_exp2f((ml - M) * kLog2eF) : 0.0;
-            auto add = [](double x, uint64_t moved) { return x + __longlong_as_double((long long)moved); };
-            L = add(L, dpp_u64<0xB1>((uint64_t)__double_as_longlong(L)));
-            L = add(L, dpp_u64<0x4E>((uint64_t)__double_as_longlong(L)));
-            L = add(L, dpp_u64<0x141>((uint64_t)__double_as_longlong(L)));
-            L = add(L, dpp_u64<0x140>((uint64_t)__double_as_longlong(L)));
-        } else {
-            M = wave_max_f32(ml);
-            L = wave_sum_f64(ml > -INFINITY ? ll * (double)__builtin_amdgcn_exp2f((ml - M) * kLog2eF) : 0.0);
-        }
+        // Maximum and sum inside each 16-lane row by DPP steps alone (no lane reads: those cost a
+        // scalar round trip each); fixed order of addition.  In one line with the selection, whose
+        // chain of dependent steps leaves room for this one.
+        float M = ml;
+        M = fmaxf(M, dpp_f32<0xB1>(M));
+        M = fmaxf(M, dpp_f32<0x4E>(M));
+        M = fmaxf(M, dpp_f32<0x141>(M));
+        M = fmaxf(M, dpp_f32<0x140>(M));
+        if (!few) M = fmaxf(fmaxf(readlane_f32(M, 0), readlane_f32(M, 16)), fmaxf(readlane_f32(M, 32), readlane_f32(M, 48)));
+        double L = ml > -INFINITY ? ll * (double)__builtin_amdgcn_exp2f((ml - M) * kLog2eF) : 0.0;
+        auto add = [](double x, uint64_t moved) { return x + __longlong_as_double((long long)moved); };
+        L = add(L, dpp_u64<0xB1>((uint64_t)__double_as_longlong(L)));
+        L = add(L, dpp_u64<0x4E>((uint64_t)__double_as_longlong(L)));
+        L = add(L, dpp_u64<0x141>((uint64_t)__double_as_longlong(L)));
+        L = add(L, dpp_u64<0x140>((uint64_t)__double_as_longlong(L)));
+        if (!few) L = (readlane_f64(L, 0) + readlane_f64(L, 16)) + (readlane_f64(L, 32) + readlane_f64(L, 48));
         // log in fp32 (1 ulp of a value below 14: 1e-6, a tenth of the tolerance on log-probabilities); the
         // fp64 routine costs 0.3 us on this serial path
         const double lse = (double)M + (double)logf((float)L);
+        Picked top;
+        uint64_t kk[GENERAL ? 5 : 4];
+        auto take = [&] {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) kk[e] = key_of_word(w2[e >> 1][e & 1]);
+        };
+        take();
+        if constexpr (GENERAL) {
+            kk[4] = 0;
+#pragma unroll 1
+            for (int c0 = 4 * kWave;; c0 += 4 * kWave) {           // the selection so far rides along
+                if (c0 < nslot) { look(fr, c0, 0); look(fr, c0, 1); }
+                top = wave_pick<5>(kk, K, s.wtk[w]);
+                if (c0 >= nslot) break;
+                kk[4] = carried(top, K);
+                all_there(fr, c0, true, false);
+                take();
+            }
+        } else {
+            top = wave_pick<4>(kk, K, s.wtk[w], between);
+        }
         if (top.rank < K) {
             const int tok = (int)pick_index(top.key);
             const double logp = (double)pick_value(top.key) - lse;
@@ -324,7 +263,7 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
             const int c = fr * K + top.rank;
             s.cand_sc[c] = cum;
             s.cand_tok[c] = tok;
-            if (n <= kFrontierMax) s.cand_key[c] = pick_key(cum, uint32_t(c));
+            s.cand_key[c] = pick_key(cum, uint32_t(c));
             a.cand_tokens[c] = tok;
             a.cand_scores[c] = cum;
             a.pool_tokens[a.pool_count + c] = tok;
@@ -332,11 +271,16 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
             a.pool_parents[a.pool_count + c] = ppool;
         }
     };
-    if (w < a.F) load_row(w);
+    auto look_at_row = [&](int fr) {
+        look(fr, 0, 0); look(fr, 0, 1); look(fr, 0, 2);
+        pscore = a.parent_scores[fr];
+        ppool = a.parent_pool_idx[fr];
+    };
+    if (w < a.F) look_at_row(w);
     if (!settle()) return;
     // The prediction model's operands are requested by every wavefront as its row's lists have been read, or its rows are done, and
     // arrive while the row is ranked and the frontier is chosen.  (Requested with the lists they hold those up: 2 % of a cycle.
-    // Requested after the row they came 0.75 us after it: a cycle of eight calls of 10 rows 124.4 us, now 120.2; four calls of 4 rows 48.1 and 46.6.)
+    // Requested after the row they came 0.75 us after it: a cycle of eight calls of 10 rows 124.4 us, then 120.2; four calls of 4 rows 48.1 and 46.6.)
     PolicyRegs pr;
     auto fetch = [&] {
         if constexpr (MODE == kExpPolicy) {
@@ -344,19 +288,24 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
             policy_fetch_rest<true>(a.pol, bz, a.pol_has_state != 0, pr, hidden);
         }
     };
-    if (MODE == kExpPolicy && few && w < a.F && a.F <= kExpWaves) {
+    if constexpr (GENERAL) {
+#pragma unroll 1
+        for (int fr = w; fr < a.F; fr += kExpWaves) {
+            if (fr != w) look_at_row(fr);
+            all_there(fr, 0, true, true);
+            merge_row(fr, [] {});
+        }
+        fetch();
+    } else if (w < a.F) {
+        all_there(w, 0, true, true);
         merge_row(w, fetch);
     } else {
-        if (w < a.F) merge_row(w, [] {});
-        for (int fr = w + kExpWaves; fr < a.F; fr += kExpWaves) { load_row(fr); merge_row(fr, [] {}); }
         fetch();
     }
     __syncthreads();
     float *const conf = MODE == kExpPolicy ? &s.pol.in[kPolH] : nullptr;
     if (w == 0) {
-        if (n <= kFrontierMax / 2) pick_frontier<2>(a, s, n, conf);
-        else if (n <= kFrontierMax) pick_frontier<4>(a, s, n, conf);
-        else select_frontier(a, s, n, conf);
+        pick_frontier<GENERAL>(a, s, n, conf);
     }
     auto advance = [&](int action) {                               // by one lane
         if (!cycle) return;
@@ -393,7 +342,8 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
 }
 
 // MODE: the plain expansion is compiled without any code for batches, cycle states or the prediction model.
-// A call is a chain of dependent stages, none of which is bound by bandwidth: F = 10, V = 128256, k = 10 takes 6.2 us per call on warm logits.
+// GENERAL: any number of chunks, rows and candidates at the call's end (launch_expand).
+// A call is a chain of dependent stages, none of which is bound by bandwidth: F = 10, V = 128256, k = 10 takes 6.1 us per call on warm logits.
 // (With lists announced by tickets once their stores were acknowledged 7.9; then 7.1, until the selections compared by sign
 // bits and ranked what passes in parts, radar_topk.h: ten rows of 128257 with k = 16 12.2 -> 9.1, of 200000 16.8 -> 9.0.)  Lists longer than 16 slots need no ranking at all, but
 // the last workgroup's loads are slow (from beyond its L2, 37 bytes per ns): 24 slots cost it 0.4 us, records of 32 0.7.
@@ -404,21 +354,61 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
 // 2-8 % where they are more (80 of 81 ... 256 workgroups), up to 96 or up to 48 is the same within 0.5 %.
 constexpr int kDirectArrivals = 96;
 
-template <bool VEC4, int EPT, int MODE>
+struct ExpandKernArgs {                    // the argument segment of expand_kernel
+    const float *logits;
+    int F, V, k, nchunks, pool_count;
+    radar_cycle_state *cycle;
+    uint64_t *part_keys;
+    unsigned int *counters;
+    ExpandArgs a;
+};
+typedef const __attribute__((address_space(4))) ExpandArgs *LateArgs;
+// The arguments behind the leading ones, not before this point of the program: left to itself the compiler loads them all at the start, before the
+// logits are asked for, and waits there to move them to lanes of vector registers (0.3 us of a call).
+__device__ __forceinline__ LateArgs late_args() {
+    auto p = (LateArgs)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ExpandKernArgs, a));
+    asm volatile("" : "+s"(p) :: "memory");
+    return p;
+}
+// What a call's end needs of them.
+template <int MODE>
+__device__ __forceinline__ ExpandArgs finish_args() {
+    const LateArgs p = late_args();
+    ExpandArgs a;
+    a.parent_scores = p->parent_scores; a.parent_pool_idx = p->parent_pool_idx; a.cand_tokens = p->cand_tokens; a.cand_scores = p->cand_scores;
+    a.frontier_pool_idx = p->frontier_pool_idx; a.frontier_tokens = p->frontier_tokens; a.frontier_scores = p->frontier_scores; a.frontier_conf = p->frontier_conf;
+    a.pool_tokens = p->pool_tokens; a.pool_scores = p->pool_scores; a.pool_parents = p->pool_parents; a.pool_capacity = p->pool_capacity;
+    a.part_lm = p->part_lm;
+    if constexpr (MODE == kExpPolicy) {
+        a.gate_pre = p->gate_pre; a.pol_has_state = p->pol_has_state;
+        a.pol.w_ih = p->pol.w_ih; a.pol.w_hh = p->pol.w_hh; a.pol.b_ih = p->pol.b_ih; a.pol.b_hh = p->pol.b_hh;
+        a.pol.w1 = p->pol.w1; a.pol.b1 = p->pol.b1; a.pol.w2 = p->pol.w2; a.pol.b2 = p->pol.b2;
+        a.pol.h_in = p->pol.h_in; a.pol.c_in = p->pol.c_in; a.pol.uniforms = p->pol.uniforms; a.pol.h_out = p->pol.h_out; a.pol.c_out = p->pol.c_out;
+        a.pol.logits = p->pol.logits; a.pol.probs = p->pol.probs; a.pol.action = p->pol.action; a.pol.k = p->pol.k; a.pol.M = p->pol.M;
+    }
+    return a;
+}
+
+template <bool VEC4, int EPT, int MODE, bool GENERAL>
 __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *logits, int F, int V, int k, int nchunks, int pool_count,
                                                                 radar_cycle_state *cycle_, uint64_t *part_keys, unsigned int *counters,
-                                                                ExpandArgs a) {
+                                                                ExpandArgs) {
     constexpr bool EXT = MODE != kExpPlain;
-    a.logits = logits; a.F = F; a.V = V; a.k = k; a.nchunks = nchunks; a.pool_count = pool_count;
-    a.cycle = cycle_; a.part_keys = part_keys; a.counters = counters;
+    struct { const float *logits; int F, V, k, nchunks, pool_count; radar_cycle_state *cycle; uint64_t *part_keys; unsigned int *counters; } a =
+        {logits, F, V, k, nchunks, pool_count, cycle_, part_keys, counters};
     static_assert(EPT == 4 || EPT == 8 || EPT == 16, "EPT");
-    static_assert(kFastCap <= kWave * kWaveTopkMaxEPL && kExpWaves == 16 && kStreamers == 4, "candidate list inside the selection scratch");
+    static_assert(kFastCap <= kPickMost && kExpWaves == 16 && kStreamers == 4, "candidate list inside the selection scratch");
     constexpr int kChunk = kExpThreads * EPT;
     __shared__ ExpandSmem s;
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int f = blockIdx.y, chunk = blockIdx.x;
     const int bz = EXT ? (int)blockIdx.z : 0;
-    if (EXT && bz != 0) sequence_view(a, bz);
+    if (EXT && bz != 0) {                                // sequence bz's part of what the stream needs
+        a.logits += (size_t)bz * F * V;
+        a.counters += (size_t)bz * (kCounterBytes / sizeof(unsigned int));
+        a.part_keys += (size_t)bz * F * nchunks * RADAR_K_MAX;
+        if (a.cycle) a.cycle += bz;
+    }
     radar_cycle_state *const cycle = EXT ? a.cycle : nullptr;
     // The first draft call of a cycle (the host says so: the largest count the state may hold is 0)
     // never reads the state; its last workgroup writes all of it.
@@ -487,8 +477,17 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     // handed to the last workgroup through the workspace like the chunk partials.  By the wavefronts that
     // do not stream.
     HiddenRows<2, 2 * (kExpWaves - kStreamers)> hrows;
-    const bool hidden_rows = MODE == kExpPolicy && a.pol_has_state && !streamer;
-    if (hidden_rows) hrows.load(a.pol, bz, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid / 32 - 2 * kStreamers);
+    bool hidden_rows = false;
+    PolicyArgs pol;
+    float *gate_pre = nullptr;
+    if (MODE == kExpPolicy && !streamer) {
+        const LateArgs la = late_args();
+        hidden_rows = la->pol_has_state != 0;
+        pol.w_hh = la->pol.w_hh;
+        pol.h_in = la->pol.h_in;
+        gate_pre = la->gate_pre + (size_t)bz * (kCounterBytes / sizeof(float));
+        if (hidden_rows) hrows.load(pol, bz, blockIdx.y * nchunks + blockIdx.x, nchunks * F, tid / 32 - 2 * kStreamers);
+    }
 
     // ---- the threshold of the chunk's top-k: the k-th largest of the maxima of the 32 eight-lane groups of the
     // streaming wavefronts.  At least k logits of the chunk reach it (one per group whose maximum does), and on
@@ -542,9 +541,9 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
             before = __hip_atomic_fetch_add(&a.counters[direct ? 0 : (1 + f) * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // The arguments that only the call's end needs are brought close by now: read by the last workgroup when it
         // gets there, each cache line of them would be a round trip of its own (0.3 us).
-        asm volatile("" :: "s"(a.parent_scores), "s"(a.pool_scores), "s"(a.part_lm));
-        if (MODE == kExpPolicy) asm volatile("" :: "s"(a.pol.b2), "s"(a.gate_pre));
-        if (hidden_rows) hrows.finish(a.pol, bz, [&](int r, float v) { store_shared_result(&a.gate_pre[r], __float_as_uint(v) == 0 ? -0.f : v); });
+        const auto la = (const __attribute__((address_space(4))) int *)late_args();
+        static_assert(sizeof(ExpandArgs) > 4 * 64 && sizeof(ExpandArgs) <= 5 * 64, "cache lines of the arguments");
+        asm volatile("" :: "s"(la[0]), "s"(la[16]), "s"(la[32]), "s"(la[48]), "s"(la[64]));
         if (counting && !direct)                                   // the last one of the row counts the row
             before = before == (unsigned int)(a.nchunks - 1) ? __hip_atomic_fetch_add(&a.counters[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0u;
     }
@@ -600,33 +599,38 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     const int nsurv = (int)s.nsurv;
     if (nsurv > kFastCap) {
         // Long runs of equal values (more candidates than the list holds): every streaming wavefront
-        // ranks its own logits exactly, eight per lane at a time with the selection so far riding
-        // along, then one wavefront ranks the four lists.  The logits are read again (a rolled loop
+        // ranks its own logits exactly, four per lane at a time with the selection so far riding
+        // along, then one wavefront the four selections.  The logits are read again (a rolled loop
         // over registers would index them dynamically); this path only runs on heavily tied rows.
         if (streamer) {
-            uint64_t wt = 0;
+            if (lane < RADAR_K_MAX) s.wlist[w * RADAR_K_MAX + lane] = 0;
+            uint64_t k5[5] = {0, 0, 0, 0, 0};
 #pragma unroll 1
-            for (int g0 = 0; g0 < NE / 4; g0 += 2) {
-                uint64_t kk[9];
+            for (int g = 0; g <= NE / 4; ++g) {
+                if (g == NE / 4) {
+                    __syncthreads();
+                    if (w != 0) break;
+                    k5[0] = s.wlist[lane];
+                    k5[1] = k5[2] = k5[3] = k5[4] = 0;
+                } else {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int idx = base + (g0 + (u >> 2)) * (kSLanes * 4) + tid * 4 + (u & 3);
-                    const float v = row[min(idx, a.V - 1)];
-                    kk[u] = idx < a.V ? pick_key(v, uint32_t(idx)) : 0;
+                    for (int u = 0; u < 4; ++u) {
+                        const int idx = base + g * (kSLanes * 4) + tid * 4 + u;
+                        const float v = row[min(idx, a.V - 1)];
+                        k5[u] = idx < a.V ? pick_key(v, uint32_t(idx)) : 0;
+                    }
                 }
-                kk[8] = wt;
-                wt = wave_topk<9>(kk, K, s.wtk[w]);
+                const Picked p = wave_pick<5>(k5, K, s.wtk[w]);
+                k5[4] = carried(p, K);
+                uint64_t *const best = s.wlist + w * RADAR_K_MAX;
+                if (g >= NE / 4 - 1 && p.rank < K) best[p.rank] = p.key;
             }
-            if (lane < kWaveListSlots) s.wlist[w * kWaveListSlots + lane] = wt;   // lanes 16.. hold 0
+        } else {
+            __syncthreads();
         }
-        __syncthreads();
         if (w == 0) {
-            constexpr int NS = kStreamers * kWaveListSlots / kWave;   // four lists of 32 slots, two slots per lane
-            uint64_t k2[NS];
-#pragma unroll
-            for (int e = 0; e < NS; ++e) k2[e] = s.wlist[e * kWave + lane];
-            const uint64_t top = wave_topk<NS>(k2, K, s.wtk[0]);
-            if (lane < RADAR_K_MAX) store_shared_result(list + lane, top | kThere);      // lanes from K on hold 0
+            wave_lds_sync();
+            if (lane < RADAR_K_MAX) store_shared_result(list + lane, (lane < K ? s.wlist[lane] : 0) | kThere);
         }
     } else if (w == 0 && nsurv <= RADAR_K_MAX) {
         // the candidates as they are: the finishing workgroup ranks them with the other chunks'
@@ -641,15 +645,23 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
         double l = 0.0;                                            // fixed order of addition
 #pragma unroll
         for (int i = 0; i < kStreamers; ++i) l += (double)s.wave_l[i];
+        uint64_t *const part_lm = late_args()->part_lm + (size_t)bz * F * nchunks * 2;
         if (lane < 2)
-            store_shared_result(&a.part_lm[pslot * 2 + lane], lane == 0 ? (uint64_t)__double_as_longlong(l) | kThere : uint64_t(1) << 32 | __float_as_uint(s.cmax));
+            store_shared_result(&part_lm[pslot * 2 + lane], lane == 0 ? (uint64_t)__double_as_longlong(l) | kThere : uint64_t(1) << 32 | __float_as_uint(s.cmax));
     }
+    // (Here, because nothing waits for it soon: before the candidates it held up their barrier by 0.6 us, in a call of few workgroups, which
+    // have more rows each, by 1.2.)
+    if (hidden_rows) hrows.finish(pol, bz, [&](int r, float v) { store_shared_result(&gate_pre[r], __float_as_uint(v) == 0 ? -0.f : v); });
     if (!s.last) return;
     if (tid <= a.F) store_shared_result(&a.counters[tid * kCounterStride], 0u);      // (all have counted)
 
     // ================= the workgroup that finishes the call
-    expand_finish<MODE, true>(a, s, bz, cycle, cycle_first, [] { return true; },
-                        [&](int row) { return load_shared_result(&a.gate_pre[row]); });
+    ExpandArgs fin = finish_args<MODE>();
+    fin.logits = logits; fin.F = F; fin.V = V; fin.k = k; fin.nchunks = nchunks; fin.cycle = cycle_; fin.part_keys = part_keys; fin.counters = counters;
+    if (EXT && bz != 0) sequence_view(fin, bz);
+    fin.pool_count = a.pool_count;
+    expand_finish<MODE, true, GENERAL>(fin, s, bz, cycle, cycle_first, [] { return true; },
+                        [&](int row) { return load_shared_result(&fin.gate_pre[row]); });
 }
 
 // ------------------------------------------------------------------ rerank
@@ -808,7 +820,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
         StreamFast fast;
         struct {
             WaveTopkSmem wtk[kStreamWaves];
-            uint64_t wlists[kStreamWaves][kWaveListSlots];
+            uint64_t wlist[kStreamWaves * RADAR_K_MAX];
         } ties;
     } s;
     __shared__ float gmax[8 * kStreamWaves];                       // maxima of the 32 eight-lane groups
@@ -926,28 +938,30 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
     if (n > kStreamCap) {
         // Long runs of equal values: every wavefront ranks its own logits exactly, then one ranks the four lists.
         __syncthreads();                                           // the short path's LDS is overlaid
-        uint64_t wt = 0;
+        if (lane < RADAR_K_MAX) s.ties.wlist[w * RADAR_K_MAX + lane] = 0;
+        uint64_t k5[5] = {0, 0, 0, 0, 0};
 #pragma unroll 1
-        for (int g0 = 0; g0 < EPT / 4; g0 += 2) {                  // (read again: a rolled loop would index the registers dynamically)
-            uint64_t kk[9];
+        for (int g = 0; g <= EPT / 4; ++g) {
+            if (g == EPT / 4) {
+                __syncthreads();
+                if (w != 0) break;
+                k5[0] = s.ties.wlist[lane];
+                k5[1] = k5[2] = k5[3] = k5[4] = 0;
+            } else {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = base + (g0 + (u >> 2)) * (kStreamThreads * 4) + tid * 4 + (u & 3);
-                const float v = rowp[min(idx, a.V - 1)];
-                kk[u] = idx < a.V ? pick_key(v, uint32_t(idx)) : 0;
+                for (int u = 0; u < 4; ++u) {                      // (read again: a rolled loop would index the registers dynamically)
+                    const int idx = base + g * (kStreamThreads * 4) + tid * 4 + u;
+                    const float v = rowp[min(idx, a.V - 1)];
+                    k5[u] = idx < a.V ? pick_key(v, uint32_t(idx)) : 0;
+                }
             }
-            kk[8] = wt;
-            wt = wave_topk<9>(kk, K, s.ties.wtk[w]);
+            const Picked p = wave_pick<5>(k5, K, s.ties.wtk[w]);
+            k5[4] = carried(p, K);
+            if (g >= EPT / 4 - 1 && p.rank < K) s.ties.wlist[w * RADAR_K_MAX + p.rank] = p.key;
         }
-        if (lane < kWaveListSlots) s.ties.wlists[w][lane] = wt;    // lanes 16.. hold 0
-        __syncthreads();
         if (w == 0) {
-            constexpr int NS = kStreamWaves * kWaveListSlots / kWave;
-            uint64_t kk[NS];
-#pragma unroll
-            for (int e = 0; e < NS; ++e) kk[e] = (&s.ties.wlists[0][0])[e * kWave + ((lane + 4 * e) & (kWave - 1))];
-            const uint64_t ctop = wave_topk<NS>(kk, K, s.ties.wtk[0]);
-            if (lane < RADAR_K_MAX) a.part_keys[slot * RADAR_K_MAX + lane] = ctop;    // 0 beyond the k-th
+            wave_lds_sync();
+            if (lane < RADAR_K_MAX) a.part_keys[slot * RADAR_K_MAX + lane] = lane < K ? s.ties.wlist[lane] : 0;
         }
     } else if (w == 0 && n <= RADAR_K_MAX) {
         // the candidates as they are: the finishing workgroup ranks them with the other chunks'
@@ -968,7 +982,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
 }
 
 // one workgroup per sequence, after expand_stream_kernel
-template <int MODE>
+template <int MODE, bool GENERAL>
 __global__ __launch_bounds__(kExpThreads, 1) void expand_finish_kernel(uint64_t *part_keys, uint64_t *part_lm, int F, int nchunks,
                                                                        int k, int pool_count, radar_cycle_state *cycle_, ExpandArgs a) {
     a.part_keys = part_keys; a.part_lm = part_lm;
@@ -979,7 +993,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_finish_kernel(uint64_t 
     radar_cycle_state *const cycle = a.cycle;
     const bool cycle_first = cycle != nullptr && a.pool_count == 0;
     // (the prediction model's input-free part was left in the workspace by the streaming kernel)
-    expand_finish<MODE, false>(a, s, bz, cycle, cycle_first, [&] { return !cycle_skips(cycle, a.pool_count, &a.pool_count); },
+    expand_finish<MODE, false, GENERAL>(a, s, bz, cycle, cycle_first, [&] { return !cycle_skips(cycle, a.pool_count, &a.pool_count); },
                         [&](int row) { return a.gate_pre[row]; });
 }
 
@@ -1073,6 +1087,9 @@ static radar_status launch_expand(const float *logits, const float *parent_score
     a.has_policy = pol ? 1 : 0;
     a.pol_has_state = (pol && pol->h_in) ? 1 : 0;
 
+    // Most calls' ends are one row per wavefront, one look at its lists and one at the candidates; the code for more would cost them 2-7 % (a cycle of the
+    // 8B shape 97 us without, 105 with: registers and fetches of instructions), so it has kernels of its own.
+    const bool general = nchunks > kFewChunks || d->F > kExpWaves || d->F * d->k > kFrontierBlock;
     const dim3 grid((unsigned)nchunks, (unsigned)d->F, (unsigned)B), block(kExpThreads);
     hipStream_t st = static_cast<hipStream_t>(stream_);
     hipError_t e;
@@ -1087,14 +1104,17 @@ static radar_status launch_expand(const float *logits, const float *parent_score
         auto fin = [&](auto kernel) {
             return launch("expand_finish", kernel, dim3((unsigned)B), block, 0, st, a.part_keys, a.part_lm, a.F, a.nchunks, a.k, a.pool_count, a.cycle, a);
         };
-        e = pol ? fin(expand_finish_kernel<kExpPolicy>) : fin(expand_finish_kernel<kExpExt>);
+        if (general) e = pol ? fin(expand_finish_kernel<kExpPolicy, true>) : fin(expand_finish_kernel<kExpExt, true>);
+        else         e = pol ? fin(expand_finish_kernel<kExpPolicy, false>) : fin(expand_finish_kernel<kExpExt, false>);
         return e == hipSuccess ? RADAR_OK : RADAR_HIP_ERROR;
     }
     const bool ext = cycle != nullptr || B > 1;
     auto go = [&](auto kernel) {
         return launch("expand", kernel, grid, block, 0, st, a.logits, a.F, a.V, a.k, a.nchunks, a.pool_count, a.cycle, a.part_keys, a.counters, a);
     };
-#define RADAR_EXPAND_LAUNCH(V4, E) (pol ? go(expand_kernel<V4, E, kExpPolicy>) : ext ? go(expand_kernel<V4, E, kExpExt>) : go(expand_kernel<V4, E, kExpPlain>))
+#define RADAR_EXPAND_LAUNCH(V4, E) \
+    (general ? (pol ? go(expand_kernel<V4, E, kExpPolicy, true>) : go(expand_kernel<V4, E, kExpExt, true>)) \
+             : (pol ? go(expand_kernel<V4, E, kExpPolicy, false>) : ext ? go(expand_kernel<V4, E, kExpExt, false>) : go(expand_kernel<V4, E, kExpPlain, false>)))
     if (ept == 4)      e = vec4 ? RADAR_EXPAND_LAUNCH(true, 4) : RADAR_EXPAND_LAUNCH(false, 4);
     else if (ept == 8) e = vec4 ? RADAR_EXPAND_LAUNCH(true, 8) : RADAR_EXPAND_LAUNCH(false, 8);
     else               e = vec4 ? RADAR_EXPAND_LAUNCH(true, 16) : RADAR_EXPAND_LAUNCH(false, 16);

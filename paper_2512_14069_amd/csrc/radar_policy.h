@@ -56,6 +56,17 @@ struct PolicyRegs {
     float w2[2][2], b2[2], uni;
 };
 
+// The value of lane ^ OFF, by DPP moves (through LDS it takes 130 cycles; 8, 4, 2 or 1 stay inside a row of 16 lanes).
+template <int OFF>
+__device__ __forceinline__ float lane_xor(float v) {
+    static_assert(OFF == 8 || OFF == 4 || OFF == 2 || OFF == 1, "inside a row");
+    if constexpr (OFF == 8) return dpp_f32<0x128>(v);                // row_ror:8
+    if constexpr (OFF == 2) return dpp_f32<0x4E>(v);
+    if constexpr (OFF == 1) return dpp_f32<0xB1>(v);
+    const int from_above = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x104, 0xF, 0x5, false);           // row_shl:4 into lanes 0-3 and 8-11
+    return __int_as_float(__builtin_amdgcn_update_dpp(from_above, __float_as_int(v), 0x114, 0xF, 0xA, false));  // row_shr:4 into the others
+}
+
 // v[0..N) per lane -> sums over groups of lanes.  One step with lane distance OFF halves the
 // number of values a lane carries: lanes whose bit OFF is set keep the upper half.
 template <int N, int OFF>
@@ -63,9 +74,14 @@ __device__ __forceinline__ void fold_step(float *v, int lane) {
     const bool up = (lane & OFF) != 0;
 #pragma unroll
     for (int i = 0; i < N / 2; ++i) {
-        const float send = up ? v[i] : v[i + N / 2];
-        const float keep = up ? v[i + N / 2] : v[i];
-        v[i] = keep + __shfl_xor(send, OFF);
+        if constexpr (OFF == 16) {                                   // rows 0 and 2 keep v[i], rows 1 and 3 the other
+            const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + N / 2]), false, false);
+            v[i] = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+        } else {
+            const float send = up ? v[i] : v[i + N / 2];
+            const float keep = up ? v[i + N / 2] : v[i];
+            v[i] = keep + lane_xor<OFF>(send);
+        }
     }
 }
 
@@ -114,21 +130,21 @@ struct HiddenRows {
                 fold_step<8, 8>(v, lane);
                 fold_step<4, 4>(v, lane);
                 fold_step<2, 2>(v, lane);
-                v[0] += __shfl_xor(v[0], 1);
+                v[0] += lane_xor<1>(v[0]);
                 mine = ((lane >> 4) & 1) * 8 + ((lane >> 3) & 1) * 4 + ((lane >> 2) & 1) * 2 + ((lane >> 1) & 1);
             } else if constexpr (NR == 4) {
                 fold_step<4, 16>(v, lane);
                 fold_step<2, 8>(v, lane);
-                v[0] += __shfl_xor(v[0], 4);
-                v[0] += __shfl_xor(v[0], 2);
-                v[0] += __shfl_xor(v[0], 1);
+                v[0] += lane_xor<4>(v[0]);
+                v[0] += lane_xor<2>(v[0]);
+                v[0] += lane_xor<1>(v[0]);
                 mine = ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
             } else {
                 fold_step<2, 16>(v, lane);
-                v[0] += __shfl_xor(v[0], 8);
-                v[0] += __shfl_xor(v[0], 4);
-                v[0] += __shfl_xor(v[0], 2);
-                v[0] += __shfl_xor(v[0], 1);
+                v[0] += lane_xor<8>(v[0]);
+                v[0] += lane_xor<4>(v[0]);
+                v[0] += lane_xor<2>(v[0]);
+                v[0] += lane_xor<1>(v[0]);
                 mine = (lane >> 4) & 1;
             }
             const int row = (part + parts * (i0 + mine)) * HW + hwave;

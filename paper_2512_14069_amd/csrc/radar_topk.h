@@ -159,10 +159,10 @@ __device__ __forceinline__ uint32_t kth_of_32(uint32_t g, int K) {
 // The same for the maxima of groups of floats: a threshold that at least K of them reach (at least -inf, whose image is odd).
 __device__ __forceinline__ float kth_threshold(float g, int K) { return float_of_ord(max(kth_of_32(ord_of(g) >> 1, K) << 1, 0x007fffffu)); }
 
-constexpr int kWaveTopkMaxEPL = 9;
-constexpr int kPickPad = 8;                       // entries that survivors may be padded by, where they are more than 32
+constexpr int kPickMost = 512;                    // survivors that can be ranked
+constexpr int kPickPad = 8;                       // entries that they may be padded by, where they are more than 32
 struct WaveTopkSmem {
-    alignas(16) uint64_t surv[kWave * kWaveTopkMaxEPL + kPickPad];   // complements of the survivors
+    alignas(16) uint64_t surv[kPickMost + kWave]; // complements of the survivors
     uint64_t top[16];
 };
 
@@ -228,7 +228,7 @@ __device__ __forceinline__ Picked rank_survivors(uint64_t *surv, uint64_t *top, 
 struct Nothing { __device__ __forceinline__ void operator()() const {} };
 template <int EPL, typename Between = Nothing>
 __device__ __forceinline__ Picked wave_pick(const uint64_t (&keys)[EPL], int K, WaveTopkSmem &s, Between &&between = Between()) {
-    static_assert(EPL <= kWaveTopkMaxEPL, "scratch too small");
+    static_assert(EPL * kWave + kPickPad <= kPickMost, "scratch too small");
     const int lane = lane_id();
     uint32_t tmax = 0;
 #pragma unroll
@@ -238,39 +238,22 @@ __device__ __forceinline__ Picked wave_pick(const uint64_t (&keys)[EPL], int K, 
     const auto h = __builtin_amdgcn_permlane32_swap(tmax, tmax, false, false);
     const uint32_t tau = max(kth_of_32(max(h[0], h[1]), K), 1u);   // ... so that both halves hold all 32 (never 0: absent keys do not pass)
 
+    // No branches: what does not pass goes to the scratch's last slot, which no survivor reaches.
     int n = 0;                                    // survivors so far (wave-uniform)
+    uint64_t m[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) m[e] = __ballot(uint32_t(keys[e] >> 32) >= tau);
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
-        const bool keep = uint32_t(keys[e] >> 32) >= tau;
-        const uint64_t m = __ballot(keep);
-        if (keep) s.surv[n + lanes_below(m)] = ~keys[e];
-        n += __popcll(m);
+        const int at = n + lanes_below(m[e]);
+        s.surv[uint32_t(keys[e] >> 32) >= tau ? at : kPickMost] = ~keys[e];
+        n += __popcll(m[e]);
     }
     between();
     return rank_survivors(s.surv, s.top, n, K);
 }
 
-// The same in order: the r-th largest in lane r (r < 16; 0 where fewer exist, and in lanes >= 16).
-template <int EPL>
-__device__ __forceinline__ uint64_t wave_topk(const uint64_t (&keys)[EPL], int K, WaveTopkSmem &s) {
-    const int lane = lane_id();
-    const Picked p = wave_pick<EPL>(keys, K, s);
-    if (lane < 16) s.top[lane] = 0;
-    wave_lds_sync();
-    if (p.rank < K) s.top[p.rank] = p.key;
-    wave_lds_sync();
-    const uint64_t r = s.top[lane & 15];
-    wave_lds_sync();                              // scratch may be reused right after the return
-    return lane < 16 ? r : 0;
-}
-
-constexpr int kWaveListSlots = 32;               // a wavefront's list in LDS
-
-// Lists of 16 slots, at least K of them used unless the chunk is shorter, in any order and from the first on (slot i: list
-// i / 16), taken 64 slots per step: which slot a lane takes at step e.  Lanes rotate by 4 per step, so a lane
-// meets slots of different places and every quad of lanes holds used slots.
-__device__ __forceinline__ int topk_slot_of(int e) {
-    return e * kWave + ((lane_id() + 4 * e) & (kWave - 1));
-}
+// A selection as a key of the next one: the keys picked so far in the lanes that hold them.
+__device__ __forceinline__ uint64_t carried(const Picked &p, int K) { return p.rank < K ? p.key : 0; }
 
 }  // namespace radar
