@@ -38,6 +38,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));     // a 16-byte load/store unit kept in registers
+typedef float float3u __attribute__((ext_vector_type(3), aligned(4)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 
 constexpr int kAttnThreads = 256;
 constexpr int kAttnWaves = 4;
@@ -62,7 +65,7 @@ struct AttnArgs {
     int shares;                            // > 0: the rows are dealt out on the device, to so many workgroups per unit block
     uint64_t *part_o;                      // [slot][n_ublk * 8][D/8][32][8]: partial outputs, fp16, scaled per row
     uint64_t *unit_tab;                    // [B][Hkv] dealt-out rows: first slot (low half) and number of a head's partials (high half)
-    float *part_ml;                        // [slot][n_ublk * 8][3][32]: running maximum (log2 units), sum, and the scale of part_o
+    float *part_ml;                        // [slot][n_ublk * 8][32][3]: running maximum (log2 units), sum, and the scale of part_o
 };
 
 // Byte offset of the 16-byte chunk `chunk` of cache row `key` in a K tile.  The chunks of a row are
@@ -105,7 +108,8 @@ __device__ __attribute__((aligned(16))) const uint32_t kZeroChunk[4] = {0, 0, 0,
 // Rows of the prefix: at most the cache's, so that the tree's rows can be added in 32 bits for any content of
 // ctx_lens (a length near 2^31 would wrap, and the sequence seem empty to one kernel and not to the next).
 // Where the prefix fills the cache nothing is left for the tree, as before.  Negative: no such sequence.
-__device__ __forceinline__ int prefix_rows(const AttnArgs &a, int b) { return min(a.ctx_lens[b], a.S); }
+__device__ __forceinline__ int prefix_rows(const AttnArgs &a, int b) { return min(a.ctx_lens[b], a.S); }                     // b: per lane
+__device__ __forceinline__ int prefix_rows_of(const AttnArgs &a, int b) { return min(uniform_word(a.ctx_lens, b), a.S); }    // b: the workgroup's
 
 // v = keep ? v : 0 without a branch (a select after a load tempts the compiler into a
 // conditional load, and conditional loads into register arrays wreck register allocation)
@@ -342,6 +346,13 @@ __device__ __forceinline__ void gs_store_tile(const GsTileRegs<D> &g, unsigned c
     }
 }
 
+// x * scl and y * scl as fp16, rounded once each (v_fma_mixlo and mixhi: seen together they would be two products and a conversion).
+__device__ __forceinline__ uint32_t two_halves(float x, float y, float scl) {
+    _Float16 lo = (_Float16)(x * scl);
+    asm("" : "+v"(lo));
+    return __builtin_bit_cast(uint32_t, half2v{lo, (_Float16)(y * scl)});
+}
+
 // End of a group-share kernel: a lane owns query i; its accumulator registers O(db, r) hold
 // d = 32*db + 8*(r/4) + 4*g2 + r%4 of the transposed output.
 // direct: this wavefront saw all of its rows' keys; otherwise its result is partial number `entry`.
@@ -368,45 +379,50 @@ __device__ __forceinline__ void gs_finish(const AttnArgs &a, Acc O, float m_run,
             a.lse[((size_t)b * a.T + i) * a.Hq + h] = (i < nn) ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : 0.f;
     } else {
         // Partial result of this key range: the row's output normalised by its own l and by the row's
-        // largest magnitude, as fp16 -- [D/8][32 rows][8 d], so that a wavefront's 8-byte stores cover 512
-        // contiguous bytes and the merge reads 16 bytes per lane -- plus (m, l, magnitude) in fp32.  The partials of all ranges together
+        // largest magnitude, as fp16 -- [D/8][32 rows][8 d], so that a wavefront's 16-byte stores cover 1024
+        // contiguous bytes and the merge reads 16 bytes per lane -- plus (m, l, magnitude) of a row next to each other in fp32.  The partials of all ranges together
         // outweigh the K/V bytes, and writing them is what the tail of this kernel waits for; halving
         // them costs 2^-11 of the row's largest element in precision, an eighth of the bf16 rounding of
         // the final output.  Written through: nothing is left dirty in L2 for the end of the kernel.
-        const int j32 = i & 31;
-        uint64_t *po = a.part_o + (size_t)entry * (D / 4 * 32);
-        float *pml = a.part_ml + (size_t)entry * 96;
+        // Two lanes share a row: the halves of two blocks of eight d change places, and each of the lanes stores 16 bytes of one.
+        const int j32 = i & 31, slot = __builtin_amdgcn_readfirstlane(entry);
+        const auto po = __builtin_amdgcn_make_buffer_rsrc(a.part_o + (size_t)slot * (D / 4 * 32), 0, D * 64, 0x00027000);
+        const auto pml = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + (size_t)slot * 96, 0, 96 * (int)sizeof(float), 0x00027000);
         const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-        float amax = 0.f;
+        float top[4] = {0.f, 0.f, 0.f, 0.f};                     // (one chain of maxima would be serial)
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) amax = fmaxf(amax, fabsf(O(db, r)));
+            for (int r = 0; r < 16; ++r) top[r >> 2] = fmaxf(top[r >> 2], fabsf(O(db, r)));
+        float amax = fmaxf(fmaxf(top[0], top[1]), fmaxf(top[2], top[3]));
         amax = fmaxf(amax, __shfl_xor(amax, 32)) * inv;          // both halves of the row's d range
         const float mag = amax > 0.f && amax < 3.0e38f ? amax : 1.f;
         const float scl = inv / mag;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {                     // d = 32 * db + 8 * r4 + 4 * g2 + 0..3
-                uint64_t four = 0;
+            for (int pair = 0; pair < 2; ++pair) {               // d = 32 * db + 16 * pair + 8 * (first or second) + 4 * g2 + 0..3
+                uint32_t first[2], second[2];
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    four |= (uint64_t)__builtin_bit_cast(uint16_t, (_Float16)(O(db, 4 * r4 + e) * scl)) << (16 * e);
-                store_shared_result(&po[((4 * db + r4) * 32 + j32) * 2 + g2], four);
+                for (int e = 0; e < 2; ++e) {
+                    first[e] = two_halves(O(db, 8 * pair + 2 * e), O(db, 8 * pair + 2 * e + 1), scl);
+                    second[e] = two_halves(O(db, 8 * pair + 4 + 2 * e), O(db, 8 * pair + 5 + 2 * e), scl);
+                }
+                const auto s0 = __builtin_amdgcn_permlane32_swap(first[0], second[0], false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(first[1], second[1], false, false);
+                const u32x4 eight = {s0[0], s1[0], s0[1], s1[1]};
+                __builtin_amdgcn_raw_buffer_store_b128(eight, po, ((4 * db + 2 * pair + g2) * 32 + j32) * 16, 0, 16);
             }
-        if (g2 == 0) {
-            store_shared_result(&pml[j32], m_run);
-            store_shared_result(&pml[32 + j32], l_tot);
-            store_shared_result(&pml[64 + j32], mag);
-        }
+        const u32x3 ml = {__builtin_bit_cast(uint32_t, m_run), __builtin_bit_cast(uint32_t, l_tot), __builtin_bit_cast(uint32_t, mag)};
+        if (g2 == 0) __builtin_amdgcn_raw_buffer_store_b96(ml, pml, j32 * 12, 0, 16);
     }
 }
 
+struct GsKernArgs { const __bf16 *k, *v; int64_t kv_sb, kv_sh; int kv_ss, kps, S, blocks; const __bf16 *q; AttnArgs a; };
+// blocks: n_ublk in the lower half, nqb in the upper
 template <int D, bool DEEP>
 __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(const __bf16 *k_, const __bf16 *v_, int64_t kv_sb, int64_t kv_sh, int kv_ss_, int kps,
-                                                                 int S, int n_ublk, const __bf16 *q_, AttnArgs a) {
-    a.k = k_; a.v = v_; a.kv_sb = kv_sb; a.kv_sh = kv_sh; a.kv_ss = kv_ss_; a.kps = kps; a.S = S; a.n_ublk = n_ublk; a.q = q_;
+                                                                 int S, int blocks, const __bf16 *q_, AttnArgs) {
     constexpr int DB = D / 32;              // 32-row blocks of O^T
 
     constexpr int TILE = 2 * kKT * D * 2;   // one K tile ([64][D] bf16, swizzled) + one V^T tile ([D][64], swizzled)
@@ -416,20 +432,19 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(const __bf16 *
     // The blocks of units that share a range of cache rows are ranges x KV heads apart in workgroup number:
     // a multiple of eight with eight KV heads, and consecutive numbers go to consecutive XCDs, so the
     // blocks meet in one XCD's L2 and their rows come from HBM once.
-    const int hk = blockIdx.y, ublk = blockIdx.z % a.n_ublk;
-    const int b = blockIdx.z / a.n_ublk;
-    const int kbeg = sp * a.kps;                          // < S: the grid has ceil(S / kps) ranges
+    const int n_ublk = blocks & 0xffff, nqb = blocks >> 16, hk = blockIdx.y;
+    int b = blockIdx.z, ublk = 0;
+    if (n_ublk > 1) { b = blockIdx.z / n_ublk; ublk = blockIdx.z - b * n_ublk; }      // (a division is 30 dependent instructions before the first load)
+    const int kbeg = sp * kps;                            // < S: the grid has ceil(S / kps) ranges
 
     const int u = ublk * kGsWaves + w;                    // (head within the group, block of 32 rows)
-    const int g = u / a.nqb, qb = u % a.nqb;
-    const bool active = g < a.G;
-    const int h = hk * a.G + (active ? g : 0);
+    const int g = u >> (nqb - 1), qb = u & (nqb - 1);
     const int j32 = lane & 31, g2 = lane >> 5;
     const int i = 32 * qb + j32;                          // this lane's tree row
 
-    const __bf16 *kbase = a.k + (size_t)b * a.kv_sb + (size_t)hk * a.kv_sh;
-    const __bf16 *vbase = a.v + (size_t)b * a.kv_sb + (size_t)hk * a.kv_sh;
-    const int kv_ss = (int)a.kv_ss;          // 32-bit offsets inside one head's cache (checked on the host)
+    const __bf16 *kbase = k_ + (size_t)b * kv_sb + (size_t)hk * kv_sh;
+    const __bf16 *vbase = v_ + (size_t)b * kv_sb + (size_t)hk * kv_sh;
+    const int kv_ss = kv_ss_;                // 32-bit offsets inside one head's cache (checked on the host)
 
     // The first tile and the query rows are requested before the sequence's context length and tree size
     // are known (two dependent scalar loads, most of a microsecond in a cold start): rows are clamped to
@@ -439,8 +454,23 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(const __bf16 *
     // DEEP (ranges of many tiles): staging runs two tiles ahead through two register sets, which hides
     // HBM latency better but doubles the loop's code; short ranges keep the compact one-ahead loop
     // (their time goes into a cold start, where code size counts).
+    // A range of two tiles asks for both at once (asked for after the first had come, the second was consumed 1.25 us after it: 32 heads over 2048
+    // rows 13.5 us for the call, 12.6 with this and the shorter ways to the first loads here and in the merge); with more of them the first would wait for the second's bytes (16 heads on 8 x 2 over 750 rows 10.7 -> 11.5).
     GsTileRegs<D> regs0, regs1;
-    gs_load_tile<D>(regs0, kbase, vbase, kv_ss, kbeg, a.S, tid);
+    gs_load_tile<D>(regs0, kbase, vbase, kv_ss, kbeg, S, tid);
+    const bool both = !DEEP && kps > kKT && kps <= 2 * kKT;
+    if (both) gs_load_tile<D>(regs1, kbase, vbase, kv_ss, kbeg + kKT, S, tid);
+    // The other arguments from here on (with two divisions they held up the first tile's loads by half a microsecond).
+    AttnArgs a;
+    {
+        const ArgBlock<AttnArgs> p = args_from_here<AttnArgs>(offsetof(GsKernArgs, a));
+        a.q_sb = p->q_sb; a.q_st = p->q_st; a.q_sh = p->q_sh; a.T = p->T; a.G = p->G; a.Hq = p->Hq; a.Hkv = p->Hkv; a.max_splits = p->max_splits;
+        a.ctx_lens = p->ctx_lens; a.n_nodes = p->n_nodes; a.parents = p->parents; a.scale_log2 = p->scale_log2;
+        a.out = p->out; a.lse = p->lse; a.o_sb = p->o_sb; a.o_st = p->o_st; a.o_sh = p->o_sh; a.part_o = p->part_o; a.part_ml = p->part_ml;
+        a.S = S; a.kps = kps; a.n_ublk = n_ublk; a.q = q_;
+    }
+    const bool active = g < a.G;
+    const int h = hk * a.G + (active ? g : 0);
     // this lane's query operands, kept in registers for the whole kernel: row i, d = 16*st + 8*g2 .. +8
     bf16x8 qop[D / 16];
     {
@@ -452,8 +482,8 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(const __bf16 *
             qop[st] = __builtin_bit_cast(bf16x8, raw);
         }
     }
-    const int L = prefix_rows(a, b);
-    int nn = a.n_nodes ? a.n_nodes[b] : a.T;
+    const int L = prefix_rows_of(a, b);
+    int nn = a.n_nodes ? uniform_word(a.n_nodes, b) : a.T;
     nn = max(1, min(nn, a.T));
     const int total = min(L + nn, a.S);                  // never read past the cache the caller described
     if (L < 0 || kbeg >= total) return;
@@ -463,9 +493,10 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(const __bf16 *
     if (DEEP) gs_load_tile<D>(regs1, kbase, vbase, kv_ss, kbeg + kKT, kend, tid);
     const int parent = a.parents[(size_t)b * a.T + min(lane, nn - 1)];
     gs_store_tile<D>(regs0, smem, smem + TILE / 2, kbeg, kend, tid);
+    if (both && ntiles > 1) gs_store_tile<D>(regs1, smem + TILE, smem + TILE + TILE / 2, kbeg + kKT, kend, tid);
     __syncthreads();
     if (DEEP) gs_load_tile<D>(regs0, kbase, vbase, kv_ss, kbeg + 2 * kKT, kend, tid);
-    else if (ntiles > 1) gs_load_tile<D>(regs0, kbase, vbase, kv_ss, kbeg + kKT, kend, tid);
+    else if (!both && ntiles > 1) gs_load_tile<D>(regs0, kbase, vbase, kv_ss, kbeg + kKT, kend, tid);
     uint64_t anc[1];
     anc[0] = kend > L ? ancestor_word_of(ancestor_words(parent, nn), i, nn) : 0ull;
 
@@ -490,6 +521,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(const __bf16 *
             tile_pv<D, 2, false>([&](int k, int) { return (const lds_byte *)(Vt + vt_off(32 * (k % DB) + j32, 16 * (k / DB) + 8 * g2)); },
                               pk, oacc);
         }
+        if (both) return;                                 // (there already)
         if (t + 1 < ntiles) {
             gs_store_tile<D>(next_regs, nxt, nxt + TILE / 2, kbeg + (t + 1) * kKT, kend, tid);
             __syncthreads();
@@ -913,56 +945,81 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_ld_kernel(const int32_t 
 constexpr int kOneRows = 32;                             // cache rows of a wavefront's step
 constexpr int kInvShift = 20;                            // a KV head's number times its sequence's share of 2^20
 
+struct OneKernArgs { const __bf16 *k, *v; const int32_t *ctx_lens, *n_nodes; int64_t kv_sb, kv_sh; int first; uint32_t second; AttnArgs a; };
+// first, second: what is needed first; EIGHTS: the KV heads and their share of 2^20, else the rows of the cache and their stride
 template <int D, bool EIGHTS>
 __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 *k_, const __bf16 *v_, const int32_t *ctx_lens, const int32_t *n_nodes,
-                                                                  int64_t kv_sb, int64_t kv_sh, int hkv, uint32_t hkv_inv, AttnArgs a) {
+                                                                  int64_t kv_sb, int64_t kv_sh, int first, uint32_t second, AttnArgs) {
     constexpr int DB = D / 32, ROW = D * 2, SUB = kOneRows * ROW;           // bytes of a row, of a step's K or V rows
     constexpr int LOADS = SUB / 1024, RPL = 1024 / ROW, CPR = ROW / 16;     // 1 KB loads; rows of one; 16-byte chunks of a row
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     float *const s_m = reinterpret_cast<float *>(smem + kGsWaves * 2 * SUB), *const s_l = s_m + kGsWaves * 32;
-    a.k = k_; a.v = v_; a.ctx_lens = ctx_lens; a.n_nodes = n_nodes; a.kv_sb = kv_sb; a.kv_sh = kv_sh;
-
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int j32 = lane & 31, g2 = lane >> 5;
     // Which workgroups share a KV head's rows, and whether they share an XCD: plan_attention.
     int b = blockIdx.z, hk = blockIdx.x;
     if (EIGHTS) {
         const int number = 8 * b + hk;                   // the batch's KV heads, counted through
-        b = (int)((uint32_t)number * hkv_inv >> kInvShift);
-        if (b >= a.B) return;
-        hk = number - b * hkv;
+        b = (int)((uint32_t)number * second >> kInvShift);
+        hk = number - b * first;
     }
-    const int unit = blockIdx.y, qb = unit & (a.nqb - 1), h = hk * a.G + (unit >> (a.nqb - 1));
-    const int L = prefix_rows(a, b);
-    int nn = a.n_nodes ? a.n_nodes[b] : a.T;
-    nn = max(1, min(nn, a.T));
-    const int total = min(L + nn, a.S);                  // never read past the cache the caller described
-    if (L < 0 || total < 1) return;
-    const int nsub = (total + kOneRows - 1) / kOneRows, nact = min(nsub, kGsWaves);
-    const __bf16 *const kbase = a.k + (size_t)b * a.kv_sb + (size_t)hk * a.kv_sh;
-    const __bf16 *const vbase = a.v + (size_t)b * a.kv_sb + (size_t)hk * a.kv_sh;
-    const int kv_ss = (int)a.kv_ss;                      // 32-bit offsets inside one head's cache (checked on the host)
+    const ArgBlock<AttnArgs> early = args_from_here<AttnArgs>(offsetof(OneKernArgs, a));
+    if (EIGHTS && b >= early->B) return;
+    const int S = EIGHTS ? early->S : first;
+    const int kv_ss = EIGHTS ? (int)early->kv_ss : (int)second;        // 32-bit offsets inside one head's cache (checked on the host)
+    const int32_t ctx = uniform_word(ctx_lens, b), nodes = n_nodes ? uniform_word(n_nodes, b) : RADAR_T_MAX;
+    const __bf16 *const kbase = k_ + (size_t)b * kv_sb + (size_t)hk * kv_sh;
+    const __bf16 *const vbase = v_ + (size_t)b * kv_sb + (size_t)hk * kv_sh;
 
     // This wavefront's rows of a step: K [32][D], then V [32][D], both row-major with their own swizzle (ks_off, vs_off); a
     // lane's 16 bytes land at the load's LDS base + 16 * lane, so it fetches the chunk that belongs there.  Rows past
     // the end re-read the last one in K, whose scores are masked, and are zeros in V.
     unsigned char *const mine = smem + w * 2 * SUB;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)mine);
-    auto issue = [&](const __bf16 *base, auto is_v, int sub) {
+    // Whole steps: a scalar base per load and the lane's offset in it, which repeats after 16 rows of K and is one for all of V.
+    const int lrow = lane / CPR, slot = lane % CPR;
+    uint32_t offk[16 / RPL], offv = (uint32_t)(lrow * kv_ss) * 2 + (uint32_t)((slot ^ vs_swz<D>(lrow)) << 4);
+#pragma unroll
+    for (int i = 0; i < 16 / RPL; ++i) offk[i] = (uint32_t)(lrow * kv_ss) * 2 + (uint32_t)((slot ^ ks_swz<D>(RPL * i + lrow)) << 4);
+    auto issue = [&](const __bf16 *base, auto is_v, int sub, int total) {
         constexpr bool V = decltype(is_v)::value;
+        const int row0 = __builtin_amdgcn_readfirstlane(sub * kOneRows);
+        if (row0 + kOneRows <= total) {
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+                const __bf16 *const src = base + (uint32_t)((row0 + RPL * i) * kv_ss);
+                const uint32_t dst = lds0 + (V ? SUB : 0) + i * 1024;
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(V ? offv : offk[i % (16 / RPL)]), "s"(src) : "memory", "m0");
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
-            const int row = RPL * i + lane / CPR, slot = lane % CPR;
+            const int row = RPL * i + lrow, at = row0 + row;
             const int chunk = V ? slot ^ vs_swz<D>(row) : slot ^ ks_swz<D>(row);
-            const int at = sub * kOneRows + row;
             const __bf16 *src = base + (uint32_t)(min(at, total - 1) * kv_ss) + chunk * 8;
-            if (V) src = at < total ? src : (const __bf16 *)kZeroChunk;      // (in every step: a branch around it costs 0.1 us more)
+            if (V) src = at < total ? src : (const __bf16 *)kZeroChunk;
             const uint32_t dst = lds0 + (V ? SUB : 0) + i * 1024;
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
         }
     };
     constexpr std::false_type kK{};
     constexpr std::true_type kV{};
+    // The first rows of K are asked for before the sequence's lengths are there: rows past its end, of the cache that the caller described, are
+    // masked by the softmax.  (V's have to be zeros, which takes the lengths.)
+    if (w * kOneRows < S) issue(kbase, kK, w, S);
+    AttnArgs a;
+    {
+        const ArgBlock<AttnArgs> p = args_from_here<AttnArgs>(offsetof(OneKernArgs, a));
+        a.T = p->T; a.G = p->G; a.Hq = p->Hq; a.nqb = p->nqb; a.q = p->q; a.q_sb = p->q_sb; a.q_st = p->q_st; a.q_sh = p->q_sh; a.parents = p->parents;
+        a.scale_log2 = p->scale_log2; a.out = p->out; a.lse = p->lse; a.o_sb = p->o_sb; a.o_st = p->o_st; a.o_sh = p->o_sh;
+    }
+    const int unit = blockIdx.y, qb = unit & (a.nqb - 1), h = hk * a.G + (unit >> (a.nqb - 1));
+    const int L = min(ctx, S);                           // (prefix_rows)
+    const int nn = max(1, min(nodes, a.T));
+    const int total = min(L + nn, S);                    // never read past the cache the caller described
+    if (L < 0 || total < 1) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); return; }     // (nothing may still be on its way into LDS at the end)
+    const int nsub = (total + kOneRows - 1) / kOneRows, nact = min(nsub, kGsWaves);
     const int i = 32 * qb + j32;                         // this lane's tree row
     bf16x8 qop[D / 16];                                  // its query operands: d = 16*st + 8*g2 .. +8
     floatx16 oacc[DB][1];
@@ -972,8 +1029,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
         for (int r = 0; r < 16; ++r) oacc[db][0][r] = 0.f;
     float m_run = kNegBig, l_run = 0.f;
     if (w < nact) {
-        issue(kbase, kK, w);
-        issue(vbase, kV, w);
+        issue(vbase, kV, w, total);
         const __bf16 *qrow = a.q + (size_t)b * a.q_sb + (size_t)h * a.q_sh + (uint32_t)(min(i, a.T - 1) * (int)a.q_st);
 #pragma unroll
         for (int st = 0; st < D / 16; ++st) {
@@ -987,29 +1043,36 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
         if (last * kOneRows + kOneRows > L)
             anc = ancestor_word_of(ancestor_words(a.parents[(size_t)b * a.T + min(lane, nn - 1)], nn), i, nn);
         const lds_byte *const kl = (const lds_byte *)mine, *const vl = kl + SUB;
+#pragma unroll
+        for (int st = 0; st < D / 16; ++st) asm volatile("" : "+v"(qop[st]));       // (they have landed, and with them the first K and V: no waits for them in the loop)
         for (int sub = w; sub < nsub; sub += kGsWaves) {
             const bool more = sub + kGsWaves < nsub;
             floatx16 sacc[1];
             bf16x8 pk[1][2];
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            // K has landed when no more than V's loads are under way, which are issued after it and land in order; V when K's next ones are left.
+            if (sub == w) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(LOADS) : "memory");
             tile_scores<D, 1>([&](int k) { return (lds_u32x4)(kl + ks_off<D>(j32, 2 * k + g2)); }, qop, sacc);
             if (more) {
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // the K rows have been read: the next may land there
-                issue(kbase, kK, sub + kGsWaves);
+                issue(kbase, kK, sub + kGsWaves, total);
             }
             tile_softmax<D, 1>(sacc, oacc, m_run, l_run, anc, sub * kOneRows, L, total, sub == w, a.scale_log2, 0.f, pk);
+            if (more) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(LOADS) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             tile_pv<D, 1, true>([&](int k, int hi) {
                 const int d0 = 32 * (k % DB) + (j32 & 16) + 4 * (lane & 3), kv0 = 4 * g2 + ((lane >> 2) & 3);
                 return vl + vs_off<D>(kv0, d0 >> 3) + (d0 & 7) * 2 + (k / DB) * (16 * ROW) + hi * (8 * ROW);   // (8 rows on: the same swizzle)
             }, pk, oacc);
             if (more) {
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                issue(vbase, kV, sub + kGsWaves);
+                issue(vbase, kV, sub + kGsWaves, total);
             }
         }
         const float l_tot = l_run + __shfl_xor(l_run, 32);
         if (g2 == 0) { s_m[w * 32 + j32] = m_run; s_l[w * 32 + j32] = l_tot; }
     }
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // (rows asked for in vain have landed, too)
     __syncthreads();                                     // every wavefront is done with its rows; maxima and sums are in LDS
     float *const s_o = reinterpret_cast<float *>(smem);  // [wavefront][d][32], over the rows
     if (w < nact) {
@@ -1053,47 +1116,52 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
 // of lanes take every other partial and meet in LDS (3 heads of 16000 rows 26.5 -> 24.8 us; with 11 pieces it costs
 // 0.1 us more than it gives, and four groups cost more than two nearly everywhere: a workgroup of 1024 lanes starts
 // late).  Ranges cut on the host are merged by one group, however many they are.
-template <int D, int E, int NB>
-__global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(const int32_t *ctx_lens, const int32_t *n_nodes, const uint64_t *part_o,
-                                                                          const float *part_ml, int T, int kps, int S, int max_splits, int shares, int G, AttnArgs a) {
-    __shared__ float red[E > 1 ? E - 1 : 1][10][kAttnThreads];
-    constexpr int SL = 32, DQ = 8;                          // slice width, floats per lane
-    a.ctx_lens = ctx_lens; a.n_nodes = n_nodes; a.T = T; a.kps = kps; a.S = S; a.max_splits = max_splits; a.shares = shares; a.G = G;
-    const int slice = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int L = prefix_rows(a, b);
-    int nn = a.n_nodes ? a.n_nodes[b] : a.T;
-    nn = max(1, min(nn, a.T));
-    const int hk = h / a.G, g = h - hk * a.G;
-    int slot0, count, nqb = a.nqb, shared = 0;              // partials of this head's KV head: consecutive slots, each once or twice
-    if (a.shares > 0) {
-        const uint64_t tab = a.unit_tab[b * a.Hkv + hk];
-        slot0 = (int)(uint32_t)tab;
-        count = (int)(uint32_t)(tab >> 32);
-        if (L < 0 || count == 0) return;                    // the workgroup wrote the result itself
-        nqb = flat_row_blocks(a, nn);
-        shared = flat_shared(a, nn) ? 1 : 0;
-        count <<= shared;
-    } else {
-        const int total = min(L + nn, a.S);
-        count = (total + a.kps - 1) / a.kps;
-        if (L < 0 || count <= 1) return;                    // the split kernel wrote the result itself
-        slot0 = (b * a.Hkv + hk) * a.max_splits;
+// CUT: ranges cut on the host.  The lengths come first (before them, as many partials as the grid had ranges would be 0.2 us slower where
+// there are that many, and 1.1 to 1.5 where the sequence is short); the arguments that only the end needs are read there.
+// heads: KV heads in the lower half, query heads of each in the upper; blocks: n_ublk and nqb likewise.  Not CUT: kps is unit_tab's offset from part_ml.
+struct MergeKernArgs { const uint64_t *part_o; const float *part_ml; const int32_t *ctx_lens, *n_nodes; int T, kps, S, max_splits; uint32_t heads; int blocks; AttnArgs a; };
+template <int D, int E, int NB, int SL, bool CUT>
+__global__ __launch_bounds__(E * SL * 8) void tree_attn_merge_kernel(const uint64_t *part_o, const float *part_ml, const int32_t *ctx_lens, const int32_t *n_nodes,
+                                                                          int T, int kps, int S, int max_splits, uint32_t heads, int blocks, AttnArgs) {
+    constexpr int DQ = 8, SLICES = D / SL, kGroup = SL * 8;        // floats per lane; slices of SL of the head's D; lanes of a group
+    __shared__ float red[E > 1 ? E - 1 : 1][10][kGroup];
+    const int slice = blockIdx.x % SLICES, g = blockIdx.x / SLICES, hk = blockIdx.y, b = blockIdx.z;
+    const int G = heads >> 16, Hkv = heads & 0xffff, h = hk * G + g, n_ublk = blocks & 0xffff;
+    int slot0 = (b * Hkv + hk) * max_splits, count = max_splits, nqb = blocks >> 16, shared = 0;   // partials of this head's KV head: consecutive slots, each once or twice
+    int nn = T;
+    {
+        const int L = min(uniform_word(ctx_lens, b), S);    // (prefix_rows)
+        if (n_nodes) nn = uniform_word(n_nodes, b);
+        nn = max(1, min(nn, T));
+        if (L < 0) return;
+        if constexpr (CUT) {
+            count = (min(L + nn, S) + kps - 1) / kps;
+            if (count <= 1) return;                         // the workgroup wrote the result itself
+        } else {
+            AttnArgs f;                                     // what flat_row_blocks and flat_shared ask for
+            f.G = G; f.nqb = nqb; f.n_ublk = n_ublk;
+            const int32_t *const tab = reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(part_ml) + kps);   // (unit_tab)
+            slot0 = uniform_word(tab, 2 * (b * Hkv + hk));
+            count = uniform_word(tab, 2 * (b * Hkv + hk) + 1);
+            if (count == 0) return;
+            nqb = flat_row_blocks(f, nn);
+            shared = flat_shared(f, nn) ? 1 : 0;
+            count <<= shared;
+        }
     }
 
-    const int t256 = threadIdx.x & (kAttnThreads - 1), eg = E > 1 ? (int)threadIdx.x / kAttnThreads : 0;
-    const int rbits = a.T > 32 ? 6 : a.T > 16 ? 5 : 4;
-    const int i = t256 & ((1 << rbits) - 1), part = t256 >> rbits;      // query row, which 8 of the slice's 32
+    const int tg = threadIdx.x & (kGroup - 1), eg = E > 1 ? (int)threadIdx.x / kGroup : 0;
+    const int rbits = T > 32 ? 6 : T > 16 ? 5 : 4;
+    const int i = tg & ((1 << rbits) - 1), part = tg >> rbits;          // query row, which 8 of the slice
     if (E == 1 && part >= SL / DQ) return;
     const bool live = i < nn && part < SL / DQ;
     const int d0 = slice * SL + part * DQ;
-    const int units = a.G * nqb, j32 = i & 31;
+    const int units = G * nqb, j32 = i & 31;
     // an entry's address: a uniform part, kept in scalar registers, and the lane's offset in the entries of its block
-    const int entry0 = slot0 * a.n_ublk * kGsWaves + g * nqb;
+    const int entry0 = slot0 * n_ublk * kGsWaves + g * nqb;
     const uint32_t block = nqb == 1 ? 0 : i >> 5;
-    const uint32_t lane_ml = block * 96 + j32, lane_o = block * (D / 4 * 32) + ((d0 >> 3) * 32 + j32) * 2;
-    auto entry_of = [&](int n) { return (size_t)__builtin_amdgcn_readfirstlane(entry0 + (n >> shared) * a.n_ublk * kGsWaves + ((n & shared) ? units : 0)); };
-    __bf16 *orow = a.out + (size_t)b * a.o_sb + (size_t)i * a.o_st + (size_t)h * a.o_sh + d0;
-    const bool lse_lane = a.lse && slice == 0 && part == 0;
+    const uint32_t lane_ml = block * 96 + j32 * 3, lane_o = block * (D / 4 * 32) + ((d0 >> 3) * 32 + j32) * 2;
+    auto entry_of = [&](int n) { return (size_t)__builtin_amdgcn_readfirstlane(entry0 + (n >> shared) * n_ublk * kGsWaves + ((n & shared) ? units : 0)); };
     float M = kNegBig, lsum = 0.f;
     float acc[DQ];
 #pragma unroll
@@ -1105,10 +1173,8 @@ __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(const
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             const size_t en = entry_of(min(s0 + j * E, count - 1));
-            const float *const ml = part_ml + en * 96;
-            m[j] = ml[lane_ml];
-            l[j] = ml[lane_ml + 32];
-            mag[j] = ml[lane_ml + 64];
+            const float3u ml = *reinterpret_cast<const float3u *>(part_ml + en * 96 + lane_ml);
+            m[j] = ml[0]; l[j] = ml[1]; mag[j] = ml[2];
             o[j] = *reinterpret_cast<const u32x4 *>(part_o + en * (size_t)(D / 4 * 32) + lane_o);
         }
         if constexpr (NB > 8) __builtin_amdgcn_sched_barrier(0);    // (else loads follow the arithmetic, to save registers)
@@ -1144,12 +1210,9 @@ __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(const
         if (each <= 2) take_all(std::integral_constant<int, 2>{});
         else if (NB == 4 || each <= 4) take_all(std::integral_constant<int, 4>{});
         else if (NB == 8 || each <= 8) take_all(std::integral_constant<int, 8>{});
-        else {
-            const int rounds = (each + NB - 1) / NB, most = (each + rounds - 1) / rounds;
-            if (most <= 12) take_all(std::integral_constant<int, 12>{});
-            else if (most <= 16) take_all(std::integral_constant<int, 16>{});
-            else take_all(std::integral_constant<int, NB>{});
-        }
+        else if (each <= 12 || (each > NB && each <= 24)) take_all(std::integral_constant<int, 12>{});      // (two rounds: even ones)
+        else if (each <= 16 || (each > NB && each <= 32)) take_all(std::integral_constant<int, 16>{});
+        else take_all(std::integral_constant<int, NB>{});
         // What is asked for beyond the last partial is that one again, with no weight.  Where it holds an infinity 0 * Inf has made the
         // row NaN: its partials are added up again one by one.  (The check is 0.06 us of a call over 2048 rows, 13.40 -> 13.46; masking them 0.3.)
         float any = acc[0] + acc[1];
@@ -1165,32 +1228,35 @@ __global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(const
     }
     if constexpr (E > 1) {
         if (live && eg > 0) {
-            red[eg - 1][0][t256] = M;
-            red[eg - 1][1][t256] = lsum;
+            red[eg - 1][0][tg] = M;
+            red[eg - 1][1][tg] = lsum;
 #pragma unroll
-            for (int d = 0; d < DQ; ++d) red[eg - 1][2 + d][t256] = acc[d];
+            for (int d = 0; d < DQ; ++d) red[eg - 1][2 + d][tg] = acc[d];
         }
         __syncthreads();
         if (eg > 0) return;
         if (live) {
 #pragma unroll
             for (int e = 0; e < E - 1; ++e) {
-                const float m = red[e][0][t256], Mn = fmaxf(M, m);
+                const float m = red[e][0][tg], Mn = fmaxf(M, m);
                 const float aold = __builtin_amdgcn_exp2f(M - Mn), wnew = __builtin_amdgcn_exp2f(m - Mn);
-                lsum = lsum * aold + red[e][1][t256] * wnew;
+                lsum = lsum * aold + red[e][1][tg] * wnew;
 #pragma unroll
-                for (int d = 0; d < DQ; ++d) acc[d] = acc[d] * aold + red[e][2 + d][t256] * wnew;
+                for (int d = 0; d < DQ; ++d) acc[d] = acc[d] * aold + red[e][2 + d][tg] * wnew;
                 M = Mn;
             }
         }
     }
-    if (i >= a.T || part >= SL / DQ) return;
+    if (i >= T || part >= SL / DQ) return;
+    const ArgBlock<AttnArgs> a = args_from_here<AttnArgs>(offsetof(MergeKernArgs, a));
+    __bf16 *const orow = a->out + (size_t)b * a->o_sb + (size_t)i * a->o_st + (size_t)h * a->o_sh + d0;
+    float *const lse = a->lse;
     const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
     bf16x8 o8;
 #pragma unroll
     for (int e = 0; e < 8; ++e) o8[e] = (__bf16)(live ? acc[e] * inv : 0.f);      // rows past the tree are zeroed
     *reinterpret_cast<bf16x8 *>(orow) = o8;
-    if (lse_lane) a.lse[((size_t)b * a.T + i) * a.Hq + h] = live ? (M + __builtin_amdgcn_logf(lsum)) * kLn2 : 0.f;
+    if (lse && slice == 0 && part == 0) lse[((size_t)b * T + i) * (Hkv * G) + h] = live ? (M + __builtin_amdgcn_logf(lsum)) * kLn2 : 0.f;
 }
 
 // ------------------------------------------------------------------ host-side planning
@@ -1347,7 +1413,7 @@ static hipError_t launch_gs(const AttnArgs &a, dim3 grid, hipStream_t s) {
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, gs_smem_bytes<D>());
     if (configured != hipSuccess) return configured;
     return launch("tree_attn_group_share", tree_attn_gs_kernel<D, DEEP>, grid, dim3(kGsThreads), gs_smem_bytes<D>(), s, a.k, a.v, a.kv_sb, a.kv_sh,
-                  (int)a.kv_ss, a.kps, a.S, a.n_ublk, a.q, a);
+                  (int)a.kv_ss, a.kps, a.S, a.n_ublk | a.nqb << 16, a.q, a);
 }
 
 template <int D, bool EIGHTS>
@@ -1359,8 +1425,8 @@ static hipError_t launch_one(const AttnArgs &a, hipStream_t s) {
     static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_one_kernel<D, EIGHTS>),
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (configured != hipSuccess) return configured;
-    return launch("tree_attn_one", tree_attn_one_kernel<D, EIGHTS>, grid, dim3(kGsThreads), bytes, s, a.k, a.v, a.ctx_lens, a.n_nodes, a.kv_sb, a.kv_sh, a.Hkv,
-                  inv, a);
+    return launch("tree_attn_one", tree_attn_one_kernel<D, EIGHTS>, grid, dim3(kGsThreads), bytes, s, a.k, a.v, a.ctx_lens, a.n_nodes, a.kv_sb, a.kv_sh,
+                  EIGHTS ? a.Hkv : a.S, EIGHTS ? inv : (uint32_t)a.kv_ss, a);
 }
 
 extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache, const void *v_cache,
@@ -1431,14 +1497,14 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
         // a time), 16 tree rows 11.7 -> 10.6, 8 heads on 2 13.7 -> 12.4, D = 64 on 4 10.6 -> 9.5; with 48 or 64 heads
         // 3000 rows would go from 17.6 to 17.8 and from 19.4 to 19.9.
         const bool wide = (long)d->D / 32 * a.Hq * a.B * (d->T_max > 32 ? 4 : d->T_max > 16 ? 2 : 1) <= 640;
-        const dim3 mgrid((unsigned)(d->D / 32), (unsigned)a.Hq, (unsigned)a.B);
-        auto go = [&](auto kernel, int groups) {
-            return launch("tree_attn_merge", kernel, mgrid, dim3((unsigned)(kAttnThreads * groups)), 0, s, a.ctx_lens, a.n_nodes, a.part_o, a.part_ml, a.T, a.kps,
-                          a.S, a.max_splits, a.shares, a.G, a);
+        auto go = [&](auto kernel, int groups, int width) {
+            return launch("tree_attn_merge", kernel, dim3((unsigned)(d->D / width * a.G), (unsigned)a.Hkv, (unsigned)a.B), dim3((unsigned)(groups * width * 8)), 0, s, a.part_o, a.part_ml, a.ctx_lens, a.n_nodes, a.T,
+                          p.shares > 0 ? (int)(p.off_tab - p.off_part_ml) : a.kps, a.S, a.max_splits, (uint32_t)a.Hkv | (uint32_t)a.G << 16, a.n_ublk | a.nqb << 16, a);
         };
-        const hipError_t e = d->D == 64 ? (wide ? go(tree_attn_merge_kernel<64, 1, 18>, 1) : go(tree_attn_merge_kernel<64, 1, 8>, 1))
-                           : many       ? (wide ? go(tree_attn_merge_kernel<128, 2, 18>, 2) : go(tree_attn_merge_kernel<128, 2, 4>, 2))
-                                        : (wide ? go(tree_attn_merge_kernel<128, 1, 18>, 1) : go(tree_attn_merge_kernel<128, 1, 8>, 1));
+        const hipError_t e = d->D == 64 ? (wide ? go(tree_attn_merge_kernel<64, 1, 18, 32, true>, 1, 32) : go(tree_attn_merge_kernel<64, 1, 8, 32, true>, 1, 32))
+                           : p.shares == 0 ? (wide ? go(tree_attn_merge_kernel<128, 1, 18, 32, true>, 1, 32) : go(tree_attn_merge_kernel<128, 1, 8, 32, true>, 1, 32))
+                           : many       ? (wide ? go(tree_attn_merge_kernel<128, 2, 18, 32, false>, 2, 32) : go(tree_attn_merge_kernel<128, 2, 4, 32, false>, 2, 32))
+                                        : (wide ? go(tree_attn_merge_kernel<128, 1, 18, 32, false>, 1, 32) : go(tree_attn_merge_kernel<128, 1, 8, 32, false>, 1, 32));
         if (e != hipSuccess) return RADAR_HIP_ERROR;
     }
     return RADAR_OK;

@@ -194,4 +194,22 @@ __device__ __forceinline__ unsigned int publish_then_ticket(unsigned int *counte
     return *flag;
 }
 
+// ------------------------------------------------- arguments that are needed later
+// A kernel's leading scalar arguments are in registers when it starts; the rest is a block behind them (type Args, the last parameter), every
+// cache line of which is a round trip of 0.3 us.  Left to itself the compiler loads all of it at the start and waits for it,
+// to work out or to move away what is needed at the end, before the first loads from memory are asked for.  This gives the block's
+// address to loads that come after it in the program.  Lead: the leading parameters and the block, in order.
+template <typename Args>
+using ArgBlock = const __attribute__((address_space(4))) Args *;
+template <typename Args>
+__device__ __forceinline__ ArgBlock<Args> args_from_here(size_t at) {
+    auto p = (ArgBlock<Args>)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + at);
+    asm volatile("" : "+s"(p) :: "memory");
+    return p;
+}
+
+// A word that is the same for the whole workgroup and that nothing writes while the kernel runs: by a scalar load wherever it stands (behind
+// args_from_here the compiler would take a vector load, and branches on the word for divergent ones).
+__device__ __forceinline__ int32_t uniform_word(const int32_t *p, int i) { return ((const __attribute__((address_space(4))) int32_t *)p)[i]; }
+
 }  // namespace radar

@@ -362,14 +362,8 @@ struct ExpandKernArgs {                    // the argument segment of expand_ker
     unsigned int *counters;
     ExpandArgs a;
 };
-typedef const __attribute__((address_space(4))) ExpandArgs *LateArgs;
-// The arguments behind the leading ones, not before this point of the program: left to itself the compiler loads them all at the start, before the
-// logits are asked for, and waits there to move them to lanes of vector registers (0.3 us of a call).
-__device__ __forceinline__ LateArgs late_args() {
-    auto p = (LateArgs)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ExpandKernArgs, a));
-    asm volatile("" : "+s"(p) :: "memory");
-    return p;
-}
+typedef ArgBlock<ExpandArgs> LateArgs;
+__device__ __forceinline__ LateArgs late_args() { return args_from_here<ExpandArgs>(offsetof(ExpandKernArgs, a)); }
 // What a call's end needs of them.
 template <int MODE>
 __device__ __forceinline__ ExpandArgs finish_args() {

@@ -305,6 +305,32 @@ def test_merge_takes_any_number_of_partials(oracle, parts):
         assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)     # unused rows are zeroed
 
 
+@pytest.mark.parametrize("D,T,kps", [(128, 16, 128), (128, 60, 128), (64, 33, 128), (128, 32, 64), (64, 60, 192), (128, 60, 192)])
+def test_short_sequences_after_a_call_that_filled_every_range(oracle, D, T, kps):
+    """A range of two tiles asks for both at once, before the lengths are there; sequences end in their first range, at a tile's
+    edge, one row past it, within the second tile and in the last range.  What lies past the end is NaN in the cache, and the workspace holds
+    NaN partials of a call over all of it.  The outputs and the log-sum-exp: as the other tests."""
+    from paper_2512_14069_amd import binding as b
+    nn = [T, 1, (T + 1) // 2, T, 2, T]
+    rows = [kps - 1, 64, kps + 65, kps + 64 + T, 2 * kps, 9 * kps - 3]
+    a = shape(6, 4, 2, D, T, [max(r - n, 0) for r, n in zip(rows, nn)], nn, [max(1, min(6, n - 1)) for n in nn], k=64)
+    x = synth.attention_inputs(a, seed=synth.seed_for(1, D + T + kps), shuffle=True)
+    ref, ref_lse = oracle.tree_attention(x["q"], x["k_cache"], x["v_cache"], x["parents"], x["ctx_lens"], x["n_nodes"], want_lse=True)
+    for i, n in enumerate(nn):
+        x["k_cache"][i, :, x["ctx_lens"][i] + n:] = x["v_cache"][i, :, x["ctx_lens"][i] + n:] = 0x7fc0
+    q, kc, vc = bf16_dev(x["q"]), bf16_dev(x["k_cache"]), bf16_dev(x["v_cache"])
+    lse = torch.full((6, T, 4), 7.0, dtype=torch.float32, device="cuda")
+    ws = b.new_workspace(b.radar_tree_attention_workspace_bytes(b.attn_desc(q, kc, keys_per_split=kps)))
+    attend = lambda k, v, ctx: b.radar_tree_attention(q, k, v, dev(x["parents"]), dev(ctx), dev(x["n_nodes"]), workspace=ws, keys_per_split=kps,
+                                                      lse_out=lse, out=torch.full(q.shape, 3.0, dtype=torch.bfloat16, device="cuda"))
+    attend(kc, torch.full_like(vc, float("nan")), np.full(6, a.S - T, np.int32))
+    got, lse = bf16_bits(attend(kc, vc, x["ctx_lens"])), host(lse)
+    for i, n in enumerate(nn):
+        check_close(got[i, :n], ref[i, :n], f"b={i}")
+        assert np.max(np.abs(lse[i, :n] - ref_lse[i, :n])) < LSE_TOL
+        assert np.all(got[i, n:] == 0) and np.all(lse[i, n:] == 0)
+
+
 def test_chain_and_star_trees_depth_63(oracle):
     from paper_2512_14069_amd import binding as b
     a = shape(2, 4, 1, 128, 64, [100, 31], [64, 64], [8, 8], k=10)
