@@ -116,26 +116,21 @@ __device__ __forceinline__ void load_block(const float *row, int i_block, int V,
         const int i = i_block + (CONTIG ? lane * kAccEPT + 4 * g : g * (kWave * 4) + lane * 4);
         first[g] = i;
         // branch-free: out-of-range lanes read a valid address and are masked afterwards
-        if (VEC4) {
-            raw[g] = *reinterpret_cast<const float4 *>(row + (i < V ? i : 0));
-        } else {
-            raw[g].x = row[min(i + 0, V - 1)];
-            raw[g].y = row[min(i + 1, V - 1)];
-            raw[g].z = row[min(i + 2, V - 1)];
-            raw[g].w = row[min(i + 3, V - 1)];
-        }
+        if (VEC4) raw[g] = *reinterpret_cast<const float4 *>(row + (i < V ? i : 0));
     }
-    const bool tail = i_block + kAccSub > V;                  // wave-uniform: only a row's last block needs masking
+    if (!VEC4 && V >= 4) {
 #pragma unroll
-    for (int g = 0; g < kAccEPT / 4; ++g) {
-        const float v[4] = {raw[g].x, raw[g].y, raw[g].z, raw[g].w};
-        if (tail) {
+        for (int g = 0; g < kAccEPT / 4; ++g) raw[g] = load4_of_row(row, first[g], V);
+    } else if (!VEC4) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[4 * g + j] = (first[g] + j < V) ? v[j] : -INFINITY;
-        } else {
+        for (int g = 0; g < kAccEPT / 4; ++g) raw[g] = load4_of_short_row(row, V);
+    }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[4 * g + j] = v[j];
-        }
+    for (int g = 0; g < kAccEPT / 4; ++g) { x[4 * g] = raw[g].x; x[4 * g + 1] = raw[g].y; x[4 * g + 2] = raw[g].z; x[4 * g + 3] = raw[g].w; }
+    if (i_block + kAccSub > V) {                              // wave-uniform: only a row's last block needs masking
+        if (!VEC4) place_row_end<kAccEPT / 4>([&](int g, int j) -> float & { return x[4 * g + j]; }, first[0], CONTIG ? 4 : kWave * 4, V);
+#pragma unroll
+        for (int e = 0; e < kAccEPT; ++e) x[e] = (first[e / 4] + (e & 3) < V) ? x[e] : -INFINITY;
     }
 }
 

@@ -426,14 +426,10 @@ __global__ __launch_bounds__(kAqStream) void accept_q_stats_kernel(AqArgs a) {
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         const int i0 = lo + (k * kAqStream + tid) * 4;
-        if (VEC4) {
-            const float4 v = *reinterpret_cast<const float4 *>(row + (i0 < a.V ? i0 : 0));
-            x[k][0] = v.x; x[k][1] = v.y; x[k][2] = v.z; x[k][3] = v.w;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) x[k][j] = row[min(i0 + j, a.V - 1)];
-        }
+        const float4 v = VEC4 ? *reinterpret_cast<const float4 *>(row + (i0 < a.V ? i0 : 0)) : load4_of_row(row, i0, a.V);   // (V >= 12288)
+        x[k][0] = v.x; x[k][1] = v.y; x[k][2] = v.z; x[k][3] = v.w;
     }
+    if (!VEC4) place_row_end<R>([&](int k, int j) -> float & { return x[k][j]; }, lo + tid * 4, kAqStream * 4, a.V);
 #pragma unroll
     for (int k = 0; k < R; ++k)
 #pragma unroll
@@ -555,14 +551,9 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(const int32_t
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int i0 = at + r * kAqStream * 4;
-            if (VEC4) {
-                const float4 v = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(row) + (uint32_t)(i0 < a.V ? i0 : 0) * 4u);
-                x[r][0] = v.x; x[r][1] = v.y; x[r][2] = v.z; x[r][3] = v.w;
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    x[r][j] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(row) + (uint32_t)min(i0 + j, a.V - 1) * 4u);
-            }
+            const float4 v = VEC4 ? *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(row) + (uint32_t)(i0 < a.V ? i0 : 0) * 4u)
+                                  : load4_of_row(row, i0, a.V);    // (V > 2048 here)
+            x[r][0] = v.x; x[r][1] = v.y; x[r][2] = v.z; x[r][3] = v.w;
         }
     };
     constexpr bool kAhead = R <= 2 && !LAPS;              // rows are requested one node ahead (wider slices have no registers left)
@@ -598,6 +589,7 @@ __global__ __launch_bounds__(kAqThreads) void accept_q_coop_kernel(const int32_t
     auto settle = [&](float (&x)[R][4], int lap = 0, float none = -INFINITY) {
         if (lo + (lap + 1) * lap_tokens <= a.V) return;
         const int at = first_token(lap);
+        if (!VEC4) place_row_end<R>([&](int r, int j) -> float & { return x[r][j]; }, at, kAqStream * 4, a.V);
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll

@@ -49,6 +49,41 @@ __device__ __forceinline__ float dpp_f32(float v) {
     return __uint_as_float(dpp_u32<CTRL>(__float_as_uint(v)));
 }
 
+// ------------------------------------------------------------------- rows of any alignment
+// Rows of V floats with V % 4 != 0 start at any multiple of 4 bytes, which is all that a 16-byte load of global memory needs
+// on this chip: a wavefront's request covers one cache line more.  Four of a row of n >= 4 from i on; what would
+// reach past the row's end is read from n - 4 on, and place_row_end() brings it to its place.
+__device__ __forceinline__ float4 load4_of_row(const float *row, int i, int n) {
+    typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+    const f32x4_any v = *reinterpret_cast<const f32x4_any *>(reinterpret_cast<const char *>(row) + (uint32_t)min(i, n - 4) * 4u);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 load4_of_short_row(const float *row, int n) {   // of one shorter than four, from its start
+    return make_float4(row[0], row[min(1, n - 1)], row[min(2, n - 1)], row[n - 1]);
+}
+// x(g, 0 ... 3): four from first + g * step on, a multiple of 4, as load4_of_row left them.  Entries from n on are the caller's to mask.
+template <int G, typename X>
+__device__ __forceinline__ void place_row_end(X &&x, int first, int step, int n) {
+    const int by = n >= 4 ? -n & 3 : 0;                            // how far the last four were moved
+    auto at_end = [&](int g) { return (unsigned int)(n - 1 - (first + g * step)) < 3u; };
+    if (by == 1) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const bool c = at_end(g);
+            x(g, 0) = c ? x(g, 1) : x(g, 0); x(g, 1) = c ? x(g, 2) : x(g, 1); x(g, 2) = c ? x(g, 3) : x(g, 2);
+        }
+    } else if (by == 2) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const bool c = at_end(g);
+            x(g, 0) = c ? x(g, 2) : x(g, 0); x(g, 1) = c ? x(g, 3) : x(g, 1);
+        }
+    } else if (by == 3) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) x(g, 0) = at_end(g) ? x(g, 3) : x(g, 0);
+    }
+}
+
 __device__ __forceinline__ uint32_t readlane_u32(uint32_t v, int lane) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }

@@ -423,8 +423,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     // there (counted at the start, one row of V = 200000 7.14 us, so 6.74; counted beside the candidates 6.93).
     const bool direct = a.F * a.nchunks <= kDirectArrivals, counting = w == kExpWaves - 1 && lane == 0;
     unsigned int before = 0;
-    constexpr bool kCountFirst = VEC4 || EPT < 16;                 // (else there is no register to keep the count in)
-    if (kCountFirst && counting && !direct) before = __hip_atomic_fetch_add(&a.counters[(1 + f) * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (counting && !direct) before = __hip_atomic_fetch_add(&a.counters[(1 + f) * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // ---- stream the chunk.  Only the first four wavefronts (one per SIMD) stream and select: a
     // 64-wide vector instruction occupies its SIMD for four cycles whichever wavefront issues it, so
@@ -442,23 +441,25 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     if (streamer) {
         __builtin_amdgcn_s_setprio(3);                             // the others wait for these four
         float4 raw[NE / 4];
+        if (VEC4) {
 #pragma unroll
-        for (int g = 0; g < NE / 4; ++g) {
-            const int idx0 = base + g * (kSLanes * 4) + tid * 4;
-            if (VEC4) {
+            for (int g = 0; g < NE / 4; ++g) {
+                const int idx0 = base + g * (kSLanes * 4) + tid * 4;
                 raw[g] = *reinterpret_cast<const float4 *>(row + (idx0 < a.V ? idx0 : 0));
-            } else {
-                raw[g].x = row[min(idx0 + 0, a.V - 1)];
-                raw[g].y = row[min(idx0 + 1, a.V - 1)];
-                raw[g].z = row[min(idx0 + 2, a.V - 1)];
-                raw[g].w = row[min(idx0 + 3, a.V - 1)];
             }
+        } else if (a.V >= 4) {
+#pragma unroll
+            for (int g = 0; g < NE / 4; ++g) raw[g] = load4_of_row(row, base + g * (kSLanes * 4) + tid * 4, a.V);
+        } else {
+#pragma unroll
+            for (int g = 0; g < NE / 4; ++g) raw[g] = load4_of_short_row(row, a.V);
         }
 #pragma unroll
         for (int g = 0; g < NE / 4; ++g) {
             x[4 * g + 0] = raw[g].x; x[4 * g + 1] = raw[g].y; x[4 * g + 2] = raw[g].z; x[4 * g + 3] = raw[g].w;
         }
         if (tail) {
+            if (!VEC4) place_row_end<NE / 4>([&](int g, int j) -> float & { return x[4 * g + j]; }, base + tid * 4, kSLanes * 4, a.V);
 #pragma unroll
             for (int e = 0; e < NE; ++e) {
                 const int idx = base + (e >> 2) * (kSLanes * 4) + tid * 4 + (e & 3);
@@ -531,8 +532,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
         const auto c2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(cm), __float_as_uint(cm), false, false);
         cm = fmaxf(__uint_as_float(c2[0]), __uint_as_float(c2[1]));
     } else {
-        if (counting && (direct || !kCountFirst))
-            before = __hip_atomic_fetch_add(&a.counters[direct ? 0 : (1 + f) * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (counting && direct) before = __hip_atomic_fetch_add(&a.counters[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // The arguments that only the call's end needs are brought close by now: read by the last workgroup when it
         // gets there, each cache line of them would be a round trip of its own (0.3 us).
         const auto la = (const __attribute__((address_space(4))) int *)late_args();
@@ -843,14 +843,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
 #pragma unroll
     for (int g = 0; g < EPT / 4; ++g) {
         const int idx0 = base + g * (kStreamThreads * 4) + tid * 4;
-        if (VEC4) {
-            raw[g] = *reinterpret_cast<const float4 *>(rowp + (idx0 < a.V ? idx0 : 0));
-        } else {
-            raw[g].x = rowp[min(idx0 + 0, a.V - 1)];
-            raw[g].y = rowp[min(idx0 + 1, a.V - 1)];
-            raw[g].z = rowp[min(idx0 + 2, a.V - 1)];
-            raw[g].w = rowp[min(idx0 + 3, a.V - 1)];
-        }
+        raw[g] = VEC4 ? *reinterpret_cast<const float4 *>(rowp + (idx0 < a.V ? idx0 : 0)) : load4_of_row(rowp, idx0, a.V);   // (V >= 64)
     }
     float x[EPT];
 #pragma unroll
@@ -858,6 +851,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
         x[4 * g + 0] = raw[g].x; x[4 * g + 1] = raw[g].y; x[4 * g + 2] = raw[g].z; x[4 * g + 3] = raw[g].w;
     }
     if (base + kStreamChunk > a.V) {                               // the row's last chunk only
+        if (!VEC4) place_row_end<EPT / 4>([&](int g, int j) -> float & { return x[4 * g + j]; }, base + tid * 4, kStreamThreads * 4, a.V);
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
             const int idx = base + (e >> 2) * (kStreamThreads * 4) + tid * 4 + (e & 3);
@@ -998,12 +992,10 @@ using namespace radar;
 // Logits per lane: the fewest (shortest critical path per workgroup) that keep the launch at one
 // workgroup per CU and a row at as many chunks as are merged the short way, as far as there are such (a call over one row
 // of V = 128256 in 16 chunks takes 7.0 us, of V = 262144 in 16 instead of 64 chunks 7.0 instead of 8.0); launches too
-// large for that take the most, i.e. the fewest workgroups.  Rows without 16-byte loads do not go to the most for the
-// sake of the short way: its 64 addresses per lane do not fit the registers (V = 262143, k = 10, one row in 16 / 64 chunks 10.6 / 8.8 us, eight
-// rows in 16 / 32 chunks each 11.7 / 10.2; V = 200001, k = 16, eight rows 19.0 / 12.1).
-static int plan_expand_ept(int F, int V, bool vec4) {
+// large for that take the most, i.e. the fewest workgroups.
+static int plan_expand_ept(int F, int V) {
     for (const int most : {kFewChunks, kExpMaxChunks})
-        for (int ept = kExpMinEPT; ept <= (vec4 || most > kFewChunks ? 16 : 8); ept *= 2) {
+        for (int ept = kExpMinEPT; ept <= 16; ept *= 2) {
             const int64_t chunk = (int64_t)kExpThreads * ept, nchunks = ((int64_t)V + chunk - 1) / chunk;
             if (F * nchunks <= 256 && nchunks <= most) return ept;
         }
@@ -1053,7 +1045,7 @@ static radar_status launch_expand(const float *logits, const float *parent_score
     const bool stream = B > 1 && (int64_t)B * d->F <= 65535 &&
                         (int64_t)B * d->F * d->V >= kStreamMinLogits;
     const bool vec4 = (d->V % 4 == 0) && (((uintptr_t)logits & 15) == 0);
-    const int ept = plan_expand_ept((int)std::min<int64_t>((int64_t)d->F * B, 1 << 20), d->V, vec4);
+    const int ept = plan_expand_ept((int)std::min<int64_t>((int64_t)d->F * B, 1 << 20), d->V);
     const int64_t chunk = stream ? kStreamChunk : (int64_t)kExpThreads * ept;
     const int64_t nchunks = ((int64_t)d->V + chunk - 1) / chunk;
     if (d->F > RADAR_F_MAX || d->k > RADAR_K_MAX || nchunks > kExpMaxChunks) return RADAR_UNSUPPORTED_SHAPE;
