@@ -794,7 +794,9 @@ __device__ __forceinline__ bool cycle_skips(const radar_cycle_state *st, int poo
     return false;
 }
 
-constexpr int kStreamHot = 16;                                     // lanes of a wavefront whose logits go through LDS
+// Lanes of a wavefront whose logits go through LDS.  With k = 16 a chunk has 22 of them on average and one wavefront in some thousands more
+// than sixteen, which costs the call the exact ranking.
+constexpr int kStreamHot = 24;
 constexpr int kStreamCap = 128;                                    // candidates of a chunk; more (runs of equal values) rank per wavefront
 
 struct StreamFast {
