@@ -37,7 +37,8 @@ constexpr int kDumpCap = 32;                          // hot lanes of one of the
 constexpr int kFastCap = 512;                         // chunk candidates ranked by the short path; more (runs of equal values) rank per wavefront
 constexpr int kFewChunks = 16;                        // rows of so many chunks are merged the short way (expand_finish)
 constexpr int kFrontierBlock = 128;                   // candidates that are looked at together for the frontier
-constexpr int64_t kStreamMinLogits = 4 << 20;         // batched calls of at least 16 MB of logits take the streaming path
+constexpr int kRound = 256;                           // workgroups of the single launch that run at once, one per CU
+constexpr int64_t kStreamMinLogits = 4 << 20;         // batched calls over rows of less than a streaming workgroup's width stream from here on
 
 // What the workgroups of a single launch hand over vouches for itself: the reader looks until every word is there.  A key there
 // and a sum have bit 63 set (what the two-launch form leaves does not), a maximum has 1 in its upper half; the reader clears what it has
@@ -999,7 +1000,7 @@ static int plan_expand_ept(int F, int V) {
     for (const int most : {kFewChunks, kExpMaxChunks})
         for (int ept = kExpMinEPT; ept <= 16; ept *= 2) {
             const int64_t chunk = (int64_t)kExpThreads * ept, nchunks = ((int64_t)V + chunk - 1) / chunk;
-            if (F * nchunks <= 256 && nchunks <= most) return ept;
+            if (F * nchunks <= kRound && nchunks <= most) return ept;
         }
     return 16;
 }
@@ -1043,11 +1044,16 @@ static radar_status launch_expand(const float *logits, const float *parent_score
         return RADAR_INVALID_ARG;
     if (B < 1) return RADAR_INVALID_ARG;
     if (B > 65535) return RADAR_UNSUPPORTED_SHAPE;
-    // Batches large enough to fill the chip several times over take the two-launch streaming path.
-    const bool stream = B > 1 && (int64_t)B * d->F <= 65535 &&
-                        (int64_t)B * d->F * d->V >= kStreamMinLogits;
     const bool vec4 = (d->V % 4 == 0) && (((uintptr_t)logits & 15) == 0);
     const int ept = plan_expand_ept((int)std::min<int64_t>((int64_t)d->F * B, 1 << 20), d->V);
+    // Batches whose single launch would take more than one round of the chip stream.  In one round the single launch is the faster one at any size
+    // (ten rows of V = 128256, three sequences 7.1 us per call, streamed 9.0; four rows of 8190, 64 sequences 4.9 and 7.2), the second round
+    // starts behind the whole first (eight rows of 50257: 320 workgroups 10.5 and 9.7, 480 13.4 and 11.1).  Where sequences may have stopped, which the host does not
+    // know, the line is a quarter of a round further out: 300 workgroups of which some leave at once 0.91 ... 1.07 of the streamed time, 384 1.09 ... 0.86.
+    const int64_t groups = (int64_t)B * d->F * (((int64_t)d->V + kExpThreads * ept - 1) / (kExpThreads * ept));
+    const int64_t line = cycle != nullptr && d->pool_count > 0 ? kRound + kRound / 4 : kRound;
+    const bool stream = B > 1 && (int64_t)B * d->F <= 65535 &&
+                        (d->V >= kStreamThreads * 4 ? groups > line : (int64_t)B * d->F * d->V >= kStreamMinLogits);
     const int64_t chunk = stream ? kStreamChunk : (int64_t)kExpThreads * ept;
     const int64_t nchunks = ((int64_t)d->V + chunk - 1) / chunk;
     if (d->F > RADAR_F_MAX || d->k > RADAR_K_MAX || nchunks > kExpMaxChunks) return RADAR_UNSUPPORTED_SHAPE;

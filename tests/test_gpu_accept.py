@@ -224,3 +224,35 @@ def test_small_trees_in_a_large_launch(oracle, mode, nodes):
     x = synth.accept_inputs(small_shape(B, T, nn, tuple(max(1, min(5, n - 1)) for n in nn), k=10), V, seed=81 + nodes[0], plant=0.9, shuffle=True)
     ref, _ = compare(oracle, b, x, mode)
     assert mode == 1 or ref[0].max() >= 2
+
+
+@pytest.mark.parametrize("V,B", [(1, 2), (2, 3), (3, 2), (5, 2), (1025, 3), (2050, 3), (4099, 3), (4100, 3), (20003, 40)])   # the last: two blocks per wavefront
+@pytest.mark.parametrize("offset", [0, 2])
+def test_row_ends_at_any_alignment(oracle, V, B, offset):
+    """Rows whose decisive logits are the last ones, rows shorter than a load, logits that start off a multiple of 16 bytes; larger values that
+    are not the rows' own before and behind them."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(synth.seed_for(30, 900 + V % 100 + offset))
+    T, D = (20, 4) if V > 1000 else (3, 2)
+    par = np.full((B, T), -1, np.int32)
+    tok = np.zeros((B, T), np.int32)
+    for s in range(B):
+        for n in range(1, T):
+            par[s, n] = n - 1 if n <= D else (n - 1) // 4
+            tok[s, n] = max(0, V - 1 - n % 4)
+    logits = rng.standard_normal((B, T, V), dtype=np.float32)
+    logits[:, :, max(0, V - 4):] += 9.0
+    held = torch.full((B * T * V + 16,), 100.0, device="cuda")
+    held[4 + offset:4 + offset + B * T * V] = dev(logits).view(-1)
+    x = held[4 + offset:4 + offset + B * T * V].view(B, T, V)
+    nn = np.full(B, T, np.int32)
+
+    def clear(u):
+        m = oracle.accept_margins(logits, tok, par, nn, u, 1.0)
+        return (m[:, 0] > MARGIN) & (m[:, 1] > MARGIN)
+    u = tie_free_uniforms(clear, rng.random((B, T + 1), dtype=np.float32), rng)
+    for mode in (0, 1):
+        ref = oracle.verify_accept(logits, tok, par, nn, u if mode else None, mode=mode, temperature=1.0)
+        got = b.radar_verify_accept(x, dev(tok), dev(par), dev(nn), dev(u) if mode else None, mode=mode, temperature=1.0)
+        for g, r in zip(got, ref):
+            assert np.array_equal(host(g), r), mode

@@ -269,3 +269,28 @@ def test_expand_is_deterministic_and_workspace_reusable(oracle):
     for o in outs[1:]:
         assert all(np.array_equal(x, y) for x, y in zip(o, outs[0]))
     assert int(ws[:16384].view(torch.int32).abs().sum().item()) == 0    # counters left clean
+
+
+@pytest.mark.parametrize("V", [1, 2, 3, 5, 1026, 4095, 16387, 65534, 130001])   # rows shorter than a load, every remainder of four, each plan
+@pytest.mark.parametrize("offset", [0, 1])                                     # floats between the logits' start and a multiple of 16 bytes
+def test_expand_row_ends_at_any_alignment(oracle, V, offset):
+    """The best logits of each row are its last ones, which a 16-byte load reaches only from before where it belongs, and its
+    first; rows of any alignment, and a row that is preceded and followed by larger values that are not its own."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(synth.seed_for(3, 700 + V % 1000 + offset))
+    F, k = 5, min(V, 7)
+    logits = synth.expand_logits(rng, F, V, 1.0)
+    for f in range(F):
+        for i, j in enumerate(range(max(0, V - 4), V)):
+            logits[f, j] = 8.0 + f + ((i * 3 + f) % 4) * 0.5
+        logits[f, 0] = 7.0 if V > 4 else logits[f, 0]
+    held = torch.full((F * V + 16,), 100.0, device="cuda")
+    held[4 + offset:4 + offset + F * V] = dev(logits).view(-1)
+    x = held[4 + offset:4 + offset + F * V].view(F, V)
+    assert x.data_ptr() % 16 == 4 * offset
+    ps, ppi = (-rng.random(F) * 4).astype(np.float32), np.full(F, -1, np.int32)
+    cp = np_pool(F * k)
+    r = oracle.draft_expand(logits, ps, ppi, k, cp, 0)
+    g = b.radar_draft_expand(x, dev(ps), dev(ppi), k, b.DraftPool(F * k))
+    assert np.array_equal(host(g.cand_tokens).reshape(F, k), r["cand_tokens"])
+    assert np.max(np.abs(host(g.cand_scores).reshape(F, k).astype(np.float64) - r["cand_scores"])) <= SCORE_TOL

@@ -293,3 +293,46 @@ def test_batched_call_argument_errors(oracle):
         b.radar_draft_expand_batch(logits, ps, ppi, k, b.DraftPool(F * k))
     with pytest.raises(b.RadarError):                      # the pools would overflow
         b.radar_draft_expand_batch(logits, ps, ppi, k, b.DraftPool(F * k - 1, B=B))
+
+
+@pytest.mark.parametrize("B,F,V,k", [
+    (64, 4, 1024, 4), (65, 4, 1024, 4), (65, 4, 1026, 4), (65, 4, 1023, 4),    # one round of workgroups, one more (streamed), rows too short for that
+    (32, 4, 16385, 3), (33, 4, 16385, 3), (7, 19, 24583, 16),                  # two chunks in the single launch, three when streamed
+])
+def test_calls_at_the_line_of_the_streaming_form(oracle, B, F, V, k):
+    """Both forms where they meet, with every remainder of four at the rows' ends; the best logits are the last ones of a row."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(synth.seed_for(9, 600 + B + V % 100))
+    logits = rng.standard_normal((B, F, V), dtype=np.float32)
+    logits[:, :, V - 1] = 6.0
+    logits[:, ::2, V - 3:V - 1] = (5.5, 5.0)
+    ps, ppi = (-rng.random((B, F))).astype(np.float32), np.full((B, F), -1, np.int32)
+    pool = b.DraftPool(F * k, B=B)
+    g, _ = b.radar_draft_expand_batch(dev(logits), dev(ps), dev(ppi), k, pool)
+    torch.cuda.synchronize()
+    for s in range(B):
+        cp = dict(tokens=np.zeros(F * k, np.int32), scores=np.zeros(F * k, np.float32), parents=np.zeros(F * k, np.int32))
+        r = oracle.draft_expand(logits[s], ps[s], ppi[s], k, cp, 0)
+        assert np.array_equal(host(g.cand_tokens)[s].reshape(F, k), r["cand_tokens"]), s
+        assert np.max(np.abs(host(g.cand_scores)[s].reshape(F, k).astype(np.float64) - r["cand_scores"])) <= SCORE_TOL
+
+
+def test_a_wavefront_with_more_hot_lanes_than_it_has_room_for(oracle):
+    """k = 16 and rising numbers of lanes of one wavefront above the threshold, on both sides of what the streaming kernel keeps in LDS for them."""
+    from paper_2512_14069_amd import binding as b
+    B, F, V, k = 12, 24, 8192, 16
+    rng = np.random.default_rng(synth.seed_for(9, 650))
+    logits = rng.standard_normal((B, F, V), dtype=np.float32).clip(-3, 3)
+    for r in range(B * F):
+        n = 12 + r % 24                                            # lanes 0 ... n - 1 of the first wavefront hold one logit of 4 ... 5 each,
+        logits.reshape(-1, V)[r, 4 * np.arange(n) + r % 4] = 4.0 + rng.permutation(n) / n
+        groups = 64 + 8 * np.arange(16)                            # and lanes of sixteen other groups, so that the threshold is among these
+        logits.reshape(-1, V)[r, 4 * groups] = 3.5 + rng.permutation(16) / 64
+    ps, ppi = np.zeros((B, F), np.float32), np.full((B, F), -1, np.int32)
+    g, _ = b.radar_draft_expand_batch(dev(logits), dev(ps), dev(ppi), k, b.DraftPool(F * k, B=B))
+    torch.cuda.synchronize()
+    for s in range(B):
+        cp = dict(tokens=np.zeros(F * k, np.int32), scores=np.zeros(F * k, np.float32), parents=np.zeros(F * k, np.int32))
+        r = oracle.draft_expand(logits[s], ps[s], ppi[s], k, cp, 0)
+        assert np.array_equal(host(g.cand_tokens)[s].reshape(F, k), r["cand_tokens"]), s
+        assert np.max(np.abs(host(g.cand_scores)[s].reshape(F, k).astype(np.float64) - r["cand_scores"])) <= SCORE_TOL
