@@ -832,16 +832,6 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
     const int base = blockIdx.x * kStreamChunk;
     const float *rowp = a.logits + (size_t)row * a.V;
     const int K = a.k;
-    // The prediction model's input-free part (w_hh h) of this row's sequence is shared out over the
-    // sequence's workgroups, eight rows each, as the single launch does; the finish kernel reads it.
-    if (a.has_policy && a.pol_has_state) {
-        const int bz = row / a.F;
-        float *gate = a.gate_pre + (size_t)bz * (kCounterBytes / sizeof(float));
-        HiddenRows<4, kStreamThreads / 32> hrows;
-        hrows.load(a.pol, bz, (row - bz * a.F) * gridDim.x + blockIdx.x, a.F * gridDim.x, threadIdx.x / 32);
-        hrows.finish(a.pol, bz, [&](int r, float v) { gate[r] = v; });
-    }
-
     float4 raw[EPT / 4];
 #pragma unroll
     for (int g = 0; g < EPT / 4; ++g) {
@@ -969,6 +959,20 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
         for (int i = 0; i < kStreamWaves; ++i) l += wave_l[i];
         a.part_lm[slot * 2] = (uint64_t)__double_as_longlong(l) & ~kThere;
         a.part_lm[slot * 2 + 1] = __float_as_uint(cm);
+    }
+    // The prediction model's input-free part (w_hh h) of this row's sequence is shared out over the sequence's workgroups, as the
+    // single launch does; the finish kernel reads it.  Here, because in front of the logits it held them up by a round trip (V = 128256, 16
+    // sequences of ten rows, eight calls 147.2 us, now 146.0; 30 of four rows, six calls 91.4 and 88.3).  By the two wavefronts that have no list to write, one or
+    // two rows a lane; where a sequence has few workgroups, hence more rows for each, by all four (40 sequences of ten rows of 8190, six calls 79 us, by two 82).
+    if (a.has_policy && a.pol_has_state) {
+        const int bz = row / a.F, part = (row - bz * a.F) * gridDim.x + blockIdx.x, parts = a.F * gridDim.x;
+        float *const gate = a.gate_pre + (size_t)bz * (kCounterBytes / sizeof(float));
+        auto rows = [&](auto hrows, int hwave) {
+            hrows.load(a.pol, bz, part, parts, hwave);
+            hrows.finish(a.pol, bz, [&](int r, float v) { gate[r] = v; });
+        };
+        if (parts < 64) rows(HiddenRows<4, 2 * kStreamWaves>{}, tid / 32);
+        else if (w >= kStreamWaves / 2) rows(HiddenRows<2, kStreamWaves>{}, tid / 32 - kStreamWaves);
     }
 }
 
