@@ -102,7 +102,7 @@ def test_batches_that_leave_few_workgroups_per_sequence(oracle, V, B):
     compare(ref, got)
 
 
-@pytest.mark.parametrize("V", [2052, 65536, 65540, 131071])      # slices of one and two float4 per lane, their longest, and scalar loads
+@pytest.mark.parametrize("V", [2052, 65536, 65540, 131071])      # slices of one and two float4 per lane, their longest, and rows of any alignment
 @pytest.mark.parametrize("noise", [0.3, 1.5])
 def test_runs_of_acceptances_and_rejections(oracle, V, noise):
     """The statistics of the rows that an accepted first child needs are taken before the decision: chains and bushy

@@ -52,7 +52,7 @@ def run_both_step(oracle, b, logits, ps, ppi, k, gpu_pool, cpu_pool, ws=None):
     (4, 4096, 4),          # config 1
     (1, 128256, 10),       # first draft call of the paper's schedule
     (10, 128256, 10),      # config 3 shape
-    (3, 4097, 5),          # ragged tail, unaligned rows (scalar loads)
+    (3, 4097, 5),          # ragged tail, unaligned rows
     (2, 10, 10),           # k == V
     (7, 12290, 16),        # largest k, tail of two elements
     (64, 8192, 2),         # most rows

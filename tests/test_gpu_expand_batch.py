@@ -22,10 +22,10 @@ GAP = 1e-4
     (5, 10, 32000, 10, 37),        # several sequences, pools already holding candidates
     (16, 10, 128256, 10, 0),       # the 8B shape for a batch of 16: 16 logits per lane, several rounds of workgroups
     (3, 1, 128256, 10, 0),         # first draft call of the paper's schedule (the root alone)
-    (7, 3, 4097, 5, 11),           # ragged tail, unaligned rows (scalar loads)
+    (7, 3, 4097, 5, 11),           # ragged tail, unaligned rows
     (2, 64, 8192, 2, 0),           # most rows
     (1, 4, 4096, 4, 0),            # B = 1 through the batched entry point
-    (40, 3, 40001, 16, 11),        # streaming path (>= 4 Mi logits): odd V (scalar loads), ragged last wavefront, largest k
+    (40, 3, 40001, 16, 11),        # streaming path: odd V, ragged last wavefront, largest k
     (64, 10, 8192, 2, 0),          # streaming path with eight lists per row
     (4, 10, 128256, 10, 700),      # streaming path at its smallest 8B-shaped batch, pools nearly full
 ])
@@ -61,7 +61,7 @@ def test_batched_call_matches_oracle_per_sequence(oracle, B, F, V, k, pre):
 
 @pytest.mark.parametrize("V,k", [(70000, 16), (70001, 16), (65536, 5)])   # both kinds of loads; a last chunk of 4464 logits, none
 def test_streamed_candidate_counts_at_the_edges_of_the_lists(oracle, V, k):
-    """From 4 Mi logits on a call streams chunks of 8192: up to 16 lanes of a wavefront and 128 candidates go through LDS
+    """Calls of more than a round of workgroups stream chunks of 8192: up to 24 lanes of a wavefront and 128 candidates go through LDS
     and up to 16 candidates out unranked.  Rows with that many logits above the rest, and one more or less, distinct
     (order decides) and equal (token id decides), scattered and side by side in one wavefront's columns."""
     from paper_2512_14069_amd import binding as b
