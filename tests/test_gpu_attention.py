@@ -466,3 +466,31 @@ def test_bad_descriptors_are_rejected():
     with pytest.raises(b.RadarError) as e:
         b.radar_tree_attention(q, kv, kv, par, ctx, workspace=b.new_workspace(1 << 20))
     assert e.value.status == -1                                   # 4 query heads over 3 KV heads
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,rows,one", [
+    (8, 16, 8, 128, 20, 2300, True), (8, 16, 8, 128, 20, 2301, False),      # 64 KV heads
+    (12, 16, 8, 128, 17, 3300, True), (12, 16, 8, 128, 17, 3301, False),    # 96
+    (24, 8, 8, 128, 5, 3300, True), (32, 8, 8, 128, 5, 1700, False),        # 192, 256
+    (4, 64, 8, 128, 28, 1850, True), (3, 64, 8, 128, 28, 1401, False),      # 32 and 24 in groups of eight
+    (12, 8, 4, 64, 33, 2660, True), (12, 8, 4, 64, 33, 2661, False),        # 48
+    (8, 16, 8, 64, 9, 16640, True), (8, 16, 8, 64, 9, 16641, False),        # 64
+    (20, 12, 3, 64, 20, 9001, True), (8, 16, 4, 64, 60, 1900, True),        # 60, taken by eights; 32 with 256 units
+])
+def test_long_single_launches_of_many_kv_heads(oracle, B, Hq, Hkv, D, T, rows, one):
+    """Where there are many KV heads one launch goes on to far longer contexts; both sides of each line.  Against the oracle for
+    the longest sequence, the shortest and one in between."""
+    from paper_2512_14069_amd import binding as b
+    nodes = [max(1, T - i % 3) for i in range(B)]
+    ctx = [(rows - T) * (B - i) // B for i in range(B)]
+    a = shape(B, Hq, Hkv, D, T, ctx, nodes, [max(1, min(6, n - 1)) for n in nodes], k=64)
+    assert a.S == rows and (scratch_bytes(b, B, Hq, Hkv, D, T, rows) == 256) == one
+    x = synth.attention_inputs(a, seed=synth.seed_for(1, rows + Hq))
+    got, lse = run_gpu(b, x, want_lse=True)
+    for bb in (0, B // 2, B - 1):
+        n = nodes[bb]
+        ref, ref_lse = oracle.tree_attention(*(np.ascontiguousarray(x[name][bb:bb + 1]) for name in ("q", "k_cache", "v_cache", "parents", "ctx_lens", "n_nodes")),
+                                             want_lse=True)
+        check_close(got[bb, :n], ref[0, :n], f"b={bb}")
+        assert np.max(np.abs(lse[bb, :n] - ref_lse[0, :n])) < LSE_TOL
+        assert np.all(got[bb, n:] == 0) and np.all(lse[bb, n:] == 0)     # unused rows are zeroed
