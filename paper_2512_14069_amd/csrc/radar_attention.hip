@@ -1283,24 +1283,26 @@ struct AttnPlan {
 // (four of 32 heads over 1400 15.6 / 16.9, eight of 8 on 8 with D = 64 over 1600 11.2 / 13.4), and the host does not know which they are.
 //
 // Where there are many KV heads a few ranges of each fill the chip already, and they are long, so one launch stays the better side
-// for much longer.  One launch / ranges over 2520 calls of 96 ... 512 units, even ones and ragged ones whose shortest sequence has a half and an eighth of the rows:
+// for much longer.  One launch / ranges over 3240 calls of 32 ... 512 units, even ones and ragged ones whose shortest sequence has a half and an eighth of the rows:
 // D = 128, 96 KV heads 0.69 ... 0.77 up to 1800 rows, 0.86 ... 1.04 over 3200, 1.04 ... 1.23 over 7000; 128 0.72 ... 0.85, 0.87 ... 0.98, 0.96 ... 1.34 (256 of
-// them, one query head each, stay dealt out); 64 0.80 ... 0.98 up to 1800, 0.98 over 2200, 1.02 over 2600; 32 in groups of eight 0.80 ... 0.97 up to 1800, 1.05 over
-// 2200 (24 of them 0.95 over 1300, 1.05 over 1800).  D = 64, whose ranges are not dealt out: 48 KV heads 0.82 ... 0.98 up to 2600, 0.99 ... 1.08 over 4000; 63 and 64
-// 0.75 ... 0.93 up to 2700, 0.87 ... 0.99 over 10000, one query head each 0.42 ... 0.76 at any length; 32 with 256 units 0.75 ... 0.95 up to 1800, 1.0 over 2200.
+// them, one query head each, stay dealt out); 64 and 80 0.80 ... 0.98 up to 1800, 0.98 over 2200, 0.86 ... 1.04 over 2600; 48 0.94 ... 1.15; 32 in groups of eight 0.80 ... 0.97 up
+// to 1800, 1.05 over 2200 (24 of them 0.95 over 1300, 1.05 over 1800).  D = 64, whose ranges are not dealt out: 48 KV heads 0.82 ... 0.98 up to 2600, 0.99 ... 1.08 over 4000; 63
+// and 64 0.75 ... 0.93 up to 2700, 0.84 ... 0.99 over 10000, but with more units than CUs 0.79 ... 1.13 over 2600 (80 of them 0.93 ... 1.07, 96 0.72 ... 0.91); 96 and more in 320 ... 512
+// units 0.65 ... 0.96 over 1800, 0.45 ... 1.04 over 8000, one query head each 0.4 ... 0.9 at any length; 32 with 256 units 0.75 ... 0.95 up to 1800, 1.0 over 2200.
 static int one_launch_rows(const radar_attn_desc *d, int nqb) {
     const long units = (long)d->B * d->Hq * nqb, kv_heads = (long)d->B * d->Hkv;
     const int G = d->Hq / d->Hkv;
     if (d->D == 64) {
         if (units > 512) return 0;
-        if (units <= 256 && units >= 96 && kv_heads >= 48) return kv_heads >= 60 ? 16640 : 2660;
+        if (kv_heads >= (units <= 256 ? 60 : 96)) return 16640;
+        if (units <= 256 && kv_heads >= 48) return 2660;
         if (units <= 256 && units >= 224 && kv_heads >= 32) return 1900;
         if (units > 256 && nqb == 1) return G <= 4 ? 1600 : 832;
         if (units >= 128) return nqb == 1 && G >= 4 && units < 192 ? 1300 : 1600;
         return G * nqb <= 4 || nqb == 1 ? 832 : 1024;
     }
     if (units > 256) return 0;
-    if (units >= 128 && kv_heads >= 64 && kv_heads < 256) return kv_heads >= 96 ? 3300 : 2300;
+    if (kv_heads >= 64 && kv_heads < 256) return kv_heads >= 96 ? 3300 : 2300;
     if (units >= 192 && kv_heads >= 24 && nqb == 1 && G > 4) return units >= 224 ? 1850 : 1400;
     if (G * nqb <= 4) return units >= 96 ? 800 : units >= 64 && nqb == 2 ? 700 : 384;
     if (nqb == 2 && units >= 64) return units >= 192 ? 1600 : units >= 128 ? 1400 : 900;

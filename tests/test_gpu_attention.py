@@ -476,6 +476,8 @@ def test_bad_descriptors_are_rejected():
     (12, 8, 4, 64, 33, 2660, True), (12, 8, 4, 64, 33, 2661, False),        # 48
     (8, 16, 8, 64, 9, 16640, True), (8, 16, 8, 64, 9, 16641, False),        # 64
     (20, 12, 3, 64, 20, 9001, True), (8, 16, 4, 64, 60, 1900, True),        # 60, taken by eights; 32 with 256 units
+    (8, 8, 8, 64, 3, 7001, True), (8, 8, 8, 128, 3, 2300, True),            # 64 with as few units
+    (12, 32, 8, 64, 20, 5003, True), (20, 16, 4, 64, 20, 1601, False),      # more units than CUs: 96 and 80
 ])
 def test_long_single_launches_of_many_kv_heads(oracle, B, Hq, Hkv, D, T, rows, one):
     """Where there are many KV heads one launch goes on to far longer contexts; both sides of each line.  Against the oracle for
