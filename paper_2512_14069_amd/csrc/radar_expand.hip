@@ -112,22 +112,33 @@ __device__ __forceinline__ void put_frontier(const ExpandArgs &a, const ExpandSm
 }
 
 // Next frontier: the k largest of n candidates by cumulative score (candidate index breaks
-// ties), by one wavefront.  s.cand_key holds zeros from n on.  (By the whole workgroup, each candidate's larger ones counted in parts of the
+// ties), by one wavefront; where they are MANY every wavefront calls.  s.cand_key holds zeros from n on.  (By the whole workgroup, each candidate's larger ones counted in parts of the
 // list, it was bound by LDS: a broadcast read takes as long as any other, 0.4 us of them for 100 candidates.)
 template <bool MANY>                                               // more than kFrontierBlock of them
 __device__ __forceinline__ void pick_frontier(const ExpandArgs &a, ExpandSmem &s, int n, float *conf_lds) {
-    const int lane = lane_id();
-    Picked p;
+    const int lane = lane_id(), w = wave_id();
+    Picked p = {0, kNoRank};
     auto key = [&](int i) { return s.cand_key[i + (lane >> 1) + 32 * (lane & 1)]; };     // (the lanes of a pair far apart: a row's candidates are sorted)
     if constexpr (MANY) {
-        uint64_t kk[5] = {0, 0, 0, 0, 0};                          // (256 at a time: by 128, 256 candidates were two selections, 0.6 us more)
-#pragma unroll 1
-        for (int c0 = 0; c0 < n; c0 += 4 * kWave) {
+        // 256 to a wavefront (by 128, 256 candidates were two selections, 0.6 us more); of more than that the best of each are put together.
+        uint64_t kk[4];
+        if (w * 4 * kWave < n) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) kk[e] = key(c0 + e * kWave);
-            p = wave_pick<5>(kk, a.k, s.wtk[0]);
-            kk[4] = carried(p, a.k);
+            for (int e = 0; e < 4; ++e) kk[e] = key((w * 4 + e) * kWave);
+            p = wave_pick<4>(kk, a.k, s.wtk[w]);
         }
+        if (n > 4 * kWave) {
+            static_assert(RADAR_F_MAX * 16 <= kStreamers * 4 * kWave, "a list for each wavefront that takes part");
+            if (w < kStreamers && lane < RADAR_K_MAX) s.wlist[w * RADAR_K_MAX + lane] = 0;
+            wave_lds_sync();
+            if (w * 4 * kWave < n && p.rank < a.k) s.wlist[w * RADAR_K_MAX + p.rank] = p.key;
+            __syncthreads();
+            if (w == 0) {
+                const uint64_t best[2] = {s.wlist[lane], 0};
+                p = wave_pick<2>(best, a.k, s.wtk[0]);
+            }
+        }
+        if (w != 0) return;
     } else {
         const uint64_t kk[2] = {key(0), key(kWave)};
         p = wave_pick<2>(kk, a.k, s.wtk[0]);
@@ -305,9 +316,7 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
     }
     __syncthreads();
     float *const conf = MODE == kExpPolicy ? &s.pol.in[kPolH] : nullptr;
-    if (w == 0) {
-        pick_frontier<GENERAL>(a, s, n, conf);
-    }
+    if (GENERAL || w == 0) pick_frontier<GENERAL>(a, s, n, conf);
     auto advance = [&](int action) {                               // by one lane
         if (!cycle) return;
         cycle->pool_count = a.pool_count + n;

@@ -294,3 +294,30 @@ def test_expand_row_ends_at_any_alignment(oracle, V, offset):
     g = b.radar_draft_expand(x, dev(ps), dev(ppi), k, b.DraftPool(F * k))
     assert np.array_equal(host(g.cand_tokens).reshape(F, k), r["cand_tokens"])
     assert np.max(np.abs(host(g.cand_scores).reshape(F, k).astype(np.float64) - r["cand_scores"])) <= SCORE_TOL
+
+
+@pytest.mark.parametrize("F,k", [(16, 16), (17, 16), (32, 16), (33, 16), (64, 16), (64, 5), (52, 5), (64, 4)])    # 256 ... 1024 candidates, 256 to a wavefront
+@pytest.mark.parametrize("best", ["anywhere", "last rows", "equal"])
+def test_expand_frontier_of_many_candidates(oracle, F, k, best):
+    """The frontier's entries come from all wavefronts' shares of the candidates, from the last one's alone, and from rows that are the
+    same (the lowest candidate indices win)."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(synth.seed_for(3, 800 + F + k))
+    V = 600
+    logits = synth.expand_logits(rng, F, V, 2.0)
+    ps = (-rng.random(F) * 3).astype(np.float32)
+    if best == "last rows":
+        ps -= np.where(np.arange(F) < F - 2, np.float32(20), np.float32(0))
+    elif best == "equal":
+        logits[:] = logits[0]
+        ps[:] = -1.0
+    cp = np_pool(F * k)
+    r = oracle.draft_expand(logits, ps, np.full(F, -1, np.int32), k, cp, 0)
+    g = b.radar_draft_expand(dev(logits), dev(ps), dev(np.full(F, -1, np.int32)), k, b.DraftPool(F * k))
+    assert np.array_equal(host(g.cand_tokens).reshape(F, k), r["cand_tokens"])
+    flat = np.sort(r["cand_scores"].reshape(-1))[::-1]
+    if best == "equal" or min_boundary_gap(flat, k) > GAP:
+        assert np.array_equal(host(g.frontier_pool_idx), r["frontier_pool_idx"])
+        assert np.array_equal(host(g.frontier_tokens), r["frontier_tokens"])
+    gs = host(g.cand_scores)
+    assert np.array_equal(np.sort(gs)[::-1][:k], np.sort(gs[host(g.frontier_pool_idx)])[::-1])
