@@ -678,11 +678,22 @@ __device__ __forceinline__ LdLane ld_lane_offsets(int kv_ss, int w, int lane) {
     return o;
 }
 
-// Issues this wavefront's four loads of the tile whose first cache row is t0 into the buffer `buf`.
+// One load of 16 bytes a lane that writes LDS directly, 1 KB from the byte address lds on (the same in every lane), from base + off
+// or from the lane's own address.
 // Issued as assembly: told about loads that write LDS, the compiler waits for all of them before the
 // next LDS read it cannot tell apart from their targets, which would undo the run-ahead; the waits for
-// these loads are the explicit ones in the kernel's loop.  (m0 is a reserved register: the compiler
-// sets it right before each of its own uses and warns about the clobber.)  A tile inside the range
+// these loads are the explicit ones in the kernels' loops.  (m0 is a reserved register: the compiler
+// sets it right before each of its own uses and warns about the clobber.)  The load takes its LDS address from m0, which has to have been
+// written one wait state before; inside assembly nobody but this adds it.
+__device__ __forceinline__ void load_to_lds(uint32_t lds, const __bf16 *base, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void load_to_lds(uint32_t lds, const __bf16 *src) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(src) : "memory", "m0");
+}
+
+// Issues this wavefront's four loads of the tile whose first cache row is t0 into the buffer `buf`.
+// A tile inside the range
 // takes a scalar base and the lane's fixed offsets, no vector arithmetic; a tile that reaches past the
 // end of the range clamps every row to the range's last one in K and reads zeros in V.
 template <int D>
@@ -702,8 +713,8 @@ __device__ __forceinline__ void ld_issue_tile(unsigned char *buf, const __bf16 *
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const uint32_t ldsk = lds0 + i * 1024, ldsv = ldsk + kKT * D * 2;
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(ldsk), "v"(o.offk[i]), "s"(kt) : "memory", "m0");
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(ldsv), "v"(o.offv[i]), "s"(vt) : "memory", "m0");
+            load_to_lds(ldsk, kt, o.offk[i]);
+            load_to_lds(ldsv, vt, o.offv[i]);
         }
     } else {
 #pragma unroll
@@ -713,8 +724,8 @@ __device__ __forceinline__ void ld_issue_tile(unsigned char *buf, const __bf16 *
             const __bf16 *gk = kbase + rowoff + ((slot ^ (row & 15)) << 3);
             const __bf16 *gv = t0 + row < kend ? vbase + rowoff + ((slot ^ ((row & 3) << 2)) << 3) : (const __bf16 *)kZeroChunk;
             const uint32_t ldsk = lds0 + i * 1024, ldsv = ldsk + kKT * D * 2;
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(ldsk), "v"(gk) : "memory", "m0");
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(ldsv), "v"(gv) : "memory", "m0");
+            load_to_lds(ldsk, gk);
+            load_to_lds(ldsv, gv);
         }
     }
 }
@@ -989,7 +1000,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
             for (int i = 0; i < LOADS; ++i) {
                 const __bf16 *const src = base + (uint32_t)((row0 + RPL * i) * kv_ss);
                 const uint32_t dst = lds0 + (V ? SUB : 0) + i * 1024;
-                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(V ? offv : offk[i % (16 / RPL)]), "s"(src) : "memory", "m0");
+                load_to_lds(dst, src, V ? offv : offk[i % (16 / RPL)]);
             }
             return;
         }
@@ -1000,7 +1011,7 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
             const __bf16 *src = base + (uint32_t)(min(at, total - 1) * kv_ss) + chunk * 8;
             if (V) src = at < total ? src : (const __bf16 *)kZeroChunk;
             const uint32_t dst = lds0 + (V ? SUB : 0) + i * 1024;
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
+            load_to_lds(dst, src);
         }
     };
     constexpr std::false_type kK{};
