@@ -100,6 +100,9 @@ __device__ __forceinline__ uint64_t key_of_word(uint64_t w) { return w & ~kThere
 __device__ __forceinline__ double sum_of_word(uint64_t w) { return __longlong_as_double((long long)(w & ~kThere)); }   // (sums are not negative)
 __device__ __forceinline__ float max_of_word(uint64_t w) { return __uint_as_float((uint32_t)w); }
 
+// A key that passes any threshold, whatever the value's bits: the two lowest images belong to NaNs and have no bit in a key's upper half.
+__device__ __forceinline__ uint64_t key_of_any(float x, uint32_t idx) { return (uint64_t)max(ord_of(x), 2u) << 31 | (~idx & 0x7fffffffu); }
+
 // Entry `at` of the next frontier is candidate c.  conf_lds, when given, also receives the confidence.
 __device__ __forceinline__ void put_frontier(const ExpandArgs &a, const ExpandSmem &s, int at, int c, float *conf_lds) {
     const float sc = s.cand_sc[c];
@@ -143,7 +146,7 @@ __device__ __forceinline__ void pick_frontier(const ExpandArgs &a, ExpandSmem &s
         const uint64_t kk[2] = {key(0), key(kWave)};
         p = wave_pick<2>(kk, a.k, s.wtk[0]);
     }
-    if (p.rank < a.k) put_frontier(a, s, p.rank, min((int)pick_index(p.key), n - 1), conf_lds);   // (beyond n: only with NaN scores)
+    if (p.rank < a.k) put_frontier(a, s, p.rank, (int)pick_index(p.key), conf_lds);
 }
 
 // Sequence bz of a batched call: every array of the call, the workspace parts and the cycle states
@@ -275,7 +278,7 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
             const int c = fr * K + top.rank;
             s.cand_sc[c] = cum;
             s.cand_tok[c] = tok;
-            s.cand_key[c] = pick_key(cum, uint32_t(c));
+            s.cand_key[c] = key_of_any(cum, uint32_t(c));
             a.cand_tokens[c] = tok;
             a.cand_scores[c] = cum;
             a.pool_tokens[a.pool_count + c] = tok;
@@ -601,11 +604,12 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     const size_t pslot = (size_t)f * a.nchunks + chunk;
     uint64_t *const list = a.part_keys + pslot * RADAR_K_MAX;
     const int nsurv = (int)s.nsurv;
-    if (nsurv > kFastCap) {
-        // Long runs of equal values (more candidates than the list holds): every streaming wavefront
+    if (nsurv > kFastCap || nsurv < min(K, a.V - base)) {
+        // Long runs of equal values (more candidates than the list holds), or NaNs (fewer than the chunk has to give, so that a
+        // row would not have K of them): every streaming wavefront
         // ranks its own logits exactly, four per lane at a time with the selection so far riding
         // along, then one wavefront the four selections.  The logits are read again (a rolled loop
-        // over registers would index them dynamically); this path only runs on heavily tied rows.
+        // over registers would index them dynamically); this path only runs on heavily tied rows and rows of NaN, which rank by their bits here.
         if (streamer) {
             if (lane < RADAR_K_MAX) s.wlist[w * RADAR_K_MAX + lane] = 0;
             uint64_t k5[5] = {0, 0, 0, 0, 0};
@@ -621,7 +625,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
                     for (int u = 0; u < 4; ++u) {
                         const int idx = base + g * (kSLanes * 4) + tid * 4 + u;
                         const float v = row[min(idx, a.V - 1)];
-                        k5[u] = idx < a.V ? pick_key(v, uint32_t(idx)) : 0;
+                        k5[u] = idx < a.V ? key_of_any(v, uint32_t(idx)) : 0;
                     }
                 }
                 const Picked p = wave_pick<5>(k5, K, s.wtk[w]);
@@ -925,8 +929,8 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
     __syncthreads();
     const size_t slot = (size_t)row * a.nchunks + blockIdx.x;
     const int n = (int)nsurv;
-    if (n > kStreamCap) {
-        // Long runs of equal values: every wavefront ranks its own logits exactly, then one ranks the four lists.
+    if (n > kStreamCap || n < min(K, a.V - base)) {
+        // Long runs of equal values, or NaNs: every wavefront ranks its own logits exactly, then one ranks the four lists.
         __syncthreads();                                           // the short path's LDS is overlaid
         if (lane < RADAR_K_MAX) s.ties.wlist[w * RADAR_K_MAX + lane] = 0;
         uint64_t k5[5] = {0, 0, 0, 0, 0};
@@ -942,7 +946,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
                 for (int u = 0; u < 4; ++u) {                      // (read again: a rolled loop would index the registers dynamically)
                     const int idx = base + g * (kStreamThreads * 4) + tid * 4 + u;
                     const float v = rowp[min(idx, a.V - 1)];
-                    k5[u] = idx < a.V ? pick_key(v, uint32_t(idx)) : 0;
+                    k5[u] = idx < a.V ? key_of_any(v, uint32_t(idx)) : 0;
                 }
             }
             const Picked p = wave_pick<5>(k5, K, s.ties.wtk[w]);

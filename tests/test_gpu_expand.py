@@ -321,3 +321,48 @@ def test_expand_frontier_of_many_candidates(oracle, F, k, best):
         assert np.array_equal(host(g.frontier_tokens), r["frontier_tokens"])
     gs = host(g.cand_scores)
     assert np.array_equal(np.sort(gs)[::-1][:k], np.sort(gs[host(g.frontier_pool_idx)])[::-1])
+
+
+@pytest.mark.parametrize("B,F,V,k", [(1, 3, 8192, 6), (1, 10, 131072, 10), (1, 20, 8192, 5), (1, 64, 4096, 16), (1, 2, 524288, 16), (1, 10, 128257, 10), (40, 10, 32768, 10)])   # the last in two launches
+def test_rows_with_fewer_numbers_than_candidates(B, F, V, k):
+    """Rows with no logit that is a number, with fewer than k, with k and one more; rows of numbers among them.  Which tokens such a row
+    gives is not specified, but they are k different ones of the vocabulary, a NaN's with a NaN score, they are in the pool too, and the frontier is
+    k different candidates: nothing of an earlier call is left in any output, and a repeated call gives the same bits."""
+    from paper_2512_14069_amd import binding as b
+    rng = np.random.default_rng(synth.seed_for(3, 950 + F))
+    logits = rng.standard_normal((B, F, V), dtype=np.float32)
+    kept = [None if f % 3 == 2 else (0, 1, k - 1, k, k + 1)[(f - f // 3) % 5] for f in range(F)]
+    for f, n in enumerate(kept):
+        if n is not None:
+            at = np.sort(rng.permutation(V)[:n])
+            row = np.full(V, np.nan, np.float32)
+            row[at] = logits[0, f, at]
+            logits[:, f] = row
+    x, ps, ppi = dev(logits), dev(np.zeros((B, F), np.float32)), dev(np.full((B, F), -1, np.int32))
+    runs = []
+    for left in (123, 77):                                         # what an earlier call may have left
+        pool, out = b.DraftPool(F * k, B=B), b.ExpandOut(F, k, "cuda", B=B)
+        for t in list(vars(out).values()) + [pool.tokens, pool.scores, pool.parents]:
+            t.fill_(left)
+        b.radar_draft_expand_batch(x, ps, ppi, k, pool, out=out)
+        torch.cuda.synchronize()
+        runs.append({n: host(t).copy() for n, t in list(vars(out).items()) + [("pool_" + n, getattr(pool, n)) for n in ("tokens", "scores", "parents")]})
+    for n in runs[0]:
+        assert np.array_equal(runs[0][n], runs[1][n], equal_nan=True), n
+    r = runs[0]
+    tok, sc = r["cand_tokens"].reshape(B, F, k), r["cand_scores"].reshape(B, F, k)
+    for f, n in enumerate(kept):
+        if n is None:
+            assert np.all(np.isfinite(sc[:, f])) and np.all(tok[:, f] >= 0)
+            continue
+        for t, v in zip(tok[:, f], sc[:, f]):
+            assert np.all((t >= 0) & (t < V)) and len(set(t)) == k, (f, n)
+            assert np.all(np.isnan(v[np.isnan(logits[0, f, t])]))
+    assert np.array_equal(r["pool_tokens"].reshape(B, -1), tok.reshape(B, -1))
+    assert np.array_equal(r["pool_scores"].reshape(B, -1), sc.reshape(B, -1), equal_nan=True)
+    assert np.all(r["pool_parents"] == -1)
+    for s in range(B):
+        at = r["frontier_pool_idx"].reshape(B, k)[s]
+        assert len(set(at)) == k and at.min() >= 0 and at.max() < F * k
+        assert np.array_equal(r["frontier_tokens"].reshape(B, k)[s], tok[s].reshape(-1)[at])
+        assert np.array_equal(r["frontier_scores"].reshape(B, k)[s], sc[s].reshape(-1)[at], equal_nan=True)
