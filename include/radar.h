@@ -32,9 +32,10 @@
  *     kernels' launch attributes).
  *   - No call allocates or frees memory.  Scratch memory is a caller-owned
  *     device workspace whose size the matching *_workspace_bytes query gives.
- *     A workspace must be passed once through radar_workspace_init before its
- *     first use (it holds arrival counters that the kernels leave zeroed
- *     again); it may then be reused by any number of calls of the SAME entry
+ *     All of a workspace must be passed once through radar_workspace_init before
+ *     its first use (it holds arrival counters, which the kernels leave zeroed
+ *     again, and words from workgroup to workgroup that carry a mark when they are
+ *     there, of which the kernels leave none); it may then be reused by any number of calls of the SAME entry
  *     point with the SAME descriptor on ONE stream.  Where the counters sit
  *     depends on the entry point and on the shape, so a workspace that goes
  *     over to another entry point or another descriptor is passed through

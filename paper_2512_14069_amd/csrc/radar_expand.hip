@@ -47,7 +47,8 @@ constexpr uint64_t kThere = uint64_t(1) << 63;
 constexpr size_t kGateOffset = 12288, kStreamGateOffset = 14336;   // the prediction model's w_hh h (of which no value is 0 in a single launch), in the counter block
 static_assert((1 + RADAR_F_MAX) * kCounterStride * sizeof(unsigned int) <= kGateOffset && kGateOffset + 4 * kPolH * sizeof(float) <= kStreamGateOffset &&
               kStreamGateOffset + 4 * kPolH * sizeof(float) <= kCounterBytes, "counter block");
-constexpr unsigned int kPollLimit = 1u << 22;         // looks (0.5 us and more each) at what is always on its way: only memory that was never cleared gets there
+// (A workspace is cleared as a whole before its first use: what an uncleared one holds can look like a word.)
+constexpr unsigned int kPollLimit = 1u << 22;         // looks (0.5 us and more each) at what is on its way, unless a second call uses the workspace at the same time
 
 // what a launch carries beside the expansion itself: nothing; a batch or a cycle state; a prediction model, too
 enum { kExpPlain, kExpExt, kExpPolicy };
@@ -211,11 +212,15 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
             missing[0] = keys && !(word_there(w2[0][0]) && word_there(w2[0][1])) && c0 + lane * 2 < nslot;
             missing[1] = keys && !(word_there(w2[1][0]) && word_there(w2[1][1])) && c0 + kWave * 2 + ((lane + 4) & (kWave - 1)) * 2 < nslot;
             missing[2] = sums && !(word_there(w2[2][0]) && max_there(w2[2][1])) && c0 + (sum_at >> 4) < a.nchunks;
-            if (__ballot(missing[0] || missing[1] || missing[2]) == 0) break;
+            if (__ballot(missing[0] || missing[1] || missing[2]) == 0) return;
             asm volatile("" ::: "memory");                         // (else the loads are the ones before)
 #pragma unroll
             for (int e = 0; e < 3; ++e) if (missing[e]) look(fr, c0, e);
         }
+        // Given up (the call's words were overwritten from elsewhere): the row's scores are NaN, and nothing found in their place is taken for a token.
+        pscore = __builtin_nanf("");
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w2[e >> 1][e & 1] = lane * 4 + e < a.V ? key_of_any(pscore, uint32_t(lane * 4 + e)) : 0;
     };
     auto merge_row = [&](int fr, auto &&between) {
         float ml = sum_at < a.nchunks * 16 ? max_of_word(w2[2][1]) : -INFINITY;
@@ -330,7 +335,7 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
     };
     if constexpr (MODE == kExpPolicy) {
         if (POLL && a.pol_has_state && w >= kPolWaves / 2)          // this lane's row of w_hh h
-            for (unsigned int looks = 0; __float_as_uint(pr.hid) == 0 && looks < kPollLimit; ++looks) pr.hid = hidden(policy_gate_row());
+            for (unsigned int looks = 0; __float_as_uint(pr.hid) == 0; ++looks) pr.hid = looks < kPollLimit ? hidden(policy_gate_row()) : __builtin_nanf("");
         // ---- prediction-model step on the new frontier's confidences
         __syncthreads();
         policy_decide<true>(a.pol, bz, a.pol_has_state != 0, s.pol, pr, hidden, advance);
