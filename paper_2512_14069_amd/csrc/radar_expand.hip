@@ -1027,19 +1027,21 @@ static int plan_expand_ept(int F, int V) {
     return 16;
 }
 
-// Workspace of a call over B sequences: [B] counter blocks, [B][F][chunks] chunk lists, sums and maxima
-// (sized for the most chunks any plan uses), [B] w_hh h of the fused prediction model.
-static size_t expand_gate_bytes(size_t B) { return (B * 4 * kPolH * sizeof(float) + 255) & ~size_t(255); }
+// Workspace of a call over B sequences: [B] counter blocks, [B][F][chunks] chunk lists, then [B][F][chunks] sums and maxima: kPartBytes for
+// each chunk of the call's plan.  The size that callers are given goes by 4096 logits (the smallest chunk of any plan) at kSizedBytes each, and
+// kSpareBytes per sequence; callers keep it and the call without a workspace is limited by it, so it stays as it is.  It covers every layout:
+//   - chunks of 4096 are planned for at most kRound workgroups, which take 4 bytes each out of the spare ones;
+//   - larger ones are at most two for three of 4096 where a row has several, and one per row out of the spare bytes where it has one.
+constexpr size_t kPartBytes = (RADAR_K_MAX + 2) * sizeof(uint64_t), kSizedBytes = 140, kSpareBytes = 2048;
+static_assert(kRound * (kPartBytes - kSizedBytes) <= kSpareBytes && RADAR_F_MAX * (kPartBytes - kSizedBytes) <= kSpareBytes &&
+              2 * kPartBytes <= 3 * kSizedBytes && kStreamChunk >= 2 * kExpThreads * kExpMinEPT, "every layout inside the workspace");
 
 static size_t expand_workspace_bytes(const radar_expand_desc *d, size_t B) {
     if (!d || d->F < 1 || d->V < 1 || B < 1) return 0;
-    static_assert(kStreamChunk >= kExpThreads * kExpMinEPT, "the single launch has the smallest chunk");
-    const size_t per_chunk = (size_t)kExpThreads * kExpMinEPT;                // most chunks any plan uses
+    const size_t per_chunk = (size_t)kExpThreads * kExpMinEPT;
     const size_t nchunks = ((size_t)d->V + per_chunk - 1) / per_chunk;
-    size_t bytes = B * kCounterBytes;
-    bytes += B * d->F * nchunks * RADAR_K_MAX * sizeof(uint64_t);
-    bytes += B * d->F * nchunks * (sizeof(double) + sizeof(float));
-    return ((bytes + 255) & ~size_t(255)) + expand_gate_bytes(B);
+    auto round_up = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
+    return round_up(B * kCounterBytes + B * d->F * nchunks * kSizedBytes) + round_up(B * kSpareBytes);
 }
 
 extern "C" size_t radar_draft_expand_workspace_bytes(const radar_expand_desc *d) { return expand_workspace_bytes(d, 1); }
@@ -1079,7 +1081,8 @@ static radar_status launch_expand(const float *logits, const float *parent_score
     const int64_t chunk = stream ? kStreamChunk : (int64_t)kExpThreads * ept;
     const int64_t nchunks = ((int64_t)d->V + chunk - 1) / chunk;
     if (d->F > RADAR_F_MAX || d->k > RADAR_K_MAX || nchunks > kExpMaxChunks) return RADAR_UNSUPPORTED_SHAPE;
-    if (workspace_bytes < expand_workspace_bytes(d, (size_t)B)) return RADAR_WORKSPACE_TOO_SMALL;
+    const size_t cbytes = (size_t)B * kCounterBytes, nslots = (size_t)B * d->F * nchunks;
+    if (workspace_bytes < expand_workspace_bytes(d, (size_t)B) || workspace_bytes < cbytes + nslots * kPartBytes) return RADAR_WORKSPACE_TOO_SMALL;
     if (((uintptr_t)workspace & 255) != 0) return RADAR_INVALID_ARG;
     if (check_only) return RADAR_OK;                               // every argument is acceptable; nothing launched
 
@@ -1092,10 +1095,8 @@ static radar_status launch_expand(const float *logits, const float *parent_score
     a.F = d->F; a.V = d->V; a.k = d->k; a.nchunks = (int)nchunks; a.pool_count = d->pool_count;
     a.pool_capacity = d->pool_capacity;
     char *ws = static_cast<char *>(workspace);
-    const size_t nb = (size_t)B, cbytes = nb * kCounterBytes;
     a.counters = reinterpret_cast<unsigned int *>(ws);
     a.part_keys = reinterpret_cast<uint64_t *>(ws + cbytes);
-    const size_t nslots = nb * d->F * nchunks;
     a.part_lm = a.part_keys + nslots * RADAR_K_MAX;
     a.gate_pre = reinterpret_cast<float *>(ws + (stream ? kStreamGateOffset : kGateOffset));
     a.cycle = cycle;

@@ -126,3 +126,27 @@ def test_host_side_checks_of_the_widened_entry_points(lib):
     small = b.accept_q_desc(1, 60, 60, 1000, 10)
     assert lib.radar_verify_accept_q(one, one, one, one, one, one, one, one, one, one, ctypes.byref(small), one, 16, None) == -3
     assert b.radar_verify_accept_q_workspace_bytes(small) >= 1000 * 4
+
+
+def test_every_layout_of_a_draft_call_fits_its_workspace(lib):
+    """Counter blocks of 16 KB and, for each chunk of the plan, 16 slots, a sum and a maximum of 8 bytes, inside the size that the query
+    gives, for any plan: a single launch with chunks of 4096, 8192 or 16384 logits, or chunks of 8192 streamed."""
+    from paper_2512_14069_amd import binding as b
+
+    def chunks_of_plans(B, F, V):
+        yield -(-V // 8192)                                        # streamed
+        for most in (16, 256):
+            for ept in (4, 8, 16):
+                n = -(-V // (1024 * ept))
+                if F * B * n <= 256 and n <= most:
+                    yield n
+                    return
+        yield -(-V // 16384)
+
+    for B in (1, 2, 3, 7, 16, 64, 257, 4096):
+        for F in (1, 2, 3, 4, 10, 17, 63, 64):
+            for V in (1, 4096, 4097, 8192, 8193, 12289, 32000, 128256, 262145, 524288, 1 << 20):
+                size = b.radar_draft_expand_batch_workspace_bytes(b.expand_desc(F, V, 1, 0, F), B)
+                most = max(chunks_of_plans(B, F, V))
+                assert size >= B * 16384 + B * F * most * 144 and size % 256 == 0, (B, F, V)
+                assert size == -(-(B * 16384 + B * F * -(-V // 4096) * 140) // 256) * 256 + B * 2048       # what callers keep
