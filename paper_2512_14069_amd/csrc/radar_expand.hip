@@ -82,7 +82,8 @@ struct alignas(16) ExpandSmem {
     WaveTopkSmem wtk[kExpWaves];                  // one scratch per wavefront
     uint64_t wlist[kStreamers * RADAR_K_MAX];     // the streaming wavefronts' best (many ties only)
     float gmax[8 * kStreamers];                   // maxima of the 8-lane groups of the streaming wavefronts
-    float wave_l[kStreamers], cmax;               // sum of exp(x - chunk maximum) over each streaming wavefront; the maximum
+    double wave_l[kStreamers];                    // sum of exp(x - chunk maximum) over each streaming wavefront
+    float cmax;                                   // the maximum
     unsigned int nsurv;                           // candidates of the chunk that reached the threshold
     unsigned int ndump[kStreamers];               // lanes of each streaming wavefront whose largest logit reached it
     float tau;                                    // the threshold
@@ -561,16 +562,19 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     }
     __syncthreads();
     if (streamer) {
-        // ---- sum of exp(x - chunk maximum): fp32 exponentials; a lane adds its terms in four fp32 chains,
-        // the wavefront's 64 lanes as a fixed fp32 tree (relative error below 1e-6), the rest is fp64.
+        // ---- sum of exp(x - chunk maximum): fp32 exponentials; a lane adds its terms in fp32 chains of at most eight, as the
+        // streaming kernel does, the rest is fp64 in a fixed order.
         // (x - cm) first: folding the scale into one fused multiply-add would round cm * log2(e), an
         // absolute error in the exponent that grows with |cm|.
-        float tl[4] = {0.f, 0.f, 0.f, 0.f};
+        constexpr int kChains = NE > 32 ? NE / 8 : 4;
+        float tl[kChains] = {};
         if (cm > -INFINITY) {
 #pragma unroll
-            for (int e = 0; e < NE; ++e) tl[e & 3] += __builtin_amdgcn_exp2f((x[e] - cm) * kLog2eF);
+            for (int e = 0; e < NE; ++e) tl[e % kChains] += __builtin_amdgcn_exp2f((x[e] - cm) * kLog2eF);
         }
-        const float wl = wave_sum_f32((tl[0] + tl[1]) + (tl[2] + tl[3]));
+        double ll = ((double)tl[0] + (double)tl[1]) + ((double)tl[2] + (double)tl[3]);
+        if constexpr (kChains == 8) ll += ((double)tl[4] + (double)tl[5]) + ((double)tl[6] + (double)tl[7]);
+        const double wl = wave_sum_f64(ll);
         if (lane == 0) s.wave_l[w] = wl;
         if (tid == 0) s.cmax = cm;
         __builtin_amdgcn_s_setprio(0);
@@ -657,7 +661,7 @@ __global__ __launch_bounds__(kExpThreads, 1) void expand_kernel(const float *log
     if (w == 1) {
         double l = 0.0;                                            // fixed order of addition
 #pragma unroll
-        for (int i = 0; i < kStreamers; ++i) l += (double)s.wave_l[i];
+        for (int i = 0; i < kStreamers; ++i) l += s.wave_l[i];
         uint64_t *const part_lm = late_args()->part_lm + (size_t)bz * F * nchunks * 2;
         if (lane < 2)
             store_shared_result(&part_lm[pslot * 2 + lane], lane == 0 ? (uint64_t)__double_as_longlong(l) | kThere : uint64_t(1) << 32 | __float_as_uint(s.cmax));

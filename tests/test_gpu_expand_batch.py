@@ -336,3 +336,26 @@ def test_a_wavefront_with_more_hot_lanes_than_it_has_room_for(oracle):
         r = oracle.draft_expand(logits[s], ps[s], ppi[s], k, cp, 0)
         assert np.array_equal(host(g.cand_tokens)[s].reshape(F, k), r["cand_tokens"]), s
         assert np.max(np.abs(host(g.cand_scores)[s].reshape(F, k).astype(np.float64) - r["cand_scores"])) <= SCORE_TOL
+
+
+@pytest.mark.parametrize("B,F,V,states", [(4, 8, 131072, False), (4, 10, 131072, True), (3, 10, 131071, False), (5, 10, 131072, False)])   # one launch, the last in two
+def test_sums_keep_small_terms(B, F, V, states):
+    """One logit of 0 at the head of its lane's terms, all others so that each term is just below half an ulp of 1 and vanishes where it is
+    added to the large one in fp32.  A chain has at most eight terms, whatever the form of the call, so seven of them vanish, the sum is rounded to fp32
+    once (2^-24 each), and the small terms themselves are good to 2e-6 of 2^-7.  (With sixteen terms to a chain fifteen vanish, 8.9e-7.)"""
+    from paper_2512_14069_amd import binding as b
+    small, k = np.float32(-24 * np.log(2) - 1e-5), 4
+    x = np.full((B, F, V), small, np.float32)
+    rows = np.arange(B * F)
+    x.reshape(-1, V)[rows, (rows * 37 % 256) * 4] = 0.0
+    want = -np.log1p((V - 1) * np.exp(np.float64(small)))
+    pool = b.DraftPool(F * k + 8, B=B)
+    kw = {}
+    if states:
+        st = np.zeros((B, 4), np.int32)
+        st[:, 1] = 8
+        kw = dict(states=dev(st), pool_count_max=8)
+    g, _ = b.radar_draft_expand_batch(dev(x), dev(np.zeros((B, F), np.float32)), dev(np.full((B, F), -1, np.int32)), k, pool, **kw)
+    got = host(g.cand_scores).reshape(B, F, k)[:, :, 0].astype(np.float64)
+    assert np.array_equal(host(g.cand_tokens).reshape(B * F, k)[:, 0], (rows * 37 % 256) * 4)
+    assert np.max(np.abs(got - want)) <= 8 * 2.0 ** -24 + 2.0 ** -7 * 2e-6 + 1e-9
