@@ -1277,6 +1277,30 @@ struct AttnPlan {
     size_t off_part_o, off_part_ml, off_tab, bytes;
 };
 
+static int unit_blocks(const radar_attn_desc *d, int nqb) { return (d->Hq / d->Hkv * nqb + kGsWaves - 1) / kGsWaves; }
+
+// Number of key ranges: the one that minimises a small cost model, in units of one tile of
+// one workgroup (1.45 us): rounds of 256 resident workgroups x (tiles per range +
+// 3 for prologue and epilogue), plus what the merge of the ranges costs: the launch, and every
+// range's partials written and read again.  Counting whole rounds matters: 576 workgroups take
+// as long as 768.  What a range costs grows with the bytes of its partials (with 0.08 for any, 1300 rows of 32 heads were cut
+// into 22 ranges of one tile, 15.4 us; 11 of two take 13.7).  Over 753 calls of 900 ... 6500 rows, each timed with one to
+// eight tiles per range, this choice is 1.1 % slower than the best one in the geometric mean; 0.08 for any is 1.7 %.
+static long range_count(const radar_attn_desc *d, int nqb) {
+    const double per_range = std::max(0.078, 0.045 + 4e-7 * (double)d->B * d->Hq * d->T_max * d->D);
+    const long units = (long)d->B * d->Hkv * unit_blocks(d, nqb);
+    const long tiles_all = ((long)d->S_max + kKT - 1) / kKT;
+    double best = 1e30;
+    long best_ns = 1;
+    for (long ns = 1; ns <= 64 && ns <= tiles_all; ++ns) {
+        const long tiles = (tiles_all + ns - 1) / ns;
+        const long rounds = (units * ns + 255) / 256;
+        const double cost = (double)rounds * (double)(tiles + 3) + (ns > 1 ? 1.2 + per_range * (double)ns : 0.0);
+        if (cost < best) { best = cost; best_ns = ns; }
+    }
+    return best_ns;
+}
+
 // Up to how many cache rows a call is one launch of whole units (tree_attn_one_kernel): as long as the units are no more
 // than the chip holds at once (one per CU with D = 128, two with D = 64), to where a unit's CU takes as long to read all
 // rows as ranges and their merge take.  That is later the more units there are, because ranges then wait for each other,
@@ -1293,19 +1317,28 @@ struct AttnPlan {
 // past 32 rows in ragged batches would have it earlier (33 tree rows, three sequences of 32 heads, the longest 1533 16.8 / 14.7), in even ones not
 // (four of 32 heads over 1400 15.6 / 16.9, eight of 8 on 8 with D = 64 over 1600 11.2 / 13.4), and the host does not know which they are.
 //
-// Where there are many KV heads a few ranges of each fill the chip already, and they are long, so one launch stays the better side
-// for much longer.  One launch / ranges over 3240 calls of 32 ... 512 units, even ones and ragged ones whose shortest sequence has a half and an eighth of the rows:
-// D = 128, 96 KV heads 0.69 ... 0.77 up to 1800 rows, 0.86 ... 1.04 over 3200, 1.04 ... 1.23 over 7000; 128 0.72 ... 0.85, 0.87 ... 0.98, 0.96 ... 1.34 (256 of
-// them, one query head each, stay dealt out); 64 and 80 0.80 ... 0.98 up to 1800, 0.98 over 2200, 0.86 ... 1.04 over 2600; 48 0.94 ... 1.15; 32 in groups of eight 0.80 ... 0.97 up
-// to 1800, 1.05 over 2200 (24 of them 0.95 over 1300, 1.05 over 1800).  D = 64, whose ranges are not dealt out: 48 KV heads 0.82 ... 0.98 up to 2600, 0.99 ... 1.08 over 4000; 63
-// and 64 0.75 ... 0.93 up to 2700, 0.84 ... 0.99 over 10000, but with more units than CUs 0.79 ... 1.13 over 2600 (80 of them 0.93 ... 1.07, 96 0.72 ... 0.91); 96 and more in 320 ... 512
-// units 0.65 ... 0.96 over 1800, 0.45 ... 1.04 over 8000, one query head each 0.4 ... 0.9 at any length; 32 with 256 units 0.75 ... 0.95 up to 1800, 1.0 over 2200.
-static int one_launch_rows(const radar_attn_desc *d, int nqb) {
+// Where there are many KV heads one launch is the better side for longer.  What it takes is the longest sequence's rows, whatever
+// the others have; ranges go by the largest share of a range, or (dealt out, D = 128) by all rows.  So the lines lie where no batch loses, a
+// single long sequence among short ones included.  One launch / ranges over 10800 calls: even batches, lengths spread from an eighth up,
+// every second or only one sequence long and the others a 16th or a 500th.
+//   D = 128, worst batch: 68 ... 192 KV heads 0.74 ... 1.01 up to 1900 rows, 0.99 ... 1.07 over 2000; more of them 0.97 over 1300, 1.08 over
+//   1900 (256, one query head each, stay dealt out); 64 to 67 from 1.08 over 1200 to 0.92 over 1300, level on average.  Groups of five and
+//   more in 192 units: 40 and more KV heads 0.90 ... 1.01 up to 1400 rows, 24 ... 36 1.07 ... 1.13 over 1200.
+//   D = 64: a workgroup of a range takes four times as long over a row, so with 60 KV heads and more one long sequence loses only where the
+//   ranges are more than four: five 1.03 over 3015 rows, 1.39 over 12000, seven 1.21 over 10600; up to 2660 rows 0.92. Up to four ranges
+//   0.63 ... 0.94 up to 12000 rows (1.14 over 16640); with more units than CUs, of 96 and more KV heads, 0.67 ... 0.91 up to 8000, 1.2 over 12000;
+//   256 and more 0.58 ... 0.84 at any length.  48 KV heads 0.86 ... 1.01 up to 2660 rows, 1.08 over 4000; 32 with 224 units and more 0.80 ... 0.97 over
+//   1900, 1.04 over 2300.
+// (*ranges: the number of ranges, where the line goes by it.)
+static int one_launch_rows(const radar_attn_desc *d, int nqb, long *ranges) {
     const long units = (long)d->B * d->Hq * nqb, kv_heads = (long)d->B * d->Hkv;
     const int G = d->Hq / d->Hkv;
     if (d->D == 64) {
         if (units > 512) return 0;
-        if (kv_heads >= (units <= 256 ? 60 : 96)) return 16640;
+        if (kv_heads >= (units <= 256 ? 60 : 96)) {
+            if (d->S_max > 2660) *ranges = range_count(d, nqb);
+            return *ranges > 4 ? 2660 : kv_heads >= 256 ? INT32_MAX : units <= 256 ? 12000 : 8000;
+        }
         if (units <= 256 && kv_heads >= 48) return 2660;
         if (units <= 256 && units >= 224 && kv_heads >= 32) return 1900;
         if (units > 256 && nqb == 1) return G <= 4 ? 1600 : 832;
@@ -1313,8 +1346,8 @@ static int one_launch_rows(const radar_attn_desc *d, int nqb) {
         return G * nqb <= 4 || nqb == 1 ? 832 : 1024;
     }
     if (units > 256) return 0;
-    if (kv_heads >= 64 && kv_heads < 256) return kv_heads >= 96 ? 3300 : 2300;
-    if (units >= 192 && kv_heads >= 24 && nqb == 1 && G > 4) return units >= 224 ? 1850 : 1400;
+    if (kv_heads >= 68 && kv_heads < 256) return kv_heads <= 192 ? 1850 : 1300;
+    if (units >= 192 && kv_heads >= 40 && nqb == 1 && G > 4) return 1400;
     if (G * nqb <= 4) return units >= 96 ? 800 : units >= 64 && nqb == 2 ? 700 : 384;
     if (nqb == 2 && units >= 64) return units >= 192 ? 1600 : units >= 128 ? 1400 : 900;
     return units >= 192 ? 1100 : units >= 96 ? 800 : 640;
@@ -1341,11 +1374,11 @@ static int64_t one_launch_fetches(const radar_attn_desc *d, int nqb) {          
 
 static AttnPlan plan_attention(const radar_attn_desc *d) {
     AttnPlan p;
-    const int G = d->Hq / d->Hkv;
     p.nqb = d->T_max <= 32 ? 1 : 2;
-    p.n_ublk = (G * p.nqb + kGsWaves - 1) / kGsWaves;
+    p.n_ublk = unit_blocks(d, p.nqb);
     long kps = d->keys_per_split;
-    p.one = kps <= 0 && d->S_max <= one_launch_rows(d, p.nqb);
+    long ranges = 0;
+    p.one = kps <= 0 && d->S_max <= one_launch_rows(d, p.nqb, &ranges);
     p.by_eights = p.one && d->Hkv % 8 != 0 && one_launch_fetches(d, p.nqb) >= 28;
     if (p.by_eights && !one_launch_by_eights_fits(d, p.nqb)) {
         p.by_eights = false;
@@ -1353,25 +1386,9 @@ static AttnPlan plan_attention(const radar_attn_desc *d) {
     }
     if (p.one) kps = ((long)d->S_max + kKT - 1) / kKT * kKT;
     if (kps <= 0) {
-        // Number of key ranges: the one that minimises a small cost model, in units of one tile of
-        // one workgroup (1.45 us): rounds of 256 resident workgroups x (tiles per range +
-        // 3 for prologue and epilogue), plus what the merge of the ranges costs: the launch, and every
-        // range's partials written and read again.  Counting whole rounds matters: 576 workgroups take
-        // as long as 768.  What a range costs grows with the bytes of its partials (with 0.08 for any, 1300 rows of 32 heads were cut
-        // into 22 ranges of one tile, 15.4 us; 11 of two take 13.7).  Over 753 calls of 900 ... 6500 rows, each timed with one to
-        // eight tiles per range, this choice is 1.1 % slower than the best one in the geometric mean; 0.08 for any is 1.7 %.
-        const double per_range = std::max(0.078, 0.045 + 4e-7 * (double)d->B * d->Hq * d->T_max * d->D);
-        const long units = (long)d->B * d->Hkv * p.n_ublk;
+        if (ranges == 0) ranges = range_count(d, p.nqb);
         const long tiles_all = ((long)d->S_max + kKT - 1) / kKT;
-        double best = 1e30;
-        long best_ns = 1;
-        for (long ns = 1; ns <= 64 && ns <= tiles_all; ++ns) {
-            const long tiles = (tiles_all + ns - 1) / ns;
-            const long rounds = (units * ns + 255) / 256;
-            const double cost = (double)rounds * (double)(tiles + 3) + (ns > 1 ? 1.2 + per_range * (double)ns : 0.0);
-            if (cost < best) { best = cost; best_ns = ns; }
-        }
-        kps = (tiles_all + best_ns - 1) / best_ns * kKT;
+        kps = (tiles_all + ranges - 1) / ranges * kKT;
     }
     p.kps = (int)kps;
     p.max_splits = (int)(((long)d->S_max + kps - 1) / kps);

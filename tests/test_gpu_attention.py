@@ -469,15 +469,16 @@ def test_bad_descriptors_are_rejected():
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,D,T,rows,one", [
-    (8, 16, 8, 128, 20, 2300, True), (8, 16, 8, 128, 20, 2301, False),      # 64 KV heads
-    (12, 16, 8, 128, 17, 3300, True), (12, 16, 8, 128, 17, 3301, False),    # 96
-    (24, 8, 8, 128, 5, 3300, True), (32, 8, 8, 128, 5, 1700, False),        # 192, 256
-    (4, 64, 8, 128, 28, 1850, True), (3, 64, 8, 128, 28, 1401, False),      # 32 and 24 in groups of eight
+    (9, 8, 8, 128, 20, 1850, True), (9, 8, 8, 128, 20, 1851, False),        # 72 KV heads
+    (12, 16, 8, 128, 17, 1850, True), (8, 16, 8, 128, 20, 1300, False),     # 96, 64
+    (24, 8, 8, 128, 5, 1850, True), (25, 8, 8, 128, 5, 1301, False), (32, 8, 8, 128, 5, 1700, False),      # 192, 200, 256
+    (5, 48, 8, 128, 28, 1400, True), (4, 64, 8, 128, 28, 1101, False),      # 40 in groups of six and 32 in groups of eight
     (12, 8, 4, 64, 33, 2660, True), (12, 8, 4, 64, 33, 2661, False),        # 48
-    (8, 16, 8, 64, 9, 16640, True), (8, 16, 8, 64, 9, 16641, False),        # 64
+    (8, 16, 8, 64, 9, 12000, True), (8, 16, 8, 64, 9, 12001, False),        # 64
     (20, 12, 3, 64, 20, 9001, True), (8, 16, 4, 64, 60, 1900, True),        # 60, taken by eights; 32 with 256 units
-    (8, 8, 8, 64, 3, 7001, True), (8, 8, 8, 128, 3, 2300, True),            # 64 with as few units
-    (12, 32, 8, 64, 20, 5003, True), (20, 16, 4, 64, 20, 1601, False),      # more units than CUs: 96 and 80
+    (8, 8, 8, 64, 3, 7001, True), (9, 8, 8, 64, 3, 7001, False),            # 64 with as few units; 72, whose ranges are seven
+    (12, 32, 8, 64, 20, 2660, True), (20, 16, 4, 64, 20, 1601, False),      # more units than CUs: 96 and 80
+    (16, 16, 8, 64, 60, 8000, True), (64, 4, 4, 64, 3, 12001, True),        # 128; 256, at any length
 ])
 def test_long_single_launches_of_many_kv_heads(oracle, B, Hq, Hkv, D, T, rows, one):
     """Where there are many KV heads one launch goes on to far longer contexts; both sides of each line.  Against the oracle for

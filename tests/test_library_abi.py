@@ -150,3 +150,23 @@ def test_every_layout_of_a_draft_call_fits_its_workspace(lib):
                 most = max(chunks_of_plans(B, F, V))
                 assert size >= B * 16384 + B * F * most * 144 and size % 256 == 0, (B, F, V)
                 assert size == -(-(B * 16384 + B * F * -(-V // 4096) * 140) // 256) * 256 + B * 2048       # what callers keep
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,longest", [
+    (8, 16, 8, 128, 20, 800), (67, 1, 1, 128, 20, 384), (68, 1, 1, 128, 20, 1850), (9, 8, 8, 128, 60, 1850), (24, 8, 8, 128, 5, 1850), (25, 8, 8, 128, 5, 1300),
+    (4, 64, 8, 128, 28, 1100), (3, 64, 8, 128, 28, 1100), (5, 48, 8, 128, 28, 1400), (6, 40, 8, 128, 28, 1400),
+    (8, 16, 8, 64, 9, 12000), (16, 16, 8, 64, 60, 8000), (12, 32, 8, 64, 20, 2688), (11, 8, 8, 64, 9, 2688), (9, 8, 8, 64, 3, 4416), (65, 4, 4, 64, 9, 3072), (32, 8, 8, 64, 3, None), (64, 8, 8, 64, 20, None),
+])
+def test_how_far_many_kv_heads_go_in_one_launch(lib, B, Hq, Hkv, D, T, longest):
+    """A call of one launch holds no partials.  The lines lie where a batch of one long sequence and many short ones does not lose, which no timing
+    test here can say; 24 and 32 KV heads in groups of eight and up to 67 others are where they were for fewer heads."""
+    from paper_2512_14069_amd import binding as b
+
+    def one(rows):
+        d = b.AttnDesc()
+        d.B, d.T_max, d.Hq, d.Hkv, d.D, d.S_max = B, T, Hq, Hkv, D, rows
+        return lib.radar_tree_attention_workspace_bytes(ctypes.byref(d)) == 256
+    if longest is None:
+        assert all(one(n) for n in (1000, 3201, 12001, 16641, 64000, 1 << 20))
+    else:
+        assert one(longest) and one(longest // 2) and not one(longest + 1)
