@@ -10,9 +10,8 @@ import pytest
 
 from paper_2512_14069_amd import build
 
-# the draft call's form for 64 logits per streaming lane without 16-byte loads: their 64 clamped addresses (4 or 5 registers)
-FEW_SPILLS = re.compile(r"expand_kernelILb0ELi16E")
-MOST_SCALARS = 80                # 71 in the shared walk in laps, 74 in a draft call with the prediction model, 45 in attention over dealt-out rows
+# scalars: 67 in the shared walk in laps, 24 in a draft call with the prediction model, 59 in attention over dealt-out rows
+MOST_SCALARS = {"radar_accept_q.hip": 70, "radar_expand.hip": 28, "radar_attention.hip": 62}
 
 
 def remarks(name):
@@ -37,6 +36,5 @@ def test_no_kernel_spills(compiled, name):
     if name == "radar_accept_q.hip":
         assert sum("accept_q_coop_kernel" in n for n in found[0]) >= 8
     for kernel, scratch, vector, scalar in zip(*found):
-        most = 6 if FEW_SPILLS.search(kernel) else 0
-        assert int(vector) <= most and int(scratch) <= 4 * most, (kernel, scratch, vector)
-        assert int(scalar) <= MOST_SCALARS, (kernel, scalar)
+        assert int(vector) == 0 and int(scratch) == 0, (kernel, scratch, vector)
+        assert int(scalar) <= MOST_SCALARS.get(name, 0), (kernel, scalar)
