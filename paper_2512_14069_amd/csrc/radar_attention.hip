@@ -1131,10 +1131,12 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_one_kernel(const __bf16 
 // there are that many, and 1.1 to 1.5 where the sequence is short); the arguments that only the end needs are read there.
 // heads: KV heads in the lower half, query heads of each in the upper; blocks: n_ublk and nqb likewise.  Not CUT: kps is unit_tab's offset from part_ml.
 struct MergeKernArgs { const uint64_t *part_o; const float *part_ml; const int32_t *ctx_lens, *n_nodes; int T, kps, S, max_splits; uint32_t heads; int blocks; AttnArgs a; };
-template <int D, int E, int NB, int SL, bool CUT>
-__global__ __launch_bounds__(E * SL * 8) void tree_attn_merge_kernel(const uint64_t *part_o, const float *part_ml, const int32_t *ctx_lens, const int32_t *n_nodes,
+constexpr int kMergeSlice = 32;                          // of the head's D
+template <int D, int E, int NB, bool CUT>
+__global__ __launch_bounds__(kAttnThreads * E) void tree_attn_merge_kernel(const uint64_t *part_o, const float *part_ml, const int32_t *ctx_lens, const int32_t *n_nodes,
                                                                           int T, int kps, int S, int max_splits, uint32_t heads, int blocks, AttnArgs) {
-    constexpr int DQ = 8, SLICES = D / SL, kGroup = SL * 8;        // floats per lane; slices of SL of the head's D; lanes of a group
+    constexpr int DQ = 8, SL = kMergeSlice, SLICES = D / SL, kGroup = kAttnThreads;        // floats per lane; lanes of a group
+    static_assert(kGroup == RADAR_T_MAX * (SL / DQ), "a lane for each row and eight of a slice");
     __shared__ float red[E > 1 ? E - 1 : 1][10][kGroup];
     const int slice = blockIdx.x % SLICES, g = blockIdx.x / SLICES, hk = blockIdx.y, b = blockIdx.z;
     const int G = heads >> 16, Hkv = heads & 0xffff, h = hk * G + g, n_ublk = blocks & 0xffff;
@@ -1538,14 +1540,15 @@ extern "C" radar_status radar_tree_attention(const void *q, const void *k_cache,
         // a time), 16 tree rows 11.7 -> 10.6, 8 heads on 2 13.7 -> 12.4, D = 64 on 4 10.6 -> 9.5; with 48 or 64 heads
         // 3000 rows would go from 17.6 to 17.8 and from 19.4 to 19.9.
         const bool wide = (long)d->D / 32 * a.Hq * a.B * (d->T_max > 32 ? 4 : d->T_max > 16 ? 2 : 1) <= 640;
-        auto go = [&](auto kernel, int groups, int width) {
-            return launch("tree_attn_merge", kernel, dim3((unsigned)(d->D / width * a.G), (unsigned)a.Hkv, (unsigned)a.B), dim3((unsigned)(groups * width * 8)), 0, s, a.part_o, a.part_ml, a.ctx_lens, a.n_nodes, a.T,
+        const dim3 mgrid((unsigned)(d->D / kMergeSlice * a.G), (unsigned)a.Hkv, (unsigned)a.B);
+        auto go = [&](auto kernel, int groups) {
+            return launch("tree_attn_merge", kernel, mgrid, dim3((unsigned)(kAttnThreads * groups)), 0, s, a.part_o, a.part_ml, a.ctx_lens, a.n_nodes, a.T,
                           p.shares > 0 ? (int)(p.off_tab - p.off_part_ml) : a.kps, a.S, a.max_splits, (uint32_t)a.Hkv | (uint32_t)a.G << 16, a.n_ublk | a.nqb << 16, a);
         };
-        const hipError_t e = d->D == 64 ? (wide ? go(tree_attn_merge_kernel<64, 1, 18, 32, true>, 1, 32) : go(tree_attn_merge_kernel<64, 1, 8, 32, true>, 1, 32))
-                           : p.shares == 0 ? (wide ? go(tree_attn_merge_kernel<128, 1, 18, 32, true>, 1, 32) : go(tree_attn_merge_kernel<128, 1, 8, 32, true>, 1, 32))
-                           : many       ? (wide ? go(tree_attn_merge_kernel<128, 2, 18, 32, false>, 2, 32) : go(tree_attn_merge_kernel<128, 2, 4, 32, false>, 2, 32))
-                                        : (wide ? go(tree_attn_merge_kernel<128, 1, 18, 32, false>, 1, 32) : go(tree_attn_merge_kernel<128, 1, 8, 32, false>, 1, 32));
+        const hipError_t e = d->D == 64 ? (wide ? go(tree_attn_merge_kernel<64, 1, 18, true>, 1) : go(tree_attn_merge_kernel<64, 1, 8, true>, 1))
+                           : p.shares == 0 ? (wide ? go(tree_attn_merge_kernel<128, 1, 18, true>, 1) : go(tree_attn_merge_kernel<128, 1, 8, true>, 1))
+                           : many       ? (wide ? go(tree_attn_merge_kernel<128, 2, 18, false>, 2) : go(tree_attn_merge_kernel<128, 2, 4, false>, 2))
+                                        : (wide ? go(tree_attn_merge_kernel<128, 1, 18, false>, 1) : go(tree_attn_merge_kernel<128, 1, 8, false>, 1));
         if (e != hipSuccess) return RADAR_HIP_ERROR;
     }
     return RADAR_OK;
