@@ -378,12 +378,11 @@ __device__ __forceinline__ void gs_finish(const AttnArgs &a, Acc O, float m_run,
         if (a.lse && g2 == 0)
             a.lse[((size_t)b * a.T + i) * a.Hq + h] = (i < nn) ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : 0.f;
     } else {
-        // Partial result of this key range: the row's output normalised by its own l and by the row's
-        // largest magnitude, as fp16 -- [D/8][32 rows][8 d], so that a wavefront's 16-byte stores cover 1024
-        // contiguous bytes and the merge reads 16 bytes per lane -- plus (m, l, magnitude) of a row next to each other in fp32.  The partials of all ranges together
-        // outweigh the K/V bytes, and writing them is what the tail of this kernel waits for; halving
-        // them costs 2^-11 of the row's largest element in precision, an eighth of the bf16 rounding of
-        // the final output.  Written through: nothing is left dirty in L2 for the end of the kernel.
+        // Partial result of this key range: the row's output normalised by its own l and by the row's largest magnitude, as fp16 -- [D/8][32 rows][8
+        // d], so that a wavefront's 16-byte stores cover 1024 contiguous bytes and the merge reads 16 bytes per lane -- plus (m, l, magnitude) of a
+        // row next to each other in fp32.  The partials of all ranges together outweigh the K/V bytes, and writing them is what the tail of this
+        // kernel waits for; halving them costs 2^-11 of the row's largest element in precision, an eighth of the bf16 rounding of the final output.
+        // Written through: nothing is left dirty in L2 for the end of the kernel.
         // Two lanes share a row: the halves of two blocks of eight d change places, and each of the lanes stores 16 bytes of one.
         const int j32 = i & 31, slot = __builtin_amdgcn_readfirstlane(entry);
         const auto po = __builtin_amdgcn_make_buffer_rsrc(a.part_o + (size_t)slot * (D / 4 * 32), 0, D * 64, 0x00027000);
@@ -446,16 +445,15 @@ __global__ __launch_bounds__(kGsThreads) void tree_attn_gs_kernel(const __bf16 *
     const __bf16 *vbase = v_ + (size_t)b * kv_sb + (size_t)hk * kv_sh;
     const int kv_ss = kv_ss_;                // 32-bit offsets inside one head's cache (checked on the host)
 
-    // The first tile and the query rows are requested before the sequence's context length and tree size
-    // are known (two dependent scalar loads, most of a microsecond in a cold start): rows are clamped to
-    // the cache the caller described instead of to the end of the range.  Whatever rows past that end
-    // hold is never used: their scores are masked by selection and their V rows zeroed on the way into
-    // LDS, both from the range's real end below.
-    // DEEP (ranges of many tiles): staging runs two tiles ahead through two register sets, which hides
-    // HBM latency better but doubles the loop's code; short ranges keep the compact one-ahead loop
-    // (their time goes into a cold start, where code size counts).
+    // The first tile and the query rows are requested before the sequence's context length and tree size are known (two dependent scalar loads, most
+    // of a microsecond in a cold start): rows are clamped to the cache the caller described instead of to the end of the range.  Whatever rows past
+    // that end hold is never used: their scores are masked by selection and their V rows zeroed on the way into LDS, both from the range's real end
+    // below.
+    // DEEP (ranges of many tiles): staging runs two tiles ahead through two register sets, which hides HBM latency better but doubles the loop's
+    // code; short ranges keep the compact one-ahead loop (their time goes into a cold start, where code size counts).
     // A range of two tiles asks for both at once (asked for after the first had come, the second was consumed 1.25 us after it: 32 heads over 2048
-    // rows 13.5 us for the call, 12.6 with this and the shorter ways to the first loads here and in the merge); with more of them the first would wait for the second's bytes (16 heads on 8 x 2 over 750 rows 10.7 -> 11.5).
+    // rows 13.5 us for the call, 12.6 with this and the shorter ways to the first loads here and in the merge); with more of them the first would
+    // wait for the second's bytes (16 heads on 8 x 2 over 750 rows 10.7 -> 11.5).
     GsTileRegs<D> regs0, regs1;
     gs_load_tile<D>(regs0, kbase, vbase, kv_ss, kbeg, S, tid);
     const bool both = !DEEP && kps > kKT && kps <= 2 * kKT;
@@ -1303,21 +1301,23 @@ static long range_count(const radar_attn_desc *d, int nqb) {
     return best_ns;
 }
 
-// Up to how many cache rows a call is one launch of whole units (tree_attn_one_kernel): as long as the units are no more
-// than the chip holds at once (one per CU with D = 128, two with D = 64), to where a unit's CU takes as long to read all
-// rows as ranges and their merge take.  That is later the more units there are, because ranges then wait for each other,
-// and earlier where a KV head has at most four: half of a range's wavefronts are idle then, and it takes a tile the faster.
-// Both sides measured for 633 combinations of batch, heads and tree at ten contexts of 150 ... 1850 rows; one launch / ranges in us, at
-// D = 128, 60 tree rows: 32 heads 8.3 / 10.7 over 260 rows, 9.9 / 11.2 over 540, 11.6 / 12.1 over 820, 13.1 / 13.1 over 1050; 64
-// heads 10.3 / 13.6 over 620, 13.1 / 15.2 over 1050, 14.8 / 16.2 over 1360, 17.5 / 17.4 over 1560; four sequences of 32 heads
-// 10.6 / 15.2 over 540, 17.5 / 19.5 over 1560; 16 heads on 8 KV heads 8.6 / 9.3 over 360, 9.8 / 9.9 over 540; 16 tree rows, 32
-// heads 8.0 / 8.6 over 316, 9.2 / 8.6 over 496, three sequences 9.6 / 10.3 over 626.  D = 64, 8 heads on 4: 8.1 / 8.6 over 820, 9.1 / 8.5 over 960; 16 on 4 over 1000 rows, 60 tree
-// rows, one / four / eight sequences 9.4 / 9.8, 9.8 / 11.0, 10.2 / 15.3; eight of 16 heads 8.6 / 11.8 over 820, 11.7 / 18.3 over 1560.  Two units of at
-// most 32 tree rows per CU (D = 64, more than 256) take longer over a row: 16 tree rows, 32 sequences of 16 heads on 2 10.3 / 11.1 over
-// 640, 13.0 / 12.8 over 900; 64 of 8 on 8 22.3 / 35.1 over 900, 33.0 / 52.2 over 1600; 32 of 12 on 3 13.7 / 15.6 over 1100, 17.7 / 18.5 over 1600.
-// Over all of these the better side is missed by 0.8 % in the geometric mean, as by a line between the two sides' estimated times.  Trees just
-// past 32 rows in ragged batches would have it earlier (33 tree rows, three sequences of 32 heads, the longest 1533 16.8 / 14.7), in even ones not
-// (four of 32 heads over 1400 15.6 / 16.9, eight of 8 on 8 with D = 64 over 1600 11.2 / 13.4), and the host does not know which they are.
+// Up to how many cache rows a call is one launch of whole units (tree_attn_one_kernel): as long as the units are no more than the chip holds at once
+// (one per CU with D = 128, two with D = 64), to where a unit's CU takes as long to read all rows as ranges and their merge take.  That is later the
+// more units there are, because ranges then wait for each other, and earlier where a KV head has at most four: half of a range's wavefronts are idle
+// then, and it takes a tile the faster.
+// Both sides measured for 633 combinations of batch, heads and tree at ten contexts of 150 ... 1850 rows; one launch / ranges in us, at D = 128, 60
+// tree rows: 32 heads 8.3 / 10.7 over 260 rows, 9.9 / 11.2 over 540, 11.6 / 12.1 over 820, 13.1 / 13.1 over 1050; 64 heads 10.3 / 13.6 over 620, 13.1
+// / 15.2 over 1050, 14.8 / 16.2 over 1360, 17.5 / 17.4 over 1560; four sequences of 32 heads 10.6 / 15.2 over 540, 17.5 / 19.5 over 1560; 16 heads on
+// 8 KV heads 8.6 / 9.3 over 360, 9.8 / 9.9 over 540; 16 tree rows, 32 heads 8.0 / 8.6 over 316, 9.2 / 8.6 over 496, three sequences 9.6 / 10.3 over
+// 626.
+// D = 64, 8 heads on 4: 8.1 / 8.6 over 820, 9.1 / 8.5 over 960; 16 on 4 over 1000 rows, 60 tree rows, one / four / eight sequences 9.4 / 9.8, 9.8 /
+// 11.0, 10.2 / 15.3; eight of 16 heads 8.6 / 11.8 over 820, 11.7 / 18.3 over 1560.
+// Two units of at most 32 tree rows per CU (D = 64, more than 256) take longer over a row: 16 tree rows, 32 sequences of 16 heads on 2 10.3 / 11.1
+// over 640, 13.0 / 12.8 over 900; 64 of 8 on 8 22.3 / 35.1 over 900, 33.0 / 52.2 over 1600; 32 of 12 on 3 13.7 / 15.6 over 1100, 17.7 / 18.5 over
+// 1600.
+// Over all of these the better side is missed by 0.8 % in the geometric mean, as by a line between the two sides' estimated times.  Trees just past
+// 32 rows in ragged batches would have it earlier (33 tree rows, three sequences of 32 heads, the longest 1533 16.8 / 14.7), in even ones not (four
+// of 32 heads over 1400 15.6 / 16.9, eight of 8 on 8 with D = 64 over 1600 11.2 / 13.4), and the host does not know which they are.
 //
 // Where there are many KV heads one launch is the better side for longer.  What it takes is the longest sequence's rows, whatever
 // the others have; ranges go by the largest share of a range, or (dealt out, D = 128) by all rows.  So the lines lie where no batch loses, a

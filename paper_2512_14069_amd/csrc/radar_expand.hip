@@ -116,9 +116,9 @@ __device__ __forceinline__ void put_frontier(const ExpandArgs &a, const ExpandSm
     if (conf_lds) conf_lds[at] = conf;
 }
 
-// Next frontier: the k largest of n candidates by cumulative score (candidate index breaks
-// ties), by one wavefront; where they are MANY every wavefront calls.  s.cand_key holds zeros from n on.  (By the whole workgroup, each candidate's larger ones counted in parts of the
-// list, it was bound by LDS: a broadcast read takes as long as any other, 0.4 us of them for 100 candidates.)
+// Next frontier: the k largest of n candidates by cumulative score (candidate index breaks ties), by one wavefront; where they are MANY every
+// wavefront calls.  s.cand_key holds zeros from n on.  (By the whole workgroup, each candidate's larger ones counted in parts of the list, it was
+// bound by LDS: a broadcast read takes as long as any other, 0.4 us of them for 100 candidates.)
 template <bool MANY>                                               // more than kFrontierBlock of them
 __device__ __forceinline__ void pick_frontier(const ExpandArgs &a, ExpandSmem &s, int n, float *conf_lds) {
     const int lane = lane_id(), w = wave_id();
@@ -363,9 +363,9 @@ __device__ __forceinline__ void expand_finish(ExpandArgs &a, ExpandSmem &s, int 
 // MODE: the plain expansion is compiled without any code for batches, cycle states or the prediction model.
 // GENERAL: any number of chunks, rows and candidates at the call's end (launch_expand).
 // A call is a chain of dependent stages, none of which is bound by bandwidth: F = 10, V = 128256, k = 10 takes 6.1 us per call on warm logits.
-// (With lists announced by tickets once their stores were acknowledged 7.9; then 7.1, until the selections compared by sign
-// bits and ranked what passes in parts, radar_topk.h: ten rows of 128257 with k = 16 12.2 -> 9.1, of 200000 16.8 -> 9.0.)  Lists longer than 16 slots need no ranking at all, but
-// the last workgroup's loads are slow (from beyond its L2, 37 bytes per ns): 24 slots cost it 0.4 us, records of 32 0.7.
+// (With lists announced by tickets once their stores were acknowledged 7.9; then 7.1, until the selections compared by sign bits and ranked what
+// passes in parts, radar_topk.h: ten rows of 128257 with k = 16 12.2 -> 9.1, of 200000 16.8 -> 9.0.)  Lists longer than 16 slots need no ranking at
+// all, but the last workgroup's loads are slow (from beyond its L2, 37 bytes per ns): 24 slots cost it 0.4 us, records of 32 0.7.
 // The leading arguments are what the stream waits for; they are in registers when the kernel starts (0.25 us).
 //
 // Up to how many workgroups all count on one counter: they wait for each other there, some 10 ns each, but the last one is
@@ -873,9 +873,9 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
             x[e] = idx < a.V ? x[e] : -INFINITY;
         }
     }
-    // ---- the maxima of the 32 eight-lane groups: the chunk's maximum, and as threshold of its top-k their k-th
-    // largest (at least k logits of the chunk reach it, one per group whose maximum does; on untied data 1.2 k to 1.4 k.
-    // Of sixteen groups the 16th largest is the smallest, which lets the whole chunk through: 64 sequences of 16 rows, V = 32000, k = 16 took 57 us instead of 30.)
+    // ---- the maxima of the 32 eight-lane groups: the chunk's maximum, and as threshold of its top-k their k-th largest (at least k logits of the
+    // chunk reach it, one per group whose maximum does; on untied data 1.2 k to 1.4 k. Of sixteen groups the 16th largest is the smallest, which lets
+    // the whole chunk through: 64 sequences of 16 rows, V = 32000, k = 16 took 57 us instead of 30.)
     float tm = x[0];
 #pragma unroll
     for (int e = 1; e < EPT; ++e) tm = fmaxf(tm, x[e]);
@@ -982,10 +982,11 @@ __global__ __launch_bounds__(kStreamThreads, 8) void expand_stream_kernel(const 
         a.part_lm[slot * 2] = (uint64_t)__double_as_longlong(l) & ~kThere;
         a.part_lm[slot * 2 + 1] = __float_as_uint(cm);
     }
-    // The prediction model's input-free part (w_hh h) of this row's sequence is shared out over the sequence's workgroups, as the
-    // single launch does; the finish kernel reads it.  Here, because in front of the logits it held them up by a round trip (V = 128256, 16
-    // sequences of ten rows, eight calls 147.2 us, now 146.0; 30 of four rows, six calls 91.4 and 88.3).  By the two wavefronts that have no list to write, one or
-    // two rows a lane; where a sequence has few workgroups, hence more rows for each, by all four (40 sequences of ten rows of 8190, six calls 79 us, by two 82).
+    // The prediction model's input-free part (w_hh h) of this row's sequence is shared out over the sequence's workgroups, as the single launch does;
+    // the finish kernel reads it.  Here, because in front of the logits it held them up by a round trip (V = 128256, 16 sequences of ten rows, eight
+    // calls 147.2 us, now 146.0; 30 of four rows, six calls 91.4 and 88.3).  By the two wavefronts that have no list to write, one or two rows a
+    // lane; where a sequence has few workgroups, hence more rows for each, by all four (40 sequences of ten rows of 8190, six calls 79 us, by two
+    // 82).
     if (a.has_policy && a.pol_has_state) {
         const int bz = row / a.F, part = (row - bz * a.F) * gridDim.x + blockIdx.x, parts = a.F * gridDim.x;
         float *const gate = a.gate_pre + (size_t)bz * (kCounterBytes / sizeof(float));
@@ -1075,9 +1076,10 @@ static radar_status launch_expand(const float *logits, const float *parent_score
     const bool vec4 = (d->V % 4 == 0) && (((uintptr_t)logits & 15) == 0);
     const int ept = plan_expand_ept((int)std::min<int64_t>((int64_t)d->F * B, 1 << 20), d->V);
     // Batches whose single launch would take more than one round of the chip stream.  In one round the single launch is the faster one at any size
-    // (ten rows of V = 128256, three sequences 7.1 us per call, streamed 9.0; four rows of 8190, 64 sequences 4.9 and 7.2), the second round
-    // starts behind the whole first (eight rows of 50257: 320 workgroups 10.5 and 9.7, 480 13.4 and 11.1).  Where sequences may have stopped, which the host does not
-    // know, the line is a quarter of a round further out: 300 workgroups of which some leave at once 0.91 ... 1.07 of the streamed time, 384 1.09 ... 0.86.
+    // (ten rows of V = 128256, three sequences 7.1 us per call, streamed 9.0; four rows of 8190, 64 sequences 4.9 and 7.2), the second round starts
+    // behind the whole first (eight rows of 50257: 320 workgroups 10.5 and 9.7, 480 13.4 and 11.1).  Where sequences may have stopped, which the host
+    // does not know, the line is a quarter of a round further out: 300 workgroups of which some leave at once 0.91 ... 1.07 of the streamed time, 384
+    // 1.09 ... 0.86.
     const int64_t groups = (int64_t)B * d->F * (((int64_t)d->V + kExpThreads * ept - 1) / (kExpThreads * ept));
     const int64_t line = cycle != nullptr && d->pool_count > 0 ? kRound + kRound / 4 : kRound;
     const bool stream = B > 1 && (int64_t)B * d->F <= 65535 &&
