@@ -146,7 +146,8 @@ radar_status radar_tree_attention(const void *q, const void *k_cache, const void
  *
  * Limits: 1 <= F <= RADAR_F_MAX; 1 <= k <= min(RADAR_K_MAX, V);
  *         pool_count + F*k <= pool_capacity.  -inf logits are legal; NaN
- *         logits and rows that are entirely -inf give unspecified results.
+ *         logits and rows that are entirely -inf give unspecified results
+ *         (every output is written, tokens are tokens of the vocabulary).
  */
 typedef struct radar_expand_desc {
     int32_t F, V, k;
