@@ -3,7 +3,7 @@
 //
 // Phase 1, grid (blocks of the vocabulary, sequences, tree rows): one streaming
 // read of target logits.  Every wavefront owns NB x 1024 consecutive logits and
-// leaves, per 1024, their arg-max key and, in sampling mode, (max, sum exp) of the
+// leaves, per 1024, their arg-max key or, in sampling mode, (max, sum exp) of the
 // temperature-scaled values; nothing is combined inside a workgroup.  Phase 2: the
 // workgroup whose arrival ticket is the last of its ROW merges that row's partials
 // in one wavefront and turns the sums into masses relative to the row maximum.
@@ -69,11 +69,11 @@ struct AcceptArgs {
     double inv_temp;
     unsigned int *counters;     // [(b*T + r) * stride] workgroups of a row and its marks, [(B*T + b) * stride] finished rows
                                 // of a sequence, [(B*T + B + b) * stride] node its walk has arrived at (0: the root)
-    uint64_t *row_key;          // [B][T] arg-max key of the row
-    double *row_L;              // [B][T] sum of exp(y - row_M), y = logit / temperature
+    uint64_t *row_key;          // [B][T] greedy: arg-max key of the row
+    double *row_L;              // [B][T] sampling: sum of exp(y - row_M), y = logit / temperature
     float *row_M;               // [B][T]
-    uint64_t *part_key;         // [B][T][nsub] arg-max key of the block
-    double *part_l;             // [B][T][nsub] sum of exp(y - part_m) over the block; once the row is merged:
+    uint64_t *part_key;         // [B][T][nsub] greedy: arg-max key of the block
+    double *part_l;             // [B][T][nsub] sampling: sum of exp(y - part_m) over the block; once the row is merged:
                                 //              sum of exp(y - row_M) over the block
     float *part_m;              // [B][T][nsub] reference maximum of the block
 };
@@ -148,8 +148,13 @@ __device__ __forceinline__ unsigned int wave_fetch_add(unsigned int *p, unsigned
 
 // NB: 1024-logit blocks per wavefront, all requested at once
 // LAST: the walk is left to the last row of the sequence (greedy only).
+// A sampled walk and the distribution ask for nobody's arg-max; with the keys found, stored, fetched and merged all the same a sampled call
+// over 9 trees of 5 nodes, V = 45299, took 9.78 us (now 9.41), two of 16, V = 51757, 9.08 (8.58), the distribution of 11 trees of V = 128256
+// 18.68 (17.45).  The sampled kernel fits into 72 registers so, seven wavefronts per SIMD, but six are the better number: with more the other rows'
+// logits are in front of the root's in the memory's queue, with fewer too little is in flight (61 rows of V = 128256 with seven, six, four
+// 11.73, 11.33, 11.73 us).
 template <int MODE, bool LAST, bool VEC4, int NB>
-__global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
+__global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, MODE == RADAR_ACCEPT_SAMPLE ? 6 : 8))) void accept_kernel(AcceptArgs a) {
     __shared__ AcceptSmem s;
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int b = blockIdx.y, r = blockIdx.z;
@@ -209,13 +214,6 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
 #pragma unroll
             for (int e = 1; e < kAccEPT; ++e) tmx = fmaxf(tmx, x[i][e]);
             const float wmx = wave_max_f32(tmx);
-            uint32_t bi = 0xffffffffu;
-            if (tmx == wmx) {
-#pragma unroll
-                for (int e = kAccEPT - 1; e >= 0; --e) bi = (x[i][e] == wmx) ? uint32_t(first[i][e / 4] + (e & 3)) : bi;
-            }
-            bi = ~wave_max_u32(~bi);                              // lowest index over the wavefront
-            const uint64_t best = bi < (uint32_t)a.V ? make_key(wmx, bi) : 0;
             const size_t pslot = ((size_t)b * a.T + r) * a.nsub + sub0 + i;
             const bool live = NB == 1 || sub0 + i < a.nsub;       // wave-uniform
             if (sampling) {
@@ -237,7 +235,16 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
                     store_shared_result(&a.part_l[pslot], wl);
                 }
             }
-            if (lane == 0 && live) store_shared_result(&a.part_key[pslot], best);
+            if constexpr (!sampling) {
+                uint32_t bi = 0xffffffffu;
+                if (tmx == wmx) {
+#pragma unroll
+                    for (int e = kAccEPT - 1; e >= 0; --e) bi = (x[i][e] == wmx) ? uint32_t(first[i][e / 4] + (e & 3)) : bi;
+                }
+                bi = ~wave_max_u32(~bi);                          // lowest index over the wavefront
+                const uint64_t best = bi < (uint32_t)a.V ? make_key(wmx, bi) : 0;
+                if (lane == 0 && live) store_shared_result(&a.part_key[pslot], best);
+            }
         }
     }
     // What the walk needs to know of the tree is fetched beside the stream's last results: behind the ticket it was a round
@@ -283,8 +290,10 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         for (int i = 0; i < 2; ++i) {
             const int c0 = i * kWave + lane;
             const int cc = min(c0, a.nsub - 1);                  // branch-free: clamp, load, mask
-            const uint64_t k2 = load_shared_result(&a.part_key[p0 + cc]);
-            kb = max_u64(kb, c0 < a.nsub ? k2 : 0);
+            if constexpr (!sampling) {
+                const uint64_t k2 = load_shared_result(&a.part_key[p0 + cc]);
+                kb = max_u64(kb, c0 < a.nsub ? k2 : 0);
+            }
             m_[i] = -INFINITY; l_[i] = 0.0;
             if (sampling) {
                 const float m2 = load_shared_result(&a.part_m[p0 + cc]);
@@ -294,10 +303,10 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         }
         float mmax = fmaxf(m_[0], m_[1]);
         for (int c0 = 2 * kWave + lane; c0 < a.nsub; c0 += kWave) {
-            kb = max_u64(kb, load_shared_result(&a.part_key[p0 + c0]));
-            if (sampling) mmax = fmaxf(mmax, load_shared_result(&a.part_m[p0 + c0]));
+            if (!sampling) kb = max_u64(kb, load_shared_result(&a.part_key[p0 + c0]));
+            else mmax = fmaxf(mmax, load_shared_result(&a.part_m[p0 + c0]));
         }
-        kb = wave_max_u64(kb);
+        if constexpr (!sampling) kb = wave_max_u64(kb);
         M = wave_max_f32(mmax);
         double lsum = 0.0;
         if (sampling) {
@@ -321,8 +330,9 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
         L = wave_sum_f64(lsum);
         if (lane == 0) {
             const size_t rs = (size_t)b * a.T + r;
-            store_shared_result(&a.row_key[rs], kb);
-            if (sampling) {
+            if constexpr (!sampling) {
+                store_shared_result(&a.row_key[rs], kb);
+            } else {
                 store_shared_result(&a.row_M[rs], M);
                 store_shared_result(&a.row_L[rs], L);
             }
@@ -411,14 +421,15 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(AcceptArgs a) {
     auto take_rows = [&](bool take, bool own) {
         if (take) {
             const size_t rs = (size_t)b * a.T + lane;
-            const uint64_t key = own ? kb : load_shared_result(&a.row_key[rs]);
-            if (sampling) {
+            if constexpr (!sampling) {
+                const uint64_t key = own ? kb : load_shared_result(&a.row_key[rs]);
+                s.row_arg[lane] = (int)key_index(key);
+            } else {
                 const float Mr = own ? M : load_shared_result(&a.row_M[rs]);
                 const double Lr = own ? L : load_shared_result(&a.row_L[rs]);
                 s.row_M[lane] = Mr;
                 s.row_L[lane] = Lr;
             }
-            s.row_arg[lane] = (int)key_index(key);
         }
         const uint64_t fresh = __ballot(take);
         have |= fresh;
