@@ -188,6 +188,14 @@ def test_large_vocabulary_many_blocks(oracle, mode):
     compare(oracle, b, x, mode)
 
 
+@pytest.mark.parametrize("V", [65536, 65537, 131072, 131073, 196609])
+def test_edges_of_the_groups_of_blocks(oracle, V):
+    """64, 65, 128, 129 and 193 blocks of 1024 logits per row: the merging wavefront takes their sums and maxima 64 at a time."""
+    from paper_2512_14069_amd import binding as b
+    a = small_shape(3, 9, (9, 1, 4), (3, 0, 2), k=3)
+    compare(oracle, b, synth.accept_inputs(a, V, seed=79), 1)
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("B,T,V,chain", [(3, 64, 40000, True), (6, 64, 34000, False), (12, 64, 65539, False),
                                           (13, 64, 61001, True)])       # the rows behind the roots wait for the walk

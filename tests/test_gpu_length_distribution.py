@@ -52,7 +52,7 @@ def lift(x):
     return x
 
 
-@pytest.mark.parametrize("V,temperature", [(4096, 1.0), (5000, 0.7), (128256, 1.0)])
+@pytest.mark.parametrize("V,temperature", [(4096, 1.0), (5000, 0.7), (65537, 1.0), (128256, 1.0), (131073, 0.7)])
 def test_ragged_batch_matches_oracle(oracle, V, temperature):
     from paper_2512_14069_amd import binding as b
     a = small_shape(5, 40, (40, 1, 17, 33, 2), (6, 0, 3, 8, 1), k=5)
