@@ -24,7 +24,8 @@
 // What bounds a call is then the chain of decisions and the starting of workgroups, not
 // the logits' bytes: 61 rows of V = 128256, 16 sequences, paths of 0, 1, 2, 4 and 8 nodes 17.6, 23.3,
 // 25.1, 27.7 and 32.6 us greedy and 23.3, 29.1, 31.5, 34.5 and 42.6 sampled (129 when every row is
-// read); one sequence 7.5 ... 8.0 and 10.9 ... 14.4 us.  In a large launch the
+// read); one sequence 7.5 ... 8.0 and 10.9 ... 14.4 us (the sampled figures are from before
+// keys, pairs and the roots' order changed, which took 2 ... 14 % off them).  In a large launch the
 // workgroups behind the roots' rows hold back until the roots are decided (below).
 #include <algorithm>
 
@@ -172,7 +173,8 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
     const int b = blockIdx.y, r = blockIdx.z;
     constexpr bool sampling = MODE != RADAR_ACCEPT_GREEDY;      // row statistics are needed
     // A root's row is there whatever the number of nodes, and everything waits for it: its logits are asked for first, the number of nodes
-    // beside the tree's arrays (61 rows of V = 128256 11.08 us, so 10.90; the distribution of 11 trees 17.33 and 17.19).  Greedy roots have nothing to do meanwhile (16 trees 18.6 us, so 18.9).
+    // beside the tree's arrays (61 rows of V = 128256 11.08 us, so 10.90; the distribution of 11 trees 17.33 and 17.19).  Greedy roots have
+    // nothing to do meanwhile (16 trees 18.6 us, so 18.9).
     const bool root_first = sampling && r == 0;
     auto node_count = [&] { return max(1, min(a.n_nodes ? a.n_nodes[b] : a.T, a.T)); };
     int nn = 1;
