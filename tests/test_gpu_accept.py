@@ -188,12 +188,73 @@ def test_large_vocabulary_many_blocks(oracle, mode):
     compare(oracle, b, x, mode)
 
 
+def log_mass(rows):
+    """Logarithm of each row's sum of exponentials."""
+    m = rows.max(axis=-1).astype(np.float64)
+    return m + np.log(np.exp(rows - m[..., None]).sum(axis=-1))
+
+
 @pytest.mark.parametrize("V", [65536, 65537, 131072, 131073, 196609])
 def test_edges_of_the_groups_of_blocks(oracle, V):
-    """64, 65, 128, 129 and 193 blocks of 1024 logits per row: the merging wavefront takes their sums and maxima 64 at a time."""
+    """64, 65, 128, 129 and 193 blocks of 1024 logits per row: the merging wavefront takes their sums and maxima 64 at a time.  The last block
+    decides: its last logit weighs as much as the rest of the row, so does a child's token.  The child (a third of the row, half without the last
+    block) is rejected at 0.4 in the first sequence; the bonus token of the others is drawn from the last block."""
     from paper_2512_14069_amd import binding as b
     a = small_shape(3, 9, (9, 1, 4), (3, 0, 2), k=3)
-    compare(oracle, b, synth.accept_inputs(a, V, seed=79), 1)
+    x = synth.accept_inputs(a, V, seed=79, plant=0.0)
+    tl, tok, par, u = (x[n] for n in ("target_logits", "draft_tokens", "parents", "uniforms"))
+    rest = log_mass(tl)
+    tl[:, :, -1] = rest
+    first = [[c for c in range(1, x["n_nodes"][s]) if par[s, c] == 0][:1] for s in range(3)]
+    for s, kids in enumerate(first):
+        for c in kids:
+            tl[s, 0, tok[s, c]] = rest[s, 0]
+    u[0, :-1] = 0.4
+    u[2, :-1] = 0.999
+    u[1:, -1] = 0.8
+    ref, _ = compare(oracle, b, x, 1)
+    masked = tl.copy()
+    masked[:, :, (V - 1) // 1024 * 1024:] = -100.0
+    without = oracle.verify_accept(masked, tok, par, x["n_nodes"], u, mode=1, temperature=1.0)
+    assert ref[0][0] == 0 and without[0][0] > 0                             # what the row's sum says
+    assert (ref[2][1:] == V - 1).all() and (without[2][1:] != V - 1).all()  # where the draw lands
+
+
+def test_draws_behind_the_first_128_blocks(oracle):
+    """Bonus tokens in blocks 128 ... 191, 192 ... 255 and from 256 on: the draw goes over the masses 128 blocks at a time.  Three sequences each of
+    a root alone, of a root whose three children are rejected (one token in each of these groups, a tenth of the row each) and of a root with
+    an accepted child.  The logits are ordinary ones, a token has about 3e-6 of the row: a mass that is lost or counted twice moves the draw."""
+    from paper_2512_14069_amd import binding as b
+    V, B, T = 300001, 9, 4
+    groups = ((128, 192), (192, 256), (256, (V - 1) // 1024 + 1))
+    rng = np.random.default_rng(synth.seed_for(30, 41))
+    tl = synth.normal_logits(rng, (B, T, V), 1.5)
+    par = np.tile(np.array([-1, 0, 0, 0], np.int32), (B, 1))
+    tok = np.zeros((B, T), np.int32)
+    nn = np.array([1, 1, 1, 4, 4, 4, 2, 2, 2], np.int32)
+    u = np.zeros((B, T + 1), np.float32)
+    for s in range(B):
+        lo, hi = groups[s % 3]
+        tok[s, 1:] = [g[0] * 1024 + 5000 + 700 * s for g in groups]
+        if s >= 3:
+            tl[s, 0, tok[s, 1:nn[s]]] = log_mass(tl[s, 0]) - np.log(7.0)
+        u[s, 1:nn[s]] = 0.99999 if s < 6 else 0.0
+        # the place in the distribution of the row that is drawn from, without the rejected tokens
+        e = np.exp(tl[s, 1 if s >= 6 else 0].astype(np.float64))
+        if 3 <= s < 6:
+            e[tok[s, 1:]] = 0.0
+        cdf = np.cumsum(e) / e.sum()
+        at = int(rng.integers(lo * 1024, min(hi * 1024, V)))
+        while e[at] < 4 * MARGIN * e.sum():                                 # wide enough that its middle is clear of its ends
+            at -= 1
+        u[s, -1] = (cdf[at - 1] + cdf[at]) / 2
+    x = dict(target_logits=tl, draft_tokens=tok, parents=par, n_nodes=nn, uniforms=u)
+    margins = oracle.accept_margins(tl, tok, par, nn, u, 1.0)
+    assert (margins > MARGIN).all()                                         # these uniforms are the ones compared
+    ref, _ = compare(oracle, b, x, 1)
+    for s in range(B):
+        assert groups[s % 3][0] <= ref[2][s] // 1024 < groups[s % 3][1]
+    assert (ref[0][:6] == 0).all() and (ref[0][6:] == 1).all()
 
 
 @pytest.mark.parametrize("mode", [0, 1])

@@ -61,6 +61,19 @@ def test_ragged_batch_matches_oracle(oracle, V, temperature):
     assert (ref[:, 2:] > 1e-4).any()                 # several lengths really occur
 
 
+@pytest.mark.parametrize("V", [65537, 131073, 196609])
+def test_last_block_of_a_group_counts(oracle, V):
+    """65, 129 and 193 blocks of 1024 logits per row, of which the last holds one logit that weighs as much as a lifted token."""
+    from paper_2512_14069_amd import binding as b
+    x = make_inputs(small_shape(3, 12, (12, 1, 7), (3, 0, 2), k=4), V, 95)
+    x["target_logits"][:, :, -1] += np.float32(np.log(V))
+    ref, _ = check(oracle, b, x)
+    masked = x["target_logits"].copy()
+    masked[:, :, (V - 1) // 1024 * 1024:] = -100.0
+    without = oracle.accept_length_distribution(masked, x["draft_tokens"], x["parents"], x["n_nodes"])
+    assert (np.abs(ref - without).max(axis=1)[[0, 2]] > 1000 * DIST_TOL).all()
+
+
 def test_config3_shape_star_and_chain(oracle):
     from paper_2512_14069_amd import binding as b
     a = small_shape(3, 61, (61, 61, 61), (8, 1, 60), k=10)
