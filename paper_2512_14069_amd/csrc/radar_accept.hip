@@ -22,10 +22,10 @@
 // its logits unread.  Rows go through the grid level by level over all sequences
 // (trees are numbered from the root), so that the roots' decisions come first.
 // What bounds a call is then the chain of decisions and the starting of workgroups, not
-// the logits' bytes: 61 rows of V = 128256, 16 sequences, paths of 0, 1, 2, 4 and 8 nodes 17.6, 23.3,
-// 25.1, 27.7 and 32.6 us greedy and 23.3, 29.1, 31.5, 34.5 and 42.6 sampled (129 when every row is
-// read); one sequence 7.5 ... 8.0 and 10.9 ... 14.4 us (the sampled figures are from before
-// keys, pairs and the roots' order changed, which took 2 ... 14 % off them).  In a large launch the
+// the logits' bytes: 61 rows of V = 128256, 16 sequences, paths of 0, 1, 2, 4 and 8 nodes 17.9, 23.2,
+// 24.6, 30.7 and 36.9 us greedy and 23.2, 26.7, 28.3, 33.4 and 41.6 sampled (129 when every row is
+// read); one sequence 7.1 ... 7.6 and 9.2 ... 13.2 us (one set of logits replayed; with logits that are in no
+// cache 18.1 ... 44.1 and 23.3 ... 46.9, one sequence 9.9 ... 10.4 and 12.1 ... 15.6).  In a large launch the
 // workgroups behind the roots' rows hold back until the roots are decided (below).
 #include <algorithm>
 
@@ -147,7 +147,7 @@ __device__ __forceinline__ unsigned int wave_fetch_add(unsigned int *p, unsigned
 
 // A sum and a maximum side by side: handed over by two lanes in one request, taken in one (device scope, as load_shared_result's; entries past
 // the n behind `from` read zeros, and `from` is the same in every lane).  As two arrays, of 8 and of 4 bytes,
-// 61 rows of V = 128256 took 11.33 us, now 11.08; 9 trees of 5 nodes, V = 45299, 9.41 and 9.00; two of 16, V = 51757, 8.58 and 8.27.
+// 61 rows of V = 128256 took 11.33 us, as pairs 11.08; 9 trees of 5 nodes, V = 45299, 9.41 and 9.00; two of 16, V = 51757, 8.58 and 8.27.
 struct SumMax { double l; float m; };
 __device__ __forceinline__ void store_sum_max(uint64_t *to, double l, float m) {        // by lanes 0 and 1
     const int lane = lane_id();
@@ -162,10 +162,13 @@ __device__ __forceinline__ double load_sum(const uint64_t *from) { return __long
 // NB: 1024-logit blocks per wavefront, all requested at once
 // LAST: the walk is left to the last row of the sequence (greedy only).
 // A sampled walk and the distribution ask for nobody's arg-max; with the keys found, stored, fetched and merged all the same a sampled call
-// over 9 trees of 5 nodes, V = 45299, took 9.78 us (now 9.41), two of 16, V = 51757, 9.08 (8.58), the distribution of 11 trees of V = 128256
-// 18.68 (17.45).  The sampled kernel fits into 72 registers so, seven wavefronts per SIMD, but six are the better number: with more the other rows'
-// logits are in front of the root's in the memory's queue, with fewer too little is in flight (61 rows of V = 128256 with seven, six, four
-// 11.73, 11.33, 11.73 us).
+// over 9 trees of 5 nodes, V = 45299, took 9.78 us instead of 9.41, two of 16, V = 51757, 9.08 instead of 8.58, the distribution of 11 trees
+// of V = 128256 18.68 instead of 17.45 (before sums and maxima were pairs).
+// The sampled kernel fits into 72 registers so, seven wavefronts per SIMD, but six are the better number: with more the other rows'
+// logits are in front of the root's in the memory's queue, with fewer too little is in flight.  Over 40 shapes (1, 4, 8, 16 sequences of 61 rows,
+// V = 32000 and 128256, paths of 0 ... 8 nodes; the workgroups that wait are as many as fit) seven, five and four take 1.004, 1.023 and 1.076 times
+// as long as six on replayed logits, 1.014, 1.008 and 1.045 on logits that are in no cache.  One by one they differ: of V = 128256, 16 trees whose
+// root is the end 22.9 us with six, 21.2 with seven, 29.8 with four; 8 trees with paths of two nodes 21.9, 23.1, 22.8.
 template <int MODE, bool LAST, bool VEC4, int NB>
 __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, MODE == RADAR_ACCEPT_SAMPLE ? 6 : 8))) void accept_kernel(AcceptArgs a) {
     __shared__ AcceptSmem s;
@@ -174,7 +177,8 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
     constexpr bool sampling = MODE != RADAR_ACCEPT_GREEDY;      // row statistics are needed
     // A root's row is there whatever the number of nodes, and everything waits for it: its logits are asked for first, the number of nodes
     // beside the tree's arrays (61 rows of V = 128256 11.08 us, so 10.90; the distribution of 11 trees 17.33 and 17.19).  Greedy roots have
-    // nothing to do meanwhile (16 trees 18.6 us, so 18.9).
+    // nothing to do meanwhile (16 trees 18.6 us, so 18.9).  That the arrays are then read at clamped places, and not where there is a node, is so that
+    // they need not wait for the number of nodes; alone it changes nothing (1.00 over the 40 shapes above).
     const bool root_first = sampling && r == 0;
     auto node_count = [&] { return max(1, min(a.n_nodes ? a.n_nodes[b] : a.T, a.T)); };
     int nn = 1;
@@ -335,8 +339,8 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
         M = wave_max_f32(mmax);
         double lsum = 0.0;
         if (sampling) {
-            // each block's mass relative to the row maximum: summed for the row, and left in part_l
-            // for the residual draw
+            // each block's mass relative to the row maximum: summed for the row, and left in the first half
+            // of the block's pair for the residual draw
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int c0 = i * kWave + lane;
@@ -755,8 +759,8 @@ static radar_status launch_accept(const float *target_logits, const int32_t *dra
     const int64_t nsub = ((int64_t)d->V + kAccSub - 1) / kAccSub;
     // Blocks per wavefront: one gives the most wavefronts and the shortest chain for each; launches of many rounds
     // take two, half the workgroups to start, to be told that their row is not needed and to count.  61 rows of
-    // V = 128256, sampled: 4 sequences 18.0 us with one and 22.2 with two, 8 sequences 25.9 and 24.8, 16
-    // sequences 40.1 and 30.9 (and 40.2 with four: fewer bytes in flight for the rows that are needed).
+    // V = 128256, sampled, paths of two nodes: 4 sequences 17.4 us with one and 22.1 with two, 8 sequences 25.1 and 21.9, 16
+    // sequences 39.1 and 27.9 (four took 30 % longer than two: fewer bytes in flight for the rows that are needed).
     const int nb = (int64_t)d->B * d->T_max * nsub >= kAccManyBlocks ? 2 : 1;
     const int64_t nwg = (nsub + kAccWaves * nb - 1) / (kAccWaves * nb);
     if (d->T_max > RADAR_T_MAX || d->D_max >= RADAR_T_MAX || d->B > 65535 || nsub > kAccMaxSubs)
@@ -775,22 +779,24 @@ static radar_status launch_accept(const float *target_logits, const int32_t *dra
     accept_layout(d->B, d->T_max, (size_t)nsub, static_cast<char *>(workspace), &a);
     // Large launches: the roots' rows are read first and alone, the workgroups behind them wait for the roots' decisions (the
     // memory's queue is first come, first served: 2048 workgroups that read at once are 64 MB ahead of the roots' results, whose
-    // rows were complete after 9.5 us instead of 6.7).  Greedy 2.5 us, sampled 4.5 (its decisions are later).  Those wait that start
-    // with the launch, by their number (rows past the end of a tree count too): eight workgroups per CU of the greedy kernel, six
-    // of the sampled one.  Of the greedy kernel for rows of any length and two blocks the chip holds seven: ending at 1792
-    // there is slower all the same (16 sequences of 61 rows, V = 128257, paths of 0, 2 and 8 nodes 22.1, 34.6, 56.7 us; 21.0, 33.6, 55.3 at 2048).
+    // rows were complete after 9.5 us instead of 6.7).  Greedy 2.5 us, sampled 4.5 (its decisions are later; 3.5 and 4.0 take the same, 5.5
+    // one per cent more).  Those wait that start with the launch, by their number (rows past the end of a tree count too): eight workgroups
+    // per CU of the greedy kernel, six of the sampled one, which is what the chip holds.  Ending at 1792 in greedy launches is slower (16 sequences of 61 rows,
+    // V = 128256, paths of 0, 2 and 8 nodes 18.1, 26.7, 39.6 us; 17.8, 24.7, 36.9 at 2048).
     // Looking once before the wait changes nothing (1 %); with every workgroup waiting until the roots are decided V = 1048576 gains
     // 4-9 % (4 sequences 46.6, 56.1, 96.8 -> 44.8, 52.7, 88.2) and V = 128256 loses as much (16 sequences 17.4, 24.6, 35.3 -> 19.2, 25.6, 35.9).
     // us without / with the wait, trees of 61 rows, paths of 0, 2 and 8 nodes: greedy, V = 128256, 4 sequences 14.4 / 11.4, 16.6 / 16.3, 21.6 / 19.8;
     // 16 sequences 23.6 / 17.5, 27.4 / 24.6, 39.6 / 35.0; V = 1048576, 4 sequences 50.3 / 47.7, 59.0 / 56.3, 99 / 96.5; sampled, V = 128256, 8
-    // sequences 20.2 / 15.5, 24.3 / 24.7, 36.2 / 32.3; 16 sequences 27.8 / 23.3, 31.3 / 30.0, 46.2 / 43.8.  Smaller launches lose
-    // by it (one sequence, sampled, 2 nodes 11.1 / 14.1; two 13.2 / 14.9; greedy, 8 sequences of V = 32000 10.3 / 10.7).
+    // sequences 20.6 / 15.5, 23.8 / 21.9, 33.1 / 30.5; 16 sequences 28.0 / 22.9, 31.4 / 27.9, 45.0 / 40.7.  Smaller launches lose
+    // by it (sampled, V = 128256, 4 sequences 15.4 / 15.0, 17.4 / 18.9, 24.5 / 25.3; V = 32000, 16 sequences 15.9 / 16.0, 17.7 / 19.5, 25.2 / 27.0;
+    // greedy, 8 sequences of V = 32000 10.3 / 10.7).
     // So do small trees in a launch that is large by T_max alone, once the path leaves the root (16 trees of 6 nodes, T_max = 64, paths of
-    // 0, 2 and 5 nodes: greedy, V = 32000 6.0 / 7.2, 7.5 / 11.2, 8.0 / 11.6; sampled, V = 128256 14.7 / 10.4, 15.3 / 20.9, 18.1 / 22.5).  Only trees
+    // 0, 2 and 5 nodes: greedy, V = 32000 6.0 / 7.2, 7.5 / 11.2, 8.0 / 11.6; 0, 2 and 4 nodes, sampled, V = 128256 13.3 / 10.3, 15.6 / 19.1, 16.9 / 20.2).  Only trees
     // wait with which the launch would be half a large one if all were like them; reading the others' sizes is not worth it
     // (every workgroup starts later then: 16 x 61 rows 17.5 -> 22.4).  16 trees of 12 nodes, T_max = 64, paths of 0, 2 and 4 nodes, greedy,
     // V = 32000 8.7 / 7.6, 9.5 / 12.3, 10.5 / 12.7, of 24 nodes 12.6 / 8.5, 13.3 / 12.6, 13.6 / 13.1.  With a whole large one instead of half, batches of
-    // unlike trees lose: 16 of 2 to 60 nodes (377 rows), sampled, V = 128256 15.5 us when all wait, 16.2 with half, 17.2 with a whole.
+    // unlike trees lose: 16 of 2 to 60 nodes (377 rows), sampled, V = 128256, paths of 0, 1 and 2 nodes 15.7, 23.3, 25.7 us when all wait, 15.6, 22.3, 24.7
+    // with half, 17.3, 22.5, 25.4 with a whole.
     const int64_t blocks = (int64_t)d->B * d->T_max * nsub;
     const bool wait = mode == RADAR_ACCEPT_GREEDY ? blocks >= kAccManyBlocks / 2 : mode == RADAR_ACCEPT_SAMPLE && blocks >= kAccManyBlocks;
     a.check_from = wait ? (int)(d->B * nwg) : kAccUnchecked;
@@ -800,7 +806,7 @@ static radar_status launch_accept(const float *target_logits, const int32_t *dra
     // A greedy walk is shortest at the end of the launch, in registers over all rows' results, as long as the launch
     // is not much more than the chip holds at once (one sequence of 16 rows, V = 32000: 5.6 us against 7.1; two of
     // 61 rows, V = 128256, 3904 workgroups: 13.9 against 13.3).  A sampled one is not: its exponentials and the
-    // draw's block masses are better taken as the rows end (61 rows, V = 128256: 14.3 us at the end, 12.9 on the way).
+    // draw's block masses are better taken as the rows end (61 rows, V = 128256, when this was decided: 14.3 us at the end, 12.9 on the way).
     const bool last = mode == RADAR_ACCEPT_GREEDY && (int64_t)d->B * d->T_max * nwg <= kAccWalkLast;
 
     const dim3 grid((unsigned)nwg, (unsigned)d->B, (unsigned)d->T_max), block(kAccThreads);
